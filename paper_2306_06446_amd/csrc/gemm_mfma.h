@@ -120,6 +120,59 @@ __device__ inline void wait_loads_in_flight() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// One 16-byte chunk of converted elements (output row m of the row selection, columns n .. n + 16 / kBytes - 1) to
+// where it belongs, with the gate, residual or old value of the destination.  whole_chunks: no chunk straddles a row's end.
+template <class Store>
+__device__ __forceinline__ void store_chunk(const Store &store, uint4 v, const int32_t *rows, long m, int n, int N,
+                                            bool whole_chunks) {
+    constexpr int ES = Store::kBytes;
+    const long t = (Store::kScatter && rows) ? (long)rows[m] : m;
+    uint8_t *dst = static_cast<uint8_t *>(store.out) + ((size_t)t * N + n) * ES;
+    if constexpr (Store::kLinear) {
+        // whole chunks by construction: part_width and N are multiples of 4
+        float4 res = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (store.residual) res = *reinterpret_cast<const float4 *>(store.residual + (size_t)t * N + n);
+        v.x = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.x), store.scale, res.x));
+        v.y = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.y), store.scale, res.y));
+        v.z = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.z), store.scale, res.z));
+        v.w = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.w), store.scale, res.w));
+        const int part = n / store.part_width;
+        float *base = part == 0 ? store.parts[0] : part == 1 ? store.parts[1] : store.parts[2];
+        dst = reinterpret_cast<uint8_t *>(base + (size_t)t * store.part_width + (n - part * store.part_width));
+    }
+    if constexpr (ES == 4 && Store::kScatter) {
+        const float gt = store.gate ? store.gate[t] : 1.0f;
+        if (store.accumulate) {
+            float old[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (whole_chunks) {
+                const float4 o4 = *reinterpret_cast<const float4 *>(dst);
+                old[0] = o4.x; old[1] = o4.y; old[2] = o4.z; old[3] = o4.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) old[e] = reinterpret_cast<const float *>(dst)[e];
+            }
+            v.x = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.x), old[0]));
+            v.y = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.y), old[1]));
+            v.z = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.z), old[2]));
+            v.w = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.w), old[3]));
+        } else if (store.gate) {
+            v.x = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.x));
+            v.y = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.y));
+            v.z = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.z));
+            v.w = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.w));
+        }
+    }
+    if (ES < 4 || whole_chunks) {
+        *reinterpret_cast<uint4 *>(dst) = v;
+    } else {                          // 32-bit rows that are not a multiple of 16 bytes
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (n + e < N) reinterpret_cast<uint32_t *>(dst)[e] = w[e];
+    }
+}
+
 template <class T, int BM, int BN, int SB, int NS, int LS, int OCC, class Store>
 __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store store) {
     constexpr int kStageBytes = SB;                     // bytes of K per stage and row
@@ -401,8 +454,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
     static_assert(PER_THREAD >= 1, "a staged slab has at least one chunk per thread");
     uint8_t *tile = lds;
     uint8_t *table = lds + SLAB_BYTES;
-    const size_t out_row_bytes = (size_t)N * ES;
-    const bool whole_chunks = out_row_bytes % 16 == 0;
+    const bool whole_chunks = (size_t)N * ES % 16 == 0;
     __syncthreads();                              // the last stage has been read
     if (Store::kTableBytes != 0) table[tid] = static_cast<const uint8_t *>(store.table)[tid];
     static_for<MI>([&](auto i_c) {
@@ -432,51 +484,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
             const int n = n0 + cc * (16 / ES);
             if (m < n_rows && n < N) {
                 uint4 v = *reinterpret_cast<const uint4 *>(tile + (ml * CPR + cc) * 16);
-                const long t = (Store::kScatter && rows) ? (long)rows[m] : m;
-                uint8_t *dst = static_cast<uint8_t *>(store.out) + (size_t)t * out_row_bytes + (size_t)n * ES;
-                if constexpr (Store::kLinear) {
-                    // whole chunks by construction: part_width and N are multiples of 4
-                    float4 res = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if (store.residual) res = *reinterpret_cast<const float4 *>(store.residual + (size_t)t * N + n);
-                    v.x = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.x), store.scale, res.x));
-                    v.y = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.y), store.scale, res.y));
-                    v.z = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.z), store.scale, res.z));
-                    v.w = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.w), store.scale, res.w));
-                    const int part = n / store.part_width;
-                    float *base = part == 0 ? store.parts[0] : part == 1 ? store.parts[1] : store.parts[2];
-                    dst = reinterpret_cast<uint8_t *>(base + (size_t)t * store.part_width + (n - part * store.part_width));
-                }
-                if constexpr (ES == 4 && Store::kScatter) {
-                    const float gt = store.gate ? store.gate[t] : 1.0f;
-                    if (store.accumulate) {
-                        float old[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                        if (whole_chunks) {
-                            const float4 o4 = *reinterpret_cast<const float4 *>(dst);
-                            old[0] = o4.x; old[1] = o4.y; old[2] = o4.z; old[3] = o4.w;
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (n + e < N) old[e] = reinterpret_cast<const float *>(dst)[e];
-                        }
-                        v.x = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.x), old[0]));
-                        v.y = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.y), old[1]));
-                        v.z = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.z), old[2]));
-                        v.w = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.w), old[3]));
-                    } else if (store.gate) {
-                        v.x = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.x));
-                        v.y = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.y));
-                        v.z = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.z));
-                        v.w = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.w));
-                    }
-                }
-                if (ES < 4 || whole_chunks) {
-                    *reinterpret_cast<uint4 *>(dst) = v;
-                } else {                          // 32-bit rows that are not a multiple of 16 bytes
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (n + e < N) reinterpret_cast<uint32_t *>(dst)[e] = w[e];
-                }
+                store_chunk(store, v, rows, m, n, N, whole_chunks);
             }
         }
     });
@@ -502,13 +510,26 @@ int launch_gemm_tile(const GemmArgs &g, const Store &store, hipStream_t st, cons
     return check_launch(what);
 }
 
-// Tile choice, from timings of the expert layers of the DeiT-Base block on one MI355X:
-//  * long rows (>= 2 KiB) in whole 128-byte lines: 128-byte stages pay (every request is a
-//    whole cache line); int8 takes the 256 x 128 tile, one workgroup per CU; fp16 takes
-//    128 x 128 with a ring of three, one per CU (64 x 128, two per CU, when there are few rows);
-//  * short rows leave only a few stages per tile: int8 takes 64-byte stages so that two or
-//    three workgroups per CU hide each other's prologue and epilogue; fp16 takes 192 x 128 tiles
-//    with 128-byte stages, one per CU (128 x 64, two per CU, when there are few rows).
+}  // namespace sa
+
+#include "gemm_slice.h"
+
+namespace sa {
+
+// Tile choice, from sweeps over (K, N) of the transformer widths 64 .. 3072 and 50 .. 25088 rows on one MI355X.
+// t32, t64: tiles of 32 x 64 and 64 x 64 outputs.
+//  * t32 <= 256: not every CU gets a 32 x 64 tile, so the time is that of one tile: gemm_slice.h with 32 rows
+//    (965 x 192 <- 768 int8: 4.8 us against 9.5 with 128 x 128 tiles; 197 x 768 <- 3072: 8.7 against 21);
+//  * t64 <= 640: up to two and a half 64 x 64 tiles per CU (965 x 768 <- 3072 int8: 11.8 us against 35 with the
+//    256 x 128 tiles, 3152 x 768 <- 768: 11.7 against 12.2; fp16 with long rows only up to 320: the next tile up
+//    catches up there).  Short rows take 64-byte stages: with few stages the finer ones start sooner
+//    (1379 x 1024 <- 256 int8: 5.7 us against 6.1);
+//  * beyond, the tiles of gemm_mfma.h.  Long int8 rows (>= 2 KiB, whole 128-byte lines): 256 x 128, 128-byte stages,
+//    one workgroup per CU.  Other int8 rows: 256 x 128 (two per CU) or 128 x 128 (three per CU) with 64-byte stages;
+//    they do the same work per CU and second, so the one whose last round of workgroups is fuller
+//    (12608 x 1536 <- 384: 38 against 29 us; 12608 x 3072 <- 768: 76 against 82).  fp16: long rows 128 x 128 with a
+//    ring of three; rows of more than 768 bytes 192 x 128, both one per CU; short rows 128 x 128 with 64-byte stages.
+// A row count that lives on the device is taken to be half of its bound (two experts share the tokens).
 // Narrow (1- and 2-byte) output rows must be whole 16-byte chunks; operand rows must be a
 // multiple of 64 bytes long.
 template <class T, class Store>
@@ -522,19 +543,32 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
     SA_REQUIRE(Store::kBytes == 4 || (size_t)g.N * Store::kBytes % 16 == 0, SA_ERR_SHAPE,
                "%s: narrow output rows of %d elements are not whole 16-byte chunks", what, g.N);
     const bool lines = row_bytes % 128 == 0 && !short_a, long_rows = row_bytes >= 2048;
-    const long blocks256 = ((g.sel.max_rows + 255) / 256) * ((g.N + 127) / 128);
+    const bool counted = g.sel.counts != nullptr;
+    const long m_est = counted ? (g.sel.max_rows + 1) / 2 : g.sel.max_rows;
+    auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+    const bool whole_line_stages = lines && row_bytes >= 512;
     if constexpr (T::kPlanes == 2) {
+        if (tiles(32, 64) <= 256)
+            return whole_line_stages ? launch_slice<T, 1, 2, 128, 4, Store>(g, store, st, what)
+                                     : launch_slice<T, 1, 2, 64, 7, Store>(g, store, st, what);
+        if (tiles(64, 64) <= 640)
+            return whole_line_stages ? launch_slice<T, 2, 2, 128, 3, Store>(g, store, st, what)
+                                     : launch_slice<T, 2, 2, 64, 6, Store>(g, store, st, what);
         if (lines && long_rows) return launch_gemm_tile<T, 256, 128, 128, 2, 2, 1, Store>(g, store, st, what);
-        if (blocks256 >= 512) return launch_gemm_tile<T, 256, 128, 64, 2, 1, 2, Store>(g, store, st, what);
+        const long rounds256 = (tiles(256, 128) + 511) / 512, rounds128 = (tiles(128, 128) + 767) / 768;
+        const bool wide = counted ? ((g.sel.max_rows + 255) / 256) * ((g.N + 127) / 128) >= 512    // no rounds to speak of
+                                  : rounds256 * 5 <= rounds128 * 4;      // a round of the larger tiles takes 1.25 times as long
+        if (wide) return launch_gemm_tile<T, 256, 128, 64, 2, 1, 2, Store>(g, store, st, what);
         return launch_gemm_tile<T, 128, 128, 64, 2, 1, 3, Store>(g, store, st, what);
     } else {
-        const bool many_rows = g.sel.max_rows >= 2048;
-        if (lines && long_rows)
-            return many_rows ? launch_gemm_tile<T, 128, 128, 128, 3, 2, 1, Store>(g, store, st, what)
-                             : launch_gemm_tile<T, 64, 128, 128, 3, 2, 2, Store>(g, store, st, what);
-        if (lines)
-            return many_rows ? launch_gemm_tile<T, 192, 128, 128, 2, 2, 1, Store>(g, store, st, what)
-                             : launch_gemm_tile<T, 128, 64, 128, 2, 2, 2, Store>(g, store, st, what);
+        if (tiles(32, 64) <= 256)
+            return whole_line_stages ? launch_slice<T, 1, 2, 128, 6, Store>(g, store, st, what)
+                                     : launch_slice<T, 1, 2, 64, 8, Store>(g, store, st, what);
+        if (tiles(64, 64) <= (long_rows ? 320 : 640))
+            return whole_line_stages ? launch_slice<T, 2, 2, 128, 4, Store>(g, store, st, what)
+                                     : launch_slice<T, 2, 2, 64, 9, Store>(g, store, st, what);
+        if (lines && long_rows) return launch_gemm_tile<T, 128, 128, 128, 3, 2, 1, Store>(g, store, st, what);
+        if (lines && row_bytes > 768) return launch_gemm_tile<T, 192, 128, 128, 2, 2, 1, Store>(g, store, st, what);
         return launch_gemm_tile<T, 128, 128, 64, 3, 1, 2, Store>(g, store, st, what);
     }
 }
