@@ -72,20 +72,6 @@ __global__ __launch_bounds__(256) void ktv_kernel(const uint64_t *__restrict__ k
     }
 }
 
-// kv[i] = sum over splits of part[s][i], s ascending.
-__global__ __launch_bounds__(256) void ktv_reduce_kernel(const float4 *__restrict__ part,
-                                                         float4 *__restrict__ kv, long n4,
-                                                         int splits) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n4) return;
-    float4 a = part[i];
-    for (int s = 1; s < splits; ++s) {
-        const float4 p = part[(size_t)s * n4 + i];
-        a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
-    }
-    kv[i] = a;
-}
-
 template <int DV, bool ZO>
 __global__ __launch_bounds__(256) void qkv_kernel(const uint64_t *__restrict__ q_codes,
                                                   const float *__restrict__ kv,
@@ -274,7 +260,7 @@ extern "C" size_t sa_additive_attention_workspace_bytes(int B, int H, int Nk, in
     const KtvPlan p = plan_ktv(B, H, Nk, nbits);
     int splits = p.splits;
     if (sa::additive_mfma_ktv_supported(nbits, dv)) {
-        const sa::AdditiveMfmaPlan m = sa::plan_additive_mfma(B, H, Nk, nbits);
+        const sa::AdditiveMfmaPlan m = sa::plan_additive_mfma(B, H, Nk, nbits, dv);
         if (m.splits > splits) splits = m.splits;
     }
     if (splits <= 1) return 0;
@@ -283,13 +269,33 @@ extern "C" size_t sa_additive_attention_workspace_bytes(int B, int H, int Nk, in
 
 namespace {
 
-// The two Add layers.  zero_one: a clear code bit contributes nothing instead of -V; den (with zero_one) is the
-// row normaliser int32 [B*H, Nq]: rows leave as acc / (den + eps) instead of scale * acc.
+// What the two Add layers do beyond the plain call.  zero_one: a clear code bit contributes nothing instead of -V, the
+// bit counts are left in ksum (phase 1) or taken from there (phase 2), and rows leave as acc / (normaliser + eps) instead
+// of scale * acc.  ksum_part: room for [splits][B*H][nbits] counts; den: room for the normalisers [B*H, Nq].
 struct AddMode {
     bool zero_one = false;
-    const int32_t *den = nullptr;
+    int32_t *ksum = nullptr, *ksum_part = nullptr, *den = nullptr;
     float eps = 0.0f;
+    bool want_out = true;             // false: only the forms below are read
+    int8_t *xq = nullptr;
+    _Float16 *xh = nullptr;
+    float act_inv_scale = 0.0f;
 };
+
+// ksum by a kernel of its own (what the vector-ALU variant of phase 1 needs beside K^T V).
+int count_bits(const uint64_t *k_codes, int32_t *ksum, long BH, int Nk, int nbits, hipStream_t st) {
+    int rc = sa::launch_zero(ksum, (size_t)BH * nbits * sizeof(int32_t), st);
+    if (rc != SA_OK || Nk == 0) return rc;
+    const int W = nbits / 64;
+    // about 64 tokens per wavefront (eight batches of eight loads): short dependent chains, many wavefronts
+    long splits = ((long)Nk + 255) / 256;
+    if (splits > 1024) splits = 1024;
+    const int tokens_per_wave = (int)(((long)Nk + splits * 4 - 1) / (splits * 4));
+    const long blocks = BH * W * splits;
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_linear_attention_01: grid too large");
+    bit_count_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(k_codes, ksum, Nk, W, (int)splits, tokens_per_wave);
+    return sa::check_launch("sa_linear_attention_01(bit counts)");
+}
 
 int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, float *out, int B, int H, int Nq,
                  int Nk, int nbits, int dv, float scale, float *kv, int phases, void *workspace,
@@ -311,85 +317,107 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
     hipStream_t st = sa::as_stream(stream);
     const int W = nbits / 64;
     const long BH = (long)B * H;
+    const size_t kv_elems = (size_t)BH * nbits * dv;
+    const bool qkv_mfma = !valu && sa::additive_mfma_qkv_supported(nbits, dv);
+    if (phases & 2)
+        SA_REQUIRE(Nq == 0 || (q_codes != nullptr && out != nullptr), SA_ERR_INVALID,
+                   "sa_additive_attention: phase 2 needs q_codes and out");
+    // What phase 2 reads: K^T V (and the counts), or the partials of phase 1 where it sums them itself.
+    sa::AddFused f;
+    f.kv_in = kv;
+    f.ksum_in = mode.ksum;
+    f.scale = scale;
+    f.eps = mode.eps;
+    f.out = mode.want_out ? out : nullptr;
+    f.xq = mode.xq;
+    f.xh = mode.xh;
+    f.act_inv_scale = mode.act_inv_scale;
 
     if (phases & 1) {
-        const size_t kv_elems = (size_t)BH * nbits * dv;
         if (Nk == 0) {
             int rc = sa::launch_zero(kv, kv_elems * sizeof(float), st);   // empty sum
+            if (rc == SA_OK && mode.zero_one) rc = sa::launch_zero(mode.ksum, (size_t)BH * nbits * sizeof(int32_t), st);
             if (rc != SA_OK) return rc;
         } else {
             SA_REQUIRE(k_codes != nullptr && v != nullptr, SA_ERR_INVALID,
                        "sa_additive_attention: phase 1 needs k_codes and v");
-            if (!valu && sa::additive_mfma_ktv_supported(nbits, dv)) {
-                const sa::AdditiveMfmaPlan m = sa::plan_additive_mfma(B, H, Nk, nbits);
-                float *dst = kv;
-                if (m.splits > 1) {
-                    const size_t need = (size_t)m.splits * kv_elems * sizeof(float);
-                    SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
-                               "sa_additive_attention: workspace of %zu bytes needed, %zu given", need,
-                               workspace_bytes);
-                    dst = static_cast<float *>(workspace);
+            const bool mfma = !valu && sa::additive_mfma_ktv_supported(nbits, dv);
+            sa::AdditiveMfmaPlan m{};
+            KtvPlan p{};
+            if (mfma) m = sa::plan_additive_mfma(B, H, Nk, nbits, dv);
+            else p = plan_ktv(B, H, Nk, nbits);
+            const int splits = mfma ? m.splits : p.splits;
+            float *dst = kv;
+            int32_t *counts = mode.ksum;
+            if (splits > 1) {
+                const size_t need = (size_t)splits * kv_elems * sizeof(float);
+                SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
+                           "sa_additive_attention: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+                dst = static_cast<float *>(workspace);
+                counts = mode.ksum_part;
+            }
+            int rc;
+            if (mfma) {
+                rc = sa::launch_ktv_mfma(k_codes, v, dst, counts, B, H, Nk, nbits, dv, m, mode.zero_one, st);
+            } else {
+                const long blocks = BH * W * p.splits;
+                SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
+                const dim3 grid((unsigned)blocks), block(kKtvWaves * kWave);
+#define SA_KTV(DV_, ZO_) ktv_kernel<DV_, ZO_><<<grid, block, 0, st>>>(k_codes, v, dst, H, Nk, W, p.splits, p.tokens_per_wave)
+                switch (dv) {
+                    case 32: if (mode.zero_one) SA_KTV(32, true); else SA_KTV(32, false); break;
+                    case 64: if (mode.zero_one) SA_KTV(64, true); else SA_KTV(64, false); break;
+                    default: if (mode.zero_one) SA_KTV(128, true); else SA_KTV(128, false); break;
                 }
-                int rc = sa::launch_ktv_mfma(k_codes, v, dst, B, H, Nk, nbits, dv, m, mode.zero_one, st);
-                if (rc != SA_OK) return rc;
-                if (m.splits > 1) {
-                    const long n4 = (long)(kv_elems / 4);
-                    ktv_reduce_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(
-                        reinterpret_cast<const float4 *>(dst), reinterpret_cast<float4 *>(kv), n4, m.splits);
-                    rc = sa::check_launch("sa_additive_attention(reduce)");
+#undef SA_KTV
+                rc = sa::check_launch("sa_additive_attention(K^T V)");
+                if (rc == SA_OK && mode.zero_one) rc = count_bits(k_codes, mode.ksum, BH, Nk, nbits, st);
+            }
+            if (rc != SA_OK) return rc;
+            if (splits > 1) {
+                if (mfma && qkv_mfma && (phases & 2) && Nq > 0 && sa::additive_mfma_sums_partials(splits, nbits, dv)) {
+                    f.kv_in = dst;
+                    f.kv_out = kv;
+                    f.ksum_in = counts;
+                    f.ksum_out = mode.ksum;
+                    f.splits = splits;
+                } else {
+                    rc = sa::launch_ktv_sum(dst, kv, mfma && mode.zero_one ? counts : nullptr, mode.ksum, BH, nbits, dv, splits, st);
                     if (rc != SA_OK) return rc;
                 }
-            } else {
-            const KtvPlan p = plan_ktv(B, H, Nk, nbits);
-            float *dst = kv;
-            if (p.splits > 1) {
-                const size_t need = (size_t)p.splits * kv_elems * sizeof(float);
-                SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
-                           "sa_additive_attention: workspace of %zu bytes needed, %zu given", need,
-                           workspace_bytes);
-                dst = static_cast<float *>(workspace);
-            }
-            const long blocks = BH * W * p.splits;
-            SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
-            const dim3 grid((unsigned)blocks), block(kKtvWaves * kWave);
-#define SA_KTV(DV_, ZO_) ktv_kernel<DV_, ZO_><<<grid, block, 0, st>>>(k_codes, v, dst, H, Nk, W, p.splits, p.tokens_per_wave)
-            switch (dv) {
-                case 32: if (mode.zero_one) SA_KTV(32, true); else SA_KTV(32, false); break;
-                case 64: if (mode.zero_one) SA_KTV(64, true); else SA_KTV(64, false); break;
-                default: if (mode.zero_one) SA_KTV(128, true); else SA_KTV(128, false); break;
-            }
-#undef SA_KTV
-            int rc = sa::check_launch("sa_additive_attention(K^T V)");
-            if (rc != SA_OK) return rc;
-            if (p.splits > 1) {
-                const long n4 = (long)(kv_elems / 4);
-                ktv_reduce_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(
-                    reinterpret_cast<const float4 *>(dst), reinterpret_cast<float4 *>(kv), n4, p.splits);
-                rc = sa::check_launch("sa_additive_attention(reduce)");
-                if (rc != SA_OK) return rc;
-            }
             }
         }
     }
     if ((phases & 2) && Nq > 0) {
-        SA_REQUIRE(q_codes != nullptr && out != nullptr, SA_ERR_INVALID,
-                   "sa_additive_attention: phase 2 needs q_codes and out");
-        if (!valu && sa::additive_mfma_qkv_supported(nbits, dv))
-            return sa::launch_qkv_mfma(q_codes, kv, out, B, H, Nq, nbits, dv, scale, mode.zero_one, mode.den, mode.eps, st);
+        if (qkv_mfma) return sa::launch_qkv_mfma(q_codes, f, B, H, Nq, nbits, dv, mode.zero_one, st);
+        const int32_t *den = nullptr;
+        if (mode.zero_one) {
+            const int den_chunks = (Nq + 255) / 256;
+            const long blocks = BH * den_chunks;
+            SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_linear_attention_01: grid too large");
+            den_kernel<<<dim3((unsigned)blocks), dim3(256), (size_t)nbits * 4 * sizeof(int32_t), st>>>(q_codes, mode.ksum, mode.den, Nq,
+                                                                                                      W, den_chunks);
+            int rc = sa::check_launch("sa_linear_attention_01(normaliser)");
+            if (rc != SA_OK) return rc;
+            den = mode.den;
+        }
         const int n_chunks = (Nq + 63) / 64;
         const long n_tasks = BH * n_chunks;
         const long blocks = (n_tasks + 3) / 4;
         SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
         const dim3 grid((unsigned)blocks), block(256);
 #define SA_QKV(DV_, ZO_) \
-    qkv_kernel<DV_, ZO_><<<grid, block, 0, st>>>(q_codes, kv, out, H, Nq, W, n_chunks, n_tasks, scale, mode.den, mode.eps)
+    qkv_kernel<DV_, ZO_><<<grid, block, 0, st>>>(q_codes, kv, out, H, Nq, W, n_chunks, n_tasks, scale, den, mode.eps)
         switch (dv) {
             case 32: if (mode.zero_one) SA_QKV(32, true); else SA_QKV(32, false); break;
             case 64: if (mode.zero_one) SA_QKV(64, true); else SA_QKV(64, false); break;
             default: if (mode.zero_one) SA_QKV(128, true); else SA_QKV(128, false); break;
         }
 #undef SA_QKV
-        return sa::check_launch("sa_additive_attention(Q(K^T V))");
+        int rc = sa::check_launch("sa_additive_attention(Q(K^T V))");
+        if (rc == SA_OK && mode.xq)
+            rc = sa_quantize_act_half(out, BH * Nq * dv, mode.act_inv_scale, mode.xq, mode.xh, stream);
+        return rc;
     }
     return SA_OK;
 }
@@ -407,10 +435,38 @@ extern "C" int sa_additive_attention(const uint64_t *q_codes, const uint64_t *k_
                         stream, AddMode{});
 }
 
+int sa::additive_attention_fused(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, float *out, bool want_out,
+                                 int B, int H, int N, int nbits, int dv, float scale, float *kv, int8_t *xq, _Float16 *xh,
+                                 float act_inv_scale, void *workspace, size_t workspace_bytes, void *stream) {
+    AddMode mode;
+    mode.want_out = want_out;
+    mode.xq = xq;
+    mode.xh = xh;
+    mode.act_inv_scale = act_inv_scale;
+    return run_additive(q_codes, k_codes, v, out, B, H, N, N, nbits, dv, scale, kv, 3, workspace, workspace_bytes, stream, mode);
+}
+
+namespace {
+
+// Workspace of sa_linear_attention_01: K^T V partials | their bit counts | normalisers [B*H, Nq] (vector-ALU phase 2).
+struct ZeroOneLayout {
+    size_t add, counts, den, total;
+};
+
+ZeroOneLayout zero_one_layout(int B, int H, int Nq, int Nk, int nbits, int dv) {
+    ZeroOneLayout L;
+    L.add = up256(sa_additive_attention_workspace_bytes(B, H, Nk, nbits, dv));
+    L.counts = L.add;
+    L.den = L.counts + up256(L.add / dv);         // one int32 per row of dv floats of the partials
+    L.total = L.den + up256((size_t)B * H * (Nq > 0 ? Nq : 1) * sizeof(int32_t));
+    return L;
+}
+
+}  // namespace
+
 extern "C" size_t sa_linear_attention_01_workspace_bytes(int B, int H, int Nq, int Nk, int nbits, int dv) {
     if (B <= 0 || H <= 0 || Nq < 0 || Nk < 0 || nbits <= 0 || dv <= 0 || nbits % 64) return 0;
-    const size_t a = up256(sa_additive_attention_workspace_bytes(B, H, Nk, nbits, dv));
-    return a + up256((size_t)B * H * (Nq > 0 ? Nq : 1) * sizeof(int32_t));
+    return zero_one_layout(B, H, Nq, Nk, nbits, dv).total;
 }
 
 extern "C" int sa_linear_attention_01(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, float *out,
@@ -434,46 +490,18 @@ extern "C" int sa_linear_attention_01(const uint64_t *q_codes, const uint64_t *k
     const size_t need = sa_linear_attention_01_workspace_bytes(B, H, Nq, Nk, nbits, dv);
     SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
                "sa_linear_attention_01: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
-    const size_t add_ws = up256(sa_additive_attention_workspace_bytes(B, H, Nk, nbits, dv));
-    int32_t *den = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + add_ws);
-    hipStream_t st = sa::as_stream(stream);
-    const int W = nbits / 64;
-    const long BH = (long)B * H;
+    if (phases & 2)
+        SA_REQUIRE(Nq == 0 || (q_codes != nullptr && out != nullptr), SA_ERR_INVALID,
+                   "sa_linear_attention_01: phase 2 needs q_codes and out");
+    const ZeroOneLayout L = zero_one_layout(B, H, Nq, Nk, nbits, dv);
+    uint8_t *ws = static_cast<uint8_t *>(workspace);
     AddMode mode;
     mode.zero_one = true;
-    if (phases & 1) {
-        int rc = run_additive(nullptr, k_codes, v, nullptr, B, H, 0, Nk, nbits, dv, 1.0f, kv, 1 | (phases & SA_ADDITIVE_VALU),
-                              workspace, add_ws, stream, mode);
-        if (rc != SA_OK) return rc;
-        rc = sa::launch_zero(ksum, (size_t)BH * nbits * sizeof(int32_t), st);
-        if (rc != SA_OK) return rc;
-        if (Nk > 0) {
-            SA_REQUIRE(k_codes != nullptr, SA_ERR_INVALID, "sa_linear_attention_01: phase 1 needs k_codes");
-            // about 64 tokens per wavefront (eight batches of eight loads): short dependent chains, many wavefronts
-            long splits = ((long)Nk + 255) / 256;
-            if (splits > 1024) splits = 1024;
-            const int tokens_per_wave = (int)(((long)Nk + splits * 4 - 1) / (splits * 4));
-            const long blocks = BH * W * splits;
-            SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_linear_attention_01: grid too large");
-            bit_count_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(k_codes, ksum, Nk, W, (int)splits, tokens_per_wave);
-            rc = sa::check_launch("sa_linear_attention_01(bit counts)");
-            if (rc != SA_OK) return rc;
-        }
-    }
-    if ((phases & 2) && Nq > 0) {
-        SA_REQUIRE(q_codes != nullptr && out != nullptr, SA_ERR_INVALID, "sa_linear_attention_01: phase 2 needs q_codes and out");
-        const int n_chunks = (Nq + 255) / 256;
-        const long blocks = BH * n_chunks;
-        SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_linear_attention_01: grid too large");
-        den_kernel<<<dim3((unsigned)blocks), dim3(256), (size_t)nbits * 4 * sizeof(int32_t), st>>>(q_codes, ksum, den, Nq, W, n_chunks);
-        int rc = sa::check_launch("sa_linear_attention_01(normaliser)");
-        if (rc != SA_OK) return rc;
-        mode.den = den;
-        mode.eps = eps;
-        return run_additive(q_codes, nullptr, nullptr, out, B, H, Nq, Nk, nbits, dv, 1.0f, kv, 2 | (phases & SA_ADDITIVE_VALU),
-                            workspace, add_ws, stream, mode);
-    }
-    return SA_OK;
+    mode.ksum = ksum;
+    mode.ksum_part = reinterpret_cast<int32_t *>(ws + L.counts);
+    mode.den = reinterpret_cast<int32_t *>(ws + L.den);
+    mode.eps = eps;
+    return run_additive(q_codes, k_codes, v, out, B, H, Nq, Nk, nbits, dv, 1.0f, kv, phases, workspace, L.add, stream, mode);
 }
 
 extern "C" int sa_dwconv3x3(const float *v, const float *w, const float *bias_or_null, float *out, int accumulate,

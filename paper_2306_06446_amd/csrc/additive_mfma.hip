@@ -9,25 +9,31 @@
 // plain-VALU rate is 39 T adds/s on this chip; the three-plane bf16 form runs ~20 times faster).
 //
 //   K^T V   : M = code bits (one 64-bit word = two 32-bit tiles per wavefront), N = dv columns,
-//             K = tokens, 16 per MFMA.  The A operand is built in registers from the code words
-//             (one bit-field extract per element); V is staged through LDS transposed into its
-//             three bf16 planes, 64 tokens per chunk, double-buffered.  Token ranges are split over workgroups;
-//             partial sums meet in a second pass in ascending order (no float atomics).
-//   Q(K^T V): M = tokens (TM 32-token tiles per wavefront), N = dv columns, K = code bits.  The
-//             A operand of a step is the 8 bf16 signs of one code byte, read from a 256-entry
-//             table in LDS; K^T V is staged once per workgroup, transposed into its three planes.
+//             K = tokens, 16 per MFMA.  V is staged through LDS transposed into its three bf16
+//             planes, 64 tokens per chunk, double-buffered.  Token ranges are split over workgroups;
+//             partial sums meet in ascending order (no float atomics), in Q(K^T V) itself when they are few.
+//   Q(K^T V): M = tokens (TM 32-token tiles per wavefront), N = dv columns, K = code bits.
+//             K^T V is staged once per workgroup, transposed into its three planes.
+//
+// The +-1 operand of both is made with two vector operations per pair of elements, from dwords that hold one bit of
+// each element 16 positions apart: a shift brings the two bits to the sign positions of the two bf16 halves, an
+// and-or drops the rest and adds the exponent of 1.0.  For Q(K^T V) the query's own code words are such dwords (bit i and
+// bit i + 16 are neighbours in K, and K^T V is staged in that order: K may be permuted as long as both operands are);
+// for K^T V the key codes are staged as dwords of 16 code bits of two consecutive tokens.
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_common.h"
 
 namespace {
 
 using sa::kWave;
 
-constexpr int kStageBatch = 4;             // staging tasks whose loads a thread keeps in flight together
-
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -47,280 +53,365 @@ __device__ inline void split3_pair(float a, float b, uint32_t (&t)[3]) {
     }
 }
 
-// Rows r0, r0+1 (pairs) x columns of an fp32 matrix [n_rows, DV] with row stride `row_stride` floats
-// -> three transposed bf16 planes plane[p][col * stride + row], rows >= n_valid zero.  One task =
-// two consecutive rows x four columns; a thread issues the loads of kStageBatch tasks together.
-template <int DV>
-__device__ inline void stage_transposed(const float *__restrict__ src, size_t row_stride, int n_valid, int n_pad,
-                                        uint16_t *plane0, uint16_t *plane1, uint16_t *plane2, int stride, int tid,
-                                        int n_threads) {
-    const int n_tasks = (n_pad / 2) * (DV / 4);
-    for (int base = 0; base < n_tasks; base += n_threads * kStageBatch) {
-        float4 v0[kStageBatch], v1[kStageBatch];
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int t = base + u * n_threads + tid;
-            const int c4 = t % (DV / 4), j = 2 * (t / (DV / 4));
-            v0[u] = v1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            const float *p = src + (size_t)j * row_stride + c4 * 4;
-            if (t < n_tasks && j < n_valid) v0[u] = *reinterpret_cast<const float4 *>(p);
-            if (t < n_tasks && j + 1 < n_valid) v1[u] = *reinterpret_cast<const float4 *>(p + row_stride);
-        }
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int t = base + u * n_threads + tid;
-            if (t >= n_tasks) continue;
-            const int c4 = t % (DV / 4), j = 2 * (t / (DV / 4));
-            const float a0[4] = {v0[u].x, v0[u].y, v0[u].z, v0[u].w}, a1[4] = {v1[u].x, v1[u].y, v1[u].z, v1[u].w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                uint32_t t[3];
-                split3_pair(a0[c], a1[c], t);
-                const int off = (c4 * 4 + c) * stride + j;             // even: 4-byte aligned
-                *reinterpret_cast<uint32_t *>(plane0 + off) = t[0];
-                *reinterpret_cast<uint32_t *>(plane1 + off) = t[1];
-                *reinterpret_cast<uint32_t *>(plane2 + off) = t[2];
-            }
-        }
-    }
-}
-
-// The three transposed K^T V planes, the sign table and some slack must fit the LDS of a CU.
-constexpr bool qkv_fits(int dv, int nbits) { return (size_t)3 * dv * (nbits + 8) * 2 + 4096 <= 150 * 1024; }
-
-// Two bf16 code values in one dword: +1.0 (0x3F80) where the bit of `lo` / `hi` at position `pos` is set;
-// a clear bit stands for -1.0, or for 0.0 with ZO ({0,1} codes: the Add layer that skips zeros).
+// Two bf16 operand elements from the bits at positions 15 - sh and 31 - sh of x: +1.0 (0x3F80) for a clear and -1.0 for
+// a set bit, the negative of what the code stands for (the sums are negated where they leave); with ZO ({0,1} codes)
+// 0.0 and 1.0.
 template <bool ZO>
-__device__ inline uint32_t sign_pair(uint32_t lo, uint32_t hi, int pos) {
-    if (ZO) {
-        const uint32_t bl = __builtin_amdgcn_ubfe(lo, pos, 1), bh = __builtin_amdgcn_ubfe(hi, pos, 1);
-        return (bl * 0x3F80u) | (bh * 0x3F800000u);
-    }
-    const uint32_t nl = __builtin_amdgcn_ubfe(~lo, pos, 1), nh = __builtin_amdgcn_ubfe(~hi, pos, 1);
-    return 0x3F803F80u | (nl << 15) | (nh << 31);
+__device__ inline uint32_t code_pair(uint32_t x, int sh) {
+    if (ZO) return ((x >> (15 - sh)) & 0x00010001u) * 0x3F80u;
+    return ((x << sh) & 0x80008000u) | 0x3F803F80u;
 }
 
 // ------------------------------------------------------------------------------ K^T V ----
-// Workgroup: one (b, h), one group of up to 4 code words, one token range.  WB words per group
-// (1, 2, 3 or 4), PH token phases (wavefronts that share a word take alternate 16-token steps).
-// Tokens pass in chunks of 64 through two LDS buffers: the rows of chunk c+1 are loaded into
-// registers before chunk c is multiplied and written (split into their planes) after it.
-constexpr int kTok = 64;                   // tokens per chunk
-constexpr int kTokStride = kTok + 8;       // bf16 elements per transposed row: 144 bytes, conflict-free b128 reads
+// Workgroup: one (b, h), up to four code words, up to 64 columns, one token range; eight wavefronts.  A wavefront has WB (1 or
+// 2) words and every PH-th 16-token step, and holds that whole [64 WB bits, DVC columns] accumulator.  Its V rows and code
+// words come in by direct global -> LDS loads into a ring of its own, RING steps deep (registers for that many are not
+// there), so nothing is shared until the end and there is no barrier in the loop.  From the ring a lane reads its own MFMA
+// operands, V[8 tokens][its columns] and its tokens' code words, splits V into the three terms in registers and makes the
+// +-1 operand of a 32-bit tile with three vector operations per pair of tokens.
+// (With four words two wavefronts split the same V: a SIMD issues a vector instruction of one wavefront in 5.2 cycles
+// but of two in 2.6, and four of those fit in the shadow of an MFMA.)
+// The kernel before this one staged V's planes through LDS for four wavefronts that shared them; its phases - load, split,
+// multiply, with a barrier or two per 64 tokens - added up instead of overlapping.
+// The wavefronts' accumulators meet in LDS in ascending order.
+constexpr int kKtvWaves = 8;
 
-template <int DV>
-struct KtvChunk {
-    static constexpr int U = (kTok / 2 * (DV / 4) + 191) / 192;      // staging tasks per thread (>= 192 threads)
-    float4 v0[U], v1[U];
-    uint64_t code;
-};
-
-template <int DV>
-__device__ inline void ktv_load(KtvChunk<DV> &c, const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
-                                long bh, int b, int h, int H, int Nk, int W, int w0, int wb, int WB, long j0, int n,
-                                int tid, int n_threads) {
-    // one code word per thread: kTok * WB <= 256 of them, zero past the last token / word
-    const int j = tid / WB, wq = tid % WB;
-    c.code = (tid < kTok * WB && j < n && wq < wb) ? k_codes[((size_t)bh * Nk + j0 + j) * W + w0 + wq] : 0ull;
-    constexpr int n_tasks = kTok / 2 * (DV / 4);
-    const float *src = v + (((size_t)b * Nk + j0) * H + h) * DV;
-    const size_t row_stride = (size_t)H * DV;
-#pragma unroll
-    for (int u = 0; u < KtvChunk<DV>::U; ++u) {
-        const int t = u * n_threads + tid;
-        const int c4 = t % (DV / 4), jr = 2 * (t / (DV / 4));
-        c.v0[u] = c.v1[u] = make_float4(0.f, 0.f, 0.f, 0.f);     // rows past the last token add nothing
-        const float *p = src + (size_t)jr * row_stride + c4 * 4;
-        if (t < n_tasks && jr < n) c.v0[u] = *reinterpret_cast<const float4 *>(p);
-        if (t < n_tasks && jr + 1 < n) c.v1[u] = *reinterpret_cast<const float4 *>(p + row_stride);
-    }
-}
-
-template <int DV>
-__device__ inline void ktv_store(const KtvChunk<DV> &c, uint64_t *kc, uint16_t *plane0, uint16_t *plane1, uint16_t *plane2,
-                                 int WB, int tid, int n_threads) {
-    if (tid < kTok * WB) kc[tid] = c.code;
-    constexpr int n_tasks = kTok / 2 * (DV / 4);
-#pragma unroll
-    for (int u = 0; u < KtvChunk<DV>::U; ++u) {
-        const int t = u * n_threads + tid;
-        if (t >= n_tasks) continue;
-        const int c4 = t % (DV / 4), jr = 2 * (t / (DV / 4));
-        const float a0[4] = {c.v0[u].x, c.v0[u].y, c.v0[u].z, c.v0[u].w}, a1[4] = {c.v1[u].x, c.v1[u].y, c.v1[u].z, c.v1[u].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t t3[3];
-            split3_pair(a0[q], a1[q], t3);
-            const int off = (c4 * 4 + q) * kTokStride + jr;          // even: 4-byte aligned
-            *reinterpret_cast<uint32_t *>(plane0 + off) = t3[0];
-            *reinterpret_cast<uint32_t *>(plane1 + off) = t3[1];
-            *reinterpret_cast<uint32_t *>(plane2 + off) = t3[2];
-        }
-    }
-}
-
-template <int DV, bool ZO>
-__global__ __launch_bounds__(256) void ktv_mfma_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
-                                                       float *__restrict__ dst, int H, int Nk, int W, int WB, int PH,
-                                                       int splits, int tokens_per_block) {
-    constexpr int JT = DV / 32;
-    constexpr int PLANE = DV * kTokStride;
-    __shared__ __attribute__((aligned(16))) uint64_t kc_s[2][kTok * 4];
-    __shared__ __attribute__((aligned(16))) uint16_t vt_s[2][3 * PLANE];
-    static_assert(sizeof(vt_s) >= 4 * 2 * JT * 16 * 64 * 4 / 2, "the phase reduction reuses the V planes");
+// ksum (ZO): int32 [splits][BH][nbits], the number of tokens of the range whose code bit is set.
+template <int DVC, int WB, int PH, int RING, bool ZO>
+__global__ __launch_bounds__(kKtvWaves * 64) void ktv_mfma_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
+                                                                  float *__restrict__ dst, int32_t *__restrict__ ksum, int H, int Nk,
+                                                                  int W, int DV, int splits, int tokens_per_block) {
+    constexpr int JT = DVC / 32, TB = 2 * WB;                    // 32-column and 32-bit tiles
+    constexpr int PAIRS = kKtvWaves / PH, GW = PAIRS * WB;       // shares of words, words of a workgroup
+    constexpr int TILE = 32 * DVC;                               // floats of one 32-bit tile
+    constexpr int V_BYTES = 16 * DVC * 4, SLOT = V_BYTES + 256;  // a step in the ring: V rows, code words
+    constexpr int LOADS = V_BYTES / 1024 + 1;                    // direct loads of a step
+    __shared__ __attribute__((aligned(1024))) uint8_t ring_s[kKtvWaves * RING * SLOT];
+    static_assert(sizeof(ring_s) >= kKtvWaves * TILE * 4, "the final sum reuses the ring");
+    float *red_s = reinterpret_cast<float *>(ring_s);
+    __shared__ int32_t cnt_s[ZO ? kKtvWaves * WB * 64 : 1];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_threads = blockDim.x;
-    const int n_groups = (W + 3) / 4;
-    // blockIdx.x = (bh * n_groups + group) * splits + split
-    const int split = blockIdx.x % splits;
-    const long bhg = blockIdx.x / splits;
-    const int group = (int)(bhg % n_groups);
-    const long bh = bhg / n_groups;
+    const int phase = wave / PAIRS;
+    const int n_groups = (W + GW - 1) / GW, n_cols = DV / DVC;
+    // blockIdx.x = ((bh * n_groups + group) * n_cols + column group) * splits + split
+    const int part = blockIdx.x % splits;
+    const long rest = blockIdx.x / splits;
+    const int c0 = (int)(rest % n_cols) * DVC;
+    const int group = (int)(rest / n_cols % n_groups);
+    const long bh = rest / n_cols / n_groups;
     const int b = (int)(bh / H), h = (int)(bh % H);
-    const int w0 = group * 4;
-    const int wb = min(WB, W - w0);               // words of this group
-    const int wl = wave % WB, phase = wave / WB;  // this wavefront's word (within the group) and token phase
-    const bool active = wl < wb;
+    const int w0 = group * GW + (wave % PAIRS) * WB;             // this wavefront's first word (may lie past the last one: idle)
     const int m = lane & 31, kg = lane >> 5;
 
-    v16f acc[2][JT];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][jt][r] = 0.0f;
+    const int first = part * tokens_per_block;
+    const int last = min(Nk, first + tokens_per_block);
+    const int n_steps = w0 < W ? (last - first + 15) / 16 : 0;
+    const size_t v_row = (size_t)H * DV * 4, c_row = (size_t)W * 8;                     // bytes
+    const char *v_base = reinterpret_cast<const char *>(v + (((size_t)b * Nk + first) * H + h) * DV + c0);
+    const char *c_base = reinterpret_cast<const char *>(k_codes + ((size_t)bh * Nk + first) * W + w0);
 
-    const long first = (long)split * tokens_per_block;
-    const long last = min((long)Nk, first + tokens_per_block);
-    KtvChunk<DV> regs;
-    if (first < last)
-        ktv_load<DV>(regs, k_codes, v, bh, b, h, H, Nk, W, w0, wb, WB, first, (int)min((long)kTok, last - first), tid,
-                     n_threads);
-    int buf = 0;
-    for (long j0 = first; j0 < last; j0 += kTok, buf ^= 1) {
-        const int n = (int)min((long)kTok, last - j0);
-        const int n_pad = (n + 15) & ~15;
-        uint16_t *pl = vt_s[buf];
-        ktv_store<DV>(regs, kc_s[buf], pl, pl + PLANE, pl + 2 * PLANE, WB, tid, n_threads);
-        __syncthreads();                           // this chunk is staged; the other buffer has been consumed
-        if (j0 + kTok < last)
-            ktv_load<DV>(regs, k_codes, v, bh, b, h, H, Nk, W, w0, wb, WB, j0 + kTok,
-                         (int)min((long)kTok, last - j0 - kTok), tid, n_threads);
-        if (!active) continue;
-        const uint64_t *kc = kc_s[buf];
-        for (int k0 = 16 * phase; k0 < n_pad; k0 += 16 * PH) {
-            const int kb = k0 + 8 * kg;            // this lane's first token of the step
-            uint32_t lo[8], hi[8];
+    // Step i into a slot of this wavefront's ring.  An address is the step's (the same in every lane) plus this lane's offset in
+    // it; rows past the last token re-read the last one (step() blanks them), words past the last one likewise.
+    uint8_t *ring = ring_s + wave * (RING * SLOT);
+    const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)ring;
+    constexpr int RPI = 1024 / (DVC * 4), LPR = DVC / 4;         // V rows per load, lanes per row
+    const int c_tok = lane / (2 * WB) % 16, c_dw = min(lane % (2 * WB), 2 * (W - w0) - 1);     // (one word: the upper lanes repeat)
+    const uint32_t v_lane = (uint32_t)(lane / LPR) * (uint32_t)v_row + (lane % LPR) * 16;
+    const uint32_t c_lane = (uint32_t)c_tok * (uint32_t)c_row + c_dw * 4;
+    auto issue = [&](int i, int slot) {
+        const char *vp = v_base + (size_t)i * 16 * v_row, *cp = c_base + (size_t)i * 16 * c_row;
+        const int n = last - first - 16 * i;
+        const uint32_t at = ring_base + slot * SLOT;
+        if (n >= 16) {
+#pragma unroll
+            for (int k = 0; k < V_BYTES / 1024; ++k) sa::direct_load_16(vp + k * RPI * v_row, v_lane, at + k * 1024);
+            sa::direct_load_4(cp, c_lane, at + V_BYTES);
+        } else {
+#pragma unroll
+            for (int k = 0; k < V_BYTES / 1024; ++k)
+                sa::direct_load_16(vp, (uint32_t)min(k * RPI + lane / LPR, n - 1) * (uint32_t)v_row + (lane % LPR) * 16, at + k * 1024);
+            sa::direct_load_4(cp, (uint32_t)min(c_tok, n - 1) * (uint32_t)c_row + c_dw * 4, at + V_BYTES);
+        }
+    };
+
+    v16f acc[TB][JT];
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int j = 0; j < JT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][j][r] = 0.0f;
+    uint32_t cnt[TB] = {};                         // ZO: set bits among the even (lower half) and odd tokens of this lane
+    int32_t total[TB] = {};
+    const uint32_t pick = m < 16 ? 0x05040100u : 0x07060302u;    // the 16-bit half of a code dword that holds this lane's bit
+    const int sh = 15 - (m & 15);
+
+    // One step out of its slot: the +-1 operands, then column tile by column tile the three terms of V and their products.
+    auto step = [&](int i, int slot) {
+        const int n = last - first - 16 * i;
+        const uint8_t *at = ring + slot * SLOT;
+        float x[8][JT];
+        uint32_t c[8][TB];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t *cw = reinterpret_cast<const uint32_t *>(at + V_BYTES) + (8 * kg + e) * TB;
+            if constexpr (WB == 2) {
+                const uint4 t = *reinterpret_cast<const uint4 *>(cw);
+                c[e][0] = t.x; c[e][1] = t.y; c[e][2] = t.z; c[e][3] = t.w;
+            } else {
+                const uint2 t = *reinterpret_cast<const uint2 *>(cw);
+                c[e][0] = t.x; c[e][1] = t.y;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float *xp = reinterpret_cast<const float *>(at) + (8 * kg + e) * DVC + JT * m;
+            if constexpr (JT == 2) {
+                const float2 t = *reinterpret_cast<const float2 *>(xp);
+                x[e][0] = t.x;
+                x[e][1] = t.y;
+            } else {
+                x[e][0] = *xp;
+            }
+        }
+        if (n < 16) {                                            // tokens that do not exist add nothing
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const uint64_t wd = kc[(kb + e) * WB + wl];
-                lo[e] = (uint32_t)wd;
-                hi[e] = (uint32_t)(wd >> 32);
-            }
-            // A operands: element e of the lane is token kb + e, bit m of the lower / upper half word
-            uint32_t a0[4], a1[4];
+                const bool in = 8 * kg + e < n;
 #pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                a0[e2] = sign_pair<ZO>(lo[2 * e2], lo[2 * e2 + 1], m);
-                a1[e2] = sign_pair<ZO>(hi[2 * e2], hi[2 * e2 + 1], m);
-            }
-            const v8bf s0 = __builtin_bit_cast(v8bf, make_uint4(a0[0], a0[1], a0[2], a0[3]));
-            const v8bf s1 = __builtin_bit_cast(v8bf, make_uint4(a1[0], a1[1], a1[2], a1[3]));
+                for (int j = 0; j < JT; ++j) x[e][j] = in ? x[e][j] : 0.0f;
+                if (ZO) {
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) {
-                const int off = (jt * 32 + m) * kTokStride + kb;
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    const v8bf vp = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(pl + p * PLANE + off));
-                    acc[0][jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(s0, vp, acc[0][jt], 0, 0, 0);
-                    acc[1][jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(s1, vp, acc[1][jt], 0, 0, 0);
+                    for (int q = 0; q < TB; ++q) c[e][q] = in ? c[e][q] : 0u;
                 }
             }
         }
-    }
-
-    // token phases of one word meet in LDS, ascending phase order
-    if (PH > 1) {
-        float *red = reinterpret_cast<float *>(&vt_s[0][0]);     // 2 * JT * 16 * 64 floats per word
-        for (int ph = 1; ph < PH; ++ph) {
-            __syncthreads();
-            if (active && phase == ph) {
+        v8bf sg[TB];
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < TB; ++t) {
+            uint32_t d[4];
 #pragma unroll
-                    for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) red[((wl * 2 * JT + t * JT + jt) * 16 + r) * 64 + lane] = acc[t][jt][r];
+            for (int e2 = 0; e2 < 4; ++e2) {
+                const uint32_t pair = __builtin_amdgcn_perm(c[2 * e2 + 1][t], c[2 * e2][t], pick);
+                d[e2] = code_pair<ZO>(pair, sh);
+                if (ZO) cnt[t] += (pair >> (15 - sh)) & 0x00010001u;
             }
-            __syncthreads();
-            if (active && phase == 0) {
+            sg[t] = __builtin_bit_cast(v8bf, make_uint4(d[0], d[1], d[2], d[3]));
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): this slot has been read ...
+        if (i + RING * PH < n_steps) issue(i + RING * PH, slot);           // ... and is free for the step RING ahead
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+        for (int j = 0; j < JT; ++j) {
+            uint32_t w[3][4];
 #pragma unroll
-                    for (int jt = 0; jt < JT; ++jt)
+            for (int e2 = 0; e2 < 4; ++e2) {
+                uint32_t t3[3];
+                split3_pair(x[2 * e2][j], x[2 * e2 + 1][j], t3);
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[t][jt][r] += red[((wl * 2 * JT + t * JT + jt) * 16 + r) * 64 + lane];
+                for (int p = 0; p < 3; ++p) w[p][e2] = t3[p];
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const v8bf vp = __builtin_bit_cast(v8bf, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
+#pragma unroll
+                for (int t = 0; t < TB; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg[t], vp, acc[t][j], 0, 0, 0);
+            }
+        }
+    };
+
+#pragma unroll
+    for (int q = 0; q < RING; ++q)
+        if (phase + q * PH < n_steps) issue(phase + q * PH, q);
+    int slot = 0, done = 0;
+    for (int i = phase; i < n_steps; i += PH) {
+        const int later = (n_steps - 1 - i) / PH;                // steps of this wavefront after this one
+        if (later >= RING - 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (((RING - 1) * LOADS) & 15) | ((((RING - 1) * LOADS) >> 4) << 14));
+        else if (RING > 2 && later == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * LOADS) & 15) | (((2 * LOADS) >> 4) << 14));
+        else if (later == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15));      // (LOADS <= 5)
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        asm volatile("" ::: "memory");                           // the slot's bytes are not read before this point
+        step(i, slot);
+        slot = slot + 1 == RING ? 0 : slot + 1;
+        if (ZO && (++done & 0x1FFF) == 0) {        // before the 16-bit halves can overflow
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                total[t] += (int32_t)(cnt[t] & 0xFFFFu) + (int32_t)(cnt[t] >> 16);
+                cnt[t] = 0;
             }
         }
     }
-    if (!active || phase != 0) return;
-    // dst: [splits][BH][nbits][DV]; accumulator row = bit within the 32-bit tile, column = lane % 32
-    const size_t bh_count = (size_t)gridDim.x / splits / n_groups;
-    float *o = dst + (((size_t)split * bh_count + bh) * W + w0 + wl) * 64 * DV;
+    __syncthreads();                               // every ring has been read
+
+    // ---- the wavefronts' sums, in ascending order, one 32-bit tile of every share at a time; dst: [splits][BH][nbits][DV].
+    //      With +-1 codes the operand was -1 for a set bit (the code bit as the sign bit), so the sum is negated here.
+    const size_t bh_count = (size_t)gridDim.x / splits / n_groups / n_cols;
+    const size_t row0 = (((size_t)part * bh_count + bh) * W + group * GW) * 64;
+    const int rows_here = min(GW, W - group * GW) * 64;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < TB; ++t) {
+        if (t > 0) __syncthreads();
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt)
+        for (int r = 0; r < 16; ++r) {
+            float *at = red_s + wave * TILE + (8 * (r >> 2) + 4 * kg + (r & 3)) * DVC + JT * m;
+            if constexpr (JT == 2)
+                *reinterpret_cast<float2 *>(at) = make_float2(acc[t][0][r], acc[t][1][r]);
+            else
+                *at = acc[t][0][r];
+        }
+        __syncthreads();
+        for (int q = tid; q < PAIRS * TILE / 4; q += kKtvWaves * 64) {
+            const int share = q / (TILE / 4);
+            f32x4 a = reinterpret_cast<const f32x4 *>(red_s)[q];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int bit = t * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
-                o[(size_t)bit * DV + jt * 32 + m] = acc[t][jt][r];
-            }
+            for (int ph = 1; ph < PH; ++ph) a += reinterpret_cast<const f32x4 *>(red_s)[ph * PAIRS * (TILE / 4) + q];
+            const int row = share * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
+            if (!ZO) a = -a;
+            if (row < rows_here) *reinterpret_cast<f32x4 *>(dst + (row0 + row) * DV + c0 + col) = a;
+        }
+    }
+    if (ZO && c0 == 0) {
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            int32_t n = total[t] + (int32_t)(cnt[t] & 0xFFFFu) + (int32_t)(cnt[t] >> 16);
+            n += __shfl_xor(n, 32);
+            if (kg == 0) cnt_s[wave * WB * 64 + t * 32 + m] = n;
+        }
+        __syncthreads();
+        for (int q = tid; q < rows_here; q += kKtvWaves * 64) {
+            int32_t n = cnt_s[q];
+#pragma unroll
+            for (int ph = 1; ph < PH; ++ph) n += cnt_s[ph * PAIRS * WB * 64 + q];
+            ksum[row0 + q] = n;
+        }
+    }
+}
+
+// kv[i] = sum over splits of part[s][i].  G threads per 16 bytes: thread g takes a contiguous range of splits, s
+// ascending, and the ranges meet in LDS in ascending order (with G = 1 the plain ascending sum).  With one thread per
+// 16 bytes a small K^T V with many splits leaves the chip idle (64 KiB x 4 x 192 splits: 33 us on 64 workgroups).
+template <int G, typename V4>
+__device__ inline void reduce_splits(const V4 *__restrict__ part, V4 *__restrict__ dst, long n4, int splits, long i, int g, V4 *red) {
+    V4 a = {};
+    if (i < n4) {
+        const int per = (splits + G - 1) / G, s0 = g * per, s1 = min(splits, s0 + per);
+        int s = s0;
+        for (; s + 4 <= s1; s += 4) {
+            V4 p[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p[q] = part[(size_t)(s + q) * n4 + i];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a = (s + q == s0) ? p[q] : a + p[q];
+        }
+        for (; s < s1; ++s) a = (s == s0) ? part[(size_t)s * n4 + i] : a + part[(size_t)s * n4 + i];
+    }
+    if (G > 1) {
+        red[threadIdx.x] = a;
+        __syncthreads();
+        if (g == 0 && i < n4) {
+#pragma unroll
+            for (int k = 1; k < G; ++k)
+                if (k * ((splits + G - 1) / G) < splits) a = a + red[k * (256 / G) + threadIdx.x];
+        }
+    }
+    if (g == 0 && i < n4) dst[i] = a;
+}
+
+// Workgroups below kv_blocks reduce K^T V, the rest (ksum_part not null) the bit counts.
+template <int G>
+__global__ __launch_bounds__(256) void ktv_sum_kernel(const f32x4 *__restrict__ part, f32x4 *__restrict__ kv, long n4, int splits,
+                                                      unsigned kv_blocks, const i32x4 *__restrict__ ksum_part,
+                                                      i32x4 *__restrict__ ksum, long k4) {
+    __shared__ __attribute__((aligned(16))) f32x4 red[G > 1 ? 256 : 1];
+    const int g = threadIdx.x / (256 / G), l = threadIdx.x % (256 / G);
+    if (blockIdx.x < kv_blocks)
+        reduce_splits<G>(part, kv, n4, splits, (long)blockIdx.x * (256 / G) + l, g, red);
+    else
+        reduce_splits<G>(ksum_part, ksum, k4, splits, (long)(blockIdx.x - kv_blocks) * (256 / G) + l, g,
+                         reinterpret_cast<i32x4 *>(red));
 }
 
 // --------------------------------------------------------------------------- Q (K^T V) ----
-// Workgroup: one (b, h) and a range of token tiles; kQkvWaves wavefronts, TM 32-token tiles each per pass.
-constexpr int kQkvWaves = 8;
+// Workgroup: one (b, h), DVC (32 or 64) columns and a range of token tiles; NW wavefronts, TM 32-token tiles each per pass.
+//
+// K runs over the code bits in an order that makes the query's own code words the operand (see code_pair): step
+// ks = 2 * half + s of a 32-bit half word, lane half kg, element e is bit 8 s + 4 kg + e / 2 + 16 (e % 2) of that half.
 
-// den (optional, {0,1} codes): int32 [B*H, Nq], the row normaliser; the row then leaves as acc / (den + eps)
-// instead of scale * acc.
-template <int DV, int W, int TM, bool ZO>
-__global__ __launch_bounds__(kQkvWaves * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, const float *__restrict__ kv,
-                                                       float *__restrict__ out, int H, int Nq, int blocks_per_bh,
-                                                       int tiles_per_block, float scale, const int32_t *__restrict__ den,
-                                                       float eps) {
-    constexpr int JT = DV / 32;
+using sa::AddFused;
+
+template <int DVC, int W, int NW, int TM, bool ZO>
+__global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f,
+                                                                  int H, int Nq, int DV, long BH, int blocks_per_bh, int tiles_per_block) {
+    constexpr int JT = DVC / 32;
     constexpr int NBITS = W * 64;
     constexpr int STRIDE = NBITS + 8;             // bf16 elements per transposed K^T V row
-    __shared__ __attribute__((aligned(16))) uint16_t kvt_s[3][DV * STRIDE];
-    __shared__ __attribute__((aligned(16))) uint4 sign_s[256];
+    __shared__ __attribute__((aligned(16))) uint16_t kvt_s[3][DVC * STRIDE];
+    __shared__ int32_t tab_s[ZO ? NBITS * 4 : 1];  // normaliser: sums of the 16 subsets of every 4 bit counts
+    __shared__ int32_t ks_s[ZO ? NBITS : 1];
 
     const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int n_threads = NW * 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const long bh = blockIdx.x / blocks_per_bh;
+    // blockIdx.x = (bh * column groups + column group) * blocks_per_bh + part
     const int part = blockIdx.x % blocks_per_bh;
+    const int n_cols = DV / DVC;
+    const int c0 = (int)(blockIdx.x / blocks_per_bh % n_cols) * DVC;
+    const long bh = blockIdx.x / blocks_per_bh / n_cols;
     const int b = (int)(bh / H), h = (int)(bh % H);
     const int m = lane & 31, kg = lane >> 5;
 
-    // byte -> its 8 bits as bf16 signs, element e = bit e
-    if (tid < 256) {
-        uint32_t d[4];
+    // K^T V -> the three planes: a task is the eight rows of one lane half of a step, one column; with more than one
+    // partial they are summed on the way, in ascending order, and the first workgroup of the (b, h) leaves the sum in kv
+    for (int t = tid; t < NBITS / 8 * DVC; t += n_threads) {
+        const int col = t % DVC, grp = t / DVC;                    // grp = (half * 2 + s) * 2 + kg
+        const int bit0 = (grp >> 2) * 32 + ((grp >> 1) & 1) * 8 + (grp & 1) * 4;
+        const size_t at = ((size_t)bh * NBITS + bit0) * DV + c0 + col;
+        float x[8];
 #pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) d[e2] = sign_pair<ZO>((uint32_t)tid, (uint32_t)tid >> 1, 2 * e2);
-        sign_s[tid] = make_uint4(d[0], d[1], d[2], d[3]);
+        for (int e = 0; e < 8; ++e) x[e] = f.kv_in[at + ((e >> 1) + 16 * (e & 1)) * DV];
+        for (int s = 1; s < f.splits; ++s) {
+            const float *p = f.kv_in + (size_t)s * BH * NBITS * DV + at;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] += p[((e >> 1) + 16 * (e & 1)) * DV];
+        }
+        if (f.kv_out && part == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f.kv_out[at + ((e >> 1) + 16 * (e & 1)) * DV] = x[e];
+        }
+        uint32_t w[3][4];
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+            uint32_t t3[3];
+            split3_pair(x[2 * e2], x[2 * e2 + 1], t3);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) w[p][e2] = t3[p];
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            *reinterpret_cast<uint4 *>(&kvt_s[p][col * STRIDE + grp * 8]) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
     }
-    stage_transposed<DV>(kv + (size_t)bh * NBITS * DV, (size_t)DV, NBITS, NBITS, kvt_s[0], kvt_s[1], kvt_s[2], STRIDE, tid,
-                         kQkvWaves * 64);
+    if (ZO) {
+        for (int j = tid; j < NBITS; j += n_threads) {
+            int32_t c = f.ksum_in[(size_t)bh * NBITS + j];
+            for (int s = 1; s < f.splits; ++s) c += f.ksum_in[((size_t)s * BH + bh) * NBITS + j];
+            ks_s[j] = c;
+            if (f.ksum_out && part == 0 && c0 == 0) f.ksum_out[(size_t)bh * NBITS + j] = c;
+        }
+        __syncthreads();
+        for (int i = tid; i < NBITS * 4; i += n_threads) {
+            const int32_t *k4 = ks_s + (i >> 4) * 4;
+            tab_s[i] = ((i & 1) ? k4[0] : 0) + ((i & 2) ? k4[1] : 0) + ((i & 4) ? k4[2] : 0) + ((i & 8) ? k4[3] : 0);
+        }
+    }
     __syncthreads();
 
     const int n_tiles = (Nq + 31) / 32;
     const int tile_begin = part * tiles_per_block;
     const int tile_end = min(n_tiles, tile_begin + tiles_per_block);
-    for (int tile0 = tile_begin + wave * TM; tile0 < tile_end; tile0 += kQkvWaves * TM) {
+    for (int tile0 = tile_begin + wave * TM; tile0 < tile_end; tile0 += NW * TM) {
         uint32_t code[TM][2 * W];
+        float factor[TM];                         // ZO: 1 / (normaliser + eps) of this lane's query
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             const int n = min((tile0 + tm) * 32 + m, Nq - 1);
@@ -331,33 +422,48 @@ __global__ __launch_bounds__(kQkvWaves * 64) void qkv_mfma_kernel(const uint64_t
                 code[tm][2 * w] = (uint32_t)wd;
                 code[tm][2 * w + 1] = (uint32_t)(wd >> 32);
             }
+            if (ZO) {
+                int32_t d = 0;
+#pragma unroll
+                for (int q = 0; q < 2 * W; ++q)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        d += tab_s[((q * 8 + 4 * kg + g) << 4) + ((code[tm][q] >> (16 * kg + 4 * g)) & 15u)];
+                d += __shfl_xor(d, 32);
+                factor[tm] = 1.0f / ((float)d + f.eps);
+            }
+#pragma unroll
+            for (int q = 0; q < 2 * W; ++q) {     // the bits of lane half kg to where code_pair expects them
+                code[tm][q] = ZO ? code[tm][q] >> (4 * kg) : code[tm][q] << (4 - 4 * kg);
+            }
         }
         v16f acc[TM][JT];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt)
+            for (int j = 0; j < JT; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[tm][jt][r] = 0.0f;
+                for (int r = 0; r < 16; ++r) acc[tm][j][r] = 0.0f;
 
 #pragma unroll
         for (int ks = 0; ks < NBITS / 16; ++ks) {
-            // bits 16 ks + 8 kg .. + 7 of the code: one byte of half word ks / 2
             v8bf a[TM];
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
-                const uint32_t byte = __builtin_amdgcn_ubfe(code[tm][ks >> 1], 16 * (ks & 1) + 8 * kg, 8);
-                a[tm] = __builtin_bit_cast(v8bf, sign_s[byte]);
+                uint32_t d[4];
+#pragma unroll
+                for (int e2 = 0; e2 < 4; ++e2)
+                    d[e2] = code_pair<ZO>(code[tm][ks >> 1], (ZO ? 15 : 11) - 8 * (ks & 1) - e2);
+                a[tm] = __builtin_bit_cast(v8bf, make_uint4(d[0], d[1], d[2], d[3]));
             }
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) {
-                const int off = (jt * 32 + m) * STRIDE + 16 * ks + 8 * kg;
+            for (int j = 0; j < JT; ++j) {
+                const int off = (j * 32 + m) * STRIDE + 16 * ks + 8 * kg;
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
                     const v8bf kp = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(kvt_s[p] + off));
 #pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
-                        acc[tm][jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tm], kp, acc[tm][jt], 0, 0, 0);
+                    for (int tm = 0; tm < TM; ++tm) acc[tm][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tm], kp, acc[tm][j], 0, 0, 0);
                 }
             }
             // keep the steps apart: hoisting every operand read of the tile to the top costs hundreds of registers
@@ -366,114 +472,158 @@ __global__ __launch_bounds__(kQkvWaves * 64) void qkv_mfma_kernel(const uint64_t
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (tile0 + tm >= tile_end) continue;
+            // a row's address is the tile's (the same in every lane) plus this lane's offset in it
+            const size_t tile_at = (((size_t)b * Nq + (size_t)(tile0 + tm) * 32) * H + h) * DV + c0;
+            const uint32_t row_step = (uint32_t)H * DV, lane_at = (uint32_t)(4 * kg) * row_step + m;
+            auto store_rows = [&](auto whole_c) {
+                constexpr bool WHOLE = decltype(whole_c)::value;      // all 32 queries exist
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int n = (tile0 + tm) * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
-                if (n < Nq) {
-                    float *o = out + (((size_t)b * Nq + n) * H + h) * DV + m;
-                    const float f = den ? 1.0f / ((float)den[(size_t)bh * Nq + n] + eps) : scale;
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 8 * (r >> 2) + (r & 3);           // + 4 kg
+                    const float fr = ZO ? __shfl(factor[tm], row + 4 * kg) : -f.scale;      // (+-1: see code_pair)
+                    if (WHOLE || (tile0 + tm) * 32 + row + 4 * kg < Nq) {
+                        const size_t at = tile_at + (size_t)row * row_step;
 #pragma unroll
-                    for (int jt = 0; jt < JT; ++jt) o[jt * 32] = f * acc[tm][jt][r];
+                        for (int j = 0; j < JT; ++j) {
+                            const float val = fr * acc[tm][j][r];
+                            if (f.out) (f.out + at + j * 32)[lane_at] = val;
+                            if (f.xq) (f.xq + at + j * 32)[lane_at] = (int8_t)sa::requant_byte(val * f.act_inv_scale);
+                            if (f.xh) (f.xh + at + j * 32)[lane_at] = (_Float16)val;
+                        }
+                    }
                 }
-            }
+            };
+            if ((tile0 + tm) * 32 + 32 <= Nq)
+                store_rows(std::true_type{});
+            else
+                store_rows(std::false_type{});
         }
     }
 }
 
-template <int DV, int W>
-void launch_qkv_w(const uint64_t *q_codes, const float *kv, float *out, long BH, int H, int Nq, float scale, bool zo,
-                  const int32_t *den, float eps, hipStream_t st) {
-    constexpr int TM = DV == 128 ? 1 : 2;       // accumulators: TM * DV / 32 tiles of 16 registers
+// How the token tiles of a (b, h) are spread.
+//  * Enough work to fill the chip with 32-tile passes: all columns up to 64 in one workgroup, 16 wavefronts with two tiles
+//    each (a K^T V operand is then read once for both), one workgroup per CU and the tiles divided evenly: 50 us at 8 x 4
+//    heads x 16384 queries x 256 bits x 64 columns (32 columns per workgroup: 57 us, the +-1 operand is made twice).
+//  * Else 32 columns and eight tiles per workgroup: more, smaller workgroups (2 x 3 heads x 2000 x 128 bits x 128: 6.5 us
+//    against 11; one DeiT-Tiny image: 5.0 against 5.4).
+template <int W>
+void launch_qkv_w(const uint64_t *q_codes, const AddFused &f, long BH, int H, int Nq, int dv, bool zo, hipStream_t st) {
     const int n_tiles = (Nq + 31) / 32;
-    // enough workgroups to fill the chip, but each stages all of K^T V once: several passes of its wavefronts
-    long per_bh = (1024 + BH - 1) / BH;
-    const int passes = (size_t)W * 64 * DV * 4 >= 32768 ? 4 : 1;      // a small K^T V is cheap to stage again
-    const long max_per_bh = (n_tiles + kQkvWaves * TM * passes - 1) / (kQkvWaves * TM * passes);
-    if (per_bh > max_per_bh) per_bh = max_per_bh;
-    if (per_bh < 1) per_bh = 1;
-    const int tiles_per_block = (int)((n_tiles + per_bh - 1) / per_bh);
-    const dim3 grid((unsigned)(BH * per_bh)), block(kQkvWaves * 64);
-    if (zo)
-        qkv_mfma_kernel<DV, W, TM, true><<<grid, block, 0, st>>>(q_codes, kv, out, H, Nq, (int)per_bh, tiles_per_block, scale, den, eps);
-    else
-        qkv_mfma_kernel<DV, W, TM, false><<<grid, block, 0, st>>>(q_codes, kv, out, H, Nq, (int)per_bh, tiles_per_block, scale, den, eps);
-}
-
-template <int DV>
-bool launch_qkv_dv(int W, const uint64_t *q_codes, const float *kv, float *out, long BH, int H, int Nq, float scale, bool zo,
-                   const int32_t *den, float eps, hipStream_t st) {
-    switch (W) {
-        case 1: launch_qkv_w<DV, 1>(q_codes, kv, out, BH, H, Nq, scale, zo, den, eps, st); return true;
-        case 2: launch_qkv_w<DV, 2>(q_codes, kv, out, BH, H, Nq, scale, zo, den, eps, st); return true;
-        case 4:
-            if constexpr (qkv_fits(DV, 256)) {
-                launch_qkv_w<DV, 4>(q_codes, kv, out, BH, H, Nq, scale, zo, den, eps, st);
-                return true;
-            }
-            return false;
-        default: return false;
+#define SA_QKV(DVC_, NW_, TM_)                                                                                                      \
+    const dim3 grid((unsigned)(BH * (dv / DVC_) * per_bh)), block(NW_ * 64);                                                        \
+    if (zo) qkv_mfma_kernel<DVC_, W, NW_, TM_, true><<<grid, block, 0, st>>>(q_codes, f, H, Nq, dv, BH, per_bh, tiles_per_block);     \
+    else qkv_mfma_kernel<DVC_, W, NW_, TM_, false><<<grid, block, 0, st>>>(q_codes, f, H, Nq, dv, BH, per_bh, tiles_per_block);
+    if (dv >= 64 && BH * (dv / 64) * (n_tiles / 32) >= 256) {
+        const long base = BH * (dv / 64);
+        int per_bh = (int)((256 + base - 1) / base);
+        const int tiles_per_block = (n_tiles + per_bh - 1) / per_bh;
+        per_bh = (n_tiles + tiles_per_block - 1) / tiles_per_block;
+        SA_QKV(64, 16, 2)
+    } else {
+        const int tiles_per_block = 8, per_bh = (n_tiles + 7) / 8;
+        SA_QKV(32, 8, 1)
     }
+#undef SA_QKV
 }
 
 }  // namespace
 
 namespace sa {
 
-// Shapes the matrix-core kernels take: K^T V any nbits (multiple of 64); Q(K^T V) 64-, 128- or
-// 256-bit codes whose three K^T V planes fit the LDS.
+// Shapes the matrix-core kernels take: K^T V any nbits (multiple of 64); Q(K^T V) 64-, 128- or 256-bit codes.
 bool additive_mfma_ktv_supported(int nbits, int dv) { return nbits % 64 == 0 && (dv == 32 || dv == 64 || dv == 128); }
 
 bool additive_mfma_qkv_supported(int nbits, int dv) {
-    if (!(nbits == 64 || nbits == 128 || nbits == 256) || !(dv == 32 || dv == 64 || dv == 128)) return false;
-    return qkv_fits(dv, nbits);
+    return (nbits == 64 || nbits == 128 || nbits == 256) && (dv == 32 || dv == 64 || dv == 128);
 }
 
-// Token splits of the K^T V pass: enough workgroups to fill the chip, whole 128-token chunks each.
-AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits) {
+// Token splits of the K^T V pass: one workgroup per CU (every split writes a whole K^T V that has to be read again), and at
+// least two steps for every wavefront.
+AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv) {
     AdditiveMfmaPlan p;
     const int W = nbits / 64;
-    p.groups = (W + 3) / 4;
-    p.wb = W < 4 ? W : 4;
-    p.ph = p.wb == 1 ? 4 : (p.wb == 2 ? 2 : 1);
-    const long base = (long)B * H * p.groups;
-    long splits = (768 + base - 1) / base;
-    const long chunks = ((long)Nk + kTok - 1) / kTok;
-    if (splits > chunks) splits = chunks;
+    p.groups = W <= 2 ? 1 : (W + 3) / 4;
+    const int quantum = 16 * (W <= 2 ? 8 : 4);                   // tokens of one step of every wavefront
+    const long base = (long)B * H * p.groups * (dv > 64 ? dv / 64 : 1);
+    const long units = ((long)Nk + 2 * quantum - 1) / (2 * quantum);
+    long splits = (256 + base - 1) / base;
+    if (splits > units) splits = units;
     if (splits < 1) splits = 1;
     if (splits > 256) splits = 256;
-    const long chunks_per_block = (chunks + splits - 1) / splits;
-    p.tokens_per_block = (int)(chunks_per_block * kTok);
-    p.splits = (int)((chunks + chunks_per_block - 1) / chunks_per_block);
+    const long per = ((long)Nk + splits - 1) / splits;
+    p.tokens_per_block = (int)((per + 15) / 16 * 16);
+    p.splits = (int)(((long)Nk + p.tokens_per_block - 1) / p.tokens_per_block);
     return p;
 }
 
-int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int B, int H, int Nk, int nbits, int dv,
+int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int32_t *ksum, int B, int H, int Nk, int nbits, int dv,
                     const AdditiveMfmaPlan &p, bool zero_one, hipStream_t st) {
     const int W = nbits / 64;
-    const long blocks = (long)B * H * p.groups * p.splits;
+    const long blocks = (long)B * H * p.groups * (dv > 64 ? dv / 64 : 1) * p.splits;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
-    const dim3 grid((unsigned)blocks), block(p.wb * p.ph * kWave);
-#define SA_KTV(DV_, ZO_) ktv_mfma_kernel<DV_, ZO_><<<grid, block, 0, st>>>(k_codes, v, dst, H, Nk, W, p.wb, p.ph, p.splits, p.tokens_per_block)
-    switch (dv) {
-        case 32: if (zero_one) SA_KTV(32, true); else SA_KTV(32, false); break;
-        case 64: if (zero_one) SA_KTV(64, true); else SA_KTV(64, false); break;
-        default: if (zero_one) SA_KTV(128, true); else SA_KTV(128, false); break;
+    const dim3 grid((unsigned)blocks), block(kKtvWaves * 64);
+    // Many short sequences (workgroups for more than two rounds): one word per wavefront and a short ring, so that two
+    // workgroups share a CU and one loads or sums while the other multiplies (64 x 12 heads x 197 tokens x 128 bits).
+    const bool many = blocks > 512;
+#define SA_KTV(DVC_, WB_, PH_, RING_)                                                                                          \
+    if (zero_one) ktv_mfma_kernel<DVC_, WB_, PH_, RING_, true><<<grid, block, 0, st>>>(                                                 \
+        k_codes, v, dst, ksum, H, Nk, W, dv, p.splits, p.tokens_per_block);                                                    \
+    else ktv_mfma_kernel<DVC_, WB_, PH_, RING_, false><<<grid, block, 0, st>>>(                                                  \
+        k_codes, v, dst, ksum, H, Nk, W, dv, p.splits, p.tokens_per_block);
+#define SA_KTV_DV(DVC_)                       \
+    if (W == 1 && many) { SA_KTV(DVC_, 1, 8, 2) }       \
+    else if (W == 1) { SA_KTV(DVC_, 1, 8, 4) }          \
+    else if (W == 2 && many) { SA_KTV(DVC_, 1, 4, 2) }  \
+    else if (W == 2) { SA_KTV(DVC_, 2, 8, 4) }          \
+    else { SA_KTV(DVC_, 2, 4, 4) }
+    if (dv == 32) {
+        SA_KTV_DV(32)
+    } else {
+        SA_KTV_DV(64)
     }
+#undef SA_KTV_DV
 #undef SA_KTV
     return check_launch("sa_additive_attention(K^T V)");
 }
 
-int launch_qkv_mfma(const uint64_t *q_codes, const float *kv, float *out, int B, int H, int Nq, int nbits, int dv,
-                    float scale, bool zero_one, const int32_t *den, float eps, hipStream_t st) {
-    const long BH = (long)B * H;
-    const int W = nbits / 64;
-    bool ok;
-    switch (dv) {
-        case 32: ok = launch_qkv_dv<32>(W, q_codes, kv, out, BH, H, Nq, scale, zero_one, den, eps, st); break;
-        case 64: ok = launch_qkv_dv<64>(W, q_codes, kv, out, BH, H, Nq, scale, zero_one, den, eps, st); break;
-        default: ok = launch_qkv_dv<128>(W, q_codes, kv, out, BH, H, Nq, scale, zero_one, den, eps, st); break;
+// K^T V partials that Q(K^T V) sums while it stages them: what a workgroup then reads stays within 128 KiB.
+bool additive_mfma_sums_partials(int splits, int nbits, int dv) { return splits > 1 && (size_t)splits * nbits * dv * 4 <= 128 * 1024; }
+
+int launch_ktv_sum(const float *part, float *kv, const int32_t *ksum_part, int32_t *ksum, long BH, int nbits, int dv, int splits,
+                   hipStream_t st) {
+    const long n4 = BH * nbits * dv / 4, k4 = ksum_part ? BH * nbits / 4 : 0;
+    int G = 1;                                    // up to 16 threads per 16 bytes, until the chip has enough of them
+    if (!additive_mfma_sums_partials(splits, nbits, dv))          // (the same plain sum whether or not Q(K^T V) takes it over)
+        while (G < 16 && 4 * G <= splits && n4 * G < (1L << 17)) G *= 2;
+    const long per = 256 / G;
+    const long kv_blocks = (n4 + per - 1) / per, blocks = kv_blocks + (k4 + per - 1) / per;
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
+#define SA_SUM(G_)                                                                                                              \
+    ktv_sum_kernel<G_><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(reinterpret_cast<const f32x4 *>(part),                     \
+        reinterpret_cast<f32x4 *>(kv), n4, splits, (unsigned)kv_blocks, reinterpret_cast<const i32x4 *>(ksum_part),             \
+        reinterpret_cast<i32x4 *>(ksum), k4)
+    switch (G) {
+        case 1: SA_SUM(1); break;
+        case 2: SA_SUM(2); break;
+        case 4: SA_SUM(4); break;
+        case 8: SA_SUM(8); break;
+        default: SA_SUM(16); break;
     }
-    SA_REQUIRE(ok, SA_ERR_UNSUPPORTED, "sa_additive_attention: unsupported code width for the matrix-core path");
+#undef SA_SUM
+    return check_launch("sa_additive_attention(sum of the partials)");
+}
+
+int launch_qkv_mfma(const uint64_t *q_codes, const AddFused &f, int B, int H, int Nq, int nbits, int dv, bool zero_one,
+                    hipStream_t st) {
+    const long BH = (long)B * H;
+    SA_REQUIRE(BH * (dv / 32) * (((long)Nq + 255) / 256) < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
+    switch (nbits) {
+        case 64: launch_qkv_w<1>(q_codes, f, BH, H, Nq, dv, zero_one, st); break;
+        case 128: launch_qkv_w<2>(q_codes, f, BH, H, Nq, dv, zero_one, st); break;
+        case 256: launch_qkv_w<4>(q_codes, f, BH, H, Nq, dv, zero_one, st); break;
+        default: return fail(SA_ERR_UNSUPPORTED, "sa_additive_attention: unsupported code width for the matrix-core path");
+    }
     return check_launch("sa_additive_attention(Q(K^T V))");
 }
 

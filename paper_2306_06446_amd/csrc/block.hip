@@ -101,14 +101,15 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     if (rc != SA_OK) return rc;
     // The attention output leaves in three forms: fp32 (the block's output o), the int8 codes the
     // Shift layers read, and (with a Mult expert) the fp16 rounding its first layer reads.  The
-    // Hamming kernel writes all three from its accumulators; the linear path adds one pass over o.
+    // kernel that computes it writes all three from its accumulators.
     int8_t *xq = reinterpret_cast<int8_t *>(ws + L.xq);
     void *xh = moe ? static_cast<void *>(ws + L.xh) : nullptr;
     const bool mlp = d->hid > 0;
     if (d->attention == 0) {
-        rc = sa_additive_attention(qc, kc, d->v, d->o, d->B, d->H, d->N, d->N, d->nbits, d->dv, d->attn_scale,
-                                   reinterpret_cast<float *>(ws + L.kv), 3, ws + L.attn_ws, L.attn_ws_bytes, stream);
-        if (rc == SA_OK && mlp) rc = sa_quantize_act_half(d->o, T * E, d->act_inv_scale, xq, xh, stream);
+        rc = sa::additive_attention_fused(qc, kc, d->v, d->o, true, d->B, d->H, d->N, d->nbits, d->dv, d->attn_scale,
+                                          reinterpret_cast<float *>(ws + L.kv), mlp ? xq : nullptr,
+                                          static_cast<_Float16 *>(xh), d->act_inv_scale, ws + L.attn_ws, L.attn_ws_bytes,
+                                          stream);
     } else {
         rc = sa_hamming_attention_fused(qc, kc, d->v, d->o, d->B, d->H, d->N, d->N, d->nbits, d->dv, d->attn_scale,
                                          nullptr, mlp ? xq : nullptr, xh, d->act_inv_scale, SA_VARIANT_AUTO, stream);
@@ -245,11 +246,11 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
         if (rc != SA_OK) return rc;
     }
     if (d->attention == 0) {
-        rc = sa_additive_attention(qc, kc, v, o, d->B, d->H, d->N, d->N, d->nbits, dv, d->attn_scale,
-                                   reinterpret_cast<float *>(ws + L.kv), 3, ws + L.attn_ws, L.attn_ws_bytes, stream);
-        if (rc == SA_OK) rc = sa_quantize_act(o, T * E, d->act_inv_scale, codes8, stream);
-    } else {
         // only the int8 form of the attention output is read (by the output projection): no fp32 write
+        rc = sa::additive_attention_fused(qc, kc, v, o, false, d->B, d->H, d->N, d->nbits, dv, d->attn_scale,
+                                          reinterpret_cast<float *>(ws + L.kv), codes8, nullptr, d->act_inv_scale,
+                                          ws + L.attn_ws, L.attn_ws_bytes, stream);
+    } else {
         rc = sa_hamming_attention_fused(qc, kc, v, nullptr, d->B, d->H, d->N, d->N, d->nbits, dv, d->attn_scale, nullptr,
                                          codes8, nullptr, d->act_inv_scale, SA_VARIANT_AUTO, stream);
     }

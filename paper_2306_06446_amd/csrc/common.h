@@ -48,6 +48,46 @@ __device__ inline void resolve_rows(const RowSel &sel, const int32_t *&rows, lon
 
 int validate_rows(const sa_rows *rows, RowSel *out);
 
+// One wavefront-wide direct global -> LDS load, no registers and nothing for the compiler to wait for: lane l's 16 (4)
+// bytes at `src` land at LDS byte lds_base + 16 (4) * l (lds_base is the same in every lane).
+__device__ inline void direct_load_16(const void *src, uint32_t lds_base) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, off\n\t"
+        :
+        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src)
+        : "memory");
+}
+// The same with the address as a wavefront-uniform base and a 32-bit offset per lane (no vector address arithmetic).
+__device__ inline void direct_load_16(const void *base, uint32_t lane_off, uint32_t lds_base) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %2\n\t"
+        :
+        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(lane_off), "s"(base)
+        : "memory");
+}
+__device__ inline void direct_load_4(const void *base, uint32_t lane_off, uint32_t lds_base) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dword %1, %2\n\t"
+        :
+        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(lane_off), "s"(base)
+        : "memory");
+}
+__device__ inline void direct_load_4(const void *src, uint32_t lds_base) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dword %1, off\n\t"
+        :
+        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src)
+        : "memory");
+}
+
 // One Linear layer on the rows an expert was given, gated and scattered (the two experts of sa_moe_linear):
 //   y[rows[i], :] = gate[rows[i]] * (xh[rows[i], :] . W^T)                      fp16 operands   (mult_mlp.hip)
 //   y[rows[i], :] = gate[rows[i]] * out_scale * (xq[rows[i], :] . Wshift^T)      int8 / 4-bit    (shift_linear.hip)
@@ -70,19 +110,41 @@ int launch_binarize_mfma(const float *x0, const float *x1_or_null, const float *
 // Additive attention on the matrix cores (additive_mfma.hip).
 struct AdditiveMfmaPlan {
     int groups;             // groups of up to 4 code words
-    int wb, ph;             // words per workgroup, token phases per word
     int splits;             // token ranges (partial K^T V each)
     int tokens_per_block;
 };
+// What Q(K^T V) reads and leaves.  kv_in: [splits][B*H][nbits][dv] partials of K^T V, summed in ascending order (splits
+// = 1: K^T V itself); kv_out (or null): the sum.  ksum_in / ksum_out: the same for the bit counts of {0,1} codes, int32
+// [splits][B*H][nbits].  Rows leave as scale * acc, or acc / (normaliser + eps) with {0,1} codes, in any of three forms:
+// fp32, the int8 codes of the activation quantiser, fp16.
+struct AddFused {
+    const float *kv_in = nullptr;
+    float *kv_out = nullptr;
+    const int32_t *ksum_in = nullptr;
+    int32_t *ksum_out = nullptr;
+    int splits = 1;
+    float scale = 1.0f, eps = 0.0f;
+    float *out = nullptr;
+    int8_t *xq = nullptr;
+    _Float16 *xh = nullptr;
+    float act_inv_scale = 0.0f;
+};
 bool additive_mfma_ktv_supported(int nbits, int dv);
 bool additive_mfma_qkv_supported(int nbits, int dv);
-AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits);
-// zero_one: a clear code bit stands for 0 instead of -1; den (with zero_one): int32 [B*H, Nq] row normaliser, the
-// output row is then acc / (den + eps) instead of scale * acc.
-int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int B, int H, int Nk, int nbits, int dv,
+bool additive_mfma_sums_partials(int splits, int nbits, int dv);
+AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv);
+// zero_one: a clear code bit stands for 0 instead of -1, and the bit counts of the range are left in ksum.
+int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int32_t *ksum, int B, int H, int Nk, int nbits, int dv,
                     const AdditiveMfmaPlan &p, bool zero_one, hipStream_t st);
-int launch_qkv_mfma(const uint64_t *q_codes, const float *kv, float *out, int B, int H, int Nq, int nbits, int dv,
-                    float scale, bool zero_one, const int32_t *den, float eps, hipStream_t st);
+int launch_ktv_sum(const float *part, float *kv, const int32_t *ksum_part, int32_t *ksum, long BH, int nbits, int dv, int splits,
+                   hipStream_t st);
+int launch_qkv_mfma(const uint64_t *q_codes, const AddFused &f, int B, int H, int Nq, int nbits, int dv, bool zero_one,
+                    hipStream_t st);
+// sa_additive_attention (both phases) whose output also leaves as the int8 codes (and fp16 rounding) the MLP reads, from
+// the kernel that computes it.  `out` is always a valid buffer; want_out = false: nothing but those forms is read.
+int additive_attention_fused(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, float *out, bool want_out,
+                             int B, int H, int N, int nbits, int dv, float scale, float *kv, int8_t *xq, _Float16 *xh,
+                             float act_inv_scale, void *workspace, size_t workspace_bytes, void *stream);
 
 }  // namespace sa
 

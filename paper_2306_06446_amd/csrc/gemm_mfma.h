@@ -87,18 +87,6 @@ __device__ inline int swizzle(int r, int c) {
     return c ^ ((r / (16 / CPR)) & (CPR - 1));
 }
 
-// One wavefront-wide direct load: lane l's 16 bytes at `src` land at LDS byte lds_base + 16 * l
-// (lds_base is the same in every lane).
-__device__ inline void load_to_lds_16(const void *src, uint32_t lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, off\n\t"
-        :
-        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src)
-        : "memory");
-}
-
 // A Store type says how accumulators become output rows:
 //   static constexpr int  kBytes      : bytes per output element (1, 2 or 4)
 //   static constexpr int  kTableBytes : 0, or 256 for a byte table that is copied into LDS
@@ -255,10 +243,10 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
     auto issue_load = [&](int q, int buf, int kbyte) {
         const uint32_t base = lds_base + buf * STAGE;
         if (q < A_INSTR) {
-            load_to_lds_16(a_src[q] + (SB == 64 ? min(kbyte, a_klim) : kbyte), base + (wave * A_INSTR + q) * 1024);
+            direct_load_16(a_src[q] + (SB == 64 ? min(kbyte, a_klim) : kbyte), base + (wave * A_INSTR + q) * 1024);
         } else {
             const int p = (q - A_INSTR) / B_INSTR, i = (q - A_INSTR) % B_INSTR;
-            load_to_lds_16(b_src[p][i] + kbyte, base + A_BYTES + p * B_BYTES + (wave * B_INSTR + i) * 1024);
+            direct_load_16(b_src[p][i] + kbyte, base + A_BYTES + p * B_BYTES + (wave * B_INSTR + i) * 1024);
         }
     };
     auto issue_stage = [&](int buf, int kbyte) {

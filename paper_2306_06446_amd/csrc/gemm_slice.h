@@ -97,12 +97,12 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
         const uint32_t base = lds_base + slot_ * S::STAGE;
 #pragma unroll
         for (int i = 0; i < A_INSTR; ++i)
-            load_to_lds_16(a_src[i] + (SB == 64 ? min(kbyte, a_klim) : kbyte), base + ((wave * A_INSTR + i) % A_TOT) * 1024);
+            direct_load_16(a_src[i] + (SB == 64 ? min(kbyte, a_klim) : kbyte), base + ((wave * A_INSTR + i) % A_TOT) * 1024);
 #pragma unroll
         for (int p = 0; p < S::NP; ++p)
 #pragma unroll
             for (int i = 0; i < B_INSTR; ++i)
-                load_to_lds_16(b_src[p][i] + kbyte, base + S::A_BYTES + p * S::B_BYTES + ((wave * B_INSTR + i) % B_TOT) * 1024);
+                direct_load_16(b_src[p][i] + kbyte, base + S::A_BYTES + p * S::B_BYTES + ((wave * B_INSTR + i) % B_TOT) * 1024);
     };
 
     typename T::Acc acc[MI][S::NJW];

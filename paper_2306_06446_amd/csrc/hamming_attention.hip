@@ -356,27 +356,6 @@ __global__ __launch_bounds__(kMaxWaves *kWave) void hamming_mfma_kernel(
 // chunk switch.  The output stores of a unit drain while the next unit is computed.  Same arithmetic, same
 // order, bit-identical results.  Row reference distances (ROWREF in the kernel above) need all key codes of a
 // unit before its first step and keep the kernel above.
-//
-// One wavefront-wide direct load: lane l's 16 (4) bytes at `src` land at LDS byte lds_base + 16 (4) * l.
-__device__ inline void async_load_16(const void *src, uint32_t lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, off\n\t"
-        :
-        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src)
-        : "memory");
-}
-__device__ inline void async_load_4(const void *src, uint32_t lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dword %1, off\n\t"
-        :
-        : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src)
-        : "memory");
-}
-
 template <int DV, int W>
 __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
     const uint64_t *__restrict__ q_codes, const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
@@ -411,13 +390,13 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
         for (int k = wave; k < v_instr; k += n_waves) {
             const int key = min(k * RPI + lane / L4, n - 1);
             const float *src = v + (((size_t)b * Nk + j + key) * H + h) * DV + (lane % L4) * 4;
-            async_load_16(src, raw_base + k * 1024);
+            sa::direct_load_16(src, raw_base + k * 1024);
         }
         const int code_bytes = n * W * 8, code_instr = (n_pad * W * 8 + 255) / 256;
         const char *cg = reinterpret_cast<const char *>(k_codes + ((size_t)bh * Nk + j) * W);
         for (int k = wave; k < code_instr; k += n_waves) {
             const int off = min(k * 256 + lane * 4, code_bytes - 4);
-            async_load_4(cg + off, kc_base + buf * (kKeyChunk * W * 8) + k * 256);
+            sa::direct_load_4(cg + off, kc_base + buf * (kKeyChunk * W * 8) + k * 256);
         }
     };
     auto load_query = [&](long u, uint64_t (&dst)[W]) {

@@ -1,0 +1,55 @@
+"""The matrix-core Add kernels where their splitting of the work changes or can go wrong: fewer tokens than one step, ragged
+steps, code words that do not pair up, many short sequences, partials summed by Q(K^T V) or by a kernel of their own."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def codes(g, *shape):
+    return torch.randint(-2**63, 2**63 - 1, shape, generator=g, device="cuda", dtype=torch.int64)
+
+
+def bits_of(c):
+    """int64 code words [..., W] -> float64 {0, 1} [..., 64 W]."""
+    j = torch.arange(64, device=c.device)
+    return ((c.unsqueeze(-1) >> j) & 1).flatten(-2).double()
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,W,dv", [
+    (1, 1, 1, 1, 1, 32), (1, 2, 33, 15, 1, 64), (2, 1, 31, 17, 2, 32), (1, 3, 64, 129, 2, 64),      # below and around one step
+    (1, 2, 40, 300, 3, 64), (1, 1, 20, 500, 5, 32), (1, 2, 70, 257, 6, 128),                        # words that do not pair up
+    (2, 2, 300, 4097, 4, 64), (1, 1, 513, 9000, 4, 128), (3, 1, 95, 2000, 4, 32),                   # many partials
+    (40, 13, 50, 49, 1, 32), (30, 18, 37, 197, 2, 64), (44, 12, 33, 20, 1, 64),                     # many short sequences
+    (8, 4, 8192, 300, 1, 64),                                                                       # 32-tile passes of Q(K^T V)
+])
+def test_both_code_modes_against_fp64(sa, B, H, Nq, Nk, W, dv):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Nq * Nk + W)
+    q, k = codes(g, B, H, Nq, W), codes(g, B, H, Nk, W)
+    v = torch.randn((B, Nk, H, dv), generator=g, device="cuda")
+    nbits, vt = 64 * W, v.double().permute(0, 2, 1, 3).contiguous()
+    kb, qb = bits_of(k), bits_of(q)
+    for zero_one in (False, True):
+        ks, qs = (kb, qb) if zero_one else (2 * kb - 1, 2 * qb - 1)
+        kv_ref = torch.matmul(ks.transpose(-1, -2).contiguous(), vt)
+        ref = torch.matmul(qs, kv_ref)
+        if zero_one:
+            ksum_ref = kb.sum(2)
+            ref = ref / (torch.matmul(qb, ksum_ref.unsqueeze(-1)) + 1e-6)
+            out, kv, ksum = sa.sa_linear_attention_01(q, k, v, 1e-6, nbits)
+            assert torch.equal(ksum.long(), ksum_ref.long())
+            parts = sa.sa_linear_attention_01(None, k, v, 1e-6, nbits, phases=1)
+            again = sa.sa_linear_attention_01(q, None, None, 1e-6, nbits, phases=2, kv=parts[1], ksum=parts[2])
+            assert torch.equal(parts[2], ksum)
+        else:
+            scale = 1.0 / (Nk * nbits) ** 0.5
+            ref = ref * scale
+            out, kv = sa.sa_additive_attention(q, k, v, scale, nbits)
+            parts = sa.sa_additive_attention(None, k, v, scale, nbits, phases=1)
+            again = sa.sa_additive_attention(q, None, None, scale, nbits, phases=2, kv=parts[1])
+        assert torch.equal(parts[1], kv) and torch.equal(again[0], out)        # one call or two: the same sums
+        ref = ref.permute(0, 2, 1, 3)
+        err_kv, err = (kv.double() - kv_ref).abs(), (out.double() - ref).abs()
+        assert bool((err_kv <= 1e-4 * kv_ref.abs() + 1e-5 * max(1.0, float(kv_ref.square().mean().sqrt()))).all())
+        assert bool((err <= 1e-4 * ref.abs() + 1e-5).all()), float(err.max())
