@@ -2,356 +2,402 @@
 //
 // The code bit is DEFINED as the sign of the fp32 chain acc = fma(x_k, r_kj, acc), k ascending.
 // For almost every (row, bit) that sign is decided long before rounding matters, so the kernel
-//   1. computes z~ = x . r^_j on the bf16 matrix cores, r^_j = r_j / |r_j|, with a three-product
-//      split (x = xh + xl, r^ = rh + rl, z~ = xh rh + xh rl + xl rh: ~2^-15 relative accuracy),
-//   2. keeps sign(z~) wherever |z~| > 2^-13 * |x| (|x| |r^_j| is the Cauchy-Schwarz bound of
-//      sum |x_k r^_kj|; the split drops at most 3 * 2^-18 of that sum, the fp32 accumulation of the
-//      pre-pass and of the defining chain at most (d + 2) * 2^-24 of it each: 2^-15.4 |x| together
-//      at d = 64, so the margin is a factor of five over the worst case), and
-//   3. re-runs the defining chain, one (row, bit) per lane, for the rest (about 0.08 % of the bits
-//      on Gaussian data at d = 64; every bit if the data is degenerate) and flips the stored bit if
-//      needed.  These re-runs are the expensive part (80 uncoalesced loads per bit): a quarter of
-//      the kernel's time at a margin of 2^-12, hence the tighter one.
+//   1. computes z~ = x . r^_j on the fp16 matrix cores, r^_j = r_j / |r_j|, with a three-product split
+//      (x = xh + xl, r^ = rh + rl, each fp16 rounded to nearest; z~ = xh rh + xh rl + xl rh),
+//   2. keeps sign(z~) wherever |z~| > theta |x|.  theta covers, against |x| |r^_j| = |x| (Cauchy-Schwarz bound of
+//      sum |x_k r^_kj|): the dropped xl rl and the roundings of xl and rl, 3 * 2^-22; the fp32 accumulation of the 3 d
+//      products, 3 d * 2^-23 even if every addition truncates; that of the defining chain, (d + 2) * 2^-24.  Together
+//      2.8e-5 at d = 64: theta = 2^-15 (2^-16 at d = 32, 2^-14 at d = 128), and
+//   3. re-runs the defining chain, one (row, bit) per lane, for the rest (0.02 % of the bits on Gaussian data at
+//      d = 64; every bit if the data is degenerate) and flips the stored bit if needed.
 // NaN / Inf / denormal-range sums fail the test in step 2 and take step 3, which is the definition.
 //
-// Tiles are 32 consecutive rows of the flattened [B*N*H, d] input (one contiguous 32*d*4-byte
-// read).  The MFMA computes the TRANSPOSED tile (hash bits down, rows across), so that a lane ends
-// up with 16 bits of one row per 32-bit group: signs are packed with two integer operations per
-// bit, the margin test is one multiply and one compare per bit against a per-lane threshold, and
-// the two half-wavefronts exchange their halves with one shuffle per group.  The hash matrix
-// lives in LDS as ready-made bf16 MFMA fragments; wavefronts stride over the tiles and park their
-// unsettled bits in LDS lists that one wavefront per workgroup works off at the end.
+// A wavefront takes tiles of 32 consecutive rows of the flattened [B*N*H, d] input as two units of 16.  The MFMA
+// (16x16x32) computes the TRANSPOSED tile, hash columns down and rows across; the columns are dealt to its rows so that a
+// lane ends up with a quarter of the code bits of one row, consecutive ones, and its k to the steps so that a lane loads
+// 16-byte pieces which are 64 contiguous bytes per row and instruction.  The hash matrix lives in LDS, as ready-made
+// fragments and as fp32 columns for step 3; the rows of the next tile are in flight while a tile is multiplied.
+//
+// What bounds it: at 256 bits the products and the vector work in their shadow (16 funnel shifts and 8 three-way minima
+// per 16 bits, 7 operations to split two elements); at 128 bits and fewer the rows of Q and K, with 5.6 us before the
+// first product (3.5 of them the launch; 1.6 when the hash matrix has arrived) and 1 us of re-runs at the end.  More
+// wavefronts or rows in flight gave nothing there.  The kernel before split into bf16 terms, tested against 2^-13 |x|
+// (four times the re-runs, each with 64 uncoalesced loads of its hash column) and spread and merged the bits of a row
+// between two lanes.  Q and K, before -> now: 8 x 16384 x 4 heads x 64 -> 256 bits 143 -> 116 us, 1 x 16384 x 4 the
+// same 24.3 -> 22.8, 64 x 197 x 12 x 64 -> 128 bits 28.7 -> 28.3.
 #include "common.h"
 
 namespace sa {
 
 namespace {
 
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kListCap = 192;                 // unsettled bits parked per wavefront
-constexpr float kKeepFactor = 1.565e-8f;      // (2^-13)^2 * 1.05: keep = sqrt(kKeepFactor * |x|^2)
-constexpr float kKeepFloor = 1e-37f;          // keep >= ~3e-19: below that the relative error model does not hold
+constexpr int kListCap = 128;                 // unsettled bits parked per wavefront
+constexpr float kKeepFloor = 3.2e-19f;        // |z| below that: products and sums of the chain may be denormal
+constexpr float kColumnScale = 1024.0f;       // |r^_j| as staged: its lower terms are then normal fp16 numbers
+
+template <int D>
+constexpr float theta() { return D == 32 ? 0x1p-16f : (D == 64 ? 0x1p-15f : 0x1p-14f); }
+
+// n / d for 0 <= n < 2^31 as one multiplication and one shift.
+struct FastDiv {
+    uint32_t mul;
+    int shift;
+    explicit FastDiv(uint32_t d) {
+        int s = 0;
+        while ((1ull << s) < d) ++s;
+        shift = 31 + s;
+        mul = (uint32_t)(((1ull << shift) + d - 1) / d);
+    }
+    __device__ inline uint32_t operator()(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
 
 struct RowMap {
+    FastDiv by_h, by_n;
     int N, H, W;
-    __device__ inline size_t word_index(long row, int col) const {
-        const long nh = (long)N * H;
-        const long b = row / nh, rem = row - b * nh;
-        const long n = rem / H, h = rem - n * H;
-        return (((size_t)b * H + h) * N + n) * W + (col >> 6);
+    __device__ inline size_t row_words(uint32_t row) const {     // first code word of a row of the flattened input
+        const uint32_t t = by_h(row), h = row - t * (uint32_t)H, b = by_n(t), n = t - b * (uint32_t)N;
+        return ((size_t)(b * (uint32_t)H + h) * N + n) * W;
     }
 };
 
-__device__ inline void split_bf16(float f, __bf16 &hi, __bf16 &lo) {
-    hi = (__bf16)f;
-    lo = (__bf16)(f - (float)hi);
-}
-
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
-// The same split for a pair (a in the lower half of each dword, b in the upper): one packed conversion per term.
-__device__ inline void split_bf16_pair(float a, float b, uint32_t &upper, uint32_t &lower) {
-    v2f r = {a, b};
-    upper = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
-    r[0] -= __builtin_bit_cast(float, upper << 16);
-    r[1] -= __builtin_bit_cast(float, upper & 0xFFFF0000u);
-    lower = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
-}
-
-// Re-runs the defining chain for one parked (row, bit) entry and flips the stored bit where the
-// pre-pass had it wrong.
 // Up to two tensors of the same shape are hashed by one launch (Q and K of a block).
 struct Tensors {
     const float *x0, *x1;
     uint64_t *codes0, *codes1;
 };
 
-// RND steps of the chain per round trip of loads.
-template <int D, int RND>
-__device__ inline void settle_entry(uint64_t e, const Tensors &ts, const float *__restrict__ proj, const RowMap &map,
-                                    int nbits) {
-    const long row = (long)(e & 0xffffffffu);
+// (a, b) as fp16 terms, a in the lower half: upper terms, and what they leave.
+__device__ inline void split_f16_pair(float a, float b, uint32_t &upper, uint32_t &lower) {
+    const v2f x = {a, b};
+    const v2h h = __builtin_convertvector(x, v2h);
+    const v2f r = {a - (float)h[0], b - (float)h[1]};
+    upper = __builtin_bit_cast(uint32_t, h);
+    lower = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2h));
+}
+
+// Re-runs the defining chain for one parked (row, bit) entry and flips the stored bit where the pre-pass had it
+// wrong.  r_s: the hash columns of this workgroup, fp32 [D][C].  RND steps of the chain per round trip of loads.
+template <int D, int C, int RND>
+__device__ inline void settle_entry(uint64_t e, const Tensors &ts, const float *r_s, int c_first, const RowMap &map) {
+    const uint32_t row = (uint32_t)e;
     const int col = (int)((e >> 32) & 0xffffu);
     const bool prov = (e >> 48) & 1u;
     const bool second = (e >> 49) & 1u;
-    const float *x = second ? ts.x1 : ts.x0;
+    const float *xr = (second ? ts.x1 : ts.x0) + (size_t)row * D;
     uint64_t *codes = second ? ts.codes1 : ts.codes0;
-    const float *xr = x + (size_t)row * D;
-    const float *pc = proj + col;
     float acc = 0.0f;
     // loads first, then the fmas in their defined order
 #pragma unroll 1
     for (int k0 = 0; k0 < D; k0 += RND) {
-        float xv[RND], rv[RND];
+        float xv[RND];
 #pragma unroll
         for (int q = 0; q < RND / 4; ++q) {
             const float4 t4 = *reinterpret_cast<const float4 *>(xr + k0 + 4 * q);
             xv[4 * q] = t4.x; xv[4 * q + 1] = t4.y; xv[4 * q + 2] = t4.z; xv[4 * q + 3] = t4.w;
         }
 #pragma unroll
-        for (int k = 0; k < RND; ++k) rv[k] = pc[(size_t)(k0 + k) * nbits];
-#pragma unroll
-        for (int k = 0; k < RND; ++k) acc = __builtin_fmaf(xv[k], rv[k], acc);
+        for (int k = 0; k < RND; ++k) acc = __builtin_fmaf(xv[k], r_s[(k0 + k) * C + col - c_first], acc);
     }
     const bool exact = acc >= 0.0f;
     if (exact != prov)
-        atomicXor(reinterpret_cast<unsigned long long *>(codes + map.word_index(row, col)), 1ull << (col & 63));
+        atomicXor(reinterpret_cast<unsigned long long *>(codes + map.row_words(row) + (col >> 6)), 1ull << (col & 63));
 }
 
-// One wavefront's list, worked off 64 entries at a time.  Kept out of line: inside the tile loop it is
-// the rare path (degenerate data) and must not cost the loop its registers.
-template <int D>
-__device__ __attribute__((noinline)) void work_off_list(const uint64_t *list, int cnt, Tensors ts,
-                                                        const float *__restrict__ proj, RowMap map, int nbits) {
-    const int lane = threadIdx.x & 63;
-    __builtin_amdgcn_s_waitcnt(0x0F70);      // the words these bits live in have been stored
-    for (int t0 = 0; t0 < cnt; t0 += 64)
-        if (t0 + lane < cnt) settle_entry<D, 32>(list[t0 + lane], ts, proj, map, nbits);
-}
-
-// D: head dim; G: hash columns handled by one workgroup (blockIdx.y selects the group).
-template <int D, int G, int CG>
-__global__ __launch_bounds__(256, 2) void binarize_mfma_kernel(Tensors ts, const float *__restrict__ proj, long rows,
-                                                               RowMap map, int nbits, long n_tiles, long n_total) {
-    constexpr int S = D / 16;      // MFMA steps along k
-    constexpr int JT = G / 32;     // 32-bit groups of hash columns
-    constexpr int HALF = D / 2;    // k values one lane owns (the other half-wavefront owns the rest)
-    constexpr int FRAGS = S * JT * 2 * 64;      // fragments of one group of G columns
-    __shared__ __attribute__((aligned(16))) uint4 bfr_s[CG * FRAGS];
-    __shared__ uint64_t list_s[4][kListCap];
-    __shared__ int cnt_s[4];
+// D: head dim; C: hash columns of a workgroup (blockIdx.y selects the group); kWaves: its wavefronts.
+template <int D, int C, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, const float *__restrict__ proj, uint32_t rows,
+                                                                    RowMap map, int nbits, uint32_t n_tiles, uint32_t n_total) {
+    constexpr int S = D / 32;                     // MFMA steps along k
+    constexpr int T = C / 16;                     // 16-column tiles
+    constexpr int GROUPS = T / 4;                 // of four tiles: 16 bits of a lane
+    constexpr int L4 = D / 16;                    // 16-byte loads per lane and unit
+    constexpr int THREADS = kWaves * 64;
+    constexpr int BYTES = C / 32;                 // code bytes of a lane: columns (C / 4) g .. of its row
+    __shared__ __attribute__((aligned(16))) uint4 frag_s[T * S * 2 * 64];       // [tile][step][upper, lower][lane]
+    __shared__ __attribute__((aligned(16))) float r_s[D * C];
+    constexpr int TPC = THREADS / C;              // threads that share a column's norm
+    __shared__ float n2_s[TPC][C];
+    __shared__ uint64_t list_s[kWaves][kListCap];
+    __shared__ int cnt_s[kWaves];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i_loc = lane & 31, g = lane >> 5;
-    const int c_first = blockIdx.y * (G * CG);  // this workgroup hashes CG groups of G columns from here
+    const int n = lane & 15, g = lane >> 4;
+    const int c_first = blockIdx.y * C;
 
-    // ---- hash matrix -> normalised bf16 fragments in LDS: fragment (s, jt, hi/lo), lane L holds
-    //      r^[k = (L/32)*HALF + s*8 + e][c0 + jt*32 + L%32], e = 0..7.
-    //      Thread (column c = tid % G, slice q = tid / G) loads the D / TPC consecutive k of its column
-    //      (coalesced across c), which are exactly the elements of STEPS whole fragments.
-    constexpr int TPC = 256 / G;           // threads per column
-    constexpr int KPT = D / TPC;           // k values per thread
-    constexpr int STEPS = KPT / 8;         // fragments (per hi / lo) per thread
-    static_assert(KPT % 8 == 0 && HALF % KPT == 0, "a thread's k slice must lie inside one half");
-    __shared__ float cn2_s[TPC][G];
-#pragma unroll 1
-    for (int cg = 0; cg < CG; ++cg) {
-        const int c0 = c_first + cg * G;
-        const int c = tid % G, qs = tid / G;
-        const int k_first = qs * KPT;
-        const int fg = k_first / HALF, s_first = (k_first % HALF) / 8;
-        const int jt = c / 32, L = fg * 32 + (c & 31);
-        float rv[KPT];
+    // rows 16 u + n of a tile: lane group g loads k = 16 j + 4 g .. + 3, j = 0 .. L4 - 1.  Tiles 0 .. n_tiles - 1 belong
+    // to the first tensor, the next n_tiles to the second; rows past the end re-read the last one.
+    float4 xn[2][L4];
+    auto load_tile = [&](uint32_t tile) {
+        const bool second = tile >= n_tiles;
+        const float *x = second ? ts.x1 : ts.x0;
+        const uint32_t r0 = (second ? tile - n_tiles : tile) * 32;
 #pragma unroll
-        for (int k = 0; k < KPT; ++k) rv[k] = proj[(size_t)(k_first + k) * nbits + c0 + c];
-        float s2 = 0.0f;
+        for (int u = 0; u < 2; ++u) {
+            const float *xr = x + (size_t)min(r0 + 16 * u + n, rows - 1) * D + 4 * g;
 #pragma unroll
-        for (int k = 0; k < KPT; ++k) s2 += rv[k] * rv[k];
-        __syncthreads();                         // the previous group's sums have been read
-        cn2_s[qs][c] = s2;
-        __syncthreads();
+            for (int j = 0; j < L4; ++j) xn[u][j] = *reinterpret_cast<const float4 *>(xr + 16 * j);
+        }
+    };
+    const uint32_t tile_step = gridDim.x * kWaves;
+    uint32_t tile = blockIdx.x * kWaves + wave;
+    if (tile < n_total) load_tile(tile);
+
+    // ---- hash matrix: fp32 columns, their norms, then the fragments of the normalised columns
+    for (int i = tid; i < D * C / 4; i += THREADS) {
+        const int k = i / (C / 4), c4 = i % (C / 4);
+        reinterpret_cast<float4 *>(r_s)[i] = *reinterpret_cast<const float4 *>(proj + (size_t)k * nbits + c_first + 4 * c4);
+    }
+    __syncthreads();
+    {
+        float n2 = 0.0f;                                           // this thread's share of the norm of column tid % C
+        const int c = tid % C, k0 = tid / C * (D / TPC);
+#pragma unroll 8
+        for (int k = k0; k < k0 + D / TPC; ++k) n2 = __builtin_fmaf(r_s[k * C + c], r_s[k * C + c], n2);
+        n2_s[tid / C][c] = n2;
+    }
+    __syncthreads();
+    for (int i = tid; i < C * S * 4; i += THREADS) {               // task: eight k of one column
+        const int c = i % C, s = i / C % S, kq = i / (C * S);
+        const int q = c / (C / 4), w = c % (C / 4);               // lane group of the accumulator, bit within it
+        const int t = w / 4, rho = 4 * q + w % 4;                 // tile and its row
         float n2 = 0.0f;
 #pragma unroll
-        for (int t = 0; t < TPC; ++t) n2 += cn2_s[t][c];
+        for (int p = 0; p < TPC; ++p) n2 += n2_s[p][c];
         // a dead, overflowing or non-finite column gets an all-zero r^: z~ = 0 fails the margin test, so
         // every bit of that column is parked and settled by the defining chain
-        const float inv_raw = 1.0f / __builtin_sqrtf(n2);
-        const bool usable = inv_raw > 0.0f && inv_raw < __builtin_inff();
-        const float inv = usable ? inv_raw : 0.0f;
+        float inv = 1.0f / __builtin_sqrtf(n2);
+        inv = inv > 0.0f && inv < 3e38f ? inv : 0.0f;
+        uint32_t up[4], lo[4];
 #pragma unroll
-        for (int st = 0; st < STEPS; ++st) {
-            v8bf vh, vl;
+        for (int e2 = 0; e2 < 4; ++e2) {
+            float v[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                __bf16 hi, lo;
-                split_bf16(usable ? rv[st * 8 + e] * inv : 0.0f, hi, lo);
-                vh[e] = hi;
-                vl[e] = lo;
+            for (int h = 0; h < 2; ++h) {
+                const int e = 2 * e2 + h, k = 16 * (2 * s + e / 4) + 4 * kq + e % 4;
+                v[h] = inv > 0.0f ? r_s[k * C + c] * inv * kColumnScale : 0.0f;
             }
-            const int s = s_first + st;
-            bfr_s[cg * FRAGS + ((s * JT + jt) * 2 + 0) * 64 + L] = __builtin_bit_cast(uint4, vh);
-            bfr_s[cg * FRAGS + ((s * JT + jt) * 2 + 1) * 64 + L] = __builtin_bit_cast(uint4, vl);
+            split_f16_pair(v[0], v[1], up[e2], lo[e2]);
         }
+        frag_s[((t * S + s) * 2 + 0) * 64 + kq * 16 + rho] = make_uint4(up[0], up[1], up[2], up[3]);
+        frag_s[((t * S + s) * 2 + 1) * 64 + kq * 16 + rho] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
     __syncthreads();
 
     int cnt = 0;                   // parked entries of this wavefront (wave-uniform)
     uint64_t *list = list_s[wave];
-
-    // the next tile's rows are in flight while the current tile is multiplied and packed
-    // tiles 0 .. n_tiles-1 belong to the first tensor, the next n_tiles to the second
-    auto load_tile = [&](long tile, float (&dst)[HALF]) {
-        const bool second = tile >= n_tiles;
-        const long row_ld = min((second ? tile - n_tiles : tile) * 32 + i_loc, rows - 1);
-        const float *xr = (second ? ts.x1 : ts.x0) + (size_t)row_ld * D + g * HALF;
-#pragma unroll
-        for (int q = 0; q < HALF / 4; ++q) {
-            const float4 t4 = *reinterpret_cast<const float4 *>(xr + 4 * q);
-            dst[4 * q] = t4.x; dst[4 * q + 1] = t4.y; dst[4 * q + 2] = t4.z; dst[4 * q + 3] = t4.w;
-        }
-    };
-    const long tile_step = (long)gridDim.x * 4;
-    float xn[HALF];
-    {
-        const long first = (long)blockIdx.x * 4 + wave;
-        if (first < n_total) load_tile(first, xn);
-    }
-    for (long tile = (long)blockIdx.x * 4 + wave; tile < n_total; tile += tile_step) {
-        const bool second = tile >= n_tiles;
-        const long r0 = (second ? tile - n_tiles : tile) * 32;
-        uint64_t *codes = second ? ts.codes1 : ts.codes0;
-        float xv[HALF];
-#pragma unroll
-        for (int k = 0; k < HALF; ++k) xv[k] = xn[k];
-        if (tile + tile_step < n_total) load_tile(tile + tile_step, xn);
-        float nx2 = 0.0f;
-#pragma unroll
-        for (int k = 0; k < HALF; ++k) nx2 += xv[k] * xv[k];
-        nx2 += __shfl_xor(nx2, 32);                                // |x_row|^2, row = r0 + i_loc
-        // keep sign(z~) where |z~| > keep = 2^-13 |x| (floored); a non-finite |x|^2 keeps nothing
-        const float keep = nx2 < __builtin_inff() ? __builtin_sqrtf(__builtin_fmaxf(kKeepFactor * nx2, kKeepFloor))
-                                                  : __builtin_inff();
-
-        // the two bf16 terms of the row, once for all column groups; two elements per conversion
-        v8bf xh[S], xl[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            uint32_t up[4], lo[4];
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) split_bf16_pair(xv[s * 8 + 2 * e2], xv[s * 8 + 2 * e2 + 1], up[e2], lo[e2]);
-            xh[s] = __builtin_bit_cast(v8bf, make_uint4(up[0], up[1], up[2], up[3]));
-            xl[s] = __builtin_bit_cast(v8bf, make_uint4(lo[0], lo[1], lo[2], lo[3]));
-        }
-        const bool row_ok = (r0 + i_loc) < rows;
-
+    auto work_off = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // the words these bits live in have been stored
 #pragma unroll 1
-        for (int cg = 0; cg < CG; ++cg) {
-        const int c0 = c_first + cg * G;
-        const uint4 *frag = bfr_s + cg * FRAGS;
-        // z~^T: accumulator (jt, r) of lane (i_loc, g) = hash bit jt*32 + 8*(r/4) + 4*g + r%4 of row i_loc
-        v16f acc[JT];
+        for (int t0 = 0; t0 < cnt; t0 += 64)
+            if (t0 + lane < cnt) settle_entry<D, C, 16>(list[t0 + lane], ts, r_s, c_first, map);
+        cnt = 0;
+    };
+
+    for (; tile < n_total; tile += tile_step) {
+        const bool second = tile >= n_tiles;
+        const uint32_t r0 = (second ? tile - n_tiles : tile) * 32;
+        uint8_t *codes = reinterpret_cast<uint8_t *>(second ? ts.codes1 : ts.codes0);
+
+        // |x_row|^2: keep sign(z~) where |z~| > keep (in units of the staged columns); a non-finite |x|^2 keeps nothing
+        float keep[2];
+        v8h xh[2][S], xl[2][S];
+        float nx2[2];
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt)
+        for (int u = 0; u < 2; ++u) {
+            float a = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[jt][r] = 0.0f;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            // all fragments of the step first, then the three products term by term, so that successive
-            // MFMAs go to different accumulators and none waits for the one before it
-            v8bf rh[JT], rl[JT];
-#pragma unroll
-            for (int jt = 0; jt < JT; ++jt) {
-                rh[jt] = __builtin_bit_cast(v8bf, frag[((s * JT + jt) * 2 + 0) * 64 + lane]);
-                rl[jt] = __builtin_bit_cast(v8bf, frag[((s * JT + jt) * 2 + 1) * 64 + lane]);
+            for (int j = 0; j < L4; ++j) {
+                const float4 v = xn[u][j];
+                a = __builtin_fmaf(v.x, v.x, a); a = __builtin_fmaf(v.y, v.y, a);
+                a = __builtin_fmaf(v.z, v.z, a); a = __builtin_fmaf(v.w, v.w, a);
             }
+            a += __shfl_xor(a, 16);
+            nx2[u] = a + __shfl_xor(a, 32);
+        }
+        // Rows of ordinary magnitude (|x| in 2^-4 .. 2^12) split as they are: nothing overflows fp16, and the terms that
+        // fall below its normal range are off by at most sqrt(d) 2^-25 together.  Others are brought to |x| ~ 1 first.
+        float unit[2] = {1.0f, 1.0f};
+        const bool odd = !(nx2[0] >= 0x1p-8f && nx2[0] <= 0x1p24f && nx2[1] >= 0x1p-8f && nx2[1] <= 0x1p24f);
+        if (__ballot(odd) != 0) {                                  // wave-uniform
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rh[jt], xh[s], acc[jt], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) {
+                int e = 0;
+                if (nx2[u] > 0.0f && nx2[u] < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2[u]) / 2;
+                unit[u] = __builtin_amdgcn_ldexpf(1.0f, -e);
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rl[jt], xh[s], acc[jt], 0, 0, 0);
+                for (int j = 0; j < L4; ++j) {
+                    xn[u][j].x *= unit[u]; xn[u][j].y *= unit[u]; xn[u][j].z *= unit[u]; xn[u][j].w *= unit[u];
+                }
+            }
+        }
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rh[jt], xl[s], acc[jt], 0, 0, 0);
-            // keep the steps apart: hoisting every fragment read of the tile to the top costs
-            // 128 registers and one wavefront of occupancy
+        for (int u = 0; u < 2; ++u) {
+            keep[u] = nx2[u] < __builtin_inff()
+                          ? __builtin_fmaxf(theta<D>() * __builtin_sqrtf(nx2[u]), kKeepFloor) * unit[u] * kColumnScale
+                          : __builtin_inff();
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                uint32_t up[4], lo[4];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float4 v = xn[u][2 * s + j];
+                    split_f16_pair(v.x, v.y, up[2 * j], lo[2 * j]);
+                    split_f16_pair(v.z, v.w, up[2 * j + 1], lo[2 * j + 1]);
+                }
+                xh[u][s] = __builtin_bit_cast(v8h, make_uint4(up[0], up[1], up[2], up[3]));
+                xl[u][s] = __builtin_bit_cast(v8h, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+            }
+        }
+        if (tile + tile_step < n_total) load_tile(tile + tile_step);
+
+        // 16 bits of every lane (a group of four tiles) at a time; accumulator register r of tile t: bit 4 t + r of the
+        // lane's quarter.  The products of a group are issued with the signs and minima of the group before it between
+        // them (the wavefront issues in order: behind the products the vector work would wait for all of them), and
+        // the fragments of a step are read one step ahead.
+        constexpr int ITEMS = S * 4;                               // (step, tile) of a group
+        uint32_t word[2][(GROUPS + 1) / 2], park[2][(GROUPS + 1) / 2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int q = 0; q < (GROUPS + 1) / 2; ++q) word[u][q] = park[u][q] = 0;
+        v4f acc[2][2][4];                                          // [group parity][unit][tile]
+        v8h fr[2][2];                                              // [parity][upper, lower]
+        auto read_item = [&](int grp, int item, v8h (&f)[2]) {
+            const uint4 *at = frag_s + (((grp * 4 + item % 4) * S + item / 4) * 2) * 64 + lane;
+            f[0] = __builtin_bit_cast(v8h, at[0]);
+            f[1] = __builtin_bit_cast(v8h, at[64]);
+        };
+        auto multiply_group = [&](int grp) {
+            v4f (&a)[2][4] = acc[grp & 1];
+#pragma unroll
+            for (int item = 0; item < ITEMS; ++item) {
+                const int s = item / 4, t = item % 4;
+                const v8h rh = fr[item & 1][0], rl = fr[item & 1][1];
+                if (item + 1 < ITEMS) read_item(grp, item + 1, fr[(item + 1) & 1]);
+                else if (grp + 1 < GROUPS) read_item(grp + 1, 0, fr[(item + 1) & 1]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    a[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rh, xh[u][s], s == 0 ? v4f{0.0f, 0.0f, 0.0f, 0.0f} : a[u][t], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) a[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rl, xh[u][s], a[u][t], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) a[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rh, xl[u][s], a[u][t], 0, 0, 0);
+            }
+        };
+        static_assert(ITEMS % 2 == 0, "the fragment buffers alternate across groups");
+        read_item(0, 0, fr[0]);
+        multiply_group(0);
+#pragma unroll
+        for (int grp = 0; grp < GROUPS; ++grp) {
             __builtin_amdgcn_sched_barrier(0);
+            if (grp + 1 < GROUPS) multiply_group(grp + 1);
+            float smallest[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const v4f (&z)[4] = acc[grp & 1][u];
+                uint32_t neg = 0;                                  // bit q = sign of element q (-0 is parked anyway)
+                smallest[u] = __builtin_inff();
+#pragma unroll
+                for (int q = 15; q >= 0; --q) {
+                    const float zq = z[q / 4][q % 4];
+                    neg = __builtin_amdgcn_alignbit(neg, __builtin_bit_cast(uint32_t, zq), 31);
+                    smallest[u] = __builtin_fminf(smallest[u], __builtin_fabsf(zq));
+                }
+                word[u][grp / 2] |= (~neg & 0xFFFFu) << (16 * (grp & 1));
+            }
+            if (grp + 1 < GROUPS) {
+#pragma unroll
+                for (int item = 0; item < ITEMS; ++item) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);             // the next fragments
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // a product
+                        __builtin_amdgcn_sched_group_barrier(0x002, ITEMS == 4 ? 3 : 2, 0);    // what its shadow holds
+                    }
+                }
+            }
+            // the smallest |z~| of the 16 decides for all of them; only where one is in doubt they are looked at
+            if (__ballot(!(smallest[0] > keep[0]) || !(smallest[1] > keep[1])) != 0) {         // wave-uniform
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    uint32_t pk = 0;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q)
+                        pk |= (uint32_t)(!(__builtin_fabsf(acc[grp & 1][u][q / 4][q % 4]) > keep[u])) << q;
+                    park[u][grp / 2] |= pk << (16 * (grp & 1));
+                }
+            }
         }
 
-        // provisional bits (sign of z~; -0 is parked anyway) and the unsettled ones, one mask bit per
-        // accumulator register, per 32-bit group.  Signs: 16 funnel shifts collect the sign bits, then
-        // the four nibbles move to their byte.  Margin: the smallest |z~| of the 16 decides for all of
-        // them at once (99.7 % of the groups); only a group with a doubtful element is tested one by one.
-        uint32_t bits[JT], park[JT];
         uint32_t any_park = 0;
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt) {
-            uint32_t neg = 0;                                                 // bit r = sign of register r
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const float z = acc[jt][15 - q];
-                neg = __builtin_amdgcn_alignbit(neg, __builtin_bit_cast(uint32_t, z), 31);
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t row = r0 + 16 * u + n;
+            const bool row_ok = row < rows;
+            uint8_t *dst = codes + map.row_words(min(row, rows - 1)) * 8 + c_first / 8 + BYTES * g;
+            if (row_ok) {
+                if constexpr (BYTES == 2) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)word[u][0];
+                else if constexpr (BYTES == 4) *reinterpret_cast<uint32_t *>(dst) = word[u][0];
+                else *reinterpret_cast<uint2 *>(dst) = make_uint2(word[u][0], word[u][GROUPS / 2 - 1]);
             }
-            const uint32_t pos_bits = ~neg;
-            const uint32_t spread = (pos_bits & 0xFu) | ((pos_bits & 0xF0u) << 4) | ((pos_bits & 0xF00u) << 8) |
-                                    ((pos_bits & 0xF000u) << 12);             // register r -> bit 8*(r/4) + r%4
-            bits[jt] = spread << (4 * g);
-            float smallest = __builtin_fabsf(acc[jt][0]);
 #pragma unroll
-            for (int r = 1; r < 16; ++r) smallest = __builtin_fminf(smallest, __builtin_fabsf(acc[jt][r]));
-            uint32_t pk = 0;
-            if (__builtin_amdgcn_ballot_w64(!(smallest > keep)) != 0) {        // wave-uniform
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    pk |= (uint32_t)(!(__builtin_fabsf(acc[jt][r]) > keep)) << (8 * (r >> 2) + (r & 3));
+            for (int q = 0; q < (GROUPS + 1) / 2; ++q) {
+                if (!row_ok) park[u][q] = 0;
+                any_park |= park[u][q];
             }
-            park[jt] = row_ok ? (pk << (4 * g)) : 0u;
-            any_park |= park[jt];
-        }
-        // the other half-wavefront holds the other 16 bits of each group of the same row
-        uint32_t word[JT];
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt) word[jt] = bits[jt] | (uint32_t)__shfl_xor((int)bits[jt], 32);
-        if (lane < 32 && row_ok) {
-            uint32_t *dst = reinterpret_cast<uint32_t *>(codes + map.word_index(r0 + lane, c0));
-            if (JT == 4)
-                *reinterpret_cast<uint4 *>(dst) = make_uint4(word[0], word[1], word[2], word[3]);
-            else
-                *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[JT - 1]);
         }
 
-        // park the unsettled bits.  The list may be worked off at any point from here on: this
-        // tile's words are on their way to memory and the accumulators are dead.
+        // park the unsettled bits.  The list may be worked off at any point from here on: this tile's words are on their
+        // way to memory.
         while (__ballot(any_park != 0) != 0) {                    // wave-uniform; rarely more than 2 rounds
-            int jt = 0;
+            constexpr int PIECES = 2 * ((GROUPS + 1) / 2);
+            int which = 0;
+            uint32_t mine = 0, bits = 0;                          // this lane's first non-empty piece
 #pragma unroll
-            for (int t = JT - 1; t >= 0; --t) jt = park[t] ? t : jt;
+            for (int p = PIECES - 1; p >= 0; --p) {
+                const uint32_t pk = park[p / (PIECES / 2)][p % (PIECES / 2)];
+                if (pk) { which = p; mine = pk; bits = word[p / (PIECES / 2)][p % (PIECES / 2)]; }
+            }
             const bool parked = any_park != 0;
-            uint32_t mine = 0;                                    // this lane's first non-empty group
-#pragma unroll
-            for (int t = 0; t < JT; ++t) mine = (t == jt) ? park[t] : mine;
             const int pos = parked ? __builtin_ctz(mine) : 0;
             const uint64_t pm = __ballot(parked);
-            if (cnt + 64 > kListCap) {
-                work_off_list<D>(list, cnt, ts, proj, map, nbits);
-                cnt = 0;
-            }
+            if (cnt + 64 > kListCap) work_off();
             if (parked) {
-                const int slot = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32),
-                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u));
-                uint32_t b = 0;
-#pragma unroll
-                for (int t = 0; t < JT; ++t) b = (t == jt) ? bits[t] : b;
-                list[slot] = (uint64_t)(uint32_t)(r0 + i_loc) | ((uint64_t)(c0 + jt * 32 + pos) << 32) |
-                             ((uint64_t)((b >> pos) & 1u) << 48) | ((uint64_t)second << 49);
-                const uint32_t cleared = mine & (mine - 1u);
-#pragma unroll
-                for (int t = 0; t < JT; ++t) park[t] = (t == jt) ? cleared : park[t];
+                const int slot = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u));
+                const int u = which / (PIECES / 2), piece = which % (PIECES / 2);
+                list[slot] = (uint64_t)(r0 + 16 * u + n) | ((uint64_t)(c_first + (C / 4) * g + 32 * piece + pos) << 32) |
+                             ((uint64_t)((bits >> pos) & 1u) << 48) | ((uint64_t)second << 49);
                 any_park = 0;
 #pragma unroll
-                for (int t = 0; t < JT; ++t) any_park |= park[t];
+                for (int p = 0; p < PIECES; ++p) {
+                    uint32_t &pk = park[p / (PIECES / 2)][p % (PIECES / 2)];
+                    pk = p == which ? pk & (pk - 1u) : pk;
+                    any_park |= pk;
+                }
             }
             cnt += __builtin_popcountll(pm);
         }
-        }   // column groups
     }
 
-    // The four wavefronts' leftovers are pooled and worked off 64 entries per pass, pass p by wavefront
-    // p % 4: the cost of a pass is the latency of its uncoalesced loads, so full passes side by side
-    // beat both four nearly empty ones and a queue of full ones on one wavefront.
+    // The wavefronts' leftovers are pooled and worked off 64 entries per pass, pass p by wavefront p % kWaves: the
+    // cost of a pass is the latency of its loads, so full passes side by side beat nearly empty ones.
     __builtin_amdgcn_s_waitcnt(0x0F70);          // this wavefront's words have been stored
     if (lane == 0) cnt_s[wave] = cnt;
     __syncthreads();
-    {
-        const int n0 = cnt_s[0], n1 = n0 + cnt_s[1], n2 = n1 + cnt_s[2], n3 = n2 + cnt_s[3];
-        for (int t0 = wave * 64; t0 < n3; t0 += 256) {
-            const int t = t0 + lane;
-            if (t < n3) {
-                const int w = (t >= n0) + (t >= n1) + (t >= n2);
-                const int base = w == 0 ? 0 : (w == 1 ? n0 : (w == 2 ? n1 : n2));
-                settle_entry<D, (D <= 64 ? D : 32)>(list_s[w][t - base], ts, proj, map, nbits);   // the tile loop's registers are free now
-            }
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) total += cnt_s[w];
+    for (int t0 = wave * 64; t0 < total; t0 += THREADS) {
+        int t = t0 + lane, w = 0;
+        if (t < total) {
+            while (t >= cnt_s[w]) t -= cnt_s[w++];
+            settle_entry<D, C, D <= 64 ? D : 32>(list_s[w][t], ts, r_s, c_first, map);   // the tile loop's registers are free now
         }
     }
 }
@@ -362,40 +408,48 @@ bool binarize_mfma_supported(int d, int nbits) {
     return (d == 32 || d == 64 || d == 128) && nbits % 64 == 0;
 }
 
-template <int D, int G, int CG>
-int launch_one(const Tensors &ts, int count, const float *proj, long rows, int N, int H, int nbits, hipStream_t st) {
-    const long n_tiles = (rows + 31) / 32;
-    const long n_total = n_tiles * count;
-    // about two workgroups of 4 wavefronts per CU (what the registers allow), every wavefront the
-    // same number of tiles
-    const long tiles_per_wave = (n_total + 4 * 512 - 1) / (4 * 512);
-    const long blocks = (n_total + 4 * tiles_per_wave - 1) / (4 * tiles_per_wave);
-    const dim3 grid((unsigned)blocks, (unsigned)(nbits / (G * CG)));
-    RowMap map{N, H, nbits / 64};
-    binarize_mfma_kernel<D, G, CG><<<grid, dim3(256), 0, st>>>(ts, proj, rows, map, nbits, n_tiles, n_total);
+template <int D, int C, int kWaves>
+int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &map, int nbits, long n_tiles, long n_total,
+                 hipStream_t st) {
+    // one workgroup per CU (what the registers allow) over all column groups, every wavefront the same number of tiles
+    const long waves = 256 / (nbits / C) * kWaves;
+    const long tiles_per_wave = (n_total + waves - 1) / waves;
+    const long blocks = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
+    const dim3 grid((unsigned)blocks, (unsigned)(nbits / C));
+    binarize_mfma_kernel<D, C, kWaves><<<grid, dim3(kWaves * 64), 0, st>>>(ts, proj, (uint32_t)rows, map, nbits,
+                                                                          (uint32_t)n_tiles, (uint32_t)n_total);
     return check_launch("sa_binarize(mfma)");
 }
 
-// x1 / codes1 may be null: one tensor.  Column groups: 128 columns per pass of the matrix cores (64
-// for d = 128 or when nbits is not a multiple of 128); when nbits is a multiple of 256 a workgroup
-// takes two groups per row tile, so the rows are read and split once for both.
+// Workgroups of 8 wavefronts, of 4 where those already have one tile each: two wavefronts of one tile on a SIMD only
+// take turns (1 x 197 x 3 heads x 64 -> 64 bits: 7.6 -> 7.0 us).
+template <int D, int C>
+int launch_one(const Tensors &ts, int count, const float *proj, long rows, int N, int H, int nbits, hipStream_t st) {
+    const long n_tiles = (rows + 31) / 32, n_total = n_tiles * count;
+    const RowMap map{FastDiv((uint32_t)H), FastDiv((uint32_t)N), N, H, nbits / 64};
+    return n_total <= 256 / (nbits / C) * 4 ? launch_waves<D, C, 4>(ts, proj, rows, map, nbits, n_tiles, n_total, st)
+                                            : launch_waves<D, C, 8>(ts, proj, rows, map, nbits, n_tiles, n_total, st);
+}
+
+// x1 / codes1 may be null: one tensor.  Columns of a workgroup: as many of the code as divide it, up to 256 (128 at
+// d = 128: what the LDS holds), so that the rows are read and split as few times as possible.
 int launch_binarize_mfma(const float *x0, const float *x1, const float *proj, uint64_t *codes0, uint64_t *codes1,
                          long rows, int N, int H, int d, int nbits, hipStream_t st) {
     const Tensors ts{x0, x1, codes0, codes1};
     const int count = x1 ? 2 : 1;
-    const bool g128 = (nbits % 128 == 0), two = (nbits % 256 == 0);
+    const bool c128 = (nbits % 128 == 0), c256 = (nbits % 256 == 0);
     switch (d) {
         case 32:
-            return two    ? launch_one<32, 128, 2>(ts, count, proj, rows, N, H, nbits, st)
-                   : g128 ? launch_one<32, 128, 1>(ts, count, proj, rows, N, H, nbits, st)
-                          : launch_one<32, 64, 1>(ts, count, proj, rows, N, H, nbits, st);
+            return c256   ? launch_one<32, 256>(ts, count, proj, rows, N, H, nbits, st)
+                   : c128 ? launch_one<32, 128>(ts, count, proj, rows, N, H, nbits, st)
+                          : launch_one<32, 64>(ts, count, proj, rows, N, H, nbits, st);
         case 64:
-            return two    ? launch_one<64, 128, 2>(ts, count, proj, rows, N, H, nbits, st)
-                   : g128 ? launch_one<64, 128, 1>(ts, count, proj, rows, N, H, nbits, st)
-                          : launch_one<64, 64, 1>(ts, count, proj, rows, N, H, nbits, st);
+            return c256   ? launch_one<64, 256>(ts, count, proj, rows, N, H, nbits, st)
+                   : c128 ? launch_one<64, 128>(ts, count, proj, rows, N, H, nbits, st)
+                          : launch_one<64, 64>(ts, count, proj, rows, N, H, nbits, st);
         default:
-            return g128 ? launch_one<128, 64, 2>(ts, count, proj, rows, N, H, nbits, st)
-                        : launch_one<128, 64, 1>(ts, count, proj, rows, N, H, nbits, st);
+            return c128 ? launch_one<128, 128>(ts, count, proj, rows, N, H, nbits, st)
+                        : launch_one<128, 64>(ts, count, proj, rows, N, H, nbits, st);
     }
 }
 
