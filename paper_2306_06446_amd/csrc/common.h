@@ -97,6 +97,27 @@ int mult_linear_rows(const void *xh_all, const RowSel &sel, int K, int N, const 
 size_t shift_linear_rows_workspace_bytes(int K, int N, int variant);
 int shift_linear_rows(const int8_t *xq_all, const RowSel &sel, int K, int N, const uint8_t *w4, float out_scale, float *y,
                       const float *gate, int variant, void *planes, hipStream_t st);
+// Where the Shift expert's decoded planes are: the caller's (prepared variant) or `planes`, filled by this call (any other
+// matrix-core variant).  shift_mlp_planes: both layers of an MLP in one launch; `workspace` as sa_shift_mlp lays it out
+// (*hidden: its int8 hidden rows).
+int shift_linear_planes(const uint8_t *w4, int K, int N, int variant, void *planes, hipStream_t st, const int8_t **out);
+int shift_mlp_planes(const uint8_t *w1, const uint8_t *w2, int E, int hid, int variant, long max_rows, void *workspace,
+                     hipStream_t st, const int8_t **planes1, const int8_t **planes2, int8_t **hidden);
+
+// Shift and Mult expert side by side in one launch per layer, matrix cores only (experts.hip).  The rows of the two
+// selections add up to at most max_rows, which is the same in both; every token belongs to one of them.
+struct ExpertPair {
+    const int8_t *xq;        // int8 codes and fp16 rows of every token
+    const void *xh;
+    RowSel shift_rows, mult_rows;
+    float *y;                // [T, N]: scattered, gated
+    const float *gate;
+    float out_scale;         // of the Shift expert
+};
+int expert_pair_mlp(const ExpertPair &p, int E, int hid, const int8_t *w1_planes, const int8_t *w2_planes, const void *mw1,
+                    const void *mw2, float requant_scale, const int8_t *lut, bool accumulate, int8_t *shift_hidden,
+                    void *mult_hidden, hipStream_t st);
+int expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes, const void *w_f16, hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).
 size_t moe_dispatch_scratch_bytes(long T, int E);
 int moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,

@@ -20,8 +20,8 @@
 // only drain, the last stage) so that the steady state holds no branch around a load and no
 // branch join in front of its MFMAs.
 //
-// Outputs leave through LDS, 64 rows per pass, so that every lane stores 16 bytes of one row
-// (a scattered destination row index and its gate are then fetched once per 16 bytes).
+// Outputs leave through LDS, so that every lane stores 16 bytes of one row (a scattered destination row
+// index and its gate are then fetched once per 16 bytes).
 #pragma once
 
 #include <type_traits>
@@ -161,8 +161,18 @@ __device__ __forceinline__ void store_chunk(const Store &store, uint4 v, const i
     }
 }
 
-template <class T, int BM, int BN, int SB, int NS, int LS, int OCC, class Store>
-__global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store store) {
+template <class T, int BM, int BN, int SB, int NS, class Store>
+struct NtShape {
+    static constexpr int STAGE = (BM + T::kPlanes * BN) * SB;
+    // epilogue staging: 32 rows of a wavefront's columns each, 16 bytes apart modulo the banks
+    static constexpr int PITCH = BN / 2 * Store::kBytes + 16, SLAB_BYTES = 32 * PITCH;
+    static constexpr int EPI_BYTES = 4 * SLAB_BYTES + Store::kTableBytes;
+    static constexpr int LDS_BYTES = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
+};
+
+template <class T, int BM, int BN, int SB, int NS, int LS, class Store>
+__device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
+    using S = NtShape<T, BM, BN, SB, NS, Store>;
     constexpr int kStageBytes = SB;                     // bytes of K per stage and row
     constexpr int kChunksPerRow = SB / 16;              // 16-byte chunks per LDS row
     constexpr int KK = SB / 32;                         // 32-byte MFMA steps per stage
@@ -170,18 +180,17 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
     constexpr int NP = T::kPlanes;
     constexpr int MI = BM / 64, NJ = BN / 64;           // 32x32 tiles per wavefront
     constexpr int A_BYTES = BM * kStageBytes, B_BYTES = BN * kStageBytes;
-    constexpr int STAGE = A_BYTES + NP * B_BYTES;
+    constexpr int STAGE = S::STAGE;
     constexpr int ROWS_PER_INSTR = 1024 / kStageBytes;  // LDS rows one wavefront load fills
     constexpr int A_INSTR = BM / ROWS_PER_INSTR / 4;    // loads per wavefront and stage
     constexpr int B_INSTR = BN / ROWS_PER_INSTR / 4;
     constexpr int ES = Store::kBytes;
-    constexpr int SLAB_BYTES = 64 * BN * ES;            // epilogue staging: one 32-row slab per wavefront row
-    constexpr int EPI_BYTES = SLAB_BYTES + Store::kTableBytes;
     constexpr int LOADS = A_INSTR + NP * B_INSTR;       // direct loads per wavefront and stage
-    constexpr int LDS_BYTES = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
+    // Narrow outputs and sign codes: the MFMAs compute the transposed tile (B rows down, A rows across), so that a lane
+    // ends up with four consecutive columns of a row: a quarter of the LDS writes on the way out.  With int8 operands
+    // the chip then holds about 4 % less of its rate under full load, so 32-bit outputs are computed upright.
+    constexpr bool ROWS_ACROSS = ES < 4 || Store::kSignCodes;
     static_assert(NS >= 2 && NS <= 4, "ring of two to four stages");
-    static_assert(LDS_BYTES * OCC <= 160 * 1024, "OCC workgroups of this tile do not fit the LDS of a CU");
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_BYTES];
 
     const int32_t *rows;
     long n_rows;
@@ -194,7 +203,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
     const int col_tiles = (g.N + BN - 1) / BN;
     const int cg = g.col_groups, rg = 8 / cg;
     const int cols_per_group = (col_tiles + cg - 1) / cg;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int xcd = block & 7, slot = block >> 3;
     const long row_tile = (long)(slot / cols_per_group) * rg + xcd / cg;
     const int col_tile = (slot % cols_per_group) * cg + xcd % cg;
     const long m0 = row_tile * BM;
@@ -294,7 +303,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
         static_for<MFMAS>([&](auto m_c) {
             constexpr int m = decltype(m_c)::value;             // MFMAs issued before this one
             constexpr int p = m / (MI * NJ), i = m / NJ % MI, j = m % NJ;
-            acc[i][j] = T::mma(af[i], bf[p][j], acc[i][j]);
+            acc[i][j] = ROWS_ACROSS ? T::mma(bf[p][j], af[i], acc[i][j]) : T::mma(af[i], bf[p][j], acc[i][j]);
             // loads [m * LPS / MFMAS, (m + 1) * LPS / MFMAS) of this step's share follow MFMA m
             if constexpr (phase >= 0) {
                 constexpr int q0 = m * LPS / MFMAS, q1 = (m + 1) * LPS / MFMAS;
@@ -399,8 +408,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
         for (int s = 0; s < n_stages; ++s) stage(s, Ask{}, Ask{}, Ask{});
     }
 
-    // ---- sign codes: a wavefront's 64 columns are one code word of a head; one ballot per accumulator
-    //      register gives 32 sign bits of two rows, and lanes 0..15 write the words of the 32 rows of a tile.
+    // Transposed tile: accumulator register r of lane l holds row l % 32, column 8 (r / 4) + 4 (l / 32) + r % 4.
+    // ---- sign codes: a wavefront's 64 columns are one code word of a head; each half-wavefront has every other nibble.
     if constexpr (Store::kSignCodes) {
         if (n0 < store.code_cols) {               // uniform per workgroup
             static_assert(NJ == 2, "a wavefront must own 64 columns");
@@ -409,92 +418,124 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt_kernel(GemmArgs g, Store sto
             const int cin = col0 - part * store.part_width;
             const int head = cin / store.head_dim, w = (cin % store.head_dim) / 64, W = store.head_dim / 64;
             uint64_t *dst = part == 0 ? store.codes[0] : store.codes[1];
-            static_for<MI>([&](auto i_c) {
-                constexpr int i = decltype(i_c)::value;
-                uint64_t mine[2] = {0, 0};
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint64_t lo = __ballot(acc[i][0][r] >= 0), hi = __ballot(acc[i][1][r] >= 0);
-                    const uint64_t w0 = (lo & 0xFFFFFFFFull) | (hi << 32);              // rows of lanes 0..31
-                    const uint64_t w1 = (lo >> 32) | (hi & 0xFFFFFFFF00000000ull);      // rows of lanes 32..63
-                    if (lane == r) { mine[0] = w0; mine[1] = w1; }
-                }
-                if (lane < 16) {
+            for (int i = 0; i < MI; ++i) {
+                uint32_t word[2];
 #pragma unroll
-                    for (int half = 0; half < 2; ++half) {
-                        const long m = m0 + wm + i * 32 + 8 * (lane >> 2) + 4 * half + (lane & 3);
-                        if (m < n_rows) {
-                            const long b = m / store.tokens, n = m % store.tokens;
-                            dst[((size_t)(b * store.heads + head) * store.tokens + n) * W + w] = mine[half];
-                        }
+                for (int j = 0; j < 2; ++j) {
+                    uint32_t neg = 0;
+#pragma unroll
+                    for (int r = 15; r >= 0; --r) {
+                        neg = __builtin_amdgcn_alignbit(neg, (uint32_t)acc[i][j][r], 31);      // neg << 1 | sign
+                        if (r % 4 == 0 && r > 0) neg <<= 4;
                     }
+                    neg <<= 4 * fg;
+                    word[j] = ~(neg | (uint32_t)__shfl_xor((int)neg, 32));
                 }
-            });
+                const long m = m0 + wm + i * 32 + fr;
+                if (fg == 0 && m < n_rows) {
+                    const long b = m / store.tokens, n = m % store.tokens;
+                    dst[((size_t)(b * store.heads + head) * store.tokens + n) * W + w] = word[0] | ((uint64_t)word[1] << 32);
+                }
+            }
             return;
         }
     }
 
-    // ---- epilogue.  Every output leaves through LDS so that a lane stores 16 contiguous bytes of
-    //      one row: per pass, each wavefront converts one 32-row slab of its accumulators into a
-    //      64 x BN staging tile, then the workgroup writes the 64 rows out.
-    constexpr int CPR = BN * ES / 16;             // 16-byte chunks per staged row
-    constexpr int PER_THREAD = 64 * CPR / 256;
-    static_assert(PER_THREAD >= 1, "a staged slab has at least one chunk per thread");
-    uint8_t *tile = lds;
-    uint8_t *table = lds + SLAB_BYTES;
+    // ---- epilogue.  Every wavefront turns 32 rows of its columns at a time into rows of 16-byte chunks, through LDS of
+    //      its own.  Staging 64 rows of the workgroup's whole tile took two barriers per 32 rows of a wavefront and one
+    //      LDS write per element: 98304 x 1024 <- 256 int8 to int8 75 -> 64 us, 12608 x 1536 <- 384 28 -> 25 us.
+    constexpr int PITCH = S::PITCH, CPR = BN / 2 * ES / 16;       // 16-byte chunks of a staged row
+    uint8_t *slab = lds + wave * S::SLAB_BYTES;
+    uint8_t *table = lds + 4 * S::SLAB_BYTES;
     const bool whole_chunks = (size_t)N * ES % 16 == 0;
     __syncthreads();                              // the last stage has been read
-    if (Store::kTableBytes != 0) table[tid] = static_cast<const uint8_t *>(store.table)[tid];
-    static_for<MI>([&](auto i_c) {
-        constexpr int i = decltype(i_c)::value;
-        __syncthreads();                          // the staging tile is free (and the table is there)
+    if constexpr (Store::kTableBytes != 0) {
+        table[tid] = static_cast<const uint8_t *>(store.table)[tid];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int nl = wn + j * 32 + (lane & 31);
+            if constexpr (ROWS_ACROSS) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ml = (wave >> 1) * 32 + mfma32_row(r, lane);
-                const uint32_t v = store.convert(acc[i][j][r], min(n0 + nl, N - 1), table);
-                if (ES == 1)
-                    tile[ml * BN + nl] = (uint8_t)v;
-                else if (ES == 2)
-                    reinterpret_cast<uint16_t *>(tile)[ml * BN + nl] = (uint16_t)v;
-                else
-                    reinterpret_cast<uint32_t *>(tile)[ml * BN + nl] = v;
+                for (int q = 0; q < 4; ++q) {
+                    const int nl = j * 32 + 8 * q + 4 * fg;
+                    uint32_t v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = store.convert(acc[i][j][4 * q + e], min(n0 + wn + nl + e, N - 1), table);
+                    uint8_t *at = slab + fr * PITCH + nl * ES;
+                    if constexpr (ES == 1)
+                        *reinterpret_cast<uint32_t *>(at) = v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24);
+                    else if constexpr (ES == 2)
+                        *reinterpret_cast<uint2 *>(at) = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
+                    else
+                        *reinterpret_cast<uint4 *>(at) = make_uint4(v[0], v[1], v[2], v[3]);
+                }
+            } else {
+                const int nl = j * 32 + fr;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    *reinterpret_cast<uint32_t *>(slab + mfma32_row(r, lane) * PITCH + nl * 4) =
+                        store.convert(acc[i][j][r], min(n0 + wn + nl, N - 1), table);
             }
         }
-        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < PER_THREAD; ++q) {
-            const int c = tid + 256 * q;
-            const int ml = c / CPR, cc = c % CPR;
-            const long m = m0 + (ml >> 5) * (BM / 2) + i * 32 + (ml & 31);
-            const int n = n0 + cc * (16 / ES);
-            if (m < n_rows && n < N) {
-                uint4 v = *reinterpret_cast<const uint4 *>(tile + (ml * CPR + cc) * 16);
-                store_chunk(store, v, rows, m, n, N, whole_chunks);
-            }
+        for (int q = 0; q < CPR / 2; ++q) {
+            const int c = lane + 64 * q, ml = c / CPR, cc = c % CPR;
+            const uint4 v = *reinterpret_cast<const uint4 *>(slab + ml * PITCH + cc * 16);
+            const long m = m0 + wm + i * 32 + ml;
+            const int n = n0 + wn + cc * (16 / ES);
+            if (m < n_rows && n < N) store_chunk(store, v, rows, m, n, N, whole_chunks);
         }
-    });
+    }
 }
 
-template <class T, int BM, int BN, int SB, int NS, int LS, int OCC, class Store>
-int launch_gemm_tile(const GemmArgs &g, const Store &store, hipStream_t st, const char *what) {
-    const long row_tiles = (g.sel.max_rows + BM - 1) / BM;
-    const long col_tiles = (g.N + BN - 1) / BN;
+// A tile shape as launch_tile and the kernels below take it.
+template <class T, int BM_, int BN_, int SB, int NS, int LS>
+struct NtTile {
+    static constexpr int BM = BM_, BN = BN_;
+    template <class Store>
+    static constexpr int lds_bytes() { return NtShape<T, BM, BN, SB, NS, Store>::LDS_BYTES; }
+    template <class Store>
+    __device__ static __forceinline__ void run(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
+        nt_gemm_tile<T, BM, BN, SB, NS, LS, Store>(g, store, block, lds);
+    }
     // The fewest column groups whose share of the B planes stays resident in a 4 MiB L2 next to
     // the A rows streaming through it.  (Fewer groups fetch fewer bytes when A is the larger operand,
     // but a B share that is evicted between row tiles costs more time than the extra A traffic.)
-    const size_t b_bytes = (size_t)T::kPlanes * g.N * g.K * T::kElemBytes;
-    int cg = 1;
-    while (cg < 8 && b_bytes / cg > (size_t)(5 << 19)) cg *= 2;     // 2.5 MiB
-    const int rg = 8 / cg;
-    const long blocks = 8 * ((row_tiles + rg - 1) / rg) * ((col_tiles + cg - 1) / cg);
-    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
-    const dim3 grid((unsigned)blocks);
+    static int col_groups(const GemmArgs &g) {
+        const size_t b_bytes = (size_t)T::kPlanes * g.N * g.K * T::kElemBytes;
+        int cg = 1;
+        while (cg < 8 && b_bytes / cg > (size_t)(5 << 19)) cg *= 2;     // 2.5 MiB
+        return cg;
+    }
+};
+
+// Workgroups that cover n_rows x N with this tile (a multiple of 8: one share per XCD).
+template <class Tile>
+__host__ __device__ inline long tile_blocks(long n_rows, int N, int col_groups) {
+    const long row_tiles = (n_rows + Tile::BM - 1) / Tile::BM, col_tiles = (N + Tile::BN - 1) / Tile::BN;
+    const int rg = 8 / col_groups;
+    return 8 * ((row_tiles + rg - 1) / rg) * ((col_tiles + col_groups - 1) / col_groups);
+}
+
+template <class Tile, int OCC, class Store>
+__global__ __launch_bounds__(256, OCC) void gemm_kernel(GemmArgs g, Store store) {
+    constexpr int LDS_BYTES = Tile::template lds_bytes<Store>();
+    static_assert(LDS_BYTES * OCC <= 160 * 1024, "OCC workgroups of this tile do not fit the LDS of a CU");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_BYTES];
+    Tile::template run<Store>(g, store, blockIdx.x, lds);
+}
+
+template <class Tile, int OCC, class Store>
+int launch_tile(const GemmArgs &g, const Store &store, hipStream_t st, const char *what) {
     GemmArgs ga = g;
-    ga.col_groups = cg;
-    gemm_nt_kernel<T, BM, BN, SB, NS, LS, OCC, Store><<<grid, dim3(256), 0, st>>>(ga, store);
+    ga.col_groups = Tile::col_groups(g);
+    const long blocks = tile_blocks<Tile>(g.sel.max_rows, g.N, ga.col_groups);
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
+    gemm_kernel<Tile, OCC, Store><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(ga, store);
     return check_launch(what);
 }
 
@@ -537,27 +578,27 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
     const bool whole_line_stages = lines && row_bytes >= 512;
     if constexpr (T::kPlanes == 2) {
         if (tiles(32, 64) <= 256)
-            return whole_line_stages ? launch_slice<T, 1, 2, 128, 4, Store>(g, store, st, what)
-                                     : launch_slice<T, 1, 2, 64, 7, Store>(g, store, st, what);
+            return whole_line_stages ? launch_tile<SliceTile<T, 1, 2, 128, 4>, 1>(g, store, st, what)
+                                     : launch_tile<SliceTile<T, 1, 2, 64, 7>, 1>(g, store, st, what);
         if (tiles(64, 64) <= 640)
-            return whole_line_stages ? launch_slice<T, 2, 2, 128, 3, Store>(g, store, st, what)
-                                     : launch_slice<T, 2, 2, 64, 6, Store>(g, store, st, what);
-        if (lines && long_rows) return launch_gemm_tile<T, 256, 128, 128, 2, 2, 1, Store>(g, store, st, what);
+            return whole_line_stages ? launch_tile<SliceTile<T, 2, 2, 128, 3>, 1>(g, store, st, what)
+                                     : launch_tile<SliceTile<T, 2, 2, 64, 6>, 1>(g, store, st, what);
+        if (lines && long_rows) return launch_tile<NtTile<T, 256, 128, 128, 2, 2>, 1>(g, store, st, what);
         const long rounds256 = (tiles(256, 128) + 511) / 512, rounds128 = (tiles(128, 128) + 767) / 768;
         const bool wide = counted ? ((g.sel.max_rows + 255) / 256) * ((g.N + 127) / 128) >= 512    // no rounds to speak of
                                   : rounds256 * 5 <= rounds128 * 4;      // a round of the larger tiles takes 1.25 times as long
-        if (wide) return launch_gemm_tile<T, 256, 128, 64, 2, 1, 2, Store>(g, store, st, what);
-        return launch_gemm_tile<T, 128, 128, 64, 2, 1, 3, Store>(g, store, st, what);
+        if (wide) return launch_tile<NtTile<T, 256, 128, 64, 2, 1>, 2>(g, store, st, what);
+        return launch_tile<NtTile<T, 128, 128, 64, 2, 1>, 3>(g, store, st, what);
     } else {
         if (tiles(32, 64) <= 256)
-            return whole_line_stages ? launch_slice<T, 1, 2, 128, 6, Store>(g, store, st, what)
-                                     : launch_slice<T, 1, 2, 64, 8, Store>(g, store, st, what);
+            return whole_line_stages ? launch_tile<SliceTile<T, 1, 2, 128, 6>, 1>(g, store, st, what)
+                                     : launch_tile<SliceTile<T, 1, 2, 64, 8>, 1>(g, store, st, what);
         if (tiles(64, 64) <= (long_rows ? 320 : 640))
-            return whole_line_stages ? launch_slice<T, 2, 2, 128, 4, Store>(g, store, st, what)
-                                     : launch_slice<T, 2, 2, 64, 9, Store>(g, store, st, what);
-        if (lines && long_rows) return launch_gemm_tile<T, 128, 128, 128, 3, 2, 1, Store>(g, store, st, what);
-        if (lines && row_bytes > 768) return launch_gemm_tile<T, 192, 128, 128, 2, 2, 1, Store>(g, store, st, what);
-        return launch_gemm_tile<T, 128, 128, 64, 3, 1, 2, Store>(g, store, st, what);
+            return whole_line_stages ? launch_tile<SliceTile<T, 2, 2, 128, 4>, 1>(g, store, st, what)
+                                     : launch_tile<SliceTile<T, 2, 2, 64, 9>, 1>(g, store, st, what);
+        if (lines && long_rows) return launch_tile<NtTile<T, 128, 128, 128, 3, 2>, 1>(g, store, st, what);
+        if (lines && row_bytes > 768) return launch_tile<NtTile<T, 192, 128, 128, 2, 2>, 1>(g, store, st, what);
+        return launch_tile<NtTile<T, 128, 128, 64, 3, 1>, 2>(g, store, st, what);
     }
 }
 

@@ -52,7 +52,7 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
     const int32_t *rows;
     long n_rows;
     resolve_rows(g.sel, rows, n_rows);
-    // the same XCD-aware walk over the output as in gemm_nt_kernel
+    // the same XCD-aware walk over the output as in nt_gemm_tile
     const int col_tiles = (g.N + S::BN - 1) / S::BN;
     const int cg = g.col_groups, rg = 8 / cg;
     const int cols_per_group = (col_tiles + cg - 1) / cg;
@@ -90,7 +90,7 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
         for (int p = 0; p < S::NP; ++p)
             b_src[p][i] = static_cast<const uint8_t *>(g.b[p]) + (size_t)n * row_bytes + swizzle<CPR>(r, lc) * 16;
     }
-    // 64-byte stages: rows of A may end inside the last stage (see gemm_nt_kernel); the lane then re-reads their last 16 bytes
+    // 64-byte stages: rows of A may end inside the last stage (see nt_gemm_tile); the lane then re-reads their last 16 bytes
     const int a_klim = SB == 64 ? a_valid_bytes - 16 - swizzle<CPR>(lr, lc) * 16 : 0;
 
     auto issue_stage = [&](int slot_, int kbyte) {
@@ -231,27 +231,23 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
     }
 }
 
-template <class T, int MI, int NJ, int SB, int NS, class Store>
-__global__ __launch_bounds__(256) void gemm_slice_kernel(GemmArgs g, Store store) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[SliceShape<T, MI, NJ, SB, NS>::LDS_BYTES];
-    slice_gemm_tile<T, MI, NJ, SB, NS, Store>(g, store, blockIdx.x, lds);
-}
-
-template <class T, int MI, int NJ, int SB, int NS, class Store>
-int launch_slice(const GemmArgs &g, const Store &store, hipStream_t st, const char *what) {
-    using S = SliceShape<T, MI, NJ, SB, NS>;
-    const long row_tiles = (g.sel.max_rows + S::BM - 1) / S::BM, col_tiles = (g.N + S::BN - 1) / S::BN;
-    // column groups: A is fetched by col_groups L2s and each B plane by 8 / col_groups
-    const double a_bytes = (double)g.sel.max_rows * g.K * T::kElemBytes, b_bytes = (double)T::kPlanes * g.N * g.K * T::kElemBytes;
-    int cg = 1;
-    while (cg < 8 && 2 * cg <= col_tiles && a_bytes * 2 * cg + b_bytes * (4.0 / cg) < a_bytes * cg + b_bytes * (8.0 / cg)) cg *= 2;
-    const int rg = 8 / cg;
-    const long blocks = 8 * ((row_tiles + rg - 1) / rg) * ((col_tiles + cg - 1) / cg);
-    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
-    GemmArgs ga = g;
-    ga.col_groups = cg;
-    gemm_slice_kernel<T, MI, NJ, SB, NS, Store><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(ga, store);
-    return check_launch(what);
-}
+template <class T, int MI, int NJ, int SB, int NS>
+struct SliceTile {
+    static constexpr int BM = 32 * MI, BN = 32 * NJ;
+    template <class Store>
+    static constexpr int lds_bytes() { return SliceShape<T, MI, NJ, SB, NS>::LDS_BYTES; }
+    template <class Store>
+    __device__ static __forceinline__ void run(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
+        slice_gemm_tile<T, MI, NJ, SB, NS, Store>(g, store, block, lds);
+    }
+    // A is fetched by col_groups L2s and each B plane by 8 / col_groups: the fewest bytes
+    static int col_groups(const GemmArgs &g) {
+        const long col_tiles = (g.N + BN - 1) / BN;
+        const double a_bytes = (double)g.sel.max_rows * g.K * T::kElemBytes, b_bytes = (double)T::kPlanes * g.N * g.K * T::kElemBytes;
+        int cg = 1;
+        while (cg < 8 && 2 * cg <= col_tiles && a_bytes * 2 * cg + b_bytes * (4.0 / cg) < a_bytes * cg + b_bytes * (8.0 / cg)) cg *= 2;
+        return cg;
+    }
+};
 
 }  // namespace sa

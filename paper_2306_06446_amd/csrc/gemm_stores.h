@@ -1,0 +1,79 @@
+// How the accumulators of the two experts' matrix-core layers become output rows (the Store types of gemm_mfma.h).
+#pragma once
+
+#include "common.h"
+#include "gemm_common.h"
+
+namespace sa {
+
+inline Epilogue with_finite_scale(Epilogue e) {
+    e.rq = requant_scale_finite(e.rq);
+    return e;
+}
+
+template <int MODE>
+struct ShiftStore {
+    static constexpr int kBytes = (MODE == kEpiRequantLut) ? 1 : 4;
+    static constexpr int kTableBytes = (MODE == kEpiRequantLut) ? 256 : 0;
+    static constexpr bool kScatter = (MODE == kEpiScatterI32);
+    static constexpr bool kLinear = (MODE == kEpiLinearF32 || MODE == kEpiQkvCodes);
+    static constexpr bool kSignCodes = (MODE == kEpiQkvCodes);
+    Epilogue e;
+    void *out;             // int32 rows | int8 hidden rows | scattered fp32 rows
+    const void *table;     // the 256-entry activation table
+    const float *gate;
+    bool accumulate;
+    float *parts[3];       // kEpiLinearF32: column blocks, residual and scale
+    int part_width;
+    const float *residual;
+    float scale;
+    uint64_t *codes[2];    // kEpiQkvCodes: sign codes of column blocks 0 and 1
+    int code_cols, head_dim, tokens, heads;
+    explicit ShiftStore(const Epilogue &epi)     // epi.rq is made finite here: convert() relies on it
+        : e(with_finite_scale(epi)),
+          out(MODE == kEpiInt32 ? (void *)epi.y : MODE == kEpiRequantLut ? (void *)epi.h
+              : MODE == kEpiLinearF32 ? (void *)epi.parts[0] : MODE == kEpiQkvCodes ? (void *)epi.parts[2] : (void *)epi.yf),
+          table(epi.lut),
+          gate(MODE == kEpiScatterI32 ? epi.gate : nullptr),
+          accumulate(MODE == kEpiScatterI32 && epi.accumulate),
+          parts{epi.parts[0], epi.parts[1], epi.parts[2]},
+          part_width(epi.part_width > 0 ? epi.part_width : 4),
+          residual(epi.residual),
+          scale(epi.lin_scale),
+          codes{epi.codes[0], epi.codes[1]},
+          code_cols(MODE == kEpiQkvCodes ? 2 * epi.part_width : 0),
+          head_dim(epi.head_dim > 0 ? epi.head_dim : 64),
+          tokens(epi.tokens > 0 ? epi.tokens : 1),
+          heads(epi.heads) {}
+    __device__ inline uint32_t convert(int32_t acc, int n, const uint8_t *lds_table) const {
+        if (MODE == kEpiInt32) return (uint32_t)(acc + (e.bias ? e.bias[n] : 0));
+        if (MODE == kEpiRequantLut) return lds_table[requant_index(acc, e.rq)];
+        if (MODE == kEpiLinearF32 || MODE == kEpiQkvCodes) return __builtin_bit_cast(uint32_t, (float)acc);   // scaled at the store
+        return __builtin_bit_cast(uint32_t, e.out_scale * (float)acc);
+    }
+};
+
+__device__ inline float gelu_erf(float a) { return 0.5f * a * (1.0f + erff(a * 0.70710678118654752f)); }
+
+template <int MODE>
+struct MultStore {
+    static constexpr int kBytes = (MODE == kEpiGeluHalf) ? 2 : 4;
+    static constexpr int kTableBytes = 0;
+    static constexpr bool kScatter = (MODE == kEpiScatterF32);
+    static constexpr bool kLinear = false;
+    static constexpr bool kSignCodes = false;
+    void *out;                      // compact fp32 rows | fp16 hidden rows | scattered fp32 rows
+    const void *table = nullptr;
+    const float *gate;
+    bool accumulate;
+    explicit MultStore(const Epilogue &epi)
+        : out(MODE == kEpiFloat ? (void *)epi.of : MODE == kEpiGeluHalf ? (void *)epi.hh : (void *)epi.yf),
+          gate(MODE == kEpiScatterF32 ? epi.gate : nullptr),
+          accumulate(MODE == kEpiScatterF32 && epi.accumulate) {}
+    __device__ inline uint32_t convert(float a, int, const uint8_t *) const {
+        if (MODE == kEpiGeluHalf) return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)gelu_erf(a));
+        return __builtin_bit_cast(uint32_t, a);
+    }
+};
+
+}  // namespace sa

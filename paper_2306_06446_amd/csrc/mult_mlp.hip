@@ -7,12 +7,11 @@
 #include "common.h"
 #include "gemm_common.h"
 #include "gemm_mfma.h"
+#include "gemm_stores.h"
 
 namespace {
 
 using namespace sa;
-
-__device__ inline float gelu_erf(float a) { return 0.5f * a * (1.0f + erff(a * 0.70710678118654752f)); }
 
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
@@ -32,27 +31,6 @@ __global__ __launch_bounds__(256) void gather_half_kernel(const float4 *__restri
     h[0] = (_Float16)f.x; h[1] = (_Float16)f.y; h[2] = (_Float16)f.z; h[3] = (_Float16)f.w;
     xh[(size_t)i * E4 + c] = h;
 }
-
-template <int MODE>
-struct MultStore {
-    static constexpr int kBytes = (MODE == kEpiGeluHalf) ? 2 : 4;
-    static constexpr int kTableBytes = 0;
-    static constexpr bool kScatter = (MODE == kEpiScatterF32);
-    static constexpr bool kLinear = false;
-    static constexpr bool kSignCodes = false;
-    void *out;                      // compact fp32 rows | fp16 hidden rows | scattered fp32 rows
-    const void *table = nullptr;
-    const float *gate;
-    bool accumulate;
-    explicit MultStore(const Epilogue &epi)
-        : out(MODE == kEpiFloat ? (void *)epi.of : MODE == kEpiGeluHalf ? (void *)epi.hh : (void *)epi.yf),
-          gate(MODE == kEpiScatterF32 ? epi.gate : nullptr),
-          accumulate(MODE == kEpiScatterF32 && epi.accumulate) {}
-    __device__ inline uint32_t convert(float a, int, const uint8_t *) const {
-        if (MODE == kEpiGeluHalf) return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)gelu_erf(a));
-        return __builtin_bit_cast(uint32_t, a);
-    }
-};
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 

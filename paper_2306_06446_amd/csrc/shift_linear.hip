@@ -13,6 +13,7 @@
 #include "common.h"
 #include "gemm_common.h"
 #include "gemm_mfma.h"
+#include "gemm_stores.h"
 
 namespace {
 
@@ -194,53 +195,6 @@ __global__ __launch_bounds__(256) void decode_w4_pair_kernel(const uint4 *__rest
     pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
     pb[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
 }
-
-inline Epilogue with_finite_scale(Epilogue e) {
-    e.rq = requant_scale_finite(e.rq);
-    return e;
-}
-
-template <int MODE>
-struct ShiftStore {
-    static constexpr int kBytes = (MODE == kEpiRequantLut) ? 1 : 4;
-    static constexpr int kTableBytes = (MODE == kEpiRequantLut) ? 256 : 0;
-    static constexpr bool kScatter = (MODE == kEpiScatterI32);
-    static constexpr bool kLinear = (MODE == kEpiLinearF32 || MODE == kEpiQkvCodes);
-    static constexpr bool kSignCodes = (MODE == kEpiQkvCodes);
-    Epilogue e;
-    void *out;             // int32 rows | int8 hidden rows | scattered fp32 rows
-    const void *table;     // the 256-entry activation table
-    const float *gate;
-    bool accumulate;
-    float *parts[3];       // kEpiLinearF32: column blocks, residual and scale
-    int part_width;
-    const float *residual;
-    float scale;
-    uint64_t *codes[2];    // kEpiQkvCodes: sign codes of column blocks 0 and 1
-    int code_cols, head_dim, tokens, heads;
-    explicit ShiftStore(const Epilogue &epi)     // epi.rq is made finite here: convert() relies on it
-        : e(with_finite_scale(epi)),
-          out(MODE == kEpiInt32 ? (void *)epi.y : MODE == kEpiRequantLut ? (void *)epi.h
-              : MODE == kEpiLinearF32 ? (void *)epi.parts[0] : MODE == kEpiQkvCodes ? (void *)epi.parts[2] : (void *)epi.yf),
-          table(epi.lut),
-          gate(MODE == kEpiScatterI32 ? epi.gate : nullptr),
-          accumulate(MODE == kEpiScatterI32 && epi.accumulate),
-          parts{epi.parts[0], epi.parts[1], epi.parts[2]},
-          part_width(epi.part_width > 0 ? epi.part_width : 4),
-          residual(epi.residual),
-          scale(epi.lin_scale),
-          codes{epi.codes[0], epi.codes[1]},
-          code_cols(MODE == kEpiQkvCodes ? 2 * epi.part_width : 0),
-          head_dim(epi.head_dim > 0 ? epi.head_dim : 64),
-          tokens(epi.tokens > 0 ? epi.tokens : 1),
-          heads(epi.heads) {}
-    __device__ inline uint32_t convert(int32_t acc, int n, const uint8_t *lds_table) const {
-        if (MODE == kEpiInt32) return (uint32_t)(acc + (e.bias ? e.bias[n] : 0));
-        if (MODE == kEpiRequantLut) return lds_table[requant_index(acc, e.rq)];
-        if (MODE == kEpiLinearF32 || MODE == kEpiQkvCodes) return __builtin_bit_cast(uint32_t, (float)acc);   // scaled at the store
-        return __builtin_bit_cast(uint32_t, e.out_scale * (float)acc);
-    }
-};
 
 constexpr int kMfmaK = 32;   // K granularity of the MFMA variant (16 bytes of packed weights, 32 of activations)
 // Plane rows are padded with zeros to whole 64-byte LDS stages.
@@ -550,6 +504,25 @@ extern "C" int sa_requant_lut(const int32_t *y, long n, float s, const int8_t *l
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_requant_lut: n too large");
     requant_lut_kernel<<<dim3((unsigned)blocks), dim3(256), 0, sa::as_stream(stream)>>>(y, n, s, lut, h);
     return sa::check_launch("sa_requant_lut");
+}
+
+int sa::shift_linear_planes(const uint8_t *w4, int K, int N, int variant, void *planes, hipStream_t st, const int8_t **out) {
+    *out = variant == SA_VARIANT_MFMA_PREPARED ? reinterpret_cast<const int8_t *>(w4) : static_cast<const int8_t *>(planes);
+    return variant == SA_VARIANT_MFMA_PREPARED ? SA_OK : decode_planes(w4, K, N, planes, st);
+}
+
+int sa::shift_mlp_planes(const uint8_t *w1, const uint8_t *w2, int E, int hid, int variant, long max_rows, void *workspace,
+                         hipStream_t st, const int8_t **planes1, const int8_t **planes2, int8_t **hidden) {
+    *hidden = static_cast<int8_t *>(workspace);
+    if (variant == SA_VARIANT_MFMA_PREPARED) {
+        *planes1 = reinterpret_cast<const int8_t *>(w1);
+        *planes2 = reinterpret_cast<const int8_t *>(w2);
+        return SA_OK;
+    }
+    int8_t *p1 = *hidden + (((size_t)max_rows * hid) + 255) / 256 * 256, *p2 = p1 + planes_bytes(E, hid);
+    *planes1 = p1;
+    *planes2 = p2;
+    return decode_planes_pair(w1, E, hid, p1, w2, hid, E, p2, st);
 }
 
 // workspace layout of sa_shift_mlp: hidden int8 [max_rows, hid] | planes of w1 | planes of w2
