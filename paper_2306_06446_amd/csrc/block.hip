@@ -64,6 +64,41 @@ extern "C" size_t sa_block_workspace_bytes(const sa_block_desc *desc) {
     return L.total;
 }
 
+namespace {
+
+// The two experts of a block or layer, on the rows the routing gave them.  On the matrix cores both run in the same
+// launches, layer by layer; the Shift expert's vector-ALU variant has launches of its own.
+template <class Desc>
+int experts(const Desc &d, const int8_t *xq, const void *xh, int E, long T, const int32_t *perm, const int32_t *counts,
+            const float *gate, int flags, void *mult_ws, size_t mult_ws_bytes, void *shift_ws, size_t shift_ws_bytes,
+            void *stream) {
+    const sa_rows mult_rows{perm, counts, 0, T}, shift_rows{perm, counts, 1, T};
+    if (d.shift_variant != SA_VARIANT_VALU) {
+        SA_REQUIRE(d.shift_variant >= 0 && d.shift_variant <= 3, SA_ERR_INVALID, "experts: unknown shift variant %d", d.shift_variant);
+        SA_REQUIRE(E % 64 == 0 && d.hid % 64 == 0, SA_ERR_SHAPE, "experts: E (%d) and hid (%d) must be multiples of 64", E, d.hid);
+        SA_REQUIRE(E <= 131072 && d.hid <= 131072, SA_ERR_SHAPE, "experts: width too large");
+        SA_REQUIRE(sa::aligned16(d.w1) && sa::aligned16(d.w2) && sa::aligned16(d.lut) && sa::aligned16(d.mw1) &&
+                       sa::aligned16(d.mw2) && sa::aligned16(d.y),
+                   SA_ERR_ALIGN, "experts: pointers must be 16-byte aligned");
+        sa::ExpertPair p{xq, xh, {}, {}, d.y, gate, d.out_scale};
+        const int8_t *w1, *w2;
+        int8_t *hidden;
+        int rc = sa::validate_rows(&shift_rows, &p.shift_rows);
+        if (rc == SA_OK) rc = sa::validate_rows(&mult_rows, &p.mult_rows);
+        if (rc == SA_OK) rc = sa::shift_mlp_planes(d.w1, d.w2, E, d.hid, d.shift_variant, T, shift_ws, sa::as_stream(stream), &w1, &w2, &hidden);
+        if (rc != SA_OK) return rc;
+        return sa::expert_pair_mlp(p, E, d.hid, w1, w2, d.mw1, d.mw2, d.requant_scale, d.lut, flags != 0, hidden, mult_ws,
+                                   sa::as_stream(stream));
+    }
+    int rc = sa_mult_mlp_f16_half(xh, &mult_rows, E, d.hid, d.mw1, d.mw2, nullptr, d.y, gate, 3 | flags, mult_ws, mult_ws_bytes,
+                                  stream);
+    if (rc != SA_OK) return rc;
+    return sa_shift_mlp(xq, &shift_rows, E, d.hid, d.w1, d.w2, d.requant_scale, d.lut, nullptr, d.y, gate, d.out_scale,
+                        d.shift_variant, 3 | flags, shift_ws, shift_ws_bytes, stream);
+}
+
+}  // namespace
+
 extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     sa::clear_error();
     Layout L;
@@ -87,11 +122,7 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     int32_t *expert_of = reinterpret_cast<int32_t *>(ws + L.expert_of);
     int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
     float *gate = reinterpret_cast<float *>(ws + L.gate);
-    // Everything runs on the caller's stream, one kernel after the other.  The two experts are independent
-    // once the routing lists exist (the paper's "experts run in parallel", Sec. 4.2), but each of their GEMMs
-    // fills the chip on its own: running them on two streams was measured and gains nothing (247-252 us against
-    // 248 us per step at the DeiT-Base shape), while a caller that keeps two batches in flight on two streams of
-    // its own is 5 % faster without the library's extra stream and events in the way.
+    // Everything runs on the caller's stream, one kernel after the other.
     if (moe) {
         rc = sa_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
         if (rc != SA_OK) return rc;
@@ -116,21 +147,13 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     }
     if (rc != SA_OK || !mlp) return rc;
 
-    if (moe) {
-        const sa_rows mult_rows{perm, counts, 0, T};
-        rc = sa_mult_mlp_f16_half(xh, &mult_rows, E, d->hid, d->mw1, d->mw2, nullptr, d->y, gate, 3, ws + L.mult_ws,
-                                  L.mult_ws_bytes, stream);
-        if (rc != SA_OK) return rc;
-    }
-
     if (!moe) {
         const sa_rows all{nullptr, nullptr, 0, T};
         return sa_shift_mlp(xq, &all, E, d->hid, d->w1, d->w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
                             d->out_scale, d->shift_variant, 3, ws + L.shift_ws, L.shift_ws_bytes, stream);
     }
-    const sa_rows shift_rows{perm, counts, 1, T};
-    return sa_shift_mlp(xq, &shift_rows, E, d->hid, d->w1, d->w2, d->requant_scale, d->lut, nullptr, d->y, gate,
-                        d->out_scale, d->shift_variant, 3, ws + L.shift_ws, L.shift_ws_bytes, stream);
+    return experts(*d, xq, xh, E, T, perm, counts, gate, 0, ws + L.mult_ws, L.mult_ws_bytes, ws + L.shift_ws, L.shift_ws_bytes,
+                   stream);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -278,12 +301,7 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     float *gate = reinterpret_cast<float *>(ws + L.gate);
     rc = sa_moe_dispatch(logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
     if (rc != SA_OK) return rc;
-    // both experts on the caller's stream; they add to disjoint rows of y
-    const sa_rows mult_rows{perm, counts, 0, T};
-    rc = sa_mult_mlp_f16_half(xh, &mult_rows, E, d->hid, d->mw1, d->mw2, nullptr, d->y, gate, 3 | SA_MLP_ACCUMULATE,
-                              ws + L.mult_ws, L.mult_ws_bytes, stream);
-    if (rc != SA_OK) return rc;
-    const sa_rows shift_rows{perm, counts, 1, T};
-    return sa_shift_mlp(codes8, &shift_rows, E, d->hid, d->w1, d->w2, d->requant_scale, d->lut, nullptr, d->y, gate,
-                        d->out_scale, d->shift_variant, 3 | SA_MLP_ACCUMULATE, ws + L.shift_ws, L.shift_ws_bytes, stream);
+    // the experts add to disjoint rows of y
+    return experts(*d, codes8, xh, E, T, perm, counts, gate, SA_MLP_ACCUMULATE, ws + L.mult_ws, L.mult_ws_bytes,
+                   ws + L.shift_ws, L.shift_ws_bytes, stream);
 }

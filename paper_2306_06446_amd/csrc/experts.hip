@@ -1,0 +1,121 @@
+// Both experts of a two-expert MoE layer by layer (Sec. 4.2): one launch holds the tiles of the Shift expert (int8 x two
+// weight planes) and those of the Mult expert (fp16) for the tokens each was given.
+#include "common.h"
+#include "gemm_common.h"
+#include "gemm_mfma.h"
+#include "gemm_stores.h"
+
+namespace {
+
+using namespace sa;
+
+// Workgroups of the Shift expert first, the Mult expert's behind them.  How many tiles either has is known on the device
+// only (the routing counts): a workgroup past the end of both leaves.
+template <class TileS, class StoreS, class TileM, class StoreM, int OCC>
+__global__ __launch_bounds__(256, OCC) void expert_pair_kernel(GemmArgs gs, StoreS ss, GemmArgs gm, StoreM sm) {
+    constexpr int LDS_S = TileS::template lds_bytes<StoreS>(), LDS_M = TileM::template lds_bytes<StoreM>();
+    constexpr int LDS_BYTES = LDS_S > LDS_M ? LDS_S : LDS_M;
+    static_assert(LDS_BYTES * OCC <= 160 * 1024, "OCC workgroups of these tiles do not fit the LDS of a CU");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_BYTES];
+    const int32_t *rows;
+    long n_shift;
+    resolve_rows(gs.sel, rows, n_shift);
+    const long shift_blocks = tile_blocks<TileS>(n_shift, gs.N, gs.col_groups);      // a multiple of 8
+    if ((long)blockIdx.x < shift_blocks)
+        TileS::template run<StoreS>(gs, ss, blockIdx.x, lds);
+    else
+        TileM::template run<StoreM>(gm, sm, (int)(blockIdx.x - shift_blocks), lds);
+}
+
+template <class TileS, class TileM, int OCC, class StoreS, class StoreM>
+int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
+    GemmArgs s = gs, m = gm;
+    s.col_groups = TileS::col_groups(gs);
+    m.col_groups = TileM::col_groups(gm);
+    // the rows of both add up to max_rows: all on either side, and one more row of tiles per XCD where the other side starts
+    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, gs.N, s.col_groups), all_m = tile_blocks<TileM>(gm.sel.max_rows, gm.N, m.col_groups);
+    const long step_s = tile_blocks<TileS>(1, gs.N, s.col_groups), step_m = tile_blocks<TileM>(1, gm.N, m.col_groups);
+    const long blocks = (all_s > all_m ? all_s : all_m) + step_s + step_m;
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
+    expert_pair_kernel<TileS, StoreS, TileM, StoreM, OCC><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm);
+    return check_launch(what);
+}
+
+// Tile choice.  Up to 640 tiles of 64 x 64 the small tiles of gemm_slice.h, by the lines launch_gemm draws for the rows of
+// both experts together; beyond, from a sweep over routings of 30 / 50 / 70 % (12608 tokens unless said, one launch for both
+// experts against one each):
+//    768 -> 3072  256 x 128 and 192 x 128   112 / 109 / 105 us (128 x 128: 126 / 123 / 116; apart 131 / 130 / 112)
+//   3072 ->  768  192 x 128 both             82 /  81 /  77 us (128 x 128:  97 /  94 /  86; apart 121 / 120 /  88)
+//    768 ->  768  128 x 128 both             34 /  35 /  33 us (192 x 128:  34 /  34 /  34; apart  49 /  47 /  49)
+//    384 -> 1536, 1536 -> 384                42 /  34 us       (192 x 128:  46 /  35; apart 65 / 48)
+//   131072 tokens 256 -> 1024               238 us             (256 x 128: 251; apart 275)
+template <class StoreS, class StoreM>
+int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
+    typedef I8Traits I;
+    typedef F16Traits F;
+    const bool lines = gs.K % 128 == 0 && (gs.a_valid == 0 || gs.a_valid == gs.K);
+    const bool lines_s = lines && gs.K >= 512, lines_m = gm.K % 64 == 0 && gm.K >= 256;
+    auto tiles = [&](long bm, long bn) { return ((gs.sel.max_rows + bm - 1) / bm) * ((gs.N + bn - 1) / bn); };
+    if (tiles(32, 64) <= 256) {
+        if (lines_s) return launch_pair_tiles<SliceTile<I, 1, 2, 128, 4>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
+        if (lines_m) return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
+        return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 64, 8>, 1>(gs, ss, gm, sm, st, what);
+    }
+    if (tiles(64, 64) <= 640) {
+        if (lines_s) return launch_pair_tiles<SliceTile<I, 2, 2, 128, 3>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
+        if (lines_m) return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
+        return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 64, 9>, 2>(gs, ss, gm, sm, st, what);
+    }
+    // more than two rounds of the large Shift tile at two per CU: its higher rate counts for more than an even last round
+    if (lines_s && lines_m && tiles(256, 128) > 1024)
+        return launch_pair_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
+    if (lines_s && lines_m && gs.K >= 2048)
+        return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
+    return launch_pair_tiles<NtTile<I, 128, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 3, 1>, 3>(gs, ss, gm, sm, st, what);
+}
+
+GemmArgs args(const void *a, bool gather, const void *b0, const void *b1, const RowSel &sel, int K, int N) {
+    GemmArgs g;
+    g.a = a;
+    g.gather_a = gather;
+    g.b[0] = b0;
+    g.b[1] = b1;
+    g.sel = sel;
+    g.K = K;
+    g.N = N;
+    return g;
+}
+
+}  // namespace
+
+int sa::expert_pair_mlp(const ExpertPair &p, int E, int hid, const int8_t *w1_planes, const int8_t *w2_planes, const void *mw1,
+                        const void *mw2, float requant_scale, const int8_t *lut, bool accumulate, int8_t *shift_hidden,
+                        void *mult_hidden, hipStream_t st) {
+    Epilogue s1, m1, s2, m2;
+    s1.h = shift_hidden;
+    s1.rq = requant_scale;
+    s1.lut = lut;
+    m1.hh = static_cast<_Float16 *>(mult_hidden);
+    s2.yf = m2.yf = p.y;
+    s2.gate = m2.gate = p.gate;
+    s2.out_scale = p.out_scale;
+    s2.accumulate = m2.accumulate = accumulate;
+    int rc = launch_pair(args(p.xq, true, w1_planes, w1_planes + (size_t)hid * E, p.shift_rows, E, hid), ShiftStore<kEpiRequantLut>(s1),
+                         args(p.xh, true, mw1, nullptr, p.mult_rows, E, hid), MultStore<kEpiGeluHalf>(m1), st, "experts (fc1)");
+    if (rc != SA_OK) return rc;
+    return launch_pair(args(shift_hidden, false, w2_planes, w2_planes + (size_t)E * hid, p.shift_rows, hid, E),
+                       ShiftStore<kEpiScatterI32>(s2), args(mult_hidden, false, mw2, nullptr, p.mult_rows, hid, E),
+                       MultStore<kEpiScatterF32>(m2), st, "experts (fc2)");
+}
+
+int sa::expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes, const void *w_f16, hipStream_t st) {
+    Epilogue s, m;
+    s.yf = m.yf = p.y;
+    s.gate = m.gate = p.gate;
+    s.out_scale = p.out_scale;
+    const int Kp = (K + 63) / 64 * 64;                   // rows of the planes
+    GemmArgs gs = args(p.xq, true, w_planes, w_planes + (size_t)N * Kp, p.shift_rows, Kp, N);
+    gs.a_ld = gs.a_valid = K;
+    return launch_pair(gs, ShiftStore<kEpiScatterI32>(s), args(p.xh, true, w_f16, nullptr, p.mult_rows, K, N),
+                       MultStore<kEpiScatterF32>(m), st, "sa_moe_linear");
+}

@@ -646,6 +646,12 @@ extern "C" int sa_moe_linear(const int8_t *xq, const void *xh, const float *logi
     if (rc != SA_OK) return rc;
     // every token belongs to exactly one expert, so the two scatters write every row of y exactly once
     const sa::RowSel mult_rows{perm, counts, 0, T}, shift_rows{perm, counts, 1, T};
+    if (variant != SA_VARIANT_VALU) {
+        const int8_t *planes;
+        rc = sa::shift_linear_planes(w4, K, N, variant, ws + L.planes, st, &planes);
+        if (rc != SA_OK) return rc;
+        return sa::expert_pair_linear(sa::ExpertPair{xq, xh, shift_rows, mult_rows, y, gate, out_scale}, K, N, planes, w_f16, st);
+    }
     rc = sa::mult_linear_rows(xh, mult_rows, K, N, w_f16, y, gate, st);
     if (rc != SA_OK) return rc;
     return sa::shift_linear_rows(xq, shift_rows, K, N, w4, out_scale, y, gate, variant, ws + L.planes, st);
