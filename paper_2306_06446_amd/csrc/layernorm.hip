@@ -1,9 +1,17 @@
 // LayerNorm of Eq. 2 fused with what its consumers read: the int8 codes of the shift Linears
 // (static per-tensor scale), the fp16 rows of the Mult expert and the router logits (Sec. 4.2).
 //
-// One wavefront owns one row, held in registers (CH float4 per lane), so x is read once:
-// mean, then the centred sum of squares (two passes over registers, no E[x^2] - mean^2
-// cancellation), then the outputs.  HBM-bound: 4 B in and 1 (+2, +4) B out per element.
+// LPR lanes own one row, held in registers (CH float4 per lane), so x is read once: mean, then the
+// centred sum of squares (two passes over registers, no E[x^2] - mean^2 cancellation), then the outputs.
+// Rows of up to 256 elements take as many lanes as they have float4s (16 to 64), several rows to a
+// wavefront.
+//
+// What bounds it: HBM, 4 B in and 1 (+2, +4) B out per element, once enough rows are in flight: the next row
+// of a wavefront is loaded before the sums of the current one, and the sums go through the vector ALU's own
+// lane exchanges (a sum over 64 lanes through LDS shuffles is some 400 cycles, four of them in a row's chain).
+// int8 codes only, one wavefront per row and no row ahead -> now: 25088 x 64 13.5 -> 5.0 us, 16384 x 256 12.1 -> 8.2,
+// 12608 x 768 13.7 -> 12.9 (3.8 TB/s); codes, fp16 rows and router logits: 12608 x 768 19.4 -> 17.9, 50000 x 128
+// 25.9 -> 14.5, 131072 x 256 61.5 -> 52.5.
 #include "common.h"
 #include "gemm_common.h"
 
@@ -13,12 +21,35 @@ using namespace sa;
 
 typedef _Float16 v4h_t __attribute__((ext_vector_type(4)));
 
-constexpr int kRowsPerBlock = 4;      // one wavefront each
+constexpr int kWavesPerBlock = 4;
 constexpr int kMaxExperts = 8;
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+
+template <int CTRL>
+__device__ inline float dpp_add(float v) {
+    const int other = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true);
+    return v + __builtin_bit_cast(float, other);
+}
+
+// Sum over aligned groups of LPR lanes (16, 32 or 64); every lane of a group gets it.
+template <int LPR>
+__device__ inline float group_sum(float v) {
+    v = dpp_add<0xB1>(v);                 // lane ^ 1
+    v = dpp_add<0x4E>(v);                 // lane ^ 2
+    v = dpp_add<0x141>(v);                // mirrored within 8 lanes: the other four
+    v = dpp_add<0x140>(v);                // mirrored within 16 lanes: the other eight
+    if (LPR >= 32) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v);
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        const uint32_t r0 = r[0], r1 = r[1];
+        v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+    }
+    if (LPR == 64) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v);
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        const uint32_t r0 = r[0], r1 = r[1];
+        v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+    }
     return v;
 }
 
@@ -37,21 +68,34 @@ struct LnArgs {
     float *logits;      // [T, n_exp]
 };
 
-// ROUTE: the router has two experts and its weight columns live in registers next to gamma and
+// ROUTE2: the router has two experts and its weight columns live in registers next to gamma and
 // beta (all three depend on the column only), so a wavefront that walks over several rows loads
 // them once.  More experts take the weights from memory (the table is small and stays in cache).
-template <int CH, bool ROUTE2>
-__global__ __launch_bounds__(64 * kRowsPerBlock) void layernorm_kernel(LnArgs a, int rows_per_wave) {
-    const int lane = threadIdx.x & 63;
+template <int LPR, int CH, bool ROUTE2>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void layernorm_kernel(LnArgs a, int rows_per_group) {
+    constexpr int GROUPS = 64 / LPR;              // rows side by side in a wavefront
+    const int lane = threadIdx.x & 63, l = lane % LPR;
     const int E = a.E;
-    const long t0 = ((long)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6)) * rows_per_wave;
-    if (t0 >= a.T) return;
+    // a wavefront walks GROUPS consecutive rows at a time
+    const long t0 = ((long)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * rows_per_group * GROUPS + lane / LPR;
+    if (t0 - lane / LPR >= a.T) return;
     constexpr bool CACHE = CH <= 8;               // wider rows re-read gamma and beta per row (registers)
     constexpr int PC = CACHE ? CH : 1;
+    auto load_row = [&](long t, float4 (&v)[CH]) {
+        const float *row = a.x + (size_t)(t < a.T ? t : a.T - 1) * E;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int j = (c * LPR + l) * 4;
+            v[c] = j < E ? *reinterpret_cast<const float4 *>(row + j) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+    };
+    constexpr bool AHEAD = CH <= 4;               // the next row in flight (registers)
+    float4 nxt[AHEAD ? CH : 1];
+    if constexpr (AHEAD) load_row(t0, nxt);
     float4 gm[PC], bt[PC], w0[PC], w1[PC];
 #pragma unroll
     for (int c = 0; c < PC; ++c) {
-        const int j = (c * 64 + lane) * 4;
+        const int j = (c * LPR + l) * 4;
         const bool in = j < E;
         gm[c] = in ? *reinterpret_cast<const float4 *>(a.gamma + j) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         bt[c] = in ? *reinterpret_cast<const float4 *>(a.beta + j) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -60,34 +104,38 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void layernorm_kernel(LnArgs a,
             w1[c] = in ? *reinterpret_cast<const float4 *>(a.wg + 2 * j + 4) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
     }
-    const long t_end = t0 + rows_per_wave < a.T ? t0 + rows_per_wave : a.T;
-    for (long t = t0; t < t_end; ++t) {
-        const float *row = a.x + (size_t)t * E;
+    for (int it = 0; it < rows_per_group; ++it) {
+        const long t = t0 + (long)it * GROUPS;
+        if (t - lane / LPR >= a.T) return;        // the whole wavefront is past the end
+        const bool row_ok = t < a.T;
         float4 v[CH];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) v[c] = nxt[c];
+            if (it + 1 < rows_per_group) load_row(t + GROUPS, nxt);
+        } else {
+            load_row(t, v);
+        }
         float s = 0.0f;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int j = (c * 64 + lane) * 4;
-            v[c] = j < E ? *reinterpret_cast<const float4 *>(row + j) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            s += (v[c].x + v[c].y) + (v[c].z + v[c].w);
-        }
-        const float mean = wave_sum(s) / (float)E;
+        for (int c = 0; c < CH; ++c) s += (v[c].x + v[c].y) + (v[c].z + v[c].w);
+        const float mean = group_sum<LPR>(s) / (float)E;
         float ss = 0.0f;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int j = (c * 64 + lane) * 4;
+            const int j = (c * LPR + l) * 4;
             if (j < E) {
                 const float d0 = v[c].x - mean, d1 = v[c].y - mean, d2 = v[c].z - mean, d3 = v[c].w - mean;
                 ss += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
             }
         }
-        const float rstd = 1.0f / __builtin_sqrtf(wave_sum(ss) / (float)E + a.eps);
+        const float rstd = 1.0f / __builtin_sqrtf(group_sum<LPR>(ss) / (float)E + a.eps);
         float part[kMaxExperts];
 #pragma unroll
         for (int e = 0; e < kMaxExperts; ++e) part[e] = 0.0f;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int j = (c * 64 + lane) * 4;
+            const int j = (c * LPR + l) * 4;
             if (j >= E) continue;
             const float4 g = CACHE ? gm[CACHE ? c : 0] : *reinterpret_cast<const float4 *>(a.gamma + j);
             const float4 b = CACHE ? bt[CACHE ? c : 0] : *reinterpret_cast<const float4 *>(a.beta + j);
@@ -96,19 +144,19 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void layernorm_kernel(LnArgs a,
             y[1] = (v[c].y - mean) * rstd * g.y + b.y;
             y[2] = (v[c].z - mean) * rstd * g.z + b.z;
             y[3] = (v[c].w - mean) * rstd * g.w + b.w;
-            const size_t o = (size_t)t * E + j;
-            if (a.ln) *reinterpret_cast<float4 *>(a.ln + o) = make_float4(y[0], y[1], y[2], y[3]);
-            if (a.q) {
-                uint32_t w = 0;
+            if (row_ok) {
+                const size_t o = (size_t)t * E + j;
+                if (a.ln) *reinterpret_cast<float4 *>(a.ln + o) = make_float4(y[0], y[1], y[2], y[3]);
+                if (a.q)
+                    *reinterpret_cast<uint32_t *>(a.q + o) =
+                        requant_byte(y[0] * a.inv_scale) | (requant_byte(y[1] * a.inv_scale) << 8) |
+                        (requant_byte(y[2] * a.inv_scale) << 16) | (requant_byte(y[3] * a.inv_scale) << 24);
+                if (a.xh) {
+                    v4h_t h;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) w |= (uint32_t)(uint8_t)requant_code(y[i] * a.inv_scale) << (8 * i);
-                *reinterpret_cast<uint32_t *>(a.q + o) = w;
-            }
-            if (a.xh) {
-                v4h_t h;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) h[i] = (_Float16)y[i];
-                *reinterpret_cast<v4h_t *>(a.xh + o) = h;
+                    for (int i = 0; i < 4; ++i) h[i] = (_Float16)y[i];
+                    *reinterpret_cast<v4h_t *>(a.xh + o) = h;
+                }
             }
             if (ROUTE2 && CACHE) {
                 part[0] = __builtin_fmaf(y[0], w0[c].x, part[0]);
@@ -131,26 +179,28 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void layernorm_kernel(LnArgs a,
 #pragma unroll
             for (int e = 0; e < kMaxExperts; ++e) {
                 if (e >= a.n_exp) break;
-                const float sum = wave_sum(part[e]);
-                if (lane == 0) a.logits[(size_t)t * a.n_exp + e] = sum + a.bg[e];
+                const float sum = group_sum<LPR>(part[e]);
+                if (l == 0 && row_ok) a.logits[(size_t)t * a.n_exp + e] = sum + a.bg[e];
             }
         }
     }
 }
 
-template <int CH>
+template <int LPR, int CH>
 int launch(const LnArgs &a, hipStream_t st) {
-    // a few rows per wavefront amortise the per-column parameters; keep >= ~2000 wavefronts in flight
-    int rows_per_wave = 1;
-    while (rows_per_wave < 8 && a.T / (2 * rows_per_wave) >= 2048) rows_per_wave *= 2;
-    const long waves = (a.T + rows_per_wave - 1) / rows_per_wave;
-    const long blocks = (waves + kRowsPerBlock - 1) / kRowsPerBlock;
+    // up to four rows per lane group amortise the per-column parameters; keep >= 4096 wavefronts (16 per CU) in flight
+    constexpr int GROUPS = 64 / LPR;
+    const long steps = (a.T + GROUPS - 1) / GROUPS;
+    int rows_per_group = 1;
+    while (rows_per_group < 4 && steps / (2 * rows_per_group) >= 4096) rows_per_group *= 2;
+    const long waves = (steps + rows_per_group - 1) / rows_per_group;
+    const long blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_layernorm_quant: too many rows");
-    const dim3 grid((unsigned)blocks), block(64 * kRowsPerBlock);
+    const dim3 grid((unsigned)blocks), block(64 * kWavesPerBlock);
     if (a.logits && a.n_exp == 2 && CH <= 8)
-        layernorm_kernel<CH, true><<<grid, block, 0, st>>>(a, rows_per_wave);
+        layernorm_kernel<LPR, CH, true><<<grid, block, 0, st>>>(a, rows_per_group);
     else
-        layernorm_kernel<CH, false><<<grid, block, 0, st>>>(a, rows_per_wave);
+        layernorm_kernel<LPR, CH, false><<<grid, block, 0, st>>>(a, rows_per_group);
     return check_launch("sa_layernorm_quant");
 }
 
@@ -181,11 +231,13 @@ extern "C" int sa_layernorm_quant(const float *x, long T, int E, const float *ga
              route ? wg_or_null : nullptr, route ? bg_or_null : nullptr, route ? n_experts : 0, logits_or_null};
     hipStream_t st = sa::as_stream(stream);
     const int ch = (E + 255) / 256;
-    if (ch <= 1) return launch<1>(a, st);
-    if (ch <= 2) return launch<2>(a, st);
-    if (ch <= 3) return launch<3>(a, st);
-    if (ch <= 4) return launch<4>(a, st);
-    if (ch <= 8) return launch<8>(a, st);
-    if (ch <= 16) return launch<16>(a, st);
-    return launch<32>(a, st);
+    if (E <= 64) return launch<16, 1>(a, st);
+    if (E <= 128) return launch<32, 1>(a, st);
+    if (ch <= 1) return launch<64, 1>(a, st);
+    if (ch <= 2) return launch<64, 2>(a, st);
+    if (ch <= 3) return launch<64, 3>(a, st);
+    if (ch <= 4) return launch<64, 4>(a, st);
+    if (ch <= 8) return launch<64, 8>(a, st);
+    if (ch <= 16) return launch<64, 16>(a, st);
+    return launch<64, 32>(a, st);
 }
