@@ -47,7 +47,8 @@ int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, 
 //    768 -> 3072  256 x 128 and 192 x 128   112 / 109 / 105 us (128 x 128: 126 / 123 / 116; apart 131 / 130 / 112)
 //   3072 ->  768  192 x 128 both             82 /  81 /  77 us (128 x 128:  97 /  94 /  86; apart 121 / 120 /  88)
 //    768 ->  768  128 x 128 both             34 /  35 /  33 us (192 x 128:  34 /  34 /  34; apart  49 /  47 /  49)
-//    384 -> 1536, 1536 -> 384                42 /  34 us       (192 x 128:  46 /  35; apart 65 / 48)
+//    384 -> 1536                128 x 128 both  44 / 41 / 42 us    (192 x 128:  46 /  46 /  47; apart  64 /  66 /  55)
+//   1536 ->  384, 384 -> 384    128 x 64 and 64 x 128   33 and 16 us   (128 x 128: 35 and 20; apart 48 and 35)
 //   131072 tokens 256 -> 1024               238 us             (256 x 128: 251; apart 275)
 template <class StoreS, class StoreM>
 int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
@@ -71,6 +72,9 @@ int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const 
         return launch_pair_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
     if (lines_s && lines_m && gs.K >= 2048)
         return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
+    // not half of the chip's 768 places: finer tiles
+    if (lines_m && tiles(128, 128) <= 384)
+        return launch_pair_tiles<NtTile<I, 128, 64, 64, 3, 1>, NtTile<F, 64, 128, 128, 2, 2>, 3>(gs, ss, gm, sm, st, what);
     return launch_pair_tiles<NtTile<I, 128, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 3, 1>, 3>(gs, ss, gm, sm, st, what);
 }
 

@@ -409,10 +409,11 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     }
 
     // Transposed tile: accumulator register r of lane l holds row l % 32, column 8 (r / 4) + 4 (l / 32) + r % 4.
-    // ---- sign codes: a wavefront's 64 columns are one code word of a head; each half-wavefront has every other nibble.
+    // ---- sign codes: a wavefront's columns are one code word of a head or half of one; each half-wavefront has every
+    //      other nibble.
     if constexpr (Store::kSignCodes) {
         if (n0 < store.code_cols) {               // uniform per workgroup
-            static_assert(NJ == 2, "a wavefront must own 64 columns");
+            static_assert(NJ <= 2, "a wavefront's columns lie inside one code word");
             const int col0 = n0 + wn;
             const int part = col0 / store.part_width;
             const int cin = col0 - part * store.part_width;
@@ -420,9 +421,9 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
             uint64_t *dst = part == 0 ? store.codes[0] : store.codes[1];
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
-                uint32_t word[2];
+                uint32_t word[NJ];
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     uint32_t neg = 0;
 #pragma unroll
                     for (int r = 15; r >= 0; --r) {
@@ -435,7 +436,11 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
                 const long m = m0 + wm + i * 32 + fr;
                 if (fg == 0 && m < n_rows) {
                     const long b = m / store.tokens, n = m % store.tokens;
-                    dst[((size_t)(b * store.heads + head) * store.tokens + n) * W + w] = word[0] | ((uint64_t)word[1] << 32);
+                    uint64_t *at = dst + ((size_t)(b * store.heads + head) * store.tokens + n) * W + w;
+                    if constexpr (NJ == 2)
+                        *at = word[0] | ((uint64_t)word[NJ - 1] << 32);
+                    else
+                        reinterpret_cast<uint32_t *>(at)[cin / 32 & 1] = word[0];
                 }
             }
             return;
@@ -553,8 +558,12 @@ namespace sa {
 //    256 x 128 tiles, 3152 x 768 <- 768: 11.7 against 12.2; fp16 with long rows only up to 320: the next tile up
 //    catches up there).  Short rows take 64-byte stages: with few stages the finer ones start sooner
 //    (1379 x 1024 <- 256 int8: 5.7 us against 6.1);
-//  * beyond, the tiles of gemm_mfma.h.  Long int8 rows (>= 2 KiB, whole 128-byte lines): 256 x 128, 128-byte stages,
-//    one workgroup per CU.  Other int8 rows: 256 x 128 (two per CU) or 128 x 128 (three per CU) with 64-byte stages;
+//  * beyond, the tiles of this file.  int8 rows of 2 KiB and more in whole 128-byte lines: 128 x 64, 128-byte stages, two
+//    per CU (with a residual, 8826 x 768 <- 3072: 53 us against 61 with 256 x 128 tiles, of which 210 leave 46 CUs idle);
+//    from about three rounds of those on, 192 x 128 with 64-byte stages (43690 rows: 253 against 275).  Other int8 rows:
+//    128 x 64, three per CU with a ring of three, where 128 x 128 tiles would not fill the chip once or half of their
+//    columns would be padding (with a residual, 16384 x 256 <- 1024: 18.9 against 23.8; 12608 x 384 <- 384: 15.9
+//    against 21.0); else 256 x 128 (two per CU) or 128 x 128 (three per CU) with 64-byte stages;
 //    they do the same work per CU and second, so the one whose last round of workgroups is fuller
 //    (12608 x 1536 <- 384: 38 against 29 us; 12608 x 3072 <- 768: 76 against 82).  fp16: long rows 128 x 128 with a
 //    ring of three; rows of more than 768 bytes 192 x 128, both one per CU; short rows 128 x 128 with 64-byte stages.
@@ -583,7 +592,10 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
         if (tiles(64, 64) <= 640)
             return whole_line_stages ? launch_tile<SliceTile<T, 2, 2, 128, 3>, 1>(g, store, st, what)
                                      : launch_tile<SliceTile<T, 2, 2, 64, 6>, 1>(g, store, st, what);
-        if (lines && long_rows) return launch_tile<NtTile<T, 256, 128, 128, 2, 2>, 1>(g, store, st, what);
+        if (lines && long_rows)
+            return tiles(128, 128) <= 1536 ? launch_tile<NtTile<T, 128, 64, 128, 2, 2>, 2>(g, store, st, what)
+                                           : launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
+        if (tiles(128, 128) <= 768 || g.N <= 64) return launch_tile<NtTile<T, 128, 64, 64, 3, 1>, 3>(g, store, st, what);
         const long rounds256 = (tiles(256, 128) + 511) / 512, rounds128 = (tiles(128, 128) + 767) / 768;
         const bool wide = counted ? ((g.sel.max_rows + 255) / 256) * ((g.N + 127) / 128) >= 512    // no rounds to speak of
                                   : rounds256 * 5 <= rounds128 * 4;      // a round of the larger tiles takes 1.25 times as long

@@ -21,7 +21,9 @@ def decode(w4):
     (4129, 64, 256), (2081, 224, 512), (1300, 96, 1000),                # 64-row tiles, 64-byte stages
     (1379, 512, 900), (965, 3072, 768), (4161, 768, 260),               # 64-row tiles, 128-byte stages
     (6337, 192, 768), (6401, 768, 768), (12609, 160, 1540),             # 128 x 128
-    (12801, 768, 1300), (6400, 3072, 768),                              # 256 x 128
+    (12801, 768, 1300), (6400, 3072, 768),                              # 256 x 128, long rows
+    (2003, 96, 1700), (50001, 64, 60), (2003, 2048, 1700),              # 128 x 64, both stage widths
+    (13001, 2048, 2048),                                                # 192 x 128
 ])
 def test_shift_linear_at_the_borders_of_the_tile_choice(sa, M, K, N):
     w4 = wl.shift_weights(3, 5, N, K)
@@ -64,3 +66,19 @@ def test_mult_expert_at_the_borders_of_the_tile_choice(sa, rows, E, hid):
     assert bool((err <= 1e-3 + 2e-3 * ref.abs()).all()), float(err.max())
     rest = perm[rows:].long()
     assert bool((y[rest] == 7.0).all())
+
+
+@pytest.mark.parametrize("B,N,H,d", [(1, 50, 2, 64), (7, 197, 12, 64), (3, 300, 6, 128), (26, 500, 6, 128), (32, 197, 12, 64)])
+def test_sign_codes_of_every_tile_width(sa, B, N, H, d):
+    E = H * d
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * N)
+    x = torch.randint(-127, 128, (B * N, E), generator=g, device="cuda", dtype=torch.int8)
+    w = sa.sa_shift_planes_prepare(dev(wl.shift_weights(3, 5, 3 * E, E)))
+    qc, kc, v = sa.sa_shift_linear_qkv_codes(x, w, B, N, H, 0.5, variant=3)
+    q, k, ref_v = sa.sa_shift_linear_f32(x, w, 0.5, parts=3, variant=3)
+    assert torch.equal(v.flatten(), ref_v.flatten())
+    weight = torch.tensor([1 << j for j in range(63)] + [-(1 << 63)], device="cuda")
+    for got, f in ((qc, q), (kc, k)):
+        bits = (f.view(B, N, H, d // 64, 64) >= 0).to(torch.int64)
+        assert torch.equal(got, (bits * weight).sum(-1).permute(0, 2, 1, 3))
