@@ -22,7 +22,6 @@ using namespace sa;
 typedef _Float16 v4h_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWavesPerBlock = 4;
-constexpr int kMaxExperts = 8;
 
 
 template <int CTRL>
@@ -31,25 +30,26 @@ __device__ inline float dpp_add(float v) {
     return v + __builtin_bit_cast(float, other);
 }
 
-// Sum over aligned groups of LPR lanes (16, 32 or 64); every lane of a group gets it.
+// Sum over aligned groups of LPR lanes (16, 32 or 64) as a butterfly, the most distant lanes first; every lane of a group
+// gets it.  Once lanes 8 apart agree, a rotation of the 16 lanes of a row by 4 (then 2, 1) is an exchange of neighbours.
 template <int LPR>
 __device__ inline float group_sum(float v) {
-    v = dpp_add<0xB1>(v);                 // lane ^ 1
-    v = dpp_add<0x4E>(v);                 // lane ^ 2
-    v = dpp_add<0x141>(v);                // mirrored within 8 lanes: the other four
-    v = dpp_add<0x140>(v);                // mirrored within 16 lanes: the other eight
-    if (LPR >= 32) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, v);
-        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-        const uint32_t r0 = r[0], r1 = r[1];
-        v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
-    }
     if (LPR == 64) {
         const uint32_t u = __builtin_bit_cast(uint32_t, v);
         const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
         const uint32_t r0 = r[0], r1 = r[1];
         v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
     }
+    if (LPR >= 32) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v);
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        const uint32_t r0 = r[0], r1 = r[1];
+        v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+    }
+    v = dpp_add<0x128>(v);                // row_ror:8
+    v = dpp_add<0x124>(v);                // row_ror:4
+    v = dpp_add<0x122>(v);                // row_ror:2
+    v = dpp_add<0x121>(v);                // row_ror:1
     return v;
 }
 
