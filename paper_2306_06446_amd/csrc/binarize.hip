@@ -71,6 +71,12 @@ extern "C" int sa_binarize(const float *x, int B, int N, int H, int d, const flo
     return sa_binarize_ex(x, B, N, H, d, proj, nbits, codes, SA_VARIANT_AUTO, stream);
 }
 
+bool sa::binarize_pair_one_launch(const float *q, const float *k, const float *proj, const uint64_t *q_codes,
+                                  const uint64_t *k_codes, long rows, int d, int nbits) {
+    return proj != nullptr && rows > 0 && rows < (1L << 31) && binarize_mfma_supported(d, nbits) && nbits <= 4096 && q && k &&
+           q_codes && k_codes && aligned16(q) && aligned16(k) && aligned16(proj) && aligned16(q_codes) && aligned16(k_codes);
+}
+
 extern "C" int sa_binarize_pair(const float *q, const float *k, int B, int N, int H, int d, const float *proj,
                                 int nbits, uint64_t *q_codes, uint64_t *k_codes, void *stream) {
     sa::clear_error();
@@ -82,9 +88,7 @@ extern "C" int sa_binarize_pair(const float *q, const float *k, int B, int N, in
                    "sa_binarize_pair: pointers must be 16-byte aligned");
     }
     // one launch when the matrix-core kernel takes the shape; otherwise simply one call per tensor
-    if (proj != nullptr && B > 0 && N > 0 && H > 0 && rows < (1L << 31) && sa::binarize_mfma_supported(d, nbits) &&
-        nbits <= 4096 && q && k && q_codes && k_codes && sa::aligned16(q) && sa::aligned16(k) && sa::aligned16(proj) &&
-        sa::aligned16(q_codes) && sa::aligned16(k_codes))
+    if (B > 0 && N > 0 && H > 0 && sa::binarize_pair_one_launch(q, k, proj, q_codes, k_codes, rows, d, nbits))
         return sa::launch_binarize_mfma(q, k, proj, q_codes, k_codes, rows, N, H, d, nbits, sa::as_stream(stream));
     const int rc = sa_binarize_ex(q, B, N, H, d, proj, nbits, q_codes, SA_VARIANT_AUTO, stream);
     if (rc != SA_OK) return rc;

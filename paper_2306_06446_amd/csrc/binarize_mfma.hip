@@ -26,6 +26,7 @@
 // between two lanes.  Q and K, before -> now: 8 x 16384 x 4 heads x 64 -> 256 bits 143 -> 116 us, 1 x 16384 x 4 the
 // same 24.3 -> 22.8, 64 x 197 x 12 x 64 -> 128 bits 28.7 -> 28.3.
 #include "common.h"
+#include "side_work.h"
 
 namespace sa {
 
@@ -111,7 +112,8 @@ __device__ inline void settle_entry(uint64_t e, const Tensors &ts, const float *
 // D: head dim; C: hash columns of a workgroup (blockIdx.y selects the group); kWaves: its wavefronts.
 template <int D, int C, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, const float *__restrict__ proj, uint32_t rows,
-                                                                    RowMap map, int nbits, uint32_t n_tiles, uint32_t n_total) {
+                                                                    RowMap map, int nbits, uint32_t n_tiles, uint32_t n_total,
+                                                                    uint32_t hash_blocks, SideWork side) {
     constexpr int S = D / 32;                     // MFMA steps along k
     constexpr int T = C / 16;                     // 16-column tiles
     constexpr int GROUPS = T / 4;                 // of four tiles: 16 bits of a lane
@@ -125,6 +127,10 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
     __shared__ uint64_t list_s[kWaves][kListCap];
     __shared__ int cnt_s[kWaves];
 
+    if (blockIdx.x >= hash_blocks) {
+        side_block<kWaves * 64>(side, (long)(blockIdx.x - hash_blocks) * gridDim.y + blockIdx.y);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -144,7 +150,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
             for (int j = 0; j < L4; ++j) xn[u][j] = *reinterpret_cast<const float4 *>(xr + 16 * j);
         }
     };
-    const uint32_t tile_step = gridDim.x * kWaves;
+    const uint32_t tile_step = hash_blocks * kWaves;
     uint32_t tile = blockIdx.x * kWaves + wave;
     if (tile < n_total) load_tile(tile);
 
@@ -410,46 +416,49 @@ bool binarize_mfma_supported(int d, int nbits) {
 
 template <int D, int C, int kWaves>
 int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &map, int nbits, long n_tiles, long n_total,
-                 hipStream_t st) {
+                 const SideWork &side, hipStream_t st) {
     // one workgroup per CU (what the registers allow) over all column groups, every wavefront the same number of tiles
     const long waves = 256 / (nbits / C) * kWaves;
     const long tiles_per_wave = (n_total + waves - 1) / waves;
     const long blocks = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
-    const dim3 grid((unsigned)blocks, (unsigned)(nbits / C));
-    binarize_mfma_kernel<D, C, kWaves><<<grid, dim3(kWaves * 64), 0, st>>>(ts, proj, (uint32_t)rows, map, nbits,
-                                                                          (uint32_t)n_tiles, (uint32_t)n_total);
+    // what rides along comes behind the tiles: it fills the CUs that are done first
+    const long more = (side_blocks(side, kWaves * 64) + nbits / C - 1) / (nbits / C);
+    const dim3 grid((unsigned)(blocks + more), (unsigned)(nbits / C));
+    binarize_mfma_kernel<D, C, kWaves><<<grid, dim3(kWaves * 64), 0, st>>>(
+        ts, proj, (uint32_t)rows, map, nbits, (uint32_t)n_tiles, (uint32_t)n_total, (uint32_t)blocks, side);
     return check_launch("sa_binarize(mfma)");
 }
 
 // Workgroups of 8 wavefronts, of 4 where those already have one tile each: two wavefronts of one tile on a SIMD only
 // take turns (1 x 197 x 3 heads x 64 -> 64 bits: 7.6 -> 7.0 us).
 template <int D, int C>
-int launch_one(const Tensors &ts, int count, const float *proj, long rows, int N, int H, int nbits, hipStream_t st) {
+int launch_one(const Tensors &ts, int count, const float *proj, long rows, int N, int H, int nbits, const SideWork &side,
+               hipStream_t st) {
     const long n_tiles = (rows + 31) / 32, n_total = n_tiles * count;
     const RowMap map{FastDiv((uint32_t)H), FastDiv((uint32_t)N), N, H, nbits / 64};
-    return n_total <= 256 / (nbits / C) * 4 ? launch_waves<D, C, 4>(ts, proj, rows, map, nbits, n_tiles, n_total, st)
-                                            : launch_waves<D, C, 8>(ts, proj, rows, map, nbits, n_tiles, n_total, st);
+    return n_total <= 256 / (nbits / C) * 4 ? launch_waves<D, C, 4>(ts, proj, rows, map, nbits, n_tiles, n_total, side, st)
+                                            : launch_waves<D, C, 8>(ts, proj, rows, map, nbits, n_tiles, n_total, side, st);
 }
 
 // x1 / codes1 may be null: one tensor.  Columns of a workgroup: as many of the code as divide it, up to 256 (128 at
 // d = 128: what the LDS holds), so that the rows are read and split as few times as possible.
 int launch_binarize_mfma(const float *x0, const float *x1, const float *proj, uint64_t *codes0, uint64_t *codes1,
-                         long rows, int N, int H, int d, int nbits, hipStream_t st) {
+                         long rows, int N, int H, int d, int nbits, hipStream_t st, const SideWork &side) {
     const Tensors ts{x0, x1, codes0, codes1};
     const int count = x1 ? 2 : 1;
     const bool c128 = (nbits % 128 == 0), c256 = (nbits % 256 == 0);
     switch (d) {
         case 32:
-            return c256   ? launch_one<32, 256>(ts, count, proj, rows, N, H, nbits, st)
-                   : c128 ? launch_one<32, 128>(ts, count, proj, rows, N, H, nbits, st)
-                          : launch_one<32, 64>(ts, count, proj, rows, N, H, nbits, st);
+            return c256   ? launch_one<32, 256>(ts, count, proj, rows, N, H, nbits, side, st)
+                   : c128 ? launch_one<32, 128>(ts, count, proj, rows, N, H, nbits, side, st)
+                          : launch_one<32, 64>(ts, count, proj, rows, N, H, nbits, side, st);
         case 64:
-            return c256   ? launch_one<64, 256>(ts, count, proj, rows, N, H, nbits, st)
-                   : c128 ? launch_one<64, 128>(ts, count, proj, rows, N, H, nbits, st)
-                          : launch_one<64, 64>(ts, count, proj, rows, N, H, nbits, st);
+            return c256   ? launch_one<64, 256>(ts, count, proj, rows, N, H, nbits, side, st)
+                   : c128 ? launch_one<64, 128>(ts, count, proj, rows, N, H, nbits, side, st)
+                          : launch_one<64, 64>(ts, count, proj, rows, N, H, nbits, side, st);
         default:
-            return c128 ? launch_one<128, 128>(ts, count, proj, rows, N, H, nbits, st)
-                        : launch_one<128, 64>(ts, count, proj, rows, N, H, nbits, st);
+            return c128 ? launch_one<128, 128>(ts, count, proj, rows, N, H, nbits, side, st)
+                        : launch_one<128, 64>(ts, count, proj, rows, N, H, nbits, side, st);
     }
 }
 

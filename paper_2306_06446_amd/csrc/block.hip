@@ -66,35 +66,65 @@ extern "C" size_t sa_block_workspace_bytes(const sa_block_desc *desc) {
 
 namespace {
 
+// What the matrix-core MLP asks of its operands; checked before anything is launched.
+template <class Desc>
+int check_mlp(const Desc &d, int E) {
+    SA_REQUIRE(d.shift_variant >= 0 && d.shift_variant <= 3, SA_ERR_INVALID, "MLP: unknown shift variant %d", d.shift_variant);
+    SA_REQUIRE(E % 64 == 0 && d.hid % 64 == 0, SA_ERR_SHAPE, "MLP: E (%d) and hid (%d) must be multiples of 64", E, d.hid);
+    SA_REQUIRE(E <= 131072 && d.hid <= 131072, SA_ERR_SHAPE, "MLP: width too large");
+    SA_REQUIRE(sa::aligned16(d.w1) && sa::aligned16(d.w2) && sa::aligned16(d.lut) && sa::aligned16(d.y) &&
+                   (!d.moe || (sa::aligned16(d.mw1) && sa::aligned16(d.mw2))),
+               SA_ERR_ALIGN, "MLP: pointers must be 16-byte aligned");
+    return SA_OK;
+}
+
+// The Shift weights of an MLP as its layers take them: packed ones that the matrix cores need decoded become a job for a
+// launch before the MLP, and the planes that job fills take their place (the prepared variant).
+struct ShiftWeights {
+    const uint8_t *w1, *w2;
+    int variant;
+    template <class Desc>
+    ShiftWeights(const Desc &d, int E, long T, void *shift_ws, sa::DecodeWork *work) : w1(d.w1), w2(d.w2), variant(d.shift_variant) {
+        if (variant != SA_VARIANT_MFMA && variant != SA_VARIANT_AUTO) return;
+        sa::shift_mlp_decode(work, d.w1, d.w2, E, d.hid, T, shift_ws, &w1, &w2);
+        variant = SA_VARIANT_MFMA_PREPARED;
+    }
+};
+
+// Hash of Q and K, carrying `side` where it is one launch.
+int hash_and_side(const float *q, const float *k, int B, int N, int H, int d, const float *proj, int nbits, uint64_t *qc,
+                  uint64_t *kc, const sa::SideWork &side, void *stream) {
+    if (side.any() && sa::binarize_pair_one_launch(q, k, proj, qc, kc, (long)B * N * H, d, nbits))
+        return sa::launch_binarize_mfma(q, k, proj, qc, kc, (long)B * N * H, N, H, d, nbits, sa::as_stream(stream), side);
+    int rc = SA_OK;
+    const sa::RouteWork &r = side.route;
+    if (r.T > 0) rc = sa::moe_dispatch_launch(r.logits, r.T, r.E, r.perm, r.expert_of, r.counts, r.gate, nullptr, sa::as_stream(stream));
+    if (rc == SA_OK && side.decode.chunks[0] > 0) rc = sa::launch_decode_work(side.decode, sa::as_stream(stream));
+    if (rc != SA_OK) return rc;
+    return sa_binarize_pair(q, k, B, N, H, d, proj, nbits, qc, kc, stream);
+}
+
 // The two experts of a block or layer, on the rows the routing gave them.  On the matrix cores both run in the same
 // launches, layer by layer; the Shift expert's vector-ALU variant has launches of its own.
 template <class Desc>
-int experts(const Desc &d, const int8_t *xq, const void *xh, int E, long T, const int32_t *perm, const int32_t *counts,
-            const float *gate, int flags, void *mult_ws, size_t mult_ws_bytes, void *shift_ws, size_t shift_ws_bytes,
-            void *stream) {
+int experts(const Desc &d, const ShiftWeights &w, const int8_t *xq, const void *xh, int E, long T, const int32_t *perm,
+            const int32_t *counts, const float *gate, int flags, void *mult_ws, size_t mult_ws_bytes, void *shift_ws,
+            size_t shift_ws_bytes, void *stream) {
     const sa_rows mult_rows{perm, counts, 0, T}, shift_rows{perm, counts, 1, T};
-    if (d.shift_variant != SA_VARIANT_VALU) {
-        SA_REQUIRE(d.shift_variant >= 0 && d.shift_variant <= 3, SA_ERR_INVALID, "experts: unknown shift variant %d", d.shift_variant);
-        SA_REQUIRE(E % 64 == 0 && d.hid % 64 == 0, SA_ERR_SHAPE, "experts: E (%d) and hid (%d) must be multiples of 64", E, d.hid);
-        SA_REQUIRE(E <= 131072 && d.hid <= 131072, SA_ERR_SHAPE, "experts: width too large");
-        SA_REQUIRE(sa::aligned16(d.w1) && sa::aligned16(d.w2) && sa::aligned16(d.lut) && sa::aligned16(d.mw1) &&
-                       sa::aligned16(d.mw2) && sa::aligned16(d.y),
-                   SA_ERR_ALIGN, "experts: pointers must be 16-byte aligned");
+    if (w.variant == SA_VARIANT_MFMA_PREPARED) {
         sa::ExpertPair p{xq, xh, {}, {}, d.y, gate, d.out_scale};
-        const int8_t *w1, *w2;
-        int8_t *hidden;
         int rc = sa::validate_rows(&shift_rows, &p.shift_rows);
         if (rc == SA_OK) rc = sa::validate_rows(&mult_rows, &p.mult_rows);
-        if (rc == SA_OK) rc = sa::shift_mlp_planes(d.w1, d.w2, E, d.hid, d.shift_variant, T, shift_ws, sa::as_stream(stream), &w1, &w2, &hidden);
         if (rc != SA_OK) return rc;
-        return sa::expert_pair_mlp(p, E, d.hid, w1, w2, d.mw1, d.mw2, d.requant_scale, d.lut, flags != 0, hidden, mult_ws,
+        return sa::expert_pair_mlp(p, E, d.hid, reinterpret_cast<const int8_t *>(w.w1), reinterpret_cast<const int8_t *>(w.w2), d.mw1,
+                                   d.mw2, d.requant_scale, d.lut, flags != 0, static_cast<int8_t *>(shift_ws), mult_ws,
                                    sa::as_stream(stream));
     }
     int rc = sa_mult_mlp_f16_half(xh, &mult_rows, E, d.hid, d.mw1, d.mw2, nullptr, d.y, gate, 3 | flags, mult_ws, mult_ws_bytes,
                                   stream);
     if (rc != SA_OK) return rc;
-    return sa_shift_mlp(xq, &shift_rows, E, d.hid, d.w1, d.w2, d.requant_scale, d.lut, nullptr, d.y, gate, d.out_scale,
-                        d.shift_variant, 3 | flags, shift_ws, shift_ws_bytes, stream);
+    return sa_shift_mlp(xq, &shift_rows, E, d.hid, w.w1, w.w2, d.requant_scale, d.lut, nullptr, d.y, gate, d.out_scale, w.variant,
+                        3 | flags, shift_ws, shift_ws_bytes, stream);
 }
 
 }  // namespace
@@ -123,12 +153,22 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
     float *gate = reinterpret_cast<float *>(ws + L.gate);
     // Everything runs on the caller's stream, one kernel after the other.
+    // The routing and the decode of packed Shift weights wait for nothing: they ride in the hash's launch.
+    if (d->hid > 0) rc = check_mlp(*d, E);
+    if (rc != SA_OK) return rc;
+    sa::SideWork side;
     if (moe) {
-        rc = sa_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
-        if (rc != SA_OK) return rc;
+        if (T <= sa::kSideRouteTokens) {
+            SA_REQUIRE(sa::aligned16(d->logits), SA_ERR_ALIGN, "block: logits must be 16-byte aligned");
+            side.route = {d->logits, T, 2, expert_of, gate, counts, perm};
+        } else {
+            rc = sa_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
+            if (rc != SA_OK) return rc;
+        }
     }
-
-    rc = sa_binarize_pair(d->q, d->k, d->B, d->N, d->H, d->d, d->proj, d->nbits, qc, kc, stream);
+    sa::DecodeWork none;
+    const ShiftWeights weights(*d, E, T, ws + L.shift_ws, d->hid > 0 ? &side.decode : &none);
+    rc = hash_and_side(d->q, d->k, d->B, d->N, d->H, d->d, d->proj, d->nbits, qc, kc, side, stream);
     if (rc != SA_OK) return rc;
     // The attention output leaves in three forms: fp32 (the block's output o), the int8 codes the
     // Shift layers read, and (with a Mult expert) the fp16 rounding its first layer reads.  The
@@ -149,10 +189,10 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
 
     if (!moe) {
         const sa_rows all{nullptr, nullptr, 0, T};
-        return sa_shift_mlp(xq, &all, E, d->hid, d->w1, d->w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
-                            d->out_scale, d->shift_variant, 3, ws + L.shift_ws, L.shift_ws_bytes, stream);
+        return sa_shift_mlp(xq, &all, E, d->hid, weights.w1, weights.w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
+                            d->out_scale, weights.variant, 3, ws + L.shift_ws, L.shift_ws_bytes, stream);
     }
-    return experts(*d, xq, xh, E, T, perm, counts, gate, 0, ws + L.mult_ws, L.mult_ws_bytes, ws + L.shift_ws, L.shift_ws_bytes,
+    return experts(*d, weights, xq, xh, E, T, perm, counts, gate, 0, ws + L.mult_ws, L.mult_ws_bytes, ws + L.shift_ws, L.shift_ws_bytes,
                    stream);
 }
 
@@ -257,7 +297,13 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     const bool fused_hash = d->proj == nullptr && d->nbits == dv && (dv == 64 || dv == 128) && E % 128 == 0 &&
                             d->shift_variant != SA_VARIANT_VALU && d->qkv_scale > 0.0f &&
                             d->qkv_scale - d->qkv_scale == 0.0f;
+    rc = check_mlp(*d, E);
+    if (rc != SA_OK) return rc;
+    sa::SideWork side;
+    const ShiftWeights weights(*d, E, T, ws + L.shift_ws, &side.decode);
     if (fused_hash) {
+        if (side.any()) rc = sa::launch_decode_work(side.decode, sa::as_stream(stream));
+        if (rc != SA_OK) return rc;
         rc = sa_shift_linear_qkv_codes(codes8, d->wqkv, d->B, d->N, d->H, E, d->shift_variant, d->qkv_scale, qc, kc, v,
                                        ws + L.lin_ws, L.lin_ws_bytes, stream);
         if (rc != SA_OK) return rc;
@@ -265,7 +311,7 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
         rc = sa_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, d->qkv_scale, nullptr, 3, q, k, v,
                                  ws + L.lin_ws, L.lin_ws_bytes, stream);
         if (rc != SA_OK) return rc;
-        rc = sa_binarize_pair(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, stream);
+        rc = hash_and_side(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, side, stream);
         if (rc != SA_OK) return rc;
     }
     if (d->attention == 0) {
@@ -291,8 +337,8 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     if (rc != SA_OK) return rc;
     if (!moe) {
         const sa_rows all{nullptr, nullptr, 0, T};
-        return sa_shift_mlp(codes8, &all, E, d->hid, d->w1, d->w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
-                            d->out_scale, d->shift_variant, 3 | SA_MLP_ACCUMULATE, ws + L.shift_ws, L.shift_ws_bytes,
+        return sa_shift_mlp(codes8, &all, E, d->hid, weights.w1, weights.w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
+                            d->out_scale, weights.variant, 3 | SA_MLP_ACCUMULATE, ws + L.shift_ws, L.shift_ws_bytes,
                             stream);
     }
     int32_t *perm = reinterpret_cast<int32_t *>(ws + L.perm);
@@ -302,6 +348,6 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     rc = sa_moe_dispatch(logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
     if (rc != SA_OK) return rc;
     // the experts add to disjoint rows of y
-    return experts(*d, codes8, xh, E, T, perm, counts, gate, SA_MLP_ACCUMULATE, ws + L.mult_ws, L.mult_ws_bytes,
+    return experts(*d, weights, codes8, xh, E, T, perm, counts, gate, SA_MLP_ACCUMULATE, ws + L.mult_ws, L.mult_ws_bytes,
                    ws + L.shift_ws, L.shift_ws_bytes, stream);
 }

@@ -97,12 +97,34 @@ int mult_linear_rows(const void *xh_all, const RowSel &sel, int K, int N, const 
 size_t shift_linear_rows_workspace_bytes(int K, int N, int variant);
 int shift_linear_rows(const int8_t *xq_all, const RowSel &sel, int K, int N, const uint8_t *w4, float out_scale, float *y,
                       const float *gate, int variant, void *planes, hipStream_t st);
-// Where the Shift expert's decoded planes are: the caller's (prepared variant) or `planes`, filled by this call (any other
-// matrix-core variant).  shift_mlp_planes: both layers of an MLP in one launch; `workspace` as sa_shift_mlp lays it out
-// (*hidden: its int8 hidden rows).
+// Small jobs that can ride in another kernel's launch (side_work.h).
+constexpr int kMaxExperts = 8;
+constexpr long kSideRouteTokens = 32768;     // the one-launch routing takes up to this many tokens
+struct RouteWork {                           // sa_moe_dispatch in one launch
+    const float *logits = nullptr;
+    long T = 0;                              // 0: none
+    int E = 2;
+    int32_t *expert_of = nullptr;
+    float *gate = nullptr;
+    int32_t *counts = nullptr, *perm = nullptr;
+};
+struct DecodeWork {                          // packed weights [N, K], K a multiple of 64, to their two planes
+    const uint4 *w4[2] = {nullptr, nullptr};
+    uint4 *plane_a[2] = {nullptr, nullptr}, *plane_b[2] = {nullptr, nullptr};
+    long chunks[2] = {0, 0};                 // of 32 weights; 0: none
+};
+struct SideWork {
+    RouteWork route;
+    DecodeWork decode;
+    bool any() const { return route.T > 0 || decode.chunks[0] > 0; }
+};
+void add_decode(DecodeWork *w, const uint8_t *w4, int K, int N, void *planes);
+// Both layers of an MLP; `workspace` as sa_shift_mlp lays it out.  The planes then are what the prepared variant takes.
+void shift_mlp_decode(DecodeWork *w, const uint8_t *w1, const uint8_t *w2, int E, int hid, long max_rows, void *workspace,
+                      const uint8_t **planes1, const uint8_t **planes2);
+int launch_decode_work(const DecodeWork &w, hipStream_t st);
+// The decoded planes of one layer: the caller's (prepared variant) or `planes`, filled by this call.
 int shift_linear_planes(const uint8_t *w4, int K, int N, int variant, void *planes, hipStream_t st, const int8_t **out);
-int shift_mlp_planes(const uint8_t *w1, const uint8_t *w2, int E, int hid, int variant, long max_rows, void *workspace,
-                     hipStream_t st, const int8_t **planes1, const int8_t **planes2, int8_t **hidden);
 
 // Shift and Mult expert side by side in one launch per layer, matrix cores only (experts.hip).  The rows of the two
 // selections add up to at most max_rows, which is the same in both; every token belongs to one of them.
@@ -126,7 +148,11 @@ int moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32
 // Hash pre-pass on the matrix cores with exact fallback (binarize_mfma.hip).
 bool binarize_mfma_supported(int d, int nbits);
 int launch_binarize_mfma(const float *x0, const float *x1_or_null, const float *proj, uint64_t *codes0,
-                         uint64_t *codes1_or_null, long rows, int N, int H, int d, int nbits, hipStream_t st);
+                         uint64_t *codes1_or_null, long rows, int N, int H, int d, int nbits, hipStream_t st,
+                         const SideWork &side = SideWork());
+// Whether sa_binarize_pair runs that kernel for these operands, in one launch (binarize.hip).
+bool binarize_pair_one_launch(const float *q, const float *k, const float *proj, const uint64_t *q_codes, const uint64_t *k_codes,
+                              long rows, int d, int nbits);
 
 // Additive attention on the matrix cores (additive_mfma.hip).
 struct AdditiveMfmaPlan {

@@ -14,16 +14,15 @@
 #include <mutex>
 
 #include "common.h"
+#include "side_work.h"
 
 namespace {
 
 using namespace sa;
-constexpr int kMaxE = 8;
+constexpr int kMaxE = kMaxExperts;
 constexpr int kTok = 256;   // tokens per workgroup
 constexpr long kSelfScanBlocks = 512;   // up to this many workgroups (131072 tokens) the scatter pass sums the histograms itself
-constexpr long kOneLaunchTokens = 32768; // up to this many tokens one launch does everything (every workgroup reads all logits)
-
-__device__ inline uint64_t lanemask_lt(int lane) { return (lane == 0) ? 0ull : (~0ull >> (64 - lane)); }
+constexpr long kOneLaunchTokens = kSideRouteTokens; // up to this many tokens one launch does everything (every workgroup reads all logits)
 
 __global__ __launch_bounds__(kTok) void route_kernel(const float *__restrict__ logits, long T, int E,
                                                      int32_t *__restrict__ expert_of,
@@ -58,130 +57,14 @@ __global__ __launch_bounds__(kTok) void route_kernel(const float *__restrict__ l
     }
 }
 
-// The index of the largest logit of token t (the first one among equals).
-__device__ inline int top1(const float *__restrict__ l, int E) {
-    int best = 0;
-    float lb = l[0];
-    for (int e = 1; e < E; ++e) {
-        const float le = l[e];
-        if (le > lb) { lb = le; best = e; }
-    }
-    return best;
-}
-
-// One launch for the whole dispatch: workgroup b owns tokens [1024 b, 1024 b + 1024).  Pass 1 over all T tokens
-// (thread i takes tokens i, i + 1024, ...; the loads of a thread are independent and issued together): per expert, how
-// many tokens it gets in all and how many of them lie in workgroups before b.  Pass 2: the workgroup's own tokens,
-// ranked by ballot / popcount behind those counts.
 constexpr int kOneTok = 1024;            // tokens (and threads) per workgroup of the one-launch kernel
 
 template <int E_FIXED>
-__global__ __launch_bounds__(kOneTok) void route_scatter_kernel(const float *__restrict__ logits, long T, int E_runtime,
-                                                                int32_t *__restrict__ expert_of, float *__restrict__ gate,
-                                                                int32_t *__restrict__ counts, int32_t *__restrict__ perm) {
-    const int E = E_FIXED > 0 ? E_FIXED : E_runtime;
-    constexpr int kWaves = kOneTok / 64;
-    __shared__ int32_t wave_cnt[kWaves][kMaxE];
-    __shared__ int32_t red[kWaves][2 * kMaxE];
-    __shared__ int32_t base_s[kMaxE];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long first = (long)blockIdx.x * kOneTok;              // tokens before `first` belong to earlier workgroups
-    int below[kMaxE], all[kMaxE];
-#pragma unroll
-    for (int e = 0; e < kMaxE; ++e) below[e] = all[e] = 0;
-    float2 own = make_float2(0.0f, 0.0f);                       // E == 2: the logits of this thread's own token, met in pass 1
-    if (E_FIXED == 2) {
-        const float2 *l2 = reinterpret_cast<const float2 *>(logits);
-        constexpr int kBatch = 16;                              // independent loads in flight per thread: 16384 tokens per round trip
-        for (long t0 = tid; t0 < T; t0 += (long)kBatch * kOneTok) {
-            float2 l[kBatch];
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const long t = t0 + (long)i * kOneTok;
-                l[i] = t < T ? l2[t] : make_float2(0.0f, 0.0f);
-            }
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const long t = t0 + (long)i * kOneTok;
-                const int one = (t < T && l[i].y > l[i].x) ? 1 : 0;     // expert 1 only if strictly larger
-                all[1] += one;
-                below[1] += t < first ? one : 0;
-                if (t == first + tid) own = l[i];
-            }
-        }
-        const int mine_all = T > tid ? (int)((T - tid + kOneTok - 1) / kOneTok) : 0;    // tokens this thread looked at
-        const long fb = first - tid;
-        const int mine_below = fb > 0 ? (int)((fb + kOneTok - 1) / kOneTok) : 0;          // ... and those before `first`
-        all[0] = mine_all - all[1];
-        below[0] = mine_below - below[1];
-    } else {
-        for (long t = tid; t < T; t += kOneTok) {
-            const int best = top1(logits + (size_t)t * E, E);
-#pragma unroll
-            for (int e = 0; e < kMaxE; ++e) {
-                all[e] += best == e ? 1 : 0;
-                below[e] += (best == e && t < first) ? 1 : 0;
-            }
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < kMaxE; ++e) {
-        if (e >= E) continue;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            below[e] += __shfl_xor(below[e], off, 64);
-            all[e] += __shfl_xor(all[e], off, 64);
-        }
-        if (lane == 0) { red[wave][e] = below[e]; red[wave][kMaxE + e] = all[e]; }
-    }
-    __syncthreads();
-    if (tid < E) {
-        int bl = 0, al = 0;
-        for (int w = 0; w < kWaves; ++w) { bl += red[w][tid]; al += red[w][kMaxE + tid]; }
-        red[0][tid] = bl;                       // (row 0 of red has been read by this thread only)
-        red[0][kMaxE + tid] = al;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int start = 0;
-        for (int e = 0; e < E; ++e) {
-            base_s[e] = start + red[0][e];
-            if (blockIdx.x == 0) counts[e] = red[0][kMaxE + e];
-            start += red[0][kMaxE + e];
-        }
-    }
-    const long t = first + tid;
-    int mine = -1;
-    if (t < T) {
-        if (E_FIXED == 2) {
-            mine = own.y > own.x ? 1 : 0;
-            const float lb = mine ? own.y : own.x;
-            const float den = __expf(own.x - lb) + __expf(own.y - lb);      // the same sum, in the same order, as the general path
-            expert_of[t] = mine;
-            gate[t] = 1.0f / den;
-        } else {
-            const float *l = logits + (size_t)t * E;
-            mine = top1(l, E);
-            const float lb = l[mine];
-            float den = 0.0f;
-            for (int e = 0; e < E; ++e) den += __expf(l[e] - lb);
-            expert_of[t] = mine;
-            gate[t] = 1.0f / den;
-        }
-    }
-    int rank = 0;
-    for (int e = 0; e < E; ++e) {
-        const uint64_t m = __ballot(mine == e);
-        if (mine == e) rank = __builtin_popcountll(m & lanemask_lt(lane));
-        if (lane == 0) wave_cnt[wave][e] = __builtin_popcountll(m);
-    }
-    __syncthreads();
-    if (mine >= 0) {
-        int before = 0;
-        for (int w = 0; w < wave; ++w) before += wave_cnt[w][mine];
-        perm[base_s[mine] + before + rank] = (int32_t)t;
-    }
+__global__ __launch_bounds__(kOneTok) void route_scatter_kernel(RouteWork w) {
+    route_scatter_block<kOneTok, E_FIXED>(w, blockIdx.x);
 }
+
+__global__ __launch_bounds__(kOneTok) void side_work_kernel(SideWork w) { side_block<kOneTok>(w, blockIdx.x); }
 
 // block_base[blk][e] = first position in perm of expert e's tokens of workgroup blk: an exclusive scan
 // of the per-workgroup histograms, expert by expert, 256 workgroups' counts per pass of one workgroup.
@@ -399,10 +282,11 @@ int dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32_t *
                     void *scratch, hipStream_t st) {
     if (T <= kOneLaunchTokens) {
         const unsigned blocks = (unsigned)((T + kOneTok - 1) / kOneTok);
+        const RouteWork w{logits, T, E, expert_of, gate, counts, perm};
         if (E == 2)
-            route_scatter_kernel<2><<<dim3(blocks), dim3(kOneTok), 0, st>>>(logits, T, E, expert_of, gate, counts, perm);
+            route_scatter_kernel<2><<<dim3(blocks), dim3(kOneTok), 0, st>>>(w);
         else
-            route_scatter_kernel<0><<<dim3(blocks), dim3(kOneTok), 0, st>>>(logits, T, E, expert_of, gate, counts, perm);
+            route_scatter_kernel<0><<<dim3(blocks), dim3(kOneTok), 0, st>>>(w);
         return sa::check_launch("sa_moe_dispatch(one launch)");
     }
     const long n_blocks = (T + kTok - 1) / kTok;
@@ -642,13 +526,26 @@ extern "C" int sa_moe_linear(const int8_t *xq, const void *xh, const float *logi
     int32_t *expert_of = expert_of_or_null ? expert_of_or_null : reinterpret_cast<int32_t *>(ws + L.expert_of);
     int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
     float *gate = gate_or_null ? gate_or_null : reinterpret_cast<float *>(ws + L.gate);
-    int rc = dispatch_launch(logits, T, 2, perm, expert_of, counts, gate, ws + L.scratch, st);
+    // the routing and the decode of the weights in one launch where both are one step
+    const bool decodes = variant == SA_VARIANT_MFMA || variant == SA_VARIANT_AUTO;
+    sa::SideWork side;
+    int rc;
+    if (decodes && T <= kOneLaunchTokens && K % 64 == 0) {
+        side.route = {logits, T, 2, expert_of, gate, counts, perm};
+        sa::add_decode(&side.decode, w4, K, N, ws + L.planes);
+        const long blocks = sa::side_blocks(side, kOneTok);
+        SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_moe_linear: too many weights");
+        side_work_kernel<<<dim3((unsigned)blocks), dim3(kOneTok), 0, st>>>(side);
+        rc = sa::check_launch("sa_moe_linear(routing, weight decode)");
+    } else {
+        rc = dispatch_launch(logits, T, 2, perm, expert_of, counts, gate, ws + L.scratch, st);
+    }
     if (rc != SA_OK) return rc;
     // every token belongs to exactly one expert, so the two scatters write every row of y exactly once
     const sa::RowSel mult_rows{perm, counts, 0, T}, shift_rows{perm, counts, 1, T};
     if (variant != SA_VARIANT_VALU) {
-        const int8_t *planes;
-        rc = sa::shift_linear_planes(w4, K, N, variant, ws + L.planes, st, &planes);
+        const int8_t *planes = reinterpret_cast<const int8_t *>(ws + L.planes);
+        if (side.decode.chunks[0] == 0) rc = sa::shift_linear_planes(w4, K, N, variant, ws + L.planes, st, &planes);
         if (rc != SA_OK) return rc;
         return sa::expert_pair_linear(sa::ExpertPair{xq, xh, shift_rows, mult_rows, y, gate, out_scale}, K, N, planes, w_f16, st);
     }

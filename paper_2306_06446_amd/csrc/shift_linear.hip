@@ -14,6 +14,7 @@
 #include "gemm_common.h"
 #include "gemm_mfma.h"
 #include "gemm_stores.h"
+#include "side_work.h"
 
 namespace {
 
@@ -118,33 +119,6 @@ __global__ __launch_bounds__(256) void shift_valu_kernel(const int8_t *__restric
 // Step 1: decode the 4-bit weights once per call into two int8 planes [N, K] in the
 // workspace (they stay in the last-level cache); step 2: the shared tiled GEMM runs
 // both planes into one int32 accumulator.
-__device__ inline uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
-    return __builtin_amdgcn_perm(hi, lo, sel);
-}
-
-// 8 nibbles of `x` (k ascending from bit 0) -> 8 int8 of plane A and 8 of plane B, k order.
-__device__ inline void decode8(uint32_t x, uint32_t outA[2], uint32_t outB[2]) {
-    // magnitude tables indexed by e: bytes 0..3 in the low word, 4..7 in the high word
-    constexpr uint32_t TA_LO = 0x08040201u, TA_HI = 0x40402010u;   // 1 2 4 8 | 16 32 64 64
-    constexpr uint32_t TB_LO = 0x00000000u, TB_HI = 0x40000000u;   // 0 .. 0 64
-    const uint32_t nibs[2] = {x & 0x0F0F0F0Fu, (x >> 4) & 0x0F0F0F0Fu};   // even k, odd k
-    uint32_t a[2], b[2];
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const uint32_t sel = nibs[p] & 0x07070707u;
-        const uint32_t s1 = (nibs[p] >> 3) & 0x01010101u;          // 1 where negative
-        const uint32_t m = s1 * 0xFFu;                             // 0xFF where negative
-        const uint32_t pa = perm(TA_HI, TA_LO, sel);
-        const uint32_t pb = perm(TB_HI, TB_LO, sel);
-        a[p] = (pa ^ m) + s1;                 // per byte: ~pa + 1 = -pa (pa >= 1: no carry)
-        b[p] = pb | (m & (pb << 1));          // 0x40 -> 0xC0 = -64 where negative
-    }
-    // interleave even / odd back into k order: k0 k1 k2 k3 | k4 k5 k6 k7
-    outA[0] = perm(a[1], a[0], 0x05010400u);
-    outA[1] = perm(a[1], a[0], 0x07030602u);
-    outB[0] = perm(b[1], b[0], 0x05010400u);
-    outB[1] = perm(b[1], b[0], 0x07030602u);
-}
 
 // One thread per 32 weights of a padded plane row (row_chunks of them, the first valid_chunks from 16 bytes of
 // packed weights each, the others zero): 32 B out to each plane.
@@ -176,25 +150,8 @@ __global__ __launch_bounds__(256) void decode_w4_kernel(const uint4 *__restrict_
     plane_b[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
 }
 
-// The same for the two weight matrices of an MLP in one launch (threads past the first matrix's chunks take the second's).
-__global__ __launch_bounds__(256) void decode_w4_pair_kernel(const uint4 *__restrict__ w4_0, long n0, uint4 *__restrict__ a0,
-                                                             uint4 *__restrict__ b0, const uint4 *__restrict__ w4_1, long n1,
-                                                             uint4 *__restrict__ a1, uint4 *__restrict__ b1) {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool second = i >= n0;
-    if (second) i -= n0;
-    if (second && i >= n1) return;
-    const uint4 wv = second ? w4_1[i] : w4_0[i];
-    const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
-    uint32_t oa[8], ob[8];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) decode8(wd[q], oa + 2 * q, ob + 2 * q);
-    uint4 *pa = second ? a1 : a0, *pb = second ? b1 : b0;
-    pa[2 * i] = make_uint4(oa[0], oa[1], oa[2], oa[3]);
-    pa[2 * i + 1] = make_uint4(oa[4], oa[5], oa[6], oa[7]);
-    pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
-    pb[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
-}
+// The same for the two weight matrices of an MLP in one launch.
+__global__ __launch_bounds__(256) void decode_work_kernel(DecodeWork w) { decode_block<256>(w, blockIdx.x); }
 
 constexpr int kMfmaK = 32;   // K granularity of the MFMA variant (16 bytes of packed weights, 32 of activations)
 // Plane rows are padded with zeros to whole 64-byte LDS stages.
@@ -211,15 +168,8 @@ int decode_planes(const uint8_t *w4, int K, int N, void *planes, hipStream_t st)
     return check_launch("shift layer (weight decode)");
 }
 
-// Both weight matrices of an MLP ([N0, K0] and [N1, K1]) to their planes in one launch.
-int decode_planes_pair(const uint8_t *w4_0, int K0, int N0, void *planes0, const uint8_t *w4_1, int K1, int N1, void *planes1,
-                       hipStream_t st) {
-    int8_t *a0 = static_cast<int8_t *>(planes0), *b0 = a0 + (size_t)N0 * K0;
-    int8_t *a1 = static_cast<int8_t *>(planes1), *b1 = a1 + (size_t)N1 * K1;
-    const long n0 = (long)N0 * K0 / 32, n1 = (long)N1 * K1 / 32;
-    decode_w4_pair_kernel<<<dim3((unsigned)((n0 + n1 + 255) / 256)), dim3(256), 0, st>>>(
-        reinterpret_cast<const uint4 *>(w4_0), n0, reinterpret_cast<uint4 *>(a0), reinterpret_cast<uint4 *>(b0),
-        reinterpret_cast<const uint4 *>(w4_1), n1, reinterpret_cast<uint4 *>(a1), reinterpret_cast<uint4 *>(b1));
+int launch_decode(const DecodeWork &w, hipStream_t st) {
+    decode_work_kernel<<<dim3((unsigned)((w.chunks[0] + w.chunks[1] + 255) / 256)), dim3(256), 0, st>>>(w);
     return check_launch("shift layers (weight decode)");
 }
 
@@ -511,19 +461,24 @@ int sa::shift_linear_planes(const uint8_t *w4, int K, int N, int variant, void *
     return variant == SA_VARIANT_MFMA_PREPARED ? SA_OK : decode_planes(w4, K, N, planes, st);
 }
 
-int sa::shift_mlp_planes(const uint8_t *w1, const uint8_t *w2, int E, int hid, int variant, long max_rows, void *workspace,
-                         hipStream_t st, const int8_t **planes1, const int8_t **planes2, int8_t **hidden) {
-    *hidden = static_cast<int8_t *>(workspace);
-    if (variant == SA_VARIANT_MFMA_PREPARED) {
-        *planes1 = reinterpret_cast<const int8_t *>(w1);
-        *planes2 = reinterpret_cast<const int8_t *>(w2);
-        return SA_OK;
-    }
-    int8_t *p1 = *hidden + (((size_t)max_rows * hid) + 255) / 256 * 256, *p2 = p1 + planes_bytes(E, hid);
+void sa::add_decode(DecodeWork *w, const uint8_t *w4, int K, int N, void *planes) {
+    const int i = w->chunks[0] == 0 ? 0 : 1;
+    w->w4[i] = reinterpret_cast<const uint4 *>(w4);
+    w->plane_a[i] = static_cast<uint4 *>(planes);
+    w->plane_b[i] = w->plane_a[i] + (size_t)N * K / 16;
+    w->chunks[i] = (long)N * K / 32;
+}
+
+void sa::shift_mlp_decode(DecodeWork *w, const uint8_t *w1, const uint8_t *w2, int E, int hid, long max_rows, void *workspace,
+                          const uint8_t **planes1, const uint8_t **planes2) {
+    uint8_t *p1 = static_cast<uint8_t *>(workspace) + (((size_t)max_rows * hid) + 255) / 256 * 256, *p2 = p1 + planes_bytes(E, hid);
+    add_decode(w, w1, E, hid, p1);
+    add_decode(w, w2, hid, E, p2);
     *planes1 = p1;
     *planes2 = p2;
-    return decode_planes_pair(w1, E, hid, p1, w2, hid, E, p2, st);
 }
+
+int sa::launch_decode_work(const DecodeWork &w, hipStream_t st) { return launch_decode(w, st); }
 
 // workspace layout of sa_shift_mlp: hidden int8 [max_rows, hid] | planes of w1 | planes of w2
 size_t sa::shift_linear_rows_workspace_bytes(int K, int N, int variant) {
@@ -584,7 +539,10 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
     const int v_eff = variant == SA_VARIANT_AUTO ? SA_VARIANT_MFMA : variant;      // E and hid are multiples of 64
     const bool pair = v_eff == SA_VARIANT_MFMA && (stages & 3) == 3;
     if (pair) {
-        rc = decode_planes_pair(w1, E, hid, planes1, w2, hid, E, planes2, st);
+        sa::DecodeWork w;
+        sa::add_decode(&w, w1, E, hid, planes1);
+        sa::add_decode(&w, w2, hid, E, planes2);
+        rc = launch_decode(w, st);
         if (rc != SA_OK) return rc;
     }
     if (stages & 1) {
