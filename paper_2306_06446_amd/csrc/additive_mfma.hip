@@ -486,7 +486,11 @@ __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__res
 #pragma unroll
                         for (int j = 0; j < JT; ++j) {
                             const float val = fr * acc[tm][j][r];
-                            if (f.out) (f.out + at + j * 32)[lane_at] = val;
+                            if (f.out) {
+                                float *dst = f.out + at + j * 32 + lane_at;
+                                if (ZO) *dst = val;           // the convolution that follows reads it
+                                else __builtin_nontemporal_store(val, dst);
+                            }
                             if (f.xq) (f.xq + at + j * 32)[lane_at] = (int8_t)sa::requant_byte(val * f.act_inv_scale);
                             if (f.xh) (f.xh + at + j * 32)[lane_at] = (_Float16)val;
                         }

@@ -48,6 +48,15 @@ __device__ inline void resolve_rows(const RowSel &sel, const int32_t *&rows, lon
 
 int validate_rows(const sa_rows *rows, RowSel *out);
 
+// 16 bytes to memory past the caches' reuse order: for 32-bit outputs, which are large, written once and not read again
+// soon, and otherwise push out what is.  12608 x 1536 <- 384 and back, int32: 72 -> 60 us; the layers with fp32 outputs of
+// 12608 x 768 tokens 0 to 4 us each; Q(K^T V) at 8 x 4 x 16384 x 256 bits x 64 70 -> 64 us.  For the narrow outputs that
+// the next kernel reads it gained nothing, for the reads of Q and K it lost (pvt-sized attention 28.8 -> 30.5 us).
+__device__ inline void store_streaming(void *dst, const uint4 &v) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(u4{v.x, v.y, v.z, v.w}, reinterpret_cast<u4 *>(dst));
+}
+
 // One wavefront-wide direct global -> LDS load, no registers and nothing for the compiler to wait for: lane l's 16 (4)
 // bytes at `src` land at LDS byte lds_base + 16 (4) * l (lds_base is the same in every lane).
 __device__ inline void direct_load_16(const void *src, uint32_t lds_base) {

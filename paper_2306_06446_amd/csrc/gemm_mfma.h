@@ -151,7 +151,9 @@ __device__ __forceinline__ void store_chunk(const Store &store, uint4 v, const i
             v.w = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.w));
         }
     }
-    if (ES < 4 || whole_chunks) {
+    if (ES == 4 && whole_chunks) {
+        store_streaming(dst, v);
+    } else if (ES < 4) {
         *reinterpret_cast<uint4 *>(dst) = v;
     } else {                          // 32-bit rows that are not a multiple of 16 bytes
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};

@@ -187,7 +187,8 @@ __device__ inline void write_outputs(v16f (&acc)[DV / 32], float den, uint8_t *s
             for (int p = 0; p < 16 / RPP; ++p) {
                 const int r = p * RPP + lane / LPR, c = (lane % LPR) * 4;
                 const float4 val = *reinterpret_cast<const float4 *>(stage + r * PITCH + c * 4);
-                if (q_half0 + r < Nq) *reinterpret_cast<float4 *>(out + tile_at + (size_t)(16 * half + r) * row_elems + c) = val;
+                if (q_half0 + r < Nq)
+                    sa::store_streaming(out + tile_at + (size_t)(16 * half + r) * row_elems + c, __builtin_bit_cast(uint4, val));
             }
         }
         if (xq) {
