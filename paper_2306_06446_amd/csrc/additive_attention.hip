@@ -346,6 +346,8 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
             KtvPlan p{};
             if (mfma) m = sa::plan_additive_mfma(B, H, Nk, nbits, dv);
             else p = plan_ktv(B, H, Nk, nbits);
+            if (mfma && qkv_mfma && (phases & 2) && Nq > 0 && !mode.zero_one && sa::additive_mfma_one_launch(m, Nq, Nk, nbits))
+                return sa::launch_ktv_qkv(k_codes, v, kv, q_codes, f, B, H, Nq, Nk, nbits, dv, st);
             const int splits = mfma ? m.splits : p.splits;
             float *dst = kv;
             int32_t *counts = mode.ksum;

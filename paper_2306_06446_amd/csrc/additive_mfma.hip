@@ -27,6 +27,7 @@
 
 namespace {
 
+using sa::AddFused;
 using sa::kWave;
 
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -76,28 +77,33 @@ __device__ inline uint32_t code_pair(uint32_t x, int sh) {
 // The wavefronts' accumulators meet in LDS in ascending order.
 constexpr int kKtvWaves = 8;
 
+template <int DVC, int WB, int RING, bool ZO>
+struct KtvLds {
+    static constexpr int SLOT = 16 * DVC * 4 + 256;              // a step in the ring: V rows, code words
+    static constexpr int RING_BYTES = kKtvWaves * RING * SLOT, BYTES = RING_BYTES + (ZO ? kKtvWaves * WB * 64 * 4 : 0);
+    static_assert(RING_BYTES >= kKtvWaves * 32 * DVC * 4, "the final sum reuses the ring");
+};
+
 // ksum (ZO): int32 [splits][BH][nbits], the number of tokens of the range whose code bit is set.
+// block = ((bh * n_groups + group) * n_cols + column group) * splits + split
 template <int DVC, int WB, int PH, int RING, bool ZO>
-__global__ __launch_bounds__(kKtvWaves * 64) void ktv_mfma_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
-                                                                  float *__restrict__ dst, int32_t *__restrict__ ksum, int H, int Nk,
-                                                                  int W, int DV, int splits, int tokens_per_block) {
+__device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, const float *__restrict__ v, float *__restrict__ dst,
+                                          int32_t *__restrict__ ksum, long BH, int H, int Nk, int W, int DV, int splits,
+                                          int tokens_per_block, int block, uint8_t *ring_s) {
     constexpr int JT = DVC / 32, TB = 2 * WB;                    // 32-column and 32-bit tiles
     constexpr int PAIRS = kKtvWaves / PH, GW = PAIRS * WB;       // shares of words, words of a workgroup
     constexpr int TILE = 32 * DVC;                               // floats of one 32-bit tile
-    constexpr int V_BYTES = 16 * DVC * 4, SLOT = V_BYTES + 256;  // a step in the ring: V rows, code words
+    constexpr int V_BYTES = 16 * DVC * 4, SLOT = KtvLds<DVC, WB, RING, ZO>::SLOT;
     constexpr int LOADS = V_BYTES / 1024 + 1;                    // direct loads of a step
-    __shared__ __attribute__((aligned(1024))) uint8_t ring_s[kKtvWaves * RING * SLOT];
-    static_assert(sizeof(ring_s) >= kKtvWaves * TILE * 4, "the final sum reuses the ring");
     float *red_s = reinterpret_cast<float *>(ring_s);
-    __shared__ int32_t cnt_s[ZO ? kKtvWaves * WB * 64 : 1];
+    int32_t *cnt_s = reinterpret_cast<int32_t *>(ring_s + KtvLds<DVC, WB, RING, ZO>::RING_BYTES);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int phase = wave / PAIRS;
     const int n_groups = (W + GW - 1) / GW, n_cols = DV / DVC;
-    // blockIdx.x = ((bh * n_groups + group) * n_cols + column group) * splits + split
-    const int part = blockIdx.x % splits;
-    const long rest = blockIdx.x / splits;
+    const int part = block % splits;
+    const long rest = block / splits;
     const int c0 = (int)(rest % n_cols) * DVC;
     const int group = (int)(rest / n_cols % n_groups);
     const long bh = rest / n_cols / n_groups;
@@ -246,8 +252,7 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_mfma_kernel(const uint64_t
 
     // ---- the wavefronts' sums, in ascending order, one 32-bit tile of every share at a time; dst: [splits][BH][nbits][DV].
     //      With +-1 codes the operand was -1 for a set bit (the code bit as the sign bit), so the sum is negated here.
-    const size_t bh_count = (size_t)gridDim.x / splits / n_groups / n_cols;
-    const size_t row0 = (((size_t)part * bh_count + bh) * W + group * GW) * 64;
+    const size_t row0 = (((size_t)part * BH + bh) * W + group * GW) * 64;
     const int rows_here = min(GW, W - group * GW) * 64;
 #pragma unroll
     for (int t = 0; t < TB; ++t) {
@@ -286,6 +291,14 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_mfma_kernel(const uint64_t
             ksum[row0 + q] = n;
         }
     }
+}
+
+template <int DVC, int WB, int PH, int RING, bool ZO>
+__global__ __launch_bounds__(kKtvWaves * 64) void ktv_mfma_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
+                                                                  float *__restrict__ dst, int32_t *__restrict__ ksum, long BH, int H,
+                                                                  int Nk, int W, int DV, int splits, int tokens_per_block) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[KtvLds<DVC, WB, RING, ZO>::BYTES];
+    ktv_block<DVC, WB, PH, RING, ZO>(k_codes, v, dst, ksum, BH, H, Nk, W, DV, splits, tokens_per_block, blockIdx.x, lds);
 }
 
 // kv[i] = sum over splits of part[s][i].  G threads per 16 bytes: thread g takes a contiguous range of splits, s
@@ -338,26 +351,31 @@ __global__ __launch_bounds__(256) void ktv_sum_kernel(const f32x4 *__restrict__ 
 // K runs over the code bits in an order that makes the query's own code words the operand (see code_pair): step
 // ks = 2 * half + s of a 32-bit half word, lane half kg, element e is bit 8 s + 4 kg + e / 2 + 16 (e % 2) of that half.
 
-using sa::AddFused;
+template <int DVC, int W, bool ZO>
+struct QkvLds {
+    static constexpr int STRIDE = W * 64 + 8;                    // bf16 elements per transposed K^T V row
+    static constexpr int PLANE = DVC * STRIDE;                   // elements of a term plane
+    // behind the planes: sums of the 16 subsets of every 4 bit counts (the normaliser), the counts
+    static constexpr int BYTES = 3 * PLANE * 2 + (ZO ? W * 64 * 5 * 4 : 0);
+};
 
+// block = (bh * column groups + column group) * blocks_per_bh + part
 template <int DVC, int W, int NW, int TM, bool ZO>
-__global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f,
-                                                                  int H, int Nq, int DV, long BH, int blocks_per_bh, int tiles_per_block) {
+__device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, int Nq, int DV, long BH,
+                                          int blocks_per_bh, int tiles_per_block, int block, uint8_t *lds) {
     constexpr int JT = DVC / 32;
     constexpr int NBITS = W * 64;
-    constexpr int STRIDE = NBITS + 8;             // bf16 elements per transposed K^T V row
-    __shared__ __attribute__((aligned(16))) uint16_t kvt_s[3][DVC * STRIDE];
-    __shared__ int32_t tab_s[ZO ? NBITS * 4 : 1];  // normaliser: sums of the 16 subsets of every 4 bit counts
-    __shared__ int32_t ks_s[ZO ? NBITS : 1];
+    constexpr int STRIDE = QkvLds<DVC, W, ZO>::STRIDE, PLANE = QkvLds<DVC, W, ZO>::PLANE;
+    uint16_t *kvt_s = reinterpret_cast<uint16_t *>(lds);
+    int32_t *tab_s = reinterpret_cast<int32_t *>(lds + 3 * PLANE * 2), *ks_s = tab_s + NBITS * 4;
 
     const int tid = threadIdx.x, lane = tid & 63;
     constexpr int n_threads = NW * 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // blockIdx.x = (bh * column groups + column group) * blocks_per_bh + part
-    const int part = blockIdx.x % blocks_per_bh;
+    const int part = block % blocks_per_bh;
     const int n_cols = DV / DVC;
-    const int c0 = (int)(blockIdx.x / blocks_per_bh % n_cols) * DVC;
-    const long bh = blockIdx.x / blocks_per_bh / n_cols;
+    const int c0 = block / blocks_per_bh % n_cols * DVC;
+    const long bh = block / blocks_per_bh / n_cols;
     const int b = (int)(bh / H), h = (int)(bh % H);
     const int m = lane & 31, kg = lane >> 5;
 
@@ -389,7 +407,7 @@ __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__res
         }
 #pragma unroll
         for (int p = 0; p < 3; ++p)
-            *reinterpret_cast<uint4 *>(&kvt_s[p][col * STRIDE + grp * 8]) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+            *reinterpret_cast<uint4 *>(kvt_s + p * PLANE + col * STRIDE + grp * 8) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
     }
     if (ZO) {
         for (int j = tid; j < NBITS; j += n_threads) {
@@ -461,7 +479,7 @@ __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__res
                 const int off = (j * 32 + m) * STRIDE + 16 * ks + 8 * kg;
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
-                    const v8bf kp = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(kvt_s[p] + off));
+                    const v8bf kp = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(kvt_s + p * PLANE + off));
 #pragma unroll
                     for (int tm = 0; tm < TM; ++tm) acc[tm][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tm], kp, acc[tm][j], 0, 0, 0);
                 }
@@ -505,6 +523,29 @@ __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__res
     }
 }
 
+template <int DVC, int W, int NW, int TM, bool ZO>
+__global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f, int H, int Nq, int DV,
+                                                           long BH, int blocks_per_bh, int tiles_per_block) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[QkvLds<DVC, W, ZO>::BYTES];
+    qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds);
+}
+
+// ------------------------------------------------------------------- both, short sequences ----
+// One workgroup does K^T V and Q(K^T V) of a (b, h) and DVC columns; what it reads of K^T V it wrote itself (splits = 1), so
+// a barrier is all the order that takes.  Bound by latency for few sequences: 1 x 3 heads x 197 tokens x 64 bits 10.6 us in
+// two launches, 7.5 in one; K^T V comes back from the caches it was just written to with many: 64 x 12 x 197 x 128 bits
+// 33.2 -> 29.1, 64 x 3 x 197 x 64 bits 13.7 -> 9.9.
+template <int DVC, int W, int PH, int WB, int RING>
+__global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
+                                                                 float *__restrict__ kv, const uint64_t *__restrict__ q_codes,
+                                                                 AddFused f, int H, int Nq, int Nk, int DV, long BH) {
+    constexpr int KB = KtvLds<DVC, WB, RING, false>::BYTES, QB = QkvLds<DVC, W, false>::BYTES;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[KB > QB ? KB : QB];
+    ktv_block<DVC, WB, PH, RING, false>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
+    __syncthreads();
+    qkv_block<DVC, W, kKtvWaves, 1, false>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds);
+}
+
 // How the token tiles of a (b, h) are spread.
 //  * Enough work to fill the chip with 32-tile passes: all columns up to 64 in one workgroup, 16 wavefronts with two tiles
 //    each (a K^T V operand is then read once for both), one workgroup per CU and the tiles divided evenly: 50 us at 8 x 4
@@ -535,6 +576,10 @@ void launch_qkv_w(const uint64_t *q_codes, const AddFused &f, long BH, int H, in
 
 namespace sa {
 
+// Tokens up to which one workgroup does both products of a (b, h): two rounds of its eight wavefronts' 32-token tiles.  Beyond
+// that Q(K^T V) has tiles enough for several workgroups, which would each repeat or wait for K^T V.
+constexpr int kShortTokens = 512;
+
 // Shapes the matrix-core kernels take: K^T V any nbits (multiple of 64); Q(K^T V) 64-, 128- or 256-bit codes.
 bool additive_mfma_ktv_supported(int nbits, int dv) { return nbits % 64 == 0 && (dv == 32 || dv == 64 || dv == 128); }
 
@@ -561,20 +606,23 @@ AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv) {
     return p;
 }
 
+// Many short sequences: one word per wavefront and a short ring, so that two workgroups share a CU and one loads or sums while
+// the other multiplies.  From the second round of workgroups on: 32 x 12 heads x 197 tokens x 128 bits 16.3 -> 11.9 us, 700
+// tokens 28.2 -> 22.6, 1500 tokens 44.3 -> 39.4.  blocks: workgroups of up to 64 columns.
+static bool ktv_many(long blocks) { return blocks > 256; }
+
 int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int32_t *ksum, int B, int H, int Nk, int nbits, int dv,
                     const AdditiveMfmaPlan &p, bool zero_one, hipStream_t st) {
     const int W = nbits / 64;
     const long blocks = (long)B * H * p.groups * (dv > 64 ? dv / 64 : 1) * p.splits;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
     const dim3 grid((unsigned)blocks), block(kKtvWaves * 64);
-    // Many short sequences (workgroups for more than two rounds): one word per wavefront and a short ring, so that two
-    // workgroups share a CU and one loads or sums while the other multiplies (64 x 12 heads x 197 tokens x 128 bits).
-    const bool many = blocks > 512;
+    const bool many = ktv_many(blocks);
 #define SA_KTV(DVC_, WB_, PH_, RING_)                                                                                          \
     if (zero_one) ktv_mfma_kernel<DVC_, WB_, PH_, RING_, true><<<grid, block, 0, st>>>(                                                 \
-        k_codes, v, dst, ksum, H, Nk, W, dv, p.splits, p.tokens_per_block);                                                    \
+        k_codes, v, dst, ksum, (long)B * H, H, Nk, W, dv, p.splits, p.tokens_per_block);                                                    \
     else ktv_mfma_kernel<DVC_, WB_, PH_, RING_, false><<<grid, block, 0, st>>>(                                                  \
-        k_codes, v, dst, ksum, H, Nk, W, dv, p.splits, p.tokens_per_block);
+        k_codes, v, dst, ksum, (long)B * H, H, Nk, W, dv, p.splits, p.tokens_per_block);
 #define SA_KTV_DV(DVC_)                       \
     if (W == 1 && many) { SA_KTV(DVC_, 1, 8, 2) }       \
     else if (W == 1) { SA_KTV(DVC_, 1, 8, 4) }          \
@@ -589,6 +637,36 @@ int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int32_t
 #undef SA_KTV_DV
 #undef SA_KTV
     return check_launch("sa_additive_attention(K^T V)");
+}
+
+bool additive_mfma_one_launch(const AdditiveMfmaPlan &p, int Nq, int Nk, int nbits) {
+    return p.splits == 1 && nbits <= 128 && Nq <= kShortTokens && Nk <= kShortTokens;
+}
+
+int launch_ktv_qkv(const uint64_t *k_codes, const float *v, float *kv, const uint64_t *q_codes, const AddFused &f, int B, int H,
+                   int Nq, int Nk, int nbits, int dv, hipStream_t st) {
+    const long BH = (long)B * H;
+    // half of the columns per workgroup where that still leaves CUs idle
+    const bool half = dv > 32 && BH * (dv / 32) <= 256;
+    const int dvc = dv == 32 || half ? 32 : 64;
+    const long blocks = BH * (dv / dvc);
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
+    // The steps of a wavefront are those launch_ktv_mfma would give it, so that K^T V has the same bits either way.
+    const bool many = ktv_many(BH * (dv > 64 ? dv / 64 : 1));
+#define SA_BOTH(DVC_, W_, PH_, WB_, RING_)                                                                                      \
+    ktv_qkv_kernel<DVC_, W_, PH_, WB_, RING_><<<dim3((unsigned)blocks), dim3(kKtvWaves * 64), 0, st>>>(k_codes, v, kv, q_codes, f, H, \
+                                                                                                   Nq, Nk, dv, BH)
+#define SA_BOTH_DV(DVC_)                                                                   \
+    if (nbits == 64) { if (many) SA_BOTH(DVC_, 1, 8, 1, 2); else SA_BOTH(DVC_, 1, 8, 1, 4); } \
+    else { if (many) SA_BOTH(DVC_, 2, 4, 1, 2); else SA_BOTH(DVC_, 2, 8, 2, 4); }
+    if (dvc == 32) {
+        SA_BOTH_DV(32)
+    } else {
+        SA_BOTH_DV(64)
+    }
+#undef SA_BOTH_DV
+#undef SA_BOTH
+    return check_launch("sa_additive_attention(K^T V, Q(K^T V))");
 }
 
 // K^T V partials that Q(K^T V) sums while it stages them: what a workgroup then reads stays within 128 KiB.

@@ -194,6 +194,10 @@ int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int32_t
                     const AdditiveMfmaPlan &p, bool zero_one, hipStream_t st);
 int launch_ktv_sum(const float *part, float *kv, const int32_t *ksum_part, int32_t *ksum, long BH, int nbits, int dv, int splits,
                    hipStream_t st);
+// Short sequences, +-1 codes: both in one launch.
+bool additive_mfma_one_launch(const AdditiveMfmaPlan &p, int Nq, int Nk, int nbits);
+int launch_ktv_qkv(const uint64_t *k_codes, const float *v, float *kv, const uint64_t *q_codes, const AddFused &f, int B, int H,
+                   int Nq, int Nk, int nbits, int dv, hipStream_t st);
 int launch_qkv_mfma(const uint64_t *q_codes, const AddFused &f, int B, int H, int Nq, int nbits, int dv, bool zero_one,
                     hipStream_t st);
 // sa_additive_attention (both phases) whose output also leaves as the int8 codes (and fp16 rounding) the MLP reads, from

@@ -21,6 +21,8 @@ def bits_of(c):
     (1, 2, 40, 300, 3, 64), (1, 1, 20, 500, 5, 32), (1, 2, 70, 257, 6, 128),                        # words that do not pair up
     (2, 2, 300, 4097, 4, 64), (1, 1, 513, 9000, 4, 128), (3, 1, 95, 2000, 4, 32),                   # many partials
     (40, 13, 50, 49, 1, 32), (30, 18, 37, 197, 2, 64), (44, 12, 33, 20, 1, 64),                     # many short sequences
+    (1, 3, 197, 197, 1, 64), (2, 2, 256, 255, 2, 128), (43, 6, 512, 512, 1, 64), (22, 12, 300, 511, 2, 32),  # both products in one launch
+    (43, 6, 513, 512, 2, 64), (43, 6, 100, 513, 1, 32),                                             # one token too many for that
     (8, 4, 8192, 300, 1, 64),                                                                       # 32-tile passes of Q(K^T V)
 ])
 def test_both_code_modes_against_fp64(sa, B, H, Nq, Nk, W, dv):
