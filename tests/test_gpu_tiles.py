@@ -82,3 +82,16 @@ def test_sign_codes_of_every_tile_width(sa, B, N, H, d):
     for got, f in ((qc, q), (kc, k)):
         bits = (f.view(B, N, H, d // 64, 64) >= 0).to(torch.int64)
         assert torch.equal(got, (bits * weight).sum(-1).permute(0, 2, 1, 3))
+
+
+@pytest.mark.parametrize("rows", [1024, 16384])                          # 32-row tiles, 128 x 128
+def test_gelu_of_every_finite_half(sa, rows):
+    bits = torch.arange(65536, device="cuda").remainder(65536).to(torch.int32)
+    x = torch.where(bits < 32768, bits, bits - 65536).to(torch.int16).view(torch.float16)
+    x = torch.where(torch.isfinite(x), x, torch.zeros_like(x)).view(1024, 64).repeat(rows // 1024, 1)
+    eye = torch.eye(64, device="cuda").half()
+    got = sa.sa_mult_mlp_f16_half(x.contiguous(), eye, eye).double()     # identity weights: the hidden rows as they are
+    a = x.double()
+    ref = 0.5 * a * torch.special.erfc(-a * 0.5 ** 0.5)
+    ulp = torch.exp2(torch.floor(torch.log2(ref.abs().clamp(min=2.0 ** -14))) - 10)
+    assert float(((got - ref).abs() / ulp).max()) <= 0.505
