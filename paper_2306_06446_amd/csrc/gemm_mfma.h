@@ -108,68 +108,134 @@ __device__ inline void wait_loads_in_flight() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// One 16-byte chunk of converted elements (output row m of the row selection, columns n .. n + 16 / kBytes - 1) to
-// where it belongs, with the gate, residual or old value of the destination.  whole_chunks: no chunk straddles a row's end.
+// The 16-byte chunks at columns n .. n + 16 / kBytes - 1 of the output: where they go, and what they need from memory besides
+// the product (the residual, or what the destination holds).  fetch() is apart from put() so that the reads of many chunks
+// are in flight at once: read where it was used, each waited for the one before it (two, with a row index and its gate).
 template <class Store>
-__device__ __forceinline__ void store_chunk(const Store &store, uint4 v, const int32_t *rows, long m, int n, int N,
-                                            bool whole_chunks) {
-    constexpr int ES = Store::kBytes;
-    const long t = (Store::kScatter && rows) ? (long)rows[m] : m;
-    uint8_t *dst = static_cast<uint8_t *>(store.out) + ((size_t)t * N + n) * ES;
-    if constexpr (Store::kLinear) {
-        // whole chunks by construction: part_width and N are multiples of 4
-        float4 res = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (store.residual) res = *reinterpret_cast<const float4 *>(store.residual + (size_t)t * N + n);
-        v.x = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.x), store.scale, res.x));
-        v.y = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.y), store.scale, res.y));
-        v.z = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.z), store.scale, res.z));
-        v.w = __builtin_bit_cast(uint32_t, __builtin_fmaf(__builtin_bit_cast(float, v.w), store.scale, res.w));
-        const int part = n / store.part_width;
-        float *base = part == 0 ? store.parts[0] : part == 1 ? store.parts[1] : store.parts[2];
-        dst = reinterpret_cast<uint8_t *>(base + (size_t)t * store.part_width + (n - part * store.part_width));
-    }
-    if constexpr (ES == 4 && Store::kScatter) {
-        const float gt = store.gate ? store.gate[t] : 1.0f;
-        if (store.accumulate) {
-            float old[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (whole_chunks) {
-                const float4 o4 = *reinterpret_cast<const float4 *>(dst);
-                old[0] = o4.x; old[1] = o4.y; old[2] = o4.z; old[3] = o4.w;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n + e < N) old[e] = reinterpret_cast<const float *>(dst)[e];
-            }
-            v.x = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.x), old[0]));
-            v.y = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.y), old[1]));
-            v.z = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.z), old[2]));
-            v.w = __builtin_bit_cast(uint32_t, __builtin_fmaf(gt, __builtin_bit_cast(float, v.w), old[3]));
-        } else if (store.gate) {
-            v.x = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.x));
-            v.y = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.y));
-            v.z = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.z));
-            v.w = __builtin_bit_cast(uint32_t, gt * __builtin_bit_cast(float, v.w));
+struct ChunkOut {
+    static constexpr int ES = Store::kBytes;
+    const Store &store;
+    uint8_t *dst;              // the chunk in row 0 of the output
+    const float *res = nullptr;
+    size_t pitch, res_pitch;
+    int live;                  // elements of the chunk inside a row
+    bool whole_chunks;         // no chunk straddles a row's end
+
+    __device__ __forceinline__ ChunkOut(const Store &s, int n, int N) : store(s), pitch((size_t)N * ES), res_pitch(N), live(N - n) {
+        whole_chunks = pitch % 16 == 0;
+        dst = static_cast<uint8_t *>(s.out) + (size_t)n * ES;
+        if constexpr (Store::kLinear) {            // whole chunks by construction: part_width and N are multiples of 4
+            const int part = n / s.part_width;
+            float *base = part == 0 ? s.parts[0] : part == 1 ? s.parts[1] : s.parts[2];
+            dst = reinterpret_cast<uint8_t *>(base + (n - part * s.part_width));
+            pitch = (size_t)s.part_width * ES;
+            if (s.residual) res = s.residual + min(n, N - 4);
         }
     }
-    if (ES == 4 && whole_chunks) {
-        store_streaming(dst, v);
-    } else if (ES < 4) {
-        *reinterpret_cast<uint4 *>(dst) = v;
-    } else {                          // 32-bit rows that are not a multiple of 16 bytes
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (n + e < N) reinterpret_cast<uint32_t *>(dst)[e] = w[e];
+    static constexpr bool MAY_READ = ES == 4 && !Store::kSignCodes && (Store::kLinear || Store::kScatter);
+    __device__ __forceinline__ bool reads() const {
+        if constexpr (MAY_READ && Store::kLinear) return res != nullptr;
+        else if constexpr (MAY_READ) return store.accumulate;
+        return false;
     }
-}
+    __device__ __forceinline__ float4 fetch(long t) const {
+        float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (Store::kLinear && !Store::kSignCodes) {
+            if (res) return *reinterpret_cast<const float4 *>(res + t * res_pitch);
+        } else if constexpr (Store::kScatter && ES == 4) {
+            if (store.accumulate && live > 0) {
+                const float *old = reinterpret_cast<const float *>(dst + t * pitch);
+                if (whole_chunks) return *reinterpret_cast<const float4 *>(old);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < live) x[e] = old[e];
+            }
+        }
+        return make_float4(x[0], x[1], x[2], x[3]);
+    }
+    // v: converted elements; x: what fetch() gave; gate: the factor of destination row t
+    __device__ __forceinline__ void put(uint4 v, float4 x, float gate, long t) const {
+        auto as_float = [](uint32_t b) { return __builtin_bit_cast(float, b); };
+        auto as_bits = [](float f) { return __builtin_bit_cast(uint32_t, f); };
+        if constexpr (Store::kLinear) {
+            v = make_uint4(as_bits(__builtin_fmaf(as_float(v.x), store.scale, x.x)), as_bits(__builtin_fmaf(as_float(v.y), store.scale, x.y)),
+                           as_bits(__builtin_fmaf(as_float(v.z), store.scale, x.z)), as_bits(__builtin_fmaf(as_float(v.w), store.scale, x.w)));
+        } else if constexpr (Store::kScatter && ES == 4) {
+            if (store.accumulate)
+                v = make_uint4(as_bits(__builtin_fmaf(gate, as_float(v.x), x.x)), as_bits(__builtin_fmaf(gate, as_float(v.y), x.y)),
+                               as_bits(__builtin_fmaf(gate, as_float(v.z), x.z)), as_bits(__builtin_fmaf(gate, as_float(v.w), x.w)));
+            else if (store.gate)
+                v = make_uint4(as_bits(gate * as_float(v.x)), as_bits(gate * as_float(v.y)), as_bits(gate * as_float(v.z)),
+                               as_bits(gate * as_float(v.w)));
+        }
+        uint8_t *at = dst + t * pitch;
+        if (ES == 4 && whole_chunks) {
+            store_streaming(at, v);
+        } else if (ES < 4) {
+            *reinterpret_cast<uint4 *>(at) = v;
+        } else {                      // 32-bit rows that are not a multiple of 16 bytes
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < live) reinterpret_cast<uint32_t *>(at)[e] = w[e];
+        }
+    }
+};
+
+// Behind a tile's stage buffers: what its outputs need that takes a load each, fetched beside the K loop by direct loads (the
+// compiler would wait for a load into registers, and with it for the stages).
+//   table : the byte table      dest : output row of every tile row (kScatter with a row list)      gate : its factor
+template <class Store, int BM>
+struct OutSide {
+    static constexpr int ROWS = BM < 64 ? 64 : BM;
+    static constexpr int TABLE = 0, DEST = Store::kTableBytes, GATE = DEST + ROWS * 4;
+    static constexpr int BYTES = Store::kTableBytes + (Store::kScatter ? ROWS * 8 : 0);
+    const Store &store;
+    const int32_t *rows;
+    long m0, n_rows;
+    uint8_t *lds;              // BYTES of its own
+
+    __device__ __forceinline__ long row(int ml) const { return min(m0 + ml, n_rows - 1); }
+    __device__ __forceinline__ uint32_t at(int off) const { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds + off; }
+    // before the loads of the first stage
+    __device__ __forceinline__ void fetch_rows(int wave, int lane) const {
+        if constexpr (Store::kTableBytes != 0) {
+            if (wave == 0) direct_load_4(static_cast<const uint8_t *>(store.table) + lane * 4, at(TABLE));
+        }
+        if constexpr (Store::kScatter) {
+            if (rows && wave < ROWS / 64) direct_load_4(rows + row(wave * 64 + lane), at(DEST + wave * 256));
+        }
+    }
+    // once those have landed; the wavefront reads what it fetched itself
+    __device__ __forceinline__ void fetch_gates(int wave, int lane) const {
+        if constexpr (Store::kScatter) {
+            if (store.gate && wave < ROWS / 64) direct_load_4(store.gate + dest(wave * 64 + lane), at(GATE + wave * 256));
+        }
+    }
+    // behind a barrier
+    __device__ __forceinline__ long dest(int ml) const {
+        if constexpr (Store::kScatter)
+            if (rows) return (long)reinterpret_cast<const int32_t *>(lds + DEST)[ml];
+        return row(ml);
+    }
+    __device__ __forceinline__ float gate(int ml) const {
+        if constexpr (Store::kScatter)
+            if (store.gate) return reinterpret_cast<const float *>(lds + GATE)[ml];
+        return 1.0f;
+    }
+};
 
 template <class T, int BM, int BN, int SB, int NS, class Store>
 struct NtShape {
     static constexpr int STAGE = (BM + T::kPlanes * BN) * SB;
     // epilogue staging: 32 rows of a wavefront's columns each, 16 bytes apart modulo the banks
     static constexpr int PITCH = BN / 2 * Store::kBytes + 16, SLAB_BYTES = 32 * PITCH;
-    static constexpr int EPI_BYTES = 4 * SLAB_BYTES + Store::kTableBytes;
-    static constexpr int LDS_BYTES = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
+    static constexpr int RING_BYTES = NS * STAGE > 4 * SLAB_BYTES ? NS * STAGE : 4 * SLAB_BYTES;
+    // a ring that fills half of a CU's LDS to the last byte: the side loads wait for the ring to be free
+    static constexpr bool SIDE_LATE = RING_BYTES == 80 * 1024 && OutSide<Store, BM>::BYTES > 0;
+    static constexpr int SIDE_AT = SIDE_LATE ? 4 * SLAB_BYTES : RING_BYTES;
+    static constexpr int LDS_BYTES = SIDE_LATE ? RING_BYTES : RING_BYTES + OutSide<Store, BM>::BYTES;
+    static_assert(SIDE_AT + OutSide<Store, BM>::BYTES <= LDS_BYTES, "room for the side loads");
 };
 
 template <class T, int BM, int BN, int SB, int NS, int LS, class Store>
@@ -249,6 +315,8 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
         for (int p = 0; p < NP; ++p)
             b_src[p][i] = static_cast<const uint8_t *>(g.b[p]) + (size_t)n * row_bytes + c * 16;
     }
+
+    const OutSide<Store, BM> side{store, rows, m0, n_rows, lds + S::SIDE_AT};
 
     // Direct load number q (0 .. LOADS-1) of a stage: A rows first, then the B planes.
     auto issue_load = [&](int q, int buf, int kbyte) {
@@ -336,6 +404,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     static_assert(LS >= 1 && LS <= KK, "loads of a stage are spread over at most one stage of steps");
     const int n_stages = (int)(row_bytes / kStageBytes);
     uint4 af[2][MI], bf[2][NP][NJ];
+    if constexpr (!S::SIDE_LATE) side.fetch_rows(wave, lane);
 #pragma unroll
     for (int q = 0; q < NS; ++q)
         if (q < n_stages) issue_stage(q, q * kStageBytes);
@@ -352,6 +421,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     };
     // this wavefront's loads of stage 0 have landed (later stages may still be in flight)
     wait_all_but((n_stages < NS ? n_stages : NS) - 1);
+    if constexpr (!S::SIDE_LATE) side.fetch_gates(wave, lane);
     __syncthreads();                             // ... and everyone's
     read_frags(lds, 0, af[0], bf[0]);
     int buf = 0, prev = NS - 1;                  // ring slots of stage s and of stage s-1
@@ -453,50 +523,79 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     //      its own.  Staging 64 rows of the workgroup's whole tile took two barriers per 32 rows of a wavefront and one
     //      LDS write per element: 98304 x 1024 <- 256 int8 to int8 75 -> 64 us, 12608 x 1536 <- 384 28 -> 25 us.
     constexpr int PITCH = S::PITCH, CPR = BN / 2 * ES / 16;       // 16-byte chunks of a staged row
+    constexpr int NC = CPR / 2, ROWS_PER_CHUNK = 64 / CPR;        // chunks of a lane per 32 rows, and the rows between them
     uint8_t *slab = lds + wave * S::SLAB_BYTES;
-    uint8_t *table = lds + 4 * S::SLAB_BYTES;
-    const bool whole_chunks = (size_t)N * ES % 16 == 0;
-    __syncthreads();                              // the last stage has been read
-    if constexpr (Store::kTableBytes != 0) {
-        table[tid] = static_cast<const uint8_t *>(store.table)[tid];
+    const uint8_t *table = side.lds;
+    const int cc = lane % CPR, cr = lane / CPR;                   // this lane's chunk of a row, its first row
+    const ChunkOut<Store> chunk(store, n0 + wn + cc * (16 / ES), N);
+    auto row_of = [&](int i, int q) { return wm + i * 32 + q * ROWS_PER_CHUNK + cr; };
+    wait_loads_in_flight<0>();
+    __syncthreads();                              // the last stage has been read, `side` is complete
+    if constexpr (S::SIDE_LATE) {
+        side.fetch_rows(wave, lane);
+        wait_loads_in_flight<0>();
+        side.fetch_gates(wave, lane);
+        wait_loads_in_flight<0>();
         __syncthreads();
     }
+    // Table lookups run one 32x32 tile ahead of the packing: four at a time, each four waited out the LDS's latency (131072 x
+    // 1024 <- 256: 4.5 us per 256 x 128 tile, longer than its products).
+    constexpr int AHEAD = Store::kTableBytes != 0 ? 1 : 0;
+    uint32_t conv[1 + AHEAD][16];
+    auto convert = [&](auto t_c) {
+        constexpr int t = decltype(t_c)::value, i = t / NJ, j = t % NJ;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
+        for (int r = 0; r < 16; ++r) {
+            const int nl = j * 32 + (ROWS_ACROSS ? 8 * (r / 4) + 4 * fg + r % 4 : fr);
+            conv[t & AHEAD][r] = store.convert(acc[i][j][r], min(n0 + wn + nl, N - 1), table);
+        }
+    };
+    // With nothing to read for the outputs, no registers are kept for it: 131072 x 256 <- 1024 was 87 us with them, 82 without.
+    auto emit = [&](auto reads_c) {
+        constexpr bool READS = decltype(reads_c)::value;
+        float4 ext[READS ? 2 : 1][NC];
+        auto fetch = [&](int i) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
+            for (int q = 0; q < NC; ++q) ext[READS ? i & 1 : 0][q] = READS ? chunk.fetch(side.dest(row_of(i, q))) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        };
+        fetch(0);
+        if constexpr (AHEAD) convert(std::integral_constant<int, 0>{});
+        static_for<MI * NJ>([&](auto t_c) {
+            constexpr int t = decltype(t_c)::value, i = t / NJ, j = t % NJ;
+            if constexpr (t + AHEAD < MI * NJ) convert(std::integral_constant<int, t + AHEAD>{});
+            if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+            const uint32_t(&v)[16] = conv[t & AHEAD];
             if constexpr (ROWS_ACROSS) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int nl = j * 32 + 8 * q + 4 * fg;
-                    uint32_t v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = store.convert(acc[i][j][4 * q + e], min(n0 + wn + nl + e, N - 1), table);
-                    uint8_t *at = slab + fr * PITCH + nl * ES;
+                    uint8_t *at = slab + fr * PITCH + (j * 32 + 8 * q + 4 * fg) * ES;
                     if constexpr (ES == 1)
-                        *reinterpret_cast<uint32_t *>(at) = v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24);
+                        *reinterpret_cast<uint32_t *>(at) = (v[4 * q] | (v[4 * q + 1] << 8)) | ((v[4 * q + 2] | (v[4 * q + 3] << 8)) << 16);
                     else if constexpr (ES == 2)
-                        *reinterpret_cast<uint2 *>(at) = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
+                        *reinterpret_cast<uint2 *>(at) = make_uint2(v[4 * q] | (v[4 * q + 1] << 16), v[4 * q + 2] | (v[4 * q + 3] << 16));
                     else
-                        *reinterpret_cast<uint4 *>(at) = make_uint4(v[0], v[1], v[2], v[3]);
+                        *reinterpret_cast<uint4 *>(at) = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
                 }
             } else {
-                const int nl = j * 32 + fr;
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    *reinterpret_cast<uint32_t *>(slab + mfma32_row(r, lane) * PITCH + nl * 4) =
-                        store.convert(acc[i][j][r], min(n0 + wn + nl, N - 1), table);
+                    *reinterpret_cast<uint32_t *>(slab + mfma32_row(r, lane) * PITCH + (j * 32 + fr) * 4) = v[r];
             }
-        }
+            if constexpr (j == NJ - 1) {                  // 32 rows are complete
+                if constexpr (i + 1 < MI) fetch(i + 1);
 #pragma unroll
-        for (int q = 0; q < CPR / 2; ++q) {
-            const int c = lane + 64 * q, ml = c / CPR, cc = c % CPR;
-            const uint4 v = *reinterpret_cast<const uint4 *>(slab + ml * PITCH + cc * 16);
-            const long m = m0 + wm + i * 32 + ml;
-            const int n = n0 + wn + cc * (16 / ES);
-            if (m < n_rows && n < N) store_chunk(store, v, rows, m, n, N, whole_chunks);
-        }
+                for (int q = 0; q < NC; ++q) {
+                    const int ml = row_of(i, q);
+                    const uint4 c = *reinterpret_cast<const uint4 *>(slab + (q * ROWS_PER_CHUNK + cr) * PITCH + cc * 16);
+                    if (m0 + ml < n_rows && chunk.live > 0) chunk.put(c, ext[READS ? i & 1 : 0][q], side.gate(ml), side.dest(ml));
+                }
+            }
+        });
+    };
+    if constexpr (ChunkOut<Store>::MAY_READ) {
+        if (chunk.reads()) return emit(std::true_type{});
     }
+    emit(std::false_type{});
 }
 
 // A tile shape as launch_tile and the kernels below take it.

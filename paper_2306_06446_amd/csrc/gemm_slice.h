@@ -22,7 +22,7 @@ struct AccElem<I8Traits> { typedef int32_t type; };
 template <>
 struct AccElem<F16Traits> { typedef float type; };
 
-template <class T, int MI, int NJ, int SB, int NS>
+template <class T, int MI, int NJ, int SB, int NS, class Store>
 struct SliceShape {
     static constexpr int BM = 32 * MI, BN = 32 * NJ;
     static constexpr int KK = SB / 32;                       // 32-byte steps of a stage = shares of K
@@ -32,7 +32,8 @@ struct SliceShape {
     static constexpr int A_BYTES = BM * SB, B_BYTES = BN * SB;
     static constexpr int STAGE = A_BYTES + NP * B_BYTES;
     static constexpr int RED_BYTES = KK * BM * BN * 4;       // partial tiles of the epilogue
-    static constexpr int LDS_BYTES = (NS * STAGE > RED_BYTES ? NS * STAGE : RED_BYTES) + 256;
+    static constexpr int RING_BYTES = NS * STAGE > RED_BYTES ? NS * STAGE : RED_BYTES;
+    static constexpr int LDS_BYTES = RING_BYTES + OutSide<Store, BM>::BYTES;
     static_assert(SB == 64 || SB == 128, "stage rows of 64 or 128 bytes");
     static_assert(NJ % NW == 0 && NS >= 2, "tile shape");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
@@ -40,7 +41,7 @@ struct SliceShape {
 
 template <class T, int MI, int NJ, int SB, int NS, class Store>
 __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
-    using S = SliceShape<T, MI, NJ, SB, NS>;
+    using S = SliceShape<T, MI, NJ, SB, NS, Store>;
     constexpr int CPR = SB / 16, RPI = 1024 / SB;            // 16-byte chunks per LDS row, LDS rows per direct load
     constexpr int A_TOT = S::BM / RPI, B_TOT = S::BN / RPI;  // direct loads per stage: A, one plane of B
     constexpr int A_INSTR = A_TOT < 4 ? 1 : A_TOT / 4;       // per wavefront (fewer than four: two wavefronts load the same rows)
@@ -118,6 +119,8 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
     const int frag = fr * SB + swizzle<CPR>(fr, 2 * kk + fg) * 16;      // the swizzle depends on the row modulo 16 only
 
     const int n_stages = (int)(row_bytes / SB);
+    const OutSide<Store, S::BM> side{store, rows, m0, n_rows, lds + S::RING_BYTES};
+    side.fetch_rows(wave, lane);
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
         if (q < n_stages) issue_stage(q, q * SB);
@@ -132,6 +135,7 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
                 if (later == l) wait_loads_in_flight<l * LOADS>();
             });
         __syncthreads();                                      // stage s is there; everyone has read stage s - 1
+        if (s == 0) side.fetch_gates(wave, lane);
         if (s + NS - 1 < n_stages) issue_stage(slot_w, (s + NS - 1) * SB);
         const uint8_t *A = lds + slot_r * S::STAGE + frag, *B = lds + slot_r * S::STAGE + S::A_BYTES + wn * SB + frag;
         uint4 af[MI], bf[S::NP][S::NJW];
@@ -152,12 +156,21 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
         slot_w = slot_w + 1 == NS ? 0 : slot_w + 1;
     }
 
+    // ---- where this lane's chunks go and what they need from memory: asked for before the partial tiles meet
+    constexpr int ES = Store::kBytes, EPC = 16 / ES;          // elements of a 16-byte output chunk
+    constexpr int CHUNK_ROWS = 256 / (S::BN / EPC), NC = (S::BM + CHUNK_ROWS - 1) / CHUNK_ROWS;
+    const int nl = tid % (S::BN / EPC) * EPC, cr = tid / (S::BN / EPC);       // its first column, its first row
+    const ChunkOut<Store> chunk(store, n0 + nl, N);
+    wait_loads_in_flight<0>();
+    float4 ext[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) ext[q] = chunk.fetch(side.dest(min(q * CHUNK_ROWS + cr, S::BM - 1)));
+
     // ---- the partial tiles meet in LDS
     elem_t *red = reinterpret_cast<elem_t *>(lds);
-    uint8_t *table = lds + S::LDS_BYTES - 256;
+    const uint8_t *table = side.lds;
     constexpr int TILE = S::BM * S::BN;
-    __syncthreads();                                          // the last stage has been read
-    if (Store::kTableBytes != 0) table[tid] = static_cast<const uint8_t *>(store.table)[tid];
+    __syncthreads();                                          // the last stage has been read, `side` is complete
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -191,14 +204,10 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
         }
     }
 
-    constexpr int ES = Store::kBytes, EPC = 16 / ES;          // elements of a 16-byte output chunk
-    constexpr int CHUNKS = TILE / EPC;
-    const bool whole_chunks = (size_t)N * ES % 16 == 0;
-    for (int c = tid; c < CHUNKS; c += 256) {
-        const int ml = c / (S::BN / EPC), nl = (c % (S::BN / EPC)) * EPC;
-        const long m = m0 + ml;
-        const int n = n0 + nl;
-        if (m >= n_rows || n >= N) continue;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        const int ml = q * CHUNK_ROWS + cr, n = n0 + nl;
+        if (ml >= S::BM || m0 + ml >= n_rows || chunk.live <= 0) continue;
         uint32_t bits[EPC];
 #pragma unroll
         for (int e4 = 0; e4 < EPC / 4; ++e4) {
@@ -227,7 +236,7 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
             for (int q = 0; q < 4; ++q) w[q] = bits[4 * q] | (bits[4 * q + 1] << 8) | (bits[4 * q + 2] << 16) | (bits[4 * q + 3] << 24);
             v = make_uint4(w[0], w[1], w[2], w[3]);
         }
-        store_chunk(store, v, rows, m, n, N, whole_chunks);
+        chunk.put(v, ext[q], side.gate(ml), side.dest(ml));
     }
 }
 
@@ -235,7 +244,7 @@ template <class T, int MI, int NJ, int SB, int NS>
 struct SliceTile {
     static constexpr int BM = 32 * MI, BN = 32 * NJ;
     template <class Store>
-    static constexpr int lds_bytes() { return SliceShape<T, MI, NJ, SB, NS>::LDS_BYTES; }
+    static constexpr int lds_bytes() { return SliceShape<T, MI, NJ, SB, NS, Store>::LDS_BYTES; }
     template <class Store>
     __device__ static __forceinline__ void run(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
         slice_gemm_tile<T, MI, NJ, SB, NS, Store>(g, store, block, lds);
