@@ -124,6 +124,8 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
     const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)ring;
     constexpr int RPI = 1024 / (DVC * 4), LPR = DVC / 4;         // V rows per load, lanes per row
     const int c_tok = lane / (2 * WB) % 16, c_dw = min(lane % (2 * WB), 2 * (W - w0) - 1);     // (one word: the upper lanes repeat)
+    // (32-bit lane offsets: at most RPI - 1 rows of H * DV floats, and with B * H < 2^20 heads that is 7 x 2^27 bytes with 32
+    // columns to a workgroup, 3 x 2^29 with 64.  Whole rows beyond those go into the step's 64-bit part.)
     const uint32_t v_lane = (uint32_t)(lane / LPR) * (uint32_t)v_row + (lane % LPR) * 16;
     const uint32_t c_lane = (uint32_t)c_tok * (uint32_t)c_row + c_dw * 4;
     auto issue = [&](int i, int slot) {
@@ -136,8 +138,11 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
             sa::direct_load_4(cp, c_lane, at + V_BYTES);
         } else {
 #pragma unroll
-            for (int k = 0; k < V_BYTES / 1024; ++k)
-                sa::direct_load_16(vp, (uint32_t)min(k * RPI + lane / LPR, n - 1) * (uint32_t)v_row + (lane % LPR) * 16, at + k * 1024);
+            for (int k = 0; k < V_BYTES / 1024; ++k) {
+                const int row0 = min(k * RPI, n - 1);            // row min(k * RPI + lane / LPR, n - 1), in two parts
+                sa::direct_load_16(vp + (size_t)row0 * v_row, (uint32_t)min(lane / LPR, n - 1 - row0) * (uint32_t)v_row + (lane % LPR) * 16,
+                                   at + k * 1024);
+            }
             sa::direct_load_4(cp, (uint32_t)min(c_tok, n - 1) * (uint32_t)c_row + c_dw * 4, at + V_BYTES);
         }
     };

@@ -55,3 +55,26 @@ def test_both_code_modes_against_fp64(sa, B, H, Nq, Nk, W, dv):
         err_kv, err = (kv.double() - kv_ref).abs(), (out.double() - ref).abs()
         assert bool((err_kv <= 1e-4 * kv_ref.abs() + 1e-5 * max(1.0, float(kv_ref.square().mean().sqrt()))).all())
         assert bool((err <= 1e-4 * ref.abs() + 1e-5).all()), float(err.max())
+
+
+@pytest.mark.parametrize("Nq", [0, 1])                     # K^T V alone, both products in one launch
+def test_rows_of_a_ragged_step_more_than_4_gib_apart(sa, Nq):
+    B, H, Nk, dv = 1, 600_000, 15, 128                     # 14 rows of V take 14 * H * dv * 4 = 4.30e9 > 2^32 bytes
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    k = codes(g, B, H, Nk, 1)
+    v = torch.randn((B, Nk, H, dv), generator=g, device="cuda")
+    if Nq:
+        q = codes(g, B, H, Nq, 1)
+        out, kv = sa.sa_additive_attention(q, k, v, 0.125, 64)
+    else:
+        kv = sa.sa_additive_attention(None, k, v, 0.125, 64, phases=1)[1]
+    heads = torch.cat((torch.tensor([0, 1, H // 2, H - 2, H - 1], device="cuda"), torch.randint(0, H, (200,), generator=g, device="cuda")))
+    ks = 2 * bits_of(k[0, heads]) - 1                      # [heads, Nk, 64]
+    ref = torch.matmul(ks.transpose(-1, -2).contiguous(), v[0][:, heads].double().transpose(0, 1).contiguous())
+    err = (kv[0, heads].double() - ref).abs()
+    assert bool((err <= 1e-4 * ref.abs() + 1e-5 * float(ref.square().mean().sqrt())).all()), float(err.max())
+    if Nq:
+        o_ref = 0.125 * torch.matmul(2 * bits_of(q[0, heads]) - 1, ref)
+        err = (out[0][:, heads].double().transpose(0, 1) - o_ref).abs()
+        assert bool((err <= 1e-4 * o_ref.abs() + 1e-5 * float(o_ref.square().mean().sqrt())).all()), float(err.max())
