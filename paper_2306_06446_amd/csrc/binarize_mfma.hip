@@ -4,10 +4,8 @@
 // For almost every (row, bit) that sign is decided long before rounding matters, so the kernel
 //   1. computes z~ = x . r^_j on the fp16 matrix cores, r^_j = r_j / |r_j|, with a three-product split
 //      (x = xh + xl, r^ = rh + rl, each fp16 rounded to nearest; z~ = xh rh + xh rl + xl rh),
-//   2. keeps sign(z~) wherever |z~| > theta |x|.  theta covers, against |x| |r^_j| = |x| (Cauchy-Schwarz bound of
-//      sum |x_k r^_kj|): the dropped xl rl and the roundings of xl and rl, 3 * 2^-22; the fp32 accumulation of the 3 d
-//      products, 3 d * 2^-23 even if every addition truncates; that of the defining chain, (d + 2) * 2^-24.  Together
-//      2.8e-5 at d = 64: theta = 2^-15 (2^-16 at d = 32, 2^-14 at d = 128), and
+//   2. keeps sign(z~) wherever |z~| > theta |x|.  theta is 2^-16, 2^-15 and 2^-14 at d = 32, 64 and 128; hash_margin.h adds up
+//      what it has to cover (1.49, 2.87 and 5.60 e-5 against 1.53, 3.05 and 6.10 e-5), and
 //   3. re-runs the defining chain, one (row, bit) per lane, for the rest (0.02 % of the bits on Gaussian data at
 //      d = 64; every bit if the data is degenerate) and flips the stored bit if needed.
 // NaN / Inf / denormal-range sums fail the test in step 2 and take step 3, which is the definition.
@@ -26,6 +24,7 @@
 // between two lanes.  Q and K, before -> now: 8 x 16384 x 4 heads x 64 -> 256 bits 143 -> 116 us, 1 x 16384 x 4 the
 // same 24.3 -> 22.8, 64 x 197 x 12 x 64 -> 128 bits 28.7 -> 28.3.
 #include "common.h"
+#include "hash_margin.h"
 #include "side_work.h"
 
 namespace sa {
@@ -38,11 +37,6 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kListCap = 128;                 // unsettled bits parked per wavefront
-constexpr float kKeepFloor = 3.2e-19f;        // |z| below that: products and sums of the chain may be denormal
-constexpr float kColumnScale = 1024.0f;       // |r^_j| as staged: its lower terms are then normal fp16 numbers
-
-template <int D>
-constexpr float theta() { return D == 32 ? 0x1p-16f : (D == 64 ? 0x1p-15f : 0x1p-14f); }
 
 // n / d for 0 <= n < 2^31 as one multiplication and one shift.
 struct FastDiv {
@@ -175,10 +169,9 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
         float n2 = 0.0f;
 #pragma unroll
         for (int p = 0; p < TPC; ++p) n2 += n2_s[p][c];
-        // a dead, overflowing or non-finite column gets an all-zero r^: z~ = 0 fails the margin test, so
+        // a dead, denormal, overflowing or non-finite column gets an all-zero r^: z~ = 0 fails the margin test, so
         // every bit of that column is parked and settled by the defining chain
-        float inv = 1.0f / __builtin_sqrtf(n2);
-        inv = inv > 0.0f && inv < 3e38f ? inv : 0.0f;
+        const float inv = n2 >= kColumnMin2 && n2 < __builtin_inff() ? 1.0f / __builtin_sqrtf(n2) : 0.0f;
         uint32_t up[4], lo[4];
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
@@ -226,10 +219,9 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
             a += __shfl_xor(a, 16);
             nx2[u] = a + __shfl_xor(a, 32);
         }
-        // Rows of ordinary magnitude (|x| in 2^-4 .. 2^12) split as they are: nothing overflows fp16, and the terms that
-        // fall below its normal range are off by at most sqrt(d) 2^-25 together.  Others are brought to |x| ~ 1 first.
+        // Rows of ordinary magnitude (|x| in 2^-2 .. 2^12) split as they are, others are brought to |x| ~ 1 first (hash_margin.h).
         float unit[2] = {1.0f, 1.0f};
-        const bool odd = !(nx2[0] >= 0x1p-8f && nx2[0] <= 0x1p24f && nx2[1] >= 0x1p-8f && nx2[1] <= 0x1p24f);
+        const bool odd = !(nx2[0] >= kOrdinaryMin2 && nx2[0] <= kOrdinaryMax2 && nx2[1] >= kOrdinaryMin2 && nx2[1] <= kOrdinaryMax2);
         if (__ballot(odd) != 0) {                                  // wave-uniform
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -245,7 +237,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             keep[u] = nx2[u] < __builtin_inff()
-                          ? __builtin_fmaxf(theta<D>() * __builtin_sqrtf(nx2[u]), kKeepFloor) * unit[u] * kColumnScale
+                          ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2[u]), kKeepFloor) * unit[u] * kColumnScale
                           : __builtin_inff();
 #pragma unroll
             for (int s = 0; s < S; ++s) {

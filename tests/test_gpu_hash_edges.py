@@ -32,3 +32,36 @@ def test_bits_are_the_chains(sa, B, N, H, d, nbits, kind):
     sa.sa_binarize_pair(x[0], x[1], proj, nbits, codes[0], codes[1])
     for t, c in zip(x, codes):
         assert torch.equal(c, sa.sa_binarize(t, proj, nbits, variant=0))
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_bits_are_the_chains_at_the_margin(sa, d):
+    """Rows whose product with a column is about what the margin allows for, at the lengths between which rows split unscaled; rows
+    whose upper and lower fp16 terms pull that product to different sides; columns whose squares underflow."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    N, H, nbits = 4096, 2, 128
+    proj = torch.randn((d, nbits), generator=g, device="cuda")
+    unit = (proj / proj.norm(dim=0)).double()
+    col = torch.randint(0, nbits, (1, N, H), generator=g, device="cuda")
+    r = unit.t()[col]                                                       # [1, N, H, d]
+    limits = torch.tensor([0.25, 0.25 * (1 - 2 ** -12), 0.25 * (1 + 2 ** -12), 0.0625, 0.5, 1.4, 4096.0, 4096.0 * 1.001],
+                          device="cuda", dtype=torch.float64)
+    length = limits[torch.randint(0, 8, (1, N, H, 1), generator=g, device="cuda")]
+    theta = {32: 2.0 ** -16, 64: 2.0 ** -15, 128: 2.0 ** -14}[d]
+    x = torch.randn((1, N, H, d), generator=g, device="cuda", dtype=torch.float64)
+    x -= (x * r).sum(-1, keepdim=True) * r
+    x = x / x.norm(dim=-1, keepdim=True)
+    near = theta * (3 * torch.rand((1, N, H, 1), generator=g, device="cuda", dtype=torch.float64) - 1.5)
+    q = ((x + near * r) * length).float()
+    up = (x * length).half().double()                                       # k: upper terms + lower terms of the opposite side
+    lower = -torch.sign((up * r).sum(-1, keepdim=True)) * r.sign() * up.abs() * 2.0 ** -12.2
+    k = (up + lower).float()
+    slim = proj.clone()
+    slim[:, ::3] *= 2.0 ** -75
+    slim[:, 1::3] *= 2.0 ** -60
+    for p in (proj, slim):
+        codes = [torch.zeros((1, H, N, nbits // 64), dtype=torch.int64, device="cuda") for _ in range(2)]
+        sa.sa_binarize_pair(q, k, p, nbits, *codes)
+        for t, c in zip((q, k), codes):
+            assert torch.equal(c, sa.sa_binarize(t, p, nbits, variant=0))
