@@ -84,10 +84,11 @@ struct KtvLds {
     static_assert(RING_BYTES >= kKtvWaves * 32 * DVC * 4, "the final sum reuses the ring");
 };
 
+// dst is not __restrict__: a kernel that goes on to Q(K^T V) reads the same memory through AddFused::kv_in.
 // ksum (ZO): int32 [splits][BH][nbits], the number of tokens of the range whose code bit is set.
 // block = ((bh * n_groups + group) * n_cols + column group) * splits + split
 template <int DVC, int WB, int PH, int RING, bool ZO>
-__device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, const float *__restrict__ v, float *__restrict__ dst,
+__device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, const float *__restrict__ v, float *dst,
                                           int32_t *__restrict__ ksum, long BH, int H, int Nk, int W, int DV, int splits,
                                           int tokens_per_block, int block, uint8_t *ring_s) {
     constexpr int JT = DVC / 32, TB = 2 * WB;                    // 32-column and 32-bit tiles
@@ -542,8 +543,8 @@ __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__res
 // 33.2 -> 29.1, 64 x 3 x 197 x 64 bits 13.7 -> 9.9.
 template <int DVC, int W, int PH, int WB, int RING>
 __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
-                                                                 float *__restrict__ kv, const uint64_t *__restrict__ q_codes,
-                                                                 AddFused f, int H, int Nq, int Nk, int DV, long BH) {
+                                                                 float *kv, const uint64_t *__restrict__ q_codes, AddFused f,
+                                                                 int H, int Nq, int Nk, int DV, long BH) {
     constexpr int KB = KtvLds<DVC, WB, RING, false>::BYTES, QB = QkvLds<DVC, W, false>::BYTES;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[KB > QB ? KB : QB];
     ktv_block<DVC, WB, PH, RING, false>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
