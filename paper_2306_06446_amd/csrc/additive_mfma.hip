@@ -212,7 +212,7 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
             }
             sg[t] = __builtin_bit_cast(v8bf, make_uint4(d[0], d[1], d[2], d[3]));
         }
-        __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): this slot has been read ...
+        sa::wait_lds_reads();                                    // this slot has been read ...
         if (i + RING * PH < n_steps) issue(i + RING * PH, slot);           // ... and is free for the step RING ahead
 #pragma unroll
         for (int j = 0; j < JT; ++j) {
@@ -239,11 +239,10 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
     int slot = 0, done = 0;
     for (int i = phase; i < n_steps; i += PH) {
         const int later = (n_steps - 1 - i) / PH;                // steps of this wavefront after this one
-        if (later >= RING - 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (((RING - 1) * LOADS) & 15) | ((((RING - 1) * LOADS) >> 4) << 14));
-        else if (RING > 2 && later == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * LOADS) & 15) | (((2 * LOADS) >> 4) << 14));
-        else if (later == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15));      // (LOADS <= 5)
-        else __builtin_amdgcn_s_waitcnt(0x0F70);
-        asm volatile("" ::: "memory");                           // the slot's bytes are not read before this point
+        if (later >= RING - 1) sa::wait_loads_in_flight<(RING - 1) * LOADS>();
+        else if (RING > 2 && later == 2) sa::wait_loads_in_flight<2 * LOADS>();
+        else if (later == 1) sa::wait_loads_in_flight<LOADS>();
+        else sa::wait_loads_in_flight<0>();
         step(i, slot);
         slot = slot + 1 == RING ? 0 : slot + 1;
         if (ZO && (++done & 0x1FFF) == 0) {        // before the 16-bit halves can overflow

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
     int cnt = 0;                   // parked entries of this wavefront (wave-uniform)
     uint64_t *list = list_s[wave];
     auto work_off = [&]() {
-        __builtin_amdgcn_s_waitcnt(0x0F70);      // the words these bits live in have been stored
+        wait_loads_in_flight<0>();               // the words these bits live in have been stored
 #pragma unroll 1
         for (int t0 = 0; t0 < cnt; t0 += 64)
             if (t0 + lane < cnt) settle_entry<D, C, 16>(list[t0 + lane], ts, r_s, c_first, map);
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
 
     // The wavefronts' leftovers are pooled and worked off 64 entries per pass, pass p by wavefront p % kWaves: the
     // cost of a pass is the latency of its loads, so full passes side by side beat nearly empty ones.
-    __builtin_amdgcn_s_waitcnt(0x0F70);          // this wavefront's words have been stored
+    wait_loads_in_flight<0>();                   // this wavefront's words have been stored
     if (lane == 0) cnt_s[wave] = cnt;
     __syncthreads();
     int total = 0;

@@ -97,6 +97,25 @@ __device__ inline void direct_load_4(const void *src, uint32_t lds_base) {
         : "memory");
 }
 
+// The waits that kernels place by hand, for what the compiler does not track (direct loads) or is not meant to wait for.  To the
+// compiler the builtin alone is no memory access: it may move a read of what a direct load brought to before it, or a store to
+// behind it.  The empty statements keep memory accesses on their sides.
+//   wait_loads_in_flight<N> : until at most N of this wavefront's vector-memory operations are still in flight (loads complete
+//                             in issue order, so the oldest ones are the ones that have landed; stores count too)
+//   wait_lds_reads          : until this wavefront's LDS operations are done
+template <int N>
+__device__ inline void wait_loads_in_flight() {
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+    asm volatile("" ::: "memory");
+}
+__device__ inline void wait_lds_reads() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    asm volatile("" ::: "memory");
+}
+
 // One Linear layer on the rows an expert was given, gated and scattered (the two experts of sa_moe_linear):
 //   y[rows[i], :] = gate[rows[i]] * (xh[rows[i], :] . W^T)                      fp16 operands   (mult_mlp.hip)
 //   y[rows[i], :] = gate[rows[i]] * out_scale * (xq[rows[i], :] . Wshift^T)      int8 / 4-bit    (shift_linear.hip)

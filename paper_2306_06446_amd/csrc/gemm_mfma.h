@@ -100,13 +100,6 @@ __device__ inline int swizzle(int r, int c) {
 //       laid out [batch, head, token, word]), int head_dim (64 or 128), tokens (per batch element), heads
 //   static constexpr bool kLinear     : fp32 outputs leave as fma(value, scale, residual[m, n]) into
 //       column blocks: float *parts[3], int part_width (a multiple of 4), const float *residual, float scale
-// Wait until at most N of this wavefront's vector-memory loads are still in flight (loads
-// complete in issue order, so the oldest ones are the ones that have landed).
-template <int N>
-__device__ inline void wait_loads_in_flight() {
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
 
 // The 16-byte chunks at columns n .. n + 16 / kBytes - 1 of the output: where they go, and what they need from memory besides
 // the product (the residual, or what the destination holds).  fetch() is apart from put() so that the reads of many chunks

@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
         }
         const int n = min(kKeyChunk, Nk - j0);
         const int n_pad = (n + 15) & ~15;
-        __builtin_amdgcn_s_waitcnt(0x0F70);          // this wavefront's direct loads of the chunk have landed
+        sa::wait_loads_in_flight<0>();               // this wavefront's direct loads of the chunk have landed
         __syncthreads();                             // ... everyone's; the planes of the previous chunk have been consumed
         // raw rows -> the two transposed bf16 planes; one task = eight consecutive keys of one column (a wavefront
         // reads 64 consecutive floats of a row per instruction, and writes 16 bytes per lane and plane)

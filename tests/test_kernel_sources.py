@@ -18,3 +18,16 @@ def test_memory_that_a_kernel_reads_back_is_not_declared_restrict():
         lists = parameters(text, function)
         assert len(lists) == 1
         assert re.search(r"float \*%s\b" % name, lists[0]), (function, lists[0])
+
+
+def test_hand_placed_waits_hold_for_the_compiler_too():
+    """s_waitcnt is no memory access to the compiler: it stands in helpers only, between two statements that are."""
+    found = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*"))):
+        lines = [l.strip() for l in open(path)]
+        for i, l in enumerate(lines):
+            if "__builtin_amdgcn_s_waitcnt" in l:
+                fence = 'asm volatile("" ::: "memory");'
+                assert os.path.basename(path) == "common.h" and lines[i - 1] == fence and lines[i + 1] == fence, (path, i + 1)
+                found += 1
+    assert found == 2
