@@ -297,9 +297,18 @@ int count_bits(const uint64_t *k_codes, int32_t *ksum, long BH, int Nk, int nbit
     return sa::check_launch("sa_linear_attention_01(bit counts)");
 }
 
-int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, float *out, int B, int H, int Nq,
-                 int Nk, int nbits, int dv, float scale, float *kv, int phases, void *workspace,
-                 size_t workspace_bytes, void *stream, const AddMode &mode) {
+// Token splits of phase 1: more than one means as many partials of K^T V in the workspace.
+int ktv_splits(bool valu, int B, int H, int Nk, int nbits, int dv) {
+    return !valu && sa::additive_mfma_ktv_supported(nbits, dv) ? sa::plan_additive_mfma(B, H, Nk, nbits, dv).splits
+                                                               : plan_ktv(B, H, Nk, nbits).splits;
+}
+
+}  // namespace
+
+// Everything sa_additive_attention asks of its arguments.
+int sa::check_additive_attention(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, const float *out, int B, int H,
+                                 int Nq, int Nk, int nbits, int dv, const float *kv, int phases, const void *workspace,
+                                 size_t workspace_bytes) {
     SA_REQUIRE(phases >= 1 && phases <= 7 && (phases & 3) != 0, SA_ERR_INVALID,
                "sa_additive_attention: phases must be 1, 2 or 3, optionally + 4");
     const bool valu = (phases & SA_ADDITIVE_VALU) != 0;
@@ -309,19 +318,42 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
                "sa_additive_attention: nbits %d must be a multiple of 64, at most 4096", nbits);
     SA_REQUIRE(dv_ok(dv), SA_ERR_UNSUPPORTED, "sa_additive_attention: dv must be 32, 64 or 128 (got %d)", dv);
     SA_REQUIRE((long)B * H < (1L << 20), SA_ERR_SHAPE, "sa_additive_attention: B*H too large");
-    if ((long)B * H == 0) return SA_OK;
+    const long BH = (long)B * H;
+    if (BH == 0) return SA_OK;
     SA_REQUIRE(kv != nullptr, SA_ERR_INVALID, "sa_additive_attention: kv is NULL");
     SA_REQUIRE(sa::aligned16(q_codes) && sa::aligned16(k_codes) && sa::aligned16(v) &&
                    sa::aligned16(out) && sa::aligned16(kv) && sa::aligned16(workspace),
                SA_ERR_ALIGN, "sa_additive_attention: pointers must be 16-byte aligned");
-    hipStream_t st = sa::as_stream(stream);
-    const int W = nbits / 64;
-    const long BH = (long)B * H;
-    const size_t kv_elems = (size_t)BH * nbits * dv;
-    const bool qkv_mfma = !valu && sa::additive_mfma_qkv_supported(nbits, dv);
-    if (phases & 2)
+    if (phases & 2) {
         SA_REQUIRE(Nq == 0 || (q_codes != nullptr && out != nullptr), SA_ERR_INVALID,
                    "sa_additive_attention: phase 2 needs q_codes and out");
+        const bool mfma = !valu && additive_mfma_qkv_supported(nbits, dv);
+        const long blocks = mfma ? BH * (dv / 32) * (((long)Nq + 255) / 256) : (BH * (((long)Nq + 63) / 64) + 3) / 4;
+        SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
+    }
+    if ((phases & 1) && Nk > 0) {
+        SA_REQUIRE(k_codes != nullptr && v != nullptr, SA_ERR_INVALID, "sa_additive_attention: phase 1 needs k_codes and v");
+        const int splits = ktv_splits(valu, B, H, Nk, nbits, dv);
+        const size_t need = splits > 1 ? (size_t)splits * BH * nbits * dv * sizeof(float) : 0;
+        SA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SA_ERR_WORKSPACE,
+                   "sa_additive_attention: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    }
+    return SA_OK;
+}
+
+namespace {
+
+int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, float *out, int B, int H, int Nq,
+                 int Nk, int nbits, int dv, float scale, float *kv, int phases, void *workspace,
+                 size_t workspace_bytes, void *stream, const AddMode &mode) {
+    const int bad = sa::check_additive_attention(q_codes, k_codes, v, out, B, H, Nq, Nk, nbits, dv, kv, phases, workspace, workspace_bytes);
+    const long BH = (long)B * H;
+    if (bad != SA_OK || BH == 0) return bad;
+    const bool valu = (phases & SA_ADDITIVE_VALU) != 0;
+    hipStream_t st = sa::as_stream(stream);
+    const int W = nbits / 64;
+    const size_t kv_elems = (size_t)BH * nbits * dv;
+    const bool qkv_mfma = !valu && sa::additive_mfma_qkv_supported(nbits, dv);
     // What phase 2 reads: K^T V (and the counts), or the partials of phase 1 where it sums them itself.
     sa::AddFused f;
     f.kv_in = kv;
@@ -339,8 +371,6 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
             if (rc == SA_OK && mode.zero_one) rc = sa::launch_zero(mode.ksum, (size_t)BH * nbits * sizeof(int32_t), st);
             if (rc != SA_OK) return rc;
         } else {
-            SA_REQUIRE(k_codes != nullptr && v != nullptr, SA_ERR_INVALID,
-                       "sa_additive_attention: phase 1 needs k_codes and v");
             const bool mfma = !valu && sa::additive_mfma_ktv_supported(nbits, dv);
             sa::AdditiveMfmaPlan m{};
             KtvPlan p{};
@@ -352,9 +382,6 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
             float *dst = kv;
             int32_t *counts = mode.ksum;
             if (splits > 1) {
-                const size_t need = (size_t)splits * kv_elems * sizeof(float);
-                SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
-                           "sa_additive_attention: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
                 dst = static_cast<float *>(workspace);
                 counts = mode.ksum_part;
             }
@@ -406,7 +433,6 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
         const int n_chunks = (Nq + 63) / 64;
         const long n_tasks = BH * n_chunks;
         const long blocks = (n_tasks + 3) / 4;
-        SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
         const dim3 grid((unsigned)blocks), block(256);
 #define SA_QKV(DV_, ZO_) \
     qkv_kernel<DV_, ZO_><<<grid, block, 0, st>>>(q_codes, kv, out, H, Nq, W, n_chunks, n_tasks, scale, den, mode.eps)

@@ -704,7 +704,6 @@ int launch_ktv_sum(const float *part, float *kv, const int32_t *ksum_part, int32
 int launch_qkv_mfma(const uint64_t *q_codes, const AddFused &f, int B, int H, int Nq, int nbits, int dv, bool zero_one,
                     hipStream_t st) {
     const long BH = (long)B * H;
-    SA_REQUIRE(BH * (dv / 32) * (((long)Nq + 255) / 256) < (1L << 31), SA_ERR_SHAPE, "sa_additive_attention: grid too large");
     switch (nbits) {
         case 64: launch_qkv_w<1>(q_codes, f, BH, H, Nq, dv, zero_one, st); break;
         case 128: launch_qkv_w<2>(q_codes, f, BH, H, Nq, dv, zero_one, st); break;

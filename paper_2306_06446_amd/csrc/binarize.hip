@@ -77,27 +77,8 @@ bool sa::binarize_pair_one_launch(const float *q, const float *k, const float *p
            q_codes && k_codes && aligned16(q) && aligned16(k) && aligned16(proj) && aligned16(q_codes) && aligned16(k_codes);
 }
 
-extern "C" int sa_binarize_pair(const float *q, const float *k, int B, int N, int H, int d, const float *proj,
-                                int nbits, uint64_t *q_codes, uint64_t *k_codes, void *stream) {
-    sa::clear_error();
-    const long rows = (long)B * N * H;
-    // both tensors are checked before anything is launched for either
-    if (rows > 0) {
-        SA_REQUIRE(q && k && q_codes && k_codes, SA_ERR_INVALID, "sa_binarize_pair: NULL buffer");
-        SA_REQUIRE(sa::aligned16(q) && sa::aligned16(k) && sa::aligned16(q_codes) && sa::aligned16(k_codes), SA_ERR_ALIGN,
-                   "sa_binarize_pair: pointers must be 16-byte aligned");
-    }
-    // one launch when the matrix-core kernel takes the shape; otherwise simply one call per tensor
-    if (B > 0 && N > 0 && H > 0 && sa::binarize_pair_one_launch(q, k, proj, q_codes, k_codes, rows, d, nbits))
-        return sa::launch_binarize_mfma(q, k, proj, q_codes, k_codes, rows, N, H, d, nbits, sa::as_stream(stream));
-    const int rc = sa_binarize_ex(q, B, N, H, d, proj, nbits, q_codes, SA_VARIANT_AUTO, stream);
-    if (rc != SA_OK) return rc;
-    return sa_binarize_ex(k, B, N, H, d, proj, nbits, k_codes, SA_VARIANT_AUTO, stream);
-}
-
-extern "C" int sa_binarize_ex(const float *x, int B, int N, int H, int d, const float *proj,
-                              int nbits, uint64_t *codes, int variant, void *stream) {
-    sa::clear_error();
+// Everything sa_binarize_ex asks of its arguments.
+int sa::check_binarize(const float *x, int B, int N, int H, int d, const float *proj, int nbits, const uint64_t *codes, int variant) {
     SA_REQUIRE(variant >= 0 && variant <= 2, SA_ERR_INVALID, "sa_binarize: unknown variant %d", variant);
     SA_REQUIRE(B >= 0 && N >= 0 && H >= 0 && d > 0 && nbits > 0, SA_ERR_INVALID,
                "sa_binarize: negative size");
@@ -110,25 +91,54 @@ extern "C" int sa_binarize_ex(const float *x, int B, int N, int H, int d, const 
     SA_REQUIRE(rows < (1L << 31), SA_ERR_SHAPE, "sa_binarize: B*N*H >= 2^31");
     if (rows == 0) return SA_OK;
     SA_REQUIRE(x != nullptr && codes != nullptr, SA_ERR_INVALID, "sa_binarize: NULL buffer");
-    SA_REQUIRE(sa::aligned16(x) && sa::aligned16(codes) && sa::aligned16(proj), SA_ERR_ALIGN,
+    SA_REQUIRE(aligned16(x) && aligned16(codes) && aligned16(proj), SA_ERR_ALIGN,
                "sa_binarize: pointers must be 16-byte aligned");
+    const long tasks = proj ? (long)B * H * ((N + 63) / 64) * (nbits / 64) : rows * (nbits / 64);      // wavefronts, vector ALU
+    SA_REQUIRE((tasks + 3) / 4 < (1L << 31), SA_ERR_SHAPE, "sa_binarize: too many rows");
+    SA_REQUIRE(!proj || d == 32 || d == 64 || d == 128, SA_ERR_UNSUPPORTED, "sa_binarize: with proj, d must be 32, 64 or 128 (got %d)", d);
+    return SA_OK;
+}
+
+int sa::check_binarize_pair(const float *q, const float *k, int B, int N, int H, int d, const float *proj, int nbits,
+                            const uint64_t *q_codes, const uint64_t *k_codes) {
+    const int rc = check_binarize(q, B, N, H, d, proj, nbits, q_codes, SA_VARIANT_AUTO);
+    return rc != SA_OK ? rc : check_binarize(k, B, N, H, d, proj, nbits, k_codes, SA_VARIANT_AUTO);
+}
+
+extern "C" int sa_binarize_pair(const float *q, const float *k, int B, int N, int H, int d, const float *proj,
+                                int nbits, uint64_t *q_codes, uint64_t *k_codes, void *stream) {
+    sa::clear_error();
+    const long rows = (long)B * N * H;
+    // both tensors are checked before anything is launched for either
+    int rc = sa::check_binarize_pair(q, k, B, N, H, d, proj, nbits, q_codes, k_codes);
+    if (rc != SA_OK || rows == 0) return rc;
+    // one launch when the matrix-core kernel takes the shape; otherwise simply one call per tensor
+    if (sa::binarize_pair_one_launch(q, k, proj, q_codes, k_codes, rows, d, nbits))
+        return sa::launch_binarize_mfma(q, k, proj, q_codes, k_codes, rows, N, H, d, nbits, sa::as_stream(stream));
+    rc = sa_binarize_ex(q, B, N, H, d, proj, nbits, q_codes, SA_VARIANT_AUTO, stream);
+    if (rc != SA_OK) return rc;
+    return sa_binarize_ex(k, B, N, H, d, proj, nbits, k_codes, SA_VARIANT_AUTO, stream);
+}
+
+extern "C" int sa_binarize_ex(const float *x, int B, int N, int H, int d, const float *proj,
+                              int nbits, uint64_t *codes, int variant, void *stream) {
+    sa::clear_error();
+    const int bad = sa::check_binarize(x, B, N, H, d, proj, nbits, codes, variant);
+    const long rows = (long)B * N * H;
+    if (bad != SA_OK || rows == 0) return bad;
     hipStream_t st = sa::as_stream(stream);
     const int W = nbits / 64;
     if (proj == nullptr) {
         const long n_words = rows * W;
         const long blocks = (n_words + 3) / 4;
-        SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_binarize: too many rows");
         binarize_sign_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(x, codes, N, H, d, n_words);
         return sa::check_launch("sa_binarize(sign)");
     }
     if (variant != SA_VARIANT_VALU && sa::binarize_mfma_supported(d, nbits))
         return sa::launch_binarize_mfma(x, nullptr, proj, codes, nullptr, rows, N, H, d, nbits, st);
-    SA_REQUIRE(variant != SA_VARIANT_MFMA, SA_ERR_UNSUPPORTED,
-               "sa_binarize: the matrix-core variant needs d in {32, 64, 128} (got %d)", d);
     const int n_chunks = (N + 63) / 64;
     const long n_tasks = (long)B * H * n_chunks * W;
     const long blocks = (n_tasks + 3) / 4;
-    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_binarize: too many rows");
     const dim3 grid((unsigned)blocks), block(256);
     switch (d) {
         case 32:
@@ -137,11 +147,9 @@ extern "C" int sa_binarize_ex(const float *x, int B, int N, int H, int d, const 
         case 64:
             binarize_proj_kernel<64><<<grid, block, 0, st>>>(x, proj, codes, N, H, nbits, n_chunks, n_tasks);
             break;
-        case 128:
+        default:
             binarize_proj_kernel<128><<<grid, block, 0, st>>>(x, proj, codes, N, H, nbits, n_chunks, n_tasks);
             break;
-        default:
-            return sa::fail(SA_ERR_UNSUPPORTED, "sa_binarize: with proj, d must be 32, 64 or 128 (got %d)", d);
     }
     return sa::check_launch("sa_binarize(proj)");
 }

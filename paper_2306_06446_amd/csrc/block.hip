@@ -66,15 +66,16 @@ extern "C" size_t sa_block_workspace_bytes(const sa_block_desc *desc) {
 
 namespace {
 
-// What the matrix-core MLP asks of its operands; checked before anything is launched.
+// What the MLP asks of its operands.
 template <class Desc>
-int check_mlp(const Desc &d, int E) {
+int check_mlp(const Desc &d, int E, long T) {
     SA_REQUIRE(d.shift_variant >= 0 && d.shift_variant <= 3, SA_ERR_INVALID, "MLP: unknown shift variant %d", d.shift_variant);
     SA_REQUIRE(E % 64 == 0 && d.hid % 64 == 0, SA_ERR_SHAPE, "MLP: E (%d) and hid (%d) must be multiples of 64", E, d.hid);
     SA_REQUIRE(E <= 131072 && d.hid <= 131072, SA_ERR_SHAPE, "MLP: width too large");
     SA_REQUIRE(sa::aligned16(d.w1) && sa::aligned16(d.w2) && sa::aligned16(d.lut) && sa::aligned16(d.y) &&
                    (!d.moe || (sa::aligned16(d.mw1) && sa::aligned16(d.mw2))),
                SA_ERR_ALIGN, "MLP: pointers must be 16-byte aligned");
+    SA_REQUIRE(sa::shift_rows_fit(T, d.shift_variant), SA_ERR_SHAPE, "MLP: too many rows for the VALU variant in one call");
     return SA_OK;
 }
 
@@ -152,35 +153,43 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     int32_t *expert_of = reinterpret_cast<int32_t *>(ws + L.expert_of);
     int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
     float *gate = reinterpret_cast<float *>(ws + L.gate);
+    int8_t *xq = reinterpret_cast<int8_t *>(ws + L.xq);
+    void *xh = moe ? static_cast<void *>(ws + L.xh) : nullptr;
+    const bool mlp = d->hid > 0;
+    float *kv = reinterpret_cast<float *>(ws + L.kv);
+
+    // Every step's arguments are checked before the first launch.
+    rc = sa::check_binarize_pair(d->q, d->k, d->B, d->N, d->H, d->d, d->proj, d->nbits, qc, kc);
+    if (rc == SA_OK)
+        rc = d->attention == 0 ? sa::check_additive_attention(qc, kc, d->v, d->o, d->B, d->H, d->N, d->N, d->nbits, d->dv, kv, 3,
+                                                              ws + L.attn_ws, L.attn_ws_bytes)
+                               : sa::check_hamming_attention(qc, kc, d->v, d->o, d->B, d->H, d->N, d->N, d->nbits, d->dv, d->attn_scale,
+                                                             nullptr, mlp ? xq : nullptr, xh, SA_VARIANT_AUTO);
+    if (rc == SA_OK && mlp) rc = check_mlp(*d, E, T);
+    if (rc == SA_OK && moe)
+        rc = sa::check_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes);
+    if (rc != SA_OK) return rc;
+
     // Everything runs on the caller's stream, one kernel after the other.
     // The routing and the decode of packed Shift weights wait for nothing: they ride in the hash's launch.
-    if (d->hid > 0) rc = check_mlp(*d, E);
-    if (rc != SA_OK) return rc;
     sa::SideWork side;
-    if (moe) {
-        if (T <= sa::kSideRouteTokens) {
-            SA_REQUIRE(sa::aligned16(d->logits), SA_ERR_ALIGN, "block: logits must be 16-byte aligned");
-            side.route = {d->logits, T, 2, expert_of, gate, counts, perm};
-        } else {
-            rc = sa_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
-            if (rc != SA_OK) return rc;
-        }
+    if (moe && T <= sa::kSideRouteTokens) {
+        side.route = {d->logits, T, 2, expert_of, gate, counts, perm};
+    } else if (moe) {
+        rc = sa_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
+        if (rc != SA_OK) return rc;
     }
     sa::DecodeWork none;
-    const ShiftWeights weights(*d, E, T, ws + L.shift_ws, d->hid > 0 ? &side.decode : &none);
+    const ShiftWeights weights(*d, E, T, ws + L.shift_ws, mlp ? &side.decode : &none);
     rc = hash_and_side(d->q, d->k, d->B, d->N, d->H, d->d, d->proj, d->nbits, qc, kc, side, stream);
     if (rc != SA_OK) return rc;
     // The attention output leaves in three forms: fp32 (the block's output o), the int8 codes the
     // Shift layers read, and (with a Mult expert) the fp16 rounding its first layer reads.  The
     // kernel that computes it writes all three from its accumulators.
-    int8_t *xq = reinterpret_cast<int8_t *>(ws + L.xq);
-    void *xh = moe ? static_cast<void *>(ws + L.xh) : nullptr;
-    const bool mlp = d->hid > 0;
     if (d->attention == 0) {
-        rc = sa::additive_attention_fused(qc, kc, d->v, d->o, true, d->B, d->H, d->N, d->nbits, d->dv, d->attn_scale,
-                                          reinterpret_cast<float *>(ws + L.kv), mlp ? xq : nullptr,
-                                          static_cast<_Float16 *>(xh), d->act_inv_scale, ws + L.attn_ws, L.attn_ws_bytes,
-                                          stream);
+        rc = sa::additive_attention_fused(qc, kc, d->v, d->o, true, d->B, d->H, d->N, d->nbits, d->dv, d->attn_scale, kv,
+                                          mlp ? xq : nullptr, static_cast<_Float16 *>(xh), d->act_inv_scale, ws + L.attn_ws,
+                                          L.attn_ws_bytes, stream);
     } else {
         rc = sa_hamming_attention_fused(qc, kc, d->v, d->o, d->B, d->H, d->N, d->N, d->nbits, d->dv, d->attn_scale,
                                          nullptr, mlp ? xq : nullptr, xh, d->act_inv_scale, SA_VARIANT_AUTO, stream);
@@ -287,17 +296,47 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     float *v = reinterpret_cast<float *>(ws + L.v);
     float *o = q;                                 // Q is dead once it is hashed
     uint64_t *qc = reinterpret_cast<uint64_t *>(ws + L.qc), *kc = reinterpret_cast<uint64_t *>(ws + L.kc);
-
-    // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y
-    rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
-                            nullptr, 0, nullptr, stream);
-    if (rc != SA_OK) return rc;
+    float *kv = reinterpret_cast<float *>(ws + L.kv);
+    const bool moe = d->moe != 0;
+    void *xh = moe ? static_cast<void *>(ws + L.xh) : nullptr;
+    float *logits = moe ? reinterpret_cast<float *>(ws + L.logits) : nullptr;
+    int32_t *perm = reinterpret_cast<int32_t *>(ws + L.perm);
+    int32_t *expert_of = reinterpret_cast<int32_t *>(ws + L.expert_of);
+    int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
+    float *gate = reinterpret_cast<float *>(ws + L.gate);
     // Sign hash (no projection): the code bits are the signs of the Q and K accumulators, taken in the epilogue of
     // the projection, so Q and K never exist as floats.  Otherwise Q, K, V leave as fp32 and Q, K are hashed.
     const bool fused_hash = d->proj == nullptr && d->nbits == dv && (dv == 64 || dv == 128) && E % 128 == 0 &&
                             d->shift_variant != SA_VARIANT_VALU && d->qkv_scale > 0.0f &&
                             d->qkv_scale - d->qkv_scale == 0.0f;
-    rc = check_mlp(*d, E);
+
+    // Every step's arguments are checked before the first launch.
+    rc = sa::check_layernorm(d->x, T, E, d->gamma1, d->beta1, nullptr, codes8, nullptr, nullptr, nullptr, 0, nullptr);
+    if (rc == SA_OK)
+        rc = fused_hash ? sa::check_shift_linear_qkv_codes(codes8, d->wqkv, d->B, d->N, d->H, E, d->shift_variant, d->qkv_scale, qc, kc, v,
+                                                           ws + L.lin_ws, L.lin_ws_bytes)
+                        : sa::check_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, nullptr, 3, q, k, v, ws + L.lin_ws,
+                                                     L.lin_ws_bytes);
+    if (rc == SA_OK && !fused_hash) rc = sa::check_binarize_pair(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc);
+    if (rc == SA_OK)
+        rc = d->attention == 0 ? sa::check_additive_attention(qc, kc, v, o, d->B, d->H, d->N, d->N, d->nbits, dv, kv, 3, ws + L.attn_ws,
+                                                              L.attn_ws_bytes)
+                               : sa::check_hamming_attention(qc, kc, v, nullptr, d->B, d->H, d->N, d->N, d->nbits, dv, d->attn_scale,
+                                                             nullptr, codes8, nullptr, SA_VARIANT_AUTO);
+    if (rc == SA_OK)
+        rc = sa::check_shift_linear_f32(codes8, d->wo, T, E, E, d->shift_variant, d->x, 1, d->y, nullptr, nullptr, ws + L.lin_ws,
+                                        L.lin_ws_bytes);
+    if (rc == SA_OK)
+        rc = sa::check_layernorm(d->y, T, E, d->gamma2, d->beta2, nullptr, codes8, xh, moe ? d->wg : nullptr, moe ? d->bg : nullptr,
+                                 moe ? 2 : 0, logits);
+    if (rc == SA_OK) rc = check_mlp(*d, E, T);
+    if (rc == SA_OK && moe)
+        rc = sa::check_moe_dispatch(logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes);
+    if (rc != SA_OK) return rc;
+
+    // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y
+    rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
+                            nullptr, 0, nullptr, stream);
     if (rc != SA_OK) return rc;
     sa::SideWork side;
     const ShiftWeights weights(*d, E, T, ws + L.shift_ws, &side.decode);
@@ -316,9 +355,8 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     }
     if (d->attention == 0) {
         // only the int8 form of the attention output is read (by the output projection): no fp32 write
-        rc = sa::additive_attention_fused(qc, kc, v, o, false, d->B, d->H, d->N, d->nbits, dv, d->attn_scale,
-                                          reinterpret_cast<float *>(ws + L.kv), codes8, nullptr, d->act_inv_scale,
-                                          ws + L.attn_ws, L.attn_ws_bytes, stream);
+        rc = sa::additive_attention_fused(qc, kc, v, o, false, d->B, d->H, d->N, d->nbits, dv, d->attn_scale, kv, codes8, nullptr,
+                                          d->act_inv_scale, ws + L.attn_ws, L.attn_ws_bytes, stream);
     } else {
         rc = sa_hamming_attention_fused(qc, kc, v, nullptr, d->B, d->H, d->N, d->N, d->nbits, dv, d->attn_scale, nullptr,
                                          codes8, nullptr, d->act_inv_scale, SA_VARIANT_AUTO, stream);
@@ -329,9 +367,6 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     if (rc != SA_OK) return rc;
 
     // MLP half: y += MLP(LayerNorm(y)); every row is read by the LayerNorm before an expert adds to it
-    const bool moe = d->moe != 0;
-    void *xh = moe ? static_cast<void *>(ws + L.xh) : nullptr;
-    float *logits = moe ? reinterpret_cast<float *>(ws + L.logits) : nullptr;
     rc = sa_layernorm_quant(d->y, T, E, d->gamma2, d->beta2, d->eps, d->ln_inv_scale, nullptr, codes8, xh,
                             moe ? d->wg : nullptr, moe ? d->bg : nullptr, moe ? 2 : 0, logits, stream);
     if (rc != SA_OK) return rc;
@@ -341,10 +376,6 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                             d->out_scale, weights.variant, 3 | SA_MLP_ACCUMULATE, ws + L.shift_ws, L.shift_ws_bytes,
                             stream);
     }
-    int32_t *perm = reinterpret_cast<int32_t *>(ws + L.perm);
-    int32_t *expert_of = reinterpret_cast<int32_t *>(ws + L.expert_of);
-    int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
-    float *gate = reinterpret_cast<float *>(ws + L.gate);
     rc = sa_moe_dispatch(logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
     if (rc != SA_OK) return rc;
     // the experts add to disjoint rows of y

@@ -48,6 +48,32 @@ __device__ inline void resolve_rows(const RowSel &sel, const int32_t *&rows, lon
 
 int validate_rows(const sa_rows *rows, RowSel *out);
 
+// The argument checks of the entry points that sa_block_forward and sa_layer_forward are made of, apart from their launches:
+// both call all of them first, so that a call that is refused has launched nothing.  Each is that entry point's whole validation;
+// sizes of zero pass.
+int check_binarize(const float *x, int B, int N, int H, int d, const float *proj, int nbits, const uint64_t *codes, int variant);
+int check_binarize_pair(const float *q, const float *k, int B, int N, int H, int d, const float *proj, int nbits,
+                        const uint64_t *q_codes, const uint64_t *k_codes);
+int check_additive_attention(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, const float *out, int B, int H, int Nq,
+                             int Nk, int nbits, int dv, const float *kv, int phases, const void *workspace, size_t workspace_bytes);
+int check_hamming_attention(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, const float *out, int B, int H, int Nq,
+                            int Nk, int nbits, int dv, float scale, const int16_t *scores_or_null, const int8_t *xq_or_null,
+                            const void *xh_or_null, int variant);
+int check_layernorm(const float *x, long T, int E, const float *gamma, const float *beta, const float *ln_or_null,
+                    const int8_t *q_or_null, const void *xh_or_null, const float *wg_or_null, const float *bg_or_null, int n_experts,
+                    const float *logits_or_null);
+int check_shift_linear_f32(const int8_t *x, const uint8_t *w4, long M, int K, int N, int variant, const float *residual_or_null,
+                           int parts, const float *y0, const float *y1, const float *y2, const void *workspace, size_t workspace_bytes);
+int check_shift_linear_qkv_codes(const int8_t *x, const uint8_t *wqkv, int B, int N, int H, int E, int variant, float scale,
+                                 const uint64_t *q_codes, const uint64_t *k_codes, const float *v, const void *workspace,
+                                 size_t workspace_bytes);
+int check_moe_dispatch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,
+                       const void *workspace, size_t workspace_bytes);
+int check_shift_mlp(const int8_t *xq, const sa_rows *rows, RowSel *sel, int E, int hid, const uint8_t *w1, const uint8_t *w2,
+                    const int8_t *lut, const int32_t *y2_or_null, const float *y_or_null, const float *gate_or_null, int variant,
+                    int stages, const void *workspace, size_t workspace_bytes);
+bool shift_rows_fit(long rows, int variant);         // rows of one launch of a Shift layer
+
 // 16 bytes to memory past the caches' reuse order: for 32-bit outputs, which are large, written once and not read again
 // soon, and otherwise push out what is.  12608 x 1536 <- 384 and back, int32: 72 -> 60 us; the layers with fp32 outputs of
 // 12608 x 768 tokens 0 to 4 us each; Q(K^T V) at 8 x 4 x 16384 x 256 bits x 64 70 -> 64 us.  For the narrow outputs that

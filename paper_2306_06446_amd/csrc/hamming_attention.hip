@@ -793,16 +793,13 @@ void launch_hamming(const Launch &L) {
 }
 
 template <int DV>
-int dispatch_w(int W, const Launch &L) {
+void dispatch_w(int W, const Launch &L) {
     switch (W) {
         case 1: launch_hamming<DV, 1>(L); break;
         case 2: launch_hamming<DV, 2>(L); break;
         case 4: launch_hamming<DV, 4>(L); break;
-        case 8: launch_hamming<DV, 8>(L); break;
-        default:
-            return sa::fail(SA_ERR_UNSUPPORTED, "sa_hamming_attention: nbits must be 64, 128, 256 or 512");
+        default: launch_hamming<DV, 8>(L); break;
     }
-    return SA_OK;
 }
 
 }  // namespace
@@ -815,11 +812,10 @@ extern "C" int sa_hamming_attention(const uint64_t *q_codes, const uint64_t *k_c
                                       nullptr, nullptr, 0.0f, SA_VARIANT_AUTO, stream);
 }
 
-extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_t *k_codes, const float *v,
-                                          float *out, int B, int H, int Nq, int Nk, int nbits, int dv, float scale,
-                                          int16_t *scores_or_null, int8_t *xq_or_null, void *xh_or_null,
-                                          float act_inv_scale, int variant, void *stream) {
-    sa::clear_error();
+// Everything sa_hamming_attention_fused asks of its arguments.
+int sa::check_hamming_attention(const uint64_t *q_codes, const uint64_t *k_codes, const float *v, const float *out, int B, int H, int Nq,
+                                int Nk, int nbits, int dv, float scale, const int16_t *scores_or_null, const int8_t *xq_or_null,
+                                const void *xh_or_null, int variant) {
     SA_REQUIRE(variant >= 0 && variant <= 2, SA_ERR_INVALID, "sa_hamming_attention: unknown variant %d", variant);
     SA_REQUIRE(B >= 0 && H >= 0 && Nq >= 0 && Nk >= 0 && nbits > 0 && dv > 0, SA_ERR_INVALID,
                "sa_hamming_attention: negative size");
@@ -836,6 +832,24 @@ extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_
     SA_REQUIRE(sa::aligned16(q_codes) && sa::aligned16(k_codes) && sa::aligned16(v) && sa::aligned16(out) &&
                    sa::aligned16(scores_or_null) && sa::aligned16(xq_or_null) && sa::aligned16(xh_or_null),
                SA_ERR_ALIGN, "sa_hamming_attention: pointers must be 16-byte aligned");
+    const int W = nbits / 64;
+    SA_REQUIRE(W == 1 || W == 2 || W == 4 || W == 8, SA_ERR_UNSUPPORTED, "sa_hamming_attention: nbits must be 64, 128, 256 or 512");
+    SA_REQUIRE(variant != SA_VARIANT_MFMA || W <= 4, SA_ERR_UNSUPPORTED,
+               "sa_hamming_attention: scores on the matrix cores need nbits <= 256 (got %d)", nbits);
+    const long BH = (long)B * H;
+    SA_REQUIRE(BH * (((long)Nq + kMaxWaves * 32 - 1) / (kMaxWaves * 32)) < (1L << 31), SA_ERR_SHAPE, "sa_hamming_attention: grid too large");
+    SA_REQUIRE(!scores_or_null || (double)BH * Nq * Nk <= 256.0 * 2147483647.0, SA_ERR_SHAPE, "sa_hamming_attention: score dump too large");
+    return SA_OK;
+}
+
+extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_t *k_codes, const float *v,
+                                          float *out, int B, int H, int Nq, int Nk, int nbits, int dv, float scale,
+                                          int16_t *scores_or_null, int8_t *xq_or_null, void *xh_or_null,
+                                          float act_inv_scale, int variant, void *stream) {
+    sa::clear_error();
+    int rc = sa::check_hamming_attention(q_codes, k_codes, v, out, B, H, Nq, Nk, nbits, dv, scale, scores_or_null, xq_or_null, xh_or_null,
+                                         variant);
+    if (rc != SA_OK || (long)B * H == 0 || Nq == 0) return rc;
     hipStream_t st = sa::as_stream(stream);
     const int W = nbits / 64;
     const long BH = (long)B * H;
@@ -843,7 +857,6 @@ extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_
     const int q_chunks = (Nq + q_per_block - 1) / q_per_block;
     const int waves = Nq >= q_per_block ? kMaxWaves : (Nq + 31) / 32;   // uniform per launch
     const long blocks = BH * q_chunks;
-    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_hamming_attention: grid too large");
     Launch L;
     L.grid = dim3((unsigned)blocks);
     L.block = dim3(q_chunks > 1 ? kMaxWaves * kWave : waves * kWave);
@@ -862,21 +875,16 @@ extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_
     // AUTO: the pipelined popcount kernel where it is built (dv <= 64, nbits <= 256, no row reference)
     L.pipeline = variant == SA_VARIANT_AUTO && !L.rowref && dv <= 64 && W <= 4;
     L.n_units = blocks;
-    SA_REQUIRE(variant != SA_VARIANT_MFMA || W <= 4, SA_ERR_UNSUPPORTED,
-               "sa_hamming_attention: scores on the matrix cores need nbits <= 256 (got %d)", nbits);
-    int rc;
     switch (dv) {
-        case 32: rc = dispatch_w<32>(W, L); break;
-        case 64: rc = dispatch_w<64>(W, L); break;
-        default: rc = dispatch_w<128>(W, L); break;
+        case 32: dispatch_w<32>(W, L); break;
+        case 64: dispatch_w<64>(W, L); break;
+        default: dispatch_w<128>(W, L); break;
     }
-    if (rc != SA_OK) return rc;
     rc = sa::check_launch("sa_hamming_attention");
     if (rc != SA_OK) return rc;
     if (scores_or_null != nullptr) {
         const long total = BH * Nq * Nk;
         const long sb = (total + 255) / 256;
-        SA_REQUIRE(sb < (1L << 31), SA_ERR_SHAPE, "sa_hamming_attention: score dump too large");
         hamming_scores_kernel<<<dim3((unsigned)sb), dim3(256), 0, st>>>(q_codes, k_codes, scores_or_null,
                                                                          Nq, Nk, W, total);
         return sa::check_launch("sa_hamming_attention(scores)");

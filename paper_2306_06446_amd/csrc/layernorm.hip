@@ -206,11 +206,10 @@ int launch(const LnArgs &a, hipStream_t st) {
 
 }  // namespace
 
-extern "C" int sa_layernorm_quant(const float *x, long T, int E, const float *gamma, const float *beta, float eps,
-                                  float inv_scale, float *ln_or_null, int8_t *q_or_null, void *xh_or_null,
-                                  const float *wg_or_null, const float *bg_or_null, int n_experts,
-                                  float *logits_or_null, void *stream) {
-    sa::clear_error();
+// Everything sa_layernorm_quant asks of its arguments.
+int sa::check_layernorm(const float *x, long T, int E, const float *gamma, const float *beta, const float *ln_or_null,
+                        const int8_t *q_or_null, const void *xh_or_null, const float *wg_or_null, const float *bg_or_null, int n_experts,
+                        const float *logits_or_null) {
     SA_REQUIRE(T >= 0 && E > 0, SA_ERR_INVALID, "sa_layernorm_quant: T < 0 or E <= 0");
     SA_REQUIRE(E % 4 == 0, SA_ERR_SHAPE, "sa_layernorm_quant: E (%d) must be a multiple of 4", E);
     SA_REQUIRE(E <= 8192, SA_ERR_UNSUPPORTED, "sa_layernorm_quant: rows of more than 8192 elements are not built");
@@ -227,6 +226,18 @@ extern "C" int sa_layernorm_quant(const float *x, long T, int E, const float *ga
                    sa::aligned16(q_or_null) && sa::aligned16(xh_or_null) && sa::aligned16(wg_or_null) &&
                    sa::aligned16(bg_or_null) && sa::aligned16(logits_or_null),
                SA_ERR_ALIGN, "sa_layernorm_quant: pointers must be 16-byte aligned");
+    return SA_OK;
+}
+
+extern "C" int sa_layernorm_quant(const float *x, long T, int E, const float *gamma, const float *beta, float eps,
+                                  float inv_scale, float *ln_or_null, int8_t *q_or_null, void *xh_or_null,
+                                  const float *wg_or_null, const float *bg_or_null, int n_experts,
+                                  float *logits_or_null, void *stream) {
+    sa::clear_error();
+    const int bad = sa::check_layernorm(x, T, E, gamma, beta, ln_or_null, q_or_null, xh_or_null, wg_or_null, bg_or_null, n_experts,
+                                        logits_or_null);
+    if (bad != SA_OK || T == 0) return bad;
+    const bool route = logits_or_null != nullptr;
     LnArgs a{x, T, E, gamma, beta, eps, inv_scale, ln_or_null, q_or_null, static_cast<_Float16 *>(xh_or_null),
              route ? wg_or_null : nullptr, route ? bg_or_null : nullptr, route ? n_experts : 0, logits_or_null};
     hipStream_t st = sa::as_stream(stream);

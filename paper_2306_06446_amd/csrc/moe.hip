@@ -330,18 +330,26 @@ int sa::moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, i
     return dispatch_launch(logits, T, E, perm, expert_of, counts, gate, scratch, st);
 }
 
+// Everything sa_moe_dispatch asks of its arguments.
+int sa::check_moe_dispatch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,
+                           const void *workspace, size_t workspace_bytes) {
+    int rc = dispatch_check("sa_moe_dispatch", logits, T, E, perm, expert_of, counts, gate);
+    if (rc != SA_OK) return rc;
+    SA_REQUIRE(sa::aligned16(workspace), SA_ERR_ALIGN, "sa_moe_dispatch: the workspace must be 16-byte aligned");
+    const size_t need = dispatch_scratch_bytes(T, E);
+    SA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SA_ERR_WORKSPACE,
+               "sa_moe_dispatch: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    return SA_OK;
+}
+
 extern "C" int sa_moe_dispatch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of,
                                int32_t *counts, float *gate, void *workspace, size_t workspace_bytes,
                                void *stream) {
     sa::clear_error();
-    int rc = dispatch_check("sa_moe_dispatch", logits, T, E, perm, expert_of, counts, gate);
+    int rc = sa::check_moe_dispatch(logits, T, E, perm, expert_of, counts, gate, workspace, workspace_bytes);
     if (rc != SA_OK) return rc;
-    SA_REQUIRE(sa::aligned16(workspace), SA_ERR_ALIGN, "sa_moe_dispatch: the workspace must be 16-byte aligned");
     hipStream_t st = sa::as_stream(stream);
     if (T == 0) return sa::launch_zero(counts, ((size_t)E * 4 + 3) / 4 * 4, st);
-    const size_t need = dispatch_scratch_bytes(T, E);
-    SA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SA_ERR_WORKSPACE,
-               "sa_moe_dispatch: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
     return dispatch_launch(logits, T, E, perm, expert_of, counts, gate, workspace, st);
 }
 
@@ -520,6 +528,7 @@ extern "C" int sa_moe_linear(const int8_t *xq, const void *xh, const float *logi
     const MoeLinearLayout L = moe_linear_layout(T, K, N, variant);
     SA_REQUIRE(workspace != nullptr && workspace_bytes >= L.total, SA_ERR_WORKSPACE,
                "sa_moe_linear: workspace of %zu bytes needed, %zu given", L.total, workspace_bytes);
+    SA_REQUIRE(sa::shift_rows_fit(T, variant), SA_ERR_SHAPE, "sa_moe_linear: too many rows for the VALU variant in one call");
     hipStream_t st = sa::as_stream(stream);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + L.perm);

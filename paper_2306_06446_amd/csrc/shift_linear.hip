@@ -351,10 +351,9 @@ extern "C" int sa_shift_linear(const int8_t *x, const uint8_t *w4, const int32_t
     return SA_OK;
 }
 
-extern "C" int sa_shift_linear_f32(const int8_t *x, const uint8_t *w4, long M, int K, int N, int variant,
-                                   float scale, const float *residual_or_null, int parts, float *y0, float *y1,
-                                   float *y2, void *workspace, size_t workspace_bytes, void *stream) {
-    sa::clear_error();
+// Everything sa_shift_linear_f32 asks of its arguments.
+int sa::check_shift_linear_f32(const int8_t *x, const uint8_t *w4, long M, int K, int N, int variant, const float *residual_or_null,
+                               int parts, const float *y0, const float *y1, const float *y2, const void *workspace, size_t workspace_bytes) {
     SA_REQUIRE(M >= 0 && K >= 0 && N >= 0, SA_ERR_INVALID, "sa_shift_linear_f32: negative size");
     SA_REQUIRE(variant >= 0 && variant <= 3, SA_ERR_INVALID, "sa_shift_linear_f32: unknown variant %d", variant);
     SA_REQUIRE(parts >= 1 && parts <= 3, SA_ERR_INVALID, "sa_shift_linear_f32: parts must be 1, 2 or 3");
@@ -376,6 +375,15 @@ extern "C" int sa_shift_linear_f32(const int8_t *x, const uint8_t *w4, long M, i
     const size_t need = sa_shift_linear_workspace_bytes(M, K, N, variant);
     SA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SA_ERR_WORKSPACE,
                "sa_shift_linear_f32: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    return SA_OK;
+}
+
+extern "C" int sa_shift_linear_f32(const int8_t *x, const uint8_t *w4, long M, int K, int N, int variant,
+                                   float scale, const float *residual_or_null, int parts, float *y0, float *y1,
+                                   float *y2, void *workspace, size_t workspace_bytes, void *stream) {
+    sa::clear_error();
+    const int bad = sa::check_shift_linear_f32(x, w4, M, K, N, variant, residual_or_null, parts, y0, y1, y2, workspace, workspace_bytes);
+    if (bad != SA_OK || M == 0 || N == 0) return bad;
     sa::Epilogue epi;
     epi.parts[0] = y0;
     epi.parts[1] = parts > 1 ? y1 : y0;
@@ -387,10 +395,10 @@ extern "C" int sa_shift_linear_f32(const int8_t *x, const uint8_t *w4, long M, i
     return launch_shift<sa::kEpiLinearF32>(variant, x, w4, sel, false, K, N, epi, workspace, sa::as_stream(stream));
 }
 
-extern "C" int sa_shift_linear_qkv_codes(const int8_t *x, const uint8_t *wqkv, int B, int N, int H, int E, int variant,
-                                         float scale, uint64_t *q_codes, uint64_t *k_codes, float *v, void *workspace,
-                                         size_t workspace_bytes, void *stream) {
-    sa::clear_error();
+// Everything sa_shift_linear_qkv_codes asks of its arguments.
+int sa::check_shift_linear_qkv_codes(const int8_t *x, const uint8_t *wqkv, int B, int N, int H, int E, int variant, float scale,
+                                     const uint64_t *q_codes, const uint64_t *k_codes, const float *v, const void *workspace,
+                                     size_t workspace_bytes) {
     SA_REQUIRE(B >= 0 && N >= 0 && H > 0 && E > 0, SA_ERR_INVALID, "sa_shift_linear_qkv_codes: bad size");
     SA_REQUIRE(variant >= 1 && variant <= 3, SA_ERR_UNSUPPORTED,
                "sa_shift_linear_qkv_codes: matrix-core variants only (1, 2 or 3; got %d)", variant);
@@ -406,10 +414,19 @@ extern "C" int sa_shift_linear_qkv_codes(const int8_t *x, const uint8_t *wqkv, i
     SA_REQUIRE(sa::aligned16(x) && sa::aligned16(wqkv) && sa::aligned16(q_codes) && sa::aligned16(k_codes) &&
                    sa::aligned16(v) && sa::aligned16(workspace),
                SA_ERR_ALIGN, "sa_shift_linear_qkv_codes: pointers must be 16-byte aligned");
-    if (variant == SA_VARIANT_AUTO) variant = SA_VARIANT_MFMA;
     const size_t need = sa_shift_linear_workspace_bytes(M, E, 3 * E, variant);
     SA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SA_ERR_WORKSPACE,
                "sa_shift_linear_qkv_codes: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    return SA_OK;
+}
+
+extern "C" int sa_shift_linear_qkv_codes(const int8_t *x, const uint8_t *wqkv, int B, int N, int H, int E, int variant,
+                                         float scale, uint64_t *q_codes, uint64_t *k_codes, float *v, void *workspace,
+                                         size_t workspace_bytes, void *stream) {
+    sa::clear_error();
+    const int bad = sa::check_shift_linear_qkv_codes(x, wqkv, B, N, H, E, variant, scale, q_codes, k_codes, v, workspace, workspace_bytes);
+    const long M = (long)B * N;
+    if (bad != SA_OK || M == 0) return bad;
     sa::Epilogue epi;
     epi.parts[0] = epi.parts[1] = epi.parts[2] = v;      // only column block 2 is written as fp32
     epi.part_width = E;
@@ -485,10 +502,10 @@ size_t sa::shift_linear_rows_workspace_bytes(int K, int N, int variant) {
     return (variant == SA_VARIANT_VALU || variant == SA_VARIANT_MFMA_PREPARED) ? 0 : planes_bytes(K, N);
 }
 
+bool sa::shift_rows_fit(long rows, int variant) { return variant != SA_VARIANT_VALU || (rows + kValuRows - 1) / kValuRows < 65536; }
+
 int sa::shift_linear_rows(const int8_t *xq_all, const RowSel &sel, int K, int N, const uint8_t *w4, float out_scale, float *y,
                           const float *gate, int variant, void *planes, hipStream_t st) {
-    SA_REQUIRE((sel.max_rows + kValuRows - 1) / kValuRows < 65536 || variant != SA_VARIANT_VALU, SA_ERR_SHAPE,
-               "sa_moe_linear: too many rows for the VALU variant in one call");
     sa::Epilogue e;
     e.yf = y;
     e.gate = gate;
@@ -502,6 +519,33 @@ extern "C" size_t sa_shift_mlp_workspace_bytes(long max_rows, int E, int hid) {
     return hidden + 2 * planes_bytes(E, hid);
 }
 
+// Everything sa_shift_mlp asks of its arguments.
+int sa::check_shift_mlp(const int8_t *xq, const sa_rows *rows, RowSel *sel, int E, int hid, const uint8_t *w1, const uint8_t *w2,
+                        const int8_t *lut, const int32_t *y2_or_null, const float *y_or_null, const float *gate_or_null, int variant,
+                        int stages, const void *workspace, size_t workspace_bytes) {
+    int rc = sa::validate_rows(rows, sel);
+    if (rc != SA_OK) return rc;
+    SA_REQUIRE(E > 0 && hid > 0, SA_ERR_INVALID, "sa_shift_mlp: E and hid must be positive");
+    SA_REQUIRE(variant >= 0 && variant <= 3, SA_ERR_INVALID, "sa_shift_mlp: unknown variant %d", variant);
+    SA_REQUIRE(E % 64 == 0 && hid % 64 == 0, SA_ERR_SHAPE,
+               "sa_shift_mlp: E (%d) and hid (%d) must be multiples of 64", E, hid);
+    SA_REQUIRE(E <= 131072 && hid <= 131072, SA_ERR_SHAPE, "sa_shift_mlp: width too large");
+    if (sel->max_rows == 0) return SA_OK;
+    SA_REQUIRE(xq && w1 && w2 && lut, SA_ERR_INVALID, "sa_shift_mlp: NULL buffer");
+    SA_REQUIRE((stages & 3) != 0 && (stages & ~(3 | SA_MLP_ACCUMULATE)) == 0, SA_ERR_INVALID,
+               "sa_shift_mlp: stages must be 1, 2 or 3, optionally | SA_MLP_ACCUMULATE");
+    SA_REQUIRE(!(stages & 2) || y2_or_null || y_or_null, SA_ERR_INVALID, "sa_shift_mlp: no output requested");
+    SA_REQUIRE(sa::aligned16(xq) && sa::aligned16(w1) && sa::aligned16(w2) && sa::aligned16(lut) &&
+                   sa::aligned16(y2_or_null) && sa::aligned16(y_or_null) && sa::aligned16(gate_or_null) &&
+                   sa::aligned16(workspace) && sa::aligned4(sel->rows),
+               SA_ERR_ALIGN, "sa_shift_mlp: pointers must be 16-byte aligned");
+    const size_t need = sa_shift_mlp_workspace_bytes(sel->max_rows, E, hid);
+    SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
+               "sa_shift_mlp: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    SA_REQUIRE(shift_rows_fit(sel->max_rows, variant), SA_ERR_SHAPE, "sa_shift_mlp: too many rows for the VALU variant in one call");
+    return SA_OK;
+}
+
 extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hid, const uint8_t *w1,
                             const uint8_t *w2, float requant_scale, const int8_t *lut,
                             int32_t *y2_or_null, float *y_or_null, const float *gate_or_null,
@@ -509,27 +553,9 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
                             size_t workspace_bytes, void *stream) {
     sa::clear_error();
     sa::RowSel sel;
-    int rc = sa::validate_rows(rows, &sel);
-    if (rc != SA_OK) return rc;
-    SA_REQUIRE(E > 0 && hid > 0, SA_ERR_INVALID, "sa_shift_mlp: E and hid must be positive");
-    SA_REQUIRE(variant >= 0 && variant <= 3, SA_ERR_INVALID, "sa_shift_mlp: unknown variant %d", variant);
-    SA_REQUIRE(E % 64 == 0 && hid % 64 == 0, SA_ERR_SHAPE,
-               "sa_shift_mlp: E (%d) and hid (%d) must be multiples of 64", E, hid);
-    SA_REQUIRE(E <= 131072 && hid <= 131072, SA_ERR_SHAPE, "sa_shift_mlp: width too large");
-    if (sel.max_rows == 0) return SA_OK;
-    SA_REQUIRE(xq && w1 && w2 && lut, SA_ERR_INVALID, "sa_shift_mlp: NULL buffer");
-    SA_REQUIRE((stages & 3) != 0 && (stages & ~(3 | SA_MLP_ACCUMULATE)) == 0, SA_ERR_INVALID,
-               "sa_shift_mlp: stages must be 1, 2 or 3, optionally | SA_MLP_ACCUMULATE");
-    SA_REQUIRE(!(stages & 2) || y2_or_null || y_or_null, SA_ERR_INVALID, "sa_shift_mlp: no output requested");
-    SA_REQUIRE(sa::aligned16(xq) && sa::aligned16(w1) && sa::aligned16(w2) && sa::aligned16(lut) &&
-                   sa::aligned16(y2_or_null) && sa::aligned16(y_or_null) && sa::aligned16(gate_or_null) &&
-                   sa::aligned16(workspace) && sa::aligned4(sel.rows),
-               SA_ERR_ALIGN, "sa_shift_mlp: pointers must be 16-byte aligned");
-    const size_t need = sa_shift_mlp_workspace_bytes(sel.max_rows, E, hid);
-    SA_REQUIRE(workspace != nullptr && workspace_bytes >= need, SA_ERR_WORKSPACE,
-               "sa_shift_mlp: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
-    SA_REQUIRE((sel.max_rows + kValuRows - 1) / kValuRows < 65536 || variant != SA_VARIANT_VALU, SA_ERR_SHAPE,
-               "sa_shift_mlp: too many rows for the VALU variant in one call");
+    int rc = sa::check_shift_mlp(xq, rows, &sel, E, hid, w1, w2, lut, y2_or_null, y_or_null, gate_or_null, variant, stages, workspace,
+                                 workspace_bytes);
+    if (rc != SA_OK || sel.max_rows == 0) return rc;
     hipStream_t st = sa::as_stream(stream);
     int8_t *hbuf = static_cast<int8_t *>(workspace);
     uint8_t *planes1 = static_cast<uint8_t *>(workspace) + (((size_t)sel.max_rows * hid) + 255) / 256 * 256;
