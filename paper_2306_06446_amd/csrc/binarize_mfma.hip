@@ -17,12 +17,15 @@
 // fragments and as fp32 columns for step 3; the rows of the next tile are in flight while a tile is multiplied.
 //
 // What bounds it: at 256 bits the products and the vector work in their shadow (16 funnel shifts and 8 three-way minima
-// per 16 bits, 7 operations to split two elements); at 128 bits and fewer the rows of Q and K, with 5.6 us before the
-// first product (3.5 of them the launch; 1.6 when the hash matrix has arrived) and 1 us of re-runs at the end.  More
-// wavefronts or rows in flight gave nothing there.  The kernel before split into bf16 terms, tested against 2^-13 |x|
-// (four times the re-runs, each with 64 uncoalesced loads of its hash column) and spread and merged the bits of a row
-// between two lanes.  Q and K, before -> now: 8 x 16384 x 4 heads x 64 -> 256 bits 143 -> 116 us, 1 x 16384 x 4 the
-// same 24.3 -> 22.8, 64 x 197 x 12 x 64 -> 128 bits 28.7 -> 28.3.
+// per 16 bits, 7 operations to split two elements); at 128 bits and fewer the rows of Q and K, with about 4.5 us before the
+// first product (3.5 of them the launch, 1 until the hash matrix has arrived) and 1 us of re-runs at the end.  More
+// wavefronts or rows in flight gave nothing there.  The fragments are made from the registers the hash matrix is loaded
+// into: through LDS, with two more barriers and two passes over its fp32 form, a launch took 0.8 us longer at d = 64 and up
+// to 3.7 at d = 128.  Q and K, before -> now (before: bf16 terms, a margin of 2^-13 |x| and so four times the re-runs):
+//    8 x 16384 x 4 heads x 64 -> 256 bits  141 -> 111 us      1 x 16384 x 4 x 64 -> 256  24.0 -> 20.6
+//   64 x 197 x 12 x 64 -> 128              27.0 -> 25.4       8 x 1000 x 3 x 128 -> 128  15.3 -> 15.0
+//    8 x 1000 x 3 x 128 -> 64              11.6 -> 11.5       1 x 197 x 3 x 64 -> 64      5.9 ->  5.8
+//   32 x 3136 x 1 x 32 -> 64               10.9 -> 11.0
 #include "common.h"
 #include "hash_margin.h"
 #include "side_work.h"
@@ -116,7 +119,10 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
     constexpr int BYTES = C / 32;                 // code bytes of a lane: columns (C / 4) g .. of its row
     __shared__ __attribute__((aligned(16))) uint4 frag_s[T * S * 2 * 64];       // [tile][step][upper, lower][lane]
     __shared__ __attribute__((aligned(16))) float r_s[D * C];
-    constexpr int TPC = THREADS / C;              // threads that share a column's norm
+    // hash matrix: a task is eight k of one column, four tasks per 32 k; a thread's tasks are of one column
+    constexpr int TPC = THREADS / C < 4 * S ? THREADS / C : 4 * S;         // threads that share a column
+    constexpr int TASKS = 4 * S / TPC;
+    static_assert(THREADS % C == 0 && TASKS * TPC == 4 * S, "the threads of a column share its tasks evenly");
     __shared__ float n2_s[TPC][C];
     __shared__ uint64_t list_s[kWaves][kListCap];
     __shared__ int cnt_s[kWaves];
@@ -146,47 +152,62 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
     };
     const uint32_t tile_step = hash_blocks * kWaves;
     uint32_t tile = blockIdx.x * kWaves + wave;
-    if (tile < n_total) load_tile(tile);
 
-    // ---- hash matrix: fp32 columns, their norms, then the fragments of the normalised columns
-    for (int i = tid; i < D * C / 4; i += THREADS) {
-        const int k = i / (C / 4), c4 = i % (C / 4);
-        reinterpret_cast<float4 *>(r_s)[i] = *reinterpret_cast<const float4 *>(proj + (size_t)k * nbits + c_first + 4 * c4);
-    }
-    __syncthreads();
+    // ---- hash matrix: fp32 columns to LDS for step 3, their norms, then the fragments of the normalised columns, from the
+    //      registers the columns came in.  Asked for before the first rows, which then need not have arrived.
     {
-        float n2 = 0.0f;                                           // this thread's share of the norm of column tid % C
-        const int c = tid % C, k0 = tid / C * (D / TPC);
-#pragma unroll 8
-        for (int k = k0; k < k0 + D / TPC; ++k) n2 = __builtin_fmaf(r_s[k * C + c], r_s[k * C + c], n2);
-        n2_s[tid / C][c] = n2;
-    }
-    __syncthreads();
-    for (int i = tid; i < C * S * 4; i += THREADS) {               // task: eight k of one column
-        const int c = i % C, s = i / C % S, kq = i / (C * S);
+        const int c = tid % C, part = tid / C;
         const int q = c / (C / 4), w = c % (C / 4);               // lane group of the accumulator, bit within it
         const int t = w / 4, rho = 4 * q + w % 4;                 // tile and its row
-        float n2 = 0.0f;
+        const bool mine = part < TPC;
+        float v[TASKS][8];
+        auto k_of = [&](int i, int e) {
+            const int j = part + i * TPC;                         // task j: s = j / 4, kq = j % 4
+            return 16 * (2 * (j >> 2) + e / 4) + 4 * (j & 3) + e % 4;
+        };
+        if (mine) {
 #pragma unroll
-        for (int p = 0; p < TPC; ++p) n2 += n2_s[p][c];
-        // a dead, denormal, overflowing or non-finite column gets an all-zero r^: z~ = 0 fails the margin test, so
-        // every bit of that column is parked and settled by the defining chain
-        const float inv = n2 >= kColumnMin2 && n2 < __builtin_inff() ? 1.0f / __builtin_sqrtf(n2) : 0.0f;
-        uint32_t up[4], lo[4];
+            for (int i = 0; i < TASKS; ++i)
 #pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) {
-            float v[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int e = 2 * e2 + h, k = 16 * (2 * s + e / 4) + 4 * kq + e % 4;
-                v[h] = inv > 0.0f ? r_s[k * C + c] * inv * kColumnScale : 0.0f;
-            }
-            split_f16_pair(v[0], v[1], up[e2], lo[e2]);
+                for (int e = 0; e < 8; ++e) v[i][e] = proj[(size_t)k_of(i, e) * nbits + c_first + c];
         }
-        frag_s[((t * S + s) * 2 + 0) * 64 + kq * 16 + rho] = make_uint4(up[0], up[1], up[2], up[3]);
-        frag_s[((t * S + s) * 2 + 1) * 64 + kq * 16 + rho] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        if (tile < n_total) load_tile(tile);
+        if (mine) {
+            float n2 = 0.0f;                                      // this thread's share of the norm
+#pragma unroll
+            for (int i = 0; i < TASKS; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    r_s[k_of(i, e) * C + c] = v[i][e];
+                    n2 = __builtin_fmaf(v[i][e], v[i][e], n2);
+                }
+            n2_s[part][c] = n2;
+        }
+        __syncthreads();
+        if (mine) {
+            float n2 = 0.0f;
+#pragma unroll
+            for (int p = 0; p < TPC; ++p) n2 += n2_s[p][c];
+            // a dead, denormal, overflowing or non-finite column gets an all-zero r^: z~ = 0 fails the margin test, so
+            // every bit of that column is parked and settled by the defining chain
+            const float inv = n2 >= kColumnMin2 && n2 < __builtin_inff() ? 1.0f / __builtin_sqrtf(n2) : 0.0f;
+#pragma unroll
+            for (int i = 0; i < TASKS; ++i) {
+                const int j = part + i * TPC, step = j >> 2, kq = j & 3;
+                uint32_t up[4], lo[4];
+#pragma unroll
+                for (int e2 = 0; e2 < 4; ++e2) {
+                    float x[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) x[h] = inv > 0.0f ? v[i][2 * e2 + h] * inv * kColumnScale : 0.0f;
+                    split_f16_pair(x[0], x[1], up[e2], lo[e2]);
+                }
+                frag_s[((t * S + step) * 2 + 0) * 64 + kq * 16 + rho] = make_uint4(up[0], up[1], up[2], up[3]);
+                frag_s[((t * S + step) * 2 + 1) * 64 + kq * 16 + rho] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
 
     int cnt = 0;                   // parked entries of this wavefront (wave-uniform)
     uint64_t *list = list_s[wave];
@@ -409,8 +430,9 @@ bool binarize_mfma_supported(int d, int nbits) {
 template <int D, int C, int kWaves>
 int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &map, int nbits, long n_tiles, long n_total,
                  const SideWork &side, hipStream_t st) {
-    // one workgroup per CU (what the registers allow) over all column groups, every wavefront the same number of tiles
-    const long waves = 256 / (nbits / C) * kWaves;
+    // eight wavefronts per CU (what the registers allow) over all column groups, every wavefront the same number of tiles
+    constexpr int PER_CU = C == 64 ? 8 / kWaves : 1;
+    const long waves = 256 * PER_CU / (nbits / C) * kWaves;
     const long tiles_per_wave = (n_total + waves - 1) / waves;
     const long blocks = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
     // what rides along comes behind the tiles: it fills the CUs that are done first
@@ -422,14 +444,18 @@ int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &
 }
 
 // Workgroups of 8 wavefronts, of 4 where those already have one tile each: two wavefronts of one tile on a SIMD only
-// take turns (1 x 197 x 3 heads x 64 -> 64 bits: 7.6 -> 7.0 us).
+// take turns (1 x 197 x 3 heads x 64 -> 64 bits: 7.6 -> 7.0 us).  64 columns take little LDS: two workgroups of 4 to a CU, each
+// of which waits for fewer wavefronts (8 x 1000 x 3 heads x 128 -> 64 bits: 12.1 -> 11.5 us, 16 x 784 x 2 x 32 -> 64 5.8 -> 5.6).
+// Unless they also route: a workgroup of 4 takes in 4096 tokens per round trip, and all of them look at all tokens (block of
+// 32 x 784 tokens x 2 heads: 47.3 us with 4 wavefronts, 44.6 with 8).
 template <int D, int C>
 int launch_one(const Tensors &ts, int count, const float *proj, long rows, int N, int H, int nbits, const SideWork &side,
                hipStream_t st) {
     const long n_tiles = (rows + 31) / 32, n_total = n_tiles * count;
     const RowMap map{FastDiv((uint32_t)H), FastDiv((uint32_t)N), N, H, nbits / 64};
-    return n_total <= 256 / (nbits / C) * 4 ? launch_waves<D, C, 4>(ts, proj, rows, map, nbits, n_tiles, n_total, side, st)
-                                            : launch_waves<D, C, 8>(ts, proj, rows, map, nbits, n_tiles, n_total, side, st);
+    const bool four = n_total <= 256 / (nbits / C) * 4 || (C == 64 && side.route.T <= 4096);
+    return four ? launch_waves<D, C, 4>(ts, proj, rows, map, nbits, n_tiles, n_total, side, st)
+                : launch_waves<D, C, 8>(ts, proj, rows, map, nbits, n_tiles, n_total, side, st);
 }
 
 // x1 / codes1 may be null: one tensor.  Columns of a workgroup: as many of the code as divide it, up to 256 (128 at

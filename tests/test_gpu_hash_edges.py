@@ -65,3 +65,48 @@ def test_bits_are_the_chains_at_the_margin(sa, d):
         sa.sa_binarize_pair(q, k, p, nbits, *codes)
         for t, c in zip((q, k), codes):
             assert torch.equal(c, sa.sa_binarize(t, p, nbits, variant=0))
+
+
+@pytest.mark.parametrize("d,nbits", [(32, 64), (64, 64), (64, 192), (128, 64), (128, 320)])
+def test_workgroups_of_64_columns_over_many_tiles(sa, d, nbits):
+    """More tiles than wavefronts: two workgroups of four wavefronts to a CU, each with several tiles, the last ones uneven."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + nbits)
+    x = [torch.randn((11, 3333, 2, d), generator=g, device="cuda") for _ in range(2)]       # 73326 rows: 2 x 2292 tiles
+    proj = torch.randn((d, nbits), generator=g, device="cuda")
+    codes = sa.sa_binarize_pair(x[0], x[1], proj, nbits)
+    for t, c in zip(x, codes):
+        assert torch.equal(c, sa.sa_binarize(t, proj, nbits, variant=0))
+
+
+@pytest.mark.parametrize("B,N,d", [(4, 1024, 64), (5, 1000, 64), (33, 500, 32)])
+def test_hash_that_routes_along(sa, B, N, d):
+    """Around the number of tokens from which the workgroups that also route are larger ones: what the hash leaves is the same (the
+    attention output of a block with a router and of one without, bit for bit), and so is the routing."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    H, T, nbits, E, hid = 2, B * N, 64, 2 * d, 128
+
+    def randn(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    kw = dict(B=B, N=N, H=H, d=d, nbits=nbits, dv=d, attention=0, attn_scale=1.0 / (N * nbits) ** 0.5, q=randn(B, N, H, d),
+              k=randn(B, N, H, d), v=randn(B, N, H, d), proj=randn(d, nbits))
+    plain, _ = sa.binding.Block(hid=0, moe=False, **kw).forward()
+    w = [torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8) for s in ((hid, E // 2), (E, hid // 2))]
+    mw = [randn(hid, E).half() * 0.1, randn(E, hid).half() * 0.1]
+    lut = torch.arange(-128, 128, device="cuda").to(torch.int8)
+    logits = randn(T, 2)
+    mlp = dict(w1=w[0], w2=w[1], lut=lut, mw1=mw[0], mw2=mw[1], act_inv_scale=30.0, requant_scale=1e-3, out_scale=1e-3)
+    o, y = sa.binding.Block(hid=hid, moe=True, logits=logits, **mlp, **kw).forward()
+    assert torch.equal(o, plain)
+    # every row of y as its expert alone gives it, times its gate
+    expert = (logits[:, 1] > logits[:, 0]).long()
+    gate = torch.softmax(logits.double(), 1).gather(1, expert[:, None])
+    ys = []
+    for e in (0, 1):
+        one = torch.full((T, 2), -200.0, device="cuda")
+        one[:, e] = 0.0                                    # gate 1
+        ys.append(sa.binding.Block(hid=hid, moe=True, logits=one, **mlp, **kw).forward()[1].double())
+    ref = torch.where(expert[:, None] == 0, ys[0], ys[1]) * gate
+    assert bool(((y.double() - ref).abs() <= 1e-5 * ref.abs() + 1e-6 * float(ref.square().mean().sqrt())).all())
