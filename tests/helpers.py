@@ -36,7 +36,7 @@ def assert_close(got, ref, rtol, atol, what=""):
                              % (what, int(bad.sum()), bad.size, i, got[i], ref[i]))
 
 
-# Spec tolerance of the floating-point attention outputs.
+# Tolerance of the floating-point attention outputs.
 ATTN_RTOL, ATTN_ATOL = 1e-4, 1e-5
 
 

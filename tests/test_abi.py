@@ -29,7 +29,7 @@ def lib():
     return lib
 
 
-def test_header_declares_the_north_star_calls():
+def test_header_declares_the_calls_of_the_block():
     names = declared_functions()
     for n in ("sa_binarize", "sa_additive_attention", "sa_hamming_attention", "sa_shift_linear",
               "sa_moe_dispatch", "sa_block_forward"):

@@ -8,7 +8,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("share", [0.0, 0.4, 1.0])
 @pytest.mark.parametrize("T,K,N", [
     (1, 32, 4), (37, 96, 100), (65, 128, 64), (200, 512, 192),                       # 32-row slices, each stage width
-    (700, 96, 300), (1300, 256, 260), (1379, 768, 768),                              # 64-row slices
+    (700, 96, 300), (1300, 256, 260),                                                # ... over many row tiles
+    (2000, 96, 300), (1801, 256, 260), (1379, 768, 768),                             # 64-row slices, each stage width
     (9001, 96, 301), (9000, 768, 512), (8700, 2048, 320), (8450, 512, 4096),         # the three larger pairs
 ])
 def test_moe_linear_against_separate_launches(sa, T, K, N, share):

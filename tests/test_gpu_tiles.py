@@ -20,9 +20,10 @@ def decode(w4):
     (1, 512, 64), (65, 640, 132), (197, 3072, 768), (33, 2048, 36),     # 32-row tiles, 128-byte stages
     (4129, 64, 256), (2081, 224, 512), (1300, 96, 1000),                # 64-row tiles, 64-byte stages
     (1379, 512, 900), (965, 3072, 768), (4161, 768, 260),               # 64-row tiles, 128-byte stages
-    (6337, 192, 768), (6401, 768, 768), (12609, 160, 1540),             # 128 x 128
-    (12801, 768, 1300), (6400, 3072, 768),                              # 256 x 128, long rows
-    (2003, 96, 1700), (50001, 64, 60), (2003, 2048, 1700),              # 128 x 64, both stage widths
+    (6337, 192, 768), (6401, 768, 768), (2003, 96, 1700), (50001, 64, 60),        # 128 x 64, 64-byte stages
+    (6400, 3072, 768), (2003, 2048, 1700),                              # 128 x 64, 128-byte stages
+    (12609, 160, 1540), (12801, 768, 1300),                             # 128 x 128
+    (11521, 192, 1300),                                                 # 256 x 128
     (13001, 2048, 2048),                                                # 192 x 128
 ])
 def test_shift_linear_at_the_borders_of_the_tile_choice(sa, M, K, N):
@@ -39,7 +40,8 @@ def test_shift_linear_at_the_borders_of_the_tile_choice(sa, M, K, N):
 @pytest.mark.parametrize("rows,E,hid", [
     (1, 32, 64), (33, 64, 96), (65, 192, 768), (197, 768, 256),         # 32-row tiles
     (1379, 192, 768), (965, 768, 1024), (1250, 1536, 192),              # 64-row tiles, short and long rows
-    (3200, 768, 992), (6500, 128, 512), (3300, 384, 1536),         # the larger tiles
+    (3200, 768, 992), (6500, 128, 512), (3300, 384, 1536),         # fc1: 192 x 128, 128 x 128 with 64-byte stages
+    (3300, 512, 1536),                                             # fc2: 128 x 128 with long rows
 ])
 def test_mult_expert_at_the_borders_of_the_tile_choice(sa, rows, E, hid):
     g = torch.Generator(device="cuda")
@@ -68,7 +70,9 @@ def test_mult_expert_at_the_borders_of_the_tile_choice(sa, rows, E, hid):
     assert bool((y[rest] == 7.0).all())
 
 
-@pytest.mark.parametrize("B,N,H,d", [(1, 50, 2, 64), (7, 197, 12, 64), (3, 300, 6, 128), (26, 500, 6, 128), (32, 197, 12, 64)])
+@pytest.mark.parametrize("B,N,H,d", [(1, 50, 2, 64), (7, 197, 12, 64), (3, 300, 6, 128), (26, 500, 6, 128), (32, 197, 12, 64),
+                                     (1, 40, 8, 64), (4, 200, 4, 64),                     # slices of either stage width
+                                     (50, 500, 4, 64), (2, 300, 16, 128), (7, 601, 16, 128)])   # 128 x 128, 128 x 64 and 192 x 128, long rows
 def test_sign_codes_of_every_tile_width(sa, B, N, H, d):
     E = H * d
     g = torch.Generator(device="cuda")
