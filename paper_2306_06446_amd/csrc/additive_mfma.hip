@@ -9,9 +9,10 @@
 // plain-VALU rate is 39 T adds/s on this chip; the three-plane bf16 form runs ~20 times faster).
 //
 //   K^T V   : M = code bits (one 64-bit word = two 32-bit tiles per wavefront), N = dv columns,
-//             K = tokens, 16 per MFMA.  V is staged through LDS transposed into its three bf16
-//             planes, 64 tokens per chunk, double-buffered.  Token ranges are split over workgroups;
-//             partial sums meet in ascending order (no float atomics), in Q(K^T V) itself when they are few.
+//             K = tokens, 16 per MFMA.  Every wavefront loads the V rows and code words of its own steps
+//             into a ring of its own in LDS and makes the three terms in registers.  Token ranges are split
+//             over workgroups; partial sums meet in ascending order (no float atomics), in Q(K^T V) itself
+//             when they are few.
 //   Q(K^T V): M = tokens (TM 32-token tiles per wavefront), N = dv columns, K = code bits.
 //             K^T V is staged once per workgroup, transposed into its three planes.
 //

@@ -74,10 +74,12 @@ int check_shift_mlp(const int8_t *xq, const sa_rows *rows, RowSel *sel, int E, i
                     int stages, const void *workspace, size_t workspace_bytes);
 bool shift_rows_fit(long rows, int variant);         // rows of one launch of a Shift layer
 
-// 16 bytes to memory past the caches' reuse order: for 32-bit outputs, which are large, written once and not read again
-// soon, and otherwise push out what is.  12608 x 1536 <- 384 and back, int32: 72 -> 60 us; the layers with fp32 outputs of
-// 12608 x 768 tokens 0 to 4 us each; Q(K^T V) at 8 x 4 x 16384 x 256 bits x 64 70 -> 64 us.  For the narrow outputs that
-// the next kernel reads it gained nothing, for the reads of Q and K it lost (pvt-sized attention 28.8 -> 30.5 us).
+// 16 bytes to memory past the caches' reuse order: for 32-bit outputs, which are large and written once, and otherwise push out
+// the operands of the launch that writes them.  12608 x 1536 <- 384 and back, int32: 72 -> 60 us; the layers with fp32 outputs of
+// 12608 x 768 tokens 0 to 4 us each; Q(K^T V) at 8 x 4 x 16384 x 256 bits x 64 70 -> 64 us.  It pays even where the next
+// launch reads them again, as Q, K, V and y of a layer: 12608 x 768 tokens 341 -> 333 us, 25088 x 64 63.0 -> 60.0, 16384 x
+// 256 128.4 -> 127.4; one image of 197 x 192, which fits the L2, 42.6 -> 43.0.  For the narrow outputs that the next kernel
+// reads it gained nothing, for the reads of Q and K it lost (pvt-sized attention 28.8 -> 30.5 us).
 __device__ inline void store_streaming(void *dst, const uint4 &v) {
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     __builtin_nontemporal_store(u4{v.x, v.y, v.z, v.w}, reinterpret_cast<u4 *>(dst));

@@ -104,6 +104,7 @@ __device__ inline int swizzle(int r, int c) {
 // The 16-byte chunks at columns n .. n + 16 / kBytes - 1 of the output: where they go, and what they need from memory besides
 // the product (the residual, or what the destination holds).  fetch() is apart from put() so that the reads of many chunks
 // are in flight at once: read where it was used, each waited for the one before it (two, with a row index and its gate).
+// Small shift linears 58.4 -> 54.4 us, 12608 x 768 tokens through a layer 362 -> 335, moe linear 32.7 -> 29.6.
 template <class Store>
 struct ChunkOut {
     static constexpr int ES = Store::kBytes;
@@ -654,7 +655,9 @@ namespace sa {
 //    (1379 x 1024 <- 256 int8: 5.7 us against 6.1);
 //  * beyond, the tiles of this file.  int8 rows of 2 KiB and more in whole 128-byte lines: 128 x 64, 128-byte stages, two
 //    per CU (with a residual, 8826 x 768 <- 3072: 53 us against 61 with 256 x 128 tiles, of which 210 leave 46 CUs idle);
-//    from about three rounds of those on, 192 x 128 with 64-byte stages (43690 rows: 253 against 275).  Other int8 rows:
+//    beyond 1536 tiles of 128 x 128 (six rounds of 128 x 64), 192 x 128 with 64-byte stages.  768 <- 3072 with a residual,
+//    128 x 64 against 192 x 128: 25600 rows 123 against 135 us, 64000 rows 345 against 303; from 1400 to 2000 tiles it
+//    depends on whose last round is fuller (29824 rows 141 against 133, 36224 rows 164 against 175).  Other int8 rows:
 //    128 x 64, three per CU with a ring of three, where 128 x 128 tiles would not fill the chip once or half of their
 //    columns would be padding (with a residual, 16384 x 256 <- 1024: 18.9 against 23.8; 12608 x 384 <- 384: 15.9
 //    against 21.0); else 256 x 128 (two per CU) or 128 x 128 (three per CU) with 64-byte stages;
