@@ -30,6 +30,16 @@ PEAK_TFLOPS = {                  # dense peaks of MI355X
     # matrix-core products of the fp32 operand's exact bf16 terms: its algorithmic flops are priced at
     # the bf16 peak / 3 (above the fp32 matrix peak of 157.3, which such a kernel can beat)
     "mfma_bf16x3": 2500.0 / 3,
+    "mfma_f16x3": 2500.0 / 3,    # the hash: three of the four products of two operands in two fp16 terms each
+}
+
+# Steps that the per-kernel pass launches alone, and how a block runs them: nothing of it is an entry point of its own there.
+IN_BLOCK = {
+    "dispatch": "rides in the launch of the hash (up to 32768 tokens)",
+    "shift_decode": "rides in the launch of the hash",
+    "quantize": "part of the launch of Q (K^T V)",
+    "mult_fc1": "one launch with shift_fc1", "shift_fc1": "one launch with mult_fc1",
+    "mult_fc2": "one launch with shift_fc2", "shift_fc2": "one launch with mult_fc2",
 }
 
 
@@ -97,7 +107,8 @@ def parse():
 
 def kernel_table(cfg, p, counts, shift_variant=1):
     """Algorithmic bytes and operations of every kernel of the block (what the method must move and
-    compute: packed codes, 4-bit weights, int8 activations; never the dense fp32 work it avoids).
+    compute: packed codes, 4-bit weights, int8 activations; never the dense fp32 work it avoids).  Every step is a launch of
+    its own here; IN_BLOCK says which ones share one in the block.
     `bytes_fetched`, where given, is what the timed kernel of this variant actually requests when that differs:
     the matrix-core Shift GEMMs read two int8 planes per weight matrix (2 bytes per weight) where the method
     stores 4 bits; with variant 1 a decode launch per step reads the 4-bit rows and writes those planes."""
@@ -108,7 +119,7 @@ def kernel_table(cfg, p, counts, shift_variant=1):
     bin_flop = 2 * rows * cfg.nbits * cfg.d
     # Q and K are hashed by one launch
     tab.append(dict(name="binarize_qk", bytes=2 * bin_bytes - cfg.d * cfg.nbits * 4, ops=2 * bin_flop,
-                    compute="mfma_bf16x3" if cfg.d in (32, 64, 128) else "alu_fp32"))
+                    compute="mfma_f16x3" if cfg.d in (32, 64, 128) else "alu_fp32"))
     code_b = rows * cfg.nbits // 8
     v_b = rows * cfg.dv * 4
     if cfg.attention == "linear":
@@ -325,6 +336,8 @@ def main():
                    compute_peak=comp)
         if "bytes_fetched" in t:
             row["bytes_fetched"] = t["bytes_fetched"]
+        if t["name"] in IN_BLOCK and (moe or not t["name"].startswith(("mult_", "shift_fc"))):
+            row["in_block"] = IN_BLOCK[t["name"]]
         if t["name"] in derived:
             row["derived"] = "both layers in one call minus the two layers alone"
         if us:
@@ -457,10 +470,10 @@ def _time_us_graph(torch, fn, reps=20, replays=10):
 
 
 def bench_experts(args, sa, wl, torch, np, cfg):
-    """The MoE MLP of the block with its two experts (a) one after the other on one stream, as sa_block_forward runs
-    them, and (b) side by side on two streams that fork after the dispatch and join before the next step (Sec. 4.2: the
-    experts are independent once the routing lists exist; the paper's tables count them as perfectly parallel, its
-    'modularized' latency = the slower expert alone)."""
+    """The MoE MLP of the block with its two experts in launches of their own, (a) one after the other on one stream and (b)
+    side by side on two streams that fork after the dispatch and join before the next step (Sec. 4.2: the experts are
+    independent once the routing lists exist; the paper's tables count them as perfectly parallel, its 'modularized'
+    latency = the slower expert alone).  sa_block_forward does neither: both experts share one launch per layer."""
     assert cfg.E and cfg.shift_frac is not None, "--experts needs a configuration with a MoE MLP (c1, c4)"
     T, E, hid = cfg.T, cfg.E, cfg.hid
     p = wl.mlp_params(cfg)
@@ -585,8 +598,8 @@ def bench_experts(args, sa, wl, torch, np, cfg):
            "experts_us": us, "modularized_us": max(us["mult_alone"], us["shift_alone"]),
            "vendor_library_gemm_for_scale": library,
            "concurrent_output_identical": same,
-           "note": "sequential = both experts on one stream (what sa_block_forward does); concurrent = two streams forked after "
-                   "the dispatch and joined; modularized = the slower expert alone, the figure the paper's tables report for "
+           "note": "sequential = both experts on one stream, a launch per expert and layer (sa_block_forward runs both experts of "
+                   "a layer in one launch); concurrent = two streams forked after the dispatch and joined; modularized = the slower expert alone, the figure the paper's tables report for "
                    "experts counted as perfectly parallel",
            "roofline": None, "cpu_baseline": None}
     print(json.dumps(out))
@@ -820,7 +833,7 @@ def bench_zero_one(args, sa, wl, torch, np, cfg):
     ms_per_step = (time.perf_counter() - t0) * 1e3 / args.steps
     rows = B * N * H
     code_b, v_b, kv_b = rows * nbits // 8, rows * dv * 4, B * H * nbits * dv * 4
-    algo = {"binarize_qk": (2 * (rows * d * 4 + code_b) + d * nbits * 4, 4 * rows * nbits * d, "mfma_bf16x3"),
+    algo = {"binarize_qk": (2 * (rows * d * 4 + code_b) + d * nbits * 4, 4 * rows * nbits * d, "mfma_f16x3"),
             "ktv01_counts": (2 * code_b + v_b + kv_b, 2 * rows * nbits * dv, "mfma_bf16x3"),
             "qkv01_normalised": (2 * code_b + kv_b + v_b, 2 * rows * nbits * dv, "mfma_bf16x3"),
             "dwconv3x3_add": (3 * v_b, 18 * rows * dv, "alu_fp32")}
@@ -947,7 +960,7 @@ def bench_layer(args, sa, wl, torch, np, cfg):
             T * E + 3 * E * E // 2 + 3 * T * E * 4, 2 * T * E * 3 * E, "mfma_i8")
         add("binarize_qk", lambda: sa.sa_binarize_pair(q4, k4, shared["proj"], cfg.nbits, q_codes=qc, k_codes=kc),
             2 * (rows * d * 4 + code_b) + (d * cfg.nbits * 4 if shared["proj"] is not None else 0),
-            4 * rows * cfg.nbits * d if shared["proj"] is not None else 2 * rows * d, "mfma_bf16x3")
+            4 * rows * cfg.nbits * d if shared["proj"] is not None else 2 * rows * d, "mfma_f16x3")
     o = torch.empty((B, N, H, d), dtype=torch.float32, device="cuda")
     if cfg.attention == "linear":
         kv = torch.empty((B, H, cfg.nbits, d), dtype=torch.float32, device="cuda")
