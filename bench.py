@@ -1023,6 +1023,8 @@ def bench_layer(args, sa, wl, torch, np, cfg):
         row = dict(name=name, us=None if us is None else round(us, 2), bytes=nbytes, ops=ops, hbm_floor_us=round(t_hbm, 2),
                    compute_floor_us=round(t_cmp, 2), bound="hbm" if t_hbm >= t_cmp else ("mfma" if comp.startswith("mfma") else "alu"),
                    compute_peak=comp)
+        if name in IN_BLOCK and name != "dispatch" and (moe or not name.startswith("shift_fc")):      # (a layer's routing waits for its logits)
+            row["in_block"] = IN_BLOCK[name]
         if us:
             row.update(hbm_frac=round(t_hbm / us, 4), binding_frac=round(max(t_hbm, t_cmp) / us, 4))
         report.append(row)

@@ -1,7 +1,7 @@
 // sa_block_forward: one pass of the reparameterised block (Eq. 2 restricted to the
 // attention MatMuls and the MLP): hash Q and K, additive or Hamming attention, then the
-// Shift MLP or the two-expert MoE.  Pure composition of the library's own entry points;
-// the expert row counts stay on the device (no host round trip).
+// Shift MLP or the two-expert MoE.  A composition of the library's own steps; the expert row counts
+// stay on the device (no host round trip).
 #include "common.h"
 
 namespace {

@@ -479,9 +479,10 @@ extern "C" int sa_moe_balance_loss(const float *logits, long T, int E, const flo
 // ---- the MoE form of one Linear layer -----------------------------------------------------------------
 // Sec. 4.1 turns the Linear layers of the attention module into Shift layers or into MoEs; this is the MoE:
 // top-1 routing between a Mult expert (fp16 weights, fp16 activations) and a Shift expert (4-bit shift weights,
-// int8 activations), each a single layer, y[t, :] = gate[t] * E_i(x[t, :]) (Sec. 4.2).  Three launches: the
-// routing, then one tiled GEMM per expert over the rows it was given (gathered by row id on the way into LDS,
-// scattered with the gate on the way out), plus the decode of the shift weights where the variant needs one.
+// int8 activations), each a single layer, y[t, :] = gate[t] * E_i(x[t, :]) (Sec. 4.2).  Two launches: the routing
+// together with the decode of packed shift weights, then the tiles of both experts over the rows each was given (gathered
+// by row id on the way into LDS, scattered with the gate on the way out).  The vector-ALU variant and inputs beyond the
+// one-launch routing take more.
 namespace {
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
