@@ -196,6 +196,12 @@ int expert_pair_mlp(const ExpertPair &p, int E, int hid, const int8_t *w1_planes
                     const void *mw2, float requant_scale, const int8_t *lut, bool accumulate, int8_t *shift_hidden,
                     void *mult_hidden, hipStream_t st);
 int expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes, const void *w_f16, hipStream_t st);
+// Both layers of a Shift MLP in one launch, on decoded planes (shift_mlp.hip): whether it takes the shape, and the launch.
+// out: yf, gate, out_scale, accumulate.
+struct Epilogue;
+bool shift_mlp_one_launch(const RowSel &sel, int E, int hid);
+int launch_shift_mlp(const int8_t *x, const RowSel &sel, int E, int hid, const int8_t *w1_planes, const int8_t *w2_planes,
+                     const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).
 size_t moe_dispatch_scratch_bytes(long T, int E);
 int moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,

@@ -571,6 +571,15 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
         rc = launch_decode(w, st);
         if (rc != SA_OK) return rc;
     }
+    if ((stages & 3) == 3 && v_eff != SA_VARIANT_VALU && y_or_null && !y2_or_null && sa::shift_mlp_one_launch(sel, E, hid)) {
+        sa::Epilogue e;
+        e.yf = y_or_null;
+        e.gate = gate_or_null;
+        e.out_scale = out_scale;
+        e.accumulate = (stages & SA_MLP_ACCUMULATE) != 0;
+        return sa::launch_shift_mlp(xq, sel, E, hid, reinterpret_cast<const int8_t *>(pair ? planes1 : w1),
+                                    reinterpret_cast<const int8_t *>(pair ? planes2 : w2), lut, requant_scale, e, st);
+    }
     if (stages & 1) {
         sa::Epilogue e1;
         e1.h = hbuf;

@@ -1,0 +1,352 @@
+// Both layers of a Shift MLP in one kernel, for widths whose output row a workgroup can hold (E = 64 .. 256):
+//     y[row] = scale * W2 . lut[requant(W1 . x[row])]
+// The hidden rows never leave the CU: 128 of their columns at a time are made from the rows of x (in registers), go through
+// the table into LDS and are multiplied into the output, while the next 128 are made.  As two launches the MLP wrote and read
+// them (134 MB for 131072 rows of 1024), and a tile of either spent as long on its way in and out as on its products (256 x 128
+// of 1024 <- 256: 3.5 us of products in 10.4).  Both planes of both weights stream past, through a ring of three stages.
+//
+// Bound by how closely the two wavefronts of a SIMD pack products and the requantiser's vector operations (at E = 256 the matrix
+// pipe is busy for half of a round); the weights, from the L2, are there in time.  Measured, two launches -> one:
+//      25088 x  64, 512 hidden   20.0 -> 10.1 us     131072 x  64   49 -> 33
+//      25088 x 192, 768 hidden   30 -> 24            131072 x 192  112 -> 93
+//      16384 x 256, 1024 hidden  31 -> 26            131072 x 256  161 -> 145
+// Layer 1 on four wavefronts and layer 2 on the other four (requantiser beside products without being interleaved): 226 us
+// for the last one.
+#include "common.h"
+#include "gemm_common.h"
+#include "gemm_mfma.h"
+#include "gemm_stores.h"
+
+namespace {
+
+using namespace sa;
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+__device__ inline v4i mma16(const uint4 &a, const uint4 &b, v4i c) {
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, a), __builtin_bit_cast(v4i, b), c, 0, 0, 0);
+}
+
+constexpr int kMlpWaves = 8, kHidChunk = 128;
+
+// NE: E / 64.  MI: 16-row tiles of a wavefront; the eight wavefronts stand 2 x 4 over rows x columns.
+template <int NE, int MI, class Store>
+struct MlpShape {
+    static constexpr int E = 64 * NE, BM = 32 * MI;
+    static constexpr int PS = NE <= 2 ? 2 : 1;               // planes of a stage
+    static constexpr int SPG = 2 / PS;                       // stages of one layer of a chunk
+    static constexpr int PLANE = kHidChunk * E;              // W1: 128 rows of E bytes; W2: E rows of 128 bytes
+    static constexpr int STAGE = PS * PLANE, RING = 3, LOADS = PS * NE;
+    static constexpr int PITCH = 64 * NE + 16;               // a staged output row of a wavefront's columns
+    static constexpr int H = RING * STAGE, H_BYTES = BM * kHidChunk, TABLE = H + 2 * H_BYTES, SIDE = TABLE + 256;
+    static constexpr int LDS_BYTES = SIDE + OutSide<Store, BM>::BYTES;
+    static_assert(kMlpWaves * 16 * PITCH <= H, "output staging reuses the ring");
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+};
+
+// 16-byte chunk c of a row of E bytes in LDS: any 16 consecutive rows hit 16 different bank groups.
+template <int NE>
+__device__ inline int swizzle_w1(int r, int c) {
+    if (NE == 4) return c ^ (r & 15);
+    if (NE == 2) return c ^ ((r >> 1) & 7);
+    return (c & ~3) | ((c & 3) ^ ((r >> 2) & 3));
+}
+__device__ inline int swizzle_128(int r, int c) { return c ^ ((r >> 1) & 7); }
+
+template <int NE, int MI, class Store>
+__global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, RowSel sel, int hid,
+                                                                   const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
+                                                                   const int8_t *__restrict__ lut, float rq, Store store) {
+    using S = MlpShape<NE, MI, Store>;
+    constexpr int E = S::E, PS = S::PS, SPG = S::SPG, LOADS = S::LOADS;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[S::LDS_BYTES];
+    const int32_t *rows;
+    long n_rows;
+    resolve_rows(sel, rows, n_rows);
+    const long m0 = (long)blockIdx.x * S::BM;
+    if (m0 >= n_rows) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 2, wc = wave & 3, fr = lane & 15, fg = lane >> 4;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
+    const int chunks = hid / kHidChunk;
+
+    const OutSide<Store, S::BM> side{store, rows, m0, n_rows, lds + S::SIDE};
+    side.fetch_rows(wave, lane);
+    if (wave == kMlpWaves - 1) direct_load_4(lut + lane * 4, lds_base + S::TABLE);
+
+    // this wavefront's rows of x, as operands of the first layer
+    uint4 xf[MI][NE];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const long m = min(m0 + wr * 16 * MI + 16 * i + fr, n_rows - 1);
+        const int8_t *xr = x + (size_t)(rows ? (long)rows[m] : m) * E + 16 * fg;
+#pragma unroll
+        for (int k = 0; k < NE; ++k) xf[i][k] = *reinterpret_cast<const uint4 *>(xr + 64 * k);
+    }
+
+    // Where this lane's 16 bytes of load i of a plane come from: a part that is the same in every lane (row0 rows) and one per
+    // lane, whose chunk is flipped by `flip` bytes between the loads.
+    const uint32_t lane2 = (uint32_t)(lane >> 3) * (uint32_t)hid + (uint32_t)((lane & 7) ^ (lane >> 4)) * 16;
+    uint32_t lane1[NE == 3 ? 3 : 1];
+    if constexpr (NE == 3) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int q = (wave * NE + i) * 64 + lane, r = q / (4 * NE);
+            lane1[i] = (uint32_t)(r * E + swizzle_w1<NE>(r, q % (4 * NE)) * 16);
+        }
+    } else {
+        const int r = lane / (4 * NE);
+        lane1[0] = (uint32_t)(r * E + swizzle_w1<NE>(r, lane % (4 * NE)) * 16);
+    }
+    // The stages in the order they are multiplied: layer 1 of chunk 0, then layer 1 of chunk c + 1 before layer 2 of chunk c.
+    const int n_stages = 2 * chunks * SPG;
+    auto issue = [&](int s, int slot) {
+        const int u = s / SPG, sub = s % SPG;
+        const bool second = u == 2 * chunks - 1 || (u > 0 && u % 2 == 0);
+        const int c = u == 2 * chunks - 1 ? chunks - 1 : second ? u / 2 - 1 : (u + 1) / 2;
+#pragma unroll
+        for (int p = 0; p < PS; ++p) {
+            const size_t plane = (size_t)(sub * PS + p) * hid * E;
+            const uint32_t at = lds_base + slot * S::STAGE + p * S::PLANE + wave * NE * 1024;
+            if (second) {
+                const int8_t *base = w2 + plane + (size_t)c * kHidChunk + (size_t)(wave * NE * 8) * hid;
+#pragma unroll
+                for (int i = 0; i < NE; ++i) direct_load_16(base + (size_t)i * 8 * hid, lane2 ^ ((wave * NE + i) % 2 * 64), at + i * 1024);
+            } else {
+                const int8_t *base = w1 + plane + (size_t)c * kHidChunk * E;
+#pragma unroll
+                for (int i = 0; i < NE; ++i) {
+                    if constexpr (NE == 3) direct_load_16(base, lane1[NE == 3 ? i : 0], at + i * 1024);
+                    else direct_load_16(base + (wave * NE + i) * 1024, lane1[0] ^ (NE == 4 ? i * 64 : NE == 2 ? (wave * NE + i) % 2 * 64 : 0), at + i * 1024);
+                }
+            }
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < S::RING; ++q) issue(q, q);           // (there are at least four stages)
+    wait_loads_in_flight<(S::RING - 1) * LOADS>();
+    side.fetch_gates(wave, lane);
+    __syncthreads();
+    int s = 0, slot = 0;                                     // the stage being multiplied, its place in the ring
+
+    v4i acc1[MI][2], acc2[MI][NE];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int t = 0; t < NE; ++t) acc2[i][t] = v4i{0, 0, 0, 0};
+
+    // Operands are read one step of 64 k ahead of their products.  fb: weights, fa: hidden rows.
+    uint4 fb[2][NE < 2 ? 2 : NE], fa[MI];
+    auto read1 = [&](int par, int p, int k) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int r = wc * 32 + 16 * t + fr;
+            fb[par][t] = *reinterpret_cast<const uint4 *>(lds + slot * S::STAGE + p * S::PLANE + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+        }
+    };
+    auto read2 = [&](int par, int p, int k) {
+#pragma unroll
+        for (int t = 0; t < NE; ++t) {
+            const int r = wc * 16 * NE + 16 * t + fr;
+            fb[par][t] = *reinterpret_cast<const uint4 *>(lds + slot * S::STAGE + p * S::PLANE + r * kHidChunk + swizzle_128(r, 4 * k + fg) * 16);
+        }
+    };
+    auto read_hidden = [&](int i, int k, int buf) {
+        const int r = wr * 16 * MI + 16 * i + fr;
+        fa[i] = *reinterpret_cast<const uint4 *>(lds + S::H + buf * S::H_BYTES + r * kHidChunk + swizzle_128(r, 4 * k + fg) * 16);
+    };
+    // Before the last products of a stage, whose operands are in registers by then: the next stage is there, and the place of
+    // this one is free for the stage three ahead.
+    auto hand_over = [&]() {
+        if (s + 2 < n_stages) wait_loads_in_flight<LOADS>();
+        else wait_loads_in_flight<0>();
+        __syncthreads();
+        if (s + S::RING < n_stages) issue(s + S::RING, slot);
+        ++s;
+        slot = slot == S::RING - 1 ? 0 : slot + 1;
+    };
+    enum { kNone, kLayer1, kLayer2 };
+    auto first_of = [&](auto next_c) {              // the first operands of what comes next
+        constexpr int next = decltype(next_c)::value;
+        if constexpr (next == kLayer1) read1(0, 0, 0);
+        if constexpr (next == kLayer2) read2(0, 0, 0);
+    };
+
+    // Products are computed transposed (weights down, rows across): a lane holds four consecutive columns of row lane % 16.
+    // buf: the hidden rows that a layer 2 behind this one reads.
+    auto layer1 = [&](auto next_c, int buf) {
+        constexpr int STEPS = PS * NE;                       // of a stage
+        static_for<SPG * STEPS>([&](auto n_c) {
+            constexpr int n = decltype(n_c)::value, m = n + 1;
+            if constexpr (m % STEPS != 0) {
+                read1(m & 1, m % STEPS / NE, m % NE);
+            } else {
+                hand_over();
+                if constexpr (m < SPG * STEPS) read1(m & 1, 0, 0);
+                else first_of(next_c);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                if (m == SPG * STEPS && decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc1[i][t] = mma16(fb[n & 1][t], xf[i][n % NE], n == 0 ? v4i{0, 0, 0, 0} : acc1[i][t]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // tile (i, t) of the chunk's hidden columns: table entries, then a byte each into the hidden rows
+    auto lookup = [&](int i, int t, uint32_t (&v)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = lds[S::TABLE + requant_index(acc1[i][t][r], rq)];
+    };
+    auto keep = [&](int i, int t, const uint32_t (&v)[4], int buf) {
+        const int r = wr * 16 * MI + 16 * i + fr, c = wc * 2 + t;
+        *reinterpret_cast<uint32_t *>(lds + S::H + buf * S::H_BYTES + r * kHidChunk + swizzle_128(r, c) * 16 + 4 * fg) =
+            (v[0] | (v[1] << 8)) | ((v[2] | (v[3] << 8)) << 16);
+    };
+    // Layer 2 of a chunk; between its products the next chunk's hidden columns go to the other buffer (requant), all of them
+    // before the last step, whose barrier another layer 2 may read behind.
+    auto layer2 = [&](int buf, auto requant_c, auto next_c) {
+        constexpr bool REQUANT = decltype(requant_c)::value;
+        constexpr int STEPS = PS * 2;
+        uint32_t v[4];
+        static_for<4>([&](auto n_c) {
+            constexpr int n = decltype(n_c)::value, m = n + 1;
+            if constexpr (m % STEPS != 0) {
+                read2(m & 1, m % STEPS / 2, m % 2);
+            } else {
+                hand_over();
+                if constexpr (m < 4) read2(m & 1, 0, 0);
+                else first_of(next_c);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+#pragma unroll
+                for (int t = 0; t < NE; ++t) acc2[i][t] = mma16(fb[n & 1][t], fa[i], acc2[i][t]);
+                if constexpr (m < 4) read_hidden(i, m % 2, buf);
+                else if constexpr (decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf ^ 1);
+                if constexpr (REQUANT) {
+                    // two tiles in three places of the first three steps
+                    const int at = n * MI + i, tile = at / 3 * 2 + at % 3;
+                    if (n < 3 && at % 3 != 0) keep((tile - 1) / 2, (tile - 1) % 2, v, buf ^ 1);
+                    if (n < 3 && at % 3 != 2) lookup(tile / 2, tile % 2, v);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    using Layer1 = std::integral_constant<int, kLayer1>;
+    using Layer2 = std::integral_constant<int, kLayer2>;
+    using None = std::integral_constant<int, kNone>;
+
+    read1(0, 0, 0);
+    layer1(Layer1{}, 0);
+    {
+        uint32_t v[4];
+#pragma unroll
+        for (int n = 0; n < 2 * MI; ++n) {
+            lookup(n / 2, n % 2, v);
+            keep(n / 2, n % 2, v, 0);
+        }
+    }
+    for (int c = 0; c + 2 < chunks; ++c) {
+        layer1(Layer2{}, c & 1);
+        layer2(c & 1, std::true_type{}, Layer1{});
+    }
+    layer1(Layer2{}, chunks & 1);
+    layer2(chunks & 1, std::true_type{}, Layer2{});
+    layer2((chunks & 1) ^ 1, std::false_type{}, None{});
+
+    // ---- rows out, 16 of the wavefront's columns at a time, through LDS of its own
+    __syncthreads();                                         // the ring has been read
+    uint8_t *slab = lds + wave * 16 * S::PITCH;
+    auto place = [&](int j, int &row, int &col) {            // chunk j of this lane: row of 16, first column
+        const int q = j * 64 + lane;
+        row = q / (4 * NE);
+        col = wc * 16 * NE + q % (4 * NE) * 4;
+    };
+    auto emit = [&](auto reads_c) {
+        constexpr bool READS = decltype(reads_c)::value;
+        float4 ext[READS ? 2 : 1][NE];
+        auto fetch = [&](int i) {
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                int row, col;
+                place(j, row, col);
+                ext[READS ? i & 1 : 0][j] =
+                    READS ? ChunkOut<Store>(store, col, E).fetch(side.dest(wr * 16 * MI + 16 * i + row)) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            if (i + 1 < MI) fetch(i + 1);
+#pragma unroll
+            for (int t = 0; t < NE; ++t) {
+                uint32_t w[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) w[r] = store.convert(acc2[i][t][r], 0, nullptr);
+                *reinterpret_cast<uint4 *>(slab + fr * S::PITCH + (16 * t + 4 * fg) * 4) = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                int row, col;
+                place(j, row, col);
+                const uint4 v = *reinterpret_cast<const uint4 *>(slab + row * S::PITCH + (col - wc * 16 * NE) * 4);
+                const int ml = wr * 16 * MI + 16 * i + row;
+                if (m0 + ml < n_rows) ChunkOut<Store>(store, col, E).put(v, ext[READS ? i & 1 : 0][j], side.gate(ml), side.dest(ml));
+            }
+        }
+    };
+    if (store.accumulate) emit(std::true_type{});
+    else emit(std::false_type{});
+}
+
+template <int NE, int MI>
+int launch(const int8_t *x, const RowSel &sel, int hid, const int8_t *w1, const int8_t *w2, const int8_t *lut, float rq,
+           const ShiftStore<kEpiScatterI32> &store, hipStream_t st) {
+    typedef ShiftStore<kEpiScatterI32> Store;
+    const long blocks = (sel.max_rows + 32 * MI - 1) / (32 * MI);
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_shift_mlp: too many rows for one launch");
+    shift_mlp_kernel<NE, MI, Store><<<dim3((unsigned)blocks), dim3(kMlpWaves * 64), 0, st>>>(x, sel, hid, w1, w2, lut, rq, store);
+    return check_launch("sa_shift_mlp (both layers)");
+}
+
+}  // namespace
+
+// Whether one launch is the faster way.  A workgroup passes all weights through its CU, about 1 us per 128 hidden columns and 64
+// of E / 2, whatever its rows; two launches take 11.7 us for few rows.  So for small products always (E * hid up to 96 Ki:
+// 256 x 384, 6272 rows 13.7 apart against 12.7; 64 x 512, 1568 rows 11.8 against 9.1), for others once their rows fill half of
+// the chip (256 x 1024: 6272 rows 20 against 24, 12608 rows 30 against 25; 192 x 768: 6272 rows 16.5 against 15.9, 3136 rows
+// 13.6 against 15.5).
+bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid) {
+    if (E > 256 || E % 64 != 0 || hid % kHidChunk != 0 || hid < 2 * kHidChunk) return false;
+    return (long)E * hid <= 98304 || sel.max_rows >= 40L * E;
+}
+
+// Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the
+// larger ones takes (256 x 1024: 16384 rows 26 against 36 us, 25088 rows 47 against 37, 131072 rows 181 against 145).  At
+// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).
+int sa::launch_shift_mlp(const int8_t *x, const RowSel &sel, int E, int hid, const int8_t *w1_planes, const int8_t *w2_planes,
+                         const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
+    const ShiftStore<kEpiScatterI32> store(out);
+    const float rq = requant_scale_finite(requant_scale);
+    auto rounds = [&](long rows) { return ((sel.max_rows + rows - 1) / rows + 255) / 256; };
+    const bool tall = E > 64 && 29 * rounds(128) < 20 * rounds(64);
+#define SA_MLP(NE_)                                                                                     \
+    case 64 * NE_:                                                                                      \
+        return tall ? launch<NE_, 4>(x, sel, hid, w1_planes, w2_planes, lut, rq, store, st)             \
+                    : launch<NE_, 2>(x, sel, hid, w1_planes, w2_planes, lut, rq, store, st);
+    switch (E) {
+        case 64: return launch<1, 2>(x, sel, hid, w1_planes, w2_planes, lut, rq, store, st);
+        SA_MLP(2)
+        SA_MLP(3)
+        SA_MLP(4)
+    }
+#undef SA_MLP
+    return fail(SA_ERR_UNSUPPORTED, "sa_shift_mlp: width %d in one launch", E);
+}

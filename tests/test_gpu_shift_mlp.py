@@ -1,0 +1,49 @@
+"""Both layers of a Shift MLP in one launch: bit-identical to the two layers one after the other (integers up to the one
+rounding of the output), and to the oracle, at every width and at the edges of its tiles, chunks and rules."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import dev, host
+from paper_2306_06446_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,E,hid", [
+    (1, 64, 256), (65, 64, 512), (3300, 64, 1536), (40000, 64, 384),            # 64 rows, two workgroups to a CU
+    (1, 128, 256), (129, 128, 768), (16385, 128, 640),                          # 64 and 128 rows
+    (63, 192, 384), (7681, 192, 768), (16400, 192, 256),
+    (31, 256, 384), (10240, 256, 512), (16513, 256, 1024),
+])
+def test_one_launch_equals_the_two_layers(sa, rows, E, hid):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + E + hid)
+    T = rows + 37
+    xq = torch.randint(-127, 128, (T, E), generator=g, device="cuda", dtype=torch.int8)
+    w1, w2 = (torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8) for s in ((hid, E // 2), (E, hid // 2)))
+    lut = torch.randint(-128, 128, (256,), generator=g, device="cuda", dtype=torch.int8)
+    rq, out_scale = 127.0 / (4 * 40 * 73 * E ** 0.5), 1e-3
+    perm = torch.randperm(T, generator=g, device="cuda").to(torch.int32)
+    counts = torch.tensor([T - rows, rows], dtype=torch.int32, device="cuda")
+    gate = torch.rand(T, generator=g, device="cuda")
+    ws = torch.empty(T * hid + 4 * E * hid + 4096, dtype=torch.uint8, device="cuda")
+    p1, p2 = sa.sa_shift_planes_prepare(w1), sa.sa_shift_planes_prepare(w2)
+    old = torch.randn((T, E), generator=g, device="cuda")
+
+    def go(stages, weights, variant, **kw):
+        y = old.clone()
+        for s in stages:
+            sa.sa_shift_mlp(xq, *weights, rq, lut, want_y2=False, y=y, out_scale=out_scale, variant=variant, stages=s, workspace=ws, **kw)
+        return y
+    picked = dict(rows=perm, counts=counts, expert=1, max_rows=T, gate=gate)
+    for flag in (0, 4):                                     # 4: SA_MLP_ACCUMULATE
+        for kw in ({}, picked):
+            ref = go((1, 2 | flag), (p1, p2), 3, **kw)
+            assert torch.equal(go((3 | flag,), (p1, p2), 3, **kw), ref)
+            assert torch.equal(go((3 | flag,), (w1, w2), 1, **kw), ref)
+    n = min(rows, 96)                                       # the oracle on the last rows, ungated
+    ref = oracle.shift_mlp(host(xq[-n:]), host(w1), host(w2), rq, host(lut))
+    got = host(go((3,), (p1, p2), 3)[-n:])
+    assert np.array_equal(got, np.float32(out_scale) * np.asarray(ref).astype(np.float32))
