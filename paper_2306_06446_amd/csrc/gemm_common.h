@@ -45,20 +45,24 @@ __device__ inline int8_t requant_code(float t) {
     return (t != t) ? (int8_t)0 : (int8_t)t;
 }
 
-// The same code for an int32 accumulator and a finite scale, as the table index code + 128 (1..255),
-// in five vector operations: clamp first (a finite product never is NaN), then add 1.5 * 2^23 + 128,
-// which rounds to nearest even at unit spacing and leaves the index in the low byte of the sum.
-// The host passes a finite scale (requant_scale_finite): the results are those of requant_code.
-__device__ inline uint32_t requant_index(int32_t acc, float rq_finite) {
-    const float t = __builtin_amdgcn_fmed3f((float)acc * rq_finite, -127.0f, 127.0f);
-    return __builtin_bit_cast(uint32_t, t + 12583040.0f) & 0xFFu;
+// rne(x) + 128 as an unsigned integer, for -127 <= x <= 127, in one operation: among the denormal floats, whose bits are their
+// multiple of 2^-149, the fused multiply-add rounds to nearest even at the spacing of the integers.  (Adding 1.5 * 2^23 + 128
+// does so too, but then the bits above the low byte have to be masked off.)
+__device__ inline uint32_t round_index(float x) {
+    return __builtin_bit_cast(uint32_t, __builtin_fmaf(x, 0x1p-149f, 0x1p-142f));
 }
 
-// requant_code as the byte of the int8 code, for a float that may be anything: clamp + magic add (three vector
-// operations) and one select for NaN (a median with a NaN operand is not 0).
+// The same code for an int32 accumulator and a finite scale, as the table index code + 128 (1..255), in four vector operations
+// (clamped first: a finite product never is NaN).  The host passes a finite scale (requant_scale_finite): the results are those
+// of requant_code.
+__device__ inline uint32_t requant_index(int32_t acc, float rq_finite) {
+    return round_index(__builtin_amdgcn_fmed3f((float)acc * rq_finite, -127.0f, 127.0f));
+}
+
+// requant_code as the byte of the int8 code, for a float that may be anything: clamp, round, and one select for NaN (a median
+// with a NaN operand is not 0).
 __device__ inline uint32_t requant_byte(float t) {
-    const float c = __builtin_amdgcn_fmed3f(t, -127.0f, 127.0f);
-    const uint32_t idx = __builtin_bit_cast(uint32_t, c + 12583040.0f) & 0xFFu;     // code + 128
+    const uint32_t idx = round_index(__builtin_amdgcn_fmed3f(t, -127.0f, 127.0f));     // code + 128
     return (t != t) ? 0u : (idx ^ 0x80u);
 }
 

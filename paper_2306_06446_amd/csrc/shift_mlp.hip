@@ -38,9 +38,10 @@ struct MlpShape {
     static constexpr int PLANE = kHidChunk * E;              // W1: 128 rows of E bytes; W2: E rows of 128 bytes
     static constexpr int STAGE = PS * PLANE, RING = 3, LOADS = PS * NE;
     static constexpr int PITCH = 64 * NE + 16;               // a staged output row of a wavefront's columns
-    static constexpr int H = RING * STAGE, H_BYTES = BM * kHidChunk, TABLE = H + 2 * H_BYTES, SIDE = TABLE + 256;
+    // (the table first: its offset is part of the instructions that read it)
+    static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk, SIDE = H + 2 * H_BYTES;
     static constexpr int LDS_BYTES = SIDE + OutSide<Store, BM>::BYTES;
-    static_assert(kMlpWaves * 16 * PITCH <= H, "output staging reuses the ring");
+    static_assert(kMlpWaves * 16 * PITCH <= RING * STAGE, "output staging reuses the ring");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
 };
 
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
         for (int p = 0; p < PS; ++p) {
             const size_t plane = (size_t)(sub * PS + p) * hid * E;
-            const uint32_t at = lds_base + slot * S::STAGE + p * S::PLANE + wave * NE * 1024;
+            const uint32_t at = lds_base + S::STAGES + slot * S::STAGE + p * S::PLANE + wave * NE * 1024;
             if (second) {
                 const int8_t *base = w2 + plane + (size_t)c * kHidChunk + (size_t)(wave * NE * 8) * hid;
 #pragma unroll
@@ -136,20 +137,24 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
         for (int t = 0; t < NE; ++t) acc2[i][t] = v4i{0, 0, 0, 0};
 
-    // Operands are read one step of 64 k ahead of their products.  fb: weights, fa: hidden rows.
-    uint4 fb[2][NE < 2 ? 2 : NE], fa[MI];
-    auto read1 = [&](int par, int p, int k) {
+    // Operands are read one step ahead of their products.  A step is 64 k, in layer 1 of E = 128 and 256 two of them:
+    // the products of one do not cover the latency of the LDS.  fb: weights, fa: hidden rows.
+    constexpr int KS = NE % 2 == 0 ? 2 : 1;
+    uint4 fb[2][4], fa[MI];
+    auto read1 = [&](int par, int n) {                       // step n of a stage
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int r = wc * 32 + 16 * t + fr;
-            fb[par][t] = *reinterpret_cast<const uint4 *>(lds + slot * S::STAGE + p * S::PLANE + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
-        }
+        for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int p = (n * KS + q) / NE, k = (n * KS + q) % NE, r = wc * 32 + 16 * t + fr;
+                fb[par][2 * q + t] = *reinterpret_cast<const uint4 *>(lds + S::STAGES + slot * S::STAGE + p * S::PLANE + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+            }
     };
     auto read2 = [&](int par, int p, int k) {
 #pragma unroll
         for (int t = 0; t < NE; ++t) {
             const int r = wc * 16 * NE + 16 * t + fr;
-            fb[par][t] = *reinterpret_cast<const uint4 *>(lds + slot * S::STAGE + p * S::PLANE + r * kHidChunk + swizzle_128(r, 4 * k + fg) * 16);
+            fb[par][t] = *reinterpret_cast<const uint4 *>(lds + S::STAGES + slot * S::STAGE + p * S::PLANE + r * kHidChunk + swizzle_128(r, 4 * k + fg) * 16);
         }
     };
     auto read_hidden = [&](int i, int k, int buf) {
@@ -169,30 +174,33 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     enum { kNone, kLayer1, kLayer2 };
     auto first_of = [&](auto next_c) {              // the first operands of what comes next
         constexpr int next = decltype(next_c)::value;
-        if constexpr (next == kLayer1) read1(0, 0, 0);
+        if constexpr (next == kLayer1) read1(0, 0);
         if constexpr (next == kLayer2) read2(0, 0, 0);
     };
 
     // Products are computed transposed (weights down, rows across): a lane holds four consecutive columns of row lane % 16.
     // buf: the hidden rows that a layer 2 behind this one reads.
     auto layer1 = [&](auto next_c, int buf) {
-        constexpr int STEPS = PS * NE;                       // of a stage
-        static_for<SPG * STEPS>([&](auto n_c) {
+        constexpr int STEPS = PS * NE / KS, ALL = SPG * STEPS;        // of a stage, of the layer
+        static_for<ALL>([&](auto n_c) {
             constexpr int n = decltype(n_c)::value, m = n + 1;
+            static_assert(ALL % 2 == 0, "what comes next starts with buffer 0");
             if constexpr (m % STEPS != 0) {
-                read1(m & 1, m % STEPS / NE, m % NE);
+                read1(m & 1, m % STEPS);
             } else {
                 hand_over();
-                if constexpr (m < SPG * STEPS) read1(m & 1, 0, 0);
+                if constexpr (m < ALL) read1(m & 1, 0);
                 else first_of(next_c);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
-                if (m == SPG * STEPS && decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf);
+                if (m == ALL && decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf);
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
-                    acc1[i][t] = mma16(fb[n & 1][t], xf[i][n % NE], n == 0 ? v4i{0, 0, 0, 0} : acc1[i][t]);
+                for (int q = 0; q < KS; ++q)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc1[i][t] = mma16(fb[n & 1][2 * q + t], xf[i][(n * KS + q) % NE], n == 0 && q == 0 ? v4i{0, 0, 0, 0} : acc1[i][t]);
             }
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -212,7 +220,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     auto layer2 = [&](int buf, auto requant_c, auto next_c) {
         constexpr bool REQUANT = decltype(requant_c)::value;
         constexpr int STEPS = PS * 2;
-        uint32_t v[4];
+        uint32_t v[2][4];
         static_for<4>([&](auto n_c) {
             constexpr int n = decltype(n_c)::value, m = n + 1;
             if constexpr (m % STEPS != 0) {
@@ -230,10 +238,18 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
                 if constexpr (m < 4) read_hidden(i, m % 2, buf);
                 else if constexpr (decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf ^ 1);
                 if constexpr (REQUANT) {
-                    // two tiles in three places of the first three steps
-                    const int at = n * MI + i, tile = at / 3 * 2 + at % 3;
-                    if (n < 3 && at % 3 != 0) keep((tile - 1) / 2, (tile - 1) % 2, v, buf ^ 1);
-                    if (n < 3 && at % 3 != 2) lookup(tile / 2, tile % 2, v);
+                    const int at = n * MI + i;               // the table's answers are used two places after they are asked for
+                    if (at >= 2 && at - 2 < 2 * MI) keep((at - 2) / 2, at % 2, v[at & 1], buf ^ 1);
+                    if (at < 2 * MI) lookup(at / 2, at % 2, v[at & 1]);
+                }
+            }
+            if constexpr (REQUANT && n < 3) {                // what a product's shadow holds behind each
+#pragma unroll
+                for (int q = 0; q < MI * NE; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 16 / NE, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -243,7 +259,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     using Layer2 = std::integral_constant<int, kLayer2>;
     using None = std::integral_constant<int, kNone>;
 
-    read1(0, 0, 0);
+    read1(0, 0);
     layer1(Layer1{}, 0);
     {
         uint32_t v[4];
@@ -263,7 +279,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 
     // ---- rows out, 16 of the wavefront's columns at a time, through LDS of its own
     __syncthreads();                                         // the ring has been read
-    uint8_t *slab = lds + wave * 16 * S::PITCH;
+    uint8_t *slab = lds + S::STAGES + wave * 16 * S::PITCH;
     auto place = [&](int j, int &row, int &col) {            // chunk j of this lane: row of 16, first column
         const int q = j * 64 + lane;
         row = q / (4 * NE);
