@@ -29,6 +29,7 @@
 
 #include "common.h"
 #include "gemm_common.h"
+#include "side_work.h"
 
 namespace sa {
 
@@ -51,16 +52,23 @@ struct I8Traits {
     typedef v16i_t Acc;
     static constexpr int kPlanes = 2;
     static constexpr int kElemBytes = 1;
+    static constexpr bool kPacked = false;
     __device__ static inline Acc mma(const uint4 &a, const uint4 &b, Acc c) {
         return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(v4i_t, a), __builtin_bit_cast(v4i_t, b), c,
                                                      0, 0, 0);
     }
 };
 
+// The same products on packed 4-bit weights: a stage of B is decoded into its two planes on the way into LDS.
+struct I8PackedTraits : I8Traits {
+    static constexpr bool kPacked = true;
+};
+
 struct F16Traits {
     typedef v16f_t Acc;
     static constexpr int kPlanes = 1;
     static constexpr int kElemBytes = 2;
+    static constexpr bool kPacked = false;
     __device__ static inline Acc mma(const uint4 &a, const uint4 &b, Acc c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h_t, a), __builtin_bit_cast(v8h_t, b), c,
                                                       0, 0, 0);
@@ -70,7 +78,7 @@ struct F16Traits {
 // What the kernel needs to know about its operands.
 struct GemmArgs {
     const void *a;          // [rows, K] elements, row-major
-    const void *b[2];       // planes, each [N, K] elements, row-major
+    const void *b[2];       // planes, each [N, K] elements, row-major (kPacked: b[0] alone, [N, K / 2] bytes)
     RowSel sel;             // which rows of A / of the scattered output
     bool gather_a;          // A rows are sel.rows[m] (else compact m)
     int K, N;               // K: extent of the contraction, a whole number of 64-byte stages; row length of the B planes
@@ -247,7 +255,8 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     constexpr int A_INSTR = BM / ROWS_PER_INSTR / 4;    // loads per wavefront and stage
     constexpr int B_INSTR = BN / ROWS_PER_INSTR / 4;
     constexpr int ES = Store::kBytes;
-    constexpr int LOADS = A_INSTR + NP * B_INSTR;       // direct loads per wavefront and stage
+    constexpr bool PACKED = T::kPacked;
+    constexpr int LOADS = A_INSTR + (PACKED ? 0 : NP * B_INSTR);       // direct loads per wavefront and stage
     // Narrow outputs and sign codes: the MFMAs compute the transposed tile (B rows down, A rows across), so that a lane
     // ends up with four consecutive columns of a row: a quarter of the LDS writes on the way out.  With int8 operands
     // the chip then holds about 4 % less of its rate under full load, so 32-bit outputs are computed upright.
@@ -306,9 +315,36 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
         const int c = swizzle<kChunksPerRow>(r, lane % kChunksPerRow);
         const int n = min(n0 + r, N - 1);
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
+        for (int p = 0; p < (PACKED ? 0 : NP); ++p)
             b_src[p][i] = static_cast<const uint8_t *>(g.b[p]) + (size_t)n * row_bytes + c * 16;
     }
+
+    // Packed weights: a thread takes PB bytes of a stage's row, 16 weights per 8 of them: a chunk of either plane.  The bytes of
+    // two stages are loaded at once (a row's 64 bytes: half a line, and its other half next time), one stage before the first
+    // of them is due.
+    constexpr int PB = BN / 8, PPR = 32 / PB;           // bytes of a thread and stage, threads of a row
+    static_assert(!PACKED || (SB == 64 && NS == 2 && (PB == 8 || PB == 16)), "packed stages");
+    typedef typename std::conditional<PB == 16, uint4, uint2>::type packed_t;
+    packed_t packed0, packed1;                          // of an even and the odd stage behind it
+    const int p_row = tid / PPR, p_chunk = tid % PPR * (PB / 8);
+    const uint8_t *p_src = static_cast<const uint8_t *>(g.b[0]) + (size_t)min(n0 + p_row, N - 1) * (row_bytes / 2) + tid % PPR * PB;
+    auto load_packed = [&](int s) {                     // of stages s (even) and s + 1
+        packed0 = *reinterpret_cast<const packed_t *>(p_src + s * 32);
+        packed1 = *reinterpret_cast<const packed_t *>(p_src + min(s + 1, (int)(row_bytes / 64) - 1) * 32);
+    };
+    // chunk c of a thread's PB / 8, into both planes of a stage
+    auto unpack = [&](packed_t w, int c, int slot) {
+        uint32_t x0 = w.x, x1 = w.y, a[4], b[4];
+        if constexpr (PB == 16) {
+            x0 = c == 0 ? w.x : w.z;
+            x1 = c == 0 ? w.y : w.w;
+        }
+        decode8(x0, a, b);
+        decode8(x1, a + 2, b + 2);
+        uint8_t *at = lds + slot * STAGE + A_BYTES + p_row * kStageBytes + swizzle<kChunksPerRow>(p_row, p_chunk + c) * 16;
+        *reinterpret_cast<uint4 *>(at) = make_uint4(a[0], a[1], a[2], a[3]);
+        *reinterpret_cast<uint4 *>(at + B_BYTES) = make_uint4(b[0], b[1], b[2], b[3]);
+    };
 
     const OutSide<Store, BM> side{store, rows, m0, n_rows, lds + S::SIDE_AT};
 
@@ -359,6 +395,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     // of the stage at byte kbyte are issued into ring slot `slot`, evenly spaced between the MFMAs:
     // a wavefront that issues its loads back to back stalls on the full vector-memory queue
     // (about 1 KiB per 16 cycles and CU) and leaves its matrix core idle meanwhile.
+    const int n_stages = (int)(row_bytes / kStageBytes);
     constexpr int MFMAS = NP * MI * NJ;
     constexpr int LPS = (LOADS + LS - 1) / LS;          // loads per step
     auto multiply = [&](const uint4 (&af)[MI], const uint4 (&bf)[NP][NJ], auto phase_c, auto more_c, bool more, int slot, int kbyte) {
@@ -385,6 +422,19 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            // packed weights: the stage whose first loads these are is unpacked, a chunk behind every other MFMA
+            if constexpr (PACKED && phase == 0 && MORE != 0) {
+                constexpr int CHUNKS = PB / 8, c0 = m * CHUNKS / MFMAS, c1 = (m + 1) * CHUNKS / MFMAS;
+                const bool odd = (kbyte / kStageBytes) & 1;
+                if constexpr (c1 > c0)
+                    if (MORE == 1 || more) {
+                        packed_t w = packed0;
+                        if (odd) w = packed1;
+                        unpack(w, c0, slot);
+                    }
+                if constexpr (m == MFMAS - 1)
+                    if (odd && kbyte / kStageBytes + 1 < n_stages && (MORE == 1 || more)) load_packed(kbyte / kStageBytes + 1);
+            }
         });
     };
 
@@ -396,12 +446,20 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     // first LS-1 steps of stage s+1; the first fragments of stage s+1 are read under the MFMAs
     // of the last step.
     static_assert(LS >= 1 && LS <= KK, "loads of a stage are spread over at most one stage of steps");
-    const int n_stages = (int)(row_bytes / kStageBytes);
     uint4 af[2][MI], bf[2][NP][NJ];
     if constexpr (!S::SIDE_LATE) side.fetch_rows(wave, lane);
 #pragma unroll
     for (int q = 0; q < NS; ++q)
         if (q < n_stages) issue_stage(q, q * kStageBytes);
+    if constexpr (PACKED) {
+        load_packed(0);
+#pragma unroll
+        for (int c = 0; c < PB / 8; ++c) {
+            unpack(packed0, c, 0);
+            if (n_stages > 1) unpack(packed1, c, 1);
+        }
+        if (n_stages > 2) load_packed(2);
+    }
     // Wait until all but the `later` most recently issued stages of this wavefront's loads have landed.
     auto wait_all_but = [&](int later) {
         if (NS >= 4 && later >= 3)
@@ -606,7 +664,7 @@ struct NtTile {
     // the A rows streaming through it.  (Fewer groups fetch fewer bytes when A is the larger operand,
     // but a B share that is evicted between row tiles costs more time than the extra A traffic.)
     static int col_groups(const GemmArgs &g) {
-        const size_t b_bytes = (size_t)T::kPlanes * g.N * g.K * T::kElemBytes;
+        const size_t b_bytes = T::kPacked ? (size_t)g.N * g.K / 2 : (size_t)T::kPlanes * g.N * g.K * T::kElemBytes;
         int cg = 1;
         while (cg < 8 && b_bytes / cg > (size_t)(5 << 19)) cg *= 2;     // 2.5 MiB
         return cg;
@@ -709,6 +767,36 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
         if (lines && row_bytes > 768) return launch_tile<NtTile<T, 192, 128, 128, 2, 2>, 1>(g, store, st, what);
         return launch_tile<NtTile<T, 128, 128, 64, 3, 1>, 2>(g, store, st, what);
     }
+}
+
+// The same on packed weights, without the launch that decodes them (3 to 5 us): whether that is faster for max_rows rows (as
+// launch_gemm estimates them), and the launch.  A stage's weights come in as 32 bytes of a row instead of 128, which in the
+// K loop pays for their decoding; of the tiles those that leave registers for it:
+//  * 192 x 128, two per CU, for rows of 768 bytes and more once they make one and a half tiles per CU (12608 x 768 <- 3072,
+//    decode + planes against packed: 70 -> 66 us; 12608 x 768 <- 768 26.4 -> 22.6, with 128 x 64 24.7);
+//  * 128 x 64, three per CU (12608 x 1536 <- 384 33.5 -> 27.1, with 192 x 128 31.5; 12608 x 384 <- 1536 27.9 -> 24.1;
+//    100000 x 256 <- 64 27 -> 20.5; 3000 x 1024 <- 1024 16 -> 13.5);
+//  * where gemm_slice.h would take the planes, 64 x 64 for rows up to 1024 bytes (1379 x 3072 <- 768 22 -> 15; 965 x 768 <-
+//    3072 18 -> 21.6: those stay).
+// Beyond 2^35 multiply-adds the decode is no longer worth its removal (65000 x 3072 <- 768 333 against 346, 131072 x 256 <- 1024
+// 86 against 89).
+inline bool packed_gemm(long max_rows, bool counted, int N, int K) {
+    const long m_est = counted ? (max_rows + 1) / 2 : max_rows;
+    if (K % 64 != 0 || (double)m_est * N * K > 34359738368.0) return false;
+    return ((m_est + 63) / 64) * ((N + 63) / 64) > 640 || K <= 1024;
+}
+
+template <class Store>
+int launch_gemm_packed(const GemmArgs &g, const Store &store, hipStream_t st, const char *what) {
+    typedef I8PackedTraits T;
+    if (g.sel.max_rows == 0 || g.N == 0) return SA_OK;
+    SA_REQUIRE(g.K % 64 == 0 && g.K > 0 && (Store::kBytes == 4 || (size_t)g.N * Store::kBytes % 16 == 0), SA_ERR_SHAPE,
+               "%s: rows of %d and outputs of %d", what, g.K, g.N);
+    const long m_est = g.sel.counts ? (g.sel.max_rows + 1) / 2 : g.sel.max_rows;
+    auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+    if (tiles(64, 64) <= 640) return launch_tile<NtTile<T, 64, 64, 64, 2, 1>, 4>(g, store, st, what);
+    if (g.K >= 768 && tiles(192, 128) >= 384) return launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
+    return launch_tile<NtTile<T, 128, 64, 64, 2, 1>, 3>(g, store, st, what);
 }
 
 }  // namespace sa

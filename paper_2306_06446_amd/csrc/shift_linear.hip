@@ -185,6 +185,17 @@ int launch_shift(int variant, const int8_t *x, const uint8_t *w4, const RowSel &
         SA_REQUIRE(K % kMfmaK == 0, SA_ERR_SHAPE, "shift layer: the MFMA variant needs K %% 32 == 0 (K = %d)", K);
         const int Kp = padded_k(K);
         const int8_t *pa, *pb;
+        if (variant == SA_VARIANT_MFMA && !decoded && packed_gemm(sel.max_rows, sel.counts != nullptr, N, K)) {
+            GemmArgs g;
+            g.a = x;
+            g.b[0] = w4;
+            g.sel = sel;
+            g.gather_a = gather;
+            g.K = K;
+            g.N = N;
+            ShiftStore<MODE> store(epi);
+            return launch_gemm_packed(g, store, st, "shift layer (MFMA, packed weights)");
+        }
         if (variant == SA_VARIANT_MFMA_PREPARED) {
             pa = reinterpret_cast<const int8_t *>(w4);      // the caller decoded the weights beforehand
         } else {
@@ -561,9 +572,12 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
     uint8_t *planes1 = static_cast<uint8_t *>(workspace) + (((size_t)sel.max_rows * hid) + 255) / 256 * 256;
     uint8_t *planes2 = planes1 + planes_bytes(E, hid);
 
-    // both layers in this call on the matrix cores: their 4-bit weights are decoded by one launch
+    // both layers in this call on the matrix cores: their 4-bit weights are decoded by one launch, unless both take them packed
     const int v_eff = variant == SA_VARIANT_AUTO ? SA_VARIANT_MFMA : variant;      // E and hid are multiples of 64
-    const bool pair = v_eff == SA_VARIANT_MFMA && (stages & 3) == 3;
+    const bool one_launch = (stages & 3) == 3 && v_eff != SA_VARIANT_VALU && y_or_null && !y2_or_null && sa::shift_mlp_one_launch(sel, E, hid);
+    const bool packed1 = sa::packed_gemm(sel.max_rows, sel.counts != nullptr, hid, E);
+    const bool packed2 = sa::packed_gemm(sel.max_rows, sel.counts != nullptr, E, hid);
+    const bool pair = v_eff == SA_VARIANT_MFMA && (stages & 3) == 3 && (one_launch || !packed1 || !packed2);
     if (pair) {
         sa::DecodeWork w;
         sa::add_decode(&w, w1, E, hid, planes1);
@@ -571,7 +585,7 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
         rc = launch_decode(w, st);
         if (rc != SA_OK) return rc;
     }
-    if ((stages & 3) == 3 && v_eff != SA_VARIANT_VALU && y_or_null && !y2_or_null && sa::shift_mlp_one_launch(sel, E, hid)) {
+    if (one_launch) {
         sa::Epilogue e;
         e.yf = y_or_null;
         e.gate = gate_or_null;
@@ -602,7 +616,7 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
         e3.gate = gate_or_null;
         e3.out_scale = out_scale;
         e3.accumulate = (stages & SA_MLP_ACCUMULATE) != 0;
-        rc = launch_shift<sa::kEpiScatterI32>(variant, hbuf, w2, sel, false, hid, E, e3, planes2, st, pair || y2_or_null != nullptr);
+        rc = launch_shift<sa::kEpiScatterI32>(variant, hbuf, w2, sel, false, hid, E, e3, planes2, st, pair || (y2_or_null != nullptr && !packed2));
         if (rc != SA_OK) return rc;
     }
     return SA_OK;
