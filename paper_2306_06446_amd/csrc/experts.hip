@@ -45,7 +45,9 @@ int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, 
 // both experts together; beyond, from a sweep over routings of 30 / 50 / 70 % (12608 tokens unless said, one launch for both
 // experts against one each):
 //    768 -> 3072  256 x 128 and 192 x 128   112 / 109 / 105 us (128 x 128: 126 / 123 / 116; apart 131 / 130 / 112)
-//   3072 ->  768  192 x 128 both             82 /  81 /  77 us (128 x 128:  97 /  94 /  86; apart 121 / 120 /  88)
+//   3072 ->  768  192 x 128 both             82 /  81 /  77 us (128 x 128:  97 /  94 /  86; apart 121 / 120 /  88).  Of the Mult
+//                 tiles 120 then shared a CU with a Shift tile each and were done 20 us after it: as 128 x 128, with a ring of four
+//                 short stages, the whole block 215 -> 210 us, the layer 345 -> 338
 //    768 ->  768  128 x 128 both             34 /  35 /  33 us (192 x 128:  34 /  34 /  34; apart  49 /  47 /  49)
 //    384 -> 1536                128 x 128 both  44 / 41 / 42 us    (192 x 128:  46 /  46 /  47; apart  64 /  66 /  55)
 //   1536 ->  384, 384 -> 384    128 x 64 and 64 x 128   33 and 16 us   (128 x 128: 35 and 20; apart 48 and 35)
@@ -71,7 +73,7 @@ int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const 
     if (lines_s && lines_m && tiles(256, 128) > 1024)
         return launch_pair_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
     if (lines_s && lines_m && gs.K >= 2048)
-        return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
+        return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 4, 1>, 2>(gs, ss, gm, sm, st, what);
     // not half of the chip's 768 places: finer tiles
     if (lines_m && tiles(128, 128) <= 384)
         return launch_pair_tiles<NtTile<I, 128, 64, 64, 3, 1>, NtTile<F, 64, 128, 128, 2, 2>, 3>(gs, ss, gm, sm, st, what);
