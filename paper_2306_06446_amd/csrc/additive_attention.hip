@@ -172,60 +172,87 @@ __global__ __launch_bounds__(256) void den_kernel(const uint64_t *__restrict__ q
     den[(size_t)bh * Nq + n] = d;
 }
 
-// Depthwise 3x3 over the token grid, zero padding; thread <-> four channels of one token, a few items per
-// thread.  The weights pass through LDS transposed to [tap][channel] so that a lane reads its four channels' weights
-// of a tap as one 16-byte word (their [channel][tap] layout in memory would make every lane touch another line).
-constexpr int kDwMaxItems = 8;
-constexpr int kDwMaxLdsE = 1024;      // 36 KB of weights in LDS; wider layers read them from memory
-
+// Depthwise 3x3 over the token grid, zero padding.
+// A thread computes RY outputs of one column of the token grid, one below the other, for four channels: 3 (RY + 2) neighbours
+// instead of 9 RY, all of them asked for before the first is used, the channels' weights in registers.  Lanes run along the
+// channels and then the grid, so that every load is whole lines.  The taps of an output are added in their order, those outside
+// the grid left out.  i: 4-channel columns of (image, strip of RY rows, x), 32-bit with divisions by multiplication (SMALL), as
+// 64-bit divisions took longer than the loads: 32 images of 56 x 56 x 32 15.1 -> 10.4 us with them gone and RY = 4, where the
+// bytes (v, and out read and written) take 8.
+template <int RY, bool SMALL>
 __global__ __launch_bounds__(256) void dwconv3x3_kernel(const float *__restrict__ v, const float *__restrict__ w,
-                                                        const float *__restrict__ bias, float *__restrict__ out,
-                                                        int accumulate, long n_tokens, int gh, int gw, int E4,
-                                                        int items) {
-    extern __shared__ float w_s[];                   // [9][E], or unused when E is too wide
-    const int E = E4 * 4;
-    const bool staged = E <= kDwMaxLdsE;
-    if (staged) {
-        for (int i = threadIdx.x; i < 9 * E; i += blockDim.x) w_s[(i % 9) * E + i / 9] = w[i];
-        __syncthreads();
+                                                        const float *__restrict__ bias, float *__restrict__ out, int accumulate,
+                                                        long total, int gh, int gw, int E4, int strips, sa::FastDiv by_e4,
+                                                        sa::FastDiv by_gw, sa::FastDiv by_strips) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    int c4, x, y0;
+    long b;
+    if constexpr (SMALL) {
+        const uint32_t r = by_e4((uint32_t)i), s = by_gw(r), bb = by_strips(s);
+        c4 = (int)((uint32_t)i - r * (uint32_t)E4);
+        x = (int)(r - s * (uint32_t)gw);
+        y0 = (int)(s - bb * (uint32_t)strips) * RY;
+        b = bb;
+    } else {
+        const long r = i / E4, s = r / gw;
+        c4 = (int)(i - r * E4);
+        x = (int)(r - s * gw);
+        b = s / strips;
+        y0 = (int)(s - b * strips) * RY;
     }
-    const long total = n_tokens * E4;
-    for (int it = 0; it < items; ++it) {
-        const long i = ((long)blockIdx.x * items + it) * blockDim.x + threadIdx.x;
-        if (i >= total) return;
-        const int c4 = (int)(i % E4);
-        const long tok = i / E4;
-        const int x = (int)(tok % gw), y = (int)((tok / gw) % gh);
-        const int c = c4 * 4;
-        float acc[4];
+    const size_t E = (size_t)E4 * 4, row = (size_t)gw * E;
+    const int c = c4 * 4;
+    const float *vc = v + ((size_t)b * gh * gw + x) * E + c;          // row 0 of this column
+    float *oc = out + ((size_t)b * gh * gw + x) * E + c;
+    const bool left = x > 0, right = x + 1 < gw;
+
+    float wt[4][9];                                                    // [channel][tap]
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = bias ? bias[c + q] : 0.0f;
+    for (int q = 0; q < 9; ++q) {
+        const float4 t = *reinterpret_cast<const float4 *>(w + (size_t)c * 9 + 4 * q);
+        const float tv[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-        for (int dy = -1; dy <= 1; ++dy)
+        for (int e = 0; e < 4; ++e) wt[(4 * q + e) / 9][(4 * q + e) % 9] = tv[e];
+    }
+    // (rows and columns outside the grid are read at its edge and not used)
+    float4 n[RY + 2][3];
 #pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int yy = y + dy, xx = x + dx;
-                if (yy < 0 || yy >= gh || xx < 0 || xx >= gw) continue;
-                const float4 nv = *reinterpret_cast<const float4 *>(v + (size_t)(tok + (long)dy * gw + dx) * E + c);
-                const int t = (dy + 1) * 3 + (dx + 1);
-                float4 wt;
-                if (staged)
-                    wt = *reinterpret_cast<const float4 *>(w_s + t * E + c);
-                else
-                    wt = make_float4(w[(size_t)(c + 0) * 9 + t], w[(size_t)(c + 1) * 9 + t], w[(size_t)(c + 2) * 9 + t],
-                                     w[(size_t)(c + 3) * 9 + t]);
-                acc[0] = __builtin_fmaf(wt.x, nv.x, acc[0]);
-                acc[1] = __builtin_fmaf(wt.y, nv.y, acc[1]);
-                acc[2] = __builtin_fmaf(wt.z, nv.z, acc[2]);
-                acc[3] = __builtin_fmaf(wt.w, nv.w, acc[3]);
+    for (int r = 0; r < RY + 2; ++r) {
+        const float *p = vc + (size_t)min(max(y0 + r - 1, 0), gh - 1) * row;
+        n[r][0] = *reinterpret_cast<const float4 *>(p - (left ? E : 0));
+        n[r][1] = *reinterpret_cast<const float4 *>(p);
+        n[r][2] = *reinterpret_cast<const float4 *>(p + (right ? E : 0));
+    }
+    float4 old[RY];
+    if (accumulate) {
+#pragma unroll
+        for (int r = 0; r < RY; ++r) old[r] = *reinterpret_cast<const float4 *>(oc + (size_t)min(y0 + r, gh - 1) * row);
+    }
+    float start[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) start[q] = bias ? bias[c + q] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        if (y0 + r >= gh) break;
+        float acc[4] = {start[0], start[1], start[2], start[3]};
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const int dy = t / 3 - 1, dx = t % 3 - 1;
+            const float4 nv = n[r + 1 + dy][dx + 1];
+            const bool in = (dy == 0 || (dy < 0 ? y0 + r > 0 : y0 + r + 1 < gh)) && (dx == 0 || (dx < 0 ? left : right));
+            const float x4[4] = {nv.x, nv.y, nv.z, nv.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float sum = __builtin_fmaf(wt[q][t], x4[q], acc[q]);
+                acc[q] = in ? sum : acc[q];
             }
-        float4 *o = reinterpret_cast<float4 *>(out + (size_t)tok * E + c);
-        float4 r = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        if (accumulate) {
-            const float4 old = *o;
-            r.x += old.x; r.y += old.y; r.z += old.z; r.w += old.w;
         }
-        *o = r;
+        float4 o = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        if (accumulate) {
+            o.x += old[r].x; o.y += old[r].y; o.z += old[r].z; o.w += old[r].w;
+        }
+        *reinterpret_cast<float4 *>(oc + (size_t)(y0 + r) * row) = o;
     }
 }
 
@@ -543,15 +570,18 @@ extern "C" int sa_dwconv3x3(const float *v, const float *w, const float *bias_or
     SA_REQUIRE(v != out, SA_ERR_INVALID, "sa_dwconv3x3: out must not be v (neighbours are read after they would be written)");
     SA_REQUIRE(sa::aligned16(v) && sa::aligned16(w) && sa::aligned16(bias_or_null) && sa::aligned16(out), SA_ERR_ALIGN,
                "sa_dwconv3x3: pointers must be 16-byte aligned");
+    // Four outputs of a thread (1.5 loads of a neighbour each instead of 3 and 9) once that still gives every SIMD a wavefront.
     const long n = n_tokens * (E / 4);
-    // several items per thread amortise the staging of the weights, as long as the grid still fills the chip
-    int items = (int)(n / (256L * 2048));
-    items = items < 1 ? 1 : (items > kDwMaxItems ? kDwMaxItems : items);
-    const long per_block = 256L * items;
-    const long blocks = (n + per_block - 1) / per_block;
+    const int ry = n >= 4L * 65536 ? 4 : 1, strips = (gh + ry - 1) / ry;
+    const long total = (long)B * strips * gw * (E / 4), blocks = (total + 255) / 256;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_dwconv3x3: too many elements");
-    const size_t lds = E <= kDwMaxLdsE ? (size_t)9 * E * sizeof(float) : 0;
-    dwconv3x3_kernel<<<dim3((unsigned)blocks), dim3(256), lds, sa::as_stream(stream)>>>(v, w, bias_or_null, out, accumulate,
-                                                                                         n_tokens, gh, gw, E / 4, items);
+    const sa::FastDiv by_e4((uint32_t)(E / 4)), by_gw((uint32_t)gw), by_strips((uint32_t)strips);
+    const bool small = total < (1L << 31);
+    auto go = [&](auto kernel) {
+        kernel<<<dim3((unsigned)blocks), dim3(256), 0, sa::as_stream(stream)>>>(v, w, bias_or_null, out, accumulate, total, gh, gw, E / 4,
+                                                                                strips, by_e4, by_gw, by_strips);
+    };
+    if (ry == 4) small ? go(dwconv3x3_kernel<4, true>) : go(dwconv3x3_kernel<4, false>);
+    else go(dwconv3x3_kernel<1, true>);
     return sa::check_launch("sa_dwconv3x3");
 }

@@ -41,19 +41,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kListCap = 128;                 // unsettled bits parked per wavefront
 
-// n / d for 0 <= n < 2^31 as one multiplication and one shift.
-struct FastDiv {
-    uint32_t mul;
-    int shift;
-    explicit FastDiv(uint32_t d) {
-        int s = 0;
-        while ((1ull << s) < d) ++s;
-        shift = 31 + s;
-        mul = (uint32_t)(((1ull << shift) + d - 1) / d);
-    }
-    __device__ inline uint32_t operator()(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
-};
-
 struct RowMap {
     FastDiv by_h, by_n;
     int N, H, W;

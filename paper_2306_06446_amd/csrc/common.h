@@ -26,6 +26,19 @@ inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s);
 
 constexpr int kWave = 64;
 
+// n / d for 0 <= n < 2^31 as one multiplication and one shift.
+struct FastDiv {
+    uint32_t mul;
+    int shift;
+    explicit FastDiv(uint32_t d) {
+        int s = 0;
+        while ((1ull << s) < d) ++s;
+        shift = 31 + s;
+        mul = (uint32_t)(((1ull << shift) + d - 1) / d);
+    }
+    __device__ inline uint32_t operator()(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
+
 // Resolves an sa_rows descriptor inside a kernel (all lanes get the same values).
 struct RowSel {
     const int32_t *rows;    // may be null: identity
