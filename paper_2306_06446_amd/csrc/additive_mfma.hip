@@ -64,6 +64,12 @@ __device__ inline uint32_t code_pair(uint32_t x, int sh) {
     return ((x << sh) & 0x80008000u) | 0x3F803F80u;
 }
 
+// Where K^T V's row `bit` stands in a column of Q(K^T V)'s planes (its order of K, see there).
+__device__ inline int qkv_place(int bit) {
+    const int r = bit % 16;
+    return (((bit / 32) * 2 + r / 8) * 2 + r / 4 % 2) * 8 + r % 4 * 2 + bit / 16 % 2;
+}
+
 // ------------------------------------------------------------------------------ K^T V ----
 // Workgroup: one (b, h), up to four code words, up to 64 columns, one token range; eight wavefronts.  A wavefront has WB (1 or
 // 2) words and every PH-th 16-token step, and holds that whole [64 WB bits, DVC columns] accumulator.  Its V rows and code
@@ -88,7 +94,8 @@ struct KtvLds {
 // dst is not __restrict__: a kernel that goes on to Q(K^T V) reads the same memory through AddFused::kv_in.
 // ksum (ZO): int32 [splits][BH][nbits], the number of tokens of the range whose code bit is set.
 // block = ((bh * n_groups + group) * n_cols + column group) * splits + split
-template <int DVC, int WB, int PH, int RING, bool ZO>
+// PLANES (one token range, all words in the workgroup): the sums also stay in LDS, as qkv_block stages them.
+template <int DVC, int WB, int PH, int RING, bool ZO, bool PLANES = false>
 __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, const float *__restrict__ v, float *dst,
                                           int32_t *__restrict__ ksum, long BH, int H, int Nk, int W, int DV, int splits,
                                           int tokens_per_block, int block, uint8_t *ring_s) {
@@ -260,6 +267,8 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
     //      With +-1 codes the operand was -1 for a set bit (the code bit as the sign bit), so the sum is negated here.
     const size_t row0 = (((size_t)part * BH + bh) * W + group * GW) * 64;
     const int rows_here = min(GW, W - group * GW) * 64;
+    constexpr int SUMS = PAIRS * TILE / 4, KEEP = (SUMS + kKtvWaves * 64 - 1) / (kKtvWaves * 64);       // 16-byte sums of a tile, of a thread
+    f32x4 sum[TB][KEEP];
 #pragma unroll
     for (int t = 0; t < TB; ++t) {
         if (t > 0) __syncthreads();
@@ -272,7 +281,10 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
                 *at = acc[t][0][r];
         }
         __syncthreads();
-        for (int q = tid; q < PAIRS * TILE / 4; q += kKtvWaves * 64) {
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) {
+            const int q = k * kKtvWaves * 64 + tid;
+            if (q >= SUMS) break;
             const int share = q / (TILE / 4);
             f32x4 a = reinterpret_cast<const f32x4 *>(red_s)[q];
 #pragma unroll
@@ -280,7 +292,32 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
             const int row = share * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
             if (!ZO) a = -a;
             if (row < rows_here) *reinterpret_cast<f32x4 *>(dst + (row0 + row) * DV + c0 + col) = a;
+            sum[t][k] = a;
         }
+    }
+    if constexpr (PLANES) {
+        constexpr int STRIDE = GW * 64 + 8, PLANE = DVC * STRIDE;
+        __syncthreads();                           // every sum has been read
+        uint16_t *kvt = reinterpret_cast<uint16_t *>(ring_s);
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k) {
+                const int q = k * kKtvWaves * 64 + tid;
+                if (q >= SUMS) break;
+                const int bit = q / (TILE / 4) * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
+                uint16_t *at = kvt + col * STRIDE + qkv_place(bit);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t t3[3];
+                    split3_pair(sum[t][k][2 * h], sum[t][k][2 * h + 1], t3);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        at[p * PLANE + 2 * h * STRIDE] = (uint16_t)t3[p];
+                        at[p * PLANE + (2 * h + 1) * STRIDE] = (uint16_t)(t3[p] >> 16);
+                    }
+                }
+            }
     }
     if (ZO && c0 == 0) {
 #pragma unroll
@@ -365,10 +402,24 @@ struct QkvLds {
     static constexpr int BYTES = 3 * PLANE * 2 + (ZO ? W * 64 * 5 * 4 : 0);
 };
 
+// The codes of a wavefront's TM token tiles from tile0 on: this lane's query of each.
+template <int W, int TM>
+__device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes, long bh, int Nq, int tile0, uint64_t (&c)[TM][W]) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+        const int n = min((tile0 + tm) * 32 + (int)(threadIdx.x & 31), Nq - 1);
+        const uint64_t *cp = q_codes + ((size_t)bh * Nq + n) * W;
+#pragma unroll
+        for (int w = 0; w < W; ++w) c[tm][w] = cp[w];
+    }
+}
+
 // block = (bh * column groups + column group) * blocks_per_bh + part
-template <int DVC, int W, int NW, int TM, bool ZO>
+// first: the codes of this wavefront's first tiles, asked for long before they are needed.
+// PLANES: K^T V is in LDS already (ktv_block).
+template <int DVC, int W, int NW, int TM, bool ZO, bool PLANES = false>
 __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, int Nq, int DV, long BH,
-                                          int blocks_per_bh, int tiles_per_block, int block, uint8_t *lds) {
+                                          int blocks_per_bh, int tiles_per_block, int block, uint8_t *lds, uint64_t (&first)[TM][W]) {
     constexpr int JT = DVC / 32;
     constexpr int NBITS = W * 64;
     constexpr int STRIDE = QkvLds<DVC, W, ZO>::STRIDE, PLANE = QkvLds<DVC, W, ZO>::PLANE;
@@ -387,17 +438,28 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
 
     // K^T V -> the three planes: a task is the eight rows of one lane half of a step, one column; with more than one
     // partial they are summed on the way, in ascending order, and the first workgroup of the (b, h) leaves the sum in kv
-    for (int t = tid; t < NBITS / 8 * DVC; t += n_threads) {
+    for (int t = tid; !PLANES && t < NBITS / 8 * DVC; t += n_threads) {
         const int col = t % DVC, grp = t / DVC;                    // grp = (half * 2 + s) * 2 + kg
         const int bit0 = (grp >> 2) * 32 + ((grp >> 1) & 1) * 8 + (grp & 1) * 4;
         const size_t at = ((size_t)bh * NBITS + bit0) * DV + c0 + col;
         float x[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = f.kv_in[at + ((e >> 1) + 16 * (e & 1)) * DV];
-        for (int s = 1; s < f.splits; ++s) {
-            const float *p = f.kv_in + (size_t)s * BH * NBITS * DV + at;
+        // (four partials in flight: one after the other they were as many round trips to memory)
+        const float *p = f.kv_in + at;
+        const size_t split = (size_t)BH * NBITS * DV;
+        for (int s = 1; s < f.splits; s += 4) {
+            float y[4][8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] += p[((e >> 1) + 16 * (e & 1)) * DV];
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[q][e] = p[(size_t)min(s + q, f.splits - 1) * split + ((e >> 1) + 16 * (e & 1)) * DV];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (s + q < f.splits) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] += y[q][e];
+                }
         }
         if (f.kv_out && part == 0) {
 #pragma unroll
@@ -417,8 +479,14 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
     }
     if (ZO) {
         for (int j = tid; j < NBITS; j += n_threads) {
-            int32_t c = f.ksum_in[(size_t)bh * NBITS + j];
-            for (int s = 1; s < f.splits; ++s) c += f.ksum_in[((size_t)s * BH + bh) * NBITS + j];
+            int32_t c = 0;
+            for (int s = 0; s < f.splits; s += 8) {
+                int32_t y[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) y[q] = f.ksum_in[((size_t)min(s + q, f.splits - 1) * BH + bh) * NBITS + j];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) c += s + q < f.splits ? y[q] : 0;
+            }
             ks_s[j] = c;
             if (f.ksum_out && part == 0 && c0 == 0) f.ksum_out[(size_t)bh * NBITS + j] = c;
         }
@@ -438,11 +506,9 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
         float factor[TM];                         // ZO: 1 / (normaliser + eps) of this lane's query
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
-            const int n = min((tile0 + tm) * 32 + m, Nq - 1);
-            const uint64_t *cp = q_codes + ((size_t)bh * Nq + n) * W;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                const uint64_t wd = cp[w];
+                const uint64_t wd = first[tm][w];
                 code[tm][2 * w] = (uint32_t)wd;
                 code[tm][2 * w + 1] = (uint32_t)(wd >> 32);
             }
@@ -461,6 +527,8 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                 code[tm][q] = ZO ? code[tm][q] >> (4 * kg) : code[tm][q] << (4 - 4 * kg);
             }
         }
+        // of the next tiles ({0,1} codes, which have no registers to spare: behind this tile's products)
+        if (!ZO && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, first);
         v16f acc[TM][JT];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
@@ -493,6 +561,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             // keep the steps apart: hoisting every operand read of the tile to the top costs hundreds of registers
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (ZO && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, first);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (tile0 + tm >= tile_end) continue;
@@ -533,12 +602,15 @@ template <int DVC, int W, int NW, int TM, bool ZO>
 __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f, int H, int Nq, int DV,
                                                            long BH, int blocks_per_bh, int tiles_per_block) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[QkvLds<DVC, W, ZO>::BYTES];
-    qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds);
+    uint64_t first[TM][W];
+    const int tile0 = blockIdx.x % blocks_per_bh * tiles_per_block + (threadIdx.x >> 6) * TM;
+    load_codes<W, TM>(q_codes, blockIdx.x / blocks_per_bh / (DV / DVC), Nq, tile0, first);
+    qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds, first);
 }
 
 // ------------------------------------------------------------------- both, short sequences ----
-// One workgroup does K^T V and Q(K^T V) of a (b, h) and DVC columns; what it reads of K^T V it wrote itself (splits = 1), so
-// a barrier is all the order that takes.  Bound by latency for few sequences: 1 x 3 heads x 197 tokens x 64 bits 10.6 us in
+// One workgroup does K^T V and Q(K^T V) of a (b, h) and DVC columns; K^T V goes from its sums to the second product's planes
+// without leaving the CU (it is written for the caller as well).  Bound by latency for few sequences: 1 x 3 heads x 197 tokens x 64 bits 10.6 us in
 // two launches, 7.5 in one; K^T V comes back from the caches it was just written to with many: 64 x 12 x 197 x 128 bits
 // 33.2 -> 29.1, 64 x 3 x 197 x 64 bits 13.7 -> 9.9.
 template <int DVC, int W, int PH, int WB, int RING>
@@ -547,9 +619,11 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t 
                                                                  int H, int Nq, int Nk, int DV, long BH) {
     constexpr int KB = KtvLds<DVC, WB, RING, false>::BYTES, QB = QkvLds<DVC, W, false>::BYTES;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[KB > QB ? KB : QB];
-    ktv_block<DVC, WB, PH, RING, false>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
-    __syncthreads();
-    qkv_block<DVC, W, kKtvWaves, 1, false>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds);
+    static_assert(kKtvWaves / PH * WB == W, "a workgroup has all words");
+    uint64_t first[1][W];
+    load_codes<W, 1>(q_codes, blockIdx.x / (DV / DVC), Nq, threadIdx.x >> 6, first);
+    ktv_block<DVC, WB, PH, RING, false, true>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
+    qkv_block<DVC, W, kKtvWaves, 1, false, true>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds, first);
 }
 
 // How the token tiles of a (b, h) are spread.
