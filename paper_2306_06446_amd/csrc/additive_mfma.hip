@@ -281,7 +281,7 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
                 *at = acc[t][0][r];
         }
         __syncthreads();
-#pragma unroll
+#pragma unroll(PLANES ? KEEP : 1)
         for (int k = 0; k < KEEP; ++k) {
             const int q = k * kKtvWaves * 64 + tid;
             if (q >= SUMS) break;
@@ -292,7 +292,7 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
             const int row = share * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
             if (!ZO) a = -a;
             if (row < rows_here) *reinterpret_cast<f32x4 *>(dst + (row0 + row) * DV + c0 + col) = a;
-            sum[t][k] = a;
+            if constexpr (PLANES) sum[t][k] = a;
         }
     }
     if constexpr (PLANES) {
