@@ -12,20 +12,27 @@
 //
 // A wavefront takes tiles of 32 consecutive rows of the flattened [B*N*H, d] input as two units of 16.  The MFMA
 // (16x16x32) computes the TRANSPOSED tile, hash columns down and rows across; the columns are dealt to its rows so that a
-// lane ends up with a quarter of the code bits of one row, consecutive ones, and its k to the steps so that a lane loads
-// 16-byte pieces which are 64 contiguous bytes per row and instruction.  The hash matrix lives in LDS, as ready-made
+// lane ends up with a quarter of the code bits of one row, consecutive ones.  The hash matrix lives in LDS, as ready-made
 // fragments and as fp32 columns for step 3; the rows of the next tile are in flight while a tile is multiplied.
+//
+// A load instruction takes 32 bytes of each of the 32 rows, so that its first use of a line asks for all rows' lines at
+// once; the operands, which want 64 bytes of 16 rows, are put together by lane swaps after the split.  Loaded as 64 bytes of
+// 16 rows, the attention of 32 x 3136 tokens x 1 head x 32 with 64 bits takes 25.2 us (24.5 now).
+// At 256 columns the rows are loaded as a stream: the products hide most of it, and V, which K^T V reads next, stays in
+// the caches (block of 1 x 16384 tokens x 4 heads 132.4 -> 128.9 us; at 64 columns the wait shows, 24.5 -> 28.4).
+// Products of 32x32x16 took the same time here but more power, which the kernels around it paid for in clock.
 //
 // What bounds it: at 256 bits the products and the vector work in their shadow (16 funnel shifts and 8 three-way minima
 // per 16 bits, 7 operations to split two elements); at 128 bits and fewer the rows of Q and K, with about 4.5 us before the
 // first product (3.5 of them the launch, 1 until the hash matrix has arrived) and 1 us of re-runs at the end.  More
 // wavefronts or rows in flight gave nothing there.  The fragments are made from the registers the hash matrix is loaded
 // into: through LDS, with two more barriers and two passes over its fp32 form, a launch took 0.8 us longer at d = 64 and up
-// to 3.7 at d = 128.  Q and K, before -> now (before: bf16 terms, a margin of 2^-13 |x| and so four times the re-runs):
-//    8 x 16384 x 4 heads x 64 -> 256 bits  141 -> 111 us      1 x 16384 x 4 x 64 -> 256  24.0 -> 20.6
-//   64 x 197 x 12 x 64 -> 128              27.0 -> 25.4       8 x 1000 x 3 x 128 -> 128  15.3 -> 15.0
-//    8 x 1000 x 3 x 128 -> 64              11.6 -> 11.5       1 x 197 x 3 x 64 -> 64      5.9 ->  5.8
-//   32 x 3136 x 1 x 32 -> 64               10.9 -> 11.0
+// to 3.7 at d = 128.  Q and K, alone and over and over, 64 bytes of 16 rows per load -> now:
+//   64 x 197 x 12 heads x 64 -> 128 bits  25.1 -> 23.6 us      64 x 197 x 12 x 64 -> 64  19.2 -> 18.6
+//   64 x 197 x 3 x 64 -> 64               10.0 ->  9.2          8 x 1000 x 3 x 128 -> 128  14.8 -> 14.7
+//   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3          1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
+//    1 x 16384 x 4 x 64 -> 256            20.4 -> 22.3          8 x 16384 x 4 x 64 -> 256  110 -> 112
+// The last line is what loading as a stream costs where nothing is read next.
 #include "common.h"
 #include "hash_margin.h"
 #include "side_work.h"
@@ -60,9 +67,20 @@ struct Tensors {
 __device__ inline void split_f16_pair(float a, float b, uint32_t &upper, uint32_t &lower) {
     const v2f x = {a, b};
     const v2h h = __builtin_convertvector(x, v2h);
-    const v2f r = {a - (float)h[0], b - (float)h[1]};
     upper = __builtin_bit_cast(uint32_t, h);
+    v2f r;                                        // a - h[0], b - h[1]: exact, one operation each that reads its half of h itself
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r[0]) : "v"(upper), "v"(a));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r[1]) : "v"(upper), "v"(b));
     lower = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2h));
+}
+
+// Swaps a's upper 32 lanes with b's lower 32.
+template <typename T>
+__device__ inline void swap_halves(T &a, T &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    a = __builtin_bit_cast(T, r0);
+    b = __builtin_bit_cast(T, r1);
 }
 
 // Re-runs the defining chain for one parked (row, bit) entry and flips the stored bit where the pre-pass had it
@@ -101,7 +119,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
     constexpr int S = D / 32;                     // MFMA steps along k
     constexpr int T = C / 16;                     // 16-column tiles
     constexpr int GROUPS = T / 4;                 // of four tiles: 16 bits of a lane
-    constexpr int L4 = D / 16;                    // 16-byte loads per lane and unit
+    constexpr int L4 = D / 8;                     // 16-byte loads per lane
     constexpr int THREADS = kWaves * 64;
     constexpr int BYTES = C / 32;                 // code bytes of a lane: columns (C / 4) g .. of its row
     __shared__ __attribute__((aligned(16))) uint4 frag_s[T * S * 2 * 64];       // [tile][step][upper, lower][lane]
@@ -123,18 +141,18 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
     const int n = lane & 15, g = lane >> 4;
     const int c_first = blockIdx.y * C;
 
-    // rows 16 u + n of a tile: lane group g loads k = 16 j + 4 g .. + 3, j = 0 .. L4 - 1.  Tiles 0 .. n_tiles - 1 belong
-    // to the first tensor, the next n_tiles to the second; rows past the end re-read the last one.
-    float4 xn[2][L4];
+    // row 16 (g / 2) + n of a tile: its lane loads k = 8 j + 4 (g % 2) .. + 3, j = 0 .. L4 - 1.  Tiles 0 .. n_tiles - 1
+    // belong to the first tensor, the next n_tiles to the second; rows past the end re-read the last one.
+    v4f xn[L4];
     auto load_tile = [&](uint32_t tile) {
         const bool second = tile >= n_tiles;
         const float *x = second ? ts.x1 : ts.x0;
         const uint32_t r0 = (second ? tile - n_tiles : tile) * 32;
+        const float *xr = x + (size_t)min(r0 + 16 * (g >> 1) + n, rows - 1) * D + 4 * (g & 1);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float *xr = x + (size_t)min(r0 + 16 * u + n, rows - 1) * D + 4 * g;
-#pragma unroll
-            for (int j = 0; j < L4; ++j) xn[u][j] = *reinterpret_cast<const float4 *>(xr + 16 * j);
+        for (int j = 0; j < L4; ++j) {
+            const v4f *at = reinterpret_cast<const v4f *>(xr + 8 * j);
+            xn[j] = C == 256 ? __builtin_nontemporal_load(at) : *at;
         }
     };
     const uint32_t tile_step = hash_blocks * kWaves;
@@ -150,7 +168,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
         float v[TASKS][8];
         auto k_of = [&](int i, int e) {
             const int j = part + i * TPC;                         // task j: s = j / 4, kq = j % 4
-            return 16 * (2 * (j >> 2) + e / 4) + 4 * (j & 3) + e % 4;
+            return 32 * (j >> 2) + 16 * (e / 4) + 4 * (j & 3) + e % 4;
         };
         if (mine) {
 #pragma unroll
@@ -212,52 +230,47 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
         uint8_t *codes = reinterpret_cast<uint8_t *>(second ? ts.codes1 : ts.codes0);
 
         // |x_row|^2: keep sign(z~) where |z~| > keep (in units of the staged columns); a non-finite |x|^2 keeps nothing
-        float keep[2];
-        v8h xh[2][S], xl[2][S];
-        float nx2[2];
+        float nx2 = 0.0f;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            float a = 0.0f;
+        for (int j = 0; j < L4; ++j)
 #pragma unroll
-            for (int j = 0; j < L4; ++j) {
-                const float4 v = xn[u][j];
-                a = __builtin_fmaf(v.x, v.x, a); a = __builtin_fmaf(v.y, v.y, a);
-                a = __builtin_fmaf(v.z, v.z, a); a = __builtin_fmaf(v.w, v.w, a);
-            }
-            a += __shfl_xor(a, 16);
-            nx2[u] = a + __shfl_xor(a, 32);
-        }
+            for (int i = 0; i < 4; ++i) nx2 = __builtin_fmaf(xn[j][i], xn[j][i], nx2);
+        nx2 += __shfl_xor(nx2, 16);
         // Rows of ordinary magnitude (|x| in 2^-2 .. 2^12) split as they are, others are brought to |x| ~ 1 first (hash_margin.h).
-        float unit[2] = {1.0f, 1.0f};
-        const bool odd = !(nx2[0] >= kOrdinaryMin2 && nx2[0] <= kOrdinaryMax2 && nx2[1] >= kOrdinaryMin2 && nx2[1] <= kOrdinaryMax2);
-        if (__ballot(odd) != 0) {                                  // wave-uniform
+        float unit = 1.0f;
+        if (__ballot(!(nx2 >= kOrdinaryMin2 && nx2 <= kOrdinaryMax2)) != 0) {          // wave-uniform
+            int e = 0;
+            if (nx2 > 0.0f && nx2 < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2) / 2;
+            unit = __builtin_amdgcn_ldexpf(1.0f, -e);
+#pragma unroll
+            for (int j = 0; j < L4; ++j) xn[j] *= unit;
+        }
+        const float kept = nx2 < __builtin_inff()
+                               ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2), kKeepFloor) * unit * kColumnScale
+                               : __builtin_inff();
+        float keep[2] = {kept, kept};              // of rows n and 16 + n
+        swap_halves(keep[0], keep[1]);
+        // Operands: of two loads side by side the second's lower lanes and the first's upper ones change places: then a lane
+        // has its four of both loads' 16 k of row n in one and of row 16 + n in the other.
+        v8h xh[2][S], xl[2][S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            uint32_t up[2][4], lo[2][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const v4f v = xn[4 * s + j];
+                split_f16_pair(v[0], v[1], up[j & 1][2 * (j >> 1)], lo[j & 1][2 * (j >> 1)]);
+                split_f16_pair(v[2], v[3], up[j & 1][2 * (j >> 1) + 1], lo[j & 1][2 * (j >> 1) + 1]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                swap_halves(up[0][i], up[1][i]);
+                swap_halves(lo[0][i], lo[1][i]);
+            }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                int e = 0;
-                if (nx2[u] > 0.0f && nx2[u] < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2[u]) / 2;
-                unit[u] = __builtin_amdgcn_ldexpf(1.0f, -e);
-#pragma unroll
-                for (int j = 0; j < L4; ++j) {
-                    xn[u][j].x *= unit[u]; xn[u][j].y *= unit[u]; xn[u][j].z *= unit[u]; xn[u][j].w *= unit[u];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            keep[u] = nx2[u] < __builtin_inff()
-                          ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2[u]), kKeepFloor) * unit[u] * kColumnScale
-                          : __builtin_inff();
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                uint32_t up[4], lo[4];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const float4 v = xn[u][2 * s + j];
-                    split_f16_pair(v.x, v.y, up[2 * j], lo[2 * j]);
-                    split_f16_pair(v.z, v.w, up[2 * j + 1], lo[2 * j + 1]);
-                }
-                xh[u][s] = __builtin_bit_cast(v8h, make_uint4(up[0], up[1], up[2], up[3]));
-                xl[u][s] = __builtin_bit_cast(v8h, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+                xh[u][s] = __builtin_bit_cast(v8h, make_uint4(up[u][0], up[u][1], up[u][2], up[u][3]));
+                xl[u][s] = __builtin_bit_cast(v8h, make_uint4(lo[u][0], lo[u][1], lo[u][2], lo[u][3]));
             }
         }
         if (tile + tile_step < n_total) load_tile(tile + tile_step);
@@ -328,17 +341,18 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
                     }
                 }
             }
-            // the smallest |z~| of the 16 decides for all of them; only where one is in doubt they are looked at
-            if (__ballot(!(smallest[0] > keep[0]) || !(smallest[1] > keep[1])) != 0) {         // wave-uniform
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
+            for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(word[u][grp / 2]));      // now, not behind the last group's products
+            // the smallest |z~| of the 16 decides for all of them; only where one is in doubt they are looked at
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (__ballot(!(smallest[u] > keep[u])) != 0) {     // wave-uniform
                     uint32_t pk = 0;
 #pragma unroll
                     for (int q = 0; q < 16; ++q)
                         pk |= (uint32_t)(!(__builtin_fabsf(acc[grp & 1][u][q / 4][q % 4]) > keep[u])) << q;
                     park[u][grp / 2] |= pk << (16 * (grp & 1));
                 }
-            }
         }
 
         uint32_t any_park = 0;
