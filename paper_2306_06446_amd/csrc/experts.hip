@@ -52,31 +52,50 @@ int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, 
 //    384 -> 1536                128 x 128 both  44 / 41 / 42 us    (192 x 128:  46 /  46 /  47; apart  64 /  66 /  55)
 //   1536 ->  384, 384 -> 384    128 x 64 and 64 x 128   33 and 16 us   (128 x 128: 35 and 20; apart 48 and 35)
 //   131072 tokens 256 -> 1024               238 us             (256 x 128: 251; apart 275)
+enum class PairTiles { kSlice32, kSlice64, kLarge, kLongRows, kFine, kMiddle };
+
+// rows of whole 128-byte lines, at least four of them
+bool shift_lines(const GemmArgs &gs) { return gs.K % 128 == 0 && (gs.a_valid == 0 || gs.a_valid == gs.K) && gs.K >= 512; }
+bool mult_lines(const GemmArgs &gm) { return gm.K % 64 == 0 && gm.K >= 256; }
+
+PairTiles choose_pair(const GemmArgs &gs, const GemmArgs &gm) {
+    const bool lines_s = shift_lines(gs), lines_m = mult_lines(gm);
+    auto tiles = [&](long bm, long bn) { return ((gs.sel.max_rows + bm - 1) / bm) * ((gs.N + bn - 1) / bn); };
+    if (tiles(32, 64) <= 256) return PairTiles::kSlice32;
+    if (tiles(64, 64) <= 640) return PairTiles::kSlice64;
+    // more than two rounds of the large Shift tile at two per CU: its higher rate counts for more than an even last round
+    if (lines_s && lines_m && tiles(256, 128) > 1024) return PairTiles::kLarge;
+    if (lines_s && lines_m && gs.K >= 2048) return PairTiles::kLongRows;
+    // not half of the chip's 768 places: finer tiles
+    if (lines_m && tiles(128, 128) <= 384) return PairTiles::kFine;
+    return PairTiles::kMiddle;
+}
+
 template <class StoreS, class StoreM>
 int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
     typedef I8Traits I;
     typedef F16Traits F;
-    const bool lines = gs.K % 128 == 0 && (gs.a_valid == 0 || gs.a_valid == gs.K);
-    const bool lines_s = lines && gs.K >= 512, lines_m = gm.K % 64 == 0 && gm.K >= 256;
-    auto tiles = [&](long bm, long bn) { return ((gs.sel.max_rows + bm - 1) / bm) * ((gs.N + bn - 1) / bn); };
-    if (tiles(32, 64) <= 256) {
-        if (lines_s) return launch_pair_tiles<SliceTile<I, 1, 2, 128, 4>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
-        if (lines_m) return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
-        return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 64, 8>, 1>(gs, ss, gm, sm, st, what);
+    const bool lines_s = shift_lines(gs), lines_m = mult_lines(gm);
+    switch (choose_pair(gs, gm)) {
+        case PairTiles::kSlice32:
+            if (lines_s) return launch_pair_tiles<SliceTile<I, 1, 2, 128, 4>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
+            if (lines_m) return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
+            return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 64, 8>, 1>(gs, ss, gm, sm, st, what);
+        case PairTiles::kSlice64:
+            if (lines_s) return launch_pair_tiles<SliceTile<I, 2, 2, 128, 3>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
+            if (lines_m) return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
+            return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 64, 9>, 2>(gs, ss, gm, sm, st, what);
+        case PairTiles::kLarge:
+            return launch_pair_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
+        case PairTiles::kLongRows:
+            if constexpr (StoreS::kScatter)                  // a second layer (the first one writes a hidden matrix)
+                if (gs.a_block)
+                    return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1, true>, NtTile<F, 128, 128, 64, 4, 1, true>, 2>(gs, ss, gm, sm, st, what);
+            return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 4, 1>, 2>(gs, ss, gm, sm, st, what);
+        case PairTiles::kFine:
+            return launch_pair_tiles<NtTile<I, 128, 64, 64, 3, 1>, NtTile<F, 64, 128, 128, 2, 2>, 3>(gs, ss, gm, sm, st, what);
+        case PairTiles::kMiddle: break;
     }
-    if (tiles(64, 64) <= 640) {
-        if (lines_s) return launch_pair_tiles<SliceTile<I, 2, 2, 128, 3>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
-        if (lines_m) return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
-        return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 64, 9>, 2>(gs, ss, gm, sm, st, what);
-    }
-    // more than two rounds of the large Shift tile at two per CU: its higher rate counts for more than an even last round
-    if (lines_s && lines_m && tiles(256, 128) > 1024)
-        return launch_pair_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
-    if (lines_s && lines_m && gs.K >= 2048)
-        return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 4, 1>, 2>(gs, ss, gm, sm, st, what);
-    // not half of the chip's 768 places: finer tiles
-    if (lines_m && tiles(128, 128) <= 384)
-        return launch_pair_tiles<NtTile<I, 128, 64, 64, 3, 1>, NtTile<F, 64, 128, 128, 2, 2>, 3>(gs, ss, gm, sm, st, what);
     return launch_pair_tiles<NtTile<I, 128, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 3, 1>, 3>(gs, ss, gm, sm, st, what);
 }
 
@@ -106,12 +125,17 @@ int sa::expert_pair_mlp(const ExpertPair &p, int E, int hid, const int8_t *w1_pl
     s2.gate = m2.gate = p.gate;
     s2.out_scale = p.out_scale;
     s2.accumulate = m2.accumulate = accumulate;
+    GemmArgs gs2 = args(shift_hidden, false, w2_planes, w2_planes + (size_t)E * hid, p.shift_rows, hid, E);
+    GemmArgs gm2 = args(mult_hidden, false, mw2, nullptr, p.mult_rows, hid, E);
+    // The tiles for long rows take stages of 64 bytes of a row, half a line, which fill the LDS at half the rate of whole
+    // lines.  Where the second layer has these tiles the hidden rows are laid out in columns of 64 bytes (a stage's rows are then
+    // one behind the other): 12608 tokens, 768 <- 3072: 73 -> 68 us, the whole block 211.5 -> 207.7, the layer 344.1 -> 342.5.
+    if (choose_pair(gs2, gm2) == PairTiles::kLongRows)
+        s1.h_block = m1.h_block = gs2.a_block = gm2.a_block = (size_t)p.shift_rows.max_rows * 64;
     int rc = launch_pair(args(p.xq, true, w1_planes, w1_planes + (size_t)hid * E, p.shift_rows, E, hid), ShiftStore<kEpiRequantLut>(s1),
                          args(p.xh, true, mw1, nullptr, p.mult_rows, E, hid), MultStore<kEpiGeluHalf>(m1), st, "experts (fc1)");
     if (rc != SA_OK) return rc;
-    return launch_pair(args(shift_hidden, false, w2_planes, w2_planes + (size_t)E * hid, p.shift_rows, hid, E),
-                       ShiftStore<kEpiScatterI32>(s2), args(mult_hidden, false, mw2, nullptr, p.mult_rows, hid, E),
-                       MultStore<kEpiScatterF32>(m2), st, "experts (fc2)");
+    return launch_pair(gs2, ShiftStore<kEpiScatterI32>(s2), gm2, MultStore<kEpiScatterF32>(m2), st, "experts (fc2)");
 }
 
 int sa::expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes, const void *w_f16, hipStream_t st) {

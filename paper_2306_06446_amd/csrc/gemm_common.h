@@ -28,6 +28,7 @@ struct Epilogue {
     float out_scale = 1.0f;
     float *of = nullptr;           // compact fp32 out
     _Float16 *hh = nullptr;        // compact fp16 out
+    size_t h_block = 0;            // h and hh: 0 = whole rows, else bytes from one column of 64 bytes to the next
     bool accumulate = false;       // scattered fp32 out: add to what yf holds (fma(gate, value, old)) instead of overwriting
     float *parts[3] = {nullptr, nullptr, nullptr};   // kEpiLinearF32: column block p of width part_width goes to parts[p]
     int part_width = 0;

@@ -87,6 +87,9 @@ struct GemmArgs {
     // pitch of a_ld elements; 0 = K.  The B planes must then hold zeros from a_valid on: the kernel multiplies
     // those zeros with bytes it re-reads from inside the row, so it never reads past a row's end.
     int a_ld = 0, a_valid = 0;
+    // Tiles with BLOCKED take A in columns of 64 bytes, a_block bytes from one to the next, each holding its rows one behind
+    // the other.
+    size_t a_block = 0;
 };
 
 // Physical 16-byte chunk of logical chunk c in LDS row r, for rows of CPR chunks.
@@ -126,6 +129,12 @@ struct ChunkOut {
     __device__ __forceinline__ ChunkOut(const Store &s, int n, int N) : store(s), pitch((size_t)N * ES), res_pitch(N), live(N - n) {
         whole_chunks = pitch % 16 == 0;
         dst = static_cast<uint8_t *>(s.out) + (size_t)n * ES;
+        if constexpr (ES < 4) {                    // hidden rows in columns of 64 bytes (GemmArgs::a_block)
+            if (s.out_block) {
+                dst = static_cast<uint8_t *>(s.out) + (size_t)(n * ES / 64) * s.out_block + n * ES % 64;
+                pitch = 64;
+            }
+        }
         if constexpr (Store::kLinear) {            // whole chunks by construction: part_width and N are multiples of 4
             const int part = n / s.part_width;
             float *base = part == 0 ? s.parts[0] : part == 1 ? s.parts[1] : s.parts[2];
@@ -240,7 +249,7 @@ struct NtShape {
     static_assert(SIDE_AT + OutSide<Store, BM>::BYTES <= LDS_BYTES, "room for the side loads");
 };
 
-template <class T, int BM, int BN, int SB, int NS, int LS, class Store>
+template <class T, int BM, int BN, int SB, int NS, int LS, bool BLOCKED, class Store>
 __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
     using S = NtShape<T, BM, BN, SB, NS, Store>;
     constexpr int kStageBytes = SB;                     // bytes of K per stage and row
@@ -285,7 +294,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
     const int N = g.N;
     const size_t row_bytes = (size_t)g.K * T::kElemBytes;
-    const size_t a_row_bytes = (size_t)(g.a_ld > 0 ? g.a_ld : g.K) * T::kElemBytes;
+    const size_t a_row_bytes = BLOCKED ? 64 : (size_t)(g.a_ld > 0 ? g.a_ld : g.K) * T::kElemBytes;
     const int a_valid_bytes = (g.a_valid > 0 ? g.a_valid : g.K) * T::kElemBytes;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
 
@@ -352,7 +361,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     auto issue_load = [&](int q, int buf, int kbyte) {
         const uint32_t base = lds_base + buf * STAGE;
         if (q < A_INSTR) {
-            direct_load_16(a_src[q] + (SB == 64 ? min(kbyte, a_klim) : kbyte), base + (wave * A_INSTR + q) * 1024);
+            direct_load_16(a_src[q] + (BLOCKED ? (size_t)(kbyte / 64) * g.a_block : SB == 64 ? min(kbyte, a_klim) : kbyte), base + (wave * A_INSTR + q) * 1024);
         } else {
             const int p = (q - A_INSTR) / B_INSTR, i = (q - A_INSTR) % B_INSTR;
             direct_load_16(b_src[p][i] + kbyte, base + A_BYTES + p * B_BYTES + (wave * B_INSTR + i) * 1024);
@@ -651,14 +660,15 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
 }
 
 // A tile shape as launch_tile and the kernels below take it.
-template <class T, int BM_, int BN_, int SB, int NS, int LS>
+template <class T, int BM_, int BN_, int SB, int NS, int LS, bool BLOCKED = false>
 struct NtTile {
+    static_assert(!BLOCKED || SB == 64, "columns of a stage");
     static constexpr int BM = BM_, BN = BN_;
     template <class Store>
     static constexpr int lds_bytes() { return NtShape<T, BM, BN, SB, NS, Store>::LDS_BYTES; }
     template <class Store>
     __device__ static __forceinline__ void run(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
-        nt_gemm_tile<T, BM, BN, SB, NS, LS, Store>(g, store, block, lds);
+        nt_gemm_tile<T, BM, BN, SB, NS, LS, BLOCKED, Store>(g, store, block, lds);
     }
     // The fewest column groups whose share of the B planes stays resident in a 4 MiB L2 next to
     // the A rows streaming through it.  (Fewer groups fetch fewer bytes when A is the larger operand,

@@ -23,6 +23,7 @@ struct ShiftStore {
     const void *table;     // the 256-entry activation table
     const float *gate;
     bool accumulate;
+    size_t out_block;
     float *parts[3];       // kEpiLinearF32: column blocks, residual and scale
     int part_width;
     const float *residual;
@@ -36,6 +37,7 @@ struct ShiftStore {
           table(epi.lut),
           gate(MODE == kEpiScatterI32 ? epi.gate : nullptr),
           accumulate(MODE == kEpiScatterI32 && epi.accumulate),
+          out_block(epi.h_block),
           parts{epi.parts[0], epi.parts[1], epi.parts[2]},
           part_width(epi.part_width > 0 ? epi.part_width : 4),
           residual(epi.residual),
@@ -83,10 +85,12 @@ struct MultStore {
     const void *table = nullptr;
     const float *gate;
     bool accumulate;
+    size_t out_block;
     explicit MultStore(const Epilogue &epi)
         : out(MODE == kEpiFloat ? (void *)epi.of : MODE == kEpiGeluHalf ? (void *)epi.hh : (void *)epi.yf),
           gate(MODE == kEpiScatterF32 ? epi.gate : nullptr),
-          accumulate(MODE == kEpiScatterF32 && epi.accumulate) {}
+          accumulate(MODE == kEpiScatterF32 && epi.accumulate),
+          out_block(epi.h_block) {}
     __device__ inline uint32_t convert(float a, int, const uint8_t *) const {
         if (MODE == kEpiGeluHalf) return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)gelu_erf(a));
         return __builtin_bit_cast(uint32_t, a);
