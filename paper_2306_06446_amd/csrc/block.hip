@@ -3,6 +3,7 @@
 // Shift MLP or the two-expert MoE.  A composition of the library's own steps; the expert row counts
 // stay on the device (no host round trip).
 #include "common.h"
+#include "gemm_common.h"
 
 namespace {
 
@@ -366,12 +367,25 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                              ws + L.lin_ws, L.lin_ws_bytes, stream);
     if (rc != SA_OK) return rc;
 
-    // MLP half: y += MLP(LayerNorm(y)); every row is read by the LayerNorm before an expert adds to it
+    // MLP half: y += MLP(LayerNorm(y)); every row is read by the LayerNorm before an expert adds to it.  Where the MLP is one
+    // launch its workgroups normalise their rows themselves.
+    const sa_rows all{nullptr, nullptr, 0, T};
+    sa::RowSel sel;
+    rc = sa::validate_rows(&all, &sel);
+    if (rc != SA_OK) return rc;
+    if (!moe && weights.variant == SA_VARIANT_MFMA_PREPARED && sa::shift_mlp_one_launch(sel, E, d->hid)) {
+        const sa::NormRows norm{d->y, d->gamma2, d->beta2, d->eps, d->ln_inv_scale};
+        sa::Epilogue e;
+        e.yf = d->y;
+        e.out_scale = d->out_scale;
+        e.accumulate = true;
+        return sa::launch_shift_mlp(nullptr, &norm, sel, E, d->hid, reinterpret_cast<const int8_t *>(weights.w1),
+                                    reinterpret_cast<const int8_t *>(weights.w2), d->lut, d->requant_scale, e, sa::as_stream(stream));
+    }
     rc = sa_layernorm_quant(d->y, T, E, d->gamma2, d->beta2, d->eps, d->ln_inv_scale, nullptr, codes8, xh,
                             moe ? d->wg : nullptr, moe ? d->bg : nullptr, moe ? 2 : 0, logits, stream);
     if (rc != SA_OK) return rc;
     if (!moe) {
-        const sa_rows all{nullptr, nullptr, 0, T};
         return sa_shift_mlp(codes8, &all, E, d->hid, weights.w1, weights.w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
                             d->out_scale, weights.variant, 3 | SA_MLP_ACCUMULATE, ws + L.shift_ws, L.shift_ws_bytes,
                             stream);

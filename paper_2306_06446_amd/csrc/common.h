@@ -213,8 +213,14 @@ int expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes
 // out: yf, gate, out_scale, accumulate.
 struct Epilogue;
 bool shift_mlp_one_launch(const RowSel &sel, int E, int hid);
-int launch_shift_mlp(const int8_t *x, const RowSel &sel, int E, int hid, const int8_t *w1_planes, const int8_t *w2_planes,
-                     const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st);
+// fp32 rows [max_rows, E] whose LayerNorm, as int8 codes (static scale), an MLP takes.
+struct NormRows {
+    const float *x, *gamma, *beta;
+    float eps, inv_scale;
+};
+// Of the rows x, or of all rows of norm (which may be the output's: a workgroup reads its rows before it writes them).
+int launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
+                     const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).
 size_t moe_dispatch_scratch_bytes(long T, int E);
 int moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,

@@ -14,6 +14,7 @@
 // 25.9 -> 14.5, 131072 x 256 61.5 -> 52.5.
 #include "common.h"
 #include "gemm_common.h"
+#include "layernorm.h"
 
 namespace {
 
@@ -22,36 +23,6 @@ using namespace sa;
 typedef _Float16 v4h_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWavesPerBlock = 4;
-
-
-template <int CTRL>
-__device__ inline float dpp_add(float v) {
-    const int other = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true);
-    return v + __builtin_bit_cast(float, other);
-}
-
-// Sum over aligned groups of LPR lanes (16, 32 or 64) as a butterfly, the most distant lanes first; every lane of a group
-// gets it.  Once lanes 8 apart agree, a rotation of the 16 lanes of a row by 4 (then 2, 1) is an exchange of neighbours.
-template <int LPR>
-__device__ inline float group_sum(float v) {
-    if (LPR == 64) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, v);
-        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-        const uint32_t r0 = r[0], r1 = r[1];
-        v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
-    }
-    if (LPR >= 32) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, v);
-        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-        const uint32_t r0 = r[0], r1 = r[1];
-        v = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
-    }
-    v = dpp_add<0x128>(v);                // row_ror:8
-    v = dpp_add<0x124>(v);                // row_ror:4
-    v = dpp_add<0x122>(v);                // row_ror:2
-    v = dpp_add<0x121>(v);                // row_ror:1
-    return v;
-}
 
 struct LnArgs {
     const float *x;
@@ -116,20 +87,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void layernorm_kernel(LnArgs a
         } else {
             load_row(t, v);
         }
-        float s = 0.0f;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) s += (v[c].x + v[c].y) + (v[c].z + v[c].w);
-        const float mean = group_sum<LPR>(s) / (float)E;
-        float ss = 0.0f;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int j = (c * LPR + l) * 4;
-            if (j < E) {
-                const float d0 = v[c].x - mean, d1 = v[c].y - mean, d2 = v[c].z - mean, d3 = v[c].w - mean;
-                ss += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
-            }
-        }
-        const float rstd = 1.0f / __builtin_sqrtf(group_sum<LPR>(ss) / (float)E + a.eps);
+        float mean, rstd;
+        row_stats<LPR, CH>(v, l, E, a.eps, mean, rstd);
         float part[kMaxExperts];
 #pragma unroll
         for (int e = 0; e < kMaxExperts; ++e) part[e] = 0.0f;
@@ -140,17 +99,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void layernorm_kernel(LnArgs a
             const float4 g = CACHE ? gm[CACHE ? c : 0] : *reinterpret_cast<const float4 *>(a.gamma + j);
             const float4 b = CACHE ? bt[CACHE ? c : 0] : *reinterpret_cast<const float4 *>(a.beta + j);
             float y[4];
-            y[0] = (v[c].x - mean) * rstd * g.x + b.x;
-            y[1] = (v[c].y - mean) * rstd * g.y + b.y;
-            y[2] = (v[c].z - mean) * rstd * g.z + b.z;
-            y[3] = (v[c].w - mean) * rstd * g.w + b.w;
+            normalise(v[c], mean, rstd, g, b, y);
             if (row_ok) {
                 const size_t o = (size_t)t * E + j;
                 if (a.ln) *reinterpret_cast<float4 *>(a.ln + o) = make_float4(y[0], y[1], y[2], y[3]);
-                if (a.q)
-                    *reinterpret_cast<uint32_t *>(a.q + o) =
-                        requant_byte(y[0] * a.inv_scale) | (requant_byte(y[1] * a.inv_scale) << 8) |
-                        (requant_byte(y[2] * a.inv_scale) << 16) | (requant_byte(y[3] * a.inv_scale) << 24);
+                if (a.q) *reinterpret_cast<uint32_t *>(a.q + o) = codes_of(y, a.inv_scale);
                 if (a.xh) {
                     v4h_t h;
 #pragma unroll

@@ -591,7 +591,7 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
         e.gate = gate_or_null;
         e.out_scale = out_scale;
         e.accumulate = (stages & SA_MLP_ACCUMULATE) != 0;
-        return sa::launch_shift_mlp(xq, sel, E, hid, reinterpret_cast<const int8_t *>(pair ? planes1 : w1),
+        return sa::launch_shift_mlp(xq, nullptr, sel, E, hid, reinterpret_cast<const int8_t *>(pair ? planes1 : w1),
                                     reinterpret_cast<const int8_t *>(pair ? planes2 : w2), lut, requant_scale, e, st);
     }
     if (stages & 1) {

@@ -10,12 +10,16 @@
 //      25088 x  64, 512 hidden   20.0 -> 10.1 us     131072 x  64   49 -> 33
 //      25088 x 192, 768 hidden   30 -> 24            131072 x 192  112 -> 93
 //      16384 x 256, 1024 hidden  31 -> 26            131072 x 256  161 -> 145
+// A layer's LayerNorm in front of it costs a workgroup its rows as fp32 and 4 MI of them per wavefront to normalise, beside the
+// first weights' way in, and saves the launch that wrote the codes: layer of 32 x 784 tokens x 64 52.1 -> 47.1 us, of 1 x 16384
+// x 256 122 -> 115.
 // Layer 1 on four wavefronts and layer 2 on the other four (requantiser beside products without being interleaved): 226 us
 // for the last one.
 #include "common.h"
 #include "gemm_common.h"
 #include "gemm_mfma.h"
 #include "gemm_stores.h"
+#include "layernorm.h"
 
 namespace {
 
@@ -41,6 +45,7 @@ struct MlpShape {
     // (the table first: its offset is part of the instructions that read it)
     static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk, SIDE = H + 2 * H_BYTES;
     static constexpr int LDS_BYTES = SIDE + OutSide<Store, BM>::BYTES;
+    static_assert(BM * E <= 2 * H_BYTES, "codes of normalised rows in the place of the hidden rows");
     static_assert(kMlpWaves * 16 * PITCH <= RING * STAGE, "output staging reuses the ring");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
 };
@@ -54,8 +59,9 @@ __device__ inline int swizzle_w1(int r, int c) {
 }
 __device__ inline int swizzle_128(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-template <int NE, int MI, class Store>
-__global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, RowSel sel, int hid,
+// NORM: the rows are fp32 and every wavefront turns its share of the workgroup's into codes first (LayerNorm); else x: codes.
+template <int NE, int MI, bool NORM, class Store>
+__global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
                                                                    const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
                                                                    const int8_t *__restrict__ lut, float rq, Store store) {
     using S = MlpShape<NE, MI, Store>;
@@ -78,8 +84,22 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 
     // this wavefront's rows of x, as operands of the first layer
     uint4 xf[MI][NE];
+    constexpr int LPR = NE == 1 ? 16 : NE == 2 ? 32 : 64, GROUPS = 64 / LPR, STEPS = 4 * MI / GROUPS;      // NORM: lanes of a row
+    const int l = lane % LPR, norm_row = wave * 4 * MI + lane / LPR;          // this lane's columns 4 l .. + 3 of rows norm_row + GROUPS i
+    float4 xr[NORM ? STEPS : 1], gamma, beta;
+    if constexpr (NORM) {
+        const bool in = 4 * l < E;
+        const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
+        for (int i = 0; i < STEPS; ++i) {
+            const long m = min(m0 + norm_row + GROUPS * i, n_rows - 1);
+            xr[i] = in ? *reinterpret_cast<const float4 *>(norm.x + (size_t)m * E + 4 * l) : none;
+        }
+        gamma = in ? *reinterpret_cast<const float4 *>(norm.gamma + 4 * l) : none;
+        beta = in ? *reinterpret_cast<const float4 *>(norm.beta + 4 * l) : none;
+    }
+#pragma unroll
+    for (int i = 0; i < (NORM ? 0 : MI); ++i) {
         const long m = min(m0 + wr * 16 * MI + 16 * i + fr, n_rows - 1);
         const int8_t *xr = x + (size_t)(rows ? (long)rows[m] : m) * E + 16 * fg;
 #pragma unroll
@@ -126,9 +146,30 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     };
 #pragma unroll
     for (int q = 0; q < S::RING; ++q) issue(q, q);           // (there are at least four stages)
+    if constexpr (NORM) {                                    // the codes, by way of the hidden rows' place
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            const float4 v[1] = {xr[i]};
+            float mean, rstd, y[4];
+            row_stats<LPR, 1>(v, l, E, norm.eps, mean, rstd);
+            normalise(v[0], mean, rstd, gamma, beta, y);
+            const int r = norm_row + GROUPS * i;
+            if (4 * l < E) *reinterpret_cast<uint32_t *>(lds + S::H + r * E + swizzle_w1<NE>(r, l / 4) * 16 + l % 4 * 4) = codes_of(y, norm.inv_scale);
+        }
+    }
     wait_loads_in_flight<(S::RING - 1) * LOADS>();
     side.fetch_gates(wave, lane);
     __syncthreads();
+    if constexpr (NORM) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                const int r = wr * 16 * MI + 16 * i + fr;
+                xf[i][k] = *reinterpret_cast<const uint4 *>(lds + S::H + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+            }
+        wait_lds_reads();                                    // hidden rows come here behind the first layer's barriers
+    }
     int s = 0, slot = 0;                                     // the stage being multiplied, its place in the ring
 
     v4i acc1[MI][2], acc2[MI][NE];
@@ -322,13 +363,26 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     else emit(std::false_type{});
 }
 
+struct MlpArgs {
+    const int8_t *x;
+    const NormRows *norm;                                    // or null
+    RowSel sel;
+    int hid;
+    const int8_t *w1, *w2, *lut;
+    float rq;
+    ShiftStore<kEpiScatterI32> store;
+};
+
 template <int NE, int MI>
-int launch(const int8_t *x, const RowSel &sel, int hid, const int8_t *w1, const int8_t *w2, const int8_t *lut, float rq,
-           const ShiftStore<kEpiScatterI32> &store, hipStream_t st) {
+int launch(const MlpArgs &a, hipStream_t st) {
     typedef ShiftStore<kEpiScatterI32> Store;
-    const long blocks = (sel.max_rows + 32 * MI - 1) / (32 * MI);
+    const long blocks = (a.sel.max_rows + 32 * MI - 1) / (32 * MI);
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_shift_mlp: too many rows for one launch");
-    shift_mlp_kernel<NE, MI, Store><<<dim3((unsigned)blocks), dim3(kMlpWaves * 64), 0, st>>>(x, sel, hid, w1, w2, lut, rq, store);
+    const dim3 grid((unsigned)blocks), block(kMlpWaves * 64);
+    if (a.norm)
+        shift_mlp_kernel<NE, MI, true, Store><<<grid, block, 0, st>>>(nullptr, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+    else
+        shift_mlp_kernel<NE, MI, false, Store><<<grid, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     return check_launch("sa_shift_mlp (both layers)");
 }
 
@@ -347,22 +401,16 @@ bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid) {
 // Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the
 // larger ones takes (256 x 1024: 16384 rows 26 against 36 us, 25088 rows 47 against 37, 131072 rows 181 against 145).  At
 // E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).
-int sa::launch_shift_mlp(const int8_t *x, const RowSel &sel, int E, int hid, const int8_t *w1_planes, const int8_t *w2_planes,
-                         const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
-    const ShiftStore<kEpiScatterI32> store(out);
-    const float rq = requant_scale_finite(requant_scale);
+int sa::launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
+                         const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
+    const MlpArgs a{x, norm, sel, hid, w1_planes, w2_planes, lut, requant_scale_finite(requant_scale), ShiftStore<kEpiScatterI32>(out)};
     auto rounds = [&](long rows) { return ((sel.max_rows + rows - 1) / rows + 255) / 256; };
-    const bool tall = E > 64 && 29 * rounds(128) < 20 * rounds(64);
-#define SA_MLP(NE_)                                                                                     \
-    case 64 * NE_:                                                                                      \
-        return tall ? launch<NE_, 4>(x, sel, hid, w1_planes, w2_planes, lut, rq, store, st)             \
-                    : launch<NE_, 2>(x, sel, hid, w1_planes, w2_planes, lut, rq, store, st);
+    const bool tall = 29 * rounds(128) < 20 * rounds(64);
     switch (E) {
-        case 64: return launch<1, 2>(x, sel, hid, w1_planes, w2_planes, lut, rq, store, st);
-        SA_MLP(2)
-        SA_MLP(3)
-        SA_MLP(4)
+        case 64: return launch<1, 2>(a, st);
+        case 128: return tall ? launch<2, 4>(a, st) : launch<2, 2>(a, st);
+        case 192: return tall ? launch<3, 4>(a, st) : launch<3, 2>(a, st);
+        case 256: return tall ? launch<4, 4>(a, st) : launch<4, 2>(a, st);
     }
-#undef SA_MLP
     return fail(SA_ERR_UNSUPPORTED, "sa_shift_mlp: width %d in one launch", E);
 }
