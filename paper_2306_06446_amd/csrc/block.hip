@@ -363,23 +363,37 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                                          codes8, nullptr, d->act_inv_scale, SA_VARIANT_AUTO, stream);
     }
     if (rc != SA_OK) return rc;
-    rc = sa_shift_linear_f32(codes8, d->wo, T, E, E, d->shift_variant, d->o_scale, d->x, 1, d->y, nullptr, nullptr,
-                             ws + L.lin_ws, L.lin_ws_bytes, stream);
-    if (rc != SA_OK) return rc;
 
     // MLP half: y += MLP(LayerNorm(y)); every row is read by the LayerNorm before an expert adds to it.  Where the MLP is one
-    // launch its workgroups normalise their rows themselves.
+    // launch its workgroups normalise their rows themselves, and with prepared weights they make them as well.
     const sa_rows all{nullptr, nullptr, 0, T};
     sa::RowSel sel;
     rc = sa::validate_rows(&all, &sel);
     if (rc != SA_OK) return rc;
-    if (!moe && weights.variant == SA_VARIANT_MFMA_PREPARED && sa::shift_mlp_one_launch(sel, E, d->hid)) {
-        const sa::NormRows norm{d->y, d->gamma2, d->beta2, d->eps, d->ln_inv_scale};
+    const bool one_launch = !moe && weights.variant == SA_VARIANT_MFMA_PREPARED && sa::shift_mlp_one_launch(sel, E, d->hid);
+    const bool project = one_launch && d->shift_variant == SA_VARIANT_MFMA_PREPARED;
+    if (!project) {
+        rc = sa_shift_linear_f32(codes8, d->wo, T, E, E, d->shift_variant, d->o_scale, d->x, 1, d->y, nullptr, nullptr,
+                                 ws + L.lin_ws, L.lin_ws_bytes, stream);
+        if (rc != SA_OK) return rc;
+    }
+    if (one_launch) {
+        sa::NormRows norm;
+        norm.x = norm.out = d->y;
+        norm.gamma = d->gamma2;
+        norm.beta = d->beta2;
+        norm.eps = d->eps;
+        norm.inv_scale = d->ln_inv_scale;
+        if (project) {
+            norm.wo = reinterpret_cast<const int8_t *>(d->wo);
+            norm.residual = d->x;
+            norm.scale = d->o_scale;
+        }
         sa::Epilogue e;
         e.yf = d->y;
         e.out_scale = d->out_scale;
         e.accumulate = true;
-        return sa::launch_shift_mlp(nullptr, &norm, sel, E, d->hid, reinterpret_cast<const int8_t *>(weights.w1),
+        return sa::launch_shift_mlp(codes8, &norm, sel, E, d->hid, reinterpret_cast<const int8_t *>(weights.w1),
                                     reinterpret_cast<const int8_t *>(weights.w2), d->lut, d->requant_scale, e, sa::as_stream(stream));
     }
     rc = sa_layernorm_quant(d->y, T, E, d->gamma2, d->beta2, d->eps, d->ln_inv_scale, nullptr, codes8, xh,

@@ -213,12 +213,17 @@ int expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes
 // out: yf, gate, out_scale, accumulate.
 struct Epilogue;
 bool shift_mlp_one_launch(const RowSel &sel, int E, int hid);
-// fp32 rows [max_rows, E] whose LayerNorm, as int8 codes (static scale), an MLP takes.
+// fp32 rows [max_rows, E] whose LayerNorm, as int8 codes (static scale), an MLP takes: x, or, with wo (decoded planes [E, E]),
+// out = residual + scale * wo . codes, which the launch leaves there as well.
 struct NormRows {
-    const float *x, *gamma, *beta;
-    float eps, inv_scale;
+    const float *x = nullptr, *gamma = nullptr, *beta = nullptr;
+    float eps = 0.0f, inv_scale = 1.0f;
+    const int8_t *wo = nullptr;
+    const float *residual = nullptr;
+    float scale = 1.0f, *out = nullptr;
 };
-// Of the rows x, or of all rows of norm (which may be the output's: a workgroup reads its rows before it writes them).
+// Of the rows x; of all rows of norm, or of those it makes of the codes x (they may be the output's: a workgroup reads its rows
+// before it writes them).
 int launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                      const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).

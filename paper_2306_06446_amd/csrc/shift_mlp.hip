@@ -12,7 +12,8 @@
 //      16384 x 256, 1024 hidden  31 -> 26            131072 x 256  161 -> 145
 // A layer's LayerNorm in front of it costs a workgroup its rows as fp32 and 4 MI of them per wavefront to normalise, beside the
 // first weights' way in, and saves the launch that wrote the codes: layer of 32 x 784 tokens x 64 52.1 -> 47.1 us, of 1 x 16384
-// x 256 122 -> 115.
+// x 256 122 -> 115.  With prepared weights the output projection in front of the LayerNorm is made here too, from all of Wo in
+// LDS: at E = 64 it costs this launch 0.5 us and saves one of 5.7 (layer 47.1 -> 42.1 us), at E = 256 7.4 of 9.4 (121.9 -> 120.6).
 // Layer 1 on four wavefronts and layer 2 on the other four (requantiser beside products without being interleaved): 226 us
 // for the last one.
 #include "common.h"
@@ -46,8 +47,10 @@ struct MlpShape {
     static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk, SIDE = H + 2 * H_BYTES;
     static constexpr int LDS_BYTES = SIDE + OutSide<Store, BM>::BYTES;
     static_assert(BM * E <= 2 * H_BYTES, "codes of normalised rows in the place of the hidden rows");
+    static constexpr int PROJECT_BYTES = STAGES + 2 * E * E > LDS_BYTES ? STAGES + 2 * E * E : LDS_BYTES;      // Wo's planes at STAGES
+    static_assert(BM * E * 4 <= RING * STAGE + 2 * H_BYTES, "projected rows in the place of the ring and the hidden rows");
     static_assert(kMlpWaves * 16 * PITCH <= RING * STAGE, "output staging reuses the ring");
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+    static_assert(PROJECT_BYTES <= 160 * 1024, "LDS of a CU");
 };
 
 // 16-byte chunk c of a row of E bytes in LDS: any 16 consecutive rows hit 16 different bank groups.
@@ -59,14 +62,18 @@ __device__ inline int swizzle_w1(int r, int c) {
 }
 __device__ inline int swizzle_128(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-// NORM: the rows are fp32 and every wavefront turns its share of the workgroup's into codes first (LayerNorm); else x: codes.
-template <int NE, int MI, bool NORM, class Store>
+// What the rows are: codes; fp32 rows, which every wavefront normalises its share of; or fp32 rows that the kernel makes first, as
+// x_res + Wo . codes.
+enum MlpRows { kCodes, kNorm, kProject };
+
+template <int NE, int MI, int ROWS, class Store>
 __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
                                                                    const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
                                                                    const int8_t *__restrict__ lut, float rq, Store store) {
     using S = MlpShape<NE, MI, Store>;
+    constexpr bool NORM = ROWS != kCodes, PROJECT = ROWS == kProject;
     constexpr int E = S::E, PS = S::PS, SPG = S::SPG, LOADS = S::LOADS;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[S::LDS_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[PROJECT ? S::PROJECT_BYTES : S::LDS_BYTES];
     const int32_t *rows;
     long n_rows;
     resolve_rows(sel, rows, n_rows);
@@ -82,7 +89,8 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     side.fetch_rows(wave, lane);
     if (wave == kMlpWaves - 1) direct_load_4(lut + lane * 4, lds_base + S::TABLE);
 
-    // this wavefront's rows of x, as operands of the first layer
+    v4i acc1[MI][2], acc2[MI][NE];
+    // this wavefront's rows of x, as operands of the first layer (PROJECT: of the projection, until then)
     uint4 xf[MI][NE];
     constexpr int LPR = NE == 1 ? 16 : NE == 2 ? 32 : 64, GROUPS = 64 / LPR, STEPS = 4 * MI / GROUPS;      // NORM: lanes of a row
     const int l = lane % LPR, norm_row = wave * 4 * MI + lane / LPR;          // this lane's columns 4 l .. + 3 of rows norm_row + GROUPS i
@@ -93,17 +101,64 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
             const long m = min(m0 + norm_row + GROUPS * i, n_rows - 1);
-            xr[i] = in ? *reinterpret_cast<const float4 *>(norm.x + (size_t)m * E + 4 * l) : none;
+            xr[i] = in ? *reinterpret_cast<const float4 *>((PROJECT ? norm.residual : norm.x) + (size_t)m * E + 4 * l) : none;
         }
         gamma = in ? *reinterpret_cast<const float4 *>(norm.gamma + 4 * l) : none;
         beta = in ? *reinterpret_cast<const float4 *>(norm.beta + 4 * l) : none;
     }
 #pragma unroll
-    for (int i = 0; i < (NORM ? 0 : MI); ++i) {
+    for (int i = 0; i < (ROWS == kNorm ? 0 : MI); ++i) {
         const long m = min(m0 + wr * 16 * MI + 16 * i + fr, n_rows - 1);
         const int8_t *xr = x + (size_t)(rows ? (long)rows[m] : m) * E + 16 * fg;
 #pragma unroll
         for (int k = 0; k < NE; ++k) xf[i][k] = *reinterpret_cast<const uint4 *>(xr + 64 * k);
+    }
+
+    if constexpr (PROJECT) {
+        // Wo's planes in the place of all that comes later, the products as those of the second layer, through LDS to the
+        // wavefronts that normalise the rows.
+#pragma unroll
+        for (int j = 0; j < NE * NE; ++j) {                  // 8 NE^2 KiB: the planes are one behind the other
+            const int q = j * kMlpWaves + wave, c = q * 64 + lane, r = c / (4 * NE);
+            direct_load_16(norm.wo, (uint32_t)(r * E + swizzle_w1<NE>(r, c % (4 * NE)) * 16), lds_base + S::STAGES + q * 1024);
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int t = 0; t < NE; ++t) acc2[i][t] = v4i{0, 0, 0, 0};
+        wait_loads_in_flight<0>();
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int k = 0; k < NE; ++k)
+#pragma unroll
+                for (int t = 0; t < NE; ++t) {
+                    const int r = p * E + wc * 16 * NE + 16 * t + fr;
+                    const uint4 w = *reinterpret_cast<const uint4 *>(lds + S::STAGES + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) acc2[i][t] = mma16(w, xf[i][k], acc2[i][t]);
+                }
+        __syncthreads();                                     // Wo has been read
+        auto staged = [&](int r, int c) { return reinterpret_cast<float4 *>(lds + S::STAGES + r * E * 4 + (c ^ (r & 15)) * 16); };
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int t = 0; t < NE; ++t)
+                *staged(wr * 16 * MI + 16 * i + fr, wc * 4 * NE + 4 * t + fg) =
+                    make_float4((float)acc2[i][t][0], (float)acc2[i][t][1], (float)acc2[i][t][2], (float)acc2[i][t][3]);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            const int r = norm_row + GROUPS * i;
+            if (4 * l < E) {
+                const float4 a = *staged(r, l);
+                xr[i] = make_float4(__builtin_fmaf(a.x, norm.scale, xr[i].x), __builtin_fmaf(a.y, norm.scale, xr[i].y),
+                                    __builtin_fmaf(a.z, norm.scale, xr[i].z), __builtin_fmaf(a.w, norm.scale, xr[i].w));
+                if (m0 + r < n_rows) *reinterpret_cast<float4 *>(norm.out + (size_t)(m0 + r) * E + 4 * l) = xr[i];
+            }
+        }
+        __syncthreads();                                     // the ring's place is free
     }
 
     // Where this lane's 16 bytes of load i of a plane come from: a part that is the same in every lane (row0 rows) and one per
@@ -172,7 +227,6 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     }
     int s = 0, slot = 0;                                     // the stage being multiplied, its place in the ring
 
-    v4i acc1[MI][2], acc2[MI][NE];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -379,10 +433,12 @@ int launch(const MlpArgs &a, hipStream_t st) {
     const long blocks = (a.sel.max_rows + 32 * MI - 1) / (32 * MI);
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_shift_mlp: too many rows for one launch");
     const dim3 grid((unsigned)blocks), block(kMlpWaves * 64);
-    if (a.norm)
-        shift_mlp_kernel<NE, MI, true, Store><<<grid, block, 0, st>>>(nullptr, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+    if (a.norm && a.norm->wo)
+        shift_mlp_kernel<NE, MI, kProject, Store><<<grid, block, 0, st>>>(a.x, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+    else if (a.norm)
+        shift_mlp_kernel<NE, MI, kNorm, Store><<<grid, block, 0, st>>>(nullptr, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     else
-        shift_mlp_kernel<NE, MI, false, Store><<<grid, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+        shift_mlp_kernel<NE, MI, kCodes, Store><<<grid, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     return check_launch("sa_shift_mlp (both layers)");
 }
 

@@ -1,5 +1,6 @@
-"""A layer whose MLP is one launch that normalises its rows itself, against one whose LayerNorm is a launch of its own (the
-vector-ALU variant of the Shift Linears: integers, so the same sums)."""
+"""A layer whose MLP is one launch that normalises its rows itself (and, with prepared weights, makes them: the output projection),
+against one whose LayerNorm and projection are launches of their own (the vector-ALU variant of the Shift Linears: integers, so
+the same sums)."""
 import pytest
 import torch
 
@@ -22,11 +23,13 @@ def test_normalised_in_the_mlp(sa, B, N, H, E, hid):
     proj = torch.randn((E // H, 64), generator=g, device="cuda")
     lut = torch.arange(-128, 128, device="cuda").clamp(min=0).to(torch.int8)
     y = []
-    for variant in (2, 0):
+    for variant in (0, 2, 3):
+        if variant == 3:
+            w = [sa.sa_shift_planes_prepare(t) for t in w]
         layer = sa.binding.Layer(B=B, N=N, H=H, nbits=64, E=E, hid=hid, attention=0, moe=0, shift_variant=variant, eps=1e-6,
                                  ln_inv_scale=32.0, qkv_scale=2.0**-12, attn_scale=(64.0 * N) ** -0.5, act_inv_scale=32.0,
                                  o_scale=2.0**-12, requant_scale=2.0**-11, out_scale=2.0**-12, x=x, gamma1=gamma1, beta1=beta1,
                                  gamma2=gamma2, beta2=beta2, wqkv=w[0], wo=w[1], proj=proj, w1=w[2], w2=w[3], lut=lut)
         y.append(layer.forward().clone())
     assert float((y[0] - x).abs().max()) > 0.0
-    assert torch.equal(y[0], y[1])
+    assert torch.equal(y[0], y[1]) and torch.equal(y[0], y[2])
