@@ -445,13 +445,16 @@ int launch(const MlpArgs &a, hipStream_t st) {
 }  // namespace
 
 // Whether one launch is the faster way.  A workgroup passes all weights through its CU, about 1 us per 128 hidden columns and 64
-// of E / 2, whatever its rows; two launches take 11.7 us for few rows.  So for small products always (E * hid up to 96 Ki:
-// 256 x 384, 6272 rows 13.7 apart against 12.7; 64 x 512, 1568 rows 11.8 against 9.1), for others once their rows fill half of
-// the chip (256 x 1024: 6272 rows 20 against 24, 12608 rows 30 against 25; 192 x 768: 6272 rows 16.5 against 15.9, 3136 rows
-// 13.6 against 15.5).
+// of E / 2, whatever its rows.  So for E = 64 and 128 with small products always (E * hid up to 96 Ki: 64 x 512, 1568 rows 11.8
+// apart against 9.1; layer of 33 x 128, 768 hidden 33.8 against 30.6, of 1000 39.5 against 38.8), with wider rows from where a good
+// part of the chip has some (layer of 192, 512 hidden: 1000 rows 41.1 against 44.6, 3152 rows 51.5 both, 12608 rows 83.8 against
+// 65.4; 256, 384 hidden: 1000 rows 42.1 against 46.2, 3152 rows 54.4 against 53.5), for larger products once their rows fill half
+// of it (256 x 1024: 6272 rows 20 against 24, 12608 rows 30 against 25; 192 x 768: 6272 rows 16.5 against 15.9, 3136 rows 13.6
+// against 15.5).
 bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid) {
     if (E > 256 || E % 64 != 0 || hid % kHidChunk != 0 || hid < 2 * kHidChunk) return false;
-    return (long)E * hid <= 98304 || sel.max_rows >= 40L * E;
+    if ((long)E * hid > 98304) return sel.max_rows >= 40L * E;
+    return E <= 128 || sel.max_rows >= 16L * E;
 }
 
 // Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the
