@@ -335,10 +335,13 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
         rc = sa::check_moe_dispatch(logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes);
     if (rc != SA_OK) return rc;
 
-    // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y
-    rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
-                            nullptr, 0, nullptr, stream);
-    if (rc != SA_OK) return rc;
+    // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y.  Narrow rows are normalised by the projection's workgroups.
+    const bool norm_linear = !fused_hash && d->shift_variant == SA_VARIANT_MFMA_PREPARED && sa::norm_linear_one_launch(T, E);
+    if (!norm_linear) {
+        rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
+                                nullptr, 0, nullptr, stream);
+        if (rc != SA_OK) return rc;
+    }
     sa::SideWork side;
     const ShiftWeights weights(*d, E, T, ws + L.shift_ws, &side.decode);
     if (fused_hash) {
@@ -348,8 +351,18 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                                        ws + L.lin_ws, L.lin_ws_bytes, stream);
         if (rc != SA_OK) return rc;
     } else {
-        rc = sa_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, d->qkv_scale, nullptr, 3, q, k, v,
-                                 ws + L.lin_ws, L.lin_ws_bytes, stream);
+        if (norm_linear) {
+            sa::NormRows norm;
+            norm.x = d->x;
+            norm.gamma = d->gamma1;
+            norm.beta = d->beta1;
+            norm.eps = d->eps;
+            norm.inv_scale = d->ln_inv_scale;
+            rc = sa::launch_norm_linear(norm, T, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, q, k, v, sa::as_stream(stream));
+        } else {
+            rc = sa_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, d->qkv_scale, nullptr, 3, q, k, v,
+                                     ws + L.lin_ws, L.lin_ws_bytes, stream);
+        }
         if (rc != SA_OK) return rc;
         rc = hash_and_side(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, side, stream);
         if (rc != SA_OK) return rc;

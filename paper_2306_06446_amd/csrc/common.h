@@ -226,6 +226,11 @@ struct NormRows {
 // before it writes them).
 int launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                      const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st);
+// LayerNorm of all T rows of norm.x and the Q, K, V projection of its codes (decoded planes [3E, E]) in one launch
+// (norm_linear.hip): whether it is the faster way, and the launch.
+bool norm_linear_one_launch(long T, int E);
+int launch_norm_linear(const NormRows &norm, long T, int E, const int8_t *wqkv_planes, float scale, float *q, float *k, float *v,
+                       hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).
 size_t moe_dispatch_scratch_bytes(long T, int E);
 int moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,

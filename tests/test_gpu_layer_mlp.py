@@ -1,6 +1,6 @@
 """A layer whose MLP is one launch that normalises its rows itself (and, with prepared weights, makes them: the output projection),
-against one whose LayerNorm and projection are launches of their own (the vector-ALU variant of the Shift Linears: integers, so
-the same sums)."""
+and whose Q, K, V projection normalises its rows, against one whose LayerNorms and projections are launches of their own (the
+vector-ALU variant of the Shift Linears: integers, so the same sums)."""
 import pytest
 import torch
 
@@ -11,8 +11,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,N,H,E,hid", [
     (1, 1, 1, 64, 256), (3, 77, 2, 64, 512), (1, 333, 2, 128, 256), (2, 97, 3, 192, 512), (5, 1601, 3, 192, 768),
     (1, 500, 4, 256, 384), (1, 10241, 4, 256, 1024), (7, 2801, 4, 256, 512), (9, 3001, 2, 128, 640),
+    (4, 3101, 3, 192, 256), (1, 1537, 2, 128, 256),
 ])
-def test_normalised_in_the_mlp(sa, B, N, H, E, hid):
+def test_normalised_rows_stay_on_the_chip(sa, B, N, H, E, hid):
     g = torch.Generator(device="cuda")
     g.manual_seed(N + hid)
     T = B * N
