@@ -52,7 +52,9 @@ int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, 
 //    384 -> 1536                128 x 128 both  44 / 41 / 42 us    (192 x 128:  46 /  46 /  47; apart  64 /  66 /  55)
 //   1536 ->  384, 384 -> 384    128 x 64 and 64 x 128   33 and 16 us   (128 x 128: 35 and 20; apart 48 and 35)
 //   131072 tokens 256 -> 1024               238 us             (256 x 128: 251; apart 275)
-enum class PairTiles { kSlice32, kSlice64, kLarge, kLongRows, kFine, kMiddle };
+// Few tokens with whole-line stages take 32 x 32 tiles, as in launch_gemm (block of 197 tokens x 192, 768 hidden 24.0 -> 23.6 us,
+// 197 x 768, 3072 hidden 31.9 -> 31.1, 1 x 768 23.3 -> 20.7; 300 x 768, fifteen tiles for sixteen CUs: 38.4 both).
+enum class PairTiles { kSlice32x32, kSlice32, kSlice64, kLarge, kLongRows, kFine, kMiddle };
 
 // rows of whole 128-byte lines, at least four of them
 bool shift_lines(const GemmArgs &gs) { return gs.K % 128 == 0 && (gs.a_valid == 0 || gs.a_valid == gs.K) && gs.K >= 512; }
@@ -61,6 +63,7 @@ bool mult_lines(const GemmArgs &gm) { return gm.K % 64 == 0 && gm.K >= 256; }
 PairTiles choose_pair(const GemmArgs &gs, const GemmArgs &gm) {
     const bool lines_s = shift_lines(gs), lines_m = mult_lines(gm);
     auto tiles = [&](long bm, long bn) { return ((gs.sel.max_rows + bm - 1) / bm) * ((gs.N + bn - 1) / bn); };
+    if (lines_s && tiles(32, 32) <= 192) return PairTiles::kSlice32x32;
     if (tiles(32, 64) <= 256) return PairTiles::kSlice32;
     if (tiles(64, 64) <= 640) return PairTiles::kSlice64;
     // more than two rounds of the large Shift tile at two per CU: its higher rate counts for more than an even last round
@@ -77,6 +80,8 @@ int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const 
     typedef F16Traits F;
     const bool lines_s = shift_lines(gs), lines_m = mult_lines(gm);
     switch (choose_pair(gs, gm)) {
+        case PairTiles::kSlice32x32:
+            return launch_pair_tiles<SliceTile<I, 1, 1, 128, 5>, SliceTile<F, 1, 1, 128, 8>, 1>(gs, ss, gm, sm, st, what);
         case PairTiles::kSlice32:
             if (lines_s) return launch_pair_tiles<SliceTile<I, 1, 2, 128, 4>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);
             if (lines_m) return launch_pair_tiles<SliceTile<I, 1, 2, 64, 7>, SliceTile<F, 1, 2, 128, 6>, 1>(gs, ss, gm, sm, st, what);

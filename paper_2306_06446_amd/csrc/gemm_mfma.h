@@ -716,7 +716,9 @@ namespace sa {
 // Tile choice, from sweeps over (K, N) of the transformer widths 64 .. 3072 and 50 .. 25088 rows on one MI355X.
 // t32, t64: tiles of 32 x 64 and 64 x 64 outputs.
 //  * t32 <= 256: not every CU gets a 32 x 64 tile, so the time is that of one tile: gemm_slice.h with 32 rows
-//    (965 x 192 <- 768 int8: 4.8 us against 9.5 with 128 x 128 tiles; 197 x 768 <- 3072: 8.7 against 21);
+//    (965 x 192 <- 768 int8: 4.8 us against 9.5 with 128 x 128 tiles; 197 x 768 <- 3072: 8.7 against 21).  Whole-line stages
+//    with up to three 32 x 32 tiles for four CUs: those, whose planes are there in half the time (197 x 768 <- 768 int8 4.9 ->
+//    4.2 us, 197 x 768 <- 3072 8.9 -> 6.8, 1000 x 192 <- 768 4.9 -> 4.2; 320 x 768 <- 768, fifteen for sixteen: 5.0 both);
 //  * t64 <= 640: up to two and a half 64 x 64 tiles per CU (965 x 768 <- 3072 int8: 11.8 us against 35 with the
 //    256 x 128 tiles, 3152 x 768 <- 768: 11.7 against 12.2; fp16 with long rows only up to 320: the next tile up
 //    catches up there).  Short rows take 64-byte stages: with few stages the finer ones start sooner
@@ -751,6 +753,8 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
     auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
     const bool whole_line_stages = lines && row_bytes >= 512;
     if constexpr (T::kPlanes == 2) {
+        if constexpr (!Store::kSignCodes)
+            if (whole_line_stages && tiles(32, 32) <= 192) return launch_tile<SliceTile<T, 1, 1, 128, 5>, 1>(g, store, st, what);
         if (tiles(32, 64) <= 256)
             return whole_line_stages ? launch_tile<SliceTile<T, 1, 2, 128, 4>, 1>(g, store, st, what)
                                      : launch_tile<SliceTile<T, 1, 2, 64, 7>, 1>(g, store, st, what);
@@ -767,6 +771,7 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
         if (wide) return launch_tile<NtTile<T, 256, 128, 64, 2, 1>, 2>(g, store, st, what);
         return launch_tile<NtTile<T, 128, 128, 64, 2, 1>, 3>(g, store, st, what);
     } else {
+        if (whole_line_stages && tiles(32, 32) <= 192) return launch_tile<SliceTile<T, 1, 1, 128, 8>, 1>(g, store, st, what);
         if (tiles(32, 64) <= 256)
             return whole_line_stages ? launch_tile<SliceTile<T, 1, 2, 128, 6>, 1>(g, store, st, what)
                                      : launch_tile<SliceTile<T, 1, 2, 64, 8>, 1>(g, store, st, what);

@@ -9,7 +9,7 @@
 // buffers is deep: NS - 1 stages of whole 128-byte lines are in flight at once, with one barrier per stage.
 // The four partial tiles meet in LDS in ascending order (integers: any order; floats: always the same one).
 // Measured (MI355X, 965 rows x 768 <- 3072, two int8 planes, alone): 11.8 us against 35 us with 256 x 128 tiles;
-// 197 rows x 768 <- 3072: 8.7 us against 21 us with 128 x 128 tiles.
+// 197 rows x 768 <- 3072: 6.8 us with 32 x 32 tiles and 8.9 with 32 x 64 against 21 us with 128 x 128 tiles.
 #pragma once
 
 namespace sa {
