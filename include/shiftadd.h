@@ -177,9 +177,10 @@ int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_t *k_codes,
  *   x [M,K] int8, w4 [N,K/2] packed 4-bit, bias [N] int32 or NULL, y [M,N] int32.
  * K % 32 == 0 (16-byte weight rows), for both variants.
  * Both variants are bit-exact.  The MFMA variant decodes the weights to two
- * int8 planes in the workspace before the matrix-core pass (2*N*Kp bytes, Kp = K
- * rounded up to a multiple of 64: plane rows are padded with zeros to whole
- * 64-byte stages; the activation rows are read as they are).
+ * int8 planes, on the way into the matrix-core pass or in the workspace before it
+ * (2*N*Kp bytes, Kp = K rounded up to a multiple of 64: plane rows are padded with
+ * zeros to whole 64-byte stages; the activation rows are read as they are); the
+ * workspace has to be there either way.
  *
  * The planes depend on the weights only (s * 2^min(e,6) and s * 64 * [e == 7],
  * which sum to s * 2^e of Eq. 3), so a caller with fixed weights decodes them

@@ -794,17 +794,29 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
 // launch_gemm estimates them), and the launch.  A stage's weights come in as 32 bytes of a row instead of 128, which in the
 // K loop pays for their decoding; of the tiles those that leave registers for it:
 //  * 192 x 128, two per CU, for rows of 768 bytes and more once they make one and a half tiles per CU (12608 x 768 <- 3072,
-//    decode + planes against packed: 70 -> 66 us; 12608 x 768 <- 768 26.4 -> 22.6, with 128 x 64 24.7);
+//    decode + planes against packed: 70 -> 66 us; 12608 x 768 <- 768 26.4 -> 22.6, with 128 x 64 24.7), unless an XCD's share
+//    is a little more than a round (16000 x 768 <- 768, 66 tiles for 64 places: 31.7 us, with 128 x 64 25.6; planes 29.7);
 //  * 128 x 64, three per CU (12608 x 1536 <- 384 33.5 -> 27.1, with 192 x 128 31.5; 12608 x 384 <- 1536 27.9 -> 24.1;
 //    100000 x 256 <- 64 27 -> 20.5; 3000 x 1024 <- 1024 16 -> 13.5);
 //  * where gemm_slice.h would take the planes, 64 x 64 for rows up to 1024 bytes (1379 x 3072 <- 768 22 -> 15; 965 x 768 <-
 //    3072 18 -> 21.6: those stay).
-// Beyond 2^35 multiply-adds the decode is no longer worth its removal (65000 x 3072 <- 768 333 against 346, 131072 x 256 <- 1024
-// 86 against 89).
+// The planes stay
+//  * beyond 2^35 multiply-adds, 2^34 for rows of less than 768 bytes, where the decode is no longer worth its removal (65000 x
+//    3072 <- 768 333 against 346, 131072 x 256 <- 1024 86 against 89, 50000 x 1536 <- 384 87.9 against 92.8);
+//  * for rows of 2 KiB and more that do not make 192 x 128 tiles enough (11000 x 768 <- 3072 64.7 against 72.6; 8000 rows 46.8
+//    against 45.8), or of which only the device knows how many there are, so that the tiles are chosen for half of them (768 <-
+//    3072, 8826 of 12608 rows 51.4 against 55.1, 17561 of 25088 91 against 100; 3072 <- 768 of the same 53.4 against 48.8 and 91.5
+//    against 86.3, 384 <- 1536 23.4 against 23.7);
+//  * for rows of 1 KiB and more whose planes make exactly one round of 256 x 128 tiles (40000 x 384 <- 1536 47.3 against 54.4,
+//    50000 x 256 <- 1024 34.2 against 39.5; 32000 and 40000 rows of the same, more and less than that, 49.1 against 38.2 and 28.9
+//    against 27.1).
 inline bool packed_gemm(long max_rows, bool counted, int N, int K) {
     const long m_est = counted ? (max_rows + 1) / 2 : max_rows;
-    if (K % 64 != 0 || (double)m_est * N * K > 34359738368.0) return false;
-    return ((m_est + 63) / 64) * ((N + 63) / 64) > 640 || K <= 1024;
+    auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (K % 64 != 0 || (double)m_est * N * K > (K < 768 ? 17179869184.0 : 34359738368.0)) return false;
+    if (tiles(64, 64) <= 640) return K <= 1024;
+    if (K >= 2048) return !counted && tiles(192, 128) >= 384;
+    return !(K >= 1024 && tiles(128, 128) > 768 && tiles(256, 128) <= 512);
 }
 
 template <class Store>
@@ -816,7 +828,8 @@ int launch_gemm_packed(const GemmArgs &g, const Store &store, hipStream_t st, co
     const long m_est = g.sel.counts ? (g.sel.max_rows + 1) / 2 : g.sel.max_rows;
     auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
     if (tiles(64, 64) <= 640) return launch_tile<NtTile<T, 64, 64, 64, 2, 1>, 4>(g, store, st, what);
-    if (g.K >= 768 && tiles(192, 128) >= 384) return launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
+    const long per_xcd = ((m_est + 191) / 192 + 7) / 8 * ((g.N + 127) / 128);       // of 64 places
+    if (g.K >= 768 && tiles(192, 128) >= 384 && (g.K >= 2048 || per_xcd <= 64 || per_xcd > 80)) return launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
     return launch_tile<NtTile<T, 128, 64, 64, 2, 1>, 3>(g, store, st, what);
 }
 

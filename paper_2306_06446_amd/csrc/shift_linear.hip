@@ -6,9 +6,10 @@
 //           negative weight is "xor the activation with all-ones, shift, add" and
 //           the (1 << e) terms, which depend on the weights only, are summed once
 //           per output column through a virtual all-zero activation row.
-//   MFMA  : the 4-bit weights are decoded once per call to two int8 planes,
-//           A = s * 2^min(e,6) and B = s * 64 * [e == 7] (+128 is not an int8),
-//           and both planes go through v_mfma_i32_32x32x32_i8 into one accumulator.
+//   MFMA  : the 4-bit weights are decoded to two int8 planes, A = s * 2^min(e,6) and
+//           B = s * 64 * [e == 7] (+128 is not an int8), by the matrix-core pass itself on
+//           their way into LDS or, where that is slower, once per call into the workspace;
+//           both planes go through v_mfma_i32_32x32x32_i8 into one accumulator.
 // Both share the epilogues (plain int32, requantise + table, gated fp32 scatter).
 #include "common.h"
 #include "gemm_common.h"
@@ -577,7 +578,10 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
     const bool one_launch = (stages & 3) == 3 && v_eff != SA_VARIANT_VALU && y_or_null && !y2_or_null && sa::shift_mlp_one_launch(sel, E, hid);
     const bool packed1 = sa::packed_gemm(sel.max_rows, sel.counts != nullptr, hid, E);
     const bool packed2 = sa::packed_gemm(sel.max_rows, sel.counts != nullptr, E, hid);
-    const bool pair = v_eff == SA_VARIANT_MFMA && (stages & 3) == 3 && (one_launch || !packed1 || !packed2);
+    // (one launch for both is soon worth more than two layers that decode for themselves: 12608 x 768, 3072 hidden 124.9 against
+    // 127.4 us, but 12608 x 384, 1536 hidden 46.7 against 44.1)
+    const double work = (double)(sel.counts ? (sel.max_rows + 1) / 2 : sel.max_rows) * E * hid;
+    const bool pair = v_eff == SA_VARIANT_MFMA && (stages & 3) == 3 && (one_launch || !packed1 || !packed2 || work > 17179869184.0);
     if (pair) {
         sa::DecodeWork w;
         sa::add_decode(&w, w1, E, hid, planes1);
