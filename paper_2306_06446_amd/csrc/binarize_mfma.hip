@@ -18,8 +18,9 @@
 // A load instruction takes 32 bytes of each of the 32 rows, so that its first use of a line asks for all rows' lines at
 // once; the operands, which want 64 bytes of 16 rows, are put together by lane swaps after the split.  Loaded as 64 bytes of
 // 16 rows, the attention of 32 x 3136 tokens x 1 head x 32 with 64 bits takes 25.2 us (24.5 now).
-// At 256 columns the rows are loaded as a stream: the products hide most of it, and V, which K^T V reads next, stays in
-// the caches (block of 1 x 16384 tokens x 4 heads 132.4 -> 128.9 us; at 64 columns the wait shows, 24.5 -> 28.4).
+// At 256 columns more rows than the L2s hold are loaded as a stream: the products hide most of it, and V, which K^T V reads
+// next, stays in the caches (block of 1 x 16384 tokens x 4 heads 132.4 -> 128.9 us; at 64 columns the wait shows, 24.5 -> 28.4, and
+// with few rows: attention of 4 x 137 tokens x 12 heads 26.2 -> 28.2).
 // Products of 32x32x16 took the same time here but more power, which the kernels around it paid for in clock.
 //
 // What bounds it: at 256 bits the products and the vector work in their shadow (16 funnel shifts and 8 three-way minima
@@ -112,7 +113,7 @@ __device__ inline void settle_entry(uint64_t e, const Tensors &ts, const float *
 }
 
 // D: head dim; C: hash columns of a workgroup (blockIdx.y selects the group); kWaves: its wavefronts.
-template <int D, int C, int kWaves>
+template <int D, int C, int kWaves, bool STREAM>
 __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, const float *__restrict__ proj, uint32_t rows,
                                                                     RowMap map, int nbits, uint32_t n_tiles, uint32_t n_total,
                                                                     uint32_t hash_blocks, SideWork side) {
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
 #pragma unroll
         for (int j = 0; j < L4; ++j) {
             const v4f *at = reinterpret_cast<const v4f *>(xr + 8 * j);
-            xn[j] = C == 256 ? __builtin_nontemporal_load(at) : *at;
+            xn[j] = STREAM ? __builtin_nontemporal_load(at) : *at;
         }
     };
     const uint32_t tile_step = hash_blocks * kWaves;
@@ -439,8 +440,14 @@ int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &
     // what rides along comes behind the tiles: it fills the CUs that are done first
     const long more = (side_blocks(side, kWaves * 64) + nbits / C - 1) / (nbits / C);
     const dim3 grid((unsigned)(blocks + more), (unsigned)(nbits / C));
-    binarize_mfma_kernel<D, C, kWaves><<<grid, dim3(kWaves * 64), 0, st>>>(
-        ts, proj, (uint32_t)rows, map, nbits, (uint32_t)n_tiles, (uint32_t)n_total, (uint32_t)blocks, side);
+    // what is hashed does not stay in the L2s (4 MiB each) anyway: see the top
+    const bool stream = C == 256 && n_total * 32 * D * 4 > (32L << 20);
+#define SA_HASH(STREAM_)                                                                                                          \
+    binarize_mfma_kernel<D, C, kWaves, STREAM_><<<grid, dim3(kWaves * 64), 0, st>>>(                                              \
+        ts, proj, (uint32_t)rows, map, nbits, (uint32_t)n_tiles, (uint32_t)n_total, (uint32_t)blocks, side)
+    if (stream) SA_HASH(C == 256);
+    else SA_HASH(false);
+#undef SA_HASH
     return check_launch("sa_binarize(mfma)");
 }
 
