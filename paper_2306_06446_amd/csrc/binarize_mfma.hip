@@ -467,12 +467,17 @@ int launch_one(const Tensors &ts, int count, const float *proj, long rows, int N
 }
 
 // x1 / codes1 may be null: one tensor.  Columns of a workgroup: as many of the code as divide it, up to 256 (128 at
-// d = 128: what the LDS holds), so that the rows are read and split as few times as possible.
+// d = 128: what the LDS holds), so that the rows are read and split as few times as possible.  But fewer while that leaves half
+// of the chip's SIMDs without a tile: the time is then that of one tile and of its share of the hash matrix (Q and K of 1 x 197 x 3
+// heads x 64 -> 256 bits 8.4 -> 5.8 us, -> 128 bits 6.9 -> 5.7, 4 x 137 x 12 x 64 -> 256 8.8 -> 7.3, 1 x 197 x 3 x 128 -> 128 10.4 ->
+// 8.2; from 512 to 1024 tiles it is a tie, beyond slower: 4 x 1000 x 4 x 64 -> 256 8.9 against 10.3).
 int launch_binarize_mfma(const float *x0, const float *x1, const float *proj, uint64_t *codes0, uint64_t *codes1,
                          long rows, int N, int H, int d, int nbits, hipStream_t st, const SideWork &side) {
     const Tensors ts{x0, x1, codes0, codes1};
     const int count = x1 ? 2 : 1;
-    const bool c128 = (nbits % 128 == 0), c256 = (nbits % 256 == 0);
+    const long n_total = (rows + 31) / 32 * count;
+    auto takes = [&](int c) { return nbits % c == 0 && n_total * (nbits / c) > 512; };
+    const bool c128 = takes(128), c256 = takes(256);
     switch (d) {
         case 32:
             return c256   ? launch_one<32, 256>(ts, count, proj, rows, N, H, nbits, side, st)
