@@ -414,8 +414,16 @@ __device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes,
     }
 }
 
+// Whether the codes of a wavefront's next tiles are asked for while it multiplies these: with several passes over two tiles (8 x 4 x
+// 16384 queries, {0,1} codes of 64 bits 29.9 -> 28.5 us, of 128 bits 37.4 -> 36.5).  Not {0,1} codes of 256 bits, for which 16
+// wavefronts do not leave the 16 registers: 22 of 128 were spilled on every tile's way (8 x 4 x 16384 queries 53.7 us at a tile's
+// start, 64.8 ahead; 64 x 12 x 1100 queries 112 and 139).  Nor the one tile of a wavefront of the smaller workgroups, where there
+// is nothing to hide it behind but registers to lose (64 x 12 x 197 queries of 64 bits 12.1 against 12.7 us, {0,1} 16.3 against 17.4).
+template <int TM, int W, bool ZO>
+constexpr bool kCodesAhead = TM > 1 && !(ZO && W == 4);
+
 // block = (bh * column groups + column group) * blocks_per_bh + part
-// first: the codes of this wavefront's first tiles, asked for long before they are needed.
+// first: with kCodesAhead the codes of this wavefront's first tiles.
 // PLANES: K^T V is in LDS already (ktv_block).
 template <int DVC, int W, int NW, int TM, bool ZO, bool PLANES = false>
 __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, int Nq, int DV, long BH,
@@ -479,8 +487,8 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
     }
     if (ZO) {
         for (int j = tid; j < NBITS; j += n_threads) {
-            int32_t c = 0;
-            for (int s = 0; s < f.splits; s += 8) {
+            int32_t c = f.ksum_in[(size_t)bh * NBITS + j];
+            for (int s = 1; s < f.splits; s += 8) {
                 int32_t y[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) y[q] = f.ksum_in[((size_t)min(s + q, f.splits - 1) * BH + bh) * NBITS + j];
@@ -506,9 +514,10 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
         float factor[TM];                         // ZO: 1 / (normaliser + eps) of this lane's query
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
+            const uint64_t *here = q_codes + ((size_t)bh * Nq + min((tile0 + tm) * 32 + m, Nq - 1)) * W;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                const uint64_t wd = first[tm][w];
+                const uint64_t wd = kCodesAhead<TM, W, ZO> ? first[tm][w] : here[w];
                 code[tm][2 * w] = (uint32_t)wd;
                 code[tm][2 * w + 1] = (uint32_t)(wd >> 32);
             }
@@ -527,8 +536,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                 code[tm][q] = ZO ? code[tm][q] >> (4 * kg) : code[tm][q] << (4 - 4 * kg);
             }
         }
-        // of the next tiles ({0,1} codes, which have no registers to spare: behind this tile's products)
-        if (!ZO && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, first);
+        if (kCodesAhead<TM, W, ZO> && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, first);
         v16f acc[TM][JT];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
@@ -561,7 +569,6 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             // keep the steps apart: hoisting every operand read of the tile to the top costs hundreds of registers
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (ZO && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, first);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (tile0 + tm >= tile_end) continue;
@@ -573,7 +580,9 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int row = 8 * (r >> 2) + (r & 3);           // + 4 kg
-                    const float fr = ZO ? __shfl(factor[tm], row + 4 * kg) : -f.scale;      // (+-1: see code_pair)
+                    // (+-1: see code_pair.  __shfl, which allows for other widths, took 4 registers more than 256-bit codes leave.)
+                    const float fr = ZO ? __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(16 * kg + 4 * row, __builtin_bit_cast(int, factor[tm])))
+                                        : -f.scale;
                     if (WHOLE || (tile0 + tm) * 32 + row + 4 * kg < Nq) {
                         const size_t at = tile_at + (size_t)row * row_step;
 #pragma unroll
@@ -604,7 +613,7 @@ __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__res
     __shared__ __attribute__((aligned(16))) uint8_t lds[QkvLds<DVC, W, ZO>::BYTES];
     uint64_t first[TM][W];
     const int tile0 = blockIdx.x % blocks_per_bh * tiles_per_block + (threadIdx.x >> 6) * TM;
-    load_codes<W, TM>(q_codes, blockIdx.x / blocks_per_bh / (DV / DVC), Nq, tile0, first);
+    if constexpr (kCodesAhead<TM, W, ZO>) load_codes<W, TM>(q_codes, blockIdx.x / blocks_per_bh / (DV / DVC), Nq, tile0, first);
     qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds, first);
 }
 
@@ -621,7 +630,7 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t 
     __shared__ __attribute__((aligned(1024))) uint8_t lds[KB > QB ? KB : QB];
     static_assert(kKtvWaves / PH * WB == W, "a workgroup has all words");
     uint64_t first[1][W];
-    load_codes<W, 1>(q_codes, blockIdx.x / (DV / DVC), Nq, threadIdx.x >> 6, first);
+    if constexpr (kCodesAhead<1, W, false>) load_codes<W, 1>(q_codes, blockIdx.x / (DV / DVC), Nq, threadIdx.x >> 6, first);
     ktv_block<DVC, WB, PH, RING, false, true>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
     qkv_block<DVC, W, kKtvWaves, 1, false, true>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds, first);
 }

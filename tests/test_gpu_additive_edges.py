@@ -78,3 +78,9 @@ def test_rows_of_a_ragged_step_more_than_4_gib_apart(sa, Nq):
         o_ref = 0.125 * torch.matmul(2 * bits_of(q[0, heads]) - 1, ref)
         err = (out[0][:, heads].double().transpose(0, 1) - o_ref).abs()
         assert bool((err <= 1e-4 * o_ref.abs() + 1e-5 * float(o_ref.square().mean().sqrt())).all()), float(err.max())
+
+
+# passes of 16 wavefronts over two tiles each: a whole pass and a ragged tile behind it, every code width
+@pytest.mark.parametrize("W", [1, 2, 4])
+def test_passes_of_sixteen_wavefronts(sa, W):
+    test_both_code_modes_against_fp64(sa, 8, 4, 8200, 40, W, 64)

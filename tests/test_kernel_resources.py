@@ -1,0 +1,61 @@
+"""What the compiler made of the kernels, from the metadata of the library's own code objects: kernels whose speed hangs on their
+registers neither spill nor take more than their workgroups share a CU with."""
+import os
+import re
+import struct
+
+import pytest
+
+msgpack = pytest.importorskip("msgpack")
+
+LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2306_06446_amd", "libshiftadd.so")
+
+
+def kernel_metadata(elf):
+    """name -> metadata of every kernel of a code object (its AMDGPU metadata note, a msgpack map)."""
+    shoff, = struct.unpack_from("<Q", elf, 40)
+    entry, count = struct.unpack_from("<HH", elf, 58)
+    found = {}
+    for i in range(count):
+        _, kind, _, _, at, size = struct.unpack_from("<IIQQQQ", elf, shoff + i * entry)
+        end = at + size
+        while kind == 7 and at < end:                        # SHT_NOTE
+            name_size, desc_size, note = struct.unpack_from("<III", elf, at)
+            desc = at + 12 + (name_size + 3) // 4 * 4
+            if note == 32:                                   # NT_AMDGPU_METADATA
+                meta = msgpack.unpackb(elf[desc:desc + desc_size], strict_map_key=False)
+                found.update({k[".name"]: k for k in meta["amdhsa.kernels"]})
+            at = desc + (desc_size + 3) // 4 * 4
+    return found
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    if not os.path.exists(LIB):
+        import __graft_entry__
+        __graft_entry__.build()
+    data, found, at = open(LIB, "rb").read(), {}, 0
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    while True:
+        at = data.find(magic, at)
+        if at < 0:
+            return found
+        count, = struct.unpack_from("<Q", data, at + len(magic))
+        p = at + len(magic) + 8
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, p)
+            target = data[p + 24:p + 24 + length]
+            p += 24 + length
+            if size and b"gfx950" in target:
+                found.update(kernel_metadata(data[at + offset:at + offset + size]))
+        at += len(magic)
+
+
+@pytest.mark.parametrize("pattern,instances", [
+    (r"qkv_mfma_kernel", 12),
+])
+def test_no_scratch(kernels, pattern, instances):
+    some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
+    assert len(some) == instances
+    for n, k in some.items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
