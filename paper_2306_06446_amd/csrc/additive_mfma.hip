@@ -64,12 +64,6 @@ __device__ inline uint32_t code_pair(uint32_t x, int sh) {
     return ((x << sh) & 0x80008000u) | 0x3F803F80u;
 }
 
-// Where K^T V's row `bit` stands in a column of Q(K^T V)'s planes (its order of K, see there).
-__device__ inline int qkv_place(int bit) {
-    const int r = bit % 16;
-    return (((bit / 32) * 2 + r / 8) * 2 + r / 4 % 2) * 8 + r % 4 * 2 + bit / 16 % 2;
-}
-
 // ------------------------------------------------------------------------------ K^T V ----
 // Workgroup: one (b, h), up to four code words, up to 64 columns, one token range; eight wavefronts.  A wavefront has WB (1 or
 // 2) words and every PH-th 16-token step, and holds that whole [64 WB bits, DVC columns] accumulator.  Its V rows and code
@@ -94,8 +88,7 @@ struct KtvLds {
 // dst is not __restrict__: a kernel that goes on to Q(K^T V) reads the same memory through AddFused::kv_in.
 // ksum (ZO): int32 [splits][BH][nbits], the number of tokens of the range whose code bit is set.
 // block = ((bh * n_groups + group) * n_cols + column group) * splits + split
-// PLANES (one token range, all words in the workgroup): the sums also stay in LDS, as qkv_block stages them.
-template <int DVC, int WB, int PH, int RING, bool ZO, bool PLANES = false>
+template <int DVC, int WB, int PH, int RING, bool ZO>
 __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, const float *__restrict__ v, float *dst,
                                           int32_t *__restrict__ ksum, long BH, int H, int Nk, int W, int DV, int splits,
                                           int tokens_per_block, int block, uint8_t *ring_s) {
@@ -267,8 +260,6 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
     //      With +-1 codes the operand was -1 for a set bit (the code bit as the sign bit), so the sum is negated here.
     const size_t row0 = (((size_t)part * BH + bh) * W + group * GW) * 64;
     const int rows_here = min(GW, W - group * GW) * 64;
-    constexpr int SUMS = PAIRS * TILE / 4, KEEP = (SUMS + kKtvWaves * 64 - 1) / (kKtvWaves * 64);       // 16-byte sums of a tile, of a thread
-    f32x4 sum[TB][KEEP];
 #pragma unroll
     for (int t = 0; t < TB; ++t) {
         if (t > 0) __syncthreads();
@@ -281,10 +272,7 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
                 *at = acc[t][0][r];
         }
         __syncthreads();
-#pragma unroll(PLANES ? KEEP : 1)
-        for (int k = 0; k < KEEP; ++k) {
-            const int q = k * kKtvWaves * 64 + tid;
-            if (q >= SUMS) break;
+        for (int q = tid; q < PAIRS * TILE / 4; q += kKtvWaves * 64) {
             const int share = q / (TILE / 4);
             f32x4 a = reinterpret_cast<const f32x4 *>(red_s)[q];
 #pragma unroll
@@ -292,32 +280,7 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
             const int row = share * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
             if (!ZO) a = -a;
             if (row < rows_here) *reinterpret_cast<f32x4 *>(dst + (row0 + row) * DV + c0 + col) = a;
-            if constexpr (PLANES) sum[t][k] = a;
         }
-    }
-    if constexpr (PLANES) {
-        constexpr int STRIDE = GW * 64 + 8, PLANE = DVC * STRIDE;
-        __syncthreads();                           // every sum has been read
-        uint16_t *kvt = reinterpret_cast<uint16_t *>(ring_s);
-#pragma unroll
-        for (int t = 0; t < TB; ++t)
-#pragma unroll
-            for (int k = 0; k < KEEP; ++k) {
-                const int q = k * kKtvWaves * 64 + tid;
-                if (q >= SUMS) break;
-                const int bit = q / (TILE / 4) * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
-                uint16_t *at = kvt + col * STRIDE + qkv_place(bit);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    uint32_t t3[3];
-                    split3_pair(sum[t][k][2 * h], sum[t][k][2 * h + 1], t3);
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) {
-                        at[p * PLANE + 2 * h * STRIDE] = (uint16_t)t3[p];
-                        at[p * PLANE + (2 * h + 1) * STRIDE] = (uint16_t)(t3[p] >> 16);
-                    }
-                }
-            }
     }
     if (ZO && c0 == 0) {
 #pragma unroll
@@ -423,11 +386,9 @@ template <int TM, int W, bool ZO>
 constexpr bool kCodesAhead = TM > 1 && !(ZO && W == 4);
 
 // block = (bh * column groups + column group) * blocks_per_bh + part
-// first: with kCodesAhead the codes of this wavefront's first tiles.
-// PLANES: K^T V is in LDS already (ktv_block).
-template <int DVC, int W, int NW, int TM, bool ZO, bool PLANES = false>
+template <int DVC, int W, int NW, int TM, bool ZO>
 __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, int Nq, int DV, long BH,
-                                          int blocks_per_bh, int tiles_per_block, int block, uint8_t *lds, uint64_t (&first)[TM][W]) {
+                                          int blocks_per_bh, int tiles_per_block, int block, uint8_t *lds) {
     constexpr int JT = DVC / 32;
     constexpr int NBITS = W * 64;
     constexpr int STRIDE = QkvLds<DVC, W, ZO>::STRIDE, PLANE = QkvLds<DVC, W, ZO>::PLANE;
@@ -443,10 +404,12 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
     const long bh = block / blocks_per_bh / n_cols;
     const int b = (int)(bh / H), h = (int)(bh % H);
     const int m = lane & 31, kg = lane >> 5;
+    uint64_t next[TM][W];                          // kCodesAhead: the codes of the tiles that come next
+    if constexpr (kCodesAhead<TM, W, ZO>) load_codes<W, TM>(q_codes, bh, Nq, part * tiles_per_block + wave * TM, next);
 
     // K^T V -> the three planes: a task is the eight rows of one lane half of a step, one column; with more than one
     // partial they are summed on the way, in ascending order, and the first workgroup of the (b, h) leaves the sum in kv
-    for (int t = tid; !PLANES && t < NBITS / 8 * DVC; t += n_threads) {
+    for (int t = tid; t < NBITS / 8 * DVC; t += n_threads) {
         const int col = t % DVC, grp = t / DVC;                    // grp = (half * 2 + s) * 2 + kg
         const int bit0 = (grp >> 2) * 32 + ((grp >> 1) & 1) * 8 + (grp & 1) * 4;
         const size_t at = ((size_t)bh * NBITS + bit0) * DV + c0 + col;
@@ -517,7 +480,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             const uint64_t *here = q_codes + ((size_t)bh * Nq + min((tile0 + tm) * 32 + m, Nq - 1)) * W;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                const uint64_t wd = kCodesAhead<TM, W, ZO> ? first[tm][w] : here[w];
+                const uint64_t wd = kCodesAhead<TM, W, ZO> ? next[tm][w] : here[w];
                 code[tm][2 * w] = (uint32_t)wd;
                 code[tm][2 * w + 1] = (uint32_t)(wd >> 32);
             }
@@ -536,7 +499,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                 code[tm][q] = ZO ? code[tm][q] >> (4 * kg) : code[tm][q] << (4 - 4 * kg);
             }
         }
-        if (kCodesAhead<TM, W, ZO> && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, first);
+        if (kCodesAhead<TM, W, ZO> && tile0 + NW * TM < tile_end) load_codes<W, TM>(q_codes, bh, Nq, tile0 + NW * TM, next);
         v16f acc[TM][JT];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
@@ -611,17 +574,17 @@ template <int DVC, int W, int NW, int TM, bool ZO>
 __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f, int H, int Nq, int DV,
                                                            long BH, int blocks_per_bh, int tiles_per_block) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[QkvLds<DVC, W, ZO>::BYTES];
-    uint64_t first[TM][W];
-    const int tile0 = blockIdx.x % blocks_per_bh * tiles_per_block + (threadIdx.x >> 6) * TM;
-    if constexpr (kCodesAhead<TM, W, ZO>) load_codes<W, TM>(q_codes, blockIdx.x / blocks_per_bh / (DV / DVC), Nq, tile0, first);
-    qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds, first);
+    qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------- both, short sequences ----
-// One workgroup does K^T V and Q(K^T V) of a (b, h) and DVC columns; K^T V goes from its sums to the second product's planes
-// without leaving the CU (it is written for the caller as well).  Bound by latency for few sequences: 1 x 3 heads x 197 tokens x 64 bits 10.6 us in
+// One workgroup does K^T V and Q(K^T V) of a (b, h) and DVC columns; what it reads of K^T V it wrote itself (splits = 1), so
+// a barrier is all the order that takes.  Bound by latency for few sequences: 1 x 3 heads x 197 tokens x 64 bits 10.6 us in
 // two launches, 7.5 in one; K^T V comes back from the caches it was just written to with many: 64 x 12 x 197 x 128 bits
-// 33.2 -> 29.1, 64 x 3 x 197 x 64 bits 13.7 -> 9.9.
+// 33.2 -> 29.1, 64 x 3 x 197 x 64 bits 13.7 -> 9.9.  Kept in registers from the sums to the second product's planes, and the
+// first queries' codes beside it, K^T V gained nothing for few sequences, and with many, which share a CU by twos at 128
+// registers, it was slower (64 x 12 x 197 x 128 bits, 129 registers, 30.7 -> 39.1 us; x 64 bits 21.2 -> 22.4; 64 x 3 x 197 x 64
+// 9.1 -> 10.0).
 template <int DVC, int W, int PH, int WB, int RING>
 __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
                                                                  float *kv, const uint64_t *__restrict__ q_codes, AddFused f,
@@ -629,10 +592,9 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t 
     constexpr int KB = KtvLds<DVC, WB, RING, false>::BYTES, QB = QkvLds<DVC, W, false>::BYTES;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[KB > QB ? KB : QB];
     static_assert(kKtvWaves / PH * WB == W, "a workgroup has all words");
-    uint64_t first[1][W];
-    if constexpr (kCodesAhead<1, W, false>) load_codes<W, 1>(q_codes, blockIdx.x / (DV / DVC), Nq, threadIdx.x >> 6, first);
-    ktv_block<DVC, WB, PH, RING, false, true>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
-    qkv_block<DVC, W, kKtvWaves, 1, false, true>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds, first);
+    ktv_block<DVC, WB, PH, RING, false>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
+    __syncthreads();
+    qkv_block<DVC, W, kKtvWaves, 1, false>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds);
 }
 
 // How the token tiles of a (b, h) are spread.

@@ -53,9 +53,22 @@ def kernels():
 
 @pytest.mark.parametrize("pattern,instances", [
     (r"qkv_mfma_kernel", 12),
+    (r"ktv_mfma_kernel|ktv_qkv_kernel", 28),
 ])
 def test_no_scratch(kernels, pattern, instances):
     some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
     assert len(some) == instances
     for n, k in some.items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
+
+
+# two workgroups of eight wavefronts to a CU: K^T V, alone or with Q(K^T V), for many short sequences (a ring of two)
+@pytest.mark.parametrize("pattern,instances", [
+    (r"ktv_qkv_kernelILi\d+ELi\d+ELi\d+ELi\d+ELi2EE", 4),
+    (r"ktv_mfma_kernelILi\d+ELi\d+ELi\d+ELi2ELb[01]EE", 8),
+])
+def test_registers_for_two_workgroups(kernels, pattern, instances):
+    some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
+    assert len(some) == instances
+    for n, k in some.items():
+        assert k[".vgpr_count"] <= 128, n
