@@ -84,3 +84,9 @@ def test_rows_of_a_ragged_step_more_than_4_gib_apart(sa, Nq):
 @pytest.mark.parametrize("W", [1, 2, 4])
 def test_passes_of_sixteen_wavefronts(sa, W):
     test_both_code_modes_against_fp64(sa, 8, 4, 8200, 40, W, 64)
+
+
+# K^T V in two, three, five and six partials, summed by Q(K^T V)
+@pytest.mark.parametrize("H,N,W,dv", [(12, 137, 4, 64), (8, 300, 4, 32), (3, 1200, 2, 32), (2, 1500, 1, 64)])
+def test_a_few_partials(sa, H, N, W, dv):
+    test_both_code_modes_against_fp64(sa, 1, H, N, N, W, dv)
