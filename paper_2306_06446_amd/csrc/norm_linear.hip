@@ -9,7 +9,7 @@
 // read again.  Layer, two launches -> one:
 //   25088 x  64 (32 images)  42.3 -> 39.0 us     65536 x  64   70.9 -> 62.6
 //   25088 x 128              68.6 -> 64.8        65536 x 128  126.6 -> 112.0
-//   25088 x 192             109.4 -> 99.4        65536 x 192  204.2 -> 195.9
+//   25088 x 192             109.0 -> 98.9        65536 x 192  204.0 -> 194.1
 //   16384 x 256             113.8 -> 106.3       65536 x 256  257.4 -> 250.5
 #include "common.h"
 #include "gemm_common.h"
@@ -58,13 +58,13 @@ __global__ __launch_bounds__(kWaves * 64) void norm_linear_kernel(NormRows norm,
     constexpr int LPR = NE == 1 ? 16 : NE == 2 ? 32 : 64, GROUPS = 64 / LPR, STEPS = kRows / kWaves / GROUPS;
     const int l = lane % LPR, row0 = wave * (kRows / kWaves) + lane / LPR;
     const bool in = 4 * l < E;
-    const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int col = min(4 * l, E - 4);                                   // (lanes past the row: its end, not used; see row_or_zero)
     float4 xr[STEPS];
 #pragma unroll
     for (int i = 0; i < STEPS; ++i)
-        xr[i] = in ? *reinterpret_cast<const float4 *>(norm.x + (size_t)min(m0 + row0 + GROUPS * i, n_rows - 1) * E + 4 * l) : none;
-    const float4 gamma = in ? *reinterpret_cast<const float4 *>(norm.gamma + 4 * l) : none;
-    const float4 beta = in ? *reinterpret_cast<const float4 *>(norm.beta + 4 * l) : none;
+        xr[i] = *reinterpret_cast<const float4 *>(norm.x + (size_t)min(m0 + row0 + GROUPS * i, n_rows - 1) * E + col);
+    const float4 gamma = *reinterpret_cast<const float4 *>(norm.gamma + col);
+    const float4 beta = *reinterpret_cast<const float4 *>(norm.beta + col);
 
     // unit u: plane u % 2 of columns u / 2 ROWS ..
     auto issue = [&](int u, int slot) {
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kWaves * 64) void norm_linear_kernel(NormRows norm,
 
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
-        const float4 x[1] = {xr[i]};
+        const float4 x[1] = {row_or_zero(xr[i], in)};
         float mean, rstd, y[4];
         row_stats<LPR, 1>(x, l, E, norm.eps, mean, rstd);
         normalise(x[0], mean, rstd, gamma, beta, y);

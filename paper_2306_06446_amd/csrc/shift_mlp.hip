@@ -10,8 +10,8 @@
 //      25088 x  64, 512 hidden   20.0 -> 10.1 us     131072 x  64   49 -> 33
 //      25088 x 192, 768 hidden   30 -> 24            131072 x 192  112 -> 93
 //      16384 x 256, 1024 hidden  31 -> 26            131072 x 256  161 -> 145
-// A layer's LayerNorm in front of it costs a workgroup its rows as fp32 and 4 MI of them per wavefront to normalise, beside the
-// first weights' way in, and saves the launch that wrote the codes: layer of 32 x 784 tokens x 64 52.1 -> 47.1 us, of 1 x 16384
+// A layer's LayerNorm in front of it costs a workgroup its rows as fp32, asked for ahead of the first weights, and 4 MI of them per
+// wavefront to normalise, and saves the launch that wrote the codes: layer of 32 x 784 tokens x 64 52.1 -> 47.1 us, of 1 x 16384
 // x 256 122 -> 115.  With prepared weights the output projection in front of the LayerNorm is made here too, from all of Wo in
 // LDS: at E = 64 it costs this launch 0.5 us and saves one of 5.7 (layer 47.1 -> 42.1 us), at E = 256 7.4 of 9.4 (121.9 -> 120.6).
 // Layer 1 on four wavefronts and layer 2 on the other four (requantiser beside products without being interleaved): 226 us
@@ -96,15 +96,14 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     const int l = lane % LPR, norm_row = wave * 4 * MI + lane / LPR;          // this lane's columns 4 l .. + 3 of rows norm_row + GROUPS i
     float4 xr[NORM ? STEPS : 1], gamma, beta;
     if constexpr (NORM) {
-        const bool in = 4 * l < E;
-        const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const int col = min(4 * l, E - 4);                   // (lanes past the row: its end, not used; see row_or_zero)
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
             const long m = min(m0 + norm_row + GROUPS * i, n_rows - 1);
-            xr[i] = in ? *reinterpret_cast<const float4 *>((PROJECT ? norm.residual : norm.x) + (size_t)m * E + 4 * l) : none;
+            xr[i] = *reinterpret_cast<const float4 *>((PROJECT ? norm.residual : norm.x) + (size_t)m * E + col);
         }
-        gamma = in ? *reinterpret_cast<const float4 *>(norm.gamma + 4 * l) : none;
-        beta = in ? *reinterpret_cast<const float4 *>(norm.beta + 4 * l) : none;
+        gamma = *reinterpret_cast<const float4 *>(norm.gamma + col);
+        beta = *reinterpret_cast<const float4 *>(norm.beta + col);
     }
 #pragma unroll
     for (int i = 0; i < (ROWS == kNorm ? 0 : MI); ++i) {
@@ -204,7 +203,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     if constexpr (NORM) {                                    // the codes, by way of the hidden rows' place
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
-            const float4 v[1] = {xr[i]};
+            const float4 v[1] = {row_or_zero(xr[i], 4 * l < E)};
             float mean, rstd, y[4];
             row_stats<LPR, 1>(v, l, E, norm.eps, mean, rstd);
             normalise(v[0], mean, rstd, gamma, beta, y);

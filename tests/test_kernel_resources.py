@@ -54,6 +54,8 @@ def kernels():
 @pytest.mark.parametrize("pattern,instances", [
     (r"qkv_mfma_kernel", 12),
     (r"ktv_mfma_kernel|ktv_qkv_kernel", 28),
+    (r"norm_linear_kernel", 4),
+    (r"shift_mlp_kernel", 21),
 ])
 def test_no_scratch(kernels, pattern, instances):
     some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
