@@ -151,12 +151,14 @@ int launch(const NormRows &norm, long T, const int8_t *w, float scale, float *q,
 }  // namespace
 
 // Whether one launch is the faster way: with few rows, and so few workgroups, the weights take longer through each of them than
-// two launches (layer of 197 x 192: 41.4 against 35.1 us, 3152 x 192 59.0 against 54.1, 12608 x 192 68.9 against 69.8; 197 x 256
-// 43.8 against 35.4, 12608 x 256 80.8 against 80.7; 788 x 128 36.5 against 35.9, 1576 x 128 37.8 against 38.0).  At E = 64 they
-// are 24 KiB (197 rows: 22.8 against 24.9).
+// two launches.  Layers of 192, two launches against one: 197 rows 34.5 and 40.2 us, 9456 rows 56.9 and 59.2, 10000 rows 57.3 and
+// 59.0, 10500 rows 60.4 and 59.6, 12288 rows 64.5 and 63.0; of 256: 10240 rows 69.1 both, 12608 rows 72.9 and 72.3, 16384 rows
+// 80.5 and 75.6; 788 x 128 35.9 and 36.5, 1576 x 128 38.0 and 37.8.  At E = 64 they are 24 KiB (197 rows: 24.9 and 22.8).  (Where
+// a few CUs have one workgroup more than the others it is slower by up to 3 % all the same: 17000 x 192 81.6 and 83.9, 20000 x 192
+// 87.0 and 85.2.)
 bool sa::norm_linear_one_launch(long T, int E) {
     if (E > 256 || E % 64 != 0) return false;
-    return E == 64 || T >= (E == 128 ? 12L : 64L) * E;
+    return E == 64 || T >= (E == 128 ? 12L : 54L) * E;
 }
 
 int sa::launch_norm_linear(const NormRows &norm, long T, int E, const int8_t *wqkv_planes, float scale, float *q, float *k, float *v,
