@@ -792,31 +792,60 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
 
 // The same on packed weights, without the launch that decodes them (3 to 5 us): whether that is faster for max_rows rows (as
 // launch_gemm estimates them), and the launch.  A stage's weights come in as 32 bytes of a row instead of 128, which in the
-// K loop pays for their decoding; of the tiles those that leave registers for it:
-//  * 192 x 128, two per CU, for rows of 768 bytes and more once they make one and a half tiles per CU (12608 x 768 <- 3072,
-//    decode + planes against packed: 70 -> 66 us; 12608 x 768 <- 768 26.4 -> 22.6, with 128 x 64 24.7), unless an XCD's share
-//    is a little more than a round (16000 x 768 <- 768, 66 tiles for 64 places: 31.7 us, with 128 x 64 25.6; planes 29.7);
-//  * 128 x 64, three per CU (12608 x 1536 <- 384 33.5 -> 27.1, with 192 x 128 31.5; 12608 x 384 <- 1536 27.9 -> 24.1;
-//    100000 x 256 <- 64 27 -> 20.5; 3000 x 1024 <- 1024 16 -> 13.5);
+// K loop pays for their decoding; of the tiles those that leave registers for it (below: decode and planes, packed 128 x 64, packed
+// 192 x 128; us):
+//  * 192 x 128, two per CU, for rows of 768 bytes and more where that is the fuller way (packed_tall);
+//  * 128 x 64, three per CU (12608 x 1536 <- 384 33.5, 27.1, 31.5; 12608 x 384 <- 1536 25.9, 23.1, 23.0; 100000 x 256 <- 64 27, 20.5;
+//    3000 x 1024 <- 1024 16, 13.5);
 //  * where gemm_slice.h would take the planes, 64 x 64 for rows up to 1024 bytes (1379 x 3072 <- 768 22 -> 15; 965 x 768 <-
 //    3072 18 -> 21.6: those stay).
 // The planes stay
 //  * beyond 2^35 multiply-adds, 2^34 for rows of less than 768 bytes, where the decode is no longer worth its removal (65000 x
 //    3072 <- 768 333 against 346, 131072 x 256 <- 1024 86 against 89, 50000 x 1536 <- 384 87.9 against 92.8);
-//  * for rows of 2 KiB and more that do not make 192 x 128 tiles enough (11000 x 768 <- 3072 64.7 against 72.6; 8000 rows 46.8
-//    against 45.8), or of which only the device knows how many there are, so that the tiles are chosen for half of them (768 <-
+//  * for rows of 2 KiB and more that do not fill 192 x 128 tiles (11000 x 768 <- 3072 64.7 against 72.6; 25088 x 512 <- 2048 61.6
+//    against 68.4), or of which only the device knows how many there are, so that the tiles are chosen for half of them (768 <-
 //    3072, 8826 of 12608 rows 51.4 against 55.1, 17561 of 25088 91 against 100; 3072 <- 768 of the same 53.4 against 48.8 and 91.5
 //    against 86.3, 384 <- 1536 23.4 against 23.7);
-//  * for rows of 1 KiB and more whose planes make exactly one round of 256 x 128 tiles (40000 x 384 <- 1536 47.3 against 54.4,
-//    50000 x 256 <- 1024 34.2 against 39.5; 32000 and 40000 rows of the same, more and less than that, 49.1 against 38.2 and 28.9
-//    against 27.1).
+//  * for rows of 1 KiB and more that do not, but make more than a round of the larger tiles of the planes (40000 x 384 <- 1536 47.2,
+//    58.1, 55.8; 50000 x 384 <- 1536 69.4, 74.0, 72.5; 131072 x 256 <- 1024 73.9, 83.8, 80.3; 32000 x 1024 <- 1024 74.7, 81.4, 77.6);
+//    where half of the last tile's columns would be padding, only with no more than one (40000 x 320 <- 1280 40.6, 43.0, 46.7;
+//    50000 x 320 <- 1280 55.2, 50.2, 59.7).
+// 192 x 128 tiles: an XCD takes 32 of them, one on each CU, and 32 more beside those in not much more time.  The fullest XCD's come
+// in `halves` of 32, and all eight XCDs lack `lack` tiles to fill as many:
+//  * the second half to run beside a first may lack 20 (12608 x 768 <- 768, 50 of 64: 26.3, 23.1, 22.6; 25088 x 384 <- 1536, 49: 42.1,
+//    40.2, 36.3; 16000 x 512 <- 1024, 42: 24.7, 21.7, 25.9);
+//  * the third, alone behind two others, 10 (45000 x 384 <- 1536, 88 of 96: 62.7, 66.6, 57.1; 65536 x 256 <- 1024, 86: 39.7, 42.2, 41.6);
+//  * the fourth 22 (28000 x 768 <- 768, 110 of 128: 46.7, 43.3, 41.9; 25088 rows, 98: 39.2, 39.1, 41.2);
+//  * the fifth and sixth 30 with rows of less than 1 KiB (80000 x 384 <- 768, 156 of 160: 60.8, 63.2, 56.9; 65536 rows, 128: 51.2, 48.9,
+//    52.8; 14500 x 2304 <- 768, 171 of 192: 71.6, 67.9, 63.3; 40000 x 768 <- 768, 157: 59.3, 60.5, 62.3), else any and 17 (25088 x 1024
+//    <- 1024, 131 of 160: 70.0, 66.8, 67.6; 65536 x 512 <- 1024, 171 of 192: 74.2, 84.3, 80.8);
+//  * from the seventh on any (25088 x 1536 <- 768: 78.7, 76.0, 73.9).
+// Where half of the last tile's columns would be padding only up to four halves, and less (32000 x 320 <- 1280, 63 of 64: 35.9, 34.9,
+// 32.6; 25088 rows, 49: 29.7, 25.9, 30.6; 60000 rows, 117 of 128: 63, 62.0, 59.8; 80000 x 192 <- 768, 104 of 128: 37.5, 33.3, 43.0).
+inline bool packed_tall(long m_est, int N, int K) {
+    const long row_tiles = (m_est + 191) / 192, col_tiles = (N + 127) / 128;
+    const long halves = ((row_tiles + 7) / 8 * col_tiles + 31) / 32, lack = 256 * halves - row_tiles * col_tiles;      // of all XCDs
+    if (K < 768 || halves < 2) return false;
+    if (N % 128 > 0 && N % 128 <= 64) return halves == 3 ? N > 256 && lack <= 8 * 6 : lack <= 8 * 12 && halves <= (N > 256 ? 4 : 2);
+    switch (halves) {
+        case 2: return lack <= 8 * 20;
+        case 3: return lack <= 8 * 10;
+        case 4: return lack <= 180;
+        case 5: return K >= 1024 || lack <= 8 * 30;
+        case 6: return lack <= 8 * (K >= 1024 ? 17 : 30);
+    }
+    return true;
+}
+
 inline bool packed_gemm(long max_rows, bool counted, int N, int K) {
     const long m_est = counted ? (max_rows + 1) / 2 : max_rows;
     auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((N + bn - 1) / bn); };
     if (K % 64 != 0 || (double)m_est * N * K > (K < 768 ? 17179869184.0 : 34359738368.0)) return false;
     if (tiles(64, 64) <= 640) return K <= 1024;
-    if (K >= 2048) return !counted && tiles(192, 128) >= 384;
-    return !(K >= 1024 && tiles(128, 128) > 768 && tiles(256, 128) <= 512);
+    if (packed_tall(m_est, N, K)) return K < 2048 || !counted;
+    if (K >= 2048) return false;
+    const bool padded = N % 128 > 0 && N % 128 <= 64;
+    return !(K >= 1024 && tiles(128, 128) > 768 && (!padded || tiles(256, 128) <= 512));
 }
 
 template <class Store>
@@ -828,8 +857,7 @@ int launch_gemm_packed(const GemmArgs &g, const Store &store, hipStream_t st, co
     const long m_est = g.sel.counts ? (g.sel.max_rows + 1) / 2 : g.sel.max_rows;
     auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
     if (tiles(64, 64) <= 640) return launch_tile<NtTile<T, 64, 64, 64, 2, 1>, 4>(g, store, st, what);
-    const long per_xcd = ((m_est + 191) / 192 + 7) / 8 * ((g.N + 127) / 128);       // of 64 places
-    if (g.K >= 768 && tiles(192, 128) >= 384 && (g.K >= 2048 || per_xcd <= 64 || per_xcd > 80)) return launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
+    if (packed_tall(m_est, g.N, g.K)) return launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
     return launch_tile<NtTile<T, 128, 64, 64, 2, 1>, 3>(g, store, st, what);
 }
 

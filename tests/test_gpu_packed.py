@@ -22,7 +22,9 @@ def _case(M, K, N):
 @pytest.mark.parametrize("M,K,N", [
     (1, 64, 4), (64, 128, 64), (65, 192, 100), (197, 1024, 768), (1379, 960, 1028),      # 64 x 64
     (25088, 64, 192), (16385, 128, 256), (12608, 192, 580), (3001, 1088, 1024), (12608, 1536, 384),   # 128 x 64
-    (12609, 768, 772), (12608, 3072, 768), (13000, 832, 1000),                           # 192 x 128
+    (13000, 832, 1000), (40001, 768, 192), (16001, 768, 768),                            # 128 x 64: too little for 192 x 128
+    (12609, 768, 772), (12608, 3072, 768), (12000, 832, 1000), (32000, 1280, 320), (11001, 768, 1536),    # 192 x 128
+    (25001, 2048, 512), (50001, 1536, 384),                                              # the planes after all
 ])
 def test_packed_equals_planes(sa, M, K, N):
     g, x, w = _case(M, K, N)
