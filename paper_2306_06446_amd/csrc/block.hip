@@ -383,7 +383,7 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     sa::RowSel sel;
     rc = sa::validate_rows(&all, &sel);
     if (rc != SA_OK) return rc;
-    const bool one_launch = !moe && weights.variant == SA_VARIANT_MFMA_PREPARED && sa::shift_mlp_one_launch(sel, E, d->hid);
+    const bool one_launch = !moe && weights.variant == SA_VARIANT_MFMA_PREPARED && sa::shift_mlp_one_launch(sel, E, d->hid, sa::kMlpInLayer);
     const bool project = one_launch && d->shift_variant == SA_VARIANT_MFMA_PREPARED;
     if (!project) {
         rc = sa_shift_linear_f32(codes8, d->wo, T, E, E, d->shift_variant, d->o_scale, d->x, 1, d->y, nullptr, nullptr,

@@ -212,7 +212,8 @@ int expert_pair_linear(const ExpertPair &p, int K, int N, const int8_t *w_planes
 // Both layers of a Shift MLP in one launch, on decoded planes (shift_mlp.hip): whether it takes the shape, and the launch.
 // out: yf, gate, out_scale, accumulate.
 struct Epilogue;
-bool shift_mlp_one_launch(const RowSel &sel, int E, int hid);
+enum MlpCall { kMlpPacked, kMlpPrepared, kMlpInLayer };      // weights still to be decoded; decoded; the same, rows not normalised yet
+bool shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call);
 // fp32 rows [max_rows, E] whose LayerNorm, as int8 codes (static scale), an MLP takes: x, or, with wo (decoded planes [E, E]),
 // out = residual + scale * wo . codes, which the launch leaves there as well.
 struct NormRows {

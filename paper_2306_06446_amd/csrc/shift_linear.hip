@@ -575,7 +575,8 @@ extern "C" int sa_shift_mlp(const int8_t *xq, const sa_rows *rows, int E, int hi
 
     // both layers in this call on the matrix cores: their 4-bit weights are decoded by one launch, unless both take them packed
     const int v_eff = variant == SA_VARIANT_AUTO ? SA_VARIANT_MFMA : variant;      // E and hid are multiples of 64
-    const bool one_launch = (stages & 3) == 3 && v_eff != SA_VARIANT_VALU && y_or_null && !y2_or_null && sa::shift_mlp_one_launch(sel, E, hid);
+    const bool one_launch = (stages & 3) == 3 && v_eff != SA_VARIANT_VALU && y_or_null && !y2_or_null &&
+                            sa::shift_mlp_one_launch(sel, E, hid, v_eff == SA_VARIANT_MFMA ? sa::kMlpPacked : sa::kMlpPrepared);
     const bool packed1 = sa::packed_gemm(sel.max_rows, sel.counts != nullptr, hid, E);
     const bool packed2 = sa::packed_gemm(sel.max_rows, sel.counts != nullptr, E, hid);
     // (one launch for both is soon worth more than two layers that decode for themselves: 12608 x 768, 3072 hidden 124.9 against

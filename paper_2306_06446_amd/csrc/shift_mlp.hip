@@ -443,17 +443,42 @@ int launch(const MlpArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// Whether one launch is the faster way.  A workgroup passes all weights through its CU, about 1 us per 128 hidden columns and 64
-// of E / 2, whatever its rows.  So for E = 64 and 128 with small products always (E * hid up to 96 Ki: 64 x 512, 1568 rows 11.8
-// apart against 9.1; layer of 33 x 128, 768 hidden 33.8 against 30.6, of 1000 39.5 against 38.8), with wider rows from where a good
-// part of the chip has some (layer of 192, 512 hidden: 1000 rows 41.1 against 44.6, 3152 rows 51.5 both, 12608 rows 83.8 against
-// 65.4; 256, 384 hidden: 1000 rows 42.1 against 46.2, 3152 rows 54.4 against 53.5), for larger products once their rows fill half
-// of it (256 x 1024: 6272 rows 20 against 24, 12608 rows 30 against 25; 192 x 768: 6272 rows 16.5 against 15.9, 3136 rows 13.6
-// against 15.5).
-bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid) {
+// Whether one launch is the faster way, from sweeps over 197 .. 131072 rows, 256 .. 1536 hidden columns (two launches, one; us).
+//  * Few rows: a workgroup passes all weights through its CU, about 1 us per 128 hidden columns and 64 of E / 2, whatever its rows.
+//    So for E = 64 and 128 with small products always (E * hid up to 96 Ki: 64 x 512, 1568 rows 11.8 and 9.1; layer of 33 x 128, 768
+//    hidden 33.8 and 30.6), with wider rows from where a good part of the chip has some (layer of 192, 512 hidden: 2400 rows 46.5
+//    and 48.2, 3152 rows 51.4 and 50.1; 256, 384 hidden: 1000 rows 42.1 and 46.2, 3152 rows 54.4 and 53.5), for larger products
+//    once their rows fill half of it (192 x 768: 6304 rows 16.4 and 15.6, layer 60.4 and 57.2, on packed weights 61.5 and 61.4;
+//    192 x 1024 layer 6304 rows 66.1 and 66.6), beyond 1024 hidden columns a little more (128 x 1536: 7168 rows 0.985, 9216 rows
+//    1.39 times as fast in one).
+//  * On packed weights one launch needs another that decodes them, where two layers decode for themselves: only with enough hidden
+//    columns (12608 rows of 256: 384 hidden 0.93 times, 512 0.94, 640 0.98, 768 0.96, of 16384 1.00; of 128: 256 0.98, 512 1.10).
+//  * Beyond 16384 rows a workgroup has 128 and a CU one workgroup, so the launch takes whole rounds of 32768 rows, and what the last
+//    round lacks costs as much as what it has: 256 x 1024, 32768 rows 1.26 times as fast in one, 33000 rows (two rounds) 50.1 and
+//    71.1, 40000 57.6 and 69.3, 53000 67.5 and 70.0, 57000 the same, 65536 1.10, 82000 (three) 98.6 and 100, 90000 1.06.  Narrower
+//    rows stand more of it, as two launches take longer with them, and more rounds (192 x 768: 40000 rows 42.4 and 43.7, 48000 1.03,
+//    76000 1.05; 128 x 512: 40000 22.9 and 25.3, 48000 1.01, 76000 1.13), and hidden columns that are no power of two, whose tiles
+//    the two launches fill less well (128 x 768: 40000 rows 37.1 and 33.4; 256 x 768: 20000 rows 31.5 and 28.3, 256 x 1024 33.0 and
+//    34.3).  On packed weights a little less.
+//  * In a layer the LayerNorm's launch is saved as well: only a second round that is nearly empty costs more than that (33000 x 256,
+//    1024 hidden 169.5 and 186.6, 40000 187.7 and 199.2 on packed weights, 44000 1.03; 40000 x 256, 1536 hidden 235 and 217; 33000 x
+//    192, 768 hidden 145.9 and 156, 44000 1.01; 33000 x 128, 512 hidden 1.02; 70000 x 256, three rounds, 1.06).
+// A row count that only the device knows may be anything up to its bound: no rounds to speak of.
+bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
     if (E > 256 || E % 64 != 0 || hid % kHidChunk != 0 || hid < 2 * kHidChunk) return false;
-    if ((long)E * hid > 98304) return sel.max_rows >= 40L * E;
-    return E <= 128 || sel.max_rows >= 16L * E;
+    const long rows = sel.max_rows;
+    if ((long)E * hid > 98304 ? rows < 40L * E : E > 128 && rows < 16L * E) return false;
+    if (E == 64) return true;
+    if (call == kMlpPacked && hid < (E == 256 ? 640 : 384)) return false;
+    if (call != kMlpInLayer && hid > 1024 && rows < 9000) return false;
+    if (rows <= 16384 || sel.counts) return true;
+    const long round = 32768, rounds = (rows + round - 1) / round, idle = 100 * (rounds * round - rows) / round;      // in % of a round
+    const bool packed = call == kMlpPacked, power = (hid & (hid - 1)) == 0;
+    if (call == kMlpInLayer) return E == 128 || rounds != 2 || idle <= (power ? 70 : 80);
+    if (E == 128) return idle <= (power ? 35 : 50) + 15 * rounds;
+    if (E == 256) return idle <= (packed ? 25 : rounds == 1 && !power ? 46 : 35);
+    if (rounds == 1) return idle <= (packed ? 35 : 50);
+    return idle <= (!packed ? 35 + 12 * rounds : hid < 768 ? 20 + 15 * rounds : 35 + 16 * rounds);
 }
 
 // Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the

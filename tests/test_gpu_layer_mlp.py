@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
     (1, 500, 4, 256, 384), (1, 10241, 4, 256, 1024), (7, 2801, 4, 256, 512), (9, 3001, 2, 128, 640),
     (4, 3101, 3, 192, 256), (1, 1537, 2, 128, 256), (6, 2801, 3, 192, 256),
     (1, 10367, 3, 192, 256), (1, 10368, 3, 192, 256),                       # either side of where Q, K, V take the LayerNorm in
+    (1, 33001, 4, 256, 512), (1, 42599, 4, 256, 512),                       # a second round of rows nearly empty, and less so
 ])
 def test_normalised_rows_stay_on_the_chip(sa, B, N, H, E, hid):
     g = torch.Generator(device="cuda")

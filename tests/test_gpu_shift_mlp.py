@@ -47,3 +47,10 @@ def test_one_launch_equals_the_two_layers(sa, rows, E, hid):
     ref = oracle.shift_mlp(host(xq[-n:]), host(w1), host(w2), rq, host(lut))
     got = host(go((3,), (p1, p2), 3)[-n:])
     assert np.array_equal(got, np.float32(out_scale) * np.asarray(ref).astype(np.float32))
+
+
+# either side of the sizes from which two launches are the faster way: the last round of one nearly empty, or nearly full
+@pytest.mark.parametrize("rows,E,hid", [(16385, 256, 512), (21299, 256, 512), (32769, 256, 256), (32769, 192, 512), (45000, 192, 768),
+                                        (32769, 128, 768), (46000, 128, 256)])
+def test_the_last_round_of_rows(sa, rows, E, hid):
+    test_one_launch_equals_the_two_layers(sa, rows, E, hid)
