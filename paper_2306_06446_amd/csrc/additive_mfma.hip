@@ -377,13 +377,14 @@ __device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes,
     }
 }
 
-// Whether the codes of a wavefront's next tiles are asked for while it multiplies these: with several passes over two tiles (8 x 4 x
-// 16384 queries, {0,1} codes of 64 bits 29.9 -> 28.5 us, of 128 bits 37.4 -> 36.5).  Not {0,1} codes of 256 bits, for which 16
-// wavefronts do not leave the 16 registers: 22 of 128 were spilled on every tile's way (8 x 4 x 16384 queries 53.7 us at a tile's
-// start, 64.8 ahead; 64 x 12 x 1100 queries 112 and 139).  Nor the one tile of a wavefront of the smaller workgroups, where there
-// is nothing to hide it behind but registers to lose (64 x 12 x 197 queries of 64 bits 12.1 against 12.7 us, {0,1} 16.3 against 17.4).
+// Whether the codes of a wavefront's first tiles are asked for ahead of K^T V's planes, and those of the next ones while it multiplies
+// these (32 x 3136 tokens x 1 head x 64 bits, both products 25.1 -> 24.7 us; {0,1} codes, Q(K^T V) of 8 x 4 x 16384 queries x 64 bits
+// 29.9 -> 28.5, x 128 bits 37.4 -> 36.5).  Not {0,1} codes of 256 bits, for which 16 wavefronts do not leave the 16 registers: 22 of
+// 128 were spilled on every tile's way (8 x 4 x 16384 queries 53.7 us at a tile's start, 64.8 ahead; 64 x 12 x 1100 queries 112 and
+// 139).  Nor {0,1} codes where a wavefront has one tile: the tables of the normaliser come first (64 x 12 x 197 queries x 64 bits 16.3
+// against 16.7 ahead).
 template <int TM, int W, bool ZO>
-constexpr bool kCodesAhead = TM > 1 && !(ZO && W == 4);
+constexpr bool kCodesAhead = ZO ? TM > 1 && W < 4 : true;
 
 // block = (bh * column groups + column group) * blocks_per_bh + part
 template <int DVC, int W, int NW, int TM, bool ZO>
