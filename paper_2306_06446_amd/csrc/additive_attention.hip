@@ -12,6 +12,8 @@
 //             workgroups, partial sums meet in LDS and then in a second pass,
 //             always in the same order.
 //   Q(K^T V): lane n  <-> token n, accumulators = the dv outputs of the token.
+#include <utility>
+
 #include "common.h"
 
 namespace {
@@ -179,7 +181,8 @@ __global__ __launch_bounds__(256) void den_kernel(const uint64_t *__restrict__ q
 // the grid left out.  i: 4-channel columns of (image, strip of RY rows, x), 32-bit with divisions by multiplication (SMALL), as
 // 64-bit divisions took longer than the loads: 32 images of 56 x 56 x 32 15.1 -> 10.4 us with them gone and RY = 4, where the
 // bytes (v, and out read and written) take 8.
-template <int RY, bool SMALL>
+// LINE: a grid of one row as a column of gw tokens (gh = gw, gw = 1 here), whose taps are those of the kernel's middle row.
+template <int RY, bool SMALL, bool LINE>
 __global__ __launch_bounds__(256) void dwconv3x3_kernel(const float *__restrict__ v, const float *__restrict__ w,
                                                         const float *__restrict__ bias, float *__restrict__ out, int accumulate,
                                                         long total, int gh, int gw, int E4, int strips, sa::FastDiv by_e4,
@@ -220,9 +223,9 @@ __global__ __launch_bounds__(256) void dwconv3x3_kernel(const float *__restrict_
 #pragma unroll
     for (int r = 0; r < RY + 2; ++r) {
         const float *p = vc + (size_t)min(max(y0 + r - 1, 0), gh - 1) * row;
-        n[r][0] = *reinterpret_cast<const float4 *>(p - (left ? E : 0));
+        if constexpr (!LINE) n[r][0] = *reinterpret_cast<const float4 *>(p - (left ? E : 0));
         n[r][1] = *reinterpret_cast<const float4 *>(p);
-        n[r][2] = *reinterpret_cast<const float4 *>(p + (right ? E : 0));
+        if constexpr (!LINE) n[r][2] = *reinterpret_cast<const float4 *>(p + (right ? E : 0));
     }
     float4 old[RY];
     if (accumulate) {
@@ -237,8 +240,8 @@ __global__ __launch_bounds__(256) void dwconv3x3_kernel(const float *__restrict_
         if (y0 + r >= gh) break;
         float acc[4] = {start[0], start[1], start[2], start[3]};
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int dy = t / 3 - 1, dx = t % 3 - 1;
+        for (int t = LINE ? 3 : 0; t < (LINE ? 6 : 9); ++t) {
+            const int dy = LINE ? t - 4 : t / 3 - 1, dx = LINE ? 0 : t % 3 - 1;
             const float4 nv = n[r + 1 + dy][dx + 1];
             const bool in = (dy == 0 || (dy < 0 ? y0 + r > 0 : y0 + r + 1 < gh)) && (dx == 0 || (dx < 0 ? left : right));
             const float x4[4] = {nv.x, nv.y, nv.z, nv.w};
@@ -570,9 +573,14 @@ extern "C" int sa_dwconv3x3(const float *v, const float *w, const float *bias_or
     SA_REQUIRE(v != out, SA_ERR_INVALID, "sa_dwconv3x3: out must not be v (neighbours are read after they would be written)");
     SA_REQUIRE(sa::aligned16(v) && sa::aligned16(w) && sa::aligned16(bias_or_null) && sa::aligned16(out), SA_ERR_ALIGN,
                "sa_dwconv3x3: pointers must be 16-byte aligned");
-    // Four outputs of a thread (1.5 loads of a neighbour each instead of 3 and 9) once that still gives every SIMD a wavefront.
+    // Outputs of a thread: four below each other (1.5 loads of a neighbour each instead of 3 and 9) once that still gives every SIMD
+    // a wavefront; two where there are only two rows (64 x 2 x 98 x 768 30.3 -> 27.8 us, 8 x 2 x 8192 x 256 75 -> 65, where one
+    // output each takes 38.8 and 107); of a single row four tokens beside each other (64 x 197 x 768 50.2 -> 15.8, 8 x 16384 x 256
+    // 137 -> 41, one each 37 and 105).  From three rows on four (64 x 3 x 66 x 768 24.7, one each 49).
     const long n = n_tokens * (E / 4);
-    const int ry = n >= 4L * 65536 ? 4 : 1, strips = (gh + ry - 1) / ry;
+    const bool many = n >= 4L * 65536, line = many && gh == 1;
+    if (line) std::swap(gh, gw);
+    const int ry = !many ? 1 : gh == 2 && !line ? 2 : 4, strips = (gh + ry - 1) / ry;
     const long total = (long)B * strips * gw * (E / 4), blocks = (total + 255) / 256;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_dwconv3x3: too many elements");
     const sa::FastDiv by_e4((uint32_t)(E / 4)), by_gw((uint32_t)gw), by_strips((uint32_t)strips);
@@ -581,7 +589,9 @@ extern "C" int sa_dwconv3x3(const float *v, const float *w, const float *bias_or
         kernel<<<dim3((unsigned)blocks), dim3(256), 0, sa::as_stream(stream)>>>(v, w, bias_or_null, out, accumulate, total, gh, gw, E / 4,
                                                                                 strips, by_e4, by_gw, by_strips);
     };
-    if (ry == 4) small ? go(dwconv3x3_kernel<4, true>) : go(dwconv3x3_kernel<4, false>);
-    else go(dwconv3x3_kernel<1, true>);
+    if (ry == 1) go(dwconv3x3_kernel<1, true, false>);
+    else if (line) small ? go(dwconv3x3_kernel<4, true, true>) : go(dwconv3x3_kernel<4, false, true>);
+    else if (ry == 2) small ? go(dwconv3x3_kernel<2, true, false>) : go(dwconv3x3_kernel<2, false, false>);
+    else small ? go(dwconv3x3_kernel<4, true, false>) : go(dwconv3x3_kernel<4, false, false>);
     return sa::check_launch("sa_dwconv3x3");
 }

@@ -775,3 +775,9 @@ def test_probe_runs_and_reports_its_clock(sa):
     assert 500.0 < cycles / ticks * 100.0 < 3500.0                    # MHz
     with pytest.raises(sa.SAError):
         sa.sa_probe_mfma(1, 2, 8, 10)                                 # Shift-like operands are int8 only
+
+
+# few rows, many outputs: one row as a column of tokens (a last strip of one to four), two rows, a strip that is not full
+@pytest.mark.parametrize("B,gh,gw,E", [(1, 1, 8193, 128), (5, 1, 6555, 32), (2, 1, 4098, 132), (3, 2, 1401, 128), (1, 3, 2741, 132), (7, 5, 937, 32)])
+def test_dwconv3x3_of_few_rows(sa, B, gh, gw, E):
+    test_dwconv3x3_matches_oracle(sa, B, gh, gw, E)
