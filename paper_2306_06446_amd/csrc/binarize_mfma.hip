@@ -18,9 +18,11 @@
 // A load instruction takes 32 bytes of each of the 32 rows, so that its first use of a line asks for all rows' lines at
 // once; the operands, which want 64 bytes of 16 rows, are put together by lane swaps after the split.  Loaded as 64 bytes of
 // 16 rows, the attention of 32 x 3136 tokens x 1 head x 32 with 64 bits takes 25.2 us (24.5 now).
-// At 256 columns more rows than the L2s hold are loaded as a stream: the products hide most of it, and V, which K^T V reads
-// next, stays in the caches (block of 1 x 16384 tokens x 4 heads 132.4 -> 128.9 us; at 64 columns the wait shows, 24.5 -> 28.4, and
-// with few rows: attention of 4 x 137 tokens x 12 heads 26.2 -> 28.2).
+// At 256 columns rows that fill the memory-side cache (256 MiB) by themselves are loaded as a stream: the products hide most of it,
+// and V, which K^T V reads next, stays there (block of 8 x 16384 tokens x 4 heads, 256 MiB of Q and K, 382.1 -> 378.1 us, of 6 x
+// 16384 348.5 -> 345.2; without the MLP 215.5 -> 218.5).  Fewer are still there from whoever wrote them, or from the last pass: blocks
+// of 4 x 16384 tokens, 128 MiB, 199.5 us, as a stream 210.7; of 64 x 197 x 12 heads, 73 MiB, 200.8 and 206.6; the hash of those
+// alone 34.0 and 39.1.  At 64 columns the wait shows (24.5 -> 28.4).
 // Products of 32x32x16 took the same time here but more power, which the kernels around it paid for in clock.
 //
 // What bounds it: at 256 bits the products and the vector work in their shadow (16 funnel shifts and 8 three-way minima
@@ -32,8 +34,7 @@
 //   64 x 197 x 12 heads x 64 -> 128 bits  25.1 -> 23.6 us      64 x 197 x 12 x 64 -> 64  19.2 -> 18.6
 //   64 x 197 x 3 x 64 -> 64               10.0 ->  9.2          8 x 1000 x 3 x 128 -> 128  14.8 -> 14.7
 //   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3          1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
-//    1 x 16384 x 4 x 64 -> 256            20.4 -> 22.3          8 x 16384 x 4 x 64 -> 256  110 -> 112
-// The last line is what loading as a stream costs where nothing is read next.
+//    1 x 16384 x 4 x 64 -> 256            18.5 -> 17.4          8 x 16384 x 4 x 64 -> 256  110 -> 112 (as a stream; 104 without)
 #include "common.h"
 #include "hash_margin.h"
 #include "side_work.h"
@@ -440,8 +441,7 @@ int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &
     // what rides along comes behind the tiles: it fills the CUs that are done first
     const long more = (side_blocks(side, kWaves * 64) + nbits / C - 1) / (nbits / C);
     const dim3 grid((unsigned)(blocks + more), (unsigned)(nbits / C));
-    // what is hashed does not stay in the L2s (4 MiB each) anyway: see the top
-    const bool stream = C == 256 && n_total * 32 * D * 4 > (32L << 20);
+    const bool stream = C == 256 && n_total * 32 * D * 4 >= (192L << 20);       // see the top
 #define SA_HASH(STREAM_)                                                                                                          \
     binarize_mfma_kernel<D, C, kWaves, STREAM_><<<grid, dim3(kWaves * 64), 0, st>>>(                                              \
         ts, proj, (uint32_t)rows, map, nbits, (uint32_t)n_tiles, (uint32_t)n_total, (uint32_t)blocks, side)
