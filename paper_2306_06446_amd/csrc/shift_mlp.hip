@@ -34,8 +34,8 @@ __device__ inline v4i mma16(const uint4 &a, const uint4 &b, v4i c) {
 
 constexpr int kMlpWaves = 8, kHidChunk = 128;
 
-// NE: E / 64.  MI: 16-row tiles of a wavefront; the eight wavefronts stand 2 x 4 over rows x columns.
-template <int NE, int MI, class Store>
+// NE: E / 64.  MI: 16-row tiles of a wavefront; the eight wavefronts stand 2 x 4 over rows x columns.  PROJECT: the rows are made here.
+template <int NE, int MI, bool PROJECT, class Store>
 struct MlpShape {
     static constexpr int E = 64 * NE, BM = 32 * MI;
     static constexpr int PS = NE <= 2 ? 2 : 1;               // planes of a stage
@@ -44,13 +44,14 @@ struct MlpShape {
     static constexpr int STAGE = PS * PLANE, RING = 3, LOADS = PS * NE;
     static constexpr int PITCH = 64 * NE + 16;               // a staged output row of a wavefront's columns
     // (the table first: its offset is part of the instructions that read it)
-    static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk, SIDE = H + 2 * H_BYTES;
+    static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk;
+    static constexpr int WO_END = PROJECT ? STAGES + 2 * E * E : 0;      // Wo's planes, in the place of the stages and the hidden rows
+    static constexpr int SIDE = H + 2 * H_BYTES > WO_END ? H + 2 * H_BYTES : WO_END;
     static constexpr int LDS_BYTES = SIDE + OutSide<Store, BM>::BYTES;
     static_assert(BM * E <= 2 * H_BYTES, "codes of normalised rows in the place of the hidden rows");
-    static constexpr int PROJECT_BYTES = STAGES + 2 * E * E > LDS_BYTES ? STAGES + 2 * E * E : LDS_BYTES;      // Wo's planes at STAGES
     static_assert(BM * E * 4 <= RING * STAGE + 2 * H_BYTES, "projected rows in the place of the ring and the hidden rows");
     static_assert(kMlpWaves * 16 * PITCH <= RING * STAGE, "output staging reuses the ring");
-    static_assert(PROJECT_BYTES <= 160 * 1024, "LDS of a CU");
+    static_assert(SIDE >= WO_END && LDS_BYTES <= 160 * 1024, "what the outputs read is fetched before Wo; LDS of a CU");
 };
 
 // 16-byte chunk c of a row of E bytes in LDS: any 16 consecutive rows hit 16 different bank groups.
@@ -70,10 +71,10 @@ template <int NE, int MI, int ROWS, class Store>
 __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
                                                                    const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
                                                                    const int8_t *__restrict__ lut, float rq, Store store) {
-    using S = MlpShape<NE, MI, Store>;
     constexpr bool NORM = ROWS != kCodes, PROJECT = ROWS == kProject;
+    using S = MlpShape<NE, MI, PROJECT, Store>;
     constexpr int E = S::E, PS = S::PS, SPG = S::SPG, LOADS = S::LOADS;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[PROJECT ? S::PROJECT_BYTES : S::LDS_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[S::LDS_BYTES];
     const int32_t *rows;
     long n_rows;
     resolve_rows(sel, rows, n_rows);
@@ -486,6 +487,7 @@ bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
 // E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).
 int sa::launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                          const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
+    SA_REQUIRE(!norm || (!sel.rows && !out.gate), SA_ERR_INVALID, "sa_shift_mlp: rows to normalise are all rows, ungated");
     const MlpArgs a{x, norm, sel, hid, w1_planes, w2_planes, lut, requant_scale_finite(requant_scale), ShiftStore<kEpiScatterI32>(out)};
     auto rounds = [&](long rows) { return ((sel.max_rows + rows - 1) / rows + 255) / 256; };
     const bool tall = 29 * rounds(128) < 20 * rounds(64);
