@@ -78,6 +78,14 @@ inline float requant_scale_finite(float s) {
     return s;
 }
 
+// 16-byte chunk c of a row of 64 NE bytes in LDS: any 16 consecutive rows hit 16 different bank groups.
+template <int NE>
+__device__ inline int swizzle_row(int r, int c) {
+    if (NE == 4) return c ^ (r & 15);
+    if (NE == 2) return c ^ ((r >> 1) & 7);
+    return (c & ~3) | ((c & 3) ^ ((r >> 2) & 3));
+}
+
 // Row of the 32x32 accumulator tile that register r of lane `lane` holds; the column is lane % 32.
 __device__ inline int mfma32_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 

@@ -34,14 +34,6 @@ struct NormLinearShape {
     static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups to a CU");
 };
 
-// 16-byte chunk c of a row of E bytes in LDS: any 16 consecutive rows hit 16 different bank groups.
-template <int NE>
-__device__ inline int swizzle_row(int r, int c) {
-    if (NE == 4) return c ^ (r & 15);
-    if (NE == 2) return c ^ ((r >> 1) & 7);
-    return (c & ~3) | ((c & 3) ^ ((r >> 2) & 3));
-}
-
 template <int NE>
 __global__ __launch_bounds__(kWaves * 64) void norm_linear_kernel(NormRows norm, long n_rows, const int8_t *__restrict__ w, float scale,
                                                                   float *__restrict__ q, float *__restrict__ k, float *__restrict__ v) {

@@ -54,13 +54,6 @@ struct MlpShape {
     static_assert(SIDE >= WO_END && LDS_BYTES <= 160 * 1024, "what the outputs read is fetched before Wo; LDS of a CU");
 };
 
-// 16-byte chunk c of a row of E bytes in LDS: any 16 consecutive rows hit 16 different bank groups.
-template <int NE>
-__device__ inline int swizzle_w1(int r, int c) {
-    if (NE == 4) return c ^ (r & 15);
-    if (NE == 2) return c ^ ((r >> 1) & 7);
-    return (c & ~3) | ((c & 3) ^ ((r >> 2) & 3));
-}
 __device__ inline int swizzle_128(int r, int c) { return c ^ ((r >> 1) & 7); }
 
 // What the rows are: codes; fp32 rows, which every wavefront normalises its share of; or fp32 rows that the kernel makes first, as
@@ -120,7 +113,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
         for (int j = 0; j < NE * NE; ++j) {                  // 8 NE^2 KiB: the planes are one behind the other
             const int q = j * kMlpWaves + wave, c = q * 64 + lane, r = c / (4 * NE);
-            direct_load_16(norm.wo, (uint32_t)(r * E + swizzle_w1<NE>(r, c % (4 * NE)) * 16), lds_base + S::STAGES + q * 1024);
+            direct_load_16(norm.wo, (uint32_t)(r * E + swizzle_row<NE>(r, c % (4 * NE)) * 16), lds_base + S::STAGES + q * 1024);
         }
 #pragma unroll
         for (int i = 0; i < MI; ++i)
@@ -135,7 +128,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
                 for (int t = 0; t < NE; ++t) {
                     const int r = p * E + wc * 16 * NE + 16 * t + fr;
-                    const uint4 w = *reinterpret_cast<const uint4 *>(lds + S::STAGES + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+                    const uint4 w = *reinterpret_cast<const uint4 *>(lds + S::STAGES + r * E + swizzle_row<NE>(r, 4 * k + fg) * 16);
 #pragma unroll
                     for (int i = 0; i < MI; ++i) acc2[i][t] = mma16(w, xf[i][k], acc2[i][t]);
                 }
@@ -169,11 +162,11 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const int q = (wave * NE + i) * 64 + lane, r = q / (4 * NE);
-            lane1[i] = (uint32_t)(r * E + swizzle_w1<NE>(r, q % (4 * NE)) * 16);
+            lane1[i] = (uint32_t)(r * E + swizzle_row<NE>(r, q % (4 * NE)) * 16);
         }
     } else {
         const int r = lane / (4 * NE);
-        lane1[0] = (uint32_t)(r * E + swizzle_w1<NE>(r, lane % (4 * NE)) * 16);
+        lane1[0] = (uint32_t)(r * E + swizzle_row<NE>(r, lane % (4 * NE)) * 16);
     }
     // The stages in the order they are multiplied: layer 1 of chunk 0, then layer 1 of chunk c + 1 before layer 2 of chunk c.
     const int n_stages = 2 * chunks * SPG;
@@ -209,7 +202,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
             row_stats<LPR, 1>(v, l, E, norm.eps, mean, rstd);
             normalise(v[0], mean, rstd, gamma, beta, y);
             const int r = norm_row + GROUPS * i;
-            if (4 * l < E) *reinterpret_cast<uint32_t *>(lds + S::H + r * E + swizzle_w1<NE>(r, l / 4) * 16 + l % 4 * 4) = codes_of(y, norm.inv_scale);
+            if (4 * l < E) *reinterpret_cast<uint32_t *>(lds + S::H + r * E + swizzle_row<NE>(r, l / 4) * 16 + l % 4 * 4) = codes_of(y, norm.inv_scale);
         }
     }
     wait_loads_in_flight<(S::RING - 1) * LOADS>();
@@ -221,7 +214,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
             for (int k = 0; k < NE; ++k) {
                 const int r = wr * 16 * MI + 16 * i + fr;
-                xf[i][k] = *reinterpret_cast<const uint4 *>(lds + S::H + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+                xf[i][k] = *reinterpret_cast<const uint4 *>(lds + S::H + r * E + swizzle_row<NE>(r, 4 * k + fg) * 16);
             }
         wait_lds_reads();                                    // hidden rows come here behind the first layer's barriers
     }
@@ -242,7 +235,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const int p = (n * KS + q) / NE, k = (n * KS + q) % NE, r = wc * 32 + 16 * t + fr;
-                fb[par][2 * q + t] = *reinterpret_cast<const uint4 *>(lds + S::STAGES + slot * S::STAGE + p * S::PLANE + r * E + swizzle_w1<NE>(r, 4 * k + fg) * 16);
+                fb[par][2 * q + t] = *reinterpret_cast<const uint4 *>(lds + S::STAGES + slot * S::STAGE + p * S::PLANE + r * E + swizzle_row<NE>(r, 4 * k + fg) * 16);
             }
     };
     auto read2 = [&](int par, int p, int k) {
