@@ -34,13 +34,14 @@ def test_bits_are_the_chains(sa, B, N, H, d, nbits, kind):
         assert torch.equal(c, sa.sa_binarize(t, proj, nbits, variant=0))
 
 
+@pytest.mark.parametrize("N,nbits", [(4096, 128), (4128, 128), (4128, 256)])     # workgroups of 64, 128 and (d = 128 apart) 256 columns
 @pytest.mark.parametrize("d", [32, 64, 128])
-def test_bits_are_the_chains_at_the_margin(sa, d):
+def test_bits_are_the_chains_at_the_margin(sa, d, N, nbits):
     """Rows whose product with a column is about what the margin allows for, at the lengths between which rows split unscaled; rows
     whose upper and lower fp16 terms pull that product to different sides; columns whose squares underflow."""
     g = torch.Generator(device="cuda")
     g.manual_seed(d)
-    N, H, nbits = 4096, 2, 128
+    H = 2
     proj = torch.randn((d, nbits), generator=g, device="cuda")
     unit = (proj / proj.norm(dim=0)).double()
     col = torch.randint(0, nbits, (1, N, H), generator=g, device="cuda")
@@ -65,6 +66,14 @@ def test_bits_are_the_chains_at_the_margin(sa, d):
         sa.sa_binarize_pair(q, k, p, nbits, *codes)
         for t, c in zip((q, k), codes):
             assert torch.equal(c, sa.sa_binarize(t, p, nbits, variant=0))
+
+
+# either side of the 512 tiles of 32 rows (both tensors') up to which a workgroup has fewer columns, and, at 256, of the 192 MiB of rows
+# from which they are loaded as a stream
+@pytest.mark.parametrize("d,nbits,N", [(d, nbits, N) for d in (32, 64, 128) for nbits in (128, 256) for N in (8187, 8193)] +
+                         [(32, 256, 786399), (32, 256, 786401), (64, 256, 393183), (64, 256, 393185)])
+def test_either_side_of_the_rules(sa, d, nbits, N):
+    test_bits_are_the_chains(sa, 1, N, 1, d, nbits, "plain")
 
 
 @pytest.mark.parametrize("d,nbits", [(32, 64), (64, 64), (64, 192), (128, 64), (128, 320)])

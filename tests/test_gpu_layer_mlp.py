@@ -7,12 +7,14 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-# every width, both heights of a workgroup's rows (128 of 128 and more columns from 16385 rows on), rows that fill no workgroup
+# every width, both heights of a workgroup's rows (128 of 128 and more columns from 16385 rows on), rows that fill no workgroup; 194 rows
+# of 192 and 500 of 256 keep launches of their own
 @pytest.mark.parametrize("B,N,H,E,hid", [
     (1, 1, 1, 64, 256), (3, 77, 2, 64, 512), (1, 333, 2, 128, 256), (2, 97, 3, 192, 512), (5, 1601, 3, 192, 768),
     (1, 500, 4, 256, 384), (1, 10241, 4, 256, 1024), (7, 2801, 4, 256, 512), (9, 3001, 2, 128, 640),
     (4, 3101, 3, 192, 256), (1, 1537, 2, 128, 256), (6, 2801, 3, 192, 256),
     (1, 10367, 3, 192, 256), (1, 10368, 3, 192, 256),                       # either side of where Q, K, V take the LayerNorm in
+    (2, 1601, 3, 192, 384), (4, 4201, 3, 192, 640), (1, 4099, 4, 256, 384), (2, 8301, 4, 256, 640),     # odd numbers of hidden chunks
     (1, 33001, 4, 256, 512), (1, 42599, 4, 256, 512),                       # a second round of rows nearly empty, and less so
 ])
 def test_normalised_rows_stay_on_the_chip(sa, B, N, H, E, hid):

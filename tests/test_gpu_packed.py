@@ -22,8 +22,9 @@ def _case(M, K, N):
 @pytest.mark.parametrize("M,K,N", [
     (1, 64, 4), (64, 128, 64), (65, 192, 100), (197, 1024, 768), (1379, 960, 1028),      # 64 x 64
     (25088, 64, 192), (16385, 128, 256), (12608, 192, 580), (3001, 1088, 1024), (12608, 1536, 384),   # 128 x 64
-    (13000, 832, 1000), (40001, 768, 192), (16001, 768, 768),                            # 128 x 64: too little for 192 x 128
+    (13000, 832, 1000), (16001, 768, 768),                                               # 128 x 64: too little for 192 x 128
     (12609, 768, 772), (12608, 3072, 768), (12000, 832, 1000), (32000, 1280, 320), (11001, 768, 1536),    # 192 x 128
+    (40001, 768, 192), (12609, 832, 772), (12608, 2112, 768),                            # 192 x 128: a last column tile half full, odd stages
     (25001, 2048, 512), (50001, 1536, 384),                                              # the planes after all
 ])
 def test_packed_equals_planes(sa, M, K, N):
@@ -38,6 +39,12 @@ def test_packed_equals_planes(sa, M, K, N):
     a, = sa.sa_shift_linear_f32(x, w, 0.37, residual=res, variant=1)
     b, = sa.sa_shift_linear_f32(x, planes, 0.37, residual=res, variant=3)
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("M,K,N", [(65, 192, 101), (16385, 128, 257), (12609, 832, 771)])      # rows of outputs that are no whole 16 bytes
+def test_packed_odd_columns(sa, M, K, N):
+    _, x, w = _case(M, K, N)
+    assert torch.equal(sa.sa_shift_linear(x, w, variant=1), sa.sa_shift_linear(x, sa.sa_shift_planes_prepare(w), variant=3))
 
 
 def _dense(w):

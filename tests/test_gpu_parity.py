@@ -781,3 +781,10 @@ def test_probe_runs_and_reports_its_clock(sa):
 @pytest.mark.parametrize("B,gh,gw,E", [(1, 1, 8193, 128), (5, 1, 6555, 32), (2, 1, 4098, 132), (3, 2, 1401, 128), (1, 3, 2741, 132), (7, 5, 937, 32)])
 def test_dwconv3x3_of_few_rows(sa, B, gh, gw, E):
     test_dwconv3x3_matches_oracle(sa, B, gh, gw, E)
+
+
+# four outputs below each other in a last strip of one to four rows, one column of tokens, either side of the 2^18 items it takes
+@pytest.mark.parametrize("B,gh,gw,E", [(9, 57, 33, 64), (9, 58, 61, 64), (4, 63, 66, 64), (1, 64, 64, 256), (1, 64, 63, 256), (1, 8193, 1, 128),
+                                       (8193, 1, 1, 128), (2, 4099, 1, 132)])
+def test_dwconv3x3_in_strips(sa, B, gh, gw, E):
+    test_dwconv3x3_matches_oracle(sa, B, gh, gw, E)

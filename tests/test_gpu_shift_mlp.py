@@ -1,5 +1,6 @@
 """Both layers of a Shift MLP in one launch: bit-identical to the two layers one after the other (integers up to the one
-rounding of the output), and to the oracle, at every width and at the edges of its tiles, chunks and rules."""
+rounding of the output), and to the oracle, at every width and at the edges of its tiles, chunks and rules.  One launch leaves the
+workspace's hidden rows alone, which says whether it ran."""
 import numpy as np
 import pytest
 import torch
@@ -54,3 +55,40 @@ def test_one_launch_equals_the_two_layers(sa, rows, E, hid):
                                         (32769, 128, 768), (46000, 128, 256)])
 def test_the_last_round_of_rows(sa, rows, E, hid):
     test_one_launch_equals_the_two_layers(sa, rows, E, hid)
+
+
+# One launch on decoded weights for certain: odd and even numbers of chunks of 128 hidden columns, 64 and 128 rows of a workgroup,
+# all rows and a few that only the device counts.
+@pytest.mark.parametrize("T,E,hid", [(3101, 192, 384), (16437, 192, 640), (7681, 192, 768), (4101, 256, 384), (17837, 256, 640), (22001, 256, 1024),
+                                     (20001, 128, 384), (129, 128, 768)])
+def test_one_launch_it_is(sa, T, E, hid):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + E + hid)
+    xq = torch.randint(-127, 128, (T, E), generator=g, device="cuda", dtype=torch.int8)
+    w = [torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8) for s in ((hid, E // 2), (E, hid // 2))]
+    planes = [sa.sa_shift_planes_prepare(t) for t in w]
+    lut = torch.randint(-128, 128, (256,), generator=g, device="cuda", dtype=torch.int8)
+    rq = 127.0 / (4 * 40 * 73 * E ** 0.5)
+    perm = torch.randperm(T, generator=g, device="cuda").to(torch.int32)
+    gate = torch.rand(T, generator=g, device="cuda")
+    ws = torch.zeros(T * hid + 4 * E * hid + 4096, dtype=torch.uint8, device="cuda")
+    old = torch.randn((T, E), generator=g, device="cuda")
+
+    def go(stages, **kw):
+        y = old.clone()
+        for s in stages:
+            sa.sa_shift_mlp(xq, *planes, rq, lut, want_y2=False, y=y, out_scale=1e-3, variant=3, stages=s, workspace=ws, **kw)
+        return y
+    for kept in (None, 0, 1, 31, 65, 129):
+        kw = {}
+        if kept is not None:
+            kw = dict(rows=perm, counts=torch.tensor([T - kept, kept], dtype=torch.int32, device="cuda"), expert=1, max_rows=T, gate=gate)
+        ws.fill_(77)
+        got = go((3,), **kw)
+        assert bool((ws[:T * hid] == 77).all())
+        ref = go((1, 2), **kw)
+        assert torch.equal(got, ref)
+        assert kept == 0 or not bool((ws[:T * hid] == 77).all())
+        if kept is not None:
+            idle = perm[:T - kept].long()
+            assert torch.equal(got[idle], old[idle])
