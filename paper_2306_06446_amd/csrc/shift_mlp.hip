@@ -457,15 +457,27 @@ int launch(const MlpArgs &a, hipStream_t st) {
 //  * In a layer the LayerNorm's launch is saved as well: only a second round that is nearly empty costs more than that (33000 x 256,
 //    1024 hidden 169.5 and 186.6, 40000 187.7 and 199.2 on packed weights, 44000 1.03; 40000 x 256, 1536 hidden 235 and 217; 33000 x
 //    192, 768 hidden 145.9 and 156, 44000 1.01; 33000 x 128, 512 hidden 1.02; 70000 x 256, three rounds, 1.06).
-// A row count that only the device knows may be anything up to its bound: no rounds to speak of.
+//  * Of a row count that only the device knows any share of the bound may come, in one launch's rounds as in two launches: one only
+//    where it is not the slower way for 30, 50, 70 and all of them (two launches / one, prepared weights).  128 x 512: 33000 rows
+//    1.11, 1.54, 1.69, 1.21, 2000 rows 1.31 .. 1.25; 128 x 1536: 12608 rows 0.94, 1.08, 1.37, 1.57, 8000 rows 0.68 .. 1.26; on packed
+//    weights 128 x 768: 17000 rows 1.00, 1.19, 1.42, 1.04, 8000 rows 0.91 .. 1.12.  Beyond 128 columns only small products up to one
+//    round of 64 rows (192 x 384: 12608 rows 1.15, 1.25, 1.35, 1.77; 256 x 384 0.96, 1.10, 1.40, 1.66): 192 x 768, 12608 rows 0.84 ..
+//    1.59, 33000 rows 0.85, 1.15, 1.52, 0.90; 256 x 1024, 17000 rows 0.55 .. 1.18; and on packed weights not at all (256 x 2048, 30 % of
+//    26415 rows 65.2 us in one launch, 39.5 in two).
+static bool counted_one_launch(long rows, int E, int hid, bool packed) {
+    if (E <= 128) return (E == 64 || !packed || hid >= 384) && (hid <= (E == 64 ? 1536 : packed ? 512 : 768) || rows >= 96L * E);
+    return !packed && (long)E * hid <= 98304 && rows >= 16L * E && rows <= 16384;
+}
+
 bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
     if (E > 256 || E % 64 != 0 || hid % kHidChunk != 0 || hid < 2 * kHidChunk) return false;
     const long rows = sel.max_rows;
+    if (sel.counts) return counted_one_launch(rows, E, hid, call == kMlpPacked);
     if ((long)E * hid > 98304 ? rows < 40L * E : E > 128 && rows < 16L * E) return false;
     if (E == 64) return true;
     if (call == kMlpPacked && hid < (E == 256 ? 640 : 384)) return false;
     if (call != kMlpInLayer && hid > 1024 && rows < 9000) return false;
-    if (rows <= 16384 || sel.counts) return true;
+    if (rows <= 16384) return true;
     const long round = 32768, rounds = (rows + round - 1) / round, idle = 100 * (rounds * round - rows) / round;      // in % of a round
     const bool packed = call == kMlpPacked, power = (hid & (hid - 1)) == 0;
     if (call == kMlpInLayer) return E == 128 || rounds != 2 || idle <= (power ? 70 : 80);
@@ -477,12 +489,13 @@ bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
 
 // Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the
 // larger ones takes (256 x 1024: 16384 rows 26 against 36 us, 25088 rows 47 against 37, 131072 rows 181 against 145).  At
-// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).
+// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).  Of rows that only the device counts half are expected.
 int sa::launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                          const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
     SA_REQUIRE(!norm || (!sel.rows && !out.gate), SA_ERR_INVALID, "sa_shift_mlp: rows to normalise are all rows, ungated");
     const MlpArgs a{x, norm, sel, hid, w1_planes, w2_planes, lut, requant_scale_finite(requant_scale), ShiftStore<kEpiScatterI32>(out)};
-    auto rounds = [&](long rows) { return ((sel.max_rows + rows - 1) / rows + 255) / 256; };
+    const long m_est = sel.counts ? (sel.max_rows + 1) / 2 : sel.max_rows;
+    auto rounds = [&](long rows) { return ((m_est + rows - 1) / rows + 255) / 256; };
     const bool tall = 29 * rounds(128) < 20 * rounds(64);
     switch (E) {
         case 64: return launch<1, 2>(a, st);

@@ -57,11 +57,13 @@ def test_the_last_round_of_rows(sa, rows, E, hid):
     test_one_launch_equals_the_two_layers(sa, rows, E, hid)
 
 
-# One launch on decoded weights for certain: odd and even numbers of chunks of 128 hidden columns, 64 and 128 rows of a workgroup,
-# all rows and a few that only the device counts.
-@pytest.mark.parametrize("T,E,hid", [(3101, 192, 384), (16437, 192, 640), (7681, 192, 768), (4101, 256, 384), (17837, 256, 640), (22001, 256, 1024),
-                                     (20001, 128, 384), (129, 128, 768)])
-def test_one_launch_it_is(sa, T, E, hid):
+# One launch on decoded weights for certain: odd and even numbers of chunks of 128 hidden columns, 64 and 128 rows of a workgroup, all
+# rows and a few that only the device counts.  Those keep two launches where one would be slower for some of the counts.
+@pytest.mark.parametrize("T,E,hid,counted", [
+    (3101, 192, 384, True), (16437, 192, 640, False), (7681, 192, 768, False), (4101, 256, 384, True), (17837, 256, 640, False),
+    (22001, 256, 1024, False), (20001, 128, 384, True), (40001, 128, 640, True), (129, 128, 768, True), (12287, 128, 896, False),
+    (12288, 128, 896, True), (16384, 192, 512, True), (16385, 192, 512, False)])
+def test_one_launch_it_is(sa, T, E, hid, counted):
     g = torch.Generator(device="cuda")
     g.manual_seed(T + E + hid)
     xq = torch.randint(-127, 128, (T, E), generator=g, device="cuda", dtype=torch.int8)
@@ -79,13 +81,14 @@ def test_one_launch_it_is(sa, T, E, hid):
         for s in stages:
             sa.sa_shift_mlp(xq, *planes, rq, lut, want_y2=False, y=y, out_scale=1e-3, variant=3, stages=s, workspace=ws, **kw)
         return y
-    for kept in (None, 0, 1, 31, 65, 129):
+    for kept in (None, 0, 1, 31, 65, T // 3, T):
         kw = {}
         if kept is not None:
             kw = dict(rows=perm, counts=torch.tensor([T - kept, kept], dtype=torch.int32, device="cuda"), expert=1, max_rows=T, gate=gate)
         ws.fill_(77)
         got = go((3,), **kw)
-        assert bool((ws[:T * hid] == 77).all())
+        untouched = bool((ws[:T * hid] == 77).all())
+        assert kept == 0 or untouched == (counted or kept is None)
         ref = go((1, 2), **kw)
         assert torch.equal(got, ref)
         assert kept == 0 or not bool((ws[:T * hid] == 77).all())
