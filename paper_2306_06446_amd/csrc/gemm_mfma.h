@@ -675,14 +675,16 @@ struct NtTile {
     // but a B share that is evicted between row tiles costs more time than the extra A traffic.)  More groups where the L2s
     // fetch less in all with them, A col_groups times and B 8 / col_groups times: with few rows that fetch is what takes the time
     // (3152 x 3072 <- 768 27.6 -> 25.3 us, 2600 x 1536 <- 384 10.0 -> 8.8, 4000 x 1024 <- 1024 14.8 -> 13.7; block of 2364 tokens x
-    // 768 70.4 -> 65.4, layer of 1379 84.1 -> 83.3).
+    // 768 70.4 -> 65.4, layer of 1379 84.1 -> 83.3).  Not where rows of 32-bit outputs are no whole 128-byte lines: tiles beside each
+    // other then write the same lines from different L2s, and the last columns are shared out less evenly (5932 x 1784 <- 32 12.9 ->
+    // 17.3, 8393 x 1316 <- 192 18.6 -> 21.5; of 212 such shapes 60 lost more than 3 % and 37 gained it, of 61 others 1 and 12).
     static int col_groups(const GemmArgs &g) {
         const size_t b_bytes = T::kPacked ? (size_t)g.N * g.K / 2 : (size_t)T::kPlanes * g.N * g.K * T::kElemBytes;
         int cg = 1;
         while (cg < 8 && b_bytes / cg > (size_t)(5 << 19)) cg *= 2;     // 2.5 MiB
         const long col_tiles = (g.N + BN - 1) / BN;
         const double a_bytes = (double)g.sel.max_rows * g.K * T::kElemBytes;
-        while (cg < 8 && 2 * cg <= col_tiles && a_bytes * cg < b_bytes * (4.0 / cg)) cg *= 2;
+        while (g.N % 32 == 0 && cg < 8 && 2 * cg <= col_tiles && a_bytes * cg < b_bytes * (4.0 / cg)) cg *= 2;
         return cg;
     }
 };
