@@ -811,7 +811,12 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
 //  * for rows of 1 KiB and more that do not, but make more than a round of the larger tiles of the planes (40000 x 384 <- 1536 47.2,
 //    58.1, 55.8; 50000 x 384 <- 1536 69.4, 74.0, 72.5; 131072 x 256 <- 1024 73.9, 83.8, 80.3; 32000 x 1024 <- 1024 74.7, 81.4, 77.6);
 //    where half of the last tile's columns would be padding, only with no more than one (40000 x 320 <- 1280 40.6, 43.0, 46.7;
-//    50000 x 320 <- 1280 55.2, 50.2, 59.7).
+//    50000 x 320 <- 1280 55.2, 50.2, 59.7);
+//  * for rows up to 256 bytes with many outputs in rows that are no whole 128-byte lines, of which narrower tiles share more (planes,
+//    packed: 232794 x 116 <- 64 41.7, 52.5; 18272 x 1836 <- 128 50.8, 60.1; 48347 x 748 <- 256 56.2, 61.6; 53086 x 589 <- 64 52.8, 55.2;
+//    5831 x 3220 <- 192 34.3, 38.4; with fewer 8 to 13 % for packed on average);
+//  * for less than 64 columns and rows of 768 bytes and more, where the tile is mostly padding (93878 x 37 <- 768 21.3, 25.5; 185423 x
+//    10 <- 896 31.4, 33.9; 77000 x 64 <- 768 19.0, 16.0).
 // 192 x 128 tiles: an XCD takes 32 of them, one on each CU, and 32 more beside those in not much more time.  The fullest XCD's come
 // in `halves` of 32, and all eight XCDs lack `lack` tiles to fill as many:
 //  * the second half to run beside a first may lack 20 (12608 x 768 <- 768, 50 of 64: 26.3, 23.1, 22.6; 25088 x 384 <- 1536, 49: 42.1,
@@ -827,7 +832,7 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
 inline bool packed_tall(long m_est, int N, int K) {
     const long row_tiles = (m_est + 191) / 192, col_tiles = (N + 127) / 128;
     const long halves = ((row_tiles + 7) / 8 * col_tiles + 31) / 32, lack = 256 * halves - row_tiles * col_tiles;      // of all XCDs
-    if (K < 768 || halves < 2) return false;
+    if (K < 768 || N <= 64 || halves < 2) return false;
     if (N % 128 > 0 && N % 128 <= 64) return halves == 3 ? N > 256 && lack <= 8 * 6 : lack <= 8 * 12 && halves <= (N > 256 ? 4 : 2);
     switch (halves) {
         case 2: return lack <= 8 * 20;
@@ -844,6 +849,7 @@ inline bool packed_gemm(long max_rows, bool counted, int N, int K) {
     auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((N + bn - 1) / bn); };
     if (K % 64 != 0 || (double)m_est * N * K > (K < 768 ? 17179869184.0 : 34359738368.0)) return false;
     if (tiles(64, 64) <= 640) return K <= 1024;
+    if ((N < 64 && K >= 768) || (N % 32 != 0 && K <= 256 && m_est * N >= 15 << 20)) return false;
     if (packed_tall(m_est, N, K)) return K < 2048 || !counted;
     if (K >= 2048) return false;
     const bool padded = N % 128 > 0 && N % 128 <= 64;

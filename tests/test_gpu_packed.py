@@ -47,6 +47,19 @@ def test_packed_odd_columns(sa, M, K, N):
     assert torch.equal(sa.sa_shift_linear(x, w, variant=1), sa.sa_shift_linear(x, sa.sa_shift_planes_prepare(w), variant=3))
 
 
+# the workspace takes the planes of those layers alone that are decoded before they are multiplied: narrow rows of outputs in pieces
+# of lines, padded columns, and what lies beside either
+@pytest.mark.parametrize("M,K,N,decoded", [
+    (55000, 64, 290, True), (55000, 64, 288, False), (54000, 64, 290, False), (55000, 320, 290, False),
+    (60000, 768, 60, True), (60000, 768, 64, False), (60000, 704, 60, False), (40000, 768, 60, False)])
+def test_which_layers_are_decoded_first(sa, M, K, N, decoded):
+    _, x, w = _case(M, K, N)
+    ws = torch.full((2 * N * K,), 77, dtype=torch.uint8, device="cuda")
+    got = sa.sa_shift_linear(x, w, variant=1, workspace=ws)
+    assert bool((ws != 77).any()) == decoded
+    assert torch.equal(got, sa.sa_shift_linear(x, sa.sa_shift_planes_prepare(w), variant=3))
+
+
 def _dense(w):
     nib = torch.stack([w & 15, w >> 4], dim=-1).flatten(1).cpu().to(torch.int64)
     return (torch.where(nib >= 8, -1, 1) * (1 << (nib & 7))).numpy()
