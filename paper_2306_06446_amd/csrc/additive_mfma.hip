@@ -382,9 +382,10 @@ __device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes,
 // 29.9 -> 28.5, x 128 bits 37.4 -> 36.5).  Not {0,1} codes of 256 bits, for which 16 wavefronts do not leave the 16 registers: 22 of
 // 128 were spilled on every tile's way (8 x 4 x 16384 queries 53.7 us at a tile's start, 64.8 ahead; 64 x 12 x 1100 queries 112 and
 // 139).  Nor {0,1} codes where a wavefront has one tile: the tables of the normaliser come first (64 x 12 x 197 queries x 64 bits 16.3
-// against 16.7 ahead).
+// against 16.7 ahead), nor 256-bit codes there, whose registers cost a workgroup more (+-1, both products of 40 x 3 heads x 1024 tokens
+// x 64 49.5 us, 51.5 ahead; 64 x 1 x 3136 56.5, 58.5).
 template <int TM, int W, bool ZO>
-constexpr bool kCodesAhead = ZO ? TM > 1 && W < 4 : true;
+constexpr bool kCodesAhead = ZO ? TM > 1 && W < 4 : TM > 1 || W < 4;
 
 // block = (bh * column groups + column group) * blocks_per_bh + part
 template <int DVC, int W, int NW, int TM, bool ZO>
