@@ -418,26 +418,13 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
         float x[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = f.kv_in[at + ((e >> 1) + 16 * (e & 1)) * DV];
-        // (four partials in flight: one after the other they were as many round trips to memory.  A second one alone is not read
-        // four times: 4 x 12 heads x 137 tokens x 256 bits 17.7 -> 16.8 us)
-        const float *p = f.kv_in + at;
-        const size_t split = (size_t)BH * NBITS * DV;
-        if (f.splits == 2) {
+        // (partial by partial: four at a time in flight took longer, by the registers or by what is read in vain behind the last ones.
+        // 4 x 8 heads x 4237 tokens x 128 bits x 32, 17 workgroups to a head, both products 25.2 -> 23.9 us, 4 x 12 x 3072 x 64 bits
+        // 19.7 -> 18.8, 4 x 12 x 300 x 256 bits 17.0 -> 16.5; 32 x 1 x 3136 x 64 bits 15.5 -> 15.6)
+        for (int s = 1; s < f.splits; ++s) {
+            const float *p = f.kv_in + (size_t)s * BH * NBITS * DV + at;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] += p[split + ((e >> 1) + 16 * (e & 1)) * DV];
-        }
-        for (int s = 1; f.splits > 2 && s < f.splits; s += 4) {
-            float y[4][8];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) y[q][e] = p[(size_t)min(s + q, f.splits - 1) * split + ((e >> 1) + 16 * (e & 1)) * DV];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (s + q < f.splits) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] += y[q][e];
-                }
+            for (int e = 0; e < 8; ++e) x[e] += p[((e >> 1) + 16 * (e & 1)) * DV];
         }
         if (f.kv_out && part == 0) {
 #pragma unroll
