@@ -444,7 +444,9 @@ int launch(const MlpArgs &a, hipStream_t st) {
 //    and 48.2, 3152 rows 51.4 and 50.1; 256, 384 hidden: 1000 rows 42.1 and 46.2, 3152 rows 54.4 and 53.5), for larger products
 //    once their rows fill half of it (192 x 768: 6304 rows 16.4 and 15.6, layer 60.4 and 57.2, on packed weights 61.5 and 61.4;
 //    192 x 1024 layer 6304 rows 66.1 and 66.6), beyond 1024 hidden columns a little more (128 x 1536: 7168 rows 0.985, 9216 rows
-//    1.39 times as fast in one).
+//    1.39 times as fast in one), as for 256 columns (256 x 1024: 10500 rows 21.6 and 22.4, 11200 rows 22.4 and 22.6, 12000 rows 23.2
+//    and 22.6, packed 24.1 and 26.0, 15000 rows 27.1 and 26.4), and beyond 1536 not before the chip is full of them (256 x 2048: 12000
+//    rows 35.3 and 39.2, 15000 rows 39.6 both, 16384 rows 41.6 and 40.1; 192 x 2048: 10500 rows 29.6 and 32.6, 11200 rows 35.8 and 32.6).
 //  * On packed weights one launch needs another that decodes them, where two layers decode for themselves: only with enough hidden
 //    columns (12608 rows of 256: 384 hidden 0.93 times, 512 0.94, 640 0.98, 768 0.96, of 16384 1.00; of 128: 256 0.98, 512 1.10).
 //  * Beyond 16384 rows a workgroup has 128 and a CU one workgroup, so the launch takes whole rounds of 32768 rows, and what the last
@@ -476,7 +478,11 @@ bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
     if ((long)E * hid > 98304 ? rows < 40L * E : E > 128 && rows < 16L * E) return false;
     if (E == 64) return true;
     if (call == kMlpPacked && hid < (E == 256 ? 640 : 384)) return false;
-    if (call != kMlpInLayer && hid > 1024 && rows < 9000) return false;
+    if (call != kMlpInLayer) {
+        if (hid >= 1024 && E == 256 && rows < (call == kMlpPacked ? 14000 : 11000)) return false;
+        if (hid > 1536 && E > 128 && rows < (E == 256 ? 15000 : 11000)) return false;
+        if (hid > 1024 && rows < 9000) return false;
+    }
     if (rows <= 16384) return true;
     const long round = 32768, rounds = (rows + round - 1) / round, idle = 100 * (rounds * round - rows) / round;      // in % of a round
     const bool packed = call == kMlpPacked, power = (hid & (hid - 1)) == 0;

@@ -62,7 +62,8 @@ def test_the_last_round_of_rows(sa, rows, E, hid):
 @pytest.mark.parametrize("T,E,hid,counted", [
     (3101, 192, 384, True), (16437, 192, 640, False), (7681, 192, 768, False), (4101, 256, 384, True), (17837, 256, 640, False),
     (22001, 256, 1024, False), (20001, 128, 384, True), (40001, 128, 640, True), (129, 128, 768, True), (12287, 128, 896, False),
-    (12288, 128, 896, True), (16384, 192, 512, True), (16385, 192, 512, False)])
+    (12288, 128, 896, True), (16384, 192, 512, True), (16385, 192, 512, False), (11000, 256, 1024, False), (15000, 256, 2048, False),
+    (11000, 192, 2048, False)])
 def test_one_launch_it_is(sa, T, E, hid, counted):
     g = torch.Generator(device="cuda")
     g.manual_seed(T + E + hid)
@@ -95,3 +96,16 @@ def test_one_launch_it_is(sa, T, E, hid, counted):
         if kept is not None:
             idle = perm[:T - kept].long()
             assert torch.equal(got[idle], old[idle])
+
+
+@pytest.mark.parametrize("T,E,hid", [(10999, 256, 1024), (14999, 256, 2048), (10999, 192, 2048), (8999, 128, 1536)])
+def test_two_launches_they_are(sa, T, E, hid):
+    test_one_launch_equals_the_two_layers(sa, T - 37, E, hid)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    xq = torch.randint(-127, 128, (T, E), generator=g, device="cuda", dtype=torch.int8)
+    w = [sa.sa_shift_planes_prepare(torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8)) for s in ((hid, E // 2), (E, hid // 2))]
+    ws = torch.full((T * hid + 4 * E * hid + 4096,), 77, dtype=torch.uint8, device="cuda")
+    lut = torch.zeros(256, dtype=torch.int8, device="cuda")
+    sa.sa_shift_mlp(xq, *w, 1e-3, lut, want_y2=False, y=torch.empty((T, E), device="cuda"), variant=3, workspace=ws)
+    assert not bool(ws[:T * hid].any())                      # the hidden rows, all of them 0
