@@ -14,6 +14,13 @@
 // wavefront to normalise, and saves the launch that wrote the codes: layer of 32 x 784 tokens x 64 52.1 -> 47.1 us, of 1 x 16384
 // x 256 122 -> 115.  With prepared weights the output projection in front of the LayerNorm is made here too, from all of Wo in
 // LDS: at E = 64 it costs this launch 0.5 us and saves one of 5.7 (layer 47.1 -> 42.1 us), at E = 256 7.4 of 9.4 (121.9 -> 120.6).
+// The loads of a stage go between the products that end the stage before: all of them ahead of those products, the wavefronts, which
+// have just met, all waited for the memory pipe with the matrix cores idle (16384 x 256, 1024 hidden: 2510 -> 1930 cycles per 128
+// columns).  Of codes a workgroup of 128 rows takes tile after tile, the next one's weights and rows on their way while the outputs
+// leave: a tile of 131072 x 256, 1024 hidden 81 -> 75 thousand cycles with its launch.  The clock takes part of that back (2.14 -> 2.1
+// GHz: the card's power, not its issue slots, is what this kernel runs out of); block of 8 x 16384 tokens 379.8 -> 368.5 us, layer
+// of 16384 x 256 113.2 -> 111.1, of 32 x 784 x 64 39.8 -> 39.4.  Products of 32 x 32 x 32 needed a tenth fewer cycles and took the same
+// time at 1.98 GHz, and the kernels around them longer (block 369 against 365).
 // Layer 1 on four wavefronts and layer 2 on the other four (requantiser beside products without being interleaved): 226 us
 // for the last one.
 #include "common.h"
@@ -47,7 +54,7 @@ struct MlpShape {
     static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk;
     static constexpr int WO_END = PROJECT ? STAGES + 2 * E * E : 0;      // Wo's planes, in the place of the stages and the hidden rows
     static constexpr int SIDE = H + 2 * H_BYTES > WO_END ? H + 2 * H_BYTES : WO_END;
-    static constexpr int LDS_BYTES = SIDE + OutSide<Store, BM>::BYTES;
+    static constexpr int LDS_BYTES = SIDE + (MI == 4 ? 2 : 1) * OutSide<Store, BM>::BYTES;
     static_assert(BM * E <= 2 * H_BYTES, "codes of normalised rows in the place of the hidden rows");
     static_assert(BM * E * 4 <= RING * STAGE + 2 * H_BYTES, "projected rows in the place of the ring and the hidden rows");
     static_assert(kMlpWaves * 16 * PITCH <= RING * STAGE, "output staging reuses the ring");
@@ -60,6 +67,15 @@ __device__ inline int swizzle_128(int r, int c) { return c ^ ((r >> 1) & 7); }
 // x_res + Wo . codes.
 enum MlpRows { kCodes, kNorm, kProject };
 
+// A stage of weights: of which layer (0: none; 3: of the first, behind its last chunk the last of the second), which of its parts,
+// and of which chunk.  Not live: nothing is loaded.
+template <int LAYER, int SUB>
+struct MlpStage {
+    static constexpr int kLayer = LAYER, kSub = SUB;
+    int chunk;
+    bool live = true;
+};
+
 template <int NE, int MI, int ROWS, class Store>
 __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
                                                                    const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
@@ -71,7 +87,9 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     const int32_t *rows;
     long n_rows;
     resolve_rows(sel, rows, n_rows);
-    const long m0 = (long)blockIdx.x * S::BM;
+    // Codes of 128 rows: a workgroup takes tile after tile.
+    constexpr bool WALK = ROWS == kCodes && MI == 4;
+    long m0 = (long)blockIdx.x * S::BM;
     if (m0 >= n_rows) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -79,11 +97,18 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
     const int chunks = hid / kHidChunk;
 
-    const OutSide<Store, S::BM> side{store, rows, m0, n_rows, lds + S::SIDE};
+    typedef OutSide<Store, S::BM> Side;
+    Side side{store, rows, m0, n_rows, lds + S::SIDE};
     side.fetch_rows(wave, lane);
     if (wave == kMlpWaves - 1) direct_load_4(lut + lane * 4, lds_base + S::TABLE);
 
     v4i acc1[MI][2], acc2[MI][NE];
+    auto clear = [&](v4i (&a)[MI][NE]) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int t = 0; t < NE; ++t) a[i][t] = v4i{0, 0, 0, 0};
+    };
     // this wavefront's rows of x, as operands of the first layer (PROJECT: of the projection, until then)
     uint4 xf[MI][NE];
     constexpr int LPR = NE == 1 ? 16 : NE == 2 ? 32 : 64, GROUPS = 64 / LPR, STEPS = 4 * MI / GROUPS;      // NORM: lanes of a row
@@ -99,12 +124,16 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
         gamma = *reinterpret_cast<const float4 *>(norm.gamma + col);
         beta = *reinterpret_cast<const float4 *>(norm.beta + col);
     }
+    auto load_rows = [&](int of_lane, auto &&row_of) {       // row_of: which row of x is row ml of the tile
 #pragma unroll
-    for (int i = 0; i < (ROWS == kNorm ? 0 : MI); ++i) {
-        const long m = min(m0 + wr * 16 * MI + 16 * i + fr, n_rows - 1);
-        const int8_t *xr = x + (size_t)(rows ? (long)rows[m] : m) * E + 16 * fg;
+        for (int i = 0; i < MI; ++i) {
+            const int8_t *from = x + (size_t)row_of(wr * 16 * MI + 16 * i + (of_lane & 15)) * E + 16 * (of_lane >> 4);
 #pragma unroll
-        for (int k = 0; k < NE; ++k) xf[i][k] = *reinterpret_cast<const uint4 *>(xr + 64 * k);
+            for (int k = 0; k < NE; ++k) xf[i][k] = *reinterpret_cast<const uint4 *>(from + 64 * k);
+        }
+    };
+    if constexpr (ROWS != kNorm) {
+        load_rows(lane, [&](int ml) { return rows ? (long)rows[side.row(ml)] : side.row(ml); });
     }
 
     if constexpr (PROJECT) {
@@ -115,10 +144,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
             const int q = j * kMlpWaves + wave, c = q * 64 + lane, r = c / (4 * NE);
             direct_load_16(norm.wo, (uint32_t)(r * E + swizzle_row<NE>(r, c % (4 * NE)) * 16), lds_base + S::STAGES + q * 1024);
         }
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int t = 0; t < NE; ++t) acc2[i][t] = v4i{0, 0, 0, 0};
+        clear(acc2);
         wait_loads_in_flight<0>();
         __syncthreads();
 #pragma unroll
@@ -168,32 +194,49 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
         const int r = lane / (4 * NE);
         lane1[0] = (uint32_t)(r * E + swizzle_row<NE>(r, lane % (4 * NE)) * 16);
     }
-    // The stages in the order they are multiplied: layer 1 of chunk 0, then layer 1 of chunk c + 1 before layer 2 of chunk c.
-    const int n_stages = 2 * chunks * SPG;
-    auto issue = [&](int s, int slot) {
-        const int u = s / SPG, sub = s % SPG;
-        const bool second = u == 2 * chunks - 1 || (u > 0 && u % 2 == 0);
-        const int c = u == 2 * chunks - 1 ? chunks - 1 : second ? u / 2 - 1 : (u + 1) / 2;
-#pragma unroll
-        for (int p = 0; p < PS; ++p) {
-            const size_t plane = (size_t)(sub * PS + p) * hid * E;
-            const uint32_t at = lds_base + S::STAGES + slot * S::STAGE + p * S::PLANE + wave * NE * 1024;
-            if (second) {
-                const int8_t *base = w2 + plane + (size_t)c * kHidChunk + (size_t)(wave * NE * 8) * hid;
-#pragma unroll
-                for (int i = 0; i < NE; ++i) direct_load_16(base + (size_t)i * 8 * hid, lane2 ^ ((wave * NE + i) % 2 * 64), at + i * 1024);
-            } else {
-                const int8_t *base = w1 + plane + (size_t)c * kHidChunk * E;
-#pragma unroll
-                for (int i = 0; i < NE; ++i) {
-                    if constexpr (NE == 3) direct_load_16(base, lane1[NE == 3 ? i : 0], at + i * 1024);
-                    else direct_load_16(base + (wave * NE + i) * 1024, lane1[0] ^ (NE == 4 ? i * 64 : NE == 2 ? (wave * NE + i) % 2 * 64 : 0), at + i * 1024);
-                }
-            }
+    // The stages in the order they are multiplied: layer 1 of chunk 0, then layer 1 of chunk c + 1 before layer 2 of chunk c.  A
+    // stage's loads go to the ring's place `to`, one at a time: back to back they would hold up the products.
+    auto load_stage_of = [&](auto stage, int to, int j) {
+        constexpr int LAYER = decltype(stage)::kLayer, SUB = decltype(stage)::kSub;
+        const int p = j / NE, i = j % NE;
+        uint32_t from = LAYER == 2 ? lane2 : lane1[NE == 3 ? i : 0];
+        int w = wave;
+        if constexpr (WALK) {                                // made here: no registers for every load's part of it
+            asm volatile("" : "+v"(from), "+s"(w));
+            w = __builtin_amdgcn_readfirstlane(w);
+        }
+        const int q = w * NE + i;
+        const size_t plane = (size_t)(SUB * PS + p) * hid * E;
+        const uint32_t at = lds_base + S::STAGES + to * S::STAGE + p * S::PLANE + q * 1024;
+        if constexpr (LAYER == 2) {
+            direct_load_16(w2 + plane + (size_t)stage.chunk * kHidChunk + (size_t)(q * 8) * hid, from ^ (q % 2 * 64), at);
+        } else if constexpr (LAYER == 1) {
+            const int8_t *base = w1 + plane + (size_t)stage.chunk * kHidChunk * E;
+            if constexpr (NE == 3) direct_load_16(base, from, at);
+            else direct_load_16(base + q * 1024, from ^ (NE == 4 ? i * 64 : NE == 2 ? q % 2 * 64 : 0), at);
         }
     };
+    auto load_stage = [&](auto stage, int to, int j) {
+        constexpr int LAYER = decltype(stage)::kLayer, SUB = decltype(stage)::kSub;
+        if constexpr (LAYER == 3) {
+            if (stage.chunk < chunks) load_stage_of(MlpStage<1, SUB>{stage.chunk}, to, j);
+            else load_stage_of(MlpStage<2, SUB>{chunks - 1}, to, j);
+        } else if (stage.live) {
+            load_stage_of(stage, to, j);
+        }
+    };
+    auto load_whole_stage = [&](auto stage, int to) {
 #pragma unroll
-    for (int q = 0; q < S::RING; ++q) issue(q, q);           // (there are at least four stages)
+        for (int j = 0; j < LOADS; ++j) load_stage(stage, to, j);
+    };
+    load_whole_stage(MlpStage<1, 0>{0}, 0);
+    if constexpr (SPG == 2) {
+        load_whole_stage(MlpStage<1, SPG - 1>{0}, 1);
+        load_whole_stage(MlpStage<1, 0>{1}, 2);
+    } else {
+        load_whole_stage(MlpStage<1, 0>{1}, 1);
+        load_whole_stage(MlpStage<2, 0>{0}, 2);
+    }
     if constexpr (NORM) {                                    // the codes, by way of the hidden rows' place
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
@@ -218,48 +261,60 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
             }
         wait_lds_reads();                                    // hidden rows come here behind the first layer's barriers
     }
-    int s = 0, slot = 0;                                     // the stage being multiplied, its place in the ring
-
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int t = 0; t < NE; ++t) acc2[i][t] = v4i{0, 0, 0, 0};
+    int slot = 0;                                            // the place in the ring of the stage being multiplied
 
     // Operands are read one step ahead of their products.  A step is 64 k, in layer 1 of E = 128 and 256 two of them:
     // the products of one do not cover the latency of the LDS.  fb: weights, fa: hidden rows.
     constexpr int KS = NE % 2 == 0 ? 2 : 1;
     uint4 fb[2][4], fa[MI];
+    // Addresses: the swizzles flip bits of a row's 16-byte chunks, and so does going along the contraction; tiles are whole rows apart.
+    const uint32_t at1 = S::STAGES + (wc * 32 + fr) * E + swizzle_row<NE>(wc * 32 + fr, fg) * 16;
+    const uint32_t at2 = S::STAGES + (wc * 16 * NE + fr) * kHidChunk + swizzle_128(wc * 16 * NE + fr, fg) * 16;
+    const uint32_t at_h = S::H + (wr * 16 * MI + fr) * kHidChunk + swizzle_128(fr, fg) * 16;
+    static_assert(S::STAGES % 256 == 0 && S::STAGE % 256 == 0 && S::H % 256 == 0, "the bits that are flipped are the rows' own");
+    auto operand = [&](uint32_t at, uint32_t along, uint32_t tile) { return *reinterpret_cast<const uint4 *>(lds + ((at ^ along) + tile)); };
     auto read1 = [&](int par, int n) {                       // step n of a stage
+        const uint32_t stage = at1 + slot * S::STAGE;
 #pragma unroll
         for (int q = 0; q < KS; ++q)
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const int p = (n * KS + q) / NE, k = (n * KS + q) % NE, r = wc * 32 + 16 * t + fr;
-                fb[par][2 * q + t] = *reinterpret_cast<const uint4 *>(lds + S::STAGES + slot * S::STAGE + p * S::PLANE + r * E + swizzle_row<NE>(r, 4 * k + fg) * 16);
+                const int p = (n * KS + q) / NE, k = (n * KS + q) % NE;
+                fb[par][2 * q + t] = NE == 3 ? operand(stage, 0, 64 * k + p * S::PLANE + 16 * t * E) : operand(stage, 64 * k, p * S::PLANE + 16 * t * E);
             }
     };
     auto read2 = [&](int par, int p, int k) {
+        const uint32_t stage = at2 + slot * S::STAGE;
 #pragma unroll
-        for (int t = 0; t < NE; ++t) {
-            const int r = wc * 16 * NE + 16 * t + fr;
-            fb[par][t] = *reinterpret_cast<const uint4 *>(lds + S::STAGES + slot * S::STAGE + p * S::PLANE + r * kHidChunk + swizzle_128(r, 4 * k + fg) * 16);
-        }
+        for (int t = 0; t < NE; ++t) fb[par][t] = operand(stage, 64 * k, p * S::PLANE + 16 * t * kHidChunk);
     };
-    auto read_hidden = [&](int i, int k, int buf) {
-        const int r = wr * 16 * MI + 16 * i + fr;
-        fa[i] = *reinterpret_cast<const uint4 *>(lds + S::H + buf * S::H_BYTES + r * kHidChunk + swizzle_128(r, 4 * k + fg) * 16);
+    auto hidden_at = [&](uint32_t at, int buf) {
+        if constexpr (WALK) asm volatile("" : "+v"(at));     // made here: no registers from tile to tile for either buffer's
+        return at + buf * S::H_BYTES;
     };
-    // Before the last products of a stage, whose operands are in registers by then: the next stage is there, and the place of
-    // this one is free for the stage three ahead.
-    auto hand_over = [&]() {
-        if (s + 2 < n_stages) wait_loads_in_flight<LOADS>();
+    auto read_hidden = [&](int i, int k, int buf) { fa[i] = operand(hidden_at(at_h, buf), 64 * k, 16 * i * kHidChunk); };
+    // Before the last products of a stage, whose operands are in registers by then: the next stage is there (the one behind it need
+    // not be), and the place of this one is free for the stage three ahead, whose loads go between those products.
+    auto hand_over = [&](bool behind) {
+        if (behind) wait_loads_in_flight<LOADS>();
         else wait_loads_in_flight<0>();
         __syncthreads();
-        if (s + S::RING < n_stages) issue(s + S::RING, slot);
-        ++s;
         slot = slot == S::RING - 1 ? 0 : slot + 1;
     };
+    auto left = [&]() { return slot == 0 ? S::RING - 1 : slot - 1; };
     enum { kNone, kLayer1, kLayer2 };
+    // behind product u of N: its share of the stage's loads
+    auto between = [&](auto u_c, auto n_c, auto stage) {
+        constexpr int u = decltype(u_c)::value, N = decltype(n_c)::value;
+        if constexpr (decltype(stage)::kLayer != 0) {
+#pragma unroll
+            for (int j = u * LOADS / N; j < (u + 1) * LOADS / N; ++j) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_stage(stage, left(), j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
     auto first_of = [&](auto next_c) {              // the first operands of what comes next
         constexpr int next = decltype(next_c)::value;
         if constexpr (next == kLayer1) read1(0, 0);
@@ -267,45 +322,48 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     };
 
     // Products are computed transposed (weights down, rows across): a lane holds four consecutive columns of row lane % 16.
-    // buf: the hidden rows that a layer 2 behind this one reads.
-    auto layer1 = [&](auto next_c, int buf) {
-        constexpr int STEPS = PS * NE / KS, ALL = SPG * STEPS;        // of a stage, of the layer
+    // buf: the hidden rows that a layer 2 behind this one reads; ahead0, ahead1: the stages to load as this layer's are done.
+    auto layer1 = [&](auto next_c, int buf, auto ahead0, auto ahead1) {
+        constexpr int STEPS = PS * NE / KS, ALL = SPG * STEPS;       // of a stage, of the layer
         static_for<ALL>([&](auto n_c) {
             constexpr int n = decltype(n_c)::value, m = n + 1;
             static_assert(ALL % 2 == 0, "what comes next starts with buffer 0");
             if constexpr (m % STEPS != 0) {
                 read1(m & 1, m % STEPS);
             } else {
-                hand_over();
+                hand_over(true);
                 if constexpr (m < ALL) read1(m & 1, 0);
                 else first_of(next_c);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (m == ALL && decltype(next_c)::value == kLayer2)
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                if (m == ALL && decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf);
-#pragma unroll
-                for (int q = 0; q < KS; ++q)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        acc1[i][t] = mma16(fb[n & 1][2 * q + t], xf[i][(n * KS + q) % NE], n == 0 && q == 0 ? v4i{0, 0, 0, 0} : acc1[i][t]);
-            }
+                for (int i = 0; i < MI; ++i) read_hidden(i, 0, buf);
+            static_for<KS * MI * 2>([&](auto u_c) {
+                constexpr int u = decltype(u_c)::value, i = u / (2 * KS), q = u / 2 % KS, t = u % 2;
+                acc1[i][t] = mma16(fb[n & 1][2 * q + t], xf[i][(n * KS + q) % NE], n == 0 && q == 0 ? v4i{0, 0, 0, 0} : acc1[i][t]);
+                if constexpr (m % STEPS == 0) {
+                    if constexpr (m < ALL || SPG == 1) between(u_c, std::integral_constant<int, KS * MI * 2>{}, ahead0);
+                    else between(u_c, std::integral_constant<int, KS * MI * 2>{}, ahead1);
+                }
+            });
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // tile (i, t) of the chunk's hidden columns: table entries, then a byte each into the hidden rows
-    auto lookup = [&](int i, int t, uint32_t (&v)[4]) {
+    // tile u % 2 of row tile u / 2 of the chunk's hidden columns: table entries, then a byte each into the hidden rows
+    const uint32_t at_kept = S::H + (wr * 16 * MI + fr) * kHidChunk + swizzle_128(fr, wc * 2) * 16 + 4 * fg;
+    auto lookup = [&](int u, uint32_t (&v)[4]) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = lds[S::TABLE + requant_index(acc1[i][t][r], rq)];
+        for (int r = 0; r < 4; ++r) v[r] = lds[S::TABLE + requant_index(acc1[u / 2][u % 2][r], rq)];
     };
-    auto keep = [&](int i, int t, const uint32_t (&v)[4], int buf) {
-        const int r = wr * 16 * MI + 16 * i + fr, c = wc * 2 + t;
-        *reinterpret_cast<uint32_t *>(lds + S::H + buf * S::H_BYTES + r * kHidChunk + swizzle_128(r, c) * 16 + 4 * fg) =
+    auto keep = [&](int u, const uint32_t (&v)[4], int buf) {
+        *reinterpret_cast<uint32_t *>(lds + ((hidden_at(at_kept, buf) ^ (u % 2 * 16)) + 16 * (u / 2) * kHidChunk)) =
             (v[0] | (v[1] << 8)) | ((v[2] | (v[3] << 8)) << 16);
     };
     // Layer 2 of a chunk; between its products the next chunk's hidden columns go to the other buffer (requant), all of them
     // before the last step, whose barrier another layer 2 may read behind.
-    auto layer2 = [&](int buf, auto requant_c, auto next_c) {
+    // behind0, behind1: stages that may still be on their way when this layer's are done.
+    auto layer2 = [&](int buf, auto requant_c, auto next_c, auto ahead0, auto ahead1, bool behind0, bool behind1) {
         constexpr bool REQUANT = decltype(requant_c)::value;
         constexpr int STEPS = PS * 2;
         uint32_t v[2][4];
@@ -314,32 +372,29 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
             if constexpr (m % STEPS != 0) {
                 read2(m & 1, m % STEPS / 2, m % 2);
             } else {
-                hand_over();
+                if constexpr (m < 4 || SPG == 1) hand_over(behind0);
+                else hand_over(behind1);
                 if constexpr (m < 4) read2(m & 1, 0, 0);
                 else first_of(next_c);
             }
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-#pragma unroll
-                for (int t = 0; t < NE; ++t) acc2[i][t] = mma16(fb[n & 1][t], fa[i], acc2[i][t]);
-                if constexpr (m < 4) read_hidden(i, m % 2, buf);
-                else if constexpr (decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf ^ 1);
-                if constexpr (REQUANT) {
-                    const int at = n * MI + i;               // the table's answers are used two places after they are asked for
-                    if (at >= 2 && at - 2 < 2 * MI) keep((at - 2) / 2, at % 2, v[at & 1], buf ^ 1);
-                    if (at < 2 * MI) lookup(at / 2, at % 2, v[at & 1]);
+            static_for<MI * NE>([&](auto u_c) {
+                constexpr int u = decltype(u_c)::value, i = u / NE, t = u % NE;
+                acc2[i][t] = mma16(fb[n & 1][t], fa[i], acc2[i][t]);
+                if constexpr (m % STEPS == 0) {
+                    if constexpr (m < 4 || SPG == 1) between(u_c, std::integral_constant<int, MI * NE>{}, ahead0);
+                    else between(u_c, std::integral_constant<int, MI * NE>{}, ahead1);
                 }
-            }
-            if constexpr (REQUANT && n < 3) {                // what a product's shadow holds behind each
-#pragma unroll
-                for (int q = 0; q < MI * NE; ++q) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 16 / NE, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                if constexpr (t == NE - 1) {
+                    if constexpr (m < 4) read_hidden(i, m % 2, buf);
+                    else if constexpr (decltype(next_c)::value == kLayer2) read_hidden(i, 0, buf ^ 1);
+                    if constexpr (REQUANT) {
+                        constexpr int at = n * MI + i;       // the table's answers are used two places after they are asked for
+                        if constexpr (at >= 2 && at - 2 < 2 * MI) keep(at - 2, v[at & 1], buf ^ 1);
+                        if constexpr (at < 2 * MI) lookup(at, v[at & 1]);
+                    }
                 }
-            }
+            });
             __builtin_amdgcn_sched_barrier(0);
         });
     };
@@ -347,67 +402,113 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     using Layer2 = std::integral_constant<int, kLayer2>;
     using None = std::integral_constant<int, kNone>;
 
+    using NoStage = MlpStage<0, 0>;
+
+    // The stages ahead are three further on: of two parts of a layer, or one.
+    for (;;) {
+    const long next_m0 = m0 + (long)gridDim.x * S::BM;
+    const bool more = WALK && next_m0 < n_rows;
+    const Side next_side{store, rows, next_m0, n_rows, lds + 2 * S::SIDE + Side::BYTES - (side.lds - lds)};      // the two take turns
+    clear(acc2);
     read1(0, 0);
-    layer1(Layer1{}, 0);
+    if constexpr (SPG == 2) layer1(Layer1{}, 0, MlpStage<1, 1>{1}, MlpStage<2, 0>{0});
+    else layer1(Layer1{}, 0, MlpStage<3, 0>{2}, NoStage{});
+    if (more) {                                              // behind a barrier that the outputs of the tile before are before
+        int of_lane = lane;
+        asm volatile("" : "+v"(of_lane));
+        next_side.fetch_rows(wave, of_lane);
+    }
     {
         uint32_t v[4];
 #pragma unroll
-        for (int n = 0; n < 2 * MI; ++n) {
-            lookup(n / 2, n % 2, v);
-            keep(n / 2, n % 2, v, 0);
+        for (int u = 0; u < 2 * MI; ++u) {
+            lookup(u, v);
+            keep(u, v, 0);
         }
     }
     for (int c = 0; c + 2 < chunks; ++c) {
-        layer1(Layer2{}, c & 1);
-        layer2(c & 1, std::true_type{}, Layer1{});
+        if constexpr (SPG == 2) {
+            layer1(Layer2{}, c & 1, MlpStage<2, 1>{c}, MlpStage<1, 0>{c + 2});
+            layer2(c & 1, std::true_type{}, Layer1{}, MlpStage<1, 1>{c + 2}, MlpStage<2, 0>{c + 1}, true, true);
+        } else {
+            layer1(Layer2{}, c & 1, MlpStage<2, 0>{c + 1}, NoStage{});
+            layer2(c & 1, std::true_type{}, Layer1{}, MlpStage<3, 0>{c + 3}, NoStage{}, true, true);
+        }
     }
-    layer1(Layer2{}, chunks & 1);
-    layer2(chunks & 1, std::true_type{}, Layer2{});
-    layer2((chunks & 1) ^ 1, std::false_type{}, None{});
+    if constexpr (SPG == 2) {
+        layer1(Layer2{}, chunks & 1, MlpStage<2, 1>{chunks - 2}, MlpStage<2, 0>{chunks - 1});
+        layer2(chunks & 1, std::true_type{}, Layer2{}, MlpStage<2, 1>{chunks - 1}, MlpStage<1, 0>{0, more}, true, true);
+        layer2((chunks & 1) ^ 1, std::false_type{}, None{}, MlpStage<1, 1>{0, more}, MlpStage<1, 0>{1, more}, more, more);
+    } else {
+        layer1(Layer2{}, chunks & 1, MlpStage<1, 0>{0, more}, NoStage{});
+        layer2(chunks & 1, std::true_type{}, Layer2{}, MlpStage<1, 0>{1, more}, NoStage{}, more, more);
+        layer2((chunks & 1) ^ 1, std::false_type{}, None{}, MlpStage<2, 0>{0, more}, NoStage{}, more, more);
+    }
+    int out_lane = lane;
+    asm volatile("" : "+v"(out_lane));                       // addresses of the outputs are made here, not kept from tile to tile
+    if (more) {                                              // (in time behind the outputs)
+        next_side.fetch_gates(wave, out_lane);
+        load_rows(out_lane, [&](int ml) { return next_side.dest(ml); });
+    }
 
-    // ---- rows out, 16 of the wavefront's columns at a time, through LDS of its own
-    __syncthreads();                                         // the ring has been read
-    uint8_t *slab = lds + S::STAGES + wave * 16 * S::PITCH;
-    auto place = [&](int j, int &row, int &col) {            // chunk j of this lane: row of 16, first column
-        const int q = j * 64 + lane;
-        row = q / (4 * NE);
-        col = wc * 16 * NE + q % (4 * NE) * 4;
+    // ---- rows out, 16 of the wavefront's columns at a time, through LDS of its own: in the place of the hidden rows where the ring
+    //      already has the next tile's weights
+    if constexpr (!WALK) __syncthreads();                    // the ring has been read (the last stage's hand-over says so of the hidden rows)
+    constexpr int OUT_COLS = WALK && NE % 2 == 0 ? 32 : 16 * NE, PARTS = 16 * NE / OUT_COLS, OUT_CHUNKS = OUT_COLS / 4;
+    constexpr bool SWIZZLE = OUT_CHUNKS == 8;                // whole lines of the LDS: no room for a pitch
+    constexpr int OUT_PITCH = SWIZZLE ? OUT_COLS * 4 : S::PITCH;
+    static_assert(kMlpWaves * 16 * OUT_PITCH <= (WALK ? 2 * S::H_BYTES : S::RING * S::STAGE), "room for the outputs");
+    uint8_t *slab = lds + (WALK ? S::H : S::STAGES) + wave * 16 * OUT_PITCH;
+    auto staged_out = [&](int row, int c) { return reinterpret_cast<uint4 *>(slab + row * OUT_PITCH + (SWIZZLE ? c ^ (row & 7) : c) * 16); };
+    constexpr int NC = OUT_CHUNKS / 4;                       // 16-byte chunks of a lane per part of 16 rows
+    const int out_fr = out_lane & 15, out_fg = out_lane >> 4;
+    auto place = [&](int j, int &row, int &c) {              // chunk j of this lane
+        const int q = j * 64 + out_lane;
+        row = q / OUT_CHUNKS;
+        c = q % OUT_CHUNKS;
     };
+    auto out_col = [&](int part, int c) { return wc * 16 * NE + part * OUT_COLS + 4 * c; };
     auto emit = [&](auto reads_c) {
         constexpr bool READS = decltype(reads_c)::value;
-        float4 ext[READS ? 2 : 1][NE];
-        auto fetch = [&](int i) {
+        float4 ext[READS ? 2 : 1][NC];
+        auto fetch = [&](int n) {
 #pragma unroll
-            for (int j = 0; j < NE; ++j) {
-                int row, col;
-                place(j, row, col);
-                ext[READS ? i & 1 : 0][j] =
-                    READS ? ChunkOut<Store>(store, col, E).fetch(side.dest(wr * 16 * MI + 16 * i + row)) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            for (int j = 0; j < NC; ++j) {
+                int row, c;
+                place(j, row, c);
+                ext[READS ? n & 1 : 0][j] = READS ? ChunkOut<Store>(store, out_col(n % PARTS, c), E).fetch(side.dest(wr * 16 * MI + 16 * (n / PARTS) + row))
+                                                  : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
         };
         fetch(0);
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            if (i + 1 < MI) fetch(i + 1);
+        for (int n = 0; n < MI * PARTS; ++n) {
+            const int i = n / PARTS, part = n % PARTS;
+            if (n + 1 < MI * PARTS) fetch(n + 1);
 #pragma unroll
-            for (int t = 0; t < NE; ++t) {
+            for (int t = 0; t < NE / PARTS; ++t) {
+                const v4i &a = acc2[i][part * (NE / PARTS) + t];
                 uint32_t w[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) w[r] = store.convert(acc2[i][t][r], 0, nullptr);
-                *reinterpret_cast<uint4 *>(slab + fr * S::PITCH + (16 * t + 4 * fg) * 4) = make_uint4(w[0], w[1], w[2], w[3]);
+                for (int r = 0; r < 4; ++r) w[r] = store.convert(a[r], 0, nullptr);
+                *staged_out(out_fr, 4 * t + out_fg) = make_uint4(w[0], w[1], w[2], w[3]);
             }
 #pragma unroll
-            for (int j = 0; j < NE; ++j) {
-                int row, col;
-                place(j, row, col);
-                const uint4 v = *reinterpret_cast<const uint4 *>(slab + row * S::PITCH + (col - wc * 16 * NE) * 4);
+            for (int j = 0; j < NC; ++j) {
+                int row, c;
+                place(j, row, c);
+                const uint4 v = *staged_out(row, c);
                 const int ml = wr * 16 * MI + 16 * i + row;
-                if (m0 + ml < n_rows) ChunkOut<Store>(store, col, E).put(v, ext[READS ? i & 1 : 0][j], side.gate(ml), side.dest(ml));
+                if (m0 + ml < n_rows) ChunkOut<Store>(store, out_col(part, c), E).put(v, ext[READS ? n & 1 : 0][j], side.gate(ml), side.dest(ml));
             }
         }
     };
     if (store.accumulate) emit(std::true_type{});
     else emit(std::false_type{});
+    if (!more) return;
+    m0 = side.m0 = next_m0;
+    side.lds = next_side.lds;
+    }
 }
 
 struct MlpArgs {
@@ -425,13 +526,13 @@ int launch(const MlpArgs &a, hipStream_t st) {
     typedef ShiftStore<kEpiScatterI32> Store;
     const long blocks = (a.sel.max_rows + 32 * MI - 1) / (32 * MI);
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_shift_mlp: too many rows for one launch");
-    const dim3 grid((unsigned)blocks), block(kMlpWaves * 64);
+    const dim3 grid((unsigned)blocks), block(kMlpWaves * 64), walk((unsigned)(MI == 4 && blocks > 256 ? 256 : blocks));
     if (a.norm && a.norm->wo)
         shift_mlp_kernel<NE, MI, kProject, Store><<<grid, block, 0, st>>>(a.x, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     else if (a.norm)
         shift_mlp_kernel<NE, MI, kNorm, Store><<<grid, block, 0, st>>>(nullptr, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     else
-        shift_mlp_kernel<NE, MI, kCodes, Store><<<grid, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+        shift_mlp_kernel<NE, MI, kCodes, Store><<<walk, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     return check_launch("sa_shift_mlp (both layers)");
 }
 

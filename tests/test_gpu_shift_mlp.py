@@ -109,3 +109,31 @@ def test_two_launches_they_are(sa, T, E, hid):
     lut = torch.zeros(256, dtype=torch.int8, device="cuda")
     sa.sa_shift_mlp(xq, *w, 1e-3, lut, want_y2=False, y=torch.empty((T, E), device="cuda"), variant=3, workspace=ws)
     assert not bool(ws[:T * hid].any())                      # the hidden rows, all of them 0
+
+
+# More than 256 tiles of 128 rows: a workgroup takes several, whole ones and the last one in part; two and three chunks of hidden columns,
+# so that a ring of three stages comes round differently from tile to tile.
+@pytest.mark.parametrize("rows,E,hid", [(65401, 256, 256), (65536, 256, 384), (90003, 192, 384), (65409, 128, 256), (98177, 128, 384)])
+def test_tiles_one_after_the_other(sa, rows, E, hid):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + E + hid)
+    T = rows + 131
+    xq = torch.randint(-127, 128, (T, E), generator=g, device="cuda", dtype=torch.int8)
+    w = [sa.sa_shift_planes_prepare(torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8)) for s in ((hid, E // 2), (E, hid // 2))]
+    lut = torch.randint(-128, 128, (256,), generator=g, device="cuda", dtype=torch.int8)
+    rq = 127.0 / (4 * 40 * 73 * E ** 0.5)
+    perm = torch.randperm(T, generator=g, device="cuda").to(torch.int32)
+    gate, old = torch.rand(T, generator=g, device="cuda"), torch.randn((T, E), generator=g, device="cuda")
+    ws = torch.empty(T * hid + 4 * E * hid + 4096, dtype=torch.uint8, device="cuda")
+
+    def go(x, stages, **kw):
+        y = old.clone()
+        for s in stages:
+            sa.sa_shift_mlp(x, *w, rq, lut, want_y2=False, y=y, out_scale=1e-3, variant=3, stages=s, workspace=ws, **kw)
+        return y
+    for flag in (0, 4):                                     # 4: SA_MLP_ACCUMULATE
+        for x, kw in ((xq[:rows], {}), (xq, dict(rows=perm, max_rows=rows, gate=gate))):
+            ws.fill_(77)
+            got = go(x, (3 | flag,), **kw)
+            assert bool((ws[:rows * hid] == 77).all())      # one launch
+            assert torch.equal(got, go(x, (1, 2 | flag), **kw))
