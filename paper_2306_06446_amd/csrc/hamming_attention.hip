@@ -2,8 +2,8 @@
 // replaced by the Hamming similarity S = nbits - 2 * popcount(q xor k) of the
 // codes; V stays fp32, Sec. 4.1).
 //
-// The scores are integer work for the vector ALU (XOR + popcount).  A score takes one of
-// nbits + 1 values, so the softmax numerators p = exp2(-|c2| * t), t = |dist - dist_ref|,
+// The scores are integers, from XOR + popcount on the vector ALU or from the matrix cores (+-1 products).  A score
+// takes one of nbits + 1 values, so the softmax numerators p = exp2(-|c2| * t), t = |dist - dist_ref|,
 // come from a table in LDS that is built once per workgroup; each entry holds p in fp32
 // (for the row sum) and p split into two bf16 terms, p ~ ph + pl (each rounded to nearest).
 // The second MatMul P * V is the dense contraction of this kernel and runs on the bf16
@@ -347,6 +347,18 @@ __global__ __launch_bounds__(kMaxWaves *kWave) void hamming_mfma_kernel(
                              act_inv_scale, b, h, H, Nq, chunk, wave, lane);
 }
 
+// 32 code bits as 32 fp4 values: bit 1 -> -1.0, bit 0 -> +1.0 (flip: the other way round).  Dword i takes bits 4 j + i.
+typedef int v8i __attribute__((ext_vector_type(8)));
+__device__ inline v8i signs_fp4(uint32_t bits, uint32_t one, bool flip) {      // one: 0x22222222, in a register
+    v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t sign = (bits << (3 - i)) & 0x88888888u;
+        r[i] = (int)(flip ? sign ^ 0xAAAAAAAAu : sign | one);
+    }
+    return r;
+}
+
 // ---- the same kernel as a pipeline over several (batch, head, query chunk) units per workgroup ------------
 // The kernel above runs its phases one after the other: load V, split it, multiply, store.  With every workgroup
 // of a launch resident at once (768 at the DeiT-Base shape, three per CU) the whole chip loads, then computes,
@@ -354,8 +366,16 @@ __global__ __launch_bounds__(kMaxWaves *kWave) void hamming_mfma_kernel(
 // (u = blockIdx.x, + gridDim.x, ...) and over their 128-key chunks, and the NEXT chunk's V rows and key codes are
 // already on their way while the current chunk is multiplied: they arrive through direct global -> LDS loads
 // (no registers, no waiting wavefront) as raw fp32 rows, and are split into the two bf16 planes LDS -> LDS at the
-// chunk switch.  The output stores of a unit drain while the next unit is computed.  Same arithmetic, same
-// order, bit-identical results.  Row reference distances (ROWREF in the kernel above) need all key codes of a
+// chunk switch.  The output stores of a unit drain while the next unit is computed.
+//
+// The distances come from the matrix cores here: the code bits as +-1 in fp4 (two operations per eight bits of a key, no
+// conversion in LDS), 64 bits a product of 32 keys and 32 queries, and the sum is the LDS address of the pair's numerators as it
+// stands.  That leaves three vector operations per pair (its part of the keys' signs, the row sum, the packing) where XOR and popcount
+// took eleven at 128 bits; the two dozen products of P * V per 32 keys bound the steps now (128 keys of 14 wavefronts on a CU 3.1 us,
+// 4.5 before).  Around them: 3.5 us until the first chunk has landed, 1 to 1.5 us to split a chunk, 2 to 3 us of outputs per unit, overlapped
+// as far as two workgroups to a CU do.  64 x 12 heads x 197 x 128 bits x 64, in a block with all three output forms 37.4 -> 31.5 us (68 MB
+// out, 39 MB in), in a layer, int8 alone, 33.4 -> 28.7; 7 x 12 heads x 64 bits 12.0 -> 10.6.
+// Same arithmetic, same order, bit-identical results.  Row reference distances (ROWREF in the kernel above) need all key codes of a
 // unit before its first step and keep the kernel above.
 template <int DV, int W>
 __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
@@ -388,31 +408,37 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
         const int n = min(kKeyChunk, Nk - j);
         const int n_pad = (n + 15) & ~15;
         const int v_instr = (n_pad + RPI - 1) / RPI;
+        int of_lane = lane;
+        asm volatile("" : "+v"(of_lane));            // (addresses are not kept from chunk to chunk: the steps need the registers)
         for (int k = wave; k < v_instr; k += n_waves) {
-            const int key = min(k * RPI + lane / L4, n - 1);
-            const float *src = v + (((size_t)b * Nk + j + key) * H + h) * DV + (lane % L4) * 4;
+            const int key = min(k * RPI + of_lane / L4, n - 1);
+            const float *src = v + (((size_t)b * Nk + j + key) * H + h) * DV + (of_lane % L4) * 4;
             sa::direct_load_16(src, raw_base + k * 1024);
         }
         const int code_bytes = n * W * 8, code_instr = (n_pad * W * 8 + 255) / 256;
         const char *cg = reinterpret_cast<const char *>(k_codes + ((size_t)bh * Nk + j) * W);
         for (int k = wave; k < code_instr; k += n_waves) {
-            const int off = min(k * 256 + lane * 4, code_bytes - 4);
+            const int off = min(k * 256 + of_lane * 4, code_bytes - 4);
             sa::direct_load_4(cg + off, kc_base + buf * (kKeyChunk * W * 8) + k * 256);
         }
     };
-    auto load_query = [&](long u, uint64_t (&dst)[W]) {
+    auto load_query = [&](long u, uint32_t (&dst)[W]) {
         const long bh = u / q_chunks;
         const int chunk = (int)(u % q_chunks);
-        const int qi = min(chunk * (kMaxWaves * 32) + wave * 32 + i_loc, Nq - 1);
+        int of_lane = lane;
+        asm volatile("" : "+v"(of_lane));
+        const int qi = min(chunk * (kMaxWaves * 32) + wave * 32 + (of_lane & 31), Nq - 1);
+        const uint32_t *from = reinterpret_cast<const uint32_t *>(q_codes) + ((size_t)bh * Nq + qi) * 2 * W + W * (of_lane >> 5);
 #pragma unroll
-        for (int w = 0; w < W; ++w) dst[w] = q_codes[((size_t)bh * Nq + qi) * W + w];
+        for (int w = 0; w < W; ++w) dst[w] = from[w];
     };
 
     long u = blockIdx.x;
     if (u >= n_units) return;
     issue_chunk(u, 0, 0);
-    uint64_t q[W], qn[W];
+    uint32_t qn[W];
     load_query(u, qn);
+    v8i q[W];
 
     // numerators by distance: the exponent is c2 * dist (no row reference here)
     const float c2n = c2 <= 0.0f ? c2 : -c2;
@@ -429,17 +455,47 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
         for (int r = 0; r < 16; ++r) acc[jt][r] = 0.0f;
     float den = 0.0f;
 
-    // One step: 16 keys from k0 (8 per half-wavefront).  MASK: keys from n on do not count.
-    auto step = [&](const uint64_t *kc, int k0, int n, auto mask_c) {
+    // Distances of 32 keys from k0 to this wavefront's queries: the products of the code bits as +-1 (fp4, exact), keys down and queries
+    // across.  Every product counts 4 * 2^-149 and the sums start at where distance NBITS / 2 stands in the table: their bits, among the
+    // denormal floats, are the LDS addresses of the numerators.  Row m of the tile is key m with bits 2 and 3 exchanged, so that
+    // register 8 t + e of a lane is key 16 t + 8 kg + e.
+    const uint32_t tab_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) TableEntry *)tab_s;
+    v16f middle;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) middle[r] = __builtin_bit_cast(float, tab_base + 4 * NBITS);
+    uint32_t one = 0x22222222u;
+    asm volatile("" : "+v"(middle), "+v"(one));              // kept in registers, not made anew for every tile
+    const int key_row = (i_loc & 19) | (i_loc & 4) << 1 | (i_loc & 8) >> 1;
+    auto distances = [&](const uint64_t *kc, int k0) {
+        const uint32_t *at = reinterpret_cast<const uint32_t *>(kc) + (k0 + key_row) * 2 * W + W * kg;
+        uint32_t bits[W];
+        if constexpr (W == 4) {
+            const uint4 b = *reinterpret_cast<const uint4 *>(at);
+            bits[0] = b.x; bits[1] = b.y; bits[2] = b.z; bits[3] = b.w;
+        } else if constexpr (W == 2) {
+            const uint2 b = *reinterpret_cast<const uint2 *>(at);
+            bits[0] = b.x; bits[1] = b.y;
+        } else {
+            bits[0] = *at;
+        }
+        v16f d = middle;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            d = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(signs_fp4(bits[w], one, false), q[w], d, 4, 4, 0, 127 - 74, 0, 127 - 73);
+        return d;
+    };
+    // 16 of those keys, t = 0 or 1 (8 per half-wavefront).  MASK: keys from n on do not count.
+    auto step = [&](const v16f &at, int t, int k0, int n, auto mask_c) {
         constexpr bool MASK = decltype(mask_c)::value;
-        const int kb = k0 + 8 * kg;                       // this lane's first key
+        const int kb = k0 + 16 * t + 8 * kg;              // this lane's first key
         uint32_t hl[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int t = distance<W>(q, kc + (kb + e) * W);      // padding keys hold arbitrary code bytes: still 0 .. NBITS
-            const TableEntry te = tab_s[t];
-            hl[e] = te.hl;
-            den += (!MASK || kb + e < n) ? te.p : 0.0f;
+            const float a = at[8 * t + e];
+            const uint64_t entry = *reinterpret_cast<__attribute__((address_space(3))) const uint64_t *>(__builtin_bit_cast(uint32_t, a));
+            const uint32_t p = (uint32_t)(entry >> 32);
+            hl[e] = (uint32_t)entry;
+            den += (!MASK || kb + e < n) ? __builtin_bit_cast(float, p) : 0.0f;
         }
         uint32_t ah[4], al[4];
 #pragma unroll
@@ -464,7 +520,7 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
     for (;;) {
         if (j0 == 0) {
 #pragma unroll
-            for (int w = 0; w < W; ++w) q[w] = qn[w];
+            for (int w = 0; w < W; ++w) q[w] = signs_fp4(qn[w], one, true);
         }
         const int n = min(kKeyChunk, Nk - j0);
         const int n_pad = (n + 15) & ~15;
@@ -500,15 +556,26 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
             if (j2 == 0) load_query(u2, qn);
         }
         const uint64_t *kc = kc_s[buf];
-        const int n_full = n & ~15;                  // whole steps first, then at most one masked step
-        for (int k0 = 0; k0 < n_full; k0 += 16) step(kc, k0, n, std::false_type{});
-        if (n_full < n) step(kc, n_full, n, std::true_type{});
+        const int n_full = n & ~31;                  // whole tiles first, then at most one masked one, or half of it
+        for (int k0 = 0; k0 < n_full; k0 += 32) {
+            const v16f at = distances(kc, k0);
+            step(at, 0, k0, n, std::false_type{});
+            __builtin_amdgcn_sched_barrier(0);
+            step(at, 1, k0, n, std::false_type{});
+        }
+        if (n_full < n) {
+            const v16f at = distances(kc, n_full);
+            step(at, 0, n_full, n, std::true_type{});
+            if (n_full + 16 < n) step(at, 1, n_full, n, std::true_type{});
+        }
         if (j2 == 0) {                               // last chunk of the unit
             const long bh = u / q_chunks;
             __syncthreads();                         // every wavefront is through its steps: the planes become staging rows
+            int out_lane = lane;
+            asm volatile("" : "+v"(out_lane));       // the outputs' addresses are made here, not kept through the steps
             write_outputs<DV>(acc, den, reinterpret_cast<uint8_t *>(&vt_s[0][0]) + wave * stage_bytes_per_wave<DV>(), out,
                                      xq, xh, act_inv_scale, (int)(bh / H), (int)(bh % H), H, Nq, (int)(u % q_chunks), wave,
-                                     lane);
+                                     out_lane);
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
@@ -727,7 +794,7 @@ struct Launch {
     float c2;
     bool rowref;
     bool mm_scores;         // scores as sign dot products on the matrix cores (else XOR + popcount on the vector ALU)
-    bool pipeline;          // several units per workgroup, the next chunk in flight (popcount scores, no row reference)
+    bool pipeline;          // several units per workgroup, the next chunk in flight (fp4 scores, no row reference)
     long n_units;
     int8_t *xq;
     _Float16 *xh;
@@ -869,10 +936,9 @@ extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_
     L.c2 = -2.0f * scale * 1.4426950408889634f;
     // exp2 of c2*dist stays a normal float for every possible distance -> no row reference needed
     L.rowref = !(scale >= 0.0f && -L.c2 * (float)nbits <= 100.0f);
-    // measured at the DeiT-Base shape: 38 us with popcount scores, 44 us with matrix-core scores (more LDS
-    // traffic and MFMA time than the vector work it saves), so AUTO keeps the popcount
     L.mm_scores = (variant == SA_VARIANT_MFMA);
-    // AUTO: the pipelined popcount kernel where it is built (dv <= 64, nbits <= 256, no row reference)
+    // AUTO: the pipelined kernel where it is built (dv <= 64, nbits <= 256, no row reference); at the DeiT-Base shape 31 us with all
+    // outputs, one unit per workgroup 38 with popcount scores and 44 with bf16 ones (a byte of signs for every bit in LDS)
     L.pipeline = variant == SA_VARIANT_AUTO && !L.rowref && dv <= 64 && W <= 4;
     L.n_units = blocks;
     switch (dv) {
