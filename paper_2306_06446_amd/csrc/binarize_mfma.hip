@@ -36,45 +36,14 @@
 //   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3          1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
 //    1 x 16384 x 4 x 64 -> 256            18.5 -> 17.4          8 x 16384 x 4 x 64 -> 256  110 -> 112 (as a stream; 104 without)
 #include "common.h"
-#include "hash_margin.h"
+#include "hash_tile.h"
 #include "side_work.h"
 
 namespace sa {
 
 namespace {
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 constexpr int kListCap = 128;                 // unsettled bits parked per wavefront
-
-struct RowMap {
-    FastDiv by_h, by_n;
-    int N, H, W;
-    __device__ inline size_t row_words(uint32_t row) const {     // first code word of a row of the flattened input
-        const uint32_t t = by_h(row), h = row - t * (uint32_t)H, b = by_n(t), n = t - b * (uint32_t)N;
-        return ((size_t)(b * (uint32_t)H + h) * N + n) * W;
-    }
-};
-
-// Up to two tensors of the same shape are hashed by one launch (Q and K of a block).
-struct Tensors {
-    const float *x0, *x1;
-    uint64_t *codes0, *codes1;
-};
-
-// (a, b) as fp16 terms, a in the lower half: upper terms, and what they leave.
-__device__ inline void split_f16_pair(float a, float b, uint32_t &upper, uint32_t &lower) {
-    const v2f x = {a, b};
-    const v2h h = __builtin_convertvector(x, v2h);
-    upper = __builtin_bit_cast(uint32_t, h);
-    v2f r;                                        // a - h[0], b - h[1]: exact, one operation each that reads its half of h itself
-    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r[0]) : "v"(upper), "v"(a));
-    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r[1]) : "v"(upper), "v"(b));
-    lower = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2h));
-}
 
 // Swaps a's upper 32 lanes with b's lower 32.
 template <typename T>
@@ -83,34 +52,6 @@ __device__ inline void swap_halves(T &a, T &b) {
     const uint32_t r0 = r[0], r1 = r[1];
     a = __builtin_bit_cast(T, r0);
     b = __builtin_bit_cast(T, r1);
-}
-
-// Re-runs the defining chain for one parked (row, bit) entry and flips the stored bit where the pre-pass had it
-// wrong.  r_s: the hash columns of this workgroup, fp32 [D][C].  RND steps of the chain per round trip of loads.
-template <int D, int C, int RND>
-__device__ inline void settle_entry(uint64_t e, const Tensors &ts, const float *r_s, int c_first, const RowMap &map) {
-    const uint32_t row = (uint32_t)e;
-    const int col = (int)((e >> 32) & 0xffffu);
-    const bool prov = (e >> 48) & 1u;
-    const bool second = (e >> 49) & 1u;
-    const float *xr = (second ? ts.x1 : ts.x0) + (size_t)row * D;
-    uint64_t *codes = second ? ts.codes1 : ts.codes0;
-    float acc = 0.0f;
-    // loads first, then the fmas in their defined order
-#pragma unroll 1
-    for (int k0 = 0; k0 < D; k0 += RND) {
-        float xv[RND];
-#pragma unroll
-        for (int q = 0; q < RND / 4; ++q) {
-            const float4 t4 = *reinterpret_cast<const float4 *>(xr + k0 + 4 * q);
-            xv[4 * q] = t4.x; xv[4 * q + 1] = t4.y; xv[4 * q + 2] = t4.z; xv[4 * q + 3] = t4.w;
-        }
-#pragma unroll
-        for (int k = 0; k < RND; ++k) acc = __builtin_fmaf(xv[k], r_s[(k0 + k) * C + col - c_first], acc);
-    }
-    const bool exact = acc >= 0.0f;
-    if (exact != prov)
-        atomicXor(reinterpret_cast<unsigned long long *>(codes + map.row_words(row) + (col >> 6)), 1ull << (col & 63));
 }
 
 // D: head dim; C: hash columns of a workgroup (blockIdx.y selects the group); kWaves: its wavefronts.
@@ -222,7 +163,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
         wait_loads_in_flight<0>();               // the words these bits live in have been stored
 #pragma unroll 1
         for (int t0 = 0; t0 < cnt; t0 += 64)
-            if (t0 + lane < cnt) settle_entry<D, C, 16>(list[t0 + lane], ts, r_s, c_first, map);
+            if (t0 + lane < cnt) settle_entry<D, 16>(list[t0 + lane], ts, r_s, C, c_first, map);
         cnt = 0;
     };
 
@@ -393,8 +334,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
             if (parked) {
                 const int slot = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u));
                 const int u = which / (PIECES / 2), piece = which % (PIECES / 2);
-                list[slot] = (uint64_t)(r0 + 16 * u + n) | ((uint64_t)(c_first + (C / 4) * g + 32 * piece + pos) << 32) |
-                             ((uint64_t)((bits >> pos) & 1u) << 48) | ((uint64_t)second << 49);
+                list[slot] = open_bit(r0 + 16 * u + n, c_first + (C / 4) * g + 32 * piece + pos, (bits >> pos) & 1u, second);
                 any_park = 0;
 #pragma unroll
                 for (int p = 0; p < PIECES; ++p) {
@@ -419,7 +359,7 @@ __global__ __launch_bounds__(kWaves * 64) void binarize_mfma_kernel(Tensors ts, 
         int t = t0 + lane, w = 0;
         if (t < total) {
             while (t >= cnt_s[w]) t -= cnt_s[w++];
-            settle_entry<D, C, D <= 64 ? D : 32>(list_s[w][t], ts, r_s, c_first, map);   // the tile loop's registers are free now
+            settle_entry<D, D <= 64 ? D : 32>(list_s[w][t], ts, r_s, C, c_first, map);   // the tile loop's registers are free now
         }
     }
 }

@@ -351,6 +351,7 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                                        ws + L.lin_ws, L.lin_ws_bytes, stream);
         if (rc != SA_OK) return rc;
     } else {
+        const bool norm_hash = norm_linear && d->proj && !side.any() && sa::norm_hash_one_launch(T, E, d->H, d->nbits);
         if (norm_linear) {
             sa::NormRows norm;
             norm.x = d->x;
@@ -358,13 +359,16 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
             norm.beta = d->beta1;
             norm.eps = d->eps;
             norm.inv_scale = d->ln_inv_scale;
-            rc = sa::launch_norm_linear(norm, T, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, q, k, v, sa::as_stream(stream));
+            if (norm_hash)
+                rc = sa::launch_norm_hash(norm, d->B, d->N, d->H, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, d->proj, d->nbits,
+                                          q, k, qc, kc, v, sa::as_stream(stream));
+            else
+                rc = sa::launch_norm_linear(norm, T, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, q, k, v, sa::as_stream(stream));
         } else {
             rc = sa_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, d->qkv_scale, nullptr, 3, q, k, v,
                                      ws + L.lin_ws, L.lin_ws_bytes, stream);
         }
-        if (rc != SA_OK) return rc;
-        rc = hash_and_side(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, side, stream);
+        if (rc == SA_OK && !norm_hash) rc = hash_and_side(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, side, stream);
         if (rc != SA_OK) return rc;
     }
     if (d->attention == 0) {

@@ -1,0 +1,51 @@
+"""A layer whose Q, K, V projection normalises its rows and hashes Q and K itself, against one whose LayerNorm, projection and hash are
+launches of their own (the other variants of the Shift Linears): the same integer sums, and bits that the hash's defining chain settles."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+# every width, head width and number of bits; rows that fill no workgroup, one, and more than a round of them; either side of where the
+# launch takes over.  qkv_scale brings rows in and out of the range that splits into fp16 terms as it is.
+@pytest.mark.parametrize("B,N,H,E,nbits,attention,qkv_scale", [
+    (1, 1, 2, 64, 64, 0, 2.0**-12), (3, 77, 1, 64, 64, 0, 2.0**-40), (1, 65, 1, 64, 128, 1, 2.0**30), (2, 131, 1, 64, 256, 0, 2.0**-12),
+    (5, 6661, 2, 64, 64, 0, 2.0**-12), (7, 2477, 1, 64, 256, 0, 2.0**-12), (3, 97, 2, 64, 64, 1, 2.0**-140),
+    (2, 768, 4, 128, 64, 0, 2.0**-12), (1, 1537, 2, 128, 64, 0, 2.0**20), (16, 191, 2, 128, 128, 1, 2.0**-12), (2, 1536, 2, 128, 128, 0, 2.0**-30),
+    (1, 12287, 2, 128, 256, 0, 2.0**-12), (1, 12288, 2, 128, 256, 0, 2.0**-12), (3, 32777, 4, 128, 64, 0, 2.0**-12),
+    (3, 32767, 2, 128, 64, 0, 2.0**-12), (2, 5200, 6, 192, 64, 0, 2.0**-12), (54, 199, 3, 192, 64, 1, 2.0**-12),
+    (1, 10369, 3, 192, 128, 0, 2.0**-12), (3, 4098, 3, 192, 256, 0, 2.0**-12), (2, 32801, 3, 192, 64, 0, 2.0**-12),
+    (1, 13825, 8, 256, 64, 0, 2.0**-12), (128, 127, 4, 256, 64, 1, 2.0**-12), (2, 7001, 4, 256, 128, 0, 2.0**-12),
+    (1, 16384, 4, 256, 256, 0, 2.0**-12), (1, 16385, 4, 256, 256, 0, 2.0**-12),
+])
+def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attention, qkv_scale):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + E + nbits)
+    T, hid = B * N, 256
+    x = torch.randn((T, E), generator=g, device="cuda")
+    x[T // 2] = 0.5                                          # no variance
+    if T > 64:
+        x[T // 3, 0], x[T // 5, 1] = float("nan"), float("inf")
+    gamma1, beta1, gamma2, beta2 = (torch.randn(E, generator=g, device="cuda") for _ in range(4))
+    beta1[E // 2:] = 0.0
+    w = [torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8)
+         for s in ((3 * E, E // 2), (E, E // 2), (hid, E // 2), (E, hid // 2))]
+    w[0][2 * E:] = w[0][2 * E:] & 0x33                       # V small enough for sums of every scale to mean something
+    proj = torch.randn((E // H, nbits), generator=g, device="cuda")
+    proj[:, 5] = 0.0                                         # columns left to the chain altogether
+    proj[:, 11] *= 1e-30
+    proj[1:, 17] = 0.0
+    lut = torch.arange(-128, 128, device="cuda").clamp(min=0).to(torch.int8)
+    y = []
+    for variant in (0, 2, 3):
+        if variant == 3:
+            w = [sa.sa_shift_planes_prepare(t) for t in w]
+        layer = sa.binding.Layer(B=B, N=N, H=H, nbits=nbits, E=E, hid=hid, attention=attention, moe=0, shift_variant=variant, eps=1e-6,
+                                 ln_inv_scale=32.0, qkv_scale=qkv_scale, attn_scale=(64.0 * N) ** -0.5, act_inv_scale=32.0 * 2.0**-12 / qkv_scale,
+                                 o_scale=2.0**-12, requant_scale=2.0**-11, out_scale=2.0**-12, x=x, gamma1=gamma1, beta1=beta1,
+                                 gamma2=gamma2, beta2=beta2, wqkv=w[0], wo=w[1], proj=proj, w1=w[2], w2=w[3], lut=lut)
+        y.append(layer.forward().clone())
+    rows = torch.isfinite(x).all(dim=1)
+    assert float((y[0] - x)[rows].abs().max()) > 0.0
+    for other in y[1:]:
+        assert torch.equal(y[0].nan_to_num(nan=3.0), other.nan_to_num(nan=3.0))
