@@ -33,7 +33,7 @@
 // to 3.7 at d = 128.  Q and K, alone and over and over, 64 bytes of 16 rows per load -> now:
 //   64 x 197 x 12 heads x 64 -> 128 bits  25.1 -> 23.6 us      64 x 197 x 12 x 64 -> 64  19.2 -> 18.6
 //   64 x 197 x 3 x 64 -> 64               10.0 ->  9.2          8 x 1000 x 3 x 128 -> 128  14.8 -> 14.7
-//   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3          1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
+//   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3 (launch_waves: 8.1)          1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
 //    1 x 16384 x 4 x 64 -> 256            18.5 -> 17.4          8 x 16384 x 4 x 64 -> 256  110 -> 112 (as a stream; 104 without)
 #include "common.h"
 #include "hash_tile.h"
@@ -373,11 +373,17 @@ bool binarize_mfma_supported(int d, int nbits) {
 template <int D, int C, int kWaves>
 int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &map, int nbits, long n_tiles, long n_total,
                  const SideWork &side, hipStream_t st) {
-    // eight wavefronts per CU (what the registers allow) over all column groups, every wavefront the same number of tiles
-    constexpr int PER_CU = C == 64 ? 8 / kWaves : 1;
+    // Eight wavefronts per CU (what the registers allow) over all column groups, every wavefront the same number of tiles.  At d = 32 and
+    // 64 columns, whose tiles are short and little but their loads, sixteen, each of which takes what there is: 6272 tiles were four each
+    // for 1568 wavefronts, with eight on one SIMD of two CUs and four on the next (Q and K of 32 x 3136 tokens x 32 with the Add
+    // products 24.7 -> 22.9 us; 200704 rows alone 9.5 -> 8.1, 302592 11.9 -> 10.7, 2097152 61.4 -> 50.7; with twelve 11.2 and 52.5, with 24 12.1 and 52.3).
+    // Longer tiles lose by it (d = 64: 302592 rows 18.0, 20.6; 128 bits 23.4, 28.1).
+    constexpr bool SHORT = D == 32 && C == 64;
+    constexpr int PER_CU = SHORT ? 16 / kWaves : C == 64 ? 8 / kWaves : 1;
     const long waves = 256 * PER_CU / (nbits / C) * kWaves;
-    const long tiles_per_wave = (n_total + waves - 1) / waves;
-    const long blocks = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
+    const long tiles_per_wave = SHORT ? 1 : (n_total + waves - 1) / waves;
+    const long enough = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
+    const long blocks = enough < waves / kWaves ? enough : waves / kWaves;
     // what rides along comes behind the tiles: it fills the CUs that are done first
     const long more = (side_blocks(side, kWaves * 64) + nbits / C - 1) / (nbits / C);
     const dim3 grid((unsigned)(blocks + more), (unsigned)(nbits / C));

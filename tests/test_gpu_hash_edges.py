@@ -88,6 +88,17 @@ def test_workgroups_of_64_columns_over_many_tiles(sa, d, nbits):
         assert torch.equal(c, sa.sa_binarize(t, proj, nbits, variant=0))
 
 
+@pytest.mark.parametrize("N", [65504, 65536, 65537, 131073, 200001])
+def test_short_tiles_shared_out_one_by_one(sa, N):
+    """32 to 64 columns: Q and K are one tile of each wavefront less two, one each, two over, and up to four each."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    x = [torch.randn((1, N, 1, 32), generator=g, device="cuda") for _ in range(2)]
+    proj = torch.randn((32, 64), generator=g, device="cuda")
+    for t, c in zip(x, sa.sa_binarize_pair(x[0], x[1], proj, 64)):
+        assert torch.equal(c, sa.sa_binarize(t, proj, 64, variant=0))
+
+
 @pytest.mark.parametrize("B,N,d", [(4, 1024, 64), (5, 1000, 64), (33, 500, 32)])
 def test_hash_that_routes_along(sa, B, N, d):
     """Around the number of tokens from which the workgroups that also route are larger ones: what the hash leaves is the same (the
