@@ -387,8 +387,8 @@ __device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes,
 template <int TM, int W, bool ZO>
 constexpr bool kCodesAhead = ZO ? TM > 1 && W < 4 : TM > 1 || W < 4;
 
-// block = (bh * column groups + column group) * blocks_per_bh + part
-template <int DVC, int W, int NW, int TM, bool ZO>
+// SUMS: K^T V may come as partials.  block = (bh * column groups + column group) * blocks_per_bh + part
+template <int DVC, int W, int NW, int TM, bool ZO, bool SUMS>
 __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, int Nq, int DV, long BH,
                                           int blocks_per_bh, int tiles_per_block, int block, uint8_t *lds) {
     constexpr int JT = DVC / 32;
@@ -409,27 +409,13 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
     uint64_t next[TM][W];                          // kCodesAhead: the codes of the tiles that come next
     if constexpr (kCodesAhead<TM, W, ZO>) load_codes<W, TM>(q_codes, bh, Nq, part * tiles_per_block + wave * TM, next);
 
-    // K^T V -> the three planes: a task is the eight rows of one lane half of a step, one column; with more than one
-    // partial they are summed on the way, in ascending order, and the first workgroup of the (b, h) leaves the sum in kv
-    for (int t = tid; t < NBITS / 8 * DVC; t += n_threads) {
-        const int col = t % DVC, grp = t / DVC;                    // grp = (half * 2 + s) * 2 + kg
-        const int bit0 = (grp >> 2) * 32 + ((grp >> 1) & 1) * 8 + (grp & 1) * 4;
-        const size_t at = ((size_t)bh * NBITS + bit0) * DV + c0 + col;
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = f.kv_in[at + ((e >> 1) + 16 * (e & 1)) * DV];
-        // (partial by partial: four at a time in flight took longer, by the registers or by what is read in vain behind the last ones.
-        // 4 x 8 heads x 4237 tokens x 128 bits x 32, 17 workgroups to a head, both products 25.2 -> 23.9 us, 4 x 12 x 3072 x 64 bits
-        // 19.7 -> 18.8, 4 x 12 x 300 x 256 bits 17.0 -> 16.5; 32 x 1 x 3136 x 64 bits 15.5 -> 15.6)
-        for (int s = 1; s < f.splits; ++s) {
-            const float *p = f.kv_in + (size_t)s * BH * NBITS * DV + at;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] += p[((e >> 1) + 16 * (e & 1)) * DV];
-        }
-        if (f.kv_out && part == 0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) f.kv_out[at + ((e >> 1) + 16 * (e & 1)) * DV] = x[e];
-        }
+    // K^T V -> the three planes: a task is the eight rows of one lane half of a step, one column
+    constexpr int TASKS = (NBITS / 8 * DVC + n_threads - 1) / n_threads;
+    auto bit_of = [&](int t, int e) {
+        const int grp = t / DVC;                                   // (half * 2 + s) * 2 + kg
+        return (grp >> 2) * 32 + ((grp >> 1) & 1) * 8 + (grp & 1) * 4 + (e >> 1) + 16 * (e & 1);
+    };
+    auto to_planes = [&](int t, const float (&x)[8]) {
         uint32_t w[3][4];
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
@@ -440,7 +426,63 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
         }
 #pragma unroll
         for (int p = 0; p < 3; ++p)
-            *reinterpret_cast<uint4 *>(kvt_s + p * PLANE + col * STRIDE + grp * 8) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+            *reinterpret_cast<uint4 *>(kvt_s + p * PLANE + t % DVC * STRIDE + t / DVC * 8) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+    };
+    if (SUMS && W == 1 && f.splits > 1) {
+        // More than one partial: summed on the way, in ascending order, and the first workgroup of the (b, h) leaves the sum in kv.
+        // A thread sums four columns of a row, eight partials in flight: they come from other CUs, and one after the other each took
+        // a trip of its own.  Both products of 32 x 3136 tokens x 1 head x 64 bits 17.1 -> 16.9 us, 4 x 12 x 3072 x 64 bits 29.1 -> 28.2,
+        // 128 x 1 x 2000 x 64 35.6 -> 35.1; attention of the first with its hash 22.95 -> 22.65.
+        constexpr int QUADS = NBITS * DVC / 4;
+        static_assert(QUADS % n_threads == 0 && QUADS * 16 <= 3 * PLANE * 2, "sums where the planes go");
+        f32x4 *sum_s = reinterpret_cast<f32x4 *>(lds);
+#pragma unroll
+        for (int i = 0; i < QUADS / n_threads; ++i) {
+            const int t = tid + i * n_threads;
+            const size_t at = ((size_t)bh * NBITS + t / (DVC / 4)) * DV + c0 + t % (DVC / 4) * 4, step = (size_t)BH * NBITS * DV;
+            f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int s0 = 0; s0 < f.splits; s0 += 8) {
+                f32x4 y[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (s0 + q < f.splits) y[q] = *reinterpret_cast<const f32x4 *>(f.kv_in + (s0 + q) * step + at);
+                x = s0 == 0 ? y[0] : x + y[0];
+#pragma unroll
+                for (int q = 1; q < 8; ++q)
+                    if (s0 + q < f.splits) x += y[q];
+            }
+            sum_s[t] = x;
+            if (f.kv_out && part == 0) *reinterpret_cast<f32x4 *>(f.kv_out + at) = x;
+        }
+        __syncthreads();
+        float x[TASKS][8];
+#pragma unroll
+        for (int i = 0; i < TASKS; ++i) {
+            const int t = min(tid + i * n_threads, NBITS / 8 * DVC - 1);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[i][e] = reinterpret_cast<const float *>(lds)[bit_of(t, e) * DVC + t % DVC];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < TASKS; ++i)
+            if (tid + i * n_threads < NBITS / 8 * DVC) to_planes(tid + i * n_threads, x[i]);
+    } else {
+        for (int t = tid; t < NBITS / 8 * DVC; t += n_threads) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = f.kv_in[((size_t)bh * NBITS + bit_of(t, e)) * DV + c0 + t % DVC];
+            // longer codes: fewer partials, of which the sums above have several quads a thread (4 x 8 heads x 4237 tokens x 128 bits 24.0, there
+            // 24.2; 16 x 4 x 1600 21.0, 20.6; 8 x 8 x 1500 x 256 bits 27.1, 27.4)
+            if constexpr (SUMS && W > 1) {
+                for (int s = 1; s < f.splits; ++s)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] += f.kv_in[(((size_t)s * BH + bh) * NBITS + bit_of(t, e)) * DV + c0 + t % DVC];
+                if (f.kv_out && part == 0)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) f.kv_out[((size_t)bh * NBITS + bit_of(t, e)) * DV + c0 + t % DVC] = x[e];
+            }
+            to_planes(t, x);
+        }
     }
     if (ZO) {
         for (int j = tid; j < NBITS; j += n_threads) {
@@ -568,7 +610,7 @@ template <int DVC, int W, int NW, int TM, bool ZO>
 __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f, int H, int Nq, int DV,
                                                            long BH, int blocks_per_bh, int tiles_per_block) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[QkvLds<DVC, W, ZO>::BYTES];
-    qkv_block<DVC, W, NW, TM, ZO>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds);
+    qkv_block<DVC, W, NW, TM, ZO, true>(q_codes, f, H, Nq, DV, BH, blocks_per_bh, tiles_per_block, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------- both, short sequences ----
@@ -588,7 +630,7 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t 
     static_assert(kKtvWaves / PH * WB == W, "a workgroup has all words");
     ktv_block<DVC, WB, PH, RING, false>(k_codes, v, kv, nullptr, BH, H, Nk, W, DV, 1, (Nk + 15) & ~15, blockIdx.x, lds);
     __syncthreads();
-    qkv_block<DVC, W, kKtvWaves, 1, false>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds);
+    qkv_block<DVC, W, kKtvWaves, 1, false, false>(q_codes, f, H, Nq, DV, BH, 1, (Nq + 31) / 32, blockIdx.x, lds);
 }
 
 // How the token tiles of a (b, h) are spread.

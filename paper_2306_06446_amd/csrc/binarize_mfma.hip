@@ -27,13 +27,13 @@
 //
 // What bounds it: at 256 bits the products and the vector work in their shadow (16 funnel shifts and 8 three-way minima
 // per 16 bits, 7 operations to split two elements); at 128 bits and fewer the rows of Q and K, with about 4.5 us before the
-// first product (3.5 of them the launch, 1 until the hash matrix has arrived) and 1 us of re-runs at the end.  More
+// first product (3.5 of them the launch, 1 until the hash matrix has arrived) and 1 us of re-runs at the end.  At d = 64 and 128 more
 // wavefronts or rows in flight gave nothing there.  The fragments are made from the registers the hash matrix is loaded
 // into: through LDS, with two more barriers and two passes over its fp32 form, a launch took 0.8 us longer at d = 64 and up
 // to 3.7 at d = 128.  Q and K, alone and over and over, 64 bytes of 16 rows per load -> now:
 //   64 x 197 x 12 heads x 64 -> 128 bits  25.1 -> 23.6 us      64 x 197 x 12 x 64 -> 64  19.2 -> 18.6
 //   64 x 197 x 3 x 64 -> 64               10.0 ->  9.2          8 x 1000 x 3 x 128 -> 128  14.8 -> 14.7
-//   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3 (launch_waves: 8.1)          1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
+//   32 x 3136 x 1 x 32 -> 64              11.0 -> 10.3 (8.1 by launch_waves)   1 x 197 x 3 x 64 -> 64      5.8 ->  5.7
 //    1 x 16384 x 4 x 64 -> 256            18.5 -> 17.4          8 x 16384 x 4 x 64 -> 256  110 -> 112 (as a stream; 104 without)
 #include "common.h"
 #include "hash_tile.h"

@@ -90,3 +90,10 @@ def test_passes_of_sixteen_wavefronts(sa, W):
 @pytest.mark.parametrize("H,N,W,dv", [(12, 137, 4, 64), (8, 300, 4, 32), (3, 1200, 2, 32), (2, 1500, 1, 64)])
 def test_a_few_partials(sa, H, N, W, dv):
     test_both_code_modes_against_fp64(sa, 1, H, N, N, W, dv)
+
+
+# 64 bits: two to sixteen partials, eight of which are in flight together; half of a head's columns to a workgroup; passes of sixteen wavefronts
+@pytest.mark.parametrize("H,Nq,Nk,dv", [(1, 40, 500, 32), (1, 257, 1790, 32), (2, 70, 2048, 32), (1, 300, 2300, 32), (3, 33, 4096, 32),
+                                        (1, 513, 3900, 32), (2, 600, 2040, 64), (2, 100, 1000, 128), (8, 32777, 1500, 64)])
+def test_partials_summed_by_quads(sa, H, Nq, Nk, dv):
+    test_both_code_modes_against_fp64(sa, 1, H, Nq, Nk, 1, dv)
