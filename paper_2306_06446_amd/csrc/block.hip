@@ -336,7 +336,9 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     if (rc != SA_OK) return rc;
 
     // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y.  Narrow rows are normalised by the projection's workgroups.
-    const bool norm_linear = !fused_hash && d->shift_variant == SA_VARIANT_MFMA_PREPARED && sa::norm_linear_one_launch(T, E);
+    const bool norms = !fused_hash && d->shift_variant == SA_VARIANT_MFMA_PREPARED;
+    const bool norm_hash = norms && d->proj && sa::norm_hash_one_launch(T, E, d->H, d->nbits);
+    const bool norm_linear = norm_hash || (norms && sa::norm_linear_one_launch(T, E));
     if (!norm_linear) {
         rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
                                 nullptr, 0, nullptr, stream);
@@ -351,7 +353,6 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                                        ws + L.lin_ws, L.lin_ws_bytes, stream);
         if (rc != SA_OK) return rc;
     } else {
-        const bool norm_hash = norm_linear && d->proj && !side.any() && sa::norm_hash_one_launch(T, E, d->H, d->nbits);
         if (norm_linear) {
             sa::NormRows norm;
             norm.x = d->x;

@@ -14,6 +14,9 @@
 // 25088 rows of E = 64, two heads of 32, 64 bits: 39.1, 33.4 (in a trace 12.2, 8.7 + 7.7).  Fragments of the hash matrix in registers,
 // with rows split once by the wavefront that has their sums, halve the LDS reads and make the chain longer: layers of 16384 rows 103.3
 // where these are 98.0.
+//
+// With few rows (by_chunks) each workgroup makes one chunk: DeiT-Tiny layer of one image 41.5 -> 38.7 us, of which three launches were
+// LayerNorm 2.9, projection 4.4, hash 6.6.
 #include "common.h"
 #include "gemm_common.h"
 #include "gemm_mfma.h"
@@ -64,7 +67,8 @@ __device__ inline float sum_of_rows(float v) {
     return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
 }
 
-template <int NE, int D, int NB>
+// SPLIT: workgroup 3 NE r + c makes chunk c of its rows alone.
+template <int NE, int D, int NB, bool SPLIT>
 __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_hash_kernel(NormRows norm, long n_rows, const int8_t *__restrict__ w,
                                                                                  float scale, HashOut h, float *__restrict__ v) {
     using S = NormHashShape<NE, D, NB>;
@@ -88,6 +92,8 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
         }
     };
     constexpr int UNITS = 6 * NE;
+    const int only = SPLIT ? (int)(blockIdx.x % (3 * NE)) : 0;           // the chunk of a SPLIT workgroup
+    const bool hashes = !SPLIT || only < 2 * NE;
     // this wavefront's rows to normalise, LPR lanes each
     constexpr int LPR = NE == 1 ? 16 : NE == 2 ? 32 : 64, LANES = 64 / LPR, STEPS = kRows / kWaves / LANES;
     const int l = lane % LPR, row0 = wave * (kRows / kWaves) + lane / LPR;
@@ -99,7 +105,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
         for (int i = 0; i < STEPS; ++i)
             xr[i] = *reinterpret_cast<const float4 *>(norm.x + (size_t)min(m0 + row0 + LANES * i, n_rows - 1) * E + col);
     };
-    long m0 = (long)blockIdx.x * kRows;
+    long m0 = (long)(SPLIT ? blockIdx.x / (3 * NE) : blockIdx.x) * kRows;
     if (m0 >= n_rows) return;
     load_rows(m0);
     const float4 gamma = *reinterpret_cast<const float4 *>(norm.gamma + col);
@@ -108,7 +114,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
     // ---- the hash matrix, as fragments of its normalised columns (upper and lower fp16 terms).  Lane group q of a product's result
     //      has columns COLS / 4 q .. of a wavefront's COLS.
     const int hc = tid % NB, part = tid / NB;
-    const bool mine = part < S::TPC;
+    const bool mine = hashes && part < S::TPC;
     float hv[S::TASKS][8];
     auto k_of = [&](int i, int e) {
         const int j = part + i * S::TPC;                                 // task j: 32 (j / 4) + 4 (j % 4) and 16 further on
@@ -120,8 +126,8 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
 #pragma unroll
             for (int e = 0; e < 8; ++e) hv[i][e] = h.proj[(size_t)k_of(i, e) * NB + hc];
     }
-    issue(0, 0);
-    issue(1, 1);
+    issue(2 * only, 0);
+    issue(2 * only + 1, 1);
     float *norms = reinterpret_cast<float *>(lds + S::NORMS);
     uint4 *frags = reinterpret_cast<uint4 *>(lds + S::FRAGS);
     if (mine) {
@@ -170,13 +176,14 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
     const int head = S::HEADS == 2 ? wave & 1 : 0;
     const int unit0 = (wave / (S::GROUPS * S::HEADS)) * NU;              // first of its row units
 
-    int slot = 0, ahead = 2;                                 // the unit's place in the ring; the next unit to load
+    const int units = SPLIT ? 2 * only + 2 : UNITS;
+    int slot = 0, ahead = 2 * only + 2;                      // the unit's place in the ring; the next unit to load
     // Stores that this wavefront issued at the end of the last chunk, at least: behind the loads that either half of the next one waits
     // for, which need not wait for them as well.
     int stores = 0;
     for (;;) {
         const long next_m0 = m0 + (long)gridDim.x * kRows;
-        const bool more = next_m0 < n_rows;
+        const bool more = !SPLIT && next_m0 < n_rows;
         // ---- LayerNorm: codes to LDS, from there to all wavefronts as operands
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
@@ -213,13 +220,13 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
         auto multiply = [&](int p) {
             // this unit is there, the next one need not be; everyone is through with the one before, whose place the unit after
             // the next one takes
-            if (!(ahead <= UNITS || more)) wait_loads_in_flight<0>();
+            if (!(ahead <= units || more)) wait_loads_in_flight<0>();
             else if (stores == 0) wait_loads_in_flight<S::LOADS>();
             else if (stores == 1) wait_loads_in_flight<S::LOADS + 1>();
             else wait_loads_in_flight<S::LOADS + 2>();
             __syncthreads();
             const int to = slot == 0 ? 2 : slot - 1;
-            if (ahead < UNITS) issue(ahead, to);
+            if (ahead < units) issue(ahead, to);
             else if (more) issue(ahead - UNITS, to);
             ++ahead;
 #pragma unroll
@@ -235,15 +242,17 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
         };
         // A chunk's sums are Q's or K's (staged) or V's; between the two halves of its products come the operands of the chunk before,
         // behind them that one's hash.  A chunk of staged rows is read behind a barrier and written over behind another.
+        // (A SPLIT workgroup's only chunk is hashed with no products beside it.)
         auto chunk = [&](int c, auto hash_c, auto staged_c) {
-            constexpr bool HASH = decltype(hash_c)::value, STAGED = decltype(staged_c)::value;
+            constexpr bool HASH = decltype(hash_c)::value, STAGED = decltype(staged_c)::value, PRODUCTS = !(SPLIT && HASH);
             // (the lane's addresses are made here, not kept from chunk to chunk: the registers are needed)
             int of_lane = lane;
             asm volatile("" : "+v"(of_lane));
             const int fr = of_lane & 15, fg = of_lane >> 4;
             // row 16 (unit0 + u) + fr of the chunk's head, this lane's k = 32 s + 16 o + 4 fg ..
             v4f x[NU][KS][2];
-            multiply(0);
+            if constexpr (PRODUCTS) multiply(0);
+            else __syncthreads();
             if constexpr (HASH) {
 #pragma unroll
                 for (int u = 0; u < NU; ++u)
@@ -252,7 +261,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
 #pragma unroll
                         for (int o = 0; o < 2; ++o) x[u][s][o] = *staged(c - 1, 16 * (unit0 + u) + fr, head * (D / 4) + 8 * s + 4 * o + fg);
             }
-            multiply(1);
+            if constexpr (PRODUCTS) multiply(1);
             if constexpr (HASH) {
                 const bool second = c - 1 >= NE;
                 const int head0 = (second ? c - 1 - NE : c - 1) * S::HEADS + head;       // of the layer
@@ -354,6 +363,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
                     }
                 }
             }
+            if constexpr (!PRODUCTS) return;
             stores = HASH && m0 + 16 * unit0 < n_rows ? 1 : 0;
             if constexpr (!STAGED) stores = (m0 + wr * 32 < n_rows) + (m0 + wr * 32 + 16 < n_rows);
 #pragma unroll
@@ -365,6 +375,12 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
                 else if (m0 + r < n_rows) *reinterpret_cast<v4f *>(v + (size_t)(m0 + r) * E + (c - 2 * NE) * kChunk + wc * 16 + 4 * fg) = y;
             }
         };
+        if constexpr (SPLIT) {
+            if (!hashes) return chunk(only, std::false_type{}, std::false_type{});
+            chunk(only, std::false_type{}, std::true_type{});
+            chunk(only + 1, std::true_type{}, std::false_type{});
+            break;
+        }
         chunk(0, std::false_type{}, std::true_type{});
 #pragma unroll 1
         for (int c = 1; c < 2 * NE; ++c) chunk(c, std::true_type{}, std::true_type{});
@@ -396,19 +412,22 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
 }
 
 template <int NE, int D, int NB>
-int launch(const NormRows &norm, long T, const int8_t *w, float scale, const HashOut &h, float *v, hipStream_t st) {
+int launch(const NormRows &norm, long T, const int8_t *w, float scale, const HashOut &h, float *v, bool split, hipStream_t st) {
     using S = NormHashShape<NE, D, NB>;
     const long blocks = (T + kRows - 1) / kRows, most = 256 * S::PER_CU;
-    norm_hash_kernel<NE, D, NB><<<dim3((unsigned)(blocks < most ? blocks : most)), dim3(kWaves * 64), 0, st>>>(norm, T, w, scale, h, v);
+    if (split)
+        norm_hash_kernel<NE, D, NB, true><<<dim3((unsigned)(blocks * 3 * NE)), dim3(kWaves * 64), 0, st>>>(norm, T, w, scale, h, v);
+    else
+        norm_hash_kernel<NE, D, NB, false><<<dim3((unsigned)(blocks < most ? blocks : most)), dim3(kWaves * 64), 0, st>>>(norm, T, w, scale, h, v);
     return check_launch("LayerNorm, QKV projection and hash");
 }
 
 template <int NE>
-int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, const HashOut &h, int d, int nbits, float *v, hipStream_t st) {
-    if (d == 32) return launch<NE, 32, 64>(norm, T, w, scale, h, v, st);
-    return nbits == 64    ? launch<NE, 64, 64>(norm, T, w, scale, h, v, st)
-           : nbits == 128 ? launch<NE, 64, 128>(norm, T, w, scale, h, v, st)
-                          : launch<NE, 64, 256>(norm, T, w, scale, h, v, st);
+int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, const HashOut &h, int d, int nbits, float *v, bool split, hipStream_t st) {
+    if (d == 32) return launch<NE, 32, 64>(norm, T, w, scale, h, v, split, st);
+    return nbits == 64    ? launch<NE, 64, 64>(norm, T, w, scale, h, v, split, st)
+           : nbits == 128 ? launch<NE, 64, 128>(norm, T, w, scale, h, v, split, st)
+                          : launch<NE, 64, 256>(norm, T, w, scale, h, v, split, st);
 }
 
 }  // namespace
@@ -426,10 +445,26 @@ int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, con
 //   of 64 116.6, 121.2; 65536 with 256 bits 287.8, 290.2 -- until Q, K and V outgrow the cache behind L2 and hashing from memory costs
 //   more: 64 bits (128) 95000 rows 156.6, 159.8; 100000 184.7, 182.7; 131072 229.2, 196.3; (192) 49152 160.5, 165.9; 65536 199.4, 192.8;
 //   (256) 46000 178.2, 181.8; 49152 189.9, 184.8; 80000, heads of 32 318.2, 270.0.
+//
+// Few rows: a workgroup for every 64 columns of Wqkv of 64 rows, all of which normalise the same rows and none of which does more than
+// one chunk.  Up to one for every CU, a little over for two widths; what takes the call otherwise (two or three launches, or one with all
+// chunks), and this, us:
+//   E =  64   64 bits: 197 rows 19.5, 18.1; 5440 25.8, 24.4; 16384 28.2, 30.2.  256 bits: 197 rows 32.1, 29.6; 5440 36.9, 34.3; 8000 38.3, 41.0
+//   E = 128   64 bits: 197 rows 30.5, 25.3; 2730 38.0, 32.3; 5400 39.2, 39.0.  128 bits: 5400 rows 44.5, 43.4; 8000 45.4, 49.9
+//            256 bits: 197 rows 39.5, 36.0; 3152 48.2, 43.2; 4096 47.1, 48.4
+//   E = 192   64 bits: 197 rows 34.6, 31.8; 1792 41.4, 37.6; 1856 41.6, 43.3.  256 bits: 197 rows 43.5, 42.8; 1792 55.5, 49.7; 1856 55.0, 55.5
+//   E = 256   64 bits: 49 rows 32.2, 28.9; 1344 43.3, 38.0; 1700 44.4, 44.1; 2364 51.9, 52.2.  256 bits: 1344 rows 57.2, 50.5; 1700 57.9, 55.7
+static bool by_chunks(long T, int E, int nbits) {
+    const int most = E == 128 && nbits <= 128 ? 512 : E == 128 || E == 256 ? 320 : 256;
+    return (T + kRows - 1) / kRows * (3 * E / 64) <= most;
+}
+
 bool sa::norm_hash_one_launch(long T, int E, int H, int nbits) {
     const int d = E / H;
     if (!((d == 32 && nbits == 64) || (d == 64 && (nbits == 64 || nbits == 128 || nbits == 256)))) return false;
-    if (!norm_linear_one_launch(T, E) || T * H >= (1L << 31)) return false;
+    if (E > 256 || E % 64 != 0 || T * H >= (1L << 31)) return false;
+    if (by_chunks(T, E, nbits)) return true;
+    if (!norm_linear_one_launch(T, E)) return false;
     if (E == 64) return true;
     if (T <= 256 * kRows) return nbits == 64 || T >= (nbits == 128 ? 3072 : 12288);
     return nbits == 64 && T * E >= 3L << 22;
@@ -439,11 +474,12 @@ int sa::launch_norm_hash(const NormRows &norm, int B, int N, int H, int E, const
                          float *q, float *k, uint64_t *q_codes, uint64_t *k_codes, float *v, hipStream_t st) {
     const HashOut h{proj, q, k, Tensors{q, k, q_codes, k_codes}, RowMap{FastDiv((uint32_t)H), FastDiv((uint32_t)N), N, H, nbits / 64}};
     const long T = (long)B * N;
+    const bool split = by_chunks(T, E, nbits);
     switch (E) {
-        case 64: return launch_width<1>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, st);
-        case 128: return launch_width<2>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, st);
-        case 192: return launch_width<3>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, st);
-        case 256: return launch_width<4>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, st);
+        case 64: return launch_width<1>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, split, st);
+        case 128: return launch_width<2>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, split, st);
+        case 192: return launch_width<3>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, split, st);
+        case 256: return launch_width<4>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, split, st);
     }
     return fail(SA_ERR_UNSUPPORTED, "layer: width %d with the hash in the projection", E);
 }

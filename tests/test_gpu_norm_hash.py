@@ -17,6 +17,11 @@ pytestmark = pytest.mark.gpu
     (1, 10369, 3, 192, 128, 0, 2.0**-12), (3, 4098, 3, 192, 256, 0, 2.0**-12), (2, 32801, 3, 192, 64, 0, 2.0**-12),
     (1, 13825, 8, 256, 64, 0, 2.0**-12), (128, 127, 4, 256, 64, 1, 2.0**-12), (2, 7001, 4, 256, 128, 0, 2.0**-12),
     (1, 16384, 4, 256, 256, 0, 2.0**-12), (1, 16385, 4, 256, 256, 0, 2.0**-12),
+    # a workgroup per chunk: one row, and the last rows that take it, with one more each
+    (1, 1, 3, 192, 64, 0, 2.0**-12), (1, 3, 4, 256, 256, 1, 2.0**-12), (1, 1, 4, 128, 64, 0, 2.0**20), (9, 21, 3, 192, 256, 1, 2.0**-30),
+    (1, 5440, 1, 64, 128, 0, 2.0**-12), (1, 5441, 1, 64, 128, 0, 2.0**-12), (1, 5440, 4, 128, 64, 0, 2.0**-12), (1, 5441, 2, 128, 128, 0, 2.0**-12),
+    (1, 3392, 2, 128, 256, 0, 2.0**-12), (1, 3393, 2, 128, 256, 0, 2.0**-12), (8, 224, 3, 192, 64, 1, 2.0**-12), (1, 1793, 6, 192, 64, 0, 2.0**-12),
+    (1, 1664, 8, 256, 64, 0, 2.0**-40), (1, 1665, 4, 256, 128, 0, 2.0**-12),
 ])
 def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attention, qkv_scale):
     g = torch.Generator(device="cuda")
