@@ -338,7 +338,8 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y.  Narrow rows are normalised by the projection's workgroups.
     const bool norms = !fused_hash && d->shift_variant == SA_VARIANT_MFMA_PREPARED;
     const bool norm_hash = norms && d->proj && sa::norm_hash_one_launch(T, E, d->H, d->nbits);
-    const bool norm_linear = norm_hash || (norms && sa::norm_linear_one_launch(T, E));
+    const bool linear_hash = norms && !norm_hash && d->proj && sa::linear_hash_one_launch(T, E, d->H, d->nbits);
+    const bool norm_linear = norm_hash || (norms && !linear_hash && sa::norm_linear_one_launch(T, E));
     if (!norm_linear) {
         rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
                                 nullptr, 0, nullptr, stream);
@@ -365,11 +366,14 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                                           q, k, qc, kc, v, sa::as_stream(stream));
             else
                 rc = sa::launch_norm_linear(norm, T, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, q, k, v, sa::as_stream(stream));
+        } else if (linear_hash) {
+            rc = sa::launch_linear_hash(codes8, d->B, d->N, d->H, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, d->proj, d->nbits,
+                                        q, k, qc, kc, v, sa::as_stream(stream));
         } else {
             rc = sa_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, d->qkv_scale, nullptr, 3, q, k, v,
                                      ws + L.lin_ws, L.lin_ws_bytes, stream);
         }
-        if (rc == SA_OK && !norm_hash) rc = hash_and_side(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, side, stream);
+        if (rc == SA_OK && !norm_hash && !linear_hash) rc = hash_and_side(q, k, d->B, d->N, d->H, dv, d->proj, d->nbits, qc, kc, side, stream);
         if (rc != SA_OK) return rc;
     }
     if (d->attention == 0) {

@@ -237,6 +237,10 @@ int launch_norm_linear(const NormRows &norm, long T, int E, const int8_t *wqkv_p
 bool norm_hash_one_launch(long T, int E, int H, int nbits);
 int launch_norm_hash(const NormRows &norm, int B, int N, int H, int E, const int8_t *wqkv_planes, float scale, const float *proj, int nbits,
                      float *q, float *k, uint64_t *q_codes, uint64_t *k_codes, float *v, hipStream_t st);
+// The projection of codes that are normalised already, with the hash of Q and K in it (linear_hash.hip).
+bool linear_hash_one_launch(long T, int E, int H, int nbits);
+int launch_linear_hash(const int8_t *codes, int B, int N, int H, int E, const int8_t *wqkv_planes, float scale, const float *proj, int nbits,
+                       float *q, float *k, uint64_t *q_codes, uint64_t *k_codes, float *v, hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).
 size_t moe_dispatch_scratch_bytes(long T, int E);
 int moe_dispatch_launch(const float *logits, long T, int E, int32_t *perm, int32_t *expert_of, int32_t *counts, float *gate,

@@ -109,6 +109,8 @@ __device__ inline int swizzle(int r, int c) {
 //   static constexpr bool kSignCodes  : tiles left of column code_cols leave as packed sign bits instead
 //       (bit = acc >= 0, 64 columns = one word): uint64_t *codes[2] (column block 0 / 1 of width part_width,
 //       laid out [batch, head, token, word]), int head_dim (64 or 128), tokens (per batch element), heads
+//   static constexpr int  kHashBytes  : (kSignCodes only) 0, or the LDS that hash(acc, lds, m, n_rows, col, tid) takes, which makes code
+//       words of those tiles' rows in place of their sign bits
 //   static constexpr bool kLinear     : fp32 outputs leave as fma(value, scale, residual[m, n]) into
 //       column blocks: float *parts[3], int part_width (a multiple of 4), const float *residual, float scale
 
@@ -241,7 +243,8 @@ struct NtShape {
     static constexpr int STAGE = (BM + T::kPlanes * BN) * SB;
     // epilogue staging: 32 rows of a wavefront's columns each, 16 bytes apart modulo the banks
     static constexpr int PITCH = BN / 2 * Store::kBytes + 16, SLAB_BYTES = 32 * PITCH;
-    static constexpr int RING_BYTES = NS * STAGE > 4 * SLAB_BYTES ? NS * STAGE : 4 * SLAB_BYTES;
+    static constexpr int OUT_BYTES = 4 * SLAB_BYTES > Store::kHashBytes ? 4 * SLAB_BYTES : Store::kHashBytes;
+    static constexpr int RING_BYTES = NS * STAGE > OUT_BYTES ? NS * STAGE : OUT_BYTES;
     // a ring that fills half of a CU's LDS to the last byte: the side loads wait for the ring to be free
     static constexpr bool SIDE_LATE = RING_BYTES == 80 * 1024 && OutSide<Store, BM>::BYTES > 0;
     static constexpr int SIDE_AT = SIDE_LATE ? 4 * SLAB_BYTES : RING_BYTES;
@@ -548,6 +551,10 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
         if (n0 < store.code_cols) {               // uniform per workgroup
             static_assert(NJ <= 2, "a wavefront's columns lie inside one code word");
             const int col0 = n0 + wn;
+            if constexpr (Store::kHashBytes != 0) {
+                static_assert(NJ == 2, "a wavefront has all columns of a head");
+                return store.hash(acc, lds, m0 + wm, n_rows, col0, tid);
+            }
             const int part = col0 / store.part_width;
             const int cin = col0 - part * store.part_width;
             const int head = cin / store.head_dim, w = (cin % store.head_dim) / 64, W = store.head_dim / 64;

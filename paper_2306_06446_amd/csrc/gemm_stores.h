@@ -18,6 +18,7 @@ struct ShiftStore {
     static constexpr bool kScatter = (MODE == kEpiScatterI32);
     static constexpr bool kLinear = (MODE == kEpiLinearF32 || MODE == kEpiQkvCodes);
     static constexpr bool kSignCodes = (MODE == kEpiQkvCodes);
+    static constexpr int kHashBytes = 0;
     Epilogue e;
     void *out;             // int32 rows | int8 hidden rows | scattered fp32 rows
     const void *table;     // the 256-entry activation table
@@ -81,6 +82,7 @@ struct MultStore {
     static constexpr bool kScatter = (MODE == kEpiScatterF32);
     static constexpr bool kLinear = false;
     static constexpr bool kSignCodes = false;
+    static constexpr int kHashBytes = 0;
     void *out;                      // compact fp32 rows | fp16 hidden rows | scattered fp32 rows
     const void *table = nullptr;
     const float *gate;

@@ -441,10 +441,9 @@ int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, con
 //                  128 bits: (128) 1576 rows 41.8, 42.2; 3152 43.5, 42.5; (192) 10400 65.1, 65.1; (256) 16384 86.5, 79.8
 //                  256 bits: (128) 1576 rows 45.1, 48.3; 10400 56.4, 56.7; 13900 59.0, 57.1; (192) 10400 73.9, 76.8; 12000 80.5, 80.0;
 //                            (256) 16384 102.4, 96.7
-//   beyond, rounds of workgroups that take long lose more than the traffic saved: (192) 20000 rows, 64 bits 87.3, 92.5; (256) 32700, heads
-//   of 64 116.6, 121.2; 65536 with 256 bits 287.8, 290.2 -- until Q, K and V outgrow the cache behind L2 and hashing from memory costs
-//   more: 64 bits (128) 95000 rows 156.6, 159.8; 100000 184.7, 182.7; 131072 229.2, 196.3; (192) 49152 160.5, 165.9; 65536 199.4, 192.8;
-//   (256) 46000 178.2, 181.8; 49152 189.9, 184.8; 80000, heads of 32 318.2, 270.0.
+//   beyond, rounds of workgroups that take long lose more than the traffic saved (128, 20000 rows of 64 bits 58.1 with two launches) until
+//   Q, K and V outgrow the cache behind L2: 64 bits (128) 95000 rows 156.6, 159.8; 100000 184.7, 182.7; 131072 229.2, 196.3.  Wider rows go
+//   to linear_hash.hip there (192: 65536 rows 185.3, 179.0; 256: 100000 rows 419.7, 388.9), as do few of them that this does not take.
 //
 // Few rows: a workgroup for every 64 columns of Wqkv of 64 rows, all of which normalise the same rows and none of which does more than
 // one chunk.  Up to one for every CU, a little over for two widths; what takes the call otherwise (two or three launches, or one with all
@@ -453,9 +452,9 @@ int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, con
 //   E = 128   64 bits: 197 rows 30.5, 25.3; 2730 38.0, 32.3; 5400 39.2, 39.0.  128 bits: 5400 rows 44.5, 43.4; 8000 45.4, 49.9
 //            256 bits: 197 rows 39.5, 36.0; 3152 48.2, 43.2; 4096 47.1, 48.4
 //   E = 192   64 bits: 197 rows 34.6, 31.8; 1792 41.4, 37.6; 1856 41.6, 43.3.  256 bits: 197 rows 43.5, 42.8; 1792 55.5, 49.7; 1856 55.0, 55.5
-//   E = 256   64 bits: 49 rows 32.2, 28.9; 1344 43.3, 38.0; 1700 44.4, 44.1; 2364 51.9, 52.2.  256 bits: 1344 rows 57.2, 50.5; 1700 57.9, 55.7
+//   E = 256   64 bits: 49 rows 32.2, 28.9; 1344 43.3, 38.0; 1576 43.4 (linear_hash.hip), 45.5.  256 bits: 1344 rows 57.2, 50.5; 1700 57.9, 55.7
 static bool by_chunks(long T, int E, int nbits) {
-    const int most = E == 128 && nbits <= 128 ? 512 : E == 128 || E == 256 ? 320 : 256;
+    const int most = E == 128 && nbits <= 128 ? 512 : E > 64 && E != 192 && nbits == 256 ? 320 : 256;
     return (T + kRows - 1) / kRows * (3 * E / 64) <= most;
 }
 
@@ -467,7 +466,7 @@ bool sa::norm_hash_one_launch(long T, int E, int H, int nbits) {
     if (!norm_linear_one_launch(T, E)) return false;
     if (E == 64) return true;
     if (T <= 256 * kRows) return nbits == 64 || T >= (nbits == 128 ? 3072 : 12288);
-    return nbits == 64 && T * E >= 3L << 22;
+    return E == 128 && nbits == 64 && T * E >= 3L << 22;
 }
 
 int sa::launch_norm_hash(const NormRows &norm, int B, int N, int H, int E, const int8_t *wqkv_planes, float scale, const float *proj, int nbits,

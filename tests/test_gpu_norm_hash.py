@@ -21,7 +21,15 @@ pytestmark = pytest.mark.gpu
     (1, 1, 3, 192, 64, 0, 2.0**-12), (1, 3, 4, 256, 256, 1, 2.0**-12), (1, 1, 4, 128, 64, 0, 2.0**20), (9, 21, 3, 192, 256, 1, 2.0**-30),
     (1, 5440, 1, 64, 128, 0, 2.0**-12), (1, 5441, 1, 64, 128, 0, 2.0**-12), (1, 5440, 4, 128, 64, 0, 2.0**-12), (1, 5441, 2, 128, 128, 0, 2.0**-12),
     (1, 3392, 2, 128, 256, 0, 2.0**-12), (1, 3393, 2, 128, 256, 0, 2.0**-12), (8, 224, 3, 192, 64, 1, 2.0**-12), (1, 1793, 6, 192, 64, 0, 2.0**-12),
-    (1, 1664, 8, 256, 64, 0, 2.0**-40), (1, 1665, 4, 256, 128, 0, 2.0**-12),
+    (1, 1344, 8, 256, 64, 0, 2.0**-40), (1, 1345, 4, 256, 128, 0, 2.0**-12), (1, 1664, 4, 256, 256, 0, 2.0**-12),
+    # the hash in the projection's tiles: rows too wide for a workgroup, and more narrower ones; both tiles, one row more than whole ones of
+    # them, columns of V that fill no tile, either side of the fewest rows and of a round of the smaller tiles
+    (1, 299, 12, 768, 64, 0, 2.0**-12), (4, 75, 12, 768, 64, 0, 2.0**-40), (1, 700, 6, 384, 128, 1, 2.0**20), (1, 1300, 5, 320, 256, 0, 2.0**-12),
+    (5, 197, 6, 384, 64, 0, 2.0**-12), (3, 401, 6, 384, 128, 1, 2.0**-12), (7, 197, 12, 768, 128, 1, 2.0**-140),
+    (3, 1792, 12, 768, 256, 0, 2.0**-12), (1, 5377, 12, 768, 64, 0, 2.0**-30), (33, 257, 12, 768, 128, 1, 2.0**-12), (2, 6001, 6, 384, 256, 0, 2.0**20),
+    (1, 8000, 5, 320, 128, 0, 2.0**-30), (3, 1111, 7, 448, 64, 0, 2.0**-12), (3, 1111, 14, 448, 64, 1, 2.0**-40), (1, 3000, 12, 384, 64, 0, 2.0**30),
+    (7, 450, 6, 192, 64, 0, 2.0**-12), (2, 1600, 3, 192, 128, 1, 2.0**-12), (1, 2600, 4, 256, 256, 0, 2.0**-12), (5, 4001, 8, 256, 64, 0, 2.0**-12),
+    (1, 20480, 4, 128, 64, 0, 2.0**-12), (1, 20481, 2, 128, 128, 0, 2.0**-12), (5, 8192, 4, 256, 256, 0, 2.0**-12), (3, 18205, 6, 192, 64, 0, 2.0**-12),
 ])
 def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attention, qkv_scale):
     g = torch.Generator(device="cuda")

@@ -55,6 +55,7 @@ def kernels():
     (r"qkv_mfma_kernel", 12),
     (r"ktv_mfma_kernel|ktv_qkv_kernel", 28),
     (r"norm_linear_kernel", 4),
+    (r"gemm_kernel.*HashStore", 8),
     (r"shift_mlp_kernel", 21),
 ])
 def test_no_scratch(kernels, pattern, instances):
