@@ -158,13 +158,12 @@ constexpr int stage_bytes_per_wave() { return 16 * stage_pitch<DV>(); }
 template <int DV>
 __device__ inline void write_outputs(v16f (&acc)[DV / 32], float den, uint8_t *stage, float *__restrict__ out,
                                             int8_t *__restrict__ xq, _Float16 *__restrict__ xh, float act_inv_scale, int b,
-                                            int h, int H, int Nq, int chunk, int wave, int lane) {
+                                            int h, int H, int Nq, int q_tile0, int lane) {
     constexpr int JT = DV / 32;
     constexpr int PITCH = stage_pitch<DV>();
     const int i_loc = lane & 31, kg = lane >> 5;
     den += __shfl_xor(den, 32);
     const float inv = 1.0f / den;
-    const int q_tile0 = chunk * (kMaxWaves * 32) + wave * 32;
     const size_t row_elems = (size_t)H * DV;
     const size_t tile_at = (((size_t)b * Nq + q_tile0) * H + h) * DV;      // element (q_tile0, column 0 of the head)
 #pragma unroll
@@ -344,7 +343,8 @@ __global__ __launch_bounds__(kMaxWaves *kWave) void hamming_mfma_kernel(
 
     __syncthreads();                               // every wavefront is through its steps: the planes become staging rows
     write_outputs<DV>(acc, den, reinterpret_cast<uint8_t *>(&vt_s[0][0]) + wave * stage_bytes_per_wave<DV>(), out, xq, xh,
-                             act_inv_scale, b, h, H, Nq, chunk, wave, lane);
+                             act_inv_scale, b, h, H, Nq, chunk * (kMaxWaves * 32) + wave * 32,
+                             lane);
 }
 
 // 32 code bits as 32 fp4 values: bit 1 -> -1.0, bit 0 -> +1.0 (flip: the other way round).  Dword i takes bits 4 j + i.
@@ -375,13 +375,14 @@ __device__ inline v8i signs_fp4(uint32_t bits, uint32_t one, bool flip) {      /
 // 4.5 before).  Around them: 3.5 us until the first chunk has landed, 1 to 1.5 us to split a chunk, 2 to 3 us of outputs per unit, overlapped
 // as far as two workgroups to a CU do.  64 x 12 heads x 197 x 128 bits x 64, in a block with all three output forms 37.4 -> 31.5 us (68 MB
 // out, 39 MB in), in a layer, int8 alone, 33.4 -> 28.7; 7 x 12 heads x 64 bits 12.0 -> 10.6.
+// A unit has `tiles` tiles of 32 queries, one for each of the first wavefronts; the others only load and split V.
 // Same arithmetic, same order, bit-identical results.  Row reference distances (ROWREF in the kernel above) need all key codes of a
 // unit before its first step and keep the kernel above.
 template <int DV, int W>
 __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
     const uint64_t *__restrict__ q_codes, const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
     float *__restrict__ out, int H, int Nq, int Nk, int q_chunks, float c2, int8_t *__restrict__ xq,
-    _Float16 *__restrict__ xh, float act_inv_scale, long n_units) {
+    _Float16 *__restrict__ xh, float act_inv_scale, long n_units, int tiles) {
     constexpr int JT = DV / 32;
     constexpr int NBITS = W * 64;
     constexpr int RPI = 1024 / (DV * 4);           // V rows one wavefront-wide 16-byte load brings
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
         const int chunk = (int)(u % q_chunks);
         int of_lane = lane;
         asm volatile("" : "+v"(of_lane));
-        const int qi = min(chunk * (kMaxWaves * 32) + wave * 32 + (of_lane & 31), Nq - 1);
+        const int qi = min((chunk * tiles + wave) * 32 + (of_lane & 31), Nq - 1);
         const uint32_t *from = reinterpret_cast<const uint32_t *>(q_codes) + ((size_t)bh * Nq + qi) * 2 * W + W * (of_lane >> 5);
 #pragma unroll
         for (int w = 0; w < W; ++w) dst[w] = from[w];
@@ -556,26 +557,28 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
             if (j2 == 0) load_query(u2, qn);
         }
         const uint64_t *kc = kc_s[buf];
-        const int n_full = n & ~31;                  // whole tiles first, then at most one masked one, or half of it
-        for (int k0 = 0; k0 < n_full; k0 += 32) {
-            const v16f at = distances(kc, k0);
-            step(at, 0, k0, n, std::false_type{});
-            __builtin_amdgcn_sched_barrier(0);
-            step(at, 1, k0, n, std::false_type{});
-        }
-        if (n_full < n) {
-            const v16f at = distances(kc, n_full);
-            step(at, 0, n_full, n, std::true_type{});
-            if (n_full + 16 < n) step(at, 1, n_full, n, std::true_type{});
+        if (wave < tiles) {
+            const int n_full = n & ~31;                  // whole tiles first, then at most one masked one, or half of it
+            for (int k0 = 0; k0 < n_full; k0 += 32) {
+                const v16f at = distances(kc, k0);
+                step(at, 0, k0, n, std::false_type{});
+                __builtin_amdgcn_sched_barrier(0);
+                step(at, 1, k0, n, std::false_type{});
+            }
+            if (n_full < n) {
+                const v16f at = distances(kc, n_full);
+                step(at, 0, n_full, n, std::true_type{});
+                if (n_full + 16 < n) step(at, 1, n_full, n, std::true_type{});
+            }
         }
         if (j2 == 0) {                               // last chunk of the unit
             const long bh = u / q_chunks;
             __syncthreads();                         // every wavefront is through its steps: the planes become staging rows
             int out_lane = lane;
             asm volatile("" : "+v"(out_lane));       // the outputs' addresses are made here, not kept through the steps
-            write_outputs<DV>(acc, den, reinterpret_cast<uint8_t *>(&vt_s[0][0]) + wave * stage_bytes_per_wave<DV>(), out,
-                                     xq, xh, act_inv_scale, (int)(bh / H), (int)(bh % H), H, Nq, (int)(u % q_chunks), wave,
-                                     out_lane);
+            if (wave < tiles)
+                write_outputs<DV>(acc, den, reinterpret_cast<uint8_t *>(&vt_s[0][0]) + wave * stage_bytes_per_wave<DV>(), out, xq, xh,
+                                  act_inv_scale, (int)(bh / H), (int)(bh % H), H, Nq, ((int)(u % q_chunks) * tiles + wave) * 32, out_lane);
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
@@ -762,8 +765,8 @@ __global__ __launch_bounds__(kMaxWaves *kWave) void hamming_mm_kernel(
     }
 
     __syncthreads();                               // every wavefront is through its tiles: the pool becomes staging rows
-    write_outputs<DV>(acc, den, pool_s + wave * stage_bytes_per_wave<DV>(), out, xq, xh, act_inv_scale, b, h, H, Nq, chunk,
-                             wave, lane);
+    write_outputs<DV>(acc, den, pool_s + wave * stage_bytes_per_wave<DV>(), out, xq, xh, act_inv_scale, b, h, H, Nq, chunk * (kMaxWaves * 32) + wave * 32,
+                             lane);
 }
 
 // Optional dump of the integer scores, one thread per (query, key) pair.
@@ -796,6 +799,7 @@ struct Launch {
     bool mm_scores;         // scores as sign dot products on the matrix cores (else XOR + popcount on the vector ALU)
     bool pipeline;          // several units per workgroup, the next chunk in flight (fp4 scores, no row reference)
     long n_units;
+    int tiles;              // 32-query tiles of a unit (pipeline)
     int8_t *xq;
     _Float16 *xh;
     float act_inv_scale;
@@ -835,7 +839,7 @@ void launch_hamming(const Launch &L) {
             const long slots = pipeline_slots<DV, W>((int)L.block.x);
             const long wgs = L.n_units < slots ? L.n_units : slots;
             hamming_pipe_kernel<DV, W><<<dim3((unsigned)wgs), L.block, 0, L.st>>>(L.q, L.k, L.v, L.out, L.H, L.Nq, L.Nk, L.q_chunks,
-                                                                                 L.c2, L.xq, L.xh, L.act_inv_scale, L.n_units);
+                                                                                 L.c2, L.xq, L.xh, L.act_inv_scale, L.n_units, L.tiles);
             return;
         }
     }
@@ -941,6 +945,18 @@ extern "C" int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_
     // outputs, one unit per workgroup 38 with popcount scores and 44 with bf16 ones (a byte of signs for every bit in LDS)
     L.pipeline = variant == SA_VARIANT_AUTO && !L.rowref && dv <= 64 && W <= 4;
     L.n_units = blocks;
+    L.tiles = (int)L.block.x / kWave;
+    // Few heads: units of four tiles while there is a CU for each.  Eight wavefronts split a chunk of V, four of them multiply, one a SIMD,
+    // where seven or eight shared the four SIMDs of fewer CUs.  Whole layers, us: 7 x 12 heads x 197 x 64 bits 54.7 -> 53.7, 4 x 2 x 784
+    // (width 32) 38.4 -> 35.9, 8 x 2 x 1100 51.0 -> 47.9, 20 x 3 x 400 x 128 bits 59.3 -> 57.8; with two units for some CUs 14 x 12 x 197 78.1 -> 79.6,
+    // 9 x 12 x 300 85.9 -> 87.4; units of two tiles 4 x 2 x 784 35.6, 8 x 2 x 1100 52.8.
+    const long tiles = ((long)Nq + 31) / 32, fours = (tiles + 3) / 4;
+    if (L.pipeline && tiles > 4 && BH * fours <= 256) {
+        L.tiles = 4;
+        L.q_chunks = (int)fours;
+        L.n_units = BH * fours;
+        L.block = dim3(kMaxWaves * kWave);
+    }
     switch (dv) {
         case 32: dispatch_w<32>(W, L); break;
         case 64: dispatch_w<64>(W, L); break;

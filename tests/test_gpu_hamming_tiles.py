@@ -28,3 +28,17 @@ def test_distances_of_every_remainder(sa, Nk, nbits, dv):
     p = torch.softmax(0.125 * (s[0] @ s[1].transpose(-1, -2).contiguous()), -1)
     o = (p @ v.double().transpose(1, 2).contiguous()).transpose(1, 2)
     assert float((got[0].double() - o).abs().max()) <= 1e-4 * float(o.abs().max())
+
+
+# Units of four tiles: the fewest queries that are split, last units of one row and of whole tiles, one unit for every CU and a few more.
+@pytest.mark.parametrize("B,H,Nq,Nk,nbits,dv", [(1, 1, 128, 40, 64, 64), (1, 1, 129, 197, 64, 64), (3, 4, 197, 197, 128, 64), (1, 3, 256, 300, 256, 32),
+                                                (2, 2, 385, 129, 64, 32), (64, 2, 133, 17, 128, 32), (43, 3, 133, 17, 128, 32)])
+def test_units_of_four_tiles(sa, B, H, Nq, Nk, nbits, dv):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Nq + nbits)
+    q, k = (torch.randint(-2 ** 62, 2 ** 62, (B, H, n, nbits // 64), generator=g, device="cuda") for n in (Nq, Nk))
+    v = torch.randn((B, Nk, H, dv), generator=g, device="cuda")
+    got = sa.sa_hamming_attention_fused(q, k, v, 0.125, nbits, 20.0, variant=2)
+    ref = sa.sa_hamming_attention_fused(q, k, v, 0.125, nbits, 20.0, variant=0)
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
