@@ -394,23 +394,22 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     if (rc != SA_OK) return rc;
     const bool one_launch = !moe && weights.variant == SA_VARIANT_MFMA_PREPARED && sa::shift_mlp_one_launch(sel, E, d->hid, sa::kMlpInLayer);
     const bool project = one_launch && d->shift_variant == SA_VARIANT_MFMA_PREPARED;
-    if (!project) {
+    sa::NormRows norm;
+    norm.x = norm.out = d->y;
+    norm.gamma = d->gamma2;
+    norm.beta = d->beta2;
+    norm.eps = d->eps;
+    norm.inv_scale = d->ln_inv_scale;
+    norm.residual = d->x;
+    norm.scale = d->o_scale;
+    const bool linear_norm = !one_launch && d->shift_variant == SA_VARIANT_MFMA_PREPARED && sa::linear_norm_one_launch(T, E);
+    if (project || linear_norm) norm.wo = reinterpret_cast<const int8_t *>(d->wo);
+    if (!norm.wo) {
         rc = sa_shift_linear_f32(codes8, d->wo, T, E, E, d->shift_variant, d->o_scale, d->x, 1, d->y, nullptr, nullptr,
                                  ws + L.lin_ws, L.lin_ws_bytes, stream);
         if (rc != SA_OK) return rc;
     }
     if (one_launch) {
-        sa::NormRows norm;
-        norm.x = norm.out = d->y;
-        norm.gamma = d->gamma2;
-        norm.beta = d->beta2;
-        norm.eps = d->eps;
-        norm.inv_scale = d->ln_inv_scale;
-        if (project) {
-            norm.wo = reinterpret_cast<const int8_t *>(d->wo);
-            norm.residual = d->x;
-            norm.scale = d->o_scale;
-        }
         sa::Epilogue e;
         e.yf = d->y;
         e.out_scale = d->out_scale;
@@ -418,8 +417,11 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
         return sa::launch_shift_mlp(codes8, &norm, sel, E, d->hid, reinterpret_cast<const int8_t *>(weights.w1),
                                     reinterpret_cast<const int8_t *>(weights.w2), d->lut, d->requant_scale, e, sa::as_stream(stream));
     }
-    rc = sa_layernorm_quant(d->y, T, E, d->gamma2, d->beta2, d->eps, d->ln_inv_scale, nullptr, codes8, xh,
-                            moe ? d->wg : nullptr, moe ? d->bg : nullptr, moe ? 2 : 0, logits, stream);
+    if (linear_norm)
+        rc = sa::launch_linear_norm(codes8, norm, T, E, {codes8, xh, d->wg, d->bg, logits}, sa::as_stream(stream));
+    else
+        rc = sa_layernorm_quant(d->y, T, E, d->gamma2, d->beta2, d->eps, d->ln_inv_scale, nullptr, codes8, xh,
+                                moe ? d->wg : nullptr, moe ? d->bg : nullptr, moe ? 2 : 0, logits, stream);
     if (rc != SA_OK) return rc;
     if (!moe) {
         return sa_shift_mlp(codes8, &all, E, d->hid, weights.w1, weights.w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,

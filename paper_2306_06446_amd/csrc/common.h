@@ -227,6 +227,16 @@ struct NormRows {
 // before it writes them).
 int launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                      const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st);
+// norm.out = norm.residual + norm.scale * norm.wo . codes and its LayerNorm in one launch (linear_norm.hip): whether it is the faster way,
+// and the launch.  The new codes may take the old ones' place.
+struct NormOut {
+    int8_t *codes;
+    void *half;              // fp16 rows, or null
+    const float *wg, *bg;    // router of two experts [E, 2], [2]
+    float *logits;           // [T, 2], or null
+};
+bool linear_norm_one_launch(long T, int E);
+int launch_linear_norm(const int8_t *codes, const NormRows &norm, long T, int E, const NormOut &to, hipStream_t st);
 // LayerNorm of all T rows of norm.x and the Q, K, V projection of its codes (decoded planes [3E, E]) in one launch
 // (norm_linear.hip): whether it is the faster way, and the launch.
 bool norm_linear_one_launch(long T, int E);

@@ -56,6 +56,7 @@ def kernels():
     (r"ktv_mfma_kernel|ktv_qkv_kernel", 28),
     (r"norm_linear_kernel", 4),
     (r"gemm_kernel.*HashStore", 8),
+    (r"linear_norm_kernel", 3),
     (r"shift_mlp_kernel", 21),
 ])
 def test_no_scratch(kernels, pattern, instances):
