@@ -338,7 +338,8 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     // attention half: X_attn = Attn(LayerNorm(X)) + X, left in y.  Narrow rows are normalised by the projection's workgroups.
     const bool norms = !fused_hash && d->shift_variant == SA_VARIANT_MFMA_PREPARED;
     const bool norm_hash = norms && d->proj && sa::norm_hash_one_launch(T, E, d->H, d->nbits);
-    const bool linear_hash = norms && !norm_hash && d->proj && sa::linear_hash_one_launch(T, E, d->H, d->nbits);
+    const bool packed = d->shift_variant == SA_VARIANT_MFMA || d->shift_variant == SA_VARIANT_AUTO;
+    const bool linear_hash = !fused_hash && !norm_hash && (norms || packed) && d->proj && sa::linear_hash_one_launch(T, E, d->H, d->nbits, packed);
     const bool norm_linear = norm_hash || (norms && !linear_hash && sa::norm_linear_one_launch(T, E));
     if (!norm_linear) {
         rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
@@ -367,7 +368,15 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
             else
                 rc = sa::launch_norm_linear(norm, T, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, q, k, v, sa::as_stream(stream));
         } else if (linear_hash) {
-            rc = sa::launch_linear_hash(codes8, d->B, d->N, d->H, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, d->proj, d->nbits,
+            const uint8_t *planes = d->wqkv;
+            if (packed) {                                    // decoded with the MLP's, which otherwise ride in the hash's launch
+                sa::DecodeWork wqkv;
+                sa::add_decode(&wqkv, d->wqkv, E, 3 * E, ws + L.lin_ws);
+                rc = sa::launch_decode_work(side.decode, wqkv, sa::as_stream(stream));
+                if (rc != SA_OK) return rc;
+                planes = ws + L.lin_ws;
+            }
+            rc = sa::launch_linear_hash(codes8, d->B, d->N, d->H, E, reinterpret_cast<const int8_t *>(planes), d->qkv_scale, d->proj, d->nbits,
                                         q, k, qc, kc, v, sa::as_stream(stream));
         } else {
             rc = sa_shift_linear_f32(codes8, d->wqkv, T, E, 3 * E, d->shift_variant, d->qkv_scale, nullptr, 3, q, k, v,

@@ -192,6 +192,7 @@ void add_decode(DecodeWork *w, const uint8_t *w4, int K, int N, void *planes);
 void shift_mlp_decode(DecodeWork *w, const uint8_t *w1, const uint8_t *w2, int E, int hid, long max_rows, void *workspace,
                       const uint8_t **planes1, const uint8_t **planes2);
 int launch_decode_work(const DecodeWork &w, hipStream_t st);
+int launch_decode_work(const DecodeWork &w, const DecodeWork &w2, hipStream_t st);      // both in one launch
 // The decoded planes of one layer: the caller's (prepared variant) or `planes`, filled by this call.
 int shift_linear_planes(const uint8_t *w4, int K, int N, int variant, void *planes, hipStream_t st, const int8_t **out);
 
@@ -248,7 +249,7 @@ bool norm_hash_one_launch(long T, int E, int H, int nbits);
 int launch_norm_hash(const NormRows &norm, int B, int N, int H, int E, const int8_t *wqkv_planes, float scale, const float *proj, int nbits,
                      float *q, float *k, uint64_t *q_codes, uint64_t *k_codes, float *v, hipStream_t st);
 // The projection of codes that are normalised already, with the hash of Q and K in it (linear_hash.hip).
-bool linear_hash_one_launch(long T, int E, int H, int nbits);
+bool linear_hash_one_launch(long T, int E, int H, int nbits, bool packed);
 int launch_linear_hash(const int8_t *codes, int B, int N, int H, int E, const int8_t *wqkv_planes, float scale, const float *proj, int nbits,
                        float *q, float *k, uint64_t *q_codes, uint64_t *k_codes, float *v, hipStream_t st);
 // The routing of sa_moe_dispatch without its argument checks (moe.hip).

@@ -225,9 +225,17 @@ int launch(const GemmArgs &g, const Epilogue &e, const float *proj, const Tensor
 //   E = 128  128 bits: 18000 rows 65.2, 60.7; 65536 130.6, 133.6; 90000 169.9, 166.2.  256 bits: 4096 rows 47.2, 50.2; 65536 151.5, 165.1
 // From a few hundred rows on, as the hash's share of a tile is the same for few rows; not between 20480 rows and where Q, K and V outgrow
 // the cache behind L2 (until then their way through memory costs less than what the tiles wait for each other) for narrow rows.
-bool sa::linear_hash_one_launch(long T, int E, int H, int nbits) {
+// Packed weights are decoded first, in a launch with those of the MLP, which as three launches rode in the hash's: from more rows on.
+//   E = 768   64 bits: 3152 rows 93.8, 93.7; 6304 130.3, 123.0; 12608 217.7, 195.2.  128 bits: 3152 98.4, 99.3; 12608 238.7, 221.4
+//            256 bits: 3152 rows 118.3, 118.0; 12608 270.9, 259.1
+//   E = 384  128 bits: 1576 rows 58.3, 60.0; 12608 115.4, 110.2; 50176 344.4, 310.9
+//   E = 256  128 bits: 6304 rows 71.2, 73.1; 12608 86.1, 82.6; 131072 528.0, 485.5.  256 bits: 12608 99.8, 99.0; 131072 607.9, 579.8
+//   E = 192   64 bits: 3152 rows 53.2, 53.8; 12608 68.7, 64.7; 131072 387.1, 353.1.  256 bits: 50176 217.9, 218.4
+//   E =  64   64 bits: 12608 rows 37.8, 38.0; 131072 118.1, 111.1.  256 bits: 131072 153.2, 164.6
+bool sa::linear_hash_one_launch(long T, int E, int H, int nbits, bool packed) {
     const int d = E / H;
     if (!((d == 32 && nbits == 64) || (d == 64 && (nbits == 64 || nbits == 128 || nbits == 256))) || E % 64 != 0 || T * H >= (1L << 31)) return false;
+    if (packed) return T * E >= 3L << 20 && (nbits < 256 || E >= 256);
     if (E <= 256 && T > 20480 && (T * E < 10L << 20 || (nbits == 256 && E < 256))) return false;
     if (nbits == 256) return E > 256 ? T >= 1300 : T * E >= 650L << 10;
     return T >= (nbits == 64 ? 300 : 700);

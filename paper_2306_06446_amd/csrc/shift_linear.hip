@@ -169,8 +169,16 @@ int decode_planes(const uint8_t *w4, int K, int N, void *planes, hipStream_t st)
     return check_launch("shift layer (weight decode)");
 }
 
+// Two such jobs, the second from workgroup `first` on.
+__global__ __launch_bounds__(256) void decode_works_kernel(DecodeWork w, DecodeWork w2, unsigned first) {
+    if (blockIdx.x < first) decode_block<256>(w, blockIdx.x);
+    else decode_block<256>(w2, blockIdx.x - first);
+}
+
+unsigned decode_blocks(const DecodeWork &w) { return (unsigned)((w.chunks[0] + w.chunks[1] + 255) / 256); }
+
 int launch_decode(const DecodeWork &w, hipStream_t st) {
-    decode_work_kernel<<<dim3((unsigned)((w.chunks[0] + w.chunks[1] + 255) / 256)), dim3(256), 0, st>>>(w);
+    decode_work_kernel<<<dim3(decode_blocks(w)), dim3(256), 0, st>>>(w);
     return check_launch("shift layers (weight decode)");
 }
 
@@ -508,6 +516,12 @@ void sa::shift_mlp_decode(DecodeWork *w, const uint8_t *w1, const uint8_t *w2, i
 }
 
 int sa::launch_decode_work(const DecodeWork &w, hipStream_t st) { return launch_decode(w, st); }
+
+int sa::launch_decode_work(const DecodeWork &w, const DecodeWork &w2, hipStream_t st) {
+    const unsigned blocks = decode_blocks(w);
+    decode_works_kernel<<<dim3(blocks + decode_blocks(w2)), dim3(256), 0, st>>>(w, w2, blocks);
+    return check_launch("layer (weight decode)");
+}
 
 // workspace layout of sa_shift_mlp: hidden int8 [max_rows, hid] | planes of w1 | planes of w2
 size_t sa::shift_linear_rows_workspace_bytes(int K, int N, int variant) {

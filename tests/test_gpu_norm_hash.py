@@ -30,6 +30,9 @@ pytestmark = pytest.mark.gpu
     (1, 8000, 5, 320, 128, 0, 2.0**-30), (3, 1111, 7, 448, 64, 0, 2.0**-12), (3, 1111, 14, 448, 64, 1, 2.0**-40), (1, 3000, 12, 384, 64, 0, 2.0**30),
     (7, 450, 6, 192, 64, 0, 2.0**-12), (2, 1600, 3, 192, 128, 1, 2.0**-12), (1, 2600, 4, 256, 256, 0, 2.0**-12), (5, 4001, 8, 256, 64, 0, 2.0**-12),
     (1, 20480, 4, 128, 64, 0, 2.0**-12), (1, 20481, 2, 128, 128, 0, 2.0**-12), (5, 8192, 4, 256, 256, 0, 2.0**-12), (3, 18205, 6, 192, 64, 0, 2.0**-12),
+    # packed weights: the last rows that keep launches of their own, and one more
+    (3, 1365, 12, 768, 64, 0, 2.0**-12), (1, 4096, 12, 768, 64, 0, 2.0**-12), (8, 1024, 6, 384, 128, 1, 2.0**20), (1, 8193, 6, 384, 256, 0, 2.0**-12),
+    (1, 49152, 2, 64, 64, 0, 2.0**-12), (3, 4097, 4, 256, 256, 0, 2.0**-40),
 ])
 def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attention, qkv_scale):
     g = torch.Generator(device="cuda")
