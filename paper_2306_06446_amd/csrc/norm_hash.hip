@@ -487,15 +487,19 @@ int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, con
 //   to linear_hash.hip there (192: 65536 rows 185.3, 179.0; 256: 100000 rows 419.7, 388.9), as do few of them that this does not take.
 //
 // Few rows: a workgroup for every 64 columns of Wqkv of 64 rows, all of which normalise the same rows and none of which does more than
-// one chunk.  Up to one for every CU, a little over for two widths; what takes the call otherwise (two or three launches, or one with all
-// chunks), and this, us:
-//   E =  64   64 bits: 197 rows 19.5, 18.1; 5440 25.8, 24.4; 16384 28.2, 30.2.  256 bits: 197 rows 32.1, 29.6; 5440 36.9, 34.3; 8000 38.3, 41.0
-//   E = 128   64 bits: 197 rows 30.5, 25.3; 2730 38.0, 32.3; 5400 39.2, 39.0.  128 bits: 5400 rows 44.5, 43.4; 8000 45.4, 49.9
-//            256 bits: 197 rows 39.5, 36.0; 3152 48.2, 43.2; 4096 47.1, 48.4
+// one chunk.  Up to one for every CU, and more where two share one or the other ways are slow; what takes the call otherwise (two or three
+// launches, or one with all chunks), and this, us:
+//   E =  64   64 bits: 197 rows 19.5, 18.1; 5600 25.7, 24.7; 10922 27.3, 26.4; 13000 27.7, 28.1.  256 bits: 197 rows 32.1, 29.6; 5440 36.9,
+//            34.3; 8000 38.3, 40.1
+//   E = 128   64 bits: 197 rows 30.5, 25.3; 2730 38.0, 32.3; 5600 39.1, 38.4; 6400 39.0, 40.1, heads of 32 37.0, 34.8.  128 bits: 5600 rows
+//            44.4, 42.7; 8000 45.4, 49.9.  256 bits: 197 rows 39.5, 36.0; 3500 48.7, 45.4; 4096 47.1, 48.4
 //   E = 192   64 bits: 197 rows 34.6, 31.8; 1792 41.4, 37.6; 1856 41.6, 43.3.  256 bits: 197 rows 43.5, 42.8; 1792 55.5, 49.7; 1856 55.0, 55.5
 //   E = 256   64 bits: 49 rows 32.2, 28.9; 1344 43.3, 38.0; 1576 43.4 (linear_hash.hip), 45.5.  256 bits: 1344 rows 57.2, 50.5; 1700 57.9, 55.7
-static bool by_chunks(long T, int E, int nbits) {
-    const int most = E == 128 && nbits <= 128 ? 512 : E > 64 && E != 192 && nbits == 256 ? 320 : 256;
+static bool by_chunks(long T, int E, int d, int nbits) {
+    int most = 256;
+    if (nbits == 64 && E == 64) most = 512;
+    if (E == 128) most = nbits == 256 ? 336 : d == 32 ? 640 : 544;
+    if (E == 256 && nbits == 256) most = 320;
     return (T + kRows - 1) / kRows * (3 * E / 64) <= most;
 }
 
@@ -503,7 +507,7 @@ bool sa::norm_hash_one_launch(long T, int E, int H, int nbits) {
     const int d = E / H;
     if (!((d == 32 && nbits == 64) || (d == 64 && (nbits == 64 || nbits == 128 || nbits == 256)))) return false;
     if (E > 256 || E % 64 != 0 || T * H >= (1L << 31)) return false;
-    if (by_chunks(T, E, nbits)) return true;
+    if (by_chunks(T, E, d, nbits)) return true;
     if (!norm_linear_one_launch(T, E)) return false;
     if (E == 64) return true;
     if (T <= 256 * kRows) return nbits == 64 || T >= (nbits == 128 ? 3072 : 12288);
@@ -514,7 +518,7 @@ int sa::launch_norm_hash(const NormRows &norm, int B, int N, int H, int E, const
                          float *q, float *k, uint64_t *q_codes, uint64_t *k_codes, float *v, hipStream_t st) {
     const HashOut h{proj, q, k, Tensors{q, k, q_codes, k_codes}, RowMap{FastDiv((uint32_t)H), FastDiv((uint32_t)N), N, H, nbits / 64}};
     const long T = (long)B * N;
-    const bool split = by_chunks(T, E, nbits);
+    const bool split = by_chunks(T, E, E / H, nbits);
     switch (E) {
         case 64: return launch_width<1>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, split, st);
         case 128: return launch_width<2>(norm, T, wqkv_planes, scale, h, E / H, nbits, v, split, st);

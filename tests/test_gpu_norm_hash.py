@@ -19,8 +19,9 @@ pytestmark = pytest.mark.gpu
     (1, 16384, 4, 256, 256, 0, 2.0**-12), (1, 16385, 4, 256, 256, 0, 2.0**-12),
     # a workgroup per chunk: one row, and the last rows that take it, with one more each
     (1, 1, 3, 192, 64, 0, 2.0**-12), (1, 3, 4, 256, 256, 1, 2.0**-12), (1, 1, 4, 128, 64, 0, 2.0**20), (9, 21, 3, 192, 256, 1, 2.0**-30),
-    (1, 5440, 1, 64, 128, 0, 2.0**-12), (1, 5441, 1, 64, 128, 0, 2.0**-12), (1, 5440, 4, 128, 64, 0, 2.0**-12), (1, 5441, 2, 128, 128, 0, 2.0**-12),
-    (1, 3392, 2, 128, 256, 0, 2.0**-12), (1, 3393, 2, 128, 256, 0, 2.0**-12), (8, 224, 3, 192, 64, 1, 2.0**-12), (1, 1793, 6, 192, 64, 0, 2.0**-12),
+    (1, 5440, 1, 64, 128, 0, 2.0**-12), (1, 5441, 1, 64, 128, 0, 2.0**-12), (1, 10880, 2, 64, 64, 0, 2.0**-12), (1, 10881, 1, 64, 64, 0, 2.0**-12),
+    (1, 6784, 4, 128, 64, 0, 2.0**-12), (1, 6785, 4, 128, 64, 0, 2.0**-12), (1, 5760, 2, 128, 128, 0, 2.0**-12), (1, 5761, 2, 128, 64, 0, 2.0**-12),
+    (1, 3584, 2, 128, 256, 0, 2.0**-12), (1, 3585, 2, 128, 256, 0, 2.0**-12), (8, 224, 3, 192, 64, 1, 2.0**-12), (1, 1793, 6, 192, 64, 0, 2.0**-12),
     (1, 1344, 8, 256, 64, 0, 2.0**-40), (1, 1345, 4, 256, 128, 0, 2.0**-12), (1, 1664, 4, 256, 256, 0, 2.0**-12),
     # the hash in the projection's tiles: rows too wide for a workgroup, and more narrower ones; both tiles, one row more than whole ones of
     # them, columns of V that fill no tile, either side of the fewest rows and of a round of the smaller tiles
