@@ -377,11 +377,14 @@ int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &
     // 64 columns, whose tiles are short and little but their loads, sixteen, each of which takes what there is: 6272 tiles were four each
     // for 1568 wavefronts, with eight on one SIMD of two CUs and four on the next (Q and K of 32 x 3136 tokens x 32 with the Add
     // products 24.7 -> 22.9 us; 200704 rows alone 9.5 -> 8.1, 302592 11.9 -> 10.7, 2097152 61.4 -> 50.7; with twelve 11.2 and 52.5, with 24 12.1 and 52.3).
-    // Longer tiles lose by it (d = 64: 302592 rows 18.0, 20.6; 128 bits 23.4, 28.1).
+    // Longer tiles lose by it (d = 64: 302592 rows 18.0, 20.6; 128 bits 23.4, 28.1), and so does a launch that also routes, by its tail: its
+    // last workgroups look at all tokens and wait for a place beside the sixteen (blocks with two experts, us with sixteen and eight:
+    // 35 x 567 tokens x 2 heads 42.4, 41.6; x 4 heads 68.6, 66.2; 1 x 19845 x 2 46.0, 45.0; with places left free for them 42.5, 67.2, 46.4).
     constexpr bool SHORT = D == 32 && C == 64;
-    constexpr int PER_CU = SHORT ? 16 / kWaves : C == 64 ? 8 / kWaves : 1;
-    const long waves = 256 * PER_CU / (nbits / C) * kWaves;
-    const long tiles_per_wave = SHORT ? 1 : (n_total + waves - 1) / waves;
+    const bool sixteen = SHORT && side.route.T == 0;
+    const int per_cu = C != 64 ? 1 : (sixteen ? 16 : 8) / kWaves;
+    const long waves = 256 * per_cu / (nbits / C) * kWaves;
+    const long tiles_per_wave = sixteen ? 1 : (n_total + waves - 1) / waves;
     const long enough = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
     const long blocks = enough < waves / kWaves ? enough : waves / kWaves;
     // what rides along comes behind the tiles: it fills the CUs that are done first
