@@ -42,7 +42,7 @@ __device__ inline v4i mma16(const uint4 &a, const uint4 &b, v4i c) {
 constexpr int kMlpWaves = 8, kHidChunk = 128;
 
 // NE: E / 64.  MI: 16-row tiles of a wavefront; the eight wavefronts stand 2 x 4 over rows x columns.  PROJECT: the rows are made here.
-template <int NE, int MI, bool PROJECT, class Store>
+template <int NE, int MI, bool PROJECT, bool WALK, class Store>
 struct MlpShape {
     static constexpr int E = 64 * NE, BM = 32 * MI;
     static constexpr int PS = NE <= 2 ? 2 : 1;               // planes of a stage
@@ -54,7 +54,7 @@ struct MlpShape {
     static constexpr int TABLE = 0, STAGES = 1024, H = STAGES + RING * STAGE, H_BYTES = BM * kHidChunk;
     static constexpr int WO_END = PROJECT ? STAGES + 2 * E * E : 0;      // Wo's planes, in the place of the stages and the hidden rows
     static constexpr int SIDE = H + 2 * H_BYTES > WO_END ? H + 2 * H_BYTES : WO_END;
-    static constexpr int LDS_BYTES = SIDE + (MI == 4 ? 2 : 1) * OutSide<Store, BM>::BYTES;
+    static constexpr int LDS_BYTES = SIDE + (WALK ? 2 : 1) * OutSide<Store, BM>::BYTES;
     static_assert(BM * E <= 2 * H_BYTES, "codes of normalised rows in the place of the hidden rows");
     static_assert(BM * E * 4 <= RING * STAGE + 2 * H_BYTES, "projected rows in the place of the ring and the hidden rows");
     static_assert(kMlpWaves * 16 * PITCH <= RING * STAGE, "output staging reuses the ring");
@@ -76,19 +76,19 @@ struct MlpStage {
     bool live = true;
 };
 
-template <int NE, int MI, int ROWS, class Store>
-__global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
-                                                                   const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
-                                                                   const int8_t *__restrict__ lut, float rq, Store store) {
+// WALK: a workgroup takes tile after tile (codes of 128 rows, more tiles than CUs).  A kernel of its own: what a workgroup keeps for the next
+// tile costs one that has none (one tile a workgroup, prepared weights, one way out of this code and the other: 128 x 512, 16400
+// rows 13.7 and 12.4 us, 128 x 768 17.9 and 15.9, 192 x 768 21.8 and 19.6, 256 x 1024, 32768 rows 35.5 and 33.2).
+template <int NE, int MI, int ROWS, bool WALK, class Store>
+__device__ __forceinline__ void shift_mlp_tiles(const int8_t *__restrict__ x, const NormRows &norm, const RowSel &sel, int hid,
+                                                const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
+                                                const int8_t *__restrict__ lut, float rq, const Store &store, uint8_t *lds) {
     constexpr bool NORM = ROWS != kCodes, PROJECT = ROWS == kProject;
-    using S = MlpShape<NE, MI, PROJECT, Store>;
+    using S = MlpShape<NE, MI, PROJECT, WALK, Store>;
     constexpr int E = S::E, PS = S::PS, SPG = S::SPG, LOADS = S::LOADS;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[S::LDS_BYTES];
     const int32_t *rows;
     long n_rows;
     resolve_rows(sel, rows, n_rows);
-    // Codes of 128 rows: a workgroup takes tile after tile.
-    constexpr bool WALK = ROWS == kCodes && MI == 4;
     long m0 = (long)blockIdx.x * S::BM;
     if (m0 >= n_rows) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
         const int p = j / NE, i = j % NE;
         uint32_t from = LAYER == 2 ? lane2 : lane1[NE == 3 ? i : 0];
         int w = wave;
-        if constexpr (WALK) {                                // made here: no registers for every load's part of it
+        if constexpr (WALK && NE > 2) {                      // made here: no registers for every load's part of it (at E = 128 there are)
             asm volatile("" : "+v"(from), "+s"(w));
             w = __builtin_amdgcn_readfirstlane(w);
         }
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
         for (int t = 0; t < NE; ++t) fb[par][t] = operand(stage, 64 * k, p * S::PLANE + 16 * t * kHidChunk);
     };
     auto hidden_at = [&](uint32_t at, int buf) {
-        if constexpr (WALK) asm volatile("" : "+v"(at));     // made here: no registers from tile to tile for either buffer's
+        if constexpr (WALK && NE > 2) asm volatile("" : "+v"(at));     // made here: no registers from tile to tile for either buffer's
         return at + buf * S::H_BYTES;
     };
     auto read_hidden = [&](int i, int k, int buf) { fa[i] = operand(hidden_at(at_h, buf), 64 * k, 16 * i * kHidChunk); };
@@ -511,6 +511,22 @@ __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t 
     }
 }
 
+template <int NE, int MI, int ROWS, class Store>
+__global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
+                                                                   const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
+                                                                   const int8_t *__restrict__ lut, float rq, Store store) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[MlpShape<NE, MI, ROWS == kProject, false, Store>::LDS_BYTES];
+    shift_mlp_tiles<NE, MI, ROWS, false>(x, norm, sel, hid, w1, w2, lut, rq, store, lds);
+}
+
+template <int NE, class Store>
+__global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_walk_kernel(const int8_t *__restrict__ x, RowSel sel, int hid,
+                                                                        const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
+                                                                        const int8_t *__restrict__ lut, float rq, Store store) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[MlpShape<NE, 4, false, true, Store>::LDS_BYTES];
+    shift_mlp_tiles<NE, 4, kCodes, true>(x, NormRows{}, sel, hid, w1, w2, lut, rq, store, lds);
+}
+
 struct MlpArgs {
     const int8_t *x;
     const NormRows *norm;                                    // or null
@@ -521,18 +537,21 @@ struct MlpArgs {
     ShiftStore<kEpiScatterI32> store;
 };
 
+// walk: 256 workgroups take the tiles one after the other
 template <int NE, int MI>
-int launch(const MlpArgs &a, hipStream_t st) {
+int launch(const MlpArgs &a, bool walk, hipStream_t st) {
     typedef ShiftStore<kEpiScatterI32> Store;
     const long blocks = (a.sel.max_rows + 32 * MI - 1) / (32 * MI);
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_shift_mlp: too many rows for one launch");
-    const dim3 grid((unsigned)blocks), block(kMlpWaves * 64), walk((unsigned)(MI == 4 && blocks > 256 ? 256 : blocks));
+    const dim3 grid((unsigned)blocks), block(kMlpWaves * 64);
     if (a.norm && a.norm->wo)
         shift_mlp_kernel<NE, MI, kProject, Store><<<grid, block, 0, st>>>(a.x, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     else if (a.norm)
         shift_mlp_kernel<NE, MI, kNorm, Store><<<grid, block, 0, st>>>(nullptr, *a.norm, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
-    else
-        shift_mlp_kernel<NE, MI, kCodes, Store><<<walk, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+    else if (!walk)
+        shift_mlp_kernel<NE, MI, kCodes, Store><<<grid, block, 0, st>>>(a.x, NormRows{}, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
+    else if constexpr (MI == 4)
+        shift_mlp_walk_kernel<NE, Store><<<dim3(256), block, 0, st>>>(a.x, a.sel, a.hid, a.w1, a.w2, a.lut, a.rq, a.store);
     return check_launch("sa_shift_mlp (both layers)");
 }
 
@@ -596,19 +615,21 @@ bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
 
 // Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the
 // larger ones takes (256 x 1024: 16384 rows 26 against 36 us, 25088 rows 47 against 37, 131072 rows 181 against 145).  At
-// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).  Of rows that only the device counts half are expected.
+// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).  Of rows that only the device counts half are expected.  Those
+// walk where their bound is more than a tile a CU: with fewer after all it costs 0.1 us (128 x 256, 30 % of 66000 rows 9.85, 10.0;
+// 128 x 768 17.4, 17.3), with more it saves (all of 40000 rows of 128 x 256 18.3, 16.0).
 int sa::launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                          const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
     SA_REQUIRE(!norm || (!sel.rows && !out.gate), SA_ERR_INVALID, "sa_shift_mlp: rows to normalise are all rows, ungated");
     const MlpArgs a{x, norm, sel, hid, w1_planes, w2_planes, lut, requant_scale_finite(requant_scale), ShiftStore<kEpiScatterI32>(out)};
     const long m_est = sel.counts ? (sel.max_rows + 1) / 2 : sel.max_rows;
     auto rounds = [&](long rows) { return ((m_est + rows - 1) / rows + 255) / 256; };
-    const bool tall = 29 * rounds(128) < 20 * rounds(64);
+    const bool tall = 29 * rounds(128) < 20 * rounds(64), walk = sel.max_rows > 256 * 128;
     switch (E) {
-        case 64: return launch<1, 2>(a, st);
-        case 128: return tall ? launch<2, 4>(a, st) : launch<2, 2>(a, st);
-        case 192: return tall ? launch<3, 4>(a, st) : launch<3, 2>(a, st);
-        case 256: return tall ? launch<4, 4>(a, st) : launch<4, 2>(a, st);
+        case 64: return launch<1, 2>(a, false, st);
+        case 128: return tall ? launch<2, 4>(a, walk, st) : launch<2, 2>(a, false, st);
+        case 192: return tall ? launch<3, 4>(a, walk, st) : launch<3, 2>(a, false, st);
+        case 256: return tall ? launch<4, 4>(a, walk, st) : launch<4, 2>(a, false, st);
     }
     return fail(SA_ERR_UNSUPPORTED, "sa_shift_mlp: width %d in one launch", E);
 }

@@ -111,6 +111,12 @@ def test_two_launches_they_are(sa, T, E, hid):
     assert not bool(ws[:T * hid].any())                      # the hidden rows, all of them 0
 
 
+# A tile of 128 rows for every CU, and one row more: the last rows whose workgroups take one tile each, and the first whose take several.
+@pytest.mark.parametrize("rows,E,hid", [(32768 - 37, 128, 256), (32769 - 37, 128, 384), (32768 - 37, 192, 384), (32768 - 37, 256, 1024)])
+def test_a_tile_for_every_cu(sa, rows, E, hid):
+    test_one_launch_equals_the_two_layers(sa, rows, E, hid)
+
+
 # More than 256 tiles of 128 rows: a workgroup takes several, whole ones and the last one in part; two and three chunks of hidden columns,
 # so that a ring of three stages comes round differently from tile to tile.
 @pytest.mark.parametrize("rows,E,hid", [(65401, 256, 256), (65536, 256, 384), (90003, 192, 384), (65409, 128, 256), (98177, 128, 384)])

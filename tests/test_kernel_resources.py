@@ -58,6 +58,7 @@ def kernels():
     (r"gemm_kernel.*HashStore", 8),
     (r"linear_norm_kernel", 3),
     (r"shift_mlp_kernel", 21),
+    (r"shift_mlp_walk_kernel", 3),
 ])
 def test_no_scratch(kernels, pattern, instances):
     some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
