@@ -97,3 +97,9 @@ def test_a_few_partials(sa, H, N, W, dv):
                                         (1, 513, 3900, 32), (2, 600, 2040, 64), (2, 100, 1000, 128), (8, 32777, 1500, 64)])
 def test_partials_summed_by_quads(sa, H, Nq, Nk, dv):
     test_both_code_modes_against_fp64(sa, 1, H, Nq, Nk, 1, dv)
+
+
+# 64 bits in two partials: few workgroups, and more than two for a CU, which sum by quads
+@pytest.mark.parametrize("B,H,N,dv", [(1, 12, 400, 64), (43, 3, 300, 64), (50, 4, 400, 64), (1, 127, 512, 128)])
+def test_two_partials(sa, B, H, N, dv):
+    test_both_code_modes_against_fp64(sa, B, H, N, N, 1, dv)
