@@ -835,7 +835,14 @@ long pipeline_slots(int threads) {
 template <int DV, int W>
 void launch_hamming(const Launch &L) {
     if constexpr (DV <= 64 && W <= 4) {
-        if (L.pipeline) {
+        // Up to one product's 32 keys there is nothing to pipeline, and the products' chain is all that a unit waits for: many of them go to the
+        // workgroups of one unit, of which more fit a CU (us, pipelined and not: 12000 heads x 16 tokens x 64 bits x 64 73.3, 45.6, x 32 tokens
+        // 101.8, 68.2, x 128 bits 105.2, 73.5; 1024 x 16 x 64 8.1, 5.0; 4096 x 16 x 64 bits x 32 12.7, 10.3, x 32 tokens x 128 bits 17.9, 17.9).
+        // Not fewer than ROUNDS of what the pipelined kernel holds (2048 x 32 x 128 bits x 32 10.3, 11.5; 512 x 17 x 128 bits x 64 6.4, 6.8), nor
+        // 256 bits, whose popcounts take long (1024 x 17 x 64 12.5, 12.7; 4096 x 49 x 32 29, 34).
+        constexpr int ROUNDS = W * (DV == 64 ? 1 : 2);
+        const bool pipeline = L.pipeline && !(W <= 2 && L.Nk <= 32 && L.n_units >= ROUNDS * pipeline_slots<DV, W>((int)L.block.x));
+        if (pipeline) {
             const long slots = pipeline_slots<DV, W>((int)L.block.x);
             const long wgs = L.n_units < slots ? L.n_units : slots;
             hamming_pipe_kernel<DV, W><<<dim3((unsigned)wgs), L.block, 0, L.st>>>(L.q, L.k, L.v, L.out, L.H, L.Nq, L.Nk, L.q_chunks,

@@ -42,3 +42,10 @@ def test_units_of_four_tiles(sa, B, H, Nq, Nk, nbits, dv):
     ref = sa.sa_hamming_attention_fused(q, k, v, 0.125, nbits, 20.0, variant=0)
     for a, b in zip(got, ref):
         assert torch.equal(a, b)
+
+
+# Many units of few keys: up to one product's keys they are not pipelined.  Either side of the keys and of the units from which that holds.
+@pytest.mark.parametrize("B,H,Nq,Nk,nbits,dv", [(73, 7, 16, 16, 64, 64), (128, 4, 16, 16, 64, 64), (128, 8, 33, 32, 128, 64), (128, 8, 70, 33, 64, 64),
+                                                (512, 8, 31, 17, 128, 32), (1365, 3, 32, 1, 64, 32), (64, 16, 300, 9, 64, 64)])
+def test_many_units_of_few_keys(sa, B, H, Nq, Nk, nbits, dv):
+    test_units_of_four_tiles(sa, B, H, Nq, Nk, nbits, dv)
