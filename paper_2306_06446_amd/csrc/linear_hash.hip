@@ -232,13 +232,39 @@ int launch(const GemmArgs &g, const Epilogue &e, const float *proj, const Tensor
 //   E = 256  128 bits: 6304 rows 71.2, 73.1; 12608 86.1, 82.6; 131072 528.0, 485.5.  256 bits: 12608 99.8, 99.0; 131072 607.9, 579.8
 //   E = 192   64 bits: 3152 rows 53.2, 53.8; 12608 68.7, 64.7; 131072 387.1, 353.1.  256 bits: 50176 217.9, 218.4
 //   E =  64   64 bits: 12608 rows 37.8, 38.0; 131072 118.1, 111.1.  256 bits: 131072 153.2, 164.6
+//
+// A tile with the hash behind its sums takes long, and the more bits the longer, so a last round of few tiles costs more than its launch
+// saves.  From 4000 layers with linear attention, both ways on the same buffers, separate launches / one:
+//   128 bits or heads of 32: 1024 x 322 rows 55.1 / 58.6 (64 bits 1024 x 420 67.0 / 68.6), 1024 x 669 69 / 67.5; 640 x 505 56.8 / 59.3
+//   256 bits, prepared: rows in tiles of 128 that are one for half of the CUs, 384 x 1330 63.8 / 66.6, 512 x 1784 71 / 72.5, two for most, 512 x
+//     5122 122 / 117, 1024 x 2739 159 / 150, or three, 640 x 4826 140 / 144, 896 x 4200 1.023, 448 x 8474 1.030; at 192 columns a second tile
+//     for few CUs, 6501 1.013, 7289 1.015 (256 x 5586 88.0 / 84.7)
+//   256 bits, packed: up to 1.7 rounds of the taller tiles 384 x 20169 206 / 213, 768 x 10565 287 / 296, 1024 x 5805 216 / 227; 256 columns up
+//     to 85000 rows 35351 208 / 213, 66248 381 / 394, but 90138 455 / 430
+//   widths of 320, 640 and 1280 gain least, and lose where a second round begins: 320 x 12069, 256 bits, packed 134 / 141, 16665 165 / 181, prepared
+//     18060 1.035; 128 bits packed 320 x 17838 148 / 152, 640 x 8251 180 / 183; 64 bits 320 x 17038 132 / 135; elsewhere 640 x 17875, 128 bits, 0.92
+//   packed 64 columns: 128 bits 72420 rows 125 / 131, 116472 144 / 146; two heads 70228 82 / 84; 64 bits 67792 1.025, 81952 1.010, 99356 0.969
 bool sa::linear_hash_one_launch(long T, int E, int H, int nbits, bool packed) {
     const int d = E / H;
     if (!((d == 32 && nbits == 64) || (d == 64 && (nbits == 64 || nbits == 128 || nbits == 256))) || E % 64 != 0 || T * H >= (1L << 31)) return false;
-    if (packed) return T * E >= 3L << 20 && (nbits < 256 || E >= 256);
-    if (E <= 256 && T > 20480 && (T * E < 10L << 20 || (nbits == 256 && E < 256))) return false;
-    if (nbits == 256) return E > 256 ? T >= 1300 : T * E >= 650L << 10;
-    return T >= (nbits == 64 ? 300 : 700);
+    const long cols = (3L * E + 127) / 128, tiles = (T + 127) / 128 * cols, tall = (T + 255) / 256 * cols;     // (see launch_linear_hash)
+    const bool least = E % 320 == 0;
+    if (packed) {
+        if (nbits == 256) return E >= 384 ? tall >= 870 && E <= 1024 : E == 256 && T * E >= 22L << 20;
+        if (T * E < 3L << 20) return false;
+        if (E == 64) return d == 64 && nbits == 64 && (tall <= 512 || tall >= 700);
+        return !least || tall <= 480 || tall >= (nbits == 64 ? 700 : 780);
+    }
+    if (E <= 256) {
+        if (T > 20480 && (T * E < 10L << 20 || (nbits == 256 && E < 256))) return false;
+        if (nbits == 256) return T * E >= 650L << 10 && (E == 256 || tiles < 255 || tiles >= 330);
+    } else if (nbits == 256) {
+        if (T < 1900 || E > 1024) return false;
+        if (tiles <= 768) return tiles <= (least ? 490 : 660);
+        return !least || tall <= 512 || (E > 320 && tall >= 780);
+    }
+    if (nbits == 64 && d == 64 && E <= 640) return T >= 300;
+    return T >= 640 && (E <= 512 || tiles >= 110);
 }
 
 int sa::launch_linear_hash(const int8_t *codes, int B, int N, int H, int E, const int8_t *wqkv_planes, float scale, const float *proj, int nbits,

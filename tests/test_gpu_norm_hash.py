@@ -34,6 +34,12 @@ pytestmark = pytest.mark.gpu
     # packed weights: the last rows that keep launches of their own, and one more
     (3, 1365, 12, 768, 64, 0, 2.0**-12), (1, 4096, 12, 768, 64, 0, 2.0**-12), (8, 1024, 6, 384, 128, 1, 2.0**20), (1, 8193, 6, 384, 256, 0, 2.0**-12),
     (1, 49152, 2, 64, 64, 0, 2.0**-12), (3, 4097, 4, 256, 256, 0, 2.0**-40),
+    # either side of where a tile's hash costs more than its launch saves: few rows, a last round of few tiles, prepared and packed weights
+    (1, 639, 12, 384, 64, 0, 2.0**-12), (1, 640, 12, 384, 64, 0, 2.0**-12), (4, 192, 12, 768, 64, 0, 2.0**-12), (1, 769, 12, 768, 128, 0, 2.0**-12),
+    (1, 1899, 6, 384, 256, 0, 2.0**-12), (1, 1900, 6, 384, 256, 0, 2.0**-140), (2, 4672, 6, 384, 256, 0, 2.0**-12), (1, 9345, 6, 384, 256, 0, 2.0**-12),
+    (1, 5376, 4, 256, 256, 0, 2.0**-12), (1, 5377, 4, 256, 256, 0, 2.0**-12), (1, 7808, 5, 320, 256, 0, 2.0**-12), (1, 7809, 5, 320, 256, 0, 2.0**-12),
+    (1, 16384, 5, 320, 256, 0, 2.0**-12), (1, 15361, 5, 320, 128, 0, 2.0**-12), (2, 7680, 5, 320, 128, 0, 2.0**-12), (1, 24833, 6, 384, 256, 0, 2.0**-12),
+    (1, 65536, 1, 64, 64, 0, 2.0**-12), (1, 65537, 1, 64, 64, 0, 2.0**-12), (1, 90112, 4, 256, 256, 0, 2.0**-12),
 ])
 def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attention, qkv_scale):
     g = torch.Generator(device="cuda")
