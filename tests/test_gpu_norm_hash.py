@@ -59,6 +59,12 @@ def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attent
     proj[:, 11] *= 1e-30
     proj[1:, 17] = 0.0
     lut = torch.arange(-128, 128, device="cuda").clamp(min=0).to(torch.int8)
+    # the code words as the entry points make them one by one, the hash by its defining chain
+    z = sa.sa_layernorm_quant(x, gamma1, beta1, 1e-6, 32.0, want_ln=False, want_q=True)[1]
+    rows4 = [t.view(B, N, H, E // H) for t in sa.sa_shift_linear_f32(z, w[0], qkv_scale, parts=3, variant=0)[:2]]
+    codes = [sa.sa_binarize(t, proj, nbits, variant=0) for t in rows4]
+    nbytes, up = codes[0].numel() * 8, lambda n: (n + 255) // 256 * 256
+    at = up(T * E) + 3 * up(4 * T * E)                       # in a layer's workspace they lie behind its int8 rows and Q, K and V
     y = []
     for variant in (0, 2, 3):
         if variant == 3:
@@ -68,6 +74,8 @@ def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attent
                                  o_scale=2.0**-12, requant_scale=2.0**-11, out_scale=2.0**-12, x=x, gamma1=gamma1, beta1=beta1,
                                  gamma2=gamma2, beta2=beta2, wqkv=w[0], wo=w[1], proj=proj, w1=w[2], w2=w[3], lut=lut)
         y.append(layer.forward().clone())
+        for i, ref in enumerate(codes):
+            assert torch.equal(layer.ws[at + i * up(nbytes):][:nbytes].view(torch.int64), ref.flatten()), (variant, "QK"[i])
     rows = torch.isfinite(x).all(dim=1)
     assert float((y[0] - x)[rows].abs().max()) > 0.0
     for other in y[1:]:
