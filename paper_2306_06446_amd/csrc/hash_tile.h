@@ -1,5 +1,5 @@
-// What the two kernels that hash rows on the matrix cores share (binarize_mfma.hip, norm_hash.hip): where code words lie, the fp16
-// terms of an operand, and the defining chain for what the products leave open.
+// What the three kernels that hash rows on the matrix cores share (binarize_mfma.hip, norm_hash.hip, linear_hash.hip): where code words lie,
+// the fp16 terms of an operand, and the defining chain for what the products leave open.
 #pragma once
 
 #include "common.h"
@@ -36,6 +36,26 @@ __device__ inline void split_f16_pair(float a, float b, uint32_t &upper, uint32_
     asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r[0]) : "v"(upper), "v"(a));
     asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r[1]) : "v"(upper), "v"(b));
     lower = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2h));
+}
+
+// Zeros.  Of a row of zeros, whose token may be padding, every sum of the chain is 0 and every bit set, unless a column has infinities or
+// NaN; of a column of zeros every bit of finite rows.  The products give 0 there, whose sign is right, and the kernels that hash in the
+// projection, whose chain takes its columns from memory, keep it.  Layers with a tenth of the rows of zeros, us, hash a launch of its own /
+// in the projection with the chain for them / so: 16384 x 256, 256 bits 390, 1148, 128; 12608 x 768, 128 bits 590, 832, 292; 197 x 192 51, 35, 29.
+// Whether |x|^2 = 0 says that a row is all zeros: its elements are integers times scale, whose squares then do not underflow.
+__device__ inline bool scale_is_exact(float scale) { return __builtin_fabsf(scale) >= 0x1p-60f; }
+// n2, a thread's share of a column's |r|^2, for the same: 0 only where its elements x are zeros.
+template <int N>
+__device__ inline float column_norm(float n2, const float (&x)[N][8]) {
+    if (n2 == 0.0f) {
+        uint32_t some = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) some |= __builtin_bit_cast(uint32_t, x[i][e]) << 1;
+        if (some != 0) n2 = 0x1p-126f;
+    }
+    return n2;
 }
 
 // A bit whose sign the products leave open: row of the flattened input, column, the bit as stored, which tensor.

@@ -29,8 +29,8 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
     static constexpr int GROUPS = NB / 32, STEPS = D / 16;   // of a product's columns, and of its sum
     static constexpr int TPC = 256 / NB, TASKS = D / 8 / TPC;              // threads of a hash column, eight rows of it for each task
     static_assert(D / 8 % TPC == 0 && (D == 64 || D == 32), "a hash column, once");
-    static constexpr int FRAGS = 0, NORMS = NB * D * 4, LISTS = NORMS + 256 * 4;
-    static constexpr int kHashBytes = LISTS + 4 * kList * 8;
+    static constexpr int FRAGS = 0, NORMS = NB * D * 4, LISTS = NORMS + 256 * 4, MASKS = LISTS + 4 * kList * 8;
+    static constexpr int kHashBytes = MASKS + 2 * NB / 8;
     const float *proj;                   // [D, NB]
     Tensors of;                          // Q and K (rows with open bits), and where their codes go
     RowMap map;
@@ -59,14 +59,20 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
         wait_loads_in_flight<0>();
         __syncthreads();                                     // the last stage has been read
         float *norms = reinterpret_cast<float *>(lds + NORMS);
-        norms[part * NB + hc] = n2;
+        norms[part * NB + hc] = column_norm(n2, hv);
         __syncthreads();
         uint4 *frags = reinterpret_cast<uint4 *>(lds + FRAGS);
+        uint64_t *zero_columns = reinterpret_cast<uint64_t *>(lds + MASKS), *unbounded_columns = zero_columns + NB / 64;     // bit: a column
         {
             n2 = 0.0f;
 #pragma unroll
             for (int p = 0; p < TPC; ++p) n2 += norms[p * NB + hc];
-            // a column of no use (see binarize_mfma.hip) is left to the chain altogether
+            const uint64_t zero = __ballot(n2 == 0.0f), unbounded = __ballot(!(n2 < __builtin_inff()));
+            if (part == 0 && lane == 0) {
+                zero_columns[hc / 64] = zero;
+                unbounded_columns[hc / 64] = unbounded;
+            }
+            // a column of no use (see binarize_mfma.hip) is left to the chain, unless it is all zeros
             const float inv = n2 >= kColumnMin2 && n2 < __builtin_inff() ? 1.0f / __builtin_sqrtf(n2) : 0.0f;
             const int f = hc / (NB / 2), c = hc % (NB / 2), rho = 8 * (c % 16 / 4) + 4 * f + c % 4;
 #pragma unroll
@@ -87,6 +93,10 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
         }
         __syncthreads();
 
+        uint32_t some_zeros = 0;
+#pragma unroll
+        for (int q = 0; q < NB / 32; ++q) some_zeros |= reinterpret_cast<const uint32_t *>(zero_columns)[q];
+        const bool any_zeros = __builtin_amdgcn_readfirstlane(some_zeros) != 0;
         uint64_t *list = reinterpret_cast<uint64_t *>(lds + LISTS) + wave * kList;
         int cnt = 0;                                         // entries of it (wave-uniform)
         auto work_off = [&](auto steps_c) {                  // steps of the chain whose operands are loaded at once
@@ -127,16 +137,21 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
                 }
             };
             float unit = 1.0f;
+            bool zero = false;                               // a row of zeros: hash_tile.h
             if (__ballot(!(nx2 >= kOrdinaryMin2 && nx2 <= kOrdinaryMax2)) != 0) {        // wave-uniform
                 int e = 0;
                 if (nx2 > 0.0f && nx2 < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2) / 2;
                 unit = __builtin_amdgcn_ldexpf(1.0f, -e);
                 split(unit);
+                zero = nx2 == 0.0f && scale_is_exact(scale);
+#pragma unroll
+                for (int q = 0; q < NB / 64; ++q) zero = zero && unbounded_columns[q] == 0;
             } else {
                 split(1.0f);
             }
-            const float keep = nx2 < __builtin_inff() ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2), kKeepFloor) * unit * kColumnScale
-                                                      : __builtin_inff();
+            float keep = nx2 < __builtin_inff() ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2), kKeepFloor) * unit * kColumnScale
+                                                : __builtin_inff();
+            if (zero) keep = -1.0f;
             const uint32_t t = (uint32_t)min(row, n_rows - 1), b = map.by_n(t), n = t - b * (uint32_t)map.N;
             uint8_t *word = reinterpret_cast<uint8_t *>(codes + (((size_t)b * map.H + head) * map.N + n) * (NB / 64)) + NB / 16 * fg;
             // fragments of step STEPS g + s, one step ahead of their products
@@ -148,6 +163,7 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
             read(0, part_of[0]);
 #pragma unroll 1
             for (int g = 0; g < GROUPS; ++g) {
+                const int bit0 = NB / 2 * fg + 16 * g;
                 v16f_t z;
 #pragma unroll
                 for (int q = 0; q < 16; ++q) z[q] = 0.0f;
@@ -175,6 +191,7 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
 #pragma unroll
                 for (int q = 0; q < 16; ++q) open |= (uint32_t)(!(__builtin_fabsf(z[q]) > keep)) << q;
                 if (!valid) open = 0;
+                if (any_zeros && keep < __builtin_inff()) open &= ~(uint32_t)reinterpret_cast<const uint16_t *>(zero_columns)[bit0 / 16];
                 // rows with open bits go out for the chain: both lanes of such a row have half of it
                 const uint64_t any = __ballot(open != 0);
                 if ((any >> fr | any >> (fr + 32)) & 1u) {
@@ -192,7 +209,7 @@ struct HashStore : ShiftStore<kEpiQkvCodes> {
                     if (open) {
                         const int pos = __builtin_ctz(open);
                         const int at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(pm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pm, 0u));
-                        list[at] = open_bit((uint32_t)row * (uint32_t)map.H + head, NB / 2 * fg + 16 * g + pos, (bits >> pos) & 1u, second);
+                        list[at] = open_bit((uint32_t)row * (uint32_t)map.H + head, bit0 + pos, (bits >> pos) & 1u, second);
                         open &= open - 1u;
                     }
                     cnt += __builtin_popcountll(pm);

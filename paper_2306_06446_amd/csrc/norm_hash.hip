@@ -43,9 +43,9 @@ struct NormHashShape {
     static constexpr int TOTAL = UNIT / 1024, LOADS = (TOTAL + kWaves - 1) / kWaves;       // KiB of a unit, of a wavefront
     static constexpr int LIST = 96;                          // open bits of a wavefront
     static constexpr int TPC = kWaves * 64 / NB < 4 * S ? kWaves * 64 / NB : 4 * S, TASKS = 4 * S / TPC;      // threads of a hash column
-    // LDS: ring, two chunks of staged rows (before them the codes of the normalised ones), fragments of the hash matrix, lists, norms
+    // LDS: ring, two chunks of staged rows (before them the codes of the normalised ones), fragments of the hash matrix, lists, masks, norms
     static constexpr int STAGE = RING * UNIT, STAGE_BYTES = kRows * kChunk * 4, FRAGS = STAGE + 2 * STAGE_BYTES, LISTS = FRAGS + NB * D * 4;
-    static constexpr int NORMS = LISTS + kWaves * LIST * 8, COUNTS = NORMS + TPC * NB * 4, LDS_BYTES = COUNTS + kWaves * 4;
+    static constexpr int MASKS = LISTS + kWaves * LIST * 8, NORMS = MASKS + 2 * NB / 8, COUNTS = NORMS + TPC * NB * 4, LDS_BYTES = COUNTS + kWaves * 4;
     static constexpr int PER_CU = D == 32 && NE == 1 ? 2 : 1;      // workgroups (what the registers allow)
     static_assert(kRows * E <= STAGE_BYTES && PER_CU * LDS_BYTES <= 160 * 1024, "LDS of a CU");
 };
@@ -130,20 +130,26 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
     issue(2 * only + 1, 1);
     float *norms = reinterpret_cast<float *>(lds + S::NORMS);
     uint4 *frags = reinterpret_cast<uint4 *>(lds + S::FRAGS);
+    uint64_t *zero_columns = reinterpret_cast<uint64_t *>(lds + S::MASKS), *unbounded_columns = zero_columns + NB / 64;      // bit: a column
     if (mine) {
         float n2 = 0.0f;                                                 // this thread's share of the norm
 #pragma unroll
         for (int i = 0; i < S::TASKS; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e) n2 = __builtin_fmaf(hv[i][e], hv[i][e], n2);
-        norms[part * NB + hc] = n2;
+        norms[part * NB + hc] = column_norm(n2, hv);
     }
     __syncthreads();
     if (mine) {
         float n2 = 0.0f;
 #pragma unroll
         for (int p = 0; p < S::TPC; ++p) n2 += norms[p * NB + hc];
-        // a column of no use (see binarize_mfma.hip) is left to the chain altogether
+        const uint64_t zero = __ballot(n2 == 0.0f), unbounded = __ballot(!(n2 < __builtin_inff()));
+        if (part == 0 && lane == 0) {
+            zero_columns[hc / 64] = zero;
+            unbounded_columns[hc / 64] = unbounded;
+        }
+        // a column of no use (see binarize_mfma.hip) is left to the chain, unless it is all zeros
         const float inv = n2 >= kColumnMin2 && n2 < __builtin_inff() ? 1.0f / __builtin_sqrtf(n2) : 0.0f;
         const int c = hc % S::COLS, q = c / (S::COLS / 4), b = c % (S::COLS / 4), t = b / 4, rho = 4 * q + b % 4;
 #pragma unroll
@@ -203,6 +209,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
     const int group = S::GROUPS == 1 ? 0 : wave % S::GROUPS;
     const int head = S::HEADS == 2 ? wave & 1 : 0;
     const int unit0 = (wave / (S::GROUPS * S::HEADS)) * NU;              // first of its row units
+    uint32_t zeros = 0;                                                  // which of this lane's columns are all zeros (the barrier comes below)
 
     const int units = SPLIT ? 2 * only + 2 : UNITS;
     int slot = 0, ahead = 2 * only + 2;                      // the unit's place in the ring; the next unit to load
@@ -223,6 +230,10 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
             if (in) *reinterpret_cast<uint32_t *>(lds + S::STAGE + r * E + swizzle_row<NE>(r, l / 4) * 16 + l % 4 * 4) = codes_of(y, norm.inv_scale);
         }
         __syncthreads();
+        if (hashes) {
+            const int bit0 = S::COLS * group + 4 * NT * fg;
+            zeros = (uint32_t)(zero_columns[bit0 / 64] >> bit0 % 64);
+        }
         uint4 xf[2][NE];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -328,16 +339,21 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
                     };
                     // rows of ordinary magnitude split as they are, others are brought to |x| ~ 1 first (hash_margin.h)
                     float unit = 1.0f;
+                    bool zero = false;                       // a row of zeros: hash_tile.h
                     if (__ballot(!(nx2 >= kOrdinaryMin2 && nx2 <= kOrdinaryMax2)) != 0) {        // wave-uniform
                         int e = 0;
                         if (nx2 > 0.0f && nx2 < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2) / 2;
                         unit = __builtin_amdgcn_ldexpf(1.0f, -e);
                         split(unit);
+                        zero = nx2 == 0.0f && scale_is_exact(scale);
+#pragma unroll
+                        for (int q = 0; q < NB / 64; ++q) zero = zero && unbounded_columns[q] == 0;
                     } else {
                         split(1.0f);
                     }
                     keep[u] = nx2 < __builtin_inff() ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2), kKeepFloor) * unit * kColumnScale
                                                      : __builtin_inff();
+                    if (zero) keep[u] = -1.0f;
                 }
                 // Two tiles' products by turns, their fragments read a pair ahead (the first pair's before the rows are split): left to
                 // itself the compiler read most of them a product ahead (layer of 16384 x 256, 256 bits 100.8 -> 99.6 us).
@@ -382,6 +398,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
 #pragma unroll
                     for (int q = 0; q < 4 * NT; ++q) open |= (uint32_t)(!(__builtin_fabsf(z[u][q / 4][q % 4]) > keep[u])) << q;
                     if (m >= n_rows) open = 0;
+                    if (keep[u] < __builtin_inff()) open &= ~zeros;
                     // rows with open bits go out for the chain: all four lanes of such a row have a quarter of it
                     const uint64_t any = __ballot(open != 0);
                     if (!SPLIT && ((any >> fr | any >> (fr + 16) | any >> (fr + 32) | any >> (fr + 48)) & 1u)) {

@@ -6,6 +6,21 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
+def codes_of_the_entry_points(sa, x, gamma1, beta1, wqkv, qkv_scale, proj, B, N, H, nbits):
+    """Q's and K's code words as the stages make them one by one, the hash by its defining chain."""
+    z = sa.sa_layernorm_quant(x, gamma1, beta1, 1e-6, 32.0, want_ln=False, want_q=True)[1]
+    q, k, _ = sa.sa_shift_linear_f32(z, wqkv, qkv_scale, parts=3, variant=0)
+    return [sa.sa_binarize(t.view(B, N, H, x.shape[1] // H), proj, nbits, variant=0) for t in (q, k)]
+
+
+def assert_code_words(layer, codes, T, E):
+    """In a layer's workspace they lie behind its int8 rows and Q, K and V."""
+    nbytes, up = codes[0].numel() * 8, lambda n: (n + 255) // 256 * 256
+    at = up(T * E) + 3 * up(4 * T * E)
+    for i, ref in enumerate(codes):
+        assert torch.equal(layer.ws[at + i * up(nbytes):][:nbytes].view(torch.int64), ref.flatten()), "QK"[i]
+
+
 # every width, head width and number of bits; rows that fill no workgroup, one, and more than a round of them; either side of where the
 # launch takes over.  qkv_scale brings rows in and out of the range that splits into fp16 terms as it is.
 @pytest.mark.parametrize("B,N,H,E,nbits,attention,qkv_scale", [
@@ -59,12 +74,7 @@ def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attent
     proj[:, 11] *= 1e-30
     proj[1:, 17] = 0.0
     lut = torch.arange(-128, 128, device="cuda").clamp(min=0).to(torch.int8)
-    # the code words as the entry points make them one by one, the hash by its defining chain
-    z = sa.sa_layernorm_quant(x, gamma1, beta1, 1e-6, 32.0, want_ln=False, want_q=True)[1]
-    rows4 = [t.view(B, N, H, E // H) for t in sa.sa_shift_linear_f32(z, w[0], qkv_scale, parts=3, variant=0)[:2]]
-    codes = [sa.sa_binarize(t, proj, nbits, variant=0) for t in rows4]
-    nbytes, up = codes[0].numel() * 8, lambda n: (n + 255) // 256 * 256
-    at = up(T * E) + 3 * up(4 * T * E)                       # in a layer's workspace they lie behind its int8 rows and Q, K and V
+    codes = codes_of_the_entry_points(sa, x, gamma1, beta1, w[0], qkv_scale, proj, B, N, H, nbits)
     y = []
     for variant in (0, 2, 3):
         if variant == 3:
@@ -74,9 +84,37 @@ def test_codes_of_a_layer_hashed_in_the_projection(sa, B, N, H, E, nbits, attent
                                  o_scale=2.0**-12, requant_scale=2.0**-11, out_scale=2.0**-12, x=x, gamma1=gamma1, beta1=beta1,
                                  gamma2=gamma2, beta2=beta2, wqkv=w[0], wo=w[1], proj=proj, w1=w[2], w2=w[3], lut=lut)
         y.append(layer.forward().clone())
-        for i, ref in enumerate(codes):
-            assert torch.equal(layer.ws[at + i * up(nbytes):][:nbytes].view(torch.int64), ref.flatten()), (variant, "QK"[i])
+        assert_code_words(layer, codes, T, E)
     rows = torch.isfinite(x).all(dim=1)
     assert float((y[0] - x)[rows].abs().max()) > 0.0
     for other in y[1:]:
         assert torch.equal(y[0].nan_to_num(nan=3.0), other.nan_to_num(nan=3.0))
+
+
+# Rows of zeros and columns of zeros, whose bits need no chain, beside a column that is not finite, overflows when squared or is denormal: there
+# they do.  Every kernel that hashes in the projection: a workgroup per chunk, all chunks, and the projection's tiles of either height.
+@pytest.mark.parametrize("odd", [0.0, float("nan"), float("inf"), 1e30, 1e-40])
+@pytest.mark.parametrize("B,N,H,E,nbits", [(1, 130, 3, 192, 64), (2, 300, 4, 256, 256), (3, 4567, 2, 64, 64), (1, 4200, 2, 128, 128),
+                                           (1, 16384, 4, 256, 256), (1, 900, 6, 384, 128), (1, 700, 12, 384, 64), (2, 2001, 6, 384, 256),
+                                           (2, 6001, 6, 384, 256)])
+def test_rows_and_columns_of_zeros(sa, B, N, H, E, nbits, odd):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + E + nbits)
+    T, hid = B * N, 256
+    x = torch.randn((T, E), generator=g, device="cuda")
+    x[torch.rand(T, generator=g, device="cuda") < 0.4] = 0.0
+    x[T // 2:T // 2 + 20] = 0.0
+    x[T // 3, 0], x[T // 5, 1] = float("nan"), float("inf")
+    gamma, beta = torch.randn(E, generator=g, device="cuda"), torch.zeros(E, device="cuda")
+    w = [torch.randint(0, 256, s, generator=g, device="cuda", dtype=torch.uint8) for s in ((3 * E, E // 2), (E, E // 2), (hid, E // 2), (E, hid // 2))]
+    proj = torch.randn((E // H, nbits), generator=g, device="cuda")
+    proj[:, 7], proj[:, 40] = 0.0, -0.0
+    proj[3, 21] = odd
+    codes = codes_of_the_entry_points(sa, x, gamma, beta, w[0], 2.0**-12, proj, B, N, H, nbits)
+    w = [sa.sa_shift_planes_prepare(t) for t in w]
+    layer = sa.binding.Layer(B=B, N=N, H=H, nbits=nbits, E=E, hid=hid, attention=0, moe=0, shift_variant=3, eps=1e-6, ln_inv_scale=32.0,
+                             qkv_scale=2.0**-12, attn_scale=1.0, act_inv_scale=1.0, o_scale=2.0**-12, requant_scale=2.0**-11, out_scale=2.0**-12, x=x,
+                             gamma1=gamma, beta1=beta, gamma2=gamma, beta2=beta, wqkv=w[0], wo=w[1], proj=proj, w1=w[2], w2=w[3],
+                             lut=torch.zeros(256, dtype=torch.int8, device="cuda"))
+    layer.forward()
+    assert_code_words(layer, codes, T, E)
