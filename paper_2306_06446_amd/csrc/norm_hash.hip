@@ -31,14 +31,14 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8, kRows = 64, kChunk = 64;           // wavefronts 2 x 4 over rows x columns, rows, columns of a chunk
 
-// NE: E / 64.  D: head width.  NB: code bits.  Of a chunk's rows (x heads, D = 32) a wavefront hashes NU units of 16 to NT tiles of 16
+// NE: E / 64.  D: head width.  NB: code bits.  Of a chunk's rows (x heads, D = 32) a wavefront hashes 16 to NT tiles of 16
 // columns.
 template <int NE, int D, int NB>
 struct NormHashShape {
     static constexpr int E = 64 * NE, S = D / 32;
-    static constexpr int NU = 1, NT = D == 32 ? 4 : NB / 32, COLS = 16 * NT, GROUPS = NB / COLS;
+    static constexpr int NT = D == 32 ? 4 : NB / 32, COLS = 16 * NT, GROUPS = NB / COLS;
     static constexpr int HEADS = kChunk / D;                 // of a chunk
-    static_assert(HEADS * kRows / 16 * GROUPS == kWaves * NU && (D == 64 || NB == 64), "a chunk's rows and columns, once");
+    static_assert(HEADS * kRows / 16 * GROUPS == kWaves && (D == 64 || NB == 64), "a chunk's rows and columns, once");
     static constexpr int UNIT = kChunk * E, RING = 3;        // 64 rows of a plane of Wqkv
     static constexpr int TOTAL = UNIT / 1024, LOADS = (TOTAL + kWaves - 1) / kWaves;       // KiB of a unit, of a wavefront
     static constexpr int LIST = 96;                          // open bits of a wavefront
@@ -72,7 +72,7 @@ template <int NE, int D, int NB, bool SPLIT>
 __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_hash_kernel(NormRows norm, long n_rows, const int8_t *__restrict__ w,
                                                                                  float scale, HashOut h, float *__restrict__ v) {
     using S = NormHashShape<NE, D, NB>;
-    constexpr int E = S::E, NU = S::NU, NT = S::NT, KS = S::S;
+    constexpr int E = S::E, NT = S::NT, KS = S::S;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[S::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
     // what this wavefront hashes of a chunk
     const int group = S::GROUPS == 1 ? 0 : wave % S::GROUPS;
     const int head = S::HEADS == 2 ? wave & 1 : 0;
-    const int unit0 = (wave / (S::GROUPS * S::HEADS)) * NU;              // first of its row units
+    const int row16 = wave / (S::GROUPS * S::HEADS) * 16;                // first of its rows
     uint32_t zeros = 0;                                                  // which of this lane's columns are all zeros (the barrier comes below)
 
     const int units = SPLIT ? 2 * only + 2 : UNITS;
@@ -244,11 +244,10 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
             }
 
         // where the code words of this wavefront's rows lie: word_at + head * N words
-        size_t word_at[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const uint32_t t = (uint32_t)min(m0 + 16 * (unit0 + u) + fr, n_rows - 1), b = h.map.by_n(t), n = t - b * (uint32_t)h.map.N;
-            word_at[u] = (size_t)b * h.map.H * h.map.N + n;
+        size_t word_at;
+        {
+            const uint32_t t = (uint32_t)min(m0 + row16 + fr, n_rows - 1), b = h.map.by_n(t), n = t - b * (uint32_t)h.map.N;
+            word_at = (size_t)b * h.map.H * h.map.N + n;
         }
         // ---- chunk c of the projection.  Products are computed transposed (weights down, rows across): a lane holds four consecutive
         //      columns of rows 32 wr + lane % 16 and 16 further on.
@@ -285,17 +284,15 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
             int of_lane = lane;
             asm volatile("" : "+v"(of_lane));
             const int fr = of_lane & 15, fg = of_lane >> 4;
-            // row 16 (unit0 + u) + fr of the chunk's head, this lane's k = 32 s + 16 o + 4 fg ..
-            v4f x[NU][KS][2];
+            // row row16 + fr of the chunk's head, this lane's k = 32 s + 16 o + 4 fg ..
+            v4f x[KS][2];
             if constexpr (PRODUCTS) multiply(0);
             else __syncthreads();
             if constexpr (HASH) {
 #pragma unroll
-                for (int u = 0; u < NU; ++u)
+                for (int s = 0; s < KS; ++s)
 #pragma unroll
-                    for (int s = 0; s < KS; ++s)
-#pragma unroll
-                        for (int o = 0; o < 2; ++o) x[u][s][o] = *staged(c - 1, 16 * (unit0 + u) + fr, head * (D / 4) + 8 * s + 4 * o + fg);
+                    for (int o = 0; o < 2; ++o) x[s][o] = *staged(c - 1, row16 + fr, head * (D / 4) + 8 * s + 4 * o + fg);
             }
             if constexpr (PRODUCTS) multiply(1);
             if constexpr (HASH) {
@@ -311,53 +308,49 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
                         for (int term = 0; term < 2; ++term) fr2[pair & 1][o][term] = frags[(((group * NT + t + o) * KS + s) * 2 + term) * 64 + of_lane];
                 };
                 read_pair(0);
-                float keep[NU];
-                v8h xh[NU][KS], xl[NU][KS];
+                v8h xh[KS], xl[KS];
+                float nx2 = 0.0f;
 #pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    float nx2 = 0.0f;
+                for (int s = 0; s < KS; ++s)
 #pragma unroll
-                    for (int s = 0; s < KS; ++s)
+                    for (int o = 0; o < 2; ++o)
 #pragma unroll
-                        for (int o = 0; o < 2; ++o)
+                        for (int e = 0; e < 4; ++e) nx2 = __builtin_fmaf(x[s][o][e], x[s][o][e], nx2);
+                nx2 = sum_of_rows(nx2);
+                auto split = [&](float unit) {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) nx2 = __builtin_fmaf(x[u][s][o][e], x[u][s][o][e], nx2);
-                    nx2 = sum_of_rows(nx2);
-                    auto split = [&](float unit) {
+                    for (int s = 0; s < KS; ++s) {
+                        uint32_t up[4], lo[4];
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) {
-                            uint32_t up[4], lo[4];
-#pragma unroll
-                            for (int o = 0; o < 2; ++o) {
-                                const v4f y = x[u][s][o] * unit;
-                                split_f16_pair(y[0], y[1], up[2 * o], lo[2 * o]);
-                                split_f16_pair(y[2], y[3], up[2 * o + 1], lo[2 * o + 1]);
-                            }
-                            xh[u][s] = __builtin_bit_cast(v8h, make_uint4(up[0], up[1], up[2], up[3]));
-                            xl[u][s] = __builtin_bit_cast(v8h, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+                        for (int o = 0; o < 2; ++o) {
+                            const v4f y = x[s][o] * unit;
+                            split_f16_pair(y[0], y[1], up[2 * o], lo[2 * o]);
+                            split_f16_pair(y[2], y[3], up[2 * o + 1], lo[2 * o + 1]);
                         }
-                    };
-                    // rows of ordinary magnitude split as they are, others are brought to |x| ~ 1 first (hash_margin.h)
-                    float unit = 1.0f;
-                    bool zero = false;                       // a row of zeros: hash_tile.h
-                    if (__ballot(!(nx2 >= kOrdinaryMin2 && nx2 <= kOrdinaryMax2)) != 0) {        // wave-uniform
-                        int e = 0;
-                        if (nx2 > 0.0f && nx2 < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2) / 2;
-                        unit = __builtin_amdgcn_ldexpf(1.0f, -e);
-                        split(unit);
-                        zero = nx2 == 0.0f && scale_is_exact(scale);
-#pragma unroll
-                        for (int q = 0; q < NB / 64; ++q) zero = zero && unbounded_columns[q] == 0;
-                    } else {
-                        split(1.0f);
+                        xh[s] = __builtin_bit_cast(v8h, make_uint4(up[0], up[1], up[2], up[3]));
+                        xl[s] = __builtin_bit_cast(v8h, make_uint4(lo[0], lo[1], lo[2], lo[3]));
                     }
-                    keep[u] = nx2 < __builtin_inff() ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2), kKeepFloor) * unit * kColumnScale
-                                                     : __builtin_inff();
-                    if (zero) keep[u] = -1.0f;
+                };
+                // rows of ordinary magnitude split as they are, others are brought to |x| ~ 1 first (hash_margin.h)
+                float unit = 1.0f;
+                bool zero = false;                           // a row of zeros: hash_tile.h
+                if (__ballot(!(nx2 >= kOrdinaryMin2 && nx2 <= kOrdinaryMax2)) != 0) {        // wave-uniform
+                    int e = 0;
+                    if (nx2 > 0.0f && nx2 < __builtin_inff()) e = __builtin_amdgcn_frexp_expf(nx2) / 2;
+                    unit = __builtin_amdgcn_ldexpf(1.0f, -e);
+                    split(unit);
+                    zero = nx2 == 0.0f && scale_is_exact(scale);
+#pragma unroll
+                    for (int q = 0; q < NB / 64; ++q) zero = zero && unbounded_columns[q] == 0;
+                } else {
+                    split(1.0f);
                 }
+                float keep = nx2 < __builtin_inff() ? __builtin_fmaxf(hash_theta(D) * __builtin_sqrtf(nx2), kKeepFloor) * unit * kColumnScale
+                                                  : __builtin_inff();
+                if (zero) keep = -1.0f;
                 // Two tiles' products by turns, their fragments read a pair ahead (the first pair's before the rows are split): left to
                 // itself the compiler read most of them a product ahead (layer of 16384 x 256, 256 bits 100.8 -> 99.6 us).
-                v4f z[NU][NT];
+                v4f z[NT];
 #pragma unroll
                 for (int pair = 0; pair < PAIRS; ++pair) {
                     if (pair + 1 < PAIRS) read_pair(pair + 1);
@@ -367,38 +360,34 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
 #pragma unroll
                         for (int o = 0; o < 2; ++o) {
                             const int s = pair / (NT / 2), t = pair % (NT / 2) * 2 + o;
-#pragma unroll
-                            for (int u = 0; u < NU; ++u)
-                                z[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, fr2[pair & 1][o][part == 1]), part == 2 ? xl[u][s] : xh[u][s],
-                                                                                 s == 0 && part == 0 ? v4f{0.0f, 0.0f, 0.0f, 0.0f} : z[u][t], 0, 0, 0);
+                            z[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, fr2[pair & 1][o][part == 1]), part == 2 ? xl[s] : xh[s],
+                                                                          s == 0 && part == 0 ? v4f{0.0f, 0.0f, 0.0f, 0.0f} : z[t], 0, 0, 0);
                         }
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                uint32_t neg = 0;                            // bit q: sign of element q (-0 is open anyway)
+                float smallest = __builtin_inff();
 #pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    uint32_t neg = 0;                        // bit q: sign of element q (-0 is open anyway)
-                    float smallest = __builtin_inff();
-#pragma unroll
-                    for (int q = 4 * NT - 1; q >= 0; --q) {
-                        const float zq = z[u][q / 4][q % 4];
-                        neg = __builtin_amdgcn_alignbit(neg, __builtin_bit_cast(uint32_t, zq), 31);
-                        smallest = __builtin_fminf(smallest, __builtin_fabsf(zq));
-                    }
-                    const uint32_t bits = ~neg & (uint32_t)((1ull << (4 * NT)) - 1);
-                    const long m = m0 + 16 * (unit0 + u) + fr;
-                    const int bit0 = S::COLS * group + 4 * NT * fg;      // this lane's first column
-                    uint8_t *dst = reinterpret_cast<uint8_t *>((second ? h.of.codes1 : h.of.codes0) + (word_at[u] + (size_t)head0 * h.map.N) * (NB / 64)) + bit0 / 8;
-                    if (m < n_rows) {
-                        if constexpr (NT == 8) *reinterpret_cast<uint32_t *>(dst) = bits;
-                        else if constexpr (NT == 4) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)bits;
-                        else *dst = (uint8_t)bits;
-                    }
-                    if (__ballot(m < n_rows && !(smallest > keep[u])) == 0) continue;    // wave-uniform
+                for (int q = 4 * NT - 1; q >= 0; --q) {
+                    const float zq = z[q / 4][q % 4];
+                    neg = __builtin_amdgcn_alignbit(neg, __builtin_bit_cast(uint32_t, zq), 31);
+                    smallest = __builtin_fminf(smallest, __builtin_fabsf(zq));
+                }
+                const uint32_t bits = ~neg & (uint32_t)((1ull << (4 * NT)) - 1);
+                const long m = m0 + row16 + fr;
+                const int bit0 = S::COLS * group + 4 * NT * fg;          // this lane's first column
+                uint8_t *dst = reinterpret_cast<uint8_t *>((second ? h.of.codes1 : h.of.codes0) + (word_at + (size_t)head0 * h.map.N) * (NB / 64)) + bit0 / 8;
+                if (m < n_rows) {
+                    if constexpr (NT == 8) *reinterpret_cast<uint32_t *>(dst) = bits;
+                    else if constexpr (NT == 4) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)bits;
+                    else *dst = (uint8_t)bits;
+                }
+                if (__ballot(m < n_rows && !(smallest > keep)) != 0) {   // wave-uniform
                     uint32_t open = 0;
 #pragma unroll
-                    for (int q = 0; q < 4 * NT; ++q) open |= (uint32_t)(!(__builtin_fabsf(z[u][q / 4][q % 4]) > keep[u])) << q;
+                    for (int q = 0; q < 4 * NT; ++q) open |= (uint32_t)(!(__builtin_fabsf(z[q / 4][q % 4]) > keep)) << q;
                     if (m >= n_rows) open = 0;
-                    if (keep[u] < __builtin_inff()) open &= ~zeros;
+                    if (keep < __builtin_inff()) open &= ~zeros;
                     // rows with open bits go out for the chain: all four lanes of such a row have a quarter of it
                     const uint64_t any = __ballot(open != 0);
                     if (!SPLIT && ((any >> fr | any >> (fr + 16) | any >> (fr + 32) | any >> (fr + 48)) & 1u)) {
@@ -406,7 +395,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
 #pragma unroll
                         for (int s = 0; s < KS; ++s)
 #pragma unroll
-                            for (int o = 0; o < 2; ++o) *reinterpret_cast<v4f *>(to + 32 * s + 16 * o) = x[u][s][o];
+                            for (int o = 0; o < 2; ++o) *reinterpret_cast<v4f *>(to + 32 * s + 16 * o) = x[s][o];
                     }
                     while (__ballot(open != 0) != 0) {       // wave-uniform
                         if (cnt + 64 > S::LIST) work_off();
@@ -422,7 +411,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
                 }
             }
             if constexpr (!PRODUCTS) return;
-            stores = HASH && m0 + 16 * unit0 < n_rows ? 1 : 0;
+            stores = HASH && m0 + row16 < n_rows ? 1 : 0;
             if constexpr (!STAGED) stores = (m0 + wr * 32 < n_rows) + (m0 + wr * 32 + 16 < n_rows);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {

@@ -59,6 +59,8 @@ def kernels():
     (r"linear_norm_kernel", 3),
     (r"shift_mlp_kernel", 21),
     (r"shift_mlp_walk_kernel", 3),
+    (r"norm_hash_kernel", 32),
+    (r"hamming_pipe_kernel", 6),
 ])
 def test_no_scratch(kernels, pattern, instances):
     some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
@@ -67,10 +69,12 @@ def test_no_scratch(kernels, pattern, instances):
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
 
 
-# two workgroups of eight wavefronts to a CU: K^T V, alone or with Q(K^T V), for many short sequences (a ring of two)
+# two workgroups of eight wavefronts to a CU: K^T V, alone or with Q(K^T V), for many short sequences (a ring of two), and others
 @pytest.mark.parametrize("pattern,instances", [
     (r"ktv_qkv_kernelILi\d+ELi\d+ELi\d+ELi\d+ELi2EE", 4),
     (r"ktv_mfma_kernelILi\d+ELi\d+ELi\d+ELi2ELb[01]EE", 8),
+    (r"norm_hash_kernelILi1ELi32ELi64ELb0EE", 1),           # rows of 64 columns, heads of 32
+    (r"hamming_pipe_kernel", 6),
 ])
 def test_registers_for_two_workgroups(kernels, pattern, instances):
     some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
