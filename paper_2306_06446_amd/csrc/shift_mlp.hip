@@ -15,12 +15,12 @@
 // x 256 122 -> 115.  With prepared weights the output projection in front of the LayerNorm is made here too, from all of Wo in
 // LDS: at E = 64 it costs this launch 0.5 us and saves one of 5.7 (layer 47.1 -> 42.1 us), at E = 256 7.4 of 9.4 (121.9 -> 120.6).
 // The loads of a stage go between the products that end the stage before: all of them ahead of those products, the wavefronts, which
-// have just met, all waited for the memory pipe with the matrix cores idle (16384 x 256, 1024 hidden: 2510 -> 1930 cycles per 128
-// columns).  Of codes a workgroup of 128 rows takes tile after tile, the next one's weights and rows on their way while the outputs
-// leave: a tile of 131072 x 256, 1024 hidden 81 -> 75 thousand cycles with its launch.  The clock takes part of that back (2.14 -> 2.1
-// GHz: the card's power, not its issue slots, is what this kernel runs out of); block of 8 x 16384 tokens 379.8 -> 368.5 us, layer
-// of 16384 x 256 113.2 -> 111.1, of 32 x 784 x 64 39.8 -> 39.4.  Products of 32 x 32 x 32 needed a tenth fewer cycles and took the same
-// time at 1.98 GHz, and the kernels around them longer (block 369 against 365).
+// have just met, all waited for the memory pipe with the matrix cores idle (16384 x 256: 2.07 -> 1.77 us per 128 hidden columns of both
+// layers, 4400 -> 3700 cycles of a CU whose matrix cores need 2048 for them; 131072 x 256, 1024 hidden 138.9 -> 128.1 us).  Of short hidden
+// layers a workgroup of 128 rows takes tile after tile, the next one's weights and rows on their way while the outputs leave (launch_shift_mlp).
+// The clock takes part of that back (2.14 -> 2.1 GHz: the card's power, not its issue slots, is what this kernel runs out of); layer of
+// 16384 x 256 113.2 -> 111.1, of 32 x 784 x 64 39.8 -> 39.4.  Products of 32 x 32 x 32 needed a tenth fewer cycles and took the same time at
+// 1.98 GHz, and the kernels around them longer (block of 8 x 16384 tokens 369 against 365).
 // Layer 1 on four wavefronts and layer 2 on the other four (requantiser beside products without being interleaved): 226 us
 // for the last one.
 #include "common.h"
@@ -615,16 +615,20 @@ bool sa::shift_mlp_one_launch(const RowSel &sel, int E, int hid, MlpCall call) {
 
 // Rows of a workgroup: 64, or 128 where that takes fewer rounds of the chip by more than the 1.45 times that a round of the
 // larger ones takes (256 x 1024: 16384 rows 26 against 36 us, 25088 rows 47 against 37, 131072 rows 181 against 145).  At
-// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).  Of rows that only the device counts half are expected.  Those
-// walk where their bound is more than a tile a CU: with fewer after all it costs 0.1 us (128 x 256, 30 % of 66000 rows 9.85, 10.0;
-// 128 x 768 17.4, 17.3), with more it saves (all of 40000 rows of 128 x 256 18.3, 16.0).
+// E = 64 two of the smaller share a CU (131072 rows 33 against 34 us).  Of rows that only the device counts half are expected.
+// More of the larger ones than CUs: one after the other on 256 workgroups where the hidden layer is short.  What a tile saves is its start
+// and its outputs' wait, and from 192 columns on every chunk pays for it with addresses made anew (a workgroup a tile / walking, us: 128 x
+// 512, 131072 rows 48.3, 45.4; 128 x 1024 77.9, 75.2; 128 x 2048 131.8, 133.3; 192 x 256 44.9, 42.4; 192 x 384 54.6, 53.7; 192 x 768 82.5, 86.5;
+// 256 x 512 82.3, 81.2; 256 x 768, 65536 rows 53.6, 55.2; 256 x 1024 65.1, 67.8, 131072 rows 127.8, 131.7).  By the bound of rows that only the
+// device counts: with fewer after all walking costs 0.1 us (128 x 256, 30 % of 66000 rows 9.85, 10.0), with more it saves (all of 40000
+// rows of 128 x 256 18.3, 16.0).
 int sa::launch_shift_mlp(const int8_t *x, const NormRows *norm, const RowSel &sel, int E, int hid, const int8_t *w1_planes,
                          const int8_t *w2_planes, const int8_t *lut, float requant_scale, const Epilogue &out, hipStream_t st) {
     SA_REQUIRE(!norm || (!sel.rows && !out.gate), SA_ERR_INVALID, "sa_shift_mlp: rows to normalise are all rows, ungated");
     const MlpArgs a{x, norm, sel, hid, w1_planes, w2_planes, lut, requant_scale_finite(requant_scale), ShiftStore<kEpiScatterI32>(out)};
     const long m_est = sel.counts ? (sel.max_rows + 1) / 2 : sel.max_rows;
     auto rounds = [&](long rows) { return ((m_est + rows - 1) / rows + 255) / 256; };
-    const bool tall = 29 * rounds(128) < 20 * rounds(64), walk = sel.max_rows > 256 * 128;
+    const bool tall = 29 * rounds(128) < 20 * rounds(64), walk = sel.max_rows > 256 * 128 && hid <= (E == 128 ? 1024 : E == 192 ? 384 : 512);
     switch (E) {
         case 64: return launch<1, 2>(a, false, st);
         case 128: return tall ? launch<2, 4>(a, walk, st) : launch<2, 2>(a, false, st);

@@ -111,8 +111,10 @@ def test_two_launches_they_are(sa, T, E, hid):
     assert not bool(ws[:T * hid].any())                      # the hidden rows, all of them 0
 
 
-# A tile of 128 rows for every CU, and one row more: the last rows whose workgroups take one tile each, and the first whose take several.
-@pytest.mark.parametrize("rows,E,hid", [(32768 - 37, 128, 256), (32769 - 37, 128, 384), (32768 - 37, 192, 384), (32768 - 37, 256, 1024)])
+# A tile of 128 rows for every CU, and one row more: the last rows whose workgroups take one tile each, and the first whose take several; hidden
+# layers that are too long for that.
+@pytest.mark.parametrize("rows,E,hid", [(32768 - 37, 128, 256), (32769 - 37, 128, 384), (32768 - 37, 192, 384), (32768 - 37, 256, 1024),
+                                        (65536 - 37, 256, 640), (65536 - 37, 192, 512), (65536 - 37, 128, 1152)])
 def test_a_tile_for_every_cu(sa, rows, E, hid):
     test_one_launch_equals_the_two_layers(sa, rows, E, hid)
 
