@@ -162,10 +162,11 @@ int sa_hamming_attention(const uint64_t *q_codes, const uint64_t *k_codes, const
  * variant: SA_VARIANT_VALU computes the scores by XOR + popcount on the vector ALU, one
  * (batch, head, 256 queries) unit per workgroup; SA_VARIANT_MFMA as the dot product of the
  * +-1 sign vectors on the matrix cores (the same integers, nbits <= 256); SA_VARIANT_AUTO
- * (what sa_hamming_attention uses) is the popcount form again, for dv <= 64, nbits <= 256 and
- * scales that need no per-row reference as a launch whose workgroups walk over several units
- * with the next chunk of V and key codes loading meanwhile (bit-identical to
- * SA_VARIANT_VALU), else as SA_VARIANT_VALU. */
+ * (what sa_hamming_attention uses) is bit-identical to SA_VARIANT_VALU.  For dv <= 64,
+ * nbits <= 256 and scales that need no per-row reference the distances are products of the code
+ * bits as fp4 +-1 on the matrix cores (exact), in workgroups that walk over several units of 256
+ * queries, or of 128 where a CU then has one, with the next chunk of V and key codes loading
+ * meanwhile.  Else, and for many units of up to 32 keys, it is SA_VARIANT_VALU. */
 int sa_hamming_attention_fused(const uint64_t *q_codes, const uint64_t *k_codes, const float *v,
                                float *out, int B, int H, int Nq, int Nk, int nbits, int dv,
                                float scale, int16_t *scores_or_null, int8_t *xq_or_null,

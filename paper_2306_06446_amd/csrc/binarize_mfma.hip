@@ -380,6 +380,9 @@ int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &
     // Longer tiles lose by it (d = 64: 302592 rows 18.0, 20.6; 128 bits 23.4, 28.1), and so does a launch that also routes, by its tail: its
     // last workgroups look at all tokens and wait for a place beside the sixteen (blocks with two experts, us with sixteen and eight:
     // 35 x 567 tokens x 2 heads 42.4, 41.6; x 4 heads 68.6, 66.2; 1 x 19845 x 2 46.0, 45.0; with places left free for them 42.5, 67.2, 46.4).
+    // The decode of packed weights may ride along: it looks at nothing but its own share and only fills CUs that are done (blocks with a
+    // Shift MLP on packed weights, us with eight and sixteen: 25088 tokens x 4 heads, 512 hidden 35.4, 33.6; 50176 x 2, 256 hidden 32.8,
+    // 31.1; 12544 x 8, 1024 hidden 42.4, 40.9; the same up to 6272 tokens).
     constexpr bool SHORT = D == 32 && C == 64;
     const bool sixteen = SHORT && side.route.T == 0;
     const int per_cu = C != 64 ? 1 : (sixteen ? 16 : 8) / kWaves;

@@ -1,5 +1,6 @@
-// What the matrix-core hash (binarize_mfma.hip) may get wrong before it asks the defining chain, in one place, so that its
-// margin is a proof and not a measurement.  Plain C++: the test suite compiles it on the host.
+// What the matrix-core hash (binarize_mfma.hip, and in the projection's launches norm_hash.hip and linear_hash.hip) may get wrong
+// before it asks the defining chain, in one place, so that its margin is a proof and not a measurement.  The three add their
+// products in different orders; the bound on the accumulation holds for any.  Plain C++: the test suite compiles it on the host.
 //
 // With X = |x| and a column r of which the kernel holds r^ = r / |r| in units of 1 / 1024, z~ = xh rh + xh rl + xl rh in
 // fp16 terms with fp32 sums.  The sign of z~ is that of the chain if |z~| exceeds X times the sum of, each relative to

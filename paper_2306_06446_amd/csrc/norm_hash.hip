@@ -493,8 +493,9 @@ int launch_width(const NormRows &norm, long T, const int8_t *w, float scale, con
 //   to linear_hash.hip there (192: 65536 rows 185.3, 179.0; 256: 100000 rows 419.7, 388.9), as do few of them that this does not take.
 //
 // Few rows: a workgroup for every 64 columns of Wqkv of 64 rows, all of which normalise the same rows and none of which does more than
-// one chunk.  Up to one for every CU, and more where two share one or the other ways are slow; what takes the call otherwise (two or three
-// launches, or one with all chunks), and this, us:
+// one chunk.  Up to one for every CU, and more where two share one (64 bits: E = 64, and 128 with heads of 32) or where the other ways are
+// slow enough for a second or third round: the LDS is that of the walking kernels, so that with heads of 64 and 128 columns or more (82 KB
+// and up) a CU has one at a time.  What takes the call otherwise (two or three launches, or one with all chunks), and this, us:
 //   E =  64   64 bits: 197 rows 19.5, 18.1; 5600 25.7, 24.7; 10922 27.3, 26.4; 13000 27.7, 28.1.  256 bits: 197 rows 32.1, 29.6; 5440 36.9,
 //            34.3; 8000 38.3, 40.1
 //   E = 128   64 bits: 197 rows 30.5, 25.3; 2730 38.0, 32.3; 5600 39.1, 38.4; 6400 39.0, 40.1, heads of 32 37.0, 34.8.  128 bits: 5600 rows
