@@ -431,7 +431,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
     // Two partials only where the launch has more than two workgroups for a CU: the sums' barriers cost a lone one more than the trip they save
     // (both products of 12 x 400 tokens x 64 10.55 us by quads, 10.44 below; 64 x 400 x 64 12.04, 11.93; 200 x 400 x 64 22.0, 22.6; 96 x 512 x 128
     // 19.6, 20.3).
-    if (SUMS && W == 1 && (f.splits > 2 || (f.splits == 2 && gridDim.x > 512))) {
+    if (SUMS && W == 1 && f.splits > 1 && (f.splits > 2 || gridDim.x > 512)) {
         // Partials of 64-bit codes: summed on the way, in ascending order, and the first workgroup of the (b, h) leaves the sum in kv.
         // A thread sums four columns of a row, eight partials in flight: they come from other CUs, and one after the other each took
         // a trip of its own.  Both products of 32 x 3136 tokens x 1 head x 64 bits 17.1 -> 16.9 us, 4 x 12 x 3072 x 64 bits 29.1 -> 28.2,
@@ -471,12 +471,13 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             if (tid + i * n_threads < NBITS / 8 * DVC) to_planes(tid + i * n_threads, x[i]);
     } else {
         for (int t = tid; t < NBITS / 8 * DVC; t += n_threads) {
-            // (Up to 128 bits one address and the others a constant away: made from bit_of each, both products of 400 x 20 tokens x 32 x 128
-            // bits took 8.10 us, so 7.95, of 24 x 7000 x 64 x 128 bits 42.3, 41.1.  For 256 bits that is 0.5 % longer over 200 sizes.)
-            const size_t at = ((size_t)bh * NBITS + bit_of(t, 0)) * DV + c0 + t % DVC;
+            // Of 128 bits, and of two partials, one address and the others a constant away: made from bit_of each, both products of 400 x 20 tokens
+            // x 32 x 128 bits took 8.10 us, so 7.95, of 24 x 7000 x 64 x 128 bits 42.3, 41.1.  Not for others (64 bits in one launch, layer of
+            // 64 x 197 x 12 heads 196.4, 199.3; 256 bits 0.5 % longer over 200 sizes).
+            constexpr bool NEAR = W == 2 || (W == 1 && SUMS);
             auto row = [&](int e) {
-                if constexpr (W <= 2) return at + ((e >> 1) + 16 * (e & 1)) * DV;
-                else return ((size_t)bh * NBITS + bit_of(t, e)) * DV + c0 + t % DVC;
+                return NEAR ? ((size_t)bh * NBITS + bit_of(t, 0)) * DV + c0 + t % DVC + ((e >> 1) + 16 * (e & 1)) * DV
+                            : ((size_t)bh * NBITS + bit_of(t, e)) * DV + c0 + t % DVC;
             };
             float x[8];
 #pragma unroll
@@ -484,15 +485,13 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             // Longer codes have fewer partials, of which the sums above have several quads a thread (4 x 8 heads x 4237 tokens x 128 bits 24.0,
             // there 24.2; 16 x 4 x 1600 21.0, 20.6; 8 x 8 x 1500 x 256 bits 27.1, 27.4).
             if constexpr (SUMS) {
-                for (int s = 1; s < f.splits; ++s) {
-                    const float *p = f.kv_in + (size_t)s * BH * NBITS * DV;
+                for (int s = 1; s < f.splits; ++s)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] += p[row(e)];
-                }
-                if (f.kv_out && part == 0) {
+                    for (int e = 0; e < 8; ++e)
+                        x[e] += f.kv_in[NEAR ? (size_t)s * BH * NBITS * DV + row(e) : (((size_t)s * BH + bh) * NBITS + bit_of(t, e)) * DV + c0 + t % DVC];
+                if (f.kv_out && part == 0)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) f.kv_out[row(e)] = x[e];
-                }
             }
             to_planes(t, x);
         }
