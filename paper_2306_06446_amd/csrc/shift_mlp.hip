@@ -80,12 +80,13 @@ struct MlpStage {
 // tile costs one that has none (one tile a workgroup, prepared weights, one way out of this code and the other: 128 x 512, 16400
 // rows 13.7 and 12.4 us, 128 x 768 17.9 and 15.9, 192 x 768 21.8 and 19.6, 256 x 1024, 32768 rows 35.5 and 33.2).
 template <int NE, int MI, int ROWS, bool WALK, class Store>
-__device__ __forceinline__ void shift_mlp_tiles(const int8_t *__restrict__ x, const NormRows &norm, const RowSel &sel, int hid,
+__device__ __forceinline__ void shift_mlp_tiles(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
                                                 const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
-                                                const int8_t *__restrict__ lut, float rq, const Store &store, uint8_t *lds) {
+                                                const int8_t *__restrict__ lut, float rq, Store store) {
     constexpr bool NORM = ROWS != kCodes, PROJECT = ROWS == kProject;
     using S = MlpShape<NE, MI, PROJECT, WALK, Store>;
     constexpr int E = S::E, PS = S::PS, SPG = S::SPG, LOADS = S::LOADS;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[S::LDS_BYTES];
     const int32_t *rows;
     long n_rows;
     resolve_rows(sel, rows, n_rows);
@@ -515,16 +516,14 @@ template <int NE, int MI, int ROWS, class Store>
 __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_kernel(const int8_t *__restrict__ x, NormRows norm, RowSel sel, int hid,
                                                                    const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
                                                                    const int8_t *__restrict__ lut, float rq, Store store) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[MlpShape<NE, MI, ROWS == kProject, false, Store>::LDS_BYTES];
-    shift_mlp_tiles<NE, MI, ROWS, false>(x, norm, sel, hid, w1, w2, lut, rq, store, lds);
+    shift_mlp_tiles<NE, MI, ROWS, false>(x, norm, sel, hid, w1, w2, lut, rq, store);
 }
 
 template <int NE, class Store>
 __global__ __launch_bounds__(kMlpWaves * 64) void shift_mlp_walk_kernel(const int8_t *__restrict__ x, RowSel sel, int hid,
                                                                         const int8_t *__restrict__ w1, const int8_t *__restrict__ w2,
                                                                         const int8_t *__restrict__ lut, float rq, Store store) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[MlpShape<NE, 4, false, true, Store>::LDS_BYTES];
-    shift_mlp_tiles<NE, 4, kCodes, true>(x, NormRows{}, sel, hid, w1, w2, lut, rq, store, lds);
+    shift_mlp_tiles<NE, 4, kCodes, true>(x, NormRows{}, sel, hid, w1, w2, lut, rq, store);
 }
 
 struct MlpArgs {
