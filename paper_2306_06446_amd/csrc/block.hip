@@ -8,7 +8,7 @@
 namespace {
 
 struct Layout {
-    size_t qc, kc, kv, attn_ws, xq, xh, perm, expert_of, counts, gate, disp_ws, shift_ws, mult_ws, total;
+    size_t qc, kc, kv, attn_ws, xq, xh, perm, expert_of, counts, gate, disp_ws, shift_ws, mult_ws, needed, few, total;
     size_t attn_ws_bytes, disp_ws_bytes, shift_ws_bytes, mult_ws_bytes;
 };
 
@@ -53,6 +53,8 @@ int plan(const sa_block_desc *d, Layout *L) {
             L->mult_ws = off; off += up(L->mult_ws_bytes);
         }
     }
+    L->needed = L->few = off;
+    if (d->hid > 0) off += up(sa::plan_few_rows((long)T, (int)E, d->hid, d->moe != 0, false).bytes);
     L->total = off;
     return SA_OK;
 }
@@ -93,6 +95,14 @@ struct ShiftWeights {
     }
 };
 
+// Whether the MLP of this block, or the MLP half of this layer, is one launch: with few rows on the matrix cores, where the caller's
+// workspace has room for it (the size that is asked for does; a smaller one is taken as long as the other launches' fits).
+template <class Desc>
+sa::FewRowsPlan few_rows(const Desc &d, int E, long T, bool layer, size_t workspace_bytes) {
+    if (d.hid <= 0 || d.shift_variant == SA_VARIANT_VALU || d.workspace_bytes < workspace_bytes) return {};
+    return sa::plan_few_rows(T, E, d.hid, d.moe != 0, layer);
+}
+
 // Hash of Q and K, carrying `side` where it is one launch.
 int hash_and_side(const float *q, const float *k, int B, int N, int H, int d, const float *proj, int nbits, uint64_t *qc,
                   uint64_t *kc, const sa::SideWork &side, void *stream) {
@@ -101,6 +111,7 @@ int hash_and_side(const float *q, const float *k, int B, int N, int H, int d, co
     int rc = SA_OK;
     const sa::RouteWork &r = side.route;
     if (r.T > 0) rc = sa::moe_dispatch_launch(r.logits, r.T, r.E, r.perm, r.expert_of, r.counts, r.gate, nullptr, sa::as_stream(stream));
+    if (rc == SA_OK && side.zero.n > 0) rc = sa::launch_zero(side.zero.words, 4 * (size_t)side.zero.n, sa::as_stream(stream));
     if (rc == SA_OK && side.decode.chunks[0] > 0) rc = sa::launch_decode_work(side.decode, sa::as_stream(stream));
     if (rc != SA_OK) return rc;
     return sa_binarize_pair(q, k, B, N, H, d, proj, nbits, qc, kc, stream);
@@ -137,8 +148,8 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     int rc = plan(d, &L);
     if (rc != SA_OK) return rc;
     SA_REQUIRE(d->q && d->k && d->v && d->o, SA_ERR_INVALID, "block: q, k, v and o are required");
-    SA_REQUIRE(d->workspace != nullptr && d->workspace_bytes >= L.total, SA_ERR_WORKSPACE,
-               "block: workspace of %zu bytes needed, %zu given", L.total, d->workspace_bytes);
+    SA_REQUIRE(d->workspace != nullptr && d->workspace_bytes >= L.needed, SA_ERR_WORKSPACE,
+               "block: workspace of %zu bytes needed, %zu given", L.needed, d->workspace_bytes);
     SA_REQUIRE(sa::aligned16(d->workspace), SA_ERR_ALIGN, "block: workspace must be 16-byte aligned");
     if (d->hid > 0) {
         SA_REQUIRE(d->w1 && d->w2 && d->lut && d->y, SA_ERR_INVALID, "block: w1, w2, lut and y are required");
@@ -174,7 +185,11 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     // Everything runs on the caller's stream, one kernel after the other.
     // The routing and the decode of packed Shift weights wait for nothing: they ride in the hash's launch.
     sa::SideWork side;
-    if (moe && T <= sa::kSideRouteTokens) {
+    const sa::FewRowsPlan plan = few_rows(*d, E, T, false, L.total);
+    const bool few = plan.bytes > 0;
+    if (few) {
+        side.zero = {reinterpret_cast<uint32_t *>(ws + L.few), (int)(plan.ticket_bytes / 4)};
+    } else if (moe && T <= sa::kSideRouteTokens) {
         side.route = {d->logits, T, 2, expert_of, gate, counts, perm};
     } else if (moe) {
         rc = sa_moe_dispatch(d->logits, T, 2, perm, expert_of, counts, gate, ws + L.disp_ws, L.disp_ws_bytes, stream);
@@ -197,6 +212,10 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     }
     if (rc != SA_OK || !mlp) return rc;
 
+    if (few)
+        return sa::launch_few_rows({xq, xh, nullptr, nullptr, nullptr, moe ? d->logits : nullptr, T, E, d->hid, reinterpret_cast<const int8_t *>(weights.w1),
+                                    reinterpret_cast<const int8_t *>(weights.w2), d->lut, moe ? d->mw1 : nullptr, moe ? d->mw2 : nullptr,
+                                    d->requant_scale, d->out_scale, d->y, ws + L.few}, plan, sa::as_stream(stream));
     if (!moe) {
         const sa_rows all{nullptr, nullptr, 0, T};
         return sa_shift_mlp(xq, &all, E, d->hid, weights.w1, weights.w2, d->requant_scale, d->lut, nullptr, d->y, nullptr,
@@ -214,7 +233,7 @@ namespace {
 
 struct LayerLayout {
     size_t codes8, q, k, v, qc, kc, kv, attn_ws, xh, logits, perm, expert_of, counts, gate, disp_ws, shift_ws,
-        mult_ws, lin_ws, total;
+        mult_ws, lin_ws, needed, few, few_wo, total;
     size_t attn_ws_bytes, disp_ws_bytes, shift_ws_bytes, mult_ws_bytes, lin_ws_bytes;
 };
 
@@ -265,6 +284,11 @@ int plan_layer(const sa_layer_desc *d, LayerLayout *L) {
         L->mult_ws_bytes = sa_mult_mlp_workspace_bytes((long)T, d->E, d->hid);
         L->mult_ws = off; off += up(L->mult_ws_bytes);
     }
+    L->needed = L->few = off;
+    const size_t few = sa::plan_few_rows((long)T, d->E, d->hid, d->moe != 0, true).bytes;
+    off += up(few);
+    L->few_wo = off;
+    if (few > 0 && d->shift_variant != SA_VARIANT_MFMA_PREPARED) off += up(2 * E * E);      // planes of wo
     L->total = off;
     return SA_OK;
 }
@@ -286,8 +310,8 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                    d->lut,
                SA_ERR_INVALID, "layer: x, y, the LayerNorm parameters, wqkv, wo, w1, w2 and lut are required");
     if (d->moe) SA_REQUIRE(d->wg && d->bg && d->mw1 && d->mw2, SA_ERR_INVALID, "layer: wg, bg, mw1, mw2 are required");
-    SA_REQUIRE(d->workspace != nullptr && d->workspace_bytes >= L.total, SA_ERR_WORKSPACE,
-               "layer: workspace of %zu bytes needed, %zu given", L.total, d->workspace_bytes);
+    SA_REQUIRE(d->workspace != nullptr && d->workspace_bytes >= L.needed, SA_ERR_WORKSPACE,
+               "layer: workspace of %zu bytes needed, %zu given", L.needed, d->workspace_bytes);
     SA_REQUIRE(sa::aligned16(d->workspace), SA_ERR_ALIGN, "layer: workspace must be 16-byte aligned");
     uint8_t *ws = static_cast<uint8_t *>(d->workspace);
     const long T = (long)d->B * d->N;
@@ -341,13 +365,22 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     const bool packed = d->shift_variant == SA_VARIANT_MFMA || d->shift_variant == SA_VARIANT_AUTO;
     const bool linear_hash = !fused_hash && !norm_hash && (norms || packed) && d->proj && sa::linear_hash_one_launch(T, E, d->H, d->nbits, packed);
     const bool norm_linear = norm_hash || (norms && !linear_hash && sa::norm_linear_one_launch(T, E));
+    const sa::FewRowsPlan plan = few_rows(*d, E, T, true, L.total);
+    const bool few = plan.bytes > 0;
+    sa::ZeroWork zero;                            // for the launch of the MLP half: by the layer's first launch
+    if (few) zero = {reinterpret_cast<uint32_t *>(ws + L.few), (int)(plan.ticket_bytes / 4)};
     if (!norm_linear) {
-        rc = sa_layernorm_quant(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
-                                nullptr, 0, nullptr, stream);
+        rc = sa::launch_layernorm(d->x, T, E, d->gamma1, d->beta1, d->eps, d->ln_inv_scale, nullptr, codes8, nullptr, nullptr,
+                                  nullptr, 0, nullptr, zero, sa::as_stream(stream));
         if (rc != SA_OK) return rc;
     }
     sa::SideWork side;
     const ShiftWeights weights(*d, E, T, ws + L.shift_ws, &side.decode);
+    const int8_t *wo_planes = reinterpret_cast<const int8_t *>(d->wo);
+    if (few && packed) {
+        sa::add_decode(&side.decode, d->wo, E, E, ws + L.few_wo);
+        wo_planes = reinterpret_cast<const int8_t *>(ws + L.few_wo);
+    }
     if (fused_hash) {
         if (side.any()) rc = sa::launch_decode_work(side.decode, sa::as_stream(stream));
         if (rc != SA_OK) return rc;
@@ -362,6 +395,7 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
             norm.beta = d->beta1;
             norm.eps = d->eps;
             norm.inv_scale = d->ln_inv_scale;
+            norm.zero = zero;
             if (norm_hash)
                 rc = sa::launch_norm_hash(norm, d->B, d->N, d->H, E, reinterpret_cast<const int8_t *>(d->wqkv), d->qkv_scale, d->proj, d->nbits,
                                           q, k, qc, kc, v, sa::as_stream(stream));
@@ -411,6 +445,12 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
     norm.inv_scale = d->ln_inv_scale;
     norm.residual = d->x;
     norm.scale = d->o_scale;
+    if (few) {
+        norm.wo = wo_planes;
+        return sa::launch_few_rows({codes8, nullptr, &norm, moe ? d->wg : nullptr, moe ? d->bg : nullptr, nullptr, T, E, d->hid,
+                                    reinterpret_cast<const int8_t *>(weights.w1), reinterpret_cast<const int8_t *>(weights.w2), d->lut,
+                                    moe ? d->mw1 : nullptr, moe ? d->mw2 : nullptr, d->requant_scale, d->out_scale, d->y, ws + L.few}, plan, sa::as_stream(stream));
+    }
     const bool linear_norm = !one_launch && d->shift_variant == SA_VARIANT_MFMA_PREPARED && sa::linear_norm_one_launch(T, E);
     if (project || linear_norm) norm.wo = reinterpret_cast<const int8_t *>(d->wo);
     if (!norm.wo) {

@@ -178,15 +178,23 @@ struct RouteWork {                           // sa_moe_dispatch in one launch
     int32_t *counts = nullptr, *perm = nullptr;
 };
 struct DecodeWork {                          // packed weights [N, K], K a multiple of 64, to their two planes
-    const uint4 *w4[2] = {nullptr, nullptr};
-    uint4 *plane_a[2] = {nullptr, nullptr}, *plane_b[2] = {nullptr, nullptr};
-    long chunks[2] = {0, 0};                 // of 32 weights; 0: none
+    const uint4 *w4[3] = {nullptr, nullptr, nullptr};
+    uint4 *plane_a[3] = {nullptr, nullptr, nullptr}, *plane_b[3] = {nullptr, nullptr, nullptr};
+    long chunks[3] = {0, 0, 0};              // of 32 weights; 0: none
+};
+struct ZeroWork {                            // words to be cleared for a later launch, by the first workgroup of this one
+    uint32_t *words = nullptr;
+    int n = 0;
 };
 struct SideWork {
     RouteWork route;
     DecodeWork decode;
-    bool any() const { return route.T > 0 || decode.chunks[0] > 0; }
+    ZeroWork zero;
+    bool any() const { return route.T > 0 || decode.chunks[0] > 0 || zero.n > 0; }
 };
+__device__ inline void zero_words(const ZeroWork &z) {
+    for (int i = threadIdx.x; i < z.n; i += blockDim.x) z.words[i] = 0u;
+}
 void add_decode(DecodeWork *w, const uint8_t *w4, int K, int N, void *planes);
 // Both layers of an MLP; `workspace` as sa_shift_mlp lays it out.  The planes then are what the prepared variant takes.
 void shift_mlp_decode(DecodeWork *w, const uint8_t *w1, const uint8_t *w2, int E, int hid, long max_rows, void *workspace,
@@ -223,6 +231,7 @@ struct NormRows {
     const int8_t *wo = nullptr;
     const float *residual = nullptr;
     float scale = 1.0f, *out = nullptr;
+    ZeroWork zero;           // (launch_norm_linear, launch_norm_hash)
 };
 // Of the rows x; of all rows of norm, or of those it makes of the codes x (they may be the output's: a workgroup reads its rows
 // before it writes them).
@@ -238,6 +247,31 @@ struct NormOut {
 };
 bool linear_norm_one_launch(long T, int E);
 int launch_linear_norm(const int8_t *codes, const NormRows &norm, long T, int E, const NormOut &to, hipStream_t st);
+// The whole MLP half of a layer, or the MLP of a block, in one launch for few rows (few_rows_mlp.hip): the workspace it takes (none: it
+// does not take the shape, or has no gain by it), of which the first ticket_bytes are zero before the launch; and the launch.
+struct FewRowsPlan {
+    size_t bytes = 0, ticket_bytes = 0;
+    int mi = 1;              // 16-row tiles of a workgroup
+};
+struct FewRowsMlp {
+    const int8_t *codes;     // of the attention's output (layer), of the rows (block)
+    const void *half;        // block with a Mult expert: the rows as fp16
+    const NormRows *norm;    // layer: residual, scale, wo, LayerNorm; else null
+    const float *wg, *bg;    // layer with two experts: the router
+    const float *logits;     // block with two experts: [T, 2]
+    long T;
+    int E, hid;
+    const int8_t *w1, *w2, *lut;     // decoded planes
+    const void *mw1, *mw2;   // Mult expert, or null
+    float requant_scale, out_scale;
+    float *y;                // layer: residual + ..., complete
+    void *workspace;
+};
+FewRowsPlan plan_few_rows(long T, int E, int hid, bool moe, bool layer);
+int launch_few_rows(const FewRowsMlp &m, const FewRowsPlan &p, hipStream_t st);
+// sa_layernorm_quant without its argument checks; `zero` is cleared by its first workgroup.
+int launch_layernorm(const float *x, long T, int E, const float *gamma, const float *beta, float eps, float inv_scale, float *ln, int8_t *q,
+                     void *xh, const float *wg, const float *bg, int n_experts, float *logits, const ZeroWork &zero, hipStream_t st);
 // LayerNorm of all T rows of norm.x and the Q, K, V projection of its codes (decoded planes [3E, E]) in one launch
 // (norm_linear.hip): whether it is the faster way, and the launch.
 bool norm_linear_one_launch(long T, int E);

@@ -37,6 +37,7 @@ struct LnArgs {
     const float *bg;    // [n_exp]
     int n_exp;
     float *logits;      // [T, n_exp]
+    ZeroWork zero;
 };
 
 // ROUTE2: the router has two experts and its weight columns live in registers next to gamma and
@@ -47,6 +48,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void layernorm_kernel(LnArgs a
     constexpr int GROUPS = 64 / LPR;              // rows side by side in a wavefront
     const int lane = threadIdx.x & 63, l = lane % LPR;
     const int E = a.E;
+    if (blockIdx.x == 0) zero_words(a.zero);
     // a wavefront walks GROUPS consecutive rows at a time
     const long t0 = ((long)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * rows_per_group * GROUPS + lane / LPR;
     if (t0 - lane / LPR >= a.T) return;
@@ -190,10 +192,15 @@ extern "C" int sa_layernorm_quant(const float *x, long T, int E, const float *ga
     const int bad = sa::check_layernorm(x, T, E, gamma, beta, ln_or_null, q_or_null, xh_or_null, wg_or_null, bg_or_null, n_experts,
                                         logits_or_null);
     if (bad != SA_OK || T == 0) return bad;
-    const bool route = logits_or_null != nullptr;
-    LnArgs a{x, T, E, gamma, beta, eps, inv_scale, ln_or_null, q_or_null, static_cast<_Float16 *>(xh_or_null),
-             route ? wg_or_null : nullptr, route ? bg_or_null : nullptr, route ? n_experts : 0, logits_or_null};
-    hipStream_t st = sa::as_stream(stream);
+    return sa::launch_layernorm(x, T, E, gamma, beta, eps, inv_scale, ln_or_null, q_or_null, xh_or_null, wg_or_null, bg_or_null, n_experts,
+                                logits_or_null, sa::ZeroWork(), sa::as_stream(stream));
+}
+
+int sa::launch_layernorm(const float *x, long T, int E, const float *gamma, const float *beta, float eps, float inv_scale, float *ln, int8_t *q,
+                         void *xh, const float *wg, const float *bg, int n_experts, float *logits, const ZeroWork &zero, hipStream_t st) {
+    const bool route = logits != nullptr;
+    const LnArgs a{x, T, E, gamma, beta, eps, inv_scale, ln, q, static_cast<_Float16 *>(xh),
+                   route ? wg : nullptr, route ? bg : nullptr, route ? n_experts : 0, logits, zero};
     const int ch = (E + 255) / 256;
     if (E <= 64) return launch<16, 1>(a, st);
     if (E <= 128) return launch<32, 1>(a, st);

@@ -107,6 +107,7 @@ __global__ __launch_bounds__(kWaves * 64, D == 32 && NE == 1 ? 4 : 2) void norm_
     };
     long m0 = (long)(SPLIT ? blockIdx.x / (3 * NE) : blockIdx.x) * kRows;
     if (m0 >= n_rows) return;
+    if (blockIdx.x == 0) zero_words(norm.zero);
     load_rows(m0);
     const float4 gamma = *reinterpret_cast<const float4 *>(norm.gamma + col);
     const float4 beta = *reinterpret_cast<const float4 *>(norm.beta + col);

@@ -45,6 +45,7 @@ __global__ __launch_bounds__(kWaves * 64) void norm_linear_kernel(NormRows norm,
     const int wr = wave >> 2, wc = wave & 3, fr = lane & 15, fg = lane >> 4;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
     const long m0 = (long)blockIdx.x * kRows;
+    if (blockIdx.x == 0) zero_words(norm.zero);
 
     // this wavefront's rows, LPR lanes each
     constexpr int LPR = NE == 1 ? 16 : NE == 2 ? 32 : 64, GROUPS = 64 / LPR, STEPS = kRows / kWaves / GROUPS;

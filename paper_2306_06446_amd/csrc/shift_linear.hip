@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) void decode_works_kernel(DecodeWork w, DecodeW
     else decode_block<256>(w2, blockIdx.x - first);
 }
 
-unsigned decode_blocks(const DecodeWork &w) { return (unsigned)((w.chunks[0] + w.chunks[1] + 255) / 256); }
+unsigned decode_blocks(const DecodeWork &w) { return (unsigned)((w.chunks[0] + w.chunks[1] + w.chunks[2] + 255) / 256); }
 
 int launch_decode(const DecodeWork &w, hipStream_t st) {
     decode_work_kernel<<<dim3(decode_blocks(w)), dim3(256), 0, st>>>(w);
@@ -499,7 +499,7 @@ int sa::shift_linear_planes(const uint8_t *w4, int K, int N, int variant, void *
 }
 
 void sa::add_decode(DecodeWork *w, const uint8_t *w4, int K, int N, void *planes) {
-    const int i = w->chunks[0] == 0 ? 0 : 1;
+    const int i = w->chunks[0] == 0 ? 0 : w->chunks[1] == 0 ? 1 : 2;
     w->w4[i] = reinterpret_cast<const uint4 *>(w4);
     w->plane_a[i] = static_cast<uint4 *>(planes);
     w->plane_b[i] = w->plane_a[i] + (size_t)N * K / 16;

@@ -163,15 +163,22 @@ __device__ inline void decode8(uint32_t x, uint32_t outA[2], uint32_t outB[2]) {
 template <int THREADS>
 __device__ __forceinline__ void decode_block(const DecodeWork &w, long block) {
     long i = block * THREADS + threadIdx.x;
-    const int m = i >= w.chunks[0] ? 1 : 0;
-    if (m) i -= w.chunks[0];
-    if (m && i >= w.chunks[1]) return;
-    const uint4 wv = m ? w.w4[1][i] : w.w4[0][i];
+    int m = 0;
+    if (i >= w.chunks[0]) {
+        i -= w.chunks[0];
+        m = 1;
+        if (i >= w.chunks[1]) {
+            i -= w.chunks[1];
+            m = 2;
+            if (i >= w.chunks[2]) return;
+        }
+    }
+    const uint4 wv = (m == 0 ? w.w4[0] : m == 1 ? w.w4[1] : w.w4[2])[i];
     const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
     uint32_t oa[8], ob[8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) decode8(wd[q], oa + 2 * q, ob + 2 * q);
-    uint4 *pa = m ? w.plane_a[1] : w.plane_a[0], *pb = m ? w.plane_b[1] : w.plane_b[0];
+    uint4 *pa = m == 0 ? w.plane_a[0] : m == 1 ? w.plane_a[1] : w.plane_a[2], *pb = m == 0 ? w.plane_b[0] : m == 1 ? w.plane_b[1] : w.plane_b[2];
     pa[2 * i] = make_uint4(oa[0], oa[1], oa[2], oa[3]);
     pa[2 * i + 1] = make_uint4(oa[4], oa[5], oa[6], oa[7]);
     pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
@@ -181,15 +188,19 @@ __device__ __forceinline__ void decode_block(const DecodeWork &w, long block) {
 // Workgroups of THREADS threads that a SideWork takes, and what workgroup `block` of them does (routing first: it takes
 // longest).  Routing is part of it for two experts only.
 inline long side_blocks(const SideWork &w, int threads) {
-    return (w.route.T + threads - 1) / threads + (w.decode.chunks[0] + w.decode.chunks[1] + threads - 1) / threads;
+    return (w.route.T + threads - 1) / threads + (w.decode.chunks[0] + w.decode.chunks[1] + w.decode.chunks[2] + threads - 1) / threads +
+           (w.zero.n > 0 ? 1 : 0);
 }
 template <int THREADS>
 __device__ __forceinline__ void side_block(const SideWork &w, long block) {
     const long route_blocks = (w.route.T + THREADS - 1) / THREADS;
+    const long decode_blocks = (w.decode.chunks[0] + w.decode.chunks[1] + w.decode.chunks[2] + THREADS - 1) / THREADS;
     if (block < route_blocks)
         route_scatter_block<THREADS, 2>(w.route, (int)block);
-    else
+    else if (block < route_blocks + decode_blocks)
         decode_block<THREADS>(w.decode, block - route_blocks);
+    else if (block == route_blocks + decode_blocks)
+        zero_words(w.zero);
 }
 
 }  // namespace sa
