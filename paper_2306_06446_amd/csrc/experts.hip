@@ -9,6 +9,50 @@ namespace {
 
 using namespace sa;
 
+constexpr int kPlaces = 64;                                  // of an XCD: two workgroups on each of its 32 CUs
+
+// Tiles of an XCD: `cols` of every row of tiles, of which it has every 1 / (8 >> log_cg).  (Precomputed: workgroups start with this.)
+struct XcdTiles {
+    int cols, log_rg;
+    template <class Tile>
+    static XcdTiles of(const GemmArgs &g) {
+        const int col_tiles = (g.N + Tile::BN - 1) / Tile::BN;
+        XcdTiles t{(col_tiles + g.col_groups - 1) / g.col_groups, 0};
+        while ((8 / g.col_groups) >> t.log_rg > 1) ++t.log_rg;
+        return t;
+    }
+    // rows of tiles of the fullest XCD, tiles of all XCDs
+    template <class Tile>
+    __device__ int rows(long n) const {
+        return (int)(((unsigned)((n + Tile::BM - 1) / Tile::BM) + (1u << log_rg) - 1) >> log_rg);
+    }
+    template <class Tile>
+    __device__ int blocks(long n) const { return 8 * rows<Tile>(n) * cols; }
+};
+
+// How many of the Shift expert's rows go to its higher tiles.  A CU's two workgroups share its matrix cores, so a CU with two of the higher tiles is
+// done last.  If all tiles are one round of workgroups and some CUs would have two of the higher ones: only as many of these as there are CUs.
+template <class TileS, class TileL, class TileM>
+__device__ inline long split_shift_rows(long n_shift, const XcdTiles &s, long n_mult, const XcdTiles &m, int most) {
+    const int tiles_s = s.rows<TileS>(n_shift) * s.cols, tiles_m = m.rows<TileM>(n_mult) * m.cols;
+    const long high = (long)(most << s.log_rg) * TileS::BM;              // most: rows of tiles that 32 CUs have
+    if (tiles_s <= kPlaces / 2 || tiles_s + tiles_m > kPlaces || high <= 0 || high >= n_shift) return n_shift;
+    return most * s.cols + s.rows<TileL>(n_shift - high) * s.cols + tiles_m <= kPlaces ? high : n_shift;
+}
+
+// How many of the Mult expert's rows go to its higher tiles: those of whole rounds of workgroups, if lower tiles take the other rows in one more.
+template <class TileS, class TileM, class TileL>
+__device__ inline long split_mult_rows(long n_shift, const XcdTiles &s, long n_mult, const XcdTiles &m) {
+    const int tiles_s = s.rows<TileS>(n_shift) * s.cols, rows_m = m.rows<TileM>(n_mult), all = tiles_s + rows_m * m.cols, over = all % kPlaces;
+    if (over == 0 || all < kPlaces) return n_mult;
+    int left = rows_m;                                       // rows of higher tiles
+    for (int t = over; t > 0; t -= m.cols) --left;
+    const long high = (long)(left << m.log_rg) * TileM::BM;
+    if (left <= 0) return n_mult;
+    const int places = kPlaces + all - over - (tiles_s + left * m.cols);
+    return m.rows<TileL>(n_mult - high) * m.cols <= places ? high : n_mult;
+}
+
 // Workgroups of the Shift expert first, the Mult expert's behind them.  How many tiles either has is known on the device
 // only (the routing counts): a workgroup past the end of both leaves.
 template <class TileS, class StoreS, class TileM, class StoreM, int OCC>
@@ -25,6 +69,56 @@ __global__ __launch_bounds__(256, OCC) void expert_pair_kernel(GemmArgs gs, Stor
         TileS::template run<StoreS>(gs, ss, blockIdx.x, lds);
     else
         TileM::template run<StoreM>(gm, sm, (int)(blockIdx.x - shift_blocks), lds);
+}
+
+// The same with two heights of one expert's tiles: its last rows go to the lower ones, where that fills the last round of workgroups better.
+// 12608 tokens, 70 % of them to the Shift expert: 3072 <- 768 has 840 + 480 tiles for 512 places, and 48 CUs with a sixth tile took 18 us longer
+// than the others (73 us by the tiles' own clocks; with 80 % of the Mult rows in lower tiles 67); 768 <- 3072 has 315 + 180, and the CUs with two high
+// Shift tiles were done 8 us after the others (61 and 58).  Of that the clock takes half back, the card being at its power limit: block 203.6 ->
+// 199.7 us, layer 313.1 -> 308.0; 18912 tokens, 50 % 299.7 -> 288; where no rows are taken the same as without (4728 to 15760 tokens within 0.5 %).
+// SPLIT_SHIFT: the Shift expert's (TileL: its lower tiles), else the Mult expert's.
+template <class TileS, class StoreS, class TileM, class StoreM, class TileL, bool SPLIT_SHIFT, int OCC>
+__global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, StoreS ss, XcdTiles xs, GemmArgs gm, StoreM sm, XcdTiles xm, int most) {
+    typedef typename std::conditional<SPLIT_SHIFT, StoreS, StoreM>::type StoreL;
+    constexpr int LDS_S = TileS::template lds_bytes<StoreS>(), LDS_M = TileM::template lds_bytes<StoreM>(), LDS_L = TileL::template lds_bytes<StoreL>();
+    constexpr int LDS_SM = LDS_S > LDS_M ? LDS_S : LDS_M, LDS_BYTES = LDS_SM > LDS_L ? LDS_SM : LDS_L;
+    static_assert(LDS_BYTES * OCC <= 160 * 1024, "OCC workgroups of these tiles do not fit the LDS of a CU");
+    static_assert(TileL::BN == TileS::BN && TileL::BN == TileM::BN, "one walk over the columns");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_BYTES];
+    const int32_t *rows;
+    long n_shift, n_mult;
+    resolve_rows(gs.sel, rows, n_shift);
+    resolve_rows(gm.sel, rows, n_mult);
+    const long high = SPLIT_SHIFT ? split_shift_rows<TileS, TileL, TileM>(n_shift, xs, n_mult, xm, most)
+                                  : split_mult_rows<TileS, TileM, TileL>(n_shift, xs, n_mult, xm);
+    const int s_blocks = xs.blocks<TileS>(SPLIT_SHIFT ? high : n_shift), m_blocks = xm.blocks<TileM>(SPLIT_SHIFT ? n_mult : high);
+    int b = blockIdx.x;                                      // (all of them multiples of 8)
+    if (b < s_blocks) return TileS::template run<StoreS>(gs, ss, b, lds, 0, SPLIT_SHIFT ? high : n_shift);
+    b -= s_blocks;
+    if constexpr (SPLIT_SHIFT) {
+        const int l_blocks = xs.blocks<TileL>(n_shift - high);
+        if (b < l_blocks) return TileL::template run<StoreS>(gs, ss, b, lds, high);
+        TileM::template run<StoreM>(gm, sm, b - l_blocks, lds);
+    } else {
+        if (b < m_blocks) return TileM::template run<StoreM>(gm, sm, b, lds, 0, high);
+        TileL::template run<StoreM>(gm, sm, b - m_blocks, lds, high);
+    }
+}
+
+template <class TileS, class TileM, class TileL, bool SPLIT_SHIFT, int OCC, class StoreS, class StoreM>
+int launch_split_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
+    GemmArgs s = gs, m = gm;
+    s.col_groups = TileS::col_groups(gs);
+    m.col_groups = TileM::col_groups(gm);
+    const XcdTiles xs = XcdTiles::of<TileS>(s), xm = XcdTiles::of<TileM>(m);
+    // as launch_pair_tiles, and what the lower tiles take: at most a round of workgroups more, and a row of tiles per XCD
+    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, gs.N, s.col_groups), all_m = tile_blocks<TileM>(gm.sel.max_rows, gm.N, m.col_groups);
+    const long step_s = tile_blocks<TileS>(1, gs.N, s.col_groups), step_m = tile_blocks<TileM>(1, gm.N, m.col_groups);
+    const long blocks = (all_s > all_m ? all_s : all_m) + 2 * (step_s + step_m) + 8 * kPlaces;
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
+    expert_split_kernel<TileS, StoreS, TileM, StoreM, TileL, SPLIT_SHIFT, OCC>
+        <<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, xs, m, sm, xm, kPlaces / 2 / xs.cols);
+    return check_launch(what);
 }
 
 template <class TileS, class TileM, int OCC, class StoreS, class StoreM>
@@ -91,12 +185,13 @@ int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const 
             if (lines_m) return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 128, 4>, 2>(gs, ss, gm, sm, st, what);
             return launch_pair_tiles<SliceTile<I, 2, 2, 64, 6>, SliceTile<F, 2, 2, 64, 9>, 2>(gs, ss, gm, sm, st, what);
         case PairTiles::kLarge:
-            return launch_pair_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, 2>(gs, ss, gm, sm, st, what);
+            return launch_split_tiles<NtTile<I, 256, 128, 64, 2, 1>, NtTile<F, 192, 128, 128, 2, 2>, NtTile<F, 128, 128, 128, 2, 2>, false, 2>(gs, ss, gm, sm, st, what);
         case PairTiles::kLongRows:
             if constexpr (StoreS::kScatter)                  // a second layer (the first one writes a hidden matrix)
                 if (gs.a_block)
-                    return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1, true>, NtTile<F, 128, 128, 64, 4, 1, true>, 2>(gs, ss, gm, sm, st, what);
-            return launch_pair_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 4, 1>, 2>(gs, ss, gm, sm, st, what);
+                    return launch_split_tiles<NtTile<I, 192, 128, 64, 2, 1, true>, NtTile<F, 128, 128, 64, 4, 1, true>, NtTile<I, 128, 128, 64, 3, 1, true>, true, 2>(
+                        gs, ss, gm, sm, st, what);
+            return launch_split_tiles<NtTile<I, 192, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 4, 1>, NtTile<I, 128, 128, 64, 3, 1>, true, 2>(gs, ss, gm, sm, st, what);
         case PairTiles::kFine:
             return launch_pair_tiles<NtTile<I, 128, 64, 64, 3, 1>, NtTile<F, 64, 128, 128, 2, 2>, 3>(gs, ss, gm, sm, st, what);
         case PairTiles::kMiddle: break;

@@ -253,7 +253,7 @@ struct NtShape {
 };
 
 template <class T, int BM, int BN, int SB, int NS, int LS, bool BLOCKED, class Store>
-__device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
+__device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &store, int block, uint8_t *lds, long first_row, long end_row) {
     using S = NtShape<T, BM, BN, SB, NS, Store>;
     constexpr int kStageBytes = SB;                     // bytes of K per stage and row
     constexpr int kChunksPerRow = SB / 16;              // 16-byte chunks per LDS row
@@ -278,6 +278,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     const int32_t *rows;
     long n_rows;
     resolve_rows(g.sel, rows, n_rows);
+    n_rows = n_rows < end_row ? n_rows : end_row;
     // Workgroups are handed to the 8 XCDs round-robin by their linear id, and each XCD has its own
     // 4 MiB L2.  The 8 XCDs form a (8 / col_groups) x col_groups grid over the output: an XCD owns
     // every (8 / col_groups)-th row tile and every col_groups-th column tile, and walks them row
@@ -289,7 +290,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     const int xcd = block & 7, slot = block >> 3;
     const long row_tile = (long)(slot / cols_per_group) * rg + xcd / cg;
     const int col_tile = (slot % cols_per_group) * cg + xcd % cg;
-    const long m0 = row_tile * BM;
+    const long m0 = first_row + row_tile * BM;
     if (m0 >= n_rows || col_tile >= col_tiles) return;
     const int n0 = col_tile * BN;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -312,7 +313,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
         long m = m0 + r;
         m = m < n_rows ? m : n_rows - 1;
         const long src = (g.gather_a && rows) ? (long)rows[m] : m;
-        a_src[i] = static_cast<const uint8_t *>(g.a) + (size_t)src * a_row_bytes + c * 16;
+        a_src[i] = static_cast<const uint8_t *>(g.a) + (size_t)src * a_row_bytes + (BLOCKED ? (size_t)(c / 4) * g.a_block + c % 4 * 16 : c * 16);
     }
     // The furthest stage offset at which this lane's chunk still lies inside an A row (64-byte stages: every load of
     // a lane has the same physical chunk, rows 16 apart swizzle alike).  Beyond it the lane re-reads the row's last
@@ -669,13 +670,13 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
 // A tile shape as launch_tile and the kernels below take it.
 template <class T, int BM_, int BN_, int SB, int NS, int LS, bool BLOCKED = false>
 struct NtTile {
-    static_assert(!BLOCKED || SB == 64, "columns of a stage");
     static constexpr int BM = BM_, BN = BN_;
     template <class Store>
     static constexpr int lds_bytes() { return NtShape<T, BM, BN, SB, NS, Store>::LDS_BYTES; }
     template <class Store>
-    __device__ static __forceinline__ void run(const GemmArgs &g, const Store &store, int block, uint8_t *lds) {
-        nt_gemm_tile<T, BM, BN, SB, NS, LS, BLOCKED, Store>(g, store, block, lds);
+    __device__ static __forceinline__ void run(const GemmArgs &g, const Store &store, int block, uint8_t *lds, long first_row = 0,
+                                               long end_row = 0x7fffffffL) {       // of the selected rows, those that a launch gives to these tiles
+        nt_gemm_tile<T, BM, BN, SB, NS, LS, BLOCKED, Store>(g, store, block, lds, first_row, end_row);
     }
     // The fewest column groups whose share of the B planes stays resident in a 4 MiB L2 next to
     // the A rows streaming through it.  (Fewer groups fetch fewer bytes when A is the larger operand,
