@@ -583,37 +583,56 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (tile0 + tm >= tile_end) continue;
-            // a row's address is the tile's (the same in every lane) plus this lane's offset in it
+            // a row's address is the tile's (the same in every lane) plus this lane's offset in it: no more than 4 rows of H * DV floats,
+            // with B * H < 2^20 heads 2^31 bytes
             const size_t tile_at = (((size_t)b * Nq + (size_t)(tile0 + tm) * 32) * H + h) * DV + c0;
+            int out_lane = lane;
+            asm volatile("" : "+v"(out_lane));     // (made here: no registers for it beside the products)
+            const int m = out_lane & 31, kg = out_lane >> 5;
             const uint32_t row_step = (uint32_t)H * DV, lane_at = (uint32_t)(4 * kg) * row_step + m;
-            auto store_rows = [&](auto whole_c) {
+            // FORMS: which of the three leave (1 fp32, 2 int8, 4 fp16), or -1: asked for in every row.  Every wavefront of a launch runs this for
+            // the first time, and few have more than one tile: what its instructions take to arrive counts.  So those of the common forms
+            // have no others between them, and a row's address is made from the row's before, where it is used.  All made ahead of the tiles, as
+            // the compiler does with tile_at + row * row_step, they were 300 instructions and most of the registers: Q(K^T V) of 32 x 3136
+            // queries x 1 head x 64 bits 8.0 -> 6.6 us, of 1 x 4 x 16384 x 256 bits 11.2 -> 10.0, of 8 x 4 x 16384 x 256 bits 59.7 -> 49.3,
+            // {0,1} codes of the first 11.8 -> 10.0, both products of 1 x 3 x 197 x 64 bits 7.9 -> 7.4.
+            auto store_rows = [&](auto whole_c, auto forms_c) {
                 constexpr bool WHOLE = decltype(whole_c)::value;      // all 32 queries exist
+                constexpr int FORMS = decltype(forms_c)::value;
+                const bool floats = FORMS < 0 ? f.out != nullptr : (FORMS & 1) != 0, bytes = FORMS < 0 ? f.xq != nullptr : (FORMS & 2) != 0,
+                           halves = FORMS < 0 ? f.xh != nullptr : (FORMS & 4) != 0;
+                size_t at = tile_at;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int row = 8 * (r >> 2) + (r & 3);           // + 4 kg
+                    if (r > 0) at += (size_t)(r % 4 ? 1 : 5) * row_step;
+                    asm volatile("" : "+s"(at));
                     // (+-1: see code_pair.  __shfl, which allows for other widths, took 4 registers more than 256-bit codes leave.)
                     const float fr = ZO ? __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(16 * kg + 4 * row, __builtin_bit_cast(int, factor[tm])))
                                         : -f.scale;
                     if (WHOLE || (tile0 + tm) * 32 + row + 4 * kg < Nq) {
-                        const size_t at = tile_at + (size_t)row * row_step;
 #pragma unroll
                         for (int j = 0; j < JT; ++j) {
                             const float val = fr * acc[tm][j][r];
-                            if (f.out) {
-                                float *dst = f.out + at + j * 32 + lane_at;
+                            if (floats) {
+                                float *dst = reinterpret_cast<float *>(reinterpret_cast<char *>(f.out + at + j * 32) + lane_at * 4);
                                 if (ZO) *dst = val;           // the convolution that follows reads it
                                 else __builtin_nontemporal_store(val, dst);
                             }
-                            if (f.xq) (f.xq + at + j * 32)[lane_at] = (int8_t)sa::requant_byte(val * f.act_inv_scale);
-                            if (f.xh) (f.xh + at + j * 32)[lane_at] = (_Float16)val;
+                            if (bytes) (f.xq + at + j * 32)[lane_at] = (int8_t)sa::requant_byte(val * f.act_inv_scale);
+                            if (halves) *reinterpret_cast<_Float16 *>(reinterpret_cast<char *>(f.xh + at + j * 32) + lane_at * 2) = (_Float16)val;
                         }
                     }
                 }
             };
-            if ((tile0 + tm) * 32 + 32 <= Nq)
-                store_rows(std::true_type{});
-            else
-                store_rows(std::false_type{});
+            if (__builtin_expect((tile0 + tm) * 32 + 32 <= Nq, 1)) {
+                if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{});
+                else if (!f.out && !f.xh) store_rows(std::true_type{}, std::integral_constant<int, 2>{});
+                else if (!f.xh) store_rows(std::true_type{}, std::integral_constant<int, 3>{});
+                else store_rows(std::true_type{}, std::integral_constant<int, -1>{});
+            } else {
+                store_rows(std::false_type{}, std::integral_constant<int, -1>{});
+            }
         }
     }
 }
