@@ -15,6 +15,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off",                      # only explicit fma() fuses: hash bits are order-defined
+    # a kernel's first arguments come with its wavefronts instead of by a load that all else waits for: block of 12608 x 768
+    # 195.8 -> 193.3 us, 32 x 3136 tokens' attention 20.84 -> 20.74
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
