@@ -11,16 +11,10 @@ using namespace sa;
 
 constexpr int kPlaces = 64;                                  // of an XCD: two workgroups on each of its 32 CUs
 
-// Tiles of an XCD: `cols` of every row of tiles, of which it has every 1 / (8 >> log_cg).  (Precomputed: workgroups start with this.)
+// Tiles of an XCD: `cols` of every row of tiles, of which it has one of 1 << log_rg.
 struct XcdTiles {
     int cols, log_rg;
-    template <class Tile>
-    static XcdTiles of(const GemmArgs &g) {
-        const int col_tiles = (g.N + Tile::BN - 1) / Tile::BN;
-        XcdTiles t{(col_tiles + g.col_groups - 1) / g.col_groups, 0};
-        while ((8 / g.col_groups) >> t.log_rg > 1) ++t.log_rg;
-        return t;
-    }
+    __device__ explicit XcdTiles(const GemmArgs &g) : cols(g.cols_per_group), log_rg(3 - g.log_groups) {}
     // rows of tiles of the fullest XCD, tiles of all XCDs
     template <class Tile>
     __device__ int rows(long n) const {
@@ -64,11 +58,11 @@ __global__ __launch_bounds__(256, OCC) void expert_pair_kernel(GemmArgs gs, Stor
     const int32_t *rows;
     long n_shift;
     resolve_rows(gs.sel, rows, n_shift);
-    const long shift_blocks = tile_blocks<TileS>(n_shift, gs.N, gs.col_groups);      // a multiple of 8
-    if ((long)blockIdx.x < shift_blocks)
+    const int shift_blocks = XcdTiles(gs).blocks<TileS>(n_shift);      // a multiple of 8
+    if ((int)blockIdx.x < shift_blocks)
         TileS::template run<StoreS>(gs, ss, blockIdx.x, lds);
     else
-        TileM::template run<StoreM>(gm, sm, (int)(blockIdx.x - shift_blocks), lds);
+        TileM::template run<StoreM>(gm, sm, (int)blockIdx.x - shift_blocks, lds);
 }
 
 // The same with two heights of one expert's tiles: its last rows go to the lower ones, where that fills the last round of workgroups better.
@@ -78,7 +72,7 @@ __global__ __launch_bounds__(256, OCC) void expert_pair_kernel(GemmArgs gs, Stor
 // 199.7 us, layer 313.1 -> 308.0; 18912 tokens, 50 % 299.7 -> 288; where no rows are taken the same as without (4728 to 15760 tokens within 0.5 %).
 // SPLIT_SHIFT: the Shift expert's (TileL: its lower tiles), else the Mult expert's.
 template <class TileS, class StoreS, class TileM, class StoreM, class TileL, bool SPLIT_SHIFT, int OCC>
-__global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, StoreS ss, XcdTiles xs, GemmArgs gm, StoreM sm, XcdTiles xm, int most) {
+__global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, StoreS ss, GemmArgs gm, StoreM sm, int most) {
     typedef typename std::conditional<SPLIT_SHIFT, StoreS, StoreM>::type StoreL;
     constexpr int LDS_S = TileS::template lds_bytes<StoreS>(), LDS_M = TileM::template lds_bytes<StoreM>(), LDS_L = TileL::template lds_bytes<StoreL>();
     constexpr int LDS_SM = LDS_S > LDS_M ? LDS_S : LDS_M, LDS_BYTES = LDS_SM > LDS_L ? LDS_SM : LDS_L;
@@ -89,6 +83,7 @@ __global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, Sto
     long n_shift, n_mult;
     resolve_rows(gs.sel, rows, n_shift);
     resolve_rows(gm.sel, rows, n_mult);
+    const XcdTiles xs(gs), xm(gm);
     const long high = SPLIT_SHIFT ? split_shift_rows<TileS, TileL, TileM>(n_shift, xs, n_mult, xm, most)
                                   : split_mult_rows<TileS, TileM, TileL>(n_shift, xs, n_mult, xm);
     const int s_blocks = xs.blocks<TileS>(SPLIT_SHIFT ? high : n_shift), m_blocks = xm.blocks<TileM>(SPLIT_SHIFT ? n_mult : high);
@@ -108,27 +103,26 @@ __global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, Sto
 template <class TileS, class TileM, class TileL, bool SPLIT_SHIFT, int OCC, class StoreS, class StoreM>
 int launch_split_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
     GemmArgs s = gs, m = gm;
-    s.col_groups = TileS::col_groups(gs);
-    m.col_groups = TileM::col_groups(gm);
-    const XcdTiles xs = XcdTiles::of<TileS>(s), xm = XcdTiles::of<TileM>(m);
+    s.share_out(TileS::BN, TileS::col_groups(gs));
+    m.share_out(TileM::BN, TileM::col_groups(gm));
     // as launch_pair_tiles, and what the lower tiles take: at most a round of workgroups more, and a row of tiles per XCD
-    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, gs.N, s.col_groups), all_m = tile_blocks<TileM>(gm.sel.max_rows, gm.N, m.col_groups);
-    const long step_s = tile_blocks<TileS>(1, gs.N, s.col_groups), step_m = tile_blocks<TileM>(1, gm.N, m.col_groups);
+    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
+    const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
     const long blocks = (all_s > all_m ? all_s : all_m) + 2 * (step_s + step_m) + 8 * kPlaces;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
     expert_split_kernel<TileS, StoreS, TileM, StoreM, TileL, SPLIT_SHIFT, OCC>
-        <<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, xs, m, sm, xm, kPlaces / 2 / xs.cols);
+        <<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm, kPlaces / 2 / s.cols_per_group);
     return check_launch(what);
 }
 
 template <class TileS, class TileM, int OCC, class StoreS, class StoreM>
 int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
     GemmArgs s = gs, m = gm;
-    s.col_groups = TileS::col_groups(gs);
-    m.col_groups = TileM::col_groups(gm);
+    s.share_out(TileS::BN, TileS::col_groups(gs));
+    m.share_out(TileM::BN, TileM::col_groups(gm));
     // the rows of both add up to max_rows: all on either side, and one more row of tiles per XCD where the other side starts
-    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, gs.N, s.col_groups), all_m = tile_blocks<TileM>(gm.sel.max_rows, gm.N, m.col_groups);
-    const long step_s = tile_blocks<TileS>(1, gs.N, s.col_groups), step_m = tile_blocks<TileM>(1, gm.N, m.col_groups);
+    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
+    const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
     const long blocks = (all_s > all_m ? all_s : all_m) + step_s + step_m;
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
     expert_pair_kernel<TileS, StoreS, TileM, StoreM, OCC><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm);

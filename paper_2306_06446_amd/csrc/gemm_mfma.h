@@ -82,7 +82,25 @@ struct GemmArgs {
     RowSel sel;             // which rows of A / of the scattered output
     bool gather_a;          // A rows are sel.rows[m] (else compact m)
     int K, N;               // K: extent of the contraction, a whole number of 64-byte stages; row length of the B planes
-    int col_groups = 1;     // 1, 2, 4 or 8: set by the launcher
+    // How the tiles are shared out to the XCDs (see tile_of), set by the launcher with share_out.  Kernels start with this: made there
+    // from col_groups, divisions one after the other came before every tile's first load (two experts in one launch: 576 instructions, now 130;
+    // 12608 x 768 <- 768 as a Mult and a Shift expert 30.35 -> 30.14 us, 12608 x 1536 <- 384 and back 50.1 -> 49.6).
+    int log_groups = 0, col_tiles = 0, cols_per_group = 1;
+    FastDiv by_cols{1};
+    void share_out(int BN, int col_groups) {
+        for (log_groups = 0; 1 << log_groups < col_groups;) ++log_groups;
+        col_tiles = (N + BN - 1) / BN;
+        cols_per_group = (col_tiles + col_groups - 1) / col_groups;
+        by_cols = FastDiv((uint32_t)cols_per_group);
+    }
+    // Workgroups are handed to the 8 XCDs round-robin by their linear id, and each XCD has its own 4 MiB L2.  The 8 XCDs form a (8 /
+    // col_groups) x col_groups grid over the output (col_groups = 1, 2, 4 or 8): an XCD owns every (8 / col_groups)-th row tile and every
+    // col_groups-th column tile, and walks them row tile by row tile.
+    __device__ __forceinline__ void tile_of(int block, int &row_tile, int &col_tile) const {
+        const int xcd = block & 7, slot = block >> 3, row = (int)by_cols((uint32_t)slot);
+        row_tile = (row << (3 - log_groups)) + (xcd >> log_groups);
+        col_tile = ((slot - row * cols_per_group) << log_groups) + (xcd & ((1 << log_groups) - 1));
+    }
     // A rows may be shorter than K (int8 only, 64-byte stages): a_valid elements, a multiple of 16 bytes, at a row
     // pitch of a_ld elements; 0 = K.  The B planes must then hold zeros from a_valid on: the kernel multiplies
     // those zeros with bytes it re-reads from inside the row, so it never reads past a row's end.
@@ -279,19 +297,12 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     long n_rows;
     resolve_rows(g.sel, rows, n_rows);
     n_rows = n_rows < end_row ? n_rows : end_row;
-    // Workgroups are handed to the 8 XCDs round-robin by their linear id, and each XCD has its own
-    // 4 MiB L2.  The 8 XCDs form a (8 / col_groups) x col_groups grid over the output: an XCD owns
-    // every (8 / col_groups)-th row tile and every col_groups-th column tile, and walks them row
-    // tile by row tile.  Its share of the B planes (chosen by the host to fit the L2) stays
-    // resident, and each row tile of A is fetched by col_groups L2s only.
-    const int col_tiles = (g.N + BN - 1) / BN;
-    const int cg = g.col_groups, rg = 8 / cg;
-    const int cols_per_group = (col_tiles + cg - 1) / cg;
-    const int xcd = block & 7, slot = block >> 3;
-    const long row_tile = (long)(slot / cols_per_group) * rg + xcd / cg;
-    const int col_tile = (slot % cols_per_group) * cg + xcd % cg;
-    const long m0 = first_row + row_tile * BM;
-    if (m0 >= n_rows || col_tile >= col_tiles) return;
+    // An XCD's share of the B planes (chosen by the host to fit the L2) stays resident, and each row tile of A is fetched by
+    // col_groups L2s only.
+    int row_tile, col_tile;
+    g.tile_of(block, row_tile, col_tile);
+    const long m0 = first_row + (long)row_tile * BM;
+    if (m0 >= n_rows || col_tile >= g.col_tiles) return;
     const int n0 = col_tile * BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -699,10 +710,10 @@ struct NtTile {
 
 // Workgroups that cover n_rows x N with this tile (a multiple of 8: one share per XCD).
 template <class Tile>
-__host__ __device__ inline long tile_blocks(long n_rows, int N, int col_groups) {
-    const long row_tiles = (n_rows + Tile::BM - 1) / Tile::BM, col_tiles = (N + Tile::BN - 1) / Tile::BN;
-    const int rg = 8 / col_groups;
-    return 8 * ((row_tiles + rg - 1) / rg) * ((col_tiles + col_groups - 1) / col_groups);
+__host__ __device__ inline long tile_blocks(long n_rows, const GemmArgs &g) {
+    const long row_tiles = (n_rows + Tile::BM - 1) / Tile::BM;
+    const int log_rg = 3 - g.log_groups;
+    return 8 * ((row_tiles + (1 << log_rg) - 1) >> log_rg) * g.cols_per_group;
 }
 
 template <class Tile, int OCC, class Store>
@@ -716,8 +727,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_kernel(GemmArgs g, Store store)
 template <class Tile, int OCC, class Store>
 int launch_tile(const GemmArgs &g, const Store &store, hipStream_t st, const char *what) {
     GemmArgs ga = g;
-    ga.col_groups = Tile::col_groups(g);
-    const long blocks = tile_blocks<Tile>(g.sel.max_rows, g.N, ga.col_groups);
+    ga.share_out(Tile::BN, Tile::col_groups(g));
+    const long blocks = tile_blocks<Tile>(g.sel.max_rows, ga);
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
     gemm_kernel<Tile, OCC, Store><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(ga, store);
     return check_launch(what);

@@ -54,14 +54,10 @@ __device__ __forceinline__ void slice_gemm_tile(const GemmArgs &g, const Store &
     long n_rows;
     resolve_rows(g.sel, rows, n_rows);
     // the same XCD-aware walk over the output as in nt_gemm_tile
-    const int col_tiles = (g.N + S::BN - 1) / S::BN;
-    const int cg = g.col_groups, rg = 8 / cg;
-    const int cols_per_group = (col_tiles + cg - 1) / cg;
-    const int xcd = block & 7, slot = block >> 3;
-    const long row_tile = (long)(slot / cols_per_group) * rg + xcd / cg;
-    const int col_tile = (slot % cols_per_group) * cg + xcd % cg;
-    const long m0 = row_tile * S::BM;
-    if (m0 >= n_rows || col_tile >= col_tiles) return;
+    int row_tile, col_tile;
+    g.tile_of(block, row_tile, col_tile);
+    const long m0 = (long)row_tile * S::BM;
+    if (m0 >= n_rows || col_tile >= g.col_tiles) return;
     const int n0 = col_tile * S::BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
