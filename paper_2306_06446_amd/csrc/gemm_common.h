@@ -63,11 +63,17 @@ __device__ inline uint32_t requant_index(int32_t acc, float rq_finite) {
 // requant_code as the byte of the int8 code, for a float that may be anything, in three vector operations and a mask: v_cvt_i32_f32 makes
 // 0 of NaN and holds what is beyond 32 bits at their ends, which C++ leaves open.  (Clamped and rounded as floats, NaN took a compare and
 // a select more and a wait between them: Q(K^T V) of 8 x 4 x 16384 queries x 256 bits with fp32 and int8 outputs 49.3 -> 45.2 us.)
-__device__ inline uint32_t requant_byte(float t) {
+__device__ inline int32_t requant_clamped(float t) {
     int32_t i;
     asm("v_cvt_i32_f32 %0, %1" : "=v"(i) : "v"(__builtin_rintf(t)));
     i = i < -127 ? -127 : i;
-    return (uint32_t)(i > 127 ? 127 : i) & 0xFFu;
+    return i > 127 ? 127 : i;
+}
+__device__ inline uint32_t requant_byte(float t) { return (uint32_t)requant_clamped(t) & 0xFFu; }
+// Of four floats, the first one's in the lowest byte.
+__device__ inline uint32_t requant_bytes(float a, float b, float c, float d) {
+    const uint32_t lower = __builtin_amdgcn_perm((uint32_t)requant_clamped(b), (uint32_t)requant_clamped(a), 0x0C0C0400u);
+    return lower | __builtin_amdgcn_perm((uint32_t)requant_clamped(d), (uint32_t)requant_clamped(c), 0x04000C0Cu);
 }
 
 // NaN -> 0 (every product is NaN -> code 0, as 0 * acc), +-Inf -> +-FLT_MAX (same clamped codes; 0 * acc = 0 -> code 0,

@@ -201,8 +201,7 @@ __device__ inline void write_outputs(v16f (&acc)[DV / 32], float den, uint8_t *s
 #pragma unroll
                     for (int e4 = 0; e4 < 4; ++e4) {
                         const float4 val = *reinterpret_cast<const float4 *>(stage + r * PITCH + (c + 4 * e4) * 4);
-                        w[e4] = sa::requant_byte(val.x * act_inv_scale) | (sa::requant_byte(val.y * act_inv_scale) << 8) |
-                                (sa::requant_byte(val.z * act_inv_scale) << 16) | (sa::requant_byte(val.w * act_inv_scale) << 24);
+                        w[e4] = sa::requant_bytes(val.x * act_inv_scale, val.y * act_inv_scale, val.z * act_inv_scale, val.w * act_inv_scale);
                     }
                     if (q_half0 + r < Nq)
                         *reinterpret_cast<uint4 *>(xq + tile_at + (size_t)(16 * half + r) * row_elems + c) =
@@ -382,7 +381,7 @@ template <int DV, int W>
 __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
     const uint64_t *__restrict__ q_codes, const uint64_t *__restrict__ k_codes, const float *__restrict__ v,
     float *__restrict__ out, int H, int Nq, int Nk, int q_chunks, float c2, int8_t *__restrict__ xq,
-    _Float16 *__restrict__ xh, float act_inv_scale, long n_units, int tiles) {
+    _Float16 *__restrict__ xh, float act_inv_scale, int n_units, int tiles, sa::FastDiv by_chunks, sa::FastDiv by_h) {
     constexpr int JT = DV / 32;
     constexpr int NBITS = W * 64;
     constexpr int RPI = 1024 / (DV * 4);           // V rows one wavefront-wide 16-byte load brings
@@ -403,9 +402,10 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
 
     // Chunk at key j of unit u -> raw_s and kc_s[buf].  Rows and code bytes past the last key are re-reads of
     // the last valid ones (never used: the conversion zeroes those V rows, the last step masks those keys).
-    auto issue_chunk = [&](long u, int j, int buf) {
-        const long bh = u / q_chunks;
-        const int b = (int)(bh / H), h = (int)(bh % H);
+    auto issue_chunk = [&](int u, int j, int buf) {
+        // (As 64-bit divisions, three or four a unit, these were a third of the kernel's instructions, 393 of them before its first load: 64 x 12
+        // heads x 197 tokens x 128 bits x 64 32.5 -> 30.1 us, 7 x 12 heads x 64 bits 10.2 -> 9.0.)
+        const int bh = (int)by_chunks((uint32_t)u), b = (int)by_h((uint32_t)bh), h = bh - b * H;
         const int n = min(kKeyChunk, Nk - j);
         const int n_pad = (n + 15) & ~15;
         const int v_instr = (n_pad + RPI - 1) / RPI;
@@ -423,9 +423,8 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
             sa::direct_load_4(cg + off, kc_base + buf * (kKeyChunk * W * 8) + k * 256);
         }
     };
-    auto load_query = [&](long u, uint32_t (&dst)[W]) {
-        const long bh = u / q_chunks;
-        const int chunk = (int)(u % q_chunks);
+    auto load_query = [&](int u, uint32_t (&dst)[W]) {
+        const int bh = (int)by_chunks((uint32_t)u), chunk = u - bh * q_chunks;
         int of_lane = lane;
         asm volatile("" : "+v"(of_lane));
         const int qi = min((chunk * tiles + wave) * 32 + (of_lane & 31), Nq - 1);
@@ -434,7 +433,7 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
         for (int w = 0; w < W; ++w) dst[w] = from[w];
     };
 
-    long u = blockIdx.x;
+    int u = blockIdx.x;
     if (u >= n_units) return;
     issue_chunk(u, 0, 0);
     uint32_t qn[W];
@@ -545,7 +544,7 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
             }
         }
         __syncthreads();                             // planes ready; raw_s is free again
-        long u2 = u;
+        int u2 = u;
         int j2 = j0 + kKeyChunk;
         if (j2 >= Nk) {
             u2 = u + gridDim.x;
@@ -572,13 +571,13 @@ __global__ __launch_bounds__(kMaxWaves *kWave, 4) void hamming_pipe_kernel(
             }
         }
         if (j2 == 0) {                               // last chunk of the unit
-            const long bh = u / q_chunks;
+            const int bh = (int)by_chunks((uint32_t)u), b = (int)by_h((uint32_t)bh);
             __syncthreads();                         // every wavefront is through its steps: the planes become staging rows
             int out_lane = lane;
             asm volatile("" : "+v"(out_lane));       // the outputs' addresses are made here, not kept through the steps
             if (wave < tiles)
                 write_outputs<DV>(acc, den, reinterpret_cast<uint8_t *>(&vt_s[0][0]) + wave * stage_bytes_per_wave<DV>(), out, xq, xh,
-                                  act_inv_scale, (int)(bh / H), (int)(bh % H), H, Nq, ((int)(u % q_chunks) * tiles + wave) * 32, out_lane);
+                                  act_inv_scale, b, bh - b * H, H, Nq, ((u - bh * q_chunks) * tiles + wave) * 32, out_lane);
 #pragma unroll
             for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
@@ -841,12 +840,14 @@ void launch_hamming(const Launch &L) {
         // Not fewer than ROUNDS of what the pipelined kernel holds (2048 x 32 x 128 bits x 32 10.3, 11.5; 512 x 17 x 128 bits x 64 6.4, 6.8), nor
         // 256 bits, whose popcounts take long (1024 x 17 x 64 12.5, 12.7; 4096 x 49 x 32 29, 34).
         constexpr int ROUNDS = W * (DV == 64 ? 1 : 2);
-        const bool pipeline = L.pipeline && !(W <= 2 && L.Nk <= 32 && L.n_units >= ROUNDS * pipeline_slots<DV, W>((int)L.block.x));
+        // (Units are counted in 32 bits.)
+        const bool pipeline = L.pipeline && L.n_units < (1L << 30) && !(W <= 2 && L.Nk <= 32 && L.n_units >= ROUNDS * pipeline_slots<DV, W>((int)L.block.x));
         if (pipeline) {
             const long slots = pipeline_slots<DV, W>((int)L.block.x);
             const long wgs = L.n_units < slots ? L.n_units : slots;
             hamming_pipe_kernel<DV, W><<<dim3((unsigned)wgs), L.block, 0, L.st>>>(L.q, L.k, L.v, L.out, L.H, L.Nq, L.Nk, L.q_chunks,
-                                                                                 L.c2, L.xq, L.xh, L.act_inv_scale, L.n_units, L.tiles);
+                                                                                 L.c2, L.xq, L.xh, L.act_inv_scale, (int)L.n_units, L.tiles,
+                                                                                 sa::FastDiv((uint32_t)L.q_chunks), sa::FastDiv((uint32_t)L.H));
             return;
         }
     }

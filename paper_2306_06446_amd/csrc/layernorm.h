@@ -69,8 +69,7 @@ __device__ inline void normalise(const float4 &v, float mean, float rstd, const 
 }
 
 __device__ inline uint32_t codes_of(const float (&y)[4], float inv_scale) {
-    return requant_byte(y[0] * inv_scale) | (requant_byte(y[1] * inv_scale) << 8) | (requant_byte(y[2] * inv_scale) << 16) |
-           (requant_byte(y[3] * inv_scale) << 24);
+    return requant_bytes(y[0] * inv_scale, y[1] * inv_scale, y[2] * inv_scale, y[3] * inv_scale);
 }
 
 }  // namespace sa
