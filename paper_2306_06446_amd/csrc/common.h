@@ -36,7 +36,7 @@ struct FastDiv {
         shift = 31 + s;
         mul = (uint32_t)(((1ull << shift) + d - 1) / d);
     }
-    __device__ inline uint32_t operator()(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+    __host__ __device__ inline uint32_t operator()(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
 };
 
 // Resolves an sa_rows descriptor inside a kernel (all lanes get the same values).

@@ -18,7 +18,7 @@ struct XcdTiles {
     // rows of tiles of the fullest XCD, tiles of all XCDs
     template <class Tile>
     __device__ int rows(long n) const {
-        return (int)(((unsigned)((n + Tile::BM - 1) / Tile::BM) + (1u << log_rg) - 1) >> log_rg);
+        return (int)((((uint32_t)n + Tile::BM - 1) / Tile::BM + (1u << log_rg) - 1) >> log_rg);
     }
     template <class Tile>
     __device__ int blocks(long n) const { return 8 * rows<Tile>(n) * cols; }
@@ -98,6 +98,42 @@ __global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, Sto
         if (b < m_blocks) return TileM::template run<StoreM>(gm, sm, b, lds, 0, high);
         TileL::template run<StoreM>(gm, sm, b - m_blocks, lds, high);
     }
+}
+
+// Both experts' tiles one round of workgroups: the Shift expert's last rows in tiles of half the height (even_rows).
+template <class TileS, class StoreS, class TileM, class StoreM, class TileL, int OCC>
+__global__ __launch_bounds__(256, OCC) void expert_even_kernel(GemmArgs gs, StoreS ss, GemmArgs gm, StoreM sm) {
+    constexpr int LDS_S = TileS::template lds_bytes<StoreS>(), LDS_M = TileM::template lds_bytes<StoreM>(), LDS_L = TileL::template lds_bytes<StoreS>();
+    constexpr int LDS_SM = LDS_S > LDS_M ? LDS_S : LDS_M, LDS_BYTES = LDS_SM > LDS_L ? LDS_SM : LDS_L;
+    static_assert(LDS_BYTES * OCC <= 160 * 1024, "OCC workgroups of these tiles do not fit the LDS of a CU");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_BYTES];
+    const int32_t *rows;
+    long n_shift, n_mult;
+    resolve_rows(gs.sel, rows, n_shift);
+    resolve_rows(gm.sel, rows, n_mult);
+    const XcdTiles xs(gs), xm(gm);
+    const int m_tiles = xm.rows<TileM>(n_mult) * xm.cols, m_blocks = 8 * m_tiles;
+    const long high = even_rows<TileS::BM, OCC>((uint32_t)n_shift, gs, m_tiles);
+    int b = blockIdx.x;                                      // (all of them multiples of 8)
+    const int s_blocks = xs.blocks<TileS>(high);
+    if (b < s_blocks) return TileS::template run<StoreS>(gs, ss, b, lds, 0, high);
+    b -= s_blocks;
+    if (b < m_blocks) return TileM::template run<StoreM>(gm, sm, b, lds);
+    TileL::template run<StoreS>(gs, ss, b - m_blocks, lds, high);
+}
+
+template <class TileS, class TileM, class TileL, int OCC, class StoreS, class StoreM>
+int launch_even_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
+    GemmArgs s = gs, m = gm;
+    s.share_out(TileS::BN, TileS::col_groups(gs));
+    m.share_out(TileM::BN, TileM::col_groups(gm));
+    // as launch_pair_tiles, and the lower tiles: at most one a CU and two for each of a row of tiles (even_rows)
+    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
+    const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
+    const long blocks = (all_s > all_m ? all_s : all_m) + 3 * step_s + step_m + 256;
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
+    expert_even_kernel<TileS, StoreS, TileM, StoreM, TileL, OCC><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm);
+    return check_launch(what);
 }
 
 template <class TileS, class TileM, class TileL, bool SPLIT_SHIFT, int OCC, class StoreS, class StoreM>
@@ -190,7 +226,7 @@ int launch_pair(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const 
             return launch_pair_tiles<NtTile<I, 128, 64, 64, 3, 1>, NtTile<F, 64, 128, 128, 2, 2>, 3>(gs, ss, gm, sm, st, what);
         case PairTiles::kMiddle: break;
     }
-    return launch_pair_tiles<NtTile<I, 128, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 3, 1>, 3>(gs, ss, gm, sm, st, what);
+    return launch_even_tiles<NtTile<I, 128, 128, 64, 2, 1>, NtTile<F, 128, 128, 64, 3, 1>, NtTile<I, 64, 128, 64, 2, 1>, 3>(gs, ss, gm, sm, st, what);
 }
 
 GemmArgs args(const void *a, bool gather, const void *b0, const void *b1, const RowSel &sel, int K, int N) {

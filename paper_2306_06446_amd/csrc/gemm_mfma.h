@@ -734,6 +734,47 @@ int launch_tile(const GemmArgs &g, const Store &store, hipStream_t st, const cha
     return check_launch(what);
 }
 
+// How many rows go to tiles of BM rows where tiles of half of them take the others: those of as many tiles as every CU has at least, if all
+// tiles are one round of workgroups (OCC a CU, which share its matrix cores) and no more than every other CU would have one more.  The CUs
+// then end half a tile apart instead of a whole one.  rest: tiles of an XCD that other rows have.  All rows: no gain.
+template <int BM, int OCC>
+__host__ __device__ inline uint32_t even_rows(uint32_t n_rows, const GemmArgs &g, uint32_t rest) {
+    constexpr uint32_t CUS = 32;                             // of an XCD
+    const uint32_t log_rg = 3 - g.log_groups, cols = g.cols_per_group;
+    auto rows_of = [&](uint32_t n, uint32_t bm) { return ((n + bm - 1) / bm + (1u << log_rg) - 1) >> log_rg; };
+    const uint32_t all = rows_of(n_rows, BM) * cols + rest, each = all / CUS * CUS;
+    if (all > OCC * CUS || all - each - 1 >= CUS / 2 || each <= rest) return n_rows;
+    const uint32_t left = g.by_cols(each - rest), high = (left << log_rg) * BM;          // left: rows of tiles that stay
+    if (left == 0 || high >= n_rows) return n_rows;
+    const uint32_t low = rows_of(n_rows - high, BM / 2) * cols, room = each - rest - left * cols;
+    return low <= CUS + 2 * room && rest + left * cols + low <= OCC * CUS ? high : n_rows;
+}
+
+// The last rows in tiles of half the height (even_rows).  us, without and with: packed weights 12608 x 384 <- 1536 22.7, 20.8, 9000 x 512 <- 1024
+// 16.6, 15.1, 25088 x 192 <- 1024 16.8, 15.3, 12608 x 384 <- 384 8.7, 8.3; prepared, with a residual, 12608 x 384 <- 768 15.0, 13.7.  Both experts
+// 11000 x 768 <- 768 31.7, 28.4, 7000 x 1152 <- 768 31.7, 28.9, 25088 x 384 <- 384 25.5, 23.6, 12608 x 768 <- 768, 70 % 32.2, 31.3; where no rows are
+// taken within 1 % (a workgroup works that out).  Not the tiles of long rows, two a CU (12608 x 384 <- 2304 34.2, 34.5), nor the finer pairs of
+// tiles (7000 x 512 <- 512 15.6, 16.1).
+template <class Tile, class Low, int OCC, class Store>
+__global__ __launch_bounds__(256, OCC) void gemm_even_kernel(GemmArgs g, Store store, int high_blocks, int high_rows) {
+    constexpr int LDS_H = Tile::template lds_bytes<Store>(), LDS_L = Low::template lds_bytes<Store>(), LDS_BYTES = LDS_H > LDS_L ? LDS_H : LDS_L;
+    static_assert(LDS_BYTES * OCC <= 160 * 1024 && Low::BN == Tile::BN && 2 * Low::BM == Tile::BM, "half of a tile, OCC of either to a CU");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_BYTES];
+    if ((int)blockIdx.x < high_blocks) return Tile::template run<Store>(g, store, blockIdx.x, lds, 0, high_rows);
+    Low::template run<Store>(g, store, (int)blockIdx.x - high_blocks, lds, high_rows);
+}
+
+template <class Tile, class Low, int OCC, class Store>
+int launch_even(const GemmArgs &g, const Store &store, hipStream_t st, const char *what) {
+    GemmArgs ga = g;
+    ga.share_out(Tile::BN, Tile::col_groups(g));
+    const long n = g.sel.max_rows, high = g.sel.counts || n >= (1L << 30) ? n : (long)even_rows<Tile::BM, OCC>((uint32_t)n, ga, 0);
+    if (high >= n) return launch_tile<Tile, OCC>(g, store, st, what);
+    const long high_blocks = tile_blocks<Tile>(high, ga), blocks = high_blocks + tile_blocks<Low>(n - high, ga);      // (of one round)
+    gemm_even_kernel<Tile, Low, OCC, Store><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(ga, store, (int)high_blocks, (int)high);
+    return check_launch(what);
+}
+
 }  // namespace sa
 
 #include "gemm_slice.h"
@@ -791,7 +832,7 @@ int launch_gemm(const GemmArgs &g, const Store &store, hipStream_t st, const cha
         if (lines && long_rows)
             return tiles(128, 128) <= 1536 ? launch_tile<NtTile<T, 128, 64, 128, 2, 2>, 2>(g, store, st, what)
                                            : launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
-        if (tiles(128, 128) <= 768 || g.N <= 64) return launch_tile<NtTile<T, 128, 64, 64, 3, 1>, 3>(g, store, st, what);
+        if (tiles(128, 128) <= 768 || g.N <= 64) return launch_even<NtTile<T, 128, 64, 64, 3, 1>, NtTile<T, 64, 64, 64, 3, 1>, 3>(g, store, st, what);
         const long rounds256 = (tiles(256, 128) + 511) / 512, rounds128 = (tiles(128, 128) + 767) / 768;
         const bool wide = counted ? ((g.sel.max_rows + 255) / 256) * ((g.N + 127) / 128) >= 512    // no rounds to speak of
                                   : rounds256 * 5 <= rounds128 * 4;      // a round of the larger tiles takes 1.25 times as long
@@ -885,7 +926,7 @@ int launch_gemm_packed(const GemmArgs &g, const Store &store, hipStream_t st, co
     auto tiles = [&](long bm, long bn) { return ((m_est + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
     if (tiles(64, 64) <= 640) return launch_tile<NtTile<T, 64, 64, 64, 2, 1>, 4>(g, store, st, what);
     if (packed_tall(m_est, g.N, g.K)) return launch_tile<NtTile<T, 192, 128, 64, 2, 1>, 2>(g, store, st, what);
-    return launch_tile<NtTile<T, 128, 64, 64, 2, 1>, 3>(g, store, st, what);
+    return launch_even<NtTile<T, 128, 64, 64, 2, 1>, NtTile<T, 64, 64, 64, 2, 1>, 3>(g, store, st, what);
 }
 
 }  // namespace sa
