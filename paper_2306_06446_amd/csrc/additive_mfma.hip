@@ -592,7 +592,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             asm volatile("" : "+v"(out_lane));     // (made here: no registers for it beside the products)
             const int m = out_lane & 31, kg = out_lane >> 5;
             const uint32_t row_step = (uint32_t)H * DV, lane_at = (uint32_t)(4 * kg) * row_step + m;
-            // FORMS: which of the three leave (1 fp32, 2 int8, 4 fp16), or -1: asked for in every row.  Every wavefront of a launch runs this for
+            // FORMS: which of the three leave (1 fp32, 2 int8, 4 fp16; 8: AddFused::keep), or -1: asked for in every row.  Every wavefront of a launch runs this for
             // the first time, and few have more than one tile: what its instructions take to arrive counts.  So those of the common forms
             // have no others between them, and a row's address is made from the row's before, where it is used.  All made ahead of the tiles, as
             // the compiler does with tile_at + row * row_step, they were 300 instructions and most of the registers: Q(K^T V) of 32 x 3136
@@ -601,6 +601,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             auto store_rows = [&](auto whole_c, auto forms_c) {
                 constexpr bool WHOLE = decltype(whole_c)::value;      // all 32 queries exist
                 constexpr int FORMS = decltype(forms_c)::value;
+                const bool keep = ZO && (FORMS < 0 ? f.keep : (FORMS & 8) != 0);
                 const bool floats = FORMS < 0 ? f.out != nullptr : (FORMS & 1) != 0, bytes = FORMS < 0 ? f.xq != nullptr : (FORMS & 2) != 0,
                            halves = FORMS < 0 ? f.xh != nullptr : (FORMS & 4) != 0;
                 size_t at = tile_at;
@@ -618,7 +619,7 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                             const float val = fr * acc[tm][j][r];
                             if (floats) {
                                 float *dst = reinterpret_cast<float *>(reinterpret_cast<char *>(f.out + at + j * 32) + lane_at * 4);
-                                if (ZO) *dst = val;           // the convolution that follows reads it
+                                if (keep) *dst = val;
                                 else __builtin_nontemporal_store(val, dst);
                             }
                             if (bytes) (f.xq + at + j * 32)[lane_at] = (int8_t)sa::requant_byte(val * f.act_inv_scale);
@@ -628,7 +629,8 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                 }
             };
             if (__builtin_expect((tile0 + tm) * 32 + 32 <= Nq, 1)) {
-                if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{});
+                if (ZO && f.keep) store_rows(std::true_type{}, std::integral_constant<int, ZO ? 9 : -1>{});
+                else if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{});
                 else if (!f.out && !f.xh) store_rows(std::true_type{}, std::integral_constant<int, 2>{});
                 else if (!f.xh) store_rows(std::true_type{}, std::integral_constant<int, 3>{});
                 else store_rows(std::true_type{}, std::integral_constant<int, -1>{});

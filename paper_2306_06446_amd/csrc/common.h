@@ -321,6 +321,7 @@ struct AddFused {
     int8_t *xq = nullptr;
     _Float16 *xh = nullptr;
     float act_inv_scale = 0.0f;
+    bool keep = false;       // {0,1} codes: the outputs stay in the L2s for who reads them next
 };
 bool additive_mfma_ktv_supported(int nbits, int dv);
 bool additive_mfma_qkv_supported(int nbits, int dv);
