@@ -108,8 +108,8 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
     const int phase = wave / PAIRS;
     const int n_groups = (W + GW - 1) / GW, log_cols = __builtin_ctz((unsigned)DV / DVC);       // DV: 32, 64 or 128
     const int c0 = (rest & ((1 << log_cols) - 1)) * DVC, words = rest >> log_cols;
-    const int group = n_groups == 1 ? 0 : words % n_groups;
-    const long bh = n_groups == 1 ? words : words / n_groups;
+    const long bh = n_groups == 1 ? words : n_groups == 2 ? words >> 1 : words / n_groups;
+    const int group = words - (int)bh * n_groups;
     const int b = (int)by_h((uint32_t)bh), h = (int)bh - b * H;
     const int w0 = group * GW + (wave % PAIRS) * WB;             // this wavefront's first word (may lie past the last one: idle)
     const int m = lane & 31, kg = lane >> 5;
@@ -711,14 +711,11 @@ bool additive_mfma_qkv_supported(int nbits, int dv) {
 }
 
 // Token splits of the K^T V pass: one workgroup per CU (every split writes a whole K^T V that has to be read again), and at
-// least two steps for every wavefront.
-AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv) {
+// least two steps for every wavefront.  quantum: tokens of one step of every wavefront.
+static AdditiveMfmaPlan plan_splits(long heads, int groups, int quantum, int Nk) {
     AdditiveMfmaPlan p;
-    const int W = nbits / 64;
-    p.groups = W <= 2 ? 1 : (W + 3) / 4;
-    const int quantum = 16 * (W <= 2 ? 8 : 4);                   // tokens of one step of every wavefront
-    const long base = (long)B * H * p.groups * (dv > 64 ? dv / 64 : 1);
-    const long units = ((long)Nk + 2 * quantum - 1) / (2 * quantum);
+    p.groups = groups;
+    const long base = heads * groups, units = ((long)Nk + 2 * quantum - 1) / (2 * quantum);
     long splits = (256 + base - 1) / base;
     if (splits > units) splits = units;
     if (splits < 1) splits = 1;
@@ -727,6 +724,20 @@ AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv) {
     p.tokens_per_block = (int)((per + 15) / 16 * 16);
     p.splits = (int)(((long)Nk + p.tokens_per_block - 1) / p.tokens_per_block);
     return p;
+}
+
+// Codes of more than two words: a workgroup has four of them (two wavefronts then take the same V), or two, which halves what the partials
+// write and the sum reads and lets two workgroups read V.  Two where there are partials, unless V comes from memory (both products of 256
+// bits, four words and two, us: 1 x 4 heads x 16384 tokens x 64 30.4, 27.9; 1 x 4 x 5471 23.5, 20.4; 2 x 4 x 8000 28.4, 26.8; 4 x 12 x 4000 61.3,
+// 60.9; 16 x 12 x 1024 66.1, 59.2; 8 x 6 x 700 32.1, 29.7; 1 x 3 x 197 14.5, 13.7; of 134 MB, 8 x 4 x 16384, 105.0, 107.5; without partials, 64 x 12 x
+// 197, 56.0, 68.0), and not where Q(K^T V) would then sum them itself (32 x 1 x 3136 x 32 23.1, 24.2).
+AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv) {
+    const int W = nbits / 64;
+    const long heads = (long)B * H * (dv > 64 ? dv / 64 : 1);
+    if (W <= 2) return plan_splits(heads, 1, 16 * 8, Nk);
+    const AdditiveMfmaPlan four = plan_splits(heads, (W + 3) / 4, 16 * 4, Nk), two = plan_splits(heads, (W + 1) / 2, 16 * 8, Nk);
+    if (four.splits == 1 || (double)B * H * Nk * dv * 4 > (64 << 20)) return four;
+    return two.splits == 1 || additive_mfma_sums_partials(two.splits, nbits, dv) == additive_mfma_sums_partials(four.splits, nbits, dv) ? two : four;
 }
 
 // Many short sequences: one word per wavefront and a short ring, so that two workgroups share a CU and one loads or sums while
@@ -751,6 +762,7 @@ int launch_ktv_mfma(const uint64_t *k_codes, const float *v, float *dst, int32_t
     else if (W == 1) { SA_KTV(DVC_, 1, 8, 4) }          \
     else if (W == 2 && many) { SA_KTV(DVC_, 1, 4, 2) }  \
     else if (W == 2) { SA_KTV(DVC_, 2, 8, 4) }          \
+    else if (p.groups == (W + 1) / 2) { SA_KTV(DVC_, 2, 8, 4) } \
     else { SA_KTV(DVC_, 2, 4, 4) }
     if (dv == 32) {
         SA_KTV_DV(32)
