@@ -257,7 +257,10 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
     }
     __syncthreads();                               // every ring has been read
 
-    // ---- the wavefronts' sums, in ascending order, one 32-bit tile of every share at a time; dst: [splits][BH][nbits][DV].
+    // ---- the wavefronts' sums, in ascending order, one 32-bit tile of every share at a time; dst: [splits][BH][nbits][DV].  (Two words of
+    //      more to a workgroup: in pairs of pairs.  They take the place of twice as many partials of half as many sums each, which one after
+    //      the other they would be up to 7 % further from the exact sum than; so 3 % closer.)
+    const bool in_pairs = PH == 8 && WB == 2 && n_groups > 1;
     //      With +-1 codes the operand was -1 for a set bit (the code bit as the sign bit), so the sum is negated here.
     const size_t row0 = (((size_t)part * BH + bh) * W + group * GW) * 64;
     const int rows_here = min(GW, W - group * GW) * 64;
@@ -275,9 +278,15 @@ __device__ __forceinline__ void ktv_block(const uint64_t *__restrict__ k_codes, 
         __syncthreads();
         for (int q = tid; q < PAIRS * TILE / 4; q += kKtvWaves * 64) {
             const int share = q / (TILE / 4);
-            f32x4 a = reinterpret_cast<const f32x4 *>(red_s)[q];
+            auto of = [&](int ph) { return reinterpret_cast<const f32x4 *>(red_s)[ph * PAIRS * (TILE / 4) + q]; };
+            f32x4 a;
+            if (in_pairs) {
+                a = ((of(0) + of(1)) + (of(2) + of(3))) + ((of(PH / 2) + of(PH / 2 + 1)) + (of(PH / 2 + 2) + of(PH / 2 + 3)));
+            } else {
+                a = of(0);
 #pragma unroll
-            for (int ph = 1; ph < PH; ++ph) a += reinterpret_cast<const f32x4 *>(red_s)[ph * PAIRS * (TILE / 4) + q];
+                for (int ph = 1; ph < PH; ++ph) a += of(ph);
+            }
             const int row = share * WB * 64 + t * 32 + q % (TILE / 4) / (DVC / 4), col = (q % (DVC / 4)) * 4;
             if (!ZO) a = -a;
             if (row < rows_here) *reinterpret_cast<f32x4 *>(dst + (row0 + row) * DV + c0 + col) = a;
@@ -728,15 +737,15 @@ static AdditiveMfmaPlan plan_splits(long heads, int groups, int quantum, int Nk)
 
 // Codes of more than two words: a workgroup has four of them (two wavefronts then take the same V), or two, which halves what the partials
 // write and the sum reads and lets two workgroups read V.  Two where there are partials, unless V comes from memory (both products of 256
-// bits, four words and two, us: 1 x 4 heads x 16384 tokens x 64 30.4, 27.9; 1 x 4 x 5471 23.5, 20.4; 2 x 4 x 8000 28.4, 26.8; 4 x 12 x 4000 61.3,
-// 60.9; 16 x 12 x 1024 66.1, 59.2; 8 x 6 x 700 32.1, 29.7; 1 x 3 x 197 14.5, 13.7; of 134 MB, 8 x 4 x 16384, 105.0, 107.5; without partials, 64 x 12 x
-// 197, 56.0, 68.0), and not where Q(K^T V) would then sum them itself (32 x 1 x 3136 x 32 23.1, 24.2).
+// bits, four words and two, us: 1 x 4 heads x 16384 tokens x 64 30.7, 27.8; 1 x 4 x 5471 23.4, 20.2; 2 x 4 x 8000 28.7, 26.4; 8 x 6 x 700 32.0, 29.2;
+// 1 x 3 x 197 14.5, 13.5; V of 49 MB, 4 x 12 x 4000, 58.8, 59.9, but with no partials left, 16 x 12 x 1024, 62.8, 55.6; of 134 MB, 8 x 4 x 16384,
+// 105.0, 107.5; without partials, 64 x 12 x 197, 56.0, 68.0), and not where Q(K^T V) would then sum them itself (32 x 1 x 3136 x 32 23.1, 24.2).
 AdditiveMfmaPlan plan_additive_mfma(int B, int H, int Nk, int nbits, int dv) {
     const int W = nbits / 64;
     const long heads = (long)B * H * (dv > 64 ? dv / 64 : 1);
     if (W <= 2) return plan_splits(heads, 1, 16 * 8, Nk);
     const AdditiveMfmaPlan four = plan_splits(heads, (W + 3) / 4, 16 * 4, Nk), two = plan_splits(heads, (W + 1) / 2, 16 * 8, Nk);
-    if (four.splits == 1 || (double)B * H * Nk * dv * 4 > (64 << 20)) return four;
+    if (four.splits == 1 || (double)B * H * Nk * dv * 4 > (two.splits == 1 ? 64 : 32) * 1048576.0) return four;
     return two.splits == 1 || additive_mfma_sums_partials(two.splits, nbits, dv) == additive_mfma_sums_partials(four.splits, nbits, dv) ? two : four;
 }
 

@@ -1,4 +1,4 @@
-"""K^T V of codes of three words and more, two or four of them to a workgroup: with partials and without, V up to 64 MiB and beyond it, partials
+"""K^T V of codes of three words and more, two or four of them to a workgroup: with partials and without, V up to 32 and 64 MiB and beyond them, partials
 that Q(K^T V) would sum itself, ragged steps and words that do not pair up, both kinds of codes."""
 import pytest
 import torch
@@ -15,7 +15,7 @@ def bits_of(c):
 @pytest.mark.parametrize("B,H,N,W,dv", [
     (1, 4, 5471, 4, 64), (1, 3, 197, 4, 64), (2, 2, 257, 3, 32), (1, 2, 1027, 5, 64), (1, 1, 3000, 6, 128), (3, 2, 700, 8, 32),      # two words
     (32, 8, 60, 4, 64), (100, 6, 130, 3, 32),                                                       # no partials: four
-    (8, 4, 8191, 4, 64), (8, 4, 8193, 4, 64),                                                       # V of 64 MiB, a little more
+    (8, 4, 4096, 4, 64), (8, 4, 4097, 4, 64), (16, 12, 1365, 4, 64), (16, 12, 1366, 4, 64),         # V of 32 MiB and a little more, of 64
     (32, 1, 3136, 4, 32), (16, 1, 2049, 4, 64),                                                     # Q(K^T V) would sum the partials of two words
 ])
 @pytest.mark.parametrize("zero_one", [False, True])
