@@ -391,7 +391,7 @@ int launch_waves(const Tensors &ts, const float *proj, long rows, const RowMap &
     const long enough = (n_total + kWaves * tiles_per_wave - 1) / (kWaves * tiles_per_wave);
     const long blocks = enough < waves / kWaves ? enough : waves / kWaves;
     // what rides along comes behind the tiles: it fills the CUs that are done first
-    const long more = (side_blocks(side, kWaves * 64) + nbits / C - 1) / (nbits / C);
+    const long more = (side_blocks<kWaves * 64>(side) + nbits / C - 1) / (nbits / C);
     const dim3 grid((unsigned)(blocks + more), (unsigned)(nbits / C));
     const bool stream = C == 256 && n_total * 32 * D * 4 >= (192L << 20);       // see the top
 #define SA_HASH(STREAM_)                                                                                                          \

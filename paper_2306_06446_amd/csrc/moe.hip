@@ -543,7 +543,7 @@ extern "C" int sa_moe_linear(const int8_t *xq, const void *xh, const float *logi
     if (decodes && T <= kOneLaunchTokens && K % 64 == 0) {
         side.route = {logits, T, 2, expert_of, gate, counts, perm};
         sa::add_decode(&side.decode, w4, K, N, ws + L.planes);
-        const long blocks = sa::side_blocks(side, kOneTok);
+        const long blocks = sa::side_blocks<kOneTok>(side);
         SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "sa_moe_linear: too many weights");
         side_work_kernel<<<dim3((unsigned)blocks), dim3(kOneTok), 0, st>>>(side);
         rc = sa::check_launch("sa_moe_linear(routing, weight decode)");

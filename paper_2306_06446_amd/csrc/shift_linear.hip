@@ -175,10 +175,8 @@ __global__ __launch_bounds__(256) void decode_works_kernel(DecodeWork w, DecodeW
     else decode_block<256>(w2, blockIdx.x - first);
 }
 
-unsigned decode_blocks(const DecodeWork &w) { return (unsigned)((w.chunks[0] + w.chunks[1] + w.chunks[2] + 255) / 256); }
-
 int launch_decode(const DecodeWork &w, hipStream_t st) {
-    decode_work_kernel<<<dim3(decode_blocks(w)), dim3(256), 0, st>>>(w);
+    decode_work_kernel<<<dim3((unsigned)decode_blocks<256>(w)), dim3(256), 0, st>>>(w);
     return check_launch("shift layers (weight decode)");
 }
 
@@ -518,8 +516,8 @@ void sa::shift_mlp_decode(DecodeWork *w, const uint8_t *w1, const uint8_t *w2, i
 int sa::launch_decode_work(const DecodeWork &w, hipStream_t st) { return launch_decode(w, st); }
 
 int sa::launch_decode_work(const DecodeWork &w, const DecodeWork &w2, hipStream_t st) {
-    const unsigned blocks = decode_blocks(w);
-    decode_works_kernel<<<dim3(blocks + decode_blocks(w2)), dim3(256), 0, st>>>(w, w2, blocks);
+    const unsigned blocks = (unsigned)decode_blocks<256>(w);
+    decode_works_kernel<<<dim3(blocks + (unsigned)decode_blocks<256>(w2)), dim3(256), 0, st>>>(w, w2, blocks);
     return check_launch("layer (weight decode)");
 }
 

@@ -159,47 +159,53 @@ __device__ inline void decode8(uint32_t x, uint32_t outA[2], uint32_t outB[2]) {
     outB[1] = __builtin_amdgcn_perm(b[1], b[0], 0x07030602u);
 }
 
-// Chunk i of a DecodeWork: 32 weights, 16 bytes in, 32 bytes out to each plane.  THREADS chunks per workgroup.
+// Workgroups of THREADS threads that a DecodeWork takes, a chunk (32 weights, 16 bytes in, 32 bytes out to each plane) to a thread.
+template <int THREADS>
+__host__ __device__ inline long decode_blocks(const DecodeWork &w) {
+    long n = 0;
+    for (int m = 0; m < 3; ++m) n += (w.chunks[m] + THREADS - 1) / THREADS;
+    return n;
+}
+// A workgroup has one matrix, so what is read of the kernel's arguments is the same in all lanes.  (Chosen by each lane, the compiler kept
+// a copy of the arguments in scratch memory, written and read by every thread: 768 x 3072 and 3072 x 768 weights took 9.8 us
+// in a launch of their own and 16.8 with 768 x 2304 ones; 5.7 and 6.4 so.)
 template <int THREADS>
 __device__ __forceinline__ void decode_block(const DecodeWork &w, long block) {
-    long i = block * THREADS + threadIdx.x;
-    int m = 0;
-    if (i >= w.chunks[0]) {
-        i -= w.chunks[0];
-        m = 1;
-        if (i >= w.chunks[1]) {
-            i -= w.chunks[1];
-            m = 2;
-            if (i >= w.chunks[2]) return;
-        }
-    }
-    const uint4 wv = (m == 0 ? w.w4[0] : m == 1 ? w.w4[1] : w.w4[2])[i];
-    const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
-    uint32_t oa[8], ob[8];
+    auto decode = [&](const uint4 *w4, uint4 *pa, uint4 *pb, long chunks) {
+        const long i = block * THREADS + threadIdx.x;
+        if (i >= chunks) return;
+        const uint4 wv = w4[i];
+        const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
+        uint32_t oa[8], ob[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) decode8(wd[q], oa + 2 * q, ob + 2 * q);
-    uint4 *pa = m == 0 ? w.plane_a[0] : m == 1 ? w.plane_a[1] : w.plane_a[2], *pb = m == 0 ? w.plane_b[0] : m == 1 ? w.plane_b[1] : w.plane_b[2];
-    pa[2 * i] = make_uint4(oa[0], oa[1], oa[2], oa[3]);
-    pa[2 * i + 1] = make_uint4(oa[4], oa[5], oa[6], oa[7]);
-    pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
-    pb[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
+        for (int q = 0; q < 4; ++q) decode8(wd[q], oa + 2 * q, ob + 2 * q);
+        pa[2 * i] = make_uint4(oa[0], oa[1], oa[2], oa[3]);
+        pa[2 * i + 1] = make_uint4(oa[4], oa[5], oa[6], oa[7]);
+        pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
+        pb[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
+    };
+    const long first = (w.chunks[0] + THREADS - 1) / THREADS, second = (w.chunks[1] + THREADS - 1) / THREADS;
+    if (block < first) return decode(w.w4[0], w.plane_a[0], w.plane_b[0], w.chunks[0]);
+    block -= first;
+    if (block < second) return decode(w.w4[1], w.plane_a[1], w.plane_b[1], w.chunks[1]);
+    block -= second;
+    decode(w.w4[2], w.plane_a[2], w.plane_b[2], w.chunks[2]);
 }
 
 // Workgroups of THREADS threads that a SideWork takes, and what workgroup `block` of them does (routing first: it takes
 // longest).  Routing is part of it for two experts only.
-inline long side_blocks(const SideWork &w, int threads) {
-    return (w.route.T + threads - 1) / threads + (w.decode.chunks[0] + w.decode.chunks[1] + w.decode.chunks[2] + threads - 1) / threads +
-           (w.zero.n > 0 ? 1 : 0);
+template <int THREADS>
+inline long side_blocks(const SideWork &w) {
+    return (w.route.T + THREADS - 1) / THREADS + decode_blocks<THREADS>(w.decode) + (w.zero.n > 0 ? 1 : 0);
 }
 template <int THREADS>
 __device__ __forceinline__ void side_block(const SideWork &w, long block) {
-    const long route_blocks = (w.route.T + THREADS - 1) / THREADS;
-    const long decode_blocks = (w.decode.chunks[0] + w.decode.chunks[1] + w.decode.chunks[2] + THREADS - 1) / THREADS;
-    if (block < route_blocks)
+    const long route = (w.route.T + THREADS - 1) / THREADS, decode = decode_blocks<THREADS>(w.decode);
+    if (block < route)
         route_scatter_block<THREADS, 2>(w.route, (int)block);
-    else if (block < route_blocks + decode_blocks)
-        decode_block<THREADS>(w.decode, block - route_blocks);
-    else if (block == route_blocks + decode_blocks)
+    else if (block < route + decode)
+        decode_block<THREADS>(w.decode, block - route);
+    else if (block == route + decode)
         zero_words(w.zero);
 }
 
