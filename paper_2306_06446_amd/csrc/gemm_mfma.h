@@ -608,7 +608,13 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
     const uint8_t *table = side.lds;
     const int cc = lane % CPR, cr = lane / CPR;                   // this lane's chunk of a row, its first row
     const ChunkOut<Store> chunk(store, n0 + wn + cc * (16 / ES), N);
-    auto row_of = [&](int i, int q) { return wm + i * 32 + q * ROWS_PER_CHUNK + cr; };
+    // late: the row's addresses are made where they are used.  Made ahead for all rows, beside a residual on its way, they took more registers than
+    // there are (30000 x 768 <- 768 with a residual, 128 x 128 tiles, 44 spilled: 84.5 us, 54.3 so; 60000 x 384 <- 384 70.7, 40.4).
+    auto row_of = [&](int i, int q, bool late) {
+        int r = cr;
+        if (late) asm volatile("" : "+v"(r));
+        return wm + i * 32 + q * ROWS_PER_CHUNK + r;
+    };
     wait_loads_in_flight<0>();
     __syncthreads();                              // the last stage has been read, `side` is complete
     if constexpr (S::SIDE_LATE) {
@@ -636,7 +642,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
         float4 ext[READS ? 2 : 1][NC];
         auto fetch = [&](int i) {
 #pragma unroll
-            for (int q = 0; q < NC; ++q) ext[READS ? i & 1 : 0][q] = READS ? chunk.fetch(side.dest(row_of(i, q))) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            for (int q = 0; q < NC; ++q) ext[READS ? i & 1 : 0][q] = READS ? chunk.fetch(side.dest(row_of(i, q, Store::kLinear && READS))) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         };
         fetch(0);
         if constexpr (AHEAD) convert(std::integral_constant<int, 0>{});
@@ -665,7 +671,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
                 if constexpr (i + 1 < MI) fetch(i + 1);
 #pragma unroll
                 for (int q = 0; q < NC; ++q) {
-                    const int ml = row_of(i, q);
+                    const int ml = row_of(i, q, Store::kLinear && READS);
                     const uint4 c = *reinterpret_cast<const uint4 *>(slab + (q * ROWS_PER_CHUNK + cr) * PITCH + cc * 16);
                     if (m0 + ml < n_rows && chunk.live > 0) chunk.put(c, ext[READS ? i & 1 : 0][q], side.gate(ml), side.dest(ml));
                 }

@@ -61,6 +61,7 @@ def kernels():
     (r"shift_mlp_walk_kernel", 3),
     (r"norm_hash_kernel", 32),
     (r"hamming_pipe_kernel", 6),
+    (r"gemm_kernel.*ShiftStoreILi6E|gemm_even_kernel.*ShiftStoreILi6E", 15),      # fp32 Linears with a residual, or into Q, K and V
     (r"decode_works?_kernel|decode_w4_kernel|side_work_kernel", 4),      # a choice of argument by lane keeps the arguments in scratch
 ])
 def test_no_scratch(kernels, pattern, instances):
