@@ -122,11 +122,26 @@ __global__ __launch_bounds__(256, OCC) void expert_even_kernel(GemmArgs gs, Stor
     TileL::template run<StoreS>(gs, ss, b - m_blocks, lds, high);
 }
 
+template <class TileS, class TileM, int OCC, class StoreS, class StoreM>
+int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
+    GemmArgs s = gs, m = gm;
+    s.share_out(TileS::BN, TileS::col_groups(gs));
+    m.share_out(TileM::BN, TileM::col_groups(gm));
+    // the rows of both add up to max_rows: all on either side, and one more row of tiles per XCD where the other side starts
+    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
+    const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
+    const long blocks = (all_s > all_m ? all_s : all_m) + step_s + step_m;
+    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
+    expert_pair_kernel<TileS, StoreS, TileM, StoreM, OCC><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm);
+    return check_launch(what);
+}
+
 template <class TileS, class TileM, class TileL, int OCC, class StoreS, class StoreM>
 int launch_even_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
     GemmArgs s = gs, m = gm;
     s.share_out(TileS::BN, TileS::col_groups(gs));
     m.share_out(TileM::BN, TileM::col_groups(gm));
+    if (!may_be_even<TileS::BM, TileM::BM, OCC>(s, m, gs.sel.max_rows)) return launch_pair_tiles<TileS, TileM, OCC>(gs, ss, gm, sm, st, what);
     // as launch_pair_tiles, and the lower tiles: at most one a CU and two for each of a row of tiles (even_rows)
     const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
     const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
@@ -141,6 +156,8 @@ int launch_split_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm,
     GemmArgs s = gs, m = gm;
     s.share_out(TileS::BN, TileS::col_groups(gs));
     m.share_out(TileM::BN, TileM::col_groups(gm));
+    if constexpr (SPLIT_SHIFT)                               // rows are taken of one round of workgroups only
+        if (least_tiles<TileS::BM, TileM::BM>(s, m, gs.sel.max_rows) > kPlaces) return launch_pair_tiles<TileS, TileM, OCC>(gs, ss, gm, sm, st, what);
     // as launch_pair_tiles, and what the lower tiles take: at most a round of workgroups more, and a row of tiles per XCD
     const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
     const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
@@ -148,20 +165,6 @@ int launch_split_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm,
     SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
     expert_split_kernel<TileS, StoreS, TileM, StoreM, TileL, SPLIT_SHIFT, OCC>
         <<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm, kPlaces / 2 / s.cols_per_group);
-    return check_launch(what);
-}
-
-template <class TileS, class TileM, int OCC, class StoreS, class StoreM>
-int launch_pair_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm, const StoreM &sm, hipStream_t st, const char *what) {
-    GemmArgs s = gs, m = gm;
-    s.share_out(TileS::BN, TileS::col_groups(gs));
-    m.share_out(TileM::BN, TileM::col_groups(gm));
-    // the rows of both add up to max_rows: all on either side, and one more row of tiles per XCD where the other side starts
-    const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
-    const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);
-    const long blocks = (all_s > all_m ? all_s : all_m) + step_s + step_m;
-    SA_REQUIRE(blocks < (1L << 31), SA_ERR_SHAPE, "%s: too many tiles for one launch", what);
-    expert_pair_kernel<TileS, StoreS, TileM, StoreM, OCC><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(s, ss, m, sm);
     return check_launch(what);
 }
 
