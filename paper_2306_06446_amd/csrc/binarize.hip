@@ -49,7 +49,8 @@ __global__ __launch_bounds__(256) void binarize_proj_kernel(
 // proj == NULL: bit j = [x_j >= 0]; one wavefront per 64 features of a row.
 __global__ __launch_bounds__(256) void binarize_sign_kernel(const float *__restrict__ x,
                                                             uint64_t *__restrict__ codes, int N,
-                                                            int H, int d, long n_words) {
+                                                            int H, int d, long n_words, sa::ZeroWork zero) {
+    if (blockIdx.x == 0) sa::zero_words(zero);
     const int lane = threadIdx.x & (kWave - 1);
     const long word_id = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (word_id >= n_words) return;
@@ -64,7 +65,19 @@ __global__ __launch_bounds__(256) void binarize_sign_kernel(const float *__restr
     if (lane == 0) codes[(((size_t)b * H + h) * N + n) * W + w] = word;
 }
 
+int launch_sign(const float *x, long rows, int N, int H, int d, uint64_t *codes, const sa::ZeroWork &zero, hipStream_t st) {
+    const long n_words = rows * (d / 64);
+    binarize_sign_kernel<<<dim3((unsigned)((n_words + 3) / 4)), dim3(256), 0, st>>>(x, codes, N, H, d, n_words, zero);
+    return sa::check_launch("sa_binarize(sign)");
+}
+
 }  // namespace
+
+int sa::launch_sign_pair(const float *q, const float *k, long rows, int N, int H, int d, uint64_t *q_codes, uint64_t *k_codes,
+                         const ZeroWork &zero, hipStream_t st) {
+    const int rc = launch_sign(q, rows, N, H, d, q_codes, zero, st);
+    return rc != SA_OK ? rc : launch_sign(k, rows, N, H, d, k_codes, ZeroWork(), st);
+}
 
 extern "C" int sa_binarize(const float *x, int B, int N, int H, int d, const float *proj,
                            int nbits, uint64_t *codes, void *stream) {
@@ -128,12 +141,7 @@ extern "C" int sa_binarize_ex(const float *x, int B, int N, int H, int d, const 
     if (bad != SA_OK || rows == 0) return bad;
     hipStream_t st = sa::as_stream(stream);
     const int W = nbits / 64;
-    if (proj == nullptr) {
-        const long n_words = rows * W;
-        const long blocks = (n_words + 3) / 4;
-        binarize_sign_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(x, codes, N, H, d, n_words);
-        return sa::check_launch("sa_binarize(sign)");
-    }
+    if (proj == nullptr) return launch_sign(x, rows, N, H, d, codes, sa::ZeroWork(), st);
     if (variant != SA_VARIANT_VALU && sa::binarize_mfma_supported(d, nbits))
         return sa::launch_binarize_mfma(x, nullptr, proj, codes, nullptr, rows, N, H, d, nbits, st);
     const int n_chunks = (N + 63) / 64;

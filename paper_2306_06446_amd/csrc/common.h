@@ -296,6 +296,9 @@ bool binarize_mfma_supported(int d, int nbits);
 int launch_binarize_mfma(const float *x0, const float *x1_or_null, const float *proj, uint64_t *codes0,
                          uint64_t *codes1_or_null, long rows, int N, int H, int d, int nbits, hipStream_t st,
                          const SideWork &side = SideWork());
+// sa_binarize_pair without proj, without its argument checks: a launch each; `zero` is cleared by the first.
+int launch_sign_pair(const float *q, const float *k, long rows, int N, int H, int d, uint64_t *q_codes, uint64_t *k_codes,
+                     const ZeroWork &zero, hipStream_t st);
 // Whether sa_binarize_pair runs that kernel for these operands, in one launch (binarize.hip).
 bool binarize_pair_one_launch(const float *q, const float *k, const float *proj, const uint64_t *q_codes, const uint64_t *k_codes,
                               long rows, int d, int nbits);

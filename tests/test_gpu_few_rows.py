@@ -1,6 +1,8 @@
 """The MLP half of a layer and the MLP of a block in one launch for few rows, against the launches of their own that the same call makes
 where the workspace has no room for that one: the same integer sums, the same order of the row's sums and, where those take the tiles that
 split the contraction between four wavefronts, of the Mult expert's, so the same bits."""
+import ctypes
+
 import pytest
 import torch
 
@@ -23,7 +25,9 @@ def weights(sa, g, E, hid, prepared, moe):
     return w
 
 
-def layer(sa, T, E, ratio, moe, prepared=True, seed=0, bias=0.0):
+def layer(sa, T, E, ratio, moe, prepared=True, seed=0, bias=0.0, d=None, attention=0, nbits=64):
+    """nbits = 0: the sign hash."""
+    d = d or (64 if E != 64 else 32)
     g = torch.Generator(device="cuda")
     g.manual_seed(T + E + seed)
     hid = ratio * E
@@ -33,25 +37,26 @@ def layer(sa, T, E, ratio, moe, prepared=True, seed=0, bias=0.0):
     kw = weights(sa, g, E, hid, prepared, moe)
     if moe:
         kw.update(wg=rand(g, E, 2) * E**-0.5, bg=torch.tensor([0.0, bias], device="cuda"))
-    return sa.binding.Layer(B=1, N=T, H=E // 64 if E != 64 else 2, nbits=64, E=E, hid=hid, attention=0, moe=int(moe), shift_variant=3 if prepared else 2,
+    return sa.binding.Layer(B=1, N=T, H=E // d, nbits=nbits or d, E=E, hid=hid, attention=attention, moe=int(moe), shift_variant=3 if prepared else 2,
                             eps=1e-6, ln_inv_scale=32.0, qkv_scale=2.0**-12, attn_scale=(64.0 * T) ** -0.5, act_inv_scale=32.0,
                             o_scale=2.0**-12, requant_scale=2.0**-11, out_scale=2.0**-12, x=x, gamma1=1.0 + 0.1 * rand(g, E), beta1=0.1 * rand(g, E),
-                            gamma2=1.0 + 0.1 * rand(g, E), beta2=0.1 * rand(g, E), proj=rand(g, E // (E // 64 if E != 64 else 2), 64),
+                            gamma2=1.0 + 0.1 * rand(g, E), beta2=0.1 * rand(g, E), proj=rand(g, d, nbits) if nbits else None,
                             lut=RELU.cuda(), **kw)
 
 
-def block(sa, T, E, ratio, moe, prepared=True, seed=0, bias=0.0):
+def block(sa, T, E, ratio, moe, prepared=True, seed=0, bias=0.0, d=None, attention=0, nbits=64):
+    d = d or 32
     g = torch.Generator(device="cuda")
     g.manual_seed(T + E + seed)
-    hid, H = ratio * E, E // 32
+    hid, H = ratio * E, E // d
     kw = weights(sa, g, E, hid, prepared, moe)
     del kw["wqkv"], kw["wo"]
     if moe:
         kw["logits"] = rand(g, T, 2) + torch.tensor([0.0, bias], device="cuda")
         kw["logits"][::5, 1] = kw["logits"][::5, 0]              # ties
-    return sa.binding.Block(B=1, N=T, H=H, d=32, nbits=64, dv=32, attention=0, hid=hid, moe=int(moe), attn_scale=(64.0 * T) ** -0.5,
-                            act_inv_scale=32.0, requant_scale=2.0**-11, out_scale=2.0**-12, q=rand(g, 1, T, H, 32), k=rand(g, 1, T, H, 32),
-                            v=rand(g, 1, T, H, 32), proj=rand(g, 32, 64), lut=RELU.cuda(), shift_variant=3 if prepared else 2, **kw)
+    return sa.binding.Block(B=1, N=T, H=H, d=d, nbits=nbits or d, dv=d, attention=attention, hid=hid, moe=int(moe), attn_scale=(64.0 * T) ** -0.5,
+                            act_inv_scale=32.0, requant_scale=2.0**-11, out_scale=2.0**-12, q=rand(g, 1, T, H, d), k=rand(g, 1, T, H, d),
+                            v=rand(g, 1, T, H, d), proj=rand(g, d, nbits) if nbits else None, lut=RELU.cuda(), shift_variant=3 if prepared else 2, **kw)
 
 
 def passes(made, n=1):
@@ -96,6 +101,37 @@ def test_block_against_launches_of_their_own(sa, T, E, ratio, moe):
 def test_packed_weights_and_one_sided_routings(sa, make, prepared, bias):
     for T, E in ((49, 256), (197, 192), (500, 128)):
         same(sa, make(sa, T, E, 4, True, prepared, bias=bias))
+
+
+# every kernel that clears what the launch counts with: the sign hash, alone or in the projection, and hashes of all code lengths, before either
+# attention
+@pytest.mark.parametrize("make", [layer, block])
+@pytest.mark.parametrize("prepared", [True, False])
+@pytest.mark.parametrize("attention", [0, 1])
+@pytest.mark.parametrize("d,nbits", [(64, 0), (64, 64), (64, 128), (64, 256), (128, 0), (128, 128), (32, 64), (32, 128)])
+def test_hashes_and_attentions(sa, make, prepared, attention, d, nbits):
+    for T, E, moe in ((98, 128, True), (199, 256, True), (33, 64, False), (197, 192, True)):
+        if E % d == 0:
+            same(sa, make(sa, T, E, 4 if E > 64 else 8, moe, prepared, d=d, attention=attention, nbits=nbits))
+
+
+def launches(made):
+    """Nodes of the graph of one call."""
+    passes(made)
+    hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        made.forward()
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+# what the launch counts with is cleared by a launch that is there anyway
+@pytest.mark.parametrize("nbits,most", [(0, 4), (64, 3)])        # the sign hash of Q and of K, or one hash for both; attention; MLP
+@pytest.mark.parametrize("E,ratio,moe", [(64, 8, False), (128, 4, False), (192, 4, True)])
+def test_no_launch_only_to_clear(sa, E, ratio, moe, nbits, most):
+    assert launches(block(sa, 197, E, ratio, moe, d=64, nbits=nbits)) == most
 
 
 @pytest.mark.parametrize("make", [layer, block])
