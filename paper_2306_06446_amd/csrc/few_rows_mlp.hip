@@ -475,9 +475,9 @@ int launch_width(const FewRows &a, int mi, bool layer, bool moe, hipStream_t st)
 
 }  // namespace
 
-// Where it is the faster way: `groups` workgroups of 16 rows at most, from the number of which a CU has LDS for (four at E = 64, two at 128
-// and 192, one at 256) on as a second round costs as much as the first.  Whole layers and blocks of 64-bit codes and linear attention,
-// hid = 4 E (E = 64: 8 E), launches of their own against this one, us:
+// Where it is the faster way: up to kMost workgroups of 16 rows, of which a CU has LDS for four at E = 64, two at 128 and 192, one at 256.
+// Where it replaces many launches (layers of two experts) that is more than one round of them, else less than one.  Whole layers and blocks of
+// 64-bit codes and linear attention, hid = 4 E (E = 64: 8 E), launches of their own against this one, us:
 //   layer, two experts  E =  64:   784 rows 31.5, 21.8; 3136 35.0, 29.2; 6272 41.7, 39.6; 9408 47.0, 47.1
 //                       E = 128:   200 rows 31.3, 20.4; 1600 34.7, 28.8; 2400 36.3, 33.9; 3200 39.9, 42.0
 //                       E = 192:   197 rows 36.8, 25.7;  394 37.6, 26.6
@@ -494,6 +494,16 @@ int launch_width(const FewRows &a, int mi, bool layer, bool moe, hipStream_t st)
 //                       E = 128:   200 rows 20.7, 17.9; 1600 21.6, 20.4; 2400 21.8, 23.8
 //                       E = 192:   197 rows 20.3, 19.4;  985 21.4, 20.8; 1182 22.5, 24.0
 //                       E = 256:    49 rows 17.9, 18.1;  784 20.4, 20.0: not taken
+// hid = 8 E (E = 64: 4 E), of which a Shift block of E = 64 gains nothing and a workgroup of E = 256 has twice the chain:
+//   layer, two experts  E =  64:   735 rows 29.5, 17.7; 6174 34.2, 31.2         E = 128: 294 rows 32.2, 19.6; 1274 34.3, 29.9; 2450 37.9, 38.1
+//                       E = 256:    98 rows 39.4, 28.4;  490 41.0, 35.6; 980 44.5, 40.3
+//   layer, Shift        E =  64:   784 rows 17.4, 16.6; 1519 17.5, 16.9         E = 128: 882 rows 25.7, 20.0; 1715 27.8, 21.9
+//                       E = 256:   245 rows 32.3, 27.1;  980 35.2, 28.4; 1960 44.8, 39.8
+//   block, two experts  E =  64:   784 rows 21.1, 17.1; 1519 21.0, 18.3         E = 128: 490 rows 22.6, 18.9;  980 23.2, 22.4
+//                       E = 256:    98 rows 23.6, 22.2;  147 23.9, 23.7;  392 24.9, 26.4
+//   block, Shift        E =  64:   784 rows 14.3, 14.5; 1519 14.5, 15.5: not taken      E = 128: 784 rows 19.9, 17.9; 1519 21.1, 19.7
+// The sign hash, codes of 128 and 256 bits, Hamming attention and packed weights: over the same rows between 1 % slower (at their ends) and 1.8
+// times as fast.
 // More rows of wide layers, whose chain is the longest, with 32 or 64 of them to a workgroup as long as those are one round:
 //   two experts  E = 192, 32 rows:  591 rows 38.0, 29.4; 985 39.6, 31.8; 64 rows: 1182 41.1, 36.9; 1970 45.0, 42.9
 //                E = 256, 32 rows:  588 rows 38.1, 30.9; 980 40.2, 32.9; 1176 (a second round) 42.0, 42.4
@@ -502,10 +512,11 @@ sa::FewRowsPlan sa::plan_few_rows(long T, int E, int hid, bool moe, bool layer) 
     FewRowsPlan p;
     if (T <= 0 || E <= 0 || E % 64 != 0 || E > 256 || hid % (4 * E) != 0 || hid > (E == 192 ? 4 : 8) * E) return p;
     const int ne = E / 64;
-    static const int kMost[2][2][4] = {{{400, 400, 256, 0}, {800, 512, 256, 208}},            // block: Shift, two experts; by E
-                                       {{400, 448, 256, 256}, {3200, 1280, 256, 256}}};       // layer
+    // by hid: 4 E, 8 E (none of E = 192); by E
+    static const int kMost[2][2][2][4] = {{{{0, 400, 256, 0}, {400, 400, 0, 0}}, {{800, 512, 256, 208}, {800, 512, 0, 56}}},                // block: Shift, two experts
+                                          {{{400, 448, 256, 256}, {400, 448, 0, 256}}, {{3200, 1280, 256, 256}, {3200, 1152, 0, 256}}}};    // layer
     auto groups = [&](int mi) { return (T + 16 * mi - 1) / (16 * mi) * kSlices * (moe ? 2 : 1); };
-    if (groups(1) > kMost[layer][moe][ne - 1]) {
+    if (groups(1) > kMost[layer][moe][hid > 4 * E][ne - 1]) {
         if (!layer || ne < 3) return p;
         if (groups(2) <= 256) p.mi = 2;
         else if (ne == 3 && moe && groups(4) <= 256) p.mi = 4;

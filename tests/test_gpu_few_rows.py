@@ -89,7 +89,8 @@ def test_layer_against_launches_of_their_own(sa, T, E, ratio, moe):
 
 @pytest.mark.parametrize("T,E,ratio,moe", [(1, 192, 4, True), (1, 192, 4, False), (15, 64, 8, True), (16, 128, 4, False), (17, 192, 4, True),
                                            (17, 192, 4, False), (33, 256, 4, True), (416, 256, 4, True), (512, 192, 4, True), (1024, 192, 4, False),
-                                           (1024, 128, 8, True), (1600, 128, 4, False), (1600, 64, 8, True), (1600, 64, 8, False)])
+                                           (1024, 128, 8, True), (1600, 128, 4, False), (1600, 64, 8, True), (1600, 64, 8, False),
+                                           (112, 256, 8, True)])
 def test_block_against_launches_of_their_own(sa, T, E, ratio, moe):
     same(sa, block(sa, T, E, ratio, moe))
 
