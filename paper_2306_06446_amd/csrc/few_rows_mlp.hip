@@ -466,11 +466,19 @@ int launch_width(const FewRows &a, int mi, bool layer, bool moe, hipStream_t st)
     if (mi == 1) return launch<NE, 1>(a, layer, moe, st);
     if constexpr (NE >= 3) {                                 // layers only (plan_few_rows)
         const dim3 grid((unsigned)((a.T + 16 * mi - 1) / (16 * mi) * kSlices * (moe ? 2 : 1))), block(NE * 256);
-        if (mi == 2 && moe) few_rows_kernel<NE, 2, true, true><<<grid, block, 0, st>>>(a);
-        else if (mi == 2) few_rows_kernel<NE, 2, true, false><<<grid, block, 0, st>>>(a);
-        else if constexpr (NE == 3) few_rows_kernel<3, 4, true, true><<<grid, block, 0, st>>>(a);
+        if (layer && mi == 2) {
+            if (moe) few_rows_kernel<NE, 2, true, true><<<grid, block, 0, st>>>(a);
+            else few_rows_kernel<NE, 2, true, false><<<grid, block, 0, st>>>(a);
+            return check_launch("MLP of few rows");
+        }
+        if constexpr (NE == 3) {
+            if (layer && moe && mi == 4) {
+                few_rows_kernel<3, 4, true, true><<<grid, block, 0, st>>>(a);
+                return check_launch("MLP of few rows");
+            }
+        }
     }
-    return check_launch("MLP of few rows");
+    return fail(SA_ERR_UNSUPPORTED, "MLP of few rows: %d tiles to a workgroup", mi);
 }
 
 }  // namespace

@@ -325,7 +325,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
         long m = m0 + r;
         m = m < n_rows ? m : n_rows - 1;
         const long src = (g.gather_a && rows) ? (long)rows[m] : m;
-        a_src[i] = static_cast<const uint8_t *>(g.a) + (size_t)src * a_row_bytes + (BLOCKED ? (size_t)(c / 4) * g.a_block + c % 4 * 16 : c * 16);
+        a_src[i] = static_cast<const uint8_t *>(g.a) + (size_t)src * a_row_bytes + c * 16;
     }
     // The furthest stage offset at which this lane's chunk still lies inside an A row (64-byte stages: every load of
     // a lane has the same physical chunk, rows 16 apart swizzle alike).  Beyond it the lane re-reads the row's last
@@ -688,6 +688,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmArgs &g, const Store &sto
 // A tile shape as launch_tile and the kernels below take it.
 template <class T, int BM_, int BN_, int SB, int NS, int LS, bool BLOCKED = false>
 struct NtTile {
+    static_assert(!BLOCKED || SB == 64, "columns of a stage");
     static constexpr int BM = BM_, BN = BN_;
     template <class Store>
     static constexpr int lds_bytes() { return NtShape<T, BM, BN, SB, NS, Store>::LDS_BYTES; }
