@@ -7,8 +7,9 @@
  * or keeps a pointer, and never synchronises: all work is enqueued on the
  * caller's stream (a hipStream_t passed as void*, NULL = the default stream).
  * Scratch memory comes from a caller-provided workspace whose size the
- * matching *_workspace_bytes query returns.  Arguments are validated on the
- * host before anything is launched, so error paths never touch the GPU.
+ * matching *_workspace_bytes query returns; a smaller one is refused, but for
+ * sa_block_forward and sa_layer_forward (see there).  Arguments are validated
+ * on the host before anything is launched, so error paths never touch the GPU.
  *
  * Every entry point returns SA_OK or a negative SA_ERR_* code; a text for the
  * most recent error of the calling thread is available from sa_last_error().
@@ -40,7 +41,7 @@ extern "C" {
 #define SA_ERR_INVALID (-1)     /* null pointer, negative size, bad enum value        */
 #define SA_ERR_SHAPE (-2)       /* a size the operation is not defined for            */
 #define SA_ERR_ALIGN (-3)       /* a pointer that is not 16-byte aligned              */
-#define SA_ERR_WORKSPACE (-4)   /* workspace missing or smaller than the query says   */
+#define SA_ERR_WORKSPACE (-4)   /* workspace missing or too small                     */
 #define SA_ERR_HIP (-5)         /* the HIP runtime refused a launch                   */
 #define SA_ERR_UNSUPPORTED (-6) /* defined, but no kernel is built for this size      */
 
@@ -414,6 +415,13 @@ int sa_combine_rows(const float *src, const sa_rows *rows, const float *gate_or_
  *   y     = MoE{Mult, Shift}(O) with top-1 dispatch, or Shift MLP(O) if no router
  * Q, K, V enter as fp32 [B,N,H,d] / [B,N,H,dv]; O [B,N,H,dv] = [T,E] and
  * y [T,E] leave as fp32.  All kernels are enqueued on one stream.
+ *
+ * With few rows the query asks for room in which the MLP is one launch.  A
+ * workspace without that room (what the query of an earlier version asked for)
+ * is taken too: the same call then goes by more launches, which take longer;
+ * the Shift expert's rows are the same bits, the Mult expert's fp32 sums may be
+ * in another order.  What is less than those launches need is refused, with
+ * both sizes in sa_last_error().
  */
 typedef struct sa_block_desc {
     int B, N, H, d, nbits, dv;
@@ -449,7 +457,9 @@ int sa_block_forward(const sa_block_desc *desc /* host */, void *stream);
  * and passed in.  Weights follow shift_variant (packed 4-bit rows, or planes
  * from sa_shift_planes_prepare for SA_VARIANT_MFMA_PREPARED; wqkv as one
  * [3E, E] matrix).  E % 64 == 0, hid % 64 == 0, E / H in {32, 64, 128} for the
- * Hamming variant.  y must not overlap x.
+ * Hamming variant.  y must not overlap x.  A workspace smaller than the query
+ * says is taken as by sa_block_forward; all behind the attention is one launch
+ * for few rows otherwise.
  */
 typedef struct sa_layer_desc {
     int B, N, H, nbits;

@@ -153,7 +153,7 @@ extern "C" int sa_block_forward(const sa_block_desc *d, void *stream) {
     if (rc != SA_OK) return rc;
     SA_REQUIRE(d->q && d->k && d->v && d->o, SA_ERR_INVALID, "block: q, k, v and o are required");
     SA_REQUIRE(d->workspace != nullptr && d->workspace_bytes >= L.needed, SA_ERR_WORKSPACE,
-               "block: workspace of %zu bytes needed, %zu given", L.needed, d->workspace_bytes);
+               "block: workspace of %zu bytes asked for, %zu needed, %zu given", L.total, L.needed, d->workspace_bytes);
     SA_REQUIRE(sa::aligned16(d->workspace), SA_ERR_ALIGN, "block: workspace must be 16-byte aligned");
     if (d->hid > 0) {
         SA_REQUIRE(d->w1 && d->w2 && d->lut && d->y, SA_ERR_INVALID, "block: w1, w2, lut and y are required");
@@ -315,7 +315,7 @@ extern "C" int sa_layer_forward(const sa_layer_desc *d, void *stream) {
                SA_ERR_INVALID, "layer: x, y, the LayerNorm parameters, wqkv, wo, w1, w2 and lut are required");
     if (d->moe) SA_REQUIRE(d->wg && d->bg && d->mw1 && d->mw2, SA_ERR_INVALID, "layer: wg, bg, mw1, mw2 are required");
     SA_REQUIRE(d->workspace != nullptr && d->workspace_bytes >= L.needed, SA_ERR_WORKSPACE,
-               "layer: workspace of %zu bytes needed, %zu given", L.needed, d->workspace_bytes);
+               "layer: workspace of %zu bytes asked for, %zu needed, %zu given", L.total, L.needed, d->workspace_bytes);
     SA_REQUIRE(sa::aligned16(d->workspace), SA_ERR_ALIGN, "layer: workspace must be 16-byte aligned");
     uint8_t *ws = static_cast<uint8_t *>(d->workspace);
     const long T = (long)d->B * d->N;
