@@ -1,7 +1,10 @@
 """Launches whose last rows go to tiles of half the height: row counts on either side of where CUs would end half a tile apart, whole and ragged
-lower tiles, columns that are no whole tiles, packed and prepared weights, every kind of output; both experts with routings on either side."""
+lower tiles, columns that are no whole tiles, packed and prepared weights, int32, fp32, sign-code, int8 table and scattered outputs; both experts
+with routings on either side, as Linears and as the first layer of a block."""
 import pytest
 import torch
+
+from test_gpu_hidden_columns import test_block_against_separate_launches as block_against_separate_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +67,31 @@ def test_both_experts(sa, T, K, N, share):
     assert torch.equal(got[shift], ref[shift])
     # fp32 sums of K products in two orders, as test_gpu_split_tiles.py allows
     torch.testing.assert_close(got[~shift], ref[~shift], rtol=1e-4, atol=1e-4)
+
+
+# first layers (int8 through the table) and second ones (scattered fp32 rows) of which either has lower tiles; rows as they are and picked
+@pytest.mark.parametrize("M,E,hid", [(6000, 320, 768), (7001, 320, 768), (12608, 384, 1536), (6499, 320, 768)])
+@pytest.mark.parametrize("picked", [False, True])
+def test_shift_mlp(sa, M, E, hid, picked):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + E)
+    T = M + 50
+    x = torch.randint(-127, 128, (T, E), generator=g, device="cuda", dtype=torch.int8)
+    (w1, f1), (w2, f2) = weights(g, hid, E), weights(g, E, hid)
+    lut = torch.randint(-128, 128, (256,), generator=g, device="cuda", dtype=torch.int8)
+    rows = torch.randperm(T, generator=g, device="cuda")[:M].to(torch.int32) if picked else torch.arange(M, device="cuda", dtype=torch.int32)
+    rq = 2.0**-11                                                        # a power of two: one rounding, of the product, to even
+    h = lut[(x[rows.long()].double() @ f1.T * rq).round().clamp(-127, 127).long() + 128]
+    want = torch.full((T, E), 7.0, device="cuda")
+    want[rows.long()] = (h.double() @ f2.T).float() * 0.5
+    planes = sa.sa_shift_planes_prepare(w1), sa.sa_shift_planes_prepare(w2)
+    for w, variant in (((w1, w2), 1), (planes, 3)):
+        y = torch.full((T, E), 7.0, device="cuda")
+        sa.sa_shift_mlp(x, *w, rq, lut, want_y2=False, y=y, out_scale=0.5, variant=variant, rows=rows, max_rows=M)
+        assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("share", [0.0, 0.15, 0.4, 0.65, 0.9, 1.0])
+@pytest.mark.parametrize("B,N,H,hid", [(1, 5617, 6, 1536), (1, 8501, 4, 1024)])
+def test_block_of_both_experts(sa, B, N, H, hid, share):
+    block_against_separate_launches(sa, B, N, H, hid, share)

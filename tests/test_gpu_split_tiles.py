@@ -1,7 +1,10 @@
 """Launches of both experts whose last rows go to lower tiles: routings on either side of where that fills the last round of workgroups, all
-tokens with one expert, row counts that are no whole tiles, against a launch for each expert."""
+tokens with one expert, row counts that are no whole tiles, as Linears and as both layers of a block, whose hidden rows are in columns, against a
+launch for each expert."""
 import pytest
 import torch
+
+from test_gpu_hidden_columns import test_block_against_separate_launches as block_against_separate_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -26,3 +29,9 @@ def test_lower_tiles_for_the_last_rows(sa, T, K, N, share):
     # fp32 sums of K products in two orders: a partial sum, of rms up to 1, is rounded K / 16 times (half of 2^-23 at most, 2^-24 rms): 3072 / 16 of
     # these are 200 * 2^-24 = 1.2e-5 at worst on either side, as test_gpu_experts.py allows
     torch.testing.assert_close(got[~shift], ref[~shift], rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("share", [0.0, 0.45, 0.55, 0.62, 0.70, 0.97])
+@pytest.mark.parametrize("B,N,H,hid", [(64, 197, 12, 3072), (1, 10001, 12, 3072)])
+def test_block(sa, B, N, H, hid, share):
+    block_against_separate_launches(sa, B, N, H, hid, share)

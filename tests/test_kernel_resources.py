@@ -83,3 +83,27 @@ def test_registers_for_two_workgroups(kernels, pattern, instances):
     assert len(some) == instances
     for n, k in some.items():
         assert k[".vgpr_count"] <= 128, n
+
+
+# the LayerNorm of 4097 to 8192 columns holds a row on 64 lanes, more than they have registers for
+def test_no_other_kernel_has_scratch(kernels):
+    spilled = {n for n, k in kernels.items() if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]}
+    assert len(kernels) > 350
+    assert all(re.search(r"layernorm_kernelILi64ELi32E", n) for n in spilled) and len(spilled) == 2, spilled
+
+
+# a CU's two or three workgroups of both experts' tiles, and its four, two or one of few rows
+@pytest.mark.parametrize("pattern,instances,registers,lds", [
+    (r"expert_split_kernel", 5, 256, 80 * 1024),
+    (r"expert_even_kernel", 2, 168, 160 * 1024 // 3),
+    (r"gemm_even_kernel", 10, 168, 160 * 1024 // 3),
+    (r"few_rows_kernelILi1ELi1E", 4, 128, 40 * 1024),
+    (r"few_rows_kernelILi2ELi1E", 4, 128, 80 * 1024),
+    (r"few_rows_kernelILi3ELi1E", 4, 80, 80 * 1024),         # 24 wavefronts
+    (r"few_rows_kernelILi4ELi1E|few_rows_kernelILi[34]ELi[24]E", 9, 128, 160 * 1024),
+])
+def test_workgroups_that_share_a_cu(kernels, pattern, instances, registers, lds):
+    some = {n: k for n, k in kernels.items() if re.search(pattern, n)}
+    assert len(some) == instances
+    for n, k in some.items():
+        assert k[".vgpr_count"] <= registers and k[".group_segment_fixed_size"] <= lds, n
