@@ -605,20 +605,29 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             // the first time, and few have more than one tile: what its instructions take to arrive counts.  So those of the common forms
             // have no others between them, and a row's address is made from the row's before, where it is used.  All made ahead of the tiles, as
             // the compiler does with tile_at + row * row_step, they were 300 instructions and most of the registers: Q(K^T V) of 32 x 3136
-            // queries x 1 head x 64 bits 8.0 -> 6.6 us, of 1 x 4 x 16384 x 256 bits 11.2 -> 10.0, of 8 x 4 x 16384 x 256 bits 59.7 -> 49.3,
-            // {0,1} codes of the first 11.8 -> 10.0, both products of 1 x 3 x 197 x 64 bits 7.9 -> 7.4.
-            auto store_rows = [&](auto whole_c, auto forms_c) {
+            // queries x 1 head x 64 bits 8.0 -> 6.6 us, both products of 1 x 3 x 197 x 64 bits 7.9 -> 7.4.  rows_ahead: see there.
+            auto store_rows = [&](auto whole_c, auto forms_c, auto ahead_c) {
                 constexpr bool WHOLE = decltype(whole_c)::value;      // all 32 queries exist
                 constexpr int FORMS = decltype(forms_c)::value;
+                constexpr bool AHEAD = decltype(ahead_c)::value;
                 const bool keep = ZO && (FORMS < 0 ? f.keep : (FORMS & 8) != 0);
                 const bool floats = FORMS < 0 ? f.out != nullptr : (FORMS & 1) != 0, bytes = FORMS < 0 ? f.xq != nullptr : (FORMS & 2) != 0,
                            halves = FORMS < 0 ? f.xh != nullptr : (FORMS & 4) != 0;
-                size_t at = tile_at;
+                size_t row_at[16];
+                row_at[0] = tile_at;
+                auto next_row = [&](int r) {
+                    row_at[r] = row_at[r - 1] + (size_t)(r % 4 ? 1 : 5) * row_step;
+                    asm volatile("" : "+s"(row_at[r]));
+                };
+                if constexpr (AHEAD) {
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) next_row(r);
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int row = 8 * (r >> 2) + (r & 3);           // + 4 kg
-                    if (r > 0) at += (size_t)(r % 4 ? 1 : 5) * row_step;
-                    asm volatile("" : "+s"(at));
+                    if (!AHEAD && r > 0) next_row(r);
+                    const size_t at = row_at[r];
                     // (+-1: see code_pair.  __shfl, which allows for other widths, took 4 registers more than 256-bit codes leave.)
                     const float fr = ZO ? __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(16 * kg + 4 * row, __builtin_bit_cast(int, factor[tm])))
                                         : -f.scale;
@@ -637,14 +646,18 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                     }
                 }
             };
+            auto store_whole = [&](auto ahead) {
+                if (ZO && f.keep) store_rows(std::true_type{}, std::integral_constant<int, ZO ? 9 : -1>{}, ahead);
+                else if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{}, ahead);
+                else if (!f.out && !f.xh) store_rows(std::true_type{}, std::integral_constant<int, 2>{}, ahead);
+                else if (!f.xh) store_rows(std::true_type{}, std::integral_constant<int, 3>{}, ahead);
+                else store_rows(std::true_type{}, std::integral_constant<int, -1>{}, ahead);
+            };
             if (__builtin_expect((tile0 + tm) * 32 + 32 <= Nq, 1)) {
-                if (ZO && f.keep) store_rows(std::true_type{}, std::integral_constant<int, ZO ? 9 : -1>{});
-                else if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{});
-                else if (!f.out && !f.xh) store_rows(std::true_type{}, std::integral_constant<int, 2>{});
-                else if (!f.xh) store_rows(std::true_type{}, std::integral_constant<int, 3>{});
-                else store_rows(std::true_type{}, std::integral_constant<int, -1>{});
+                if (SUMS && f.rows_ahead) store_whole(std::integral_constant<bool, SUMS>{});
+                else store_whole(std::false_type{});
             } else {
-                store_rows(std::false_type{}, std::integral_constant<int, -1>{});
+                store_rows(std::false_type{}, std::integral_constant<int, -1>{}, std::false_type{});
             }
         }
     }
