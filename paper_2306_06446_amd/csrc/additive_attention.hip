@@ -394,10 +394,11 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
     f.xq = mode.xq;
     f.xh = mode.xh;
     f.act_inv_scale = mode.act_inv_scale;
-    // The convolution that follows {0,1} codes reads them.  Up to 8 MiB; more of them hold up the launch's end, by more than the convolution then
-    // saves (attention with its convolution, kept and streamed, us: 16 x 196 tokens x 384 30.3, 30.7; 64 x 196 x 192 31.0, 30.8; 32 x 3136 x 32
-    // 33.7, 33.4; 64 x 784 x 64 32.4, 31.9; 8 x 16384 x 256 310, 305).
-    f.keep = mode.zero_one && BH * Nq * dv * 4 <= 8L << 20;
+    // The convolution that follows {0,1} codes reads and writes them, and reads V: up to 120 MiB of either both are still in the last-level
+    // cache (256 MiB) then.  More outputs leave as a stream, which ends the launch sooner than the convolution is held up (hash, attention and
+    // convolution, streamed and kept, us: 16 x 4096 tokens x 256 115.6, 108.9; 2 x 16384 x 256 63.3, 61.3; 222 x 196 x 384 124.8, 117.8; 2 x 16384 x 768
+    // 215.3, 206.4; 17 x 784 x 256 37.0, 36.5; 445 x 196 x 384, 128 MiB, 236.8, 243.5; 166 x 784 x 384 337.9, 343.4).
+    f.keep = mode.zero_one && BH * Nq * dv * 4 <= 120L << 20;
 
     if (phases & 1) {
         if (Nk == 0) {
