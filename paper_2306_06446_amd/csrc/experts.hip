@@ -156,8 +156,11 @@ int launch_split_tiles(const GemmArgs &gs, const StoreS &ss, const GemmArgs &gm,
     GemmArgs s = gs, m = gm;
     s.share_out(TileS::BN, TileS::col_groups(gs));
     m.share_out(TileM::BN, TileM::col_groups(gm));
-    if constexpr (SPLIT_SHIFT)                               // rows are taken of one round of workgroups only
-        if (least_tiles<TileS::BM, TileM::BM>(s, m, gs.sel.max_rows) > kPlaces) return launch_pair_tiles<TileS, TileM, OCC>(gs, ss, gm, sm, st, what);
+    // Shift rows are taken of one round of workgroups.  Mult rows of any last round, but behind five others that is no more than workgroups lose
+    // by asking (768 -> 3072, 30 / 50 / 70 %, us without and with: 30000 tokens 173.4 / 172.5 / 166.1, 174.8 / 172.3 / 166.1; 40000 227.6 /
+    // 224.0 / 218.8, 229.9 / 225.8 / 217.7; 60000 335.3 / 330.8 / 311.5, 340.1 / 327.9 / 313.1; 25000 147.7 / 149.0 / 143.7, 148.9 / 147.4 / 142.1).
+    if (least_tiles<TileS::BM, TileM::BM>(s, m, gs.sel.max_rows) > (SPLIT_SHIFT ? 1 : 5) * kPlaces)
+        return launch_pair_tiles<TileS, TileM, OCC>(gs, ss, gm, sm, st, what);
     // as launch_pair_tiles, and what the lower tiles take: at most a round of workgroups more, and a row of tiles per XCD
     const long all_s = tile_blocks<TileS>(gs.sel.max_rows, s), all_m = tile_blocks<TileM>(gm.sel.max_rows, m);
     const long step_s = tile_blocks<TileS>(1, s), step_m = tile_blocks<TileM>(1, m);

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,K,N,share", [
     (12608, 768, 3072, 0.70), (12608, 768, 3072, 0.62), (12608, 768, 3072, 0.0), (12608, 768, 3072, 1.0), (13001, 768, 3072, 0.45),      # Mult rows
     (12608, 3072, 768, 0.70), (12608, 3072, 768, 0.55), (12608, 3072, 768, 1.0), (11777, 2048, 640, 0.80), (10001, 3072, 768, 0.97),     # Shift rows
+    (28001, 768, 3072, 0.50), (14001, 3072, 768, 0.55),              # beyond the last round that takes lower tiles
 ])
 def test_lower_tiles_for_the_last_rows(sa, T, K, N, share):
     g = torch.Generator(device="cuda")
