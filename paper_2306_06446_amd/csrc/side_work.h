@@ -171,25 +171,30 @@ __host__ __device__ inline long decode_blocks(const DecodeWork &w) {
 // in a launch of their own and 16.8 with 768 x 2304 ones; 5.7 and 6.4 so.)
 template <int THREADS>
 __device__ __forceinline__ void decode_block(const DecodeWork &w, long block) {
-    auto decode = [&](const uint4 *w4, uint4 *pa, uint4 *pb, long chunks) {
-        const long i = block * THREADS + threadIdx.x;
-        if (i >= chunks) return;
-        const uint4 wv = w4[i];
-        const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
-        uint32_t oa[8], ob[8];
+    const uint4 *w4 = w.w4[0];
+    uint4 *pa = w.plane_a[0], *pb = w.plane_b[0];
+    long chunks = w.chunks[0];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) decode8(wd[q], oa + 2 * q, ob + 2 * q);
-        pa[2 * i] = make_uint4(oa[0], oa[1], oa[2], oa[3]);
-        pa[2 * i + 1] = make_uint4(oa[4], oa[5], oa[6], oa[7]);
-        pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
-        pb[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
-    };
-    const long first = (w.chunks[0] + THREADS - 1) / THREADS, second = (w.chunks[1] + THREADS - 1) / THREADS;
-    if (block < first) return decode(w.w4[0], w.plane_a[0], w.plane_b[0], w.chunks[0]);
-    block -= first;
-    if (block < second) return decode(w.w4[1], w.plane_a[1], w.plane_b[1], w.chunks[1]);
-    block -= second;
-    decode(w.w4[2], w.plane_a[2], w.plane_b[2], w.chunks[2]);
+    for (int m = 1; m < 3; ++m) {
+        const long blocks = (chunks + THREADS - 1) / THREADS;
+        if (block < blocks) break;
+        block -= blocks;
+        w4 = w.w4[m];
+        pa = w.plane_a[m];
+        pb = w.plane_b[m];
+        chunks = w.chunks[m];
+    }
+    const long i = block * THREADS + threadIdx.x;
+    if (i >= chunks) return;
+    const uint4 wv = w4[i];
+    const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
+    uint32_t oa[8], ob[8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) decode8(wd[q], oa + 2 * q, ob + 2 * q);
+    pa[2 * i] = make_uint4(oa[0], oa[1], oa[2], oa[3]);
+    pa[2 * i + 1] = make_uint4(oa[4], oa[5], oa[6], oa[7]);
+    pb[2 * i] = make_uint4(ob[0], ob[1], ob[2], ob[3]);
+    pb[2 * i + 1] = make_uint4(ob[4], ob[5], ob[6], ob[7]);
 }
 
 // Workgroups of THREADS threads that a SideWork takes, and what workgroup `block` of them does (routing first: it takes
