@@ -399,8 +399,8 @@ __device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes,
 template <int TM, int W, bool ZO>
 constexpr bool kCodesAhead = ZO ? TM > 1 && W < 4 : TM > 1 || W < 4;
 
-// SUMS: K^T V may come as partials.  part and rest: of block = rest * blocks_per_bh + part, rest = bh * column groups + column group
-template <int DVC, int W, int NW, int TM, bool ZO, bool SUMS>
+// SUMS: K^T V may come as partials.  AHEAD: the addresses of a tile's rows are made before the first one leaves.  part and rest: of block = rest * blocks_per_bh + part, rest = bh * column groups + column group
+template <int DVC, int W, int NW, int TM, bool ZO, bool SUMS, bool AHEAD>
 __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, FastDiv by_h, int Nq, int DV,
                                           long BH, int tiles_per_block, int part, int rest, uint8_t *lds) {
     constexpr int JT = DVC / 32;
@@ -606,28 +606,29 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             // have no others between them, and a row's address is made from the row's before, where it is used.  All made ahead of the tiles, as
             // the compiler does with tile_at + row * row_step, they were 300 instructions and most of the registers: Q(K^T V) of 32 x 3136
             // queries x 1 head x 64 bits 8.0 -> 6.6 us, both products of 1 x 3 x 197 x 64 bits 7.9 -> 7.4.  rows_ahead: see there.
-            auto store_rows = [&](auto whole_c, auto forms_c, auto ahead_c) {
+            auto store_rows = [&](auto whole_c, auto forms_c) {
                 constexpr bool WHOLE = decltype(whole_c)::value;      // all 32 queries exist
                 constexpr int FORMS = decltype(forms_c)::value;
-                constexpr bool AHEAD = decltype(ahead_c)::value;
                 const bool keep = ZO && (FORMS < 0 ? f.keep : (FORMS & 8) != 0);
                 const bool floats = FORMS < 0 ? f.out != nullptr : (FORMS & 1) != 0, bytes = FORMS < 0 ? f.xq != nullptr : (FORMS & 2) != 0,
                            halves = FORMS < 0 ? f.xh != nullptr : (FORMS & 4) != 0;
-                size_t row_at[16];
-                row_at[0] = tile_at;
+                size_t at = tile_at, ahead[16];
                 auto next_row = [&](int r) {
-                    row_at[r] = row_at[r - 1] + (size_t)(r % 4 ? 1 : 5) * row_step;
-                    asm volatile("" : "+s"(row_at[r]));
+                    if (r > 0) at += (size_t)(r % 4 ? 1 : 5) * row_step;
+                    asm volatile("" : "+s"(at));
                 };
                 if constexpr (AHEAD) {
 #pragma unroll
-                    for (int r = 1; r < 16; ++r) next_row(r);
+                    for (int r = 0; r < 16; ++r) {
+                        next_row(r);
+                        ahead[r] = at;
+                    }
                 }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int row = 8 * (r >> 2) + (r & 3);           // + 4 kg
-                    if (!AHEAD && r > 0) next_row(r);
-                    const size_t at = row_at[r];
+                    if constexpr (AHEAD) at = ahead[r];
+                    else next_row(r);
                     // (+-1: see code_pair.  __shfl, which allows for other widths, took 4 registers more than 256-bit codes leave.)
                     const float fr = ZO ? __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(16 * kg + 4 * row, __builtin_bit_cast(int, factor[tm])))
                                         : -f.scale;
@@ -646,29 +647,25 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
                     }
                 }
             };
-            auto store_whole = [&](auto ahead) {
-                if (ZO && f.keep) store_rows(std::true_type{}, std::integral_constant<int, ZO ? 9 : -1>{}, ahead);
-                else if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{}, ahead);
-                else if (!f.out && !f.xh) store_rows(std::true_type{}, std::integral_constant<int, 2>{}, ahead);
-                else if (!f.xh) store_rows(std::true_type{}, std::integral_constant<int, 3>{}, ahead);
-                else store_rows(std::true_type{}, std::integral_constant<int, -1>{}, ahead);
-            };
             if (__builtin_expect((tile0 + tm) * 32 + 32 <= Nq, 1)) {
-                if (SUMS && f.rows_ahead) store_whole(std::integral_constant<bool, SUMS>{});
-                else store_whole(std::false_type{});
+                if (ZO && f.keep) store_rows(std::true_type{}, std::integral_constant<int, ZO ? 9 : -1>{});
+                else if (ZO || (!f.xq && !f.xh)) store_rows(std::true_type{}, std::integral_constant<int, 1>{});
+                else if (!f.out && !f.xh) store_rows(std::true_type{}, std::integral_constant<int, 2>{});
+                else if (!f.xh) store_rows(std::true_type{}, std::integral_constant<int, 3>{});
+                else store_rows(std::true_type{}, std::integral_constant<int, -1>{});
             } else {
-                store_rows(std::false_type{}, std::integral_constant<int, -1>{}, std::false_type{});
+                store_rows(std::false_type{}, std::integral_constant<int, -1>{});
             }
         }
     }
 }
 
-template <int DVC, int W, int NW, int TM, bool ZO>
+template <int DVC, int W, int NW, int TM, bool ZO, bool AHEAD>
 __global__ __launch_bounds__(NW * 64) void qkv_mfma_kernel(const uint64_t *__restrict__ q_codes, AddFused f, int H, int Nq, int DV,
                                                            long BH, int blocks_per_bh, int tiles_per_block, FastDiv by_blocks, FastDiv by_h) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[QkvLds<DVC, W, ZO>::BYTES];
     const int rest = (int)by_blocks(blockIdx.x);
-    qkv_block<DVC, W, NW, TM, ZO, true>(q_codes, f, H, by_h, Nq, DV, BH, tiles_per_block, (int)blockIdx.x - rest * blocks_per_bh, rest, lds);
+    qkv_block<DVC, W, NW, TM, ZO, true, AHEAD>(q_codes, f, H, by_h, Nq, DV, BH, tiles_per_block, (int)blockIdx.x - rest * blocks_per_bh, rest, lds);
 }
 
 // ------------------------------------------------------------------- both, short sequences ----
@@ -688,7 +685,7 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t 
     static_assert(kKtvWaves / PH * WB == W, "a workgroup has all words");
     ktv_block<DVC, WB, PH, RING, false>(k_codes, v, kv, nullptr, BH, H, by_h, Nk, W, DV, (Nk + 15) & ~15, 0, blockIdx.x, lds);
     __syncthreads();
-    qkv_block<DVC, W, kKtvWaves, 1, false, false>(q_codes, f, H, by_h, Nq, DV, BH, (Nq + 31) / 32, 0, blockIdx.x, lds);
+    qkv_block<DVC, W, kKtvWaves, 1, false, false, false>(q_codes, f, H, by_h, Nq, DV, BH, (Nq + 31) / 32, 0, blockIdx.x, lds);
 }
 
 // How the token tiles of a (b, h) are spread.
@@ -700,10 +697,14 @@ __global__ __launch_bounds__(kKtvWaves * 64) void ktv_qkv_kernel(const uint64_t 
 template <int W>
 void launch_qkv_w(const uint64_t *q_codes, const AddFused &f, long BH, int H, int Nq, int dv, bool zo, hipStream_t st) {
     const int n_tiles = (Nq + 31) / 32;
+#define SA_QKV_KERNEL(DVC_, NW_, TM_, ZO_, AHEAD_)                                                                                   \
+    qkv_mfma_kernel<DVC_, W, NW_, TM_, ZO_, AHEAD_><<<grid, block, 0, st>>>(q_codes, f, H, Nq, dv, BH, per_bh, tiles_per_block, FastDiv(per_bh), FastDiv(H))
 #define SA_QKV(DVC_, NW_, TM_)                                                                                                      \
     const dim3 grid((unsigned)(BH * (dv / DVC_) * per_bh)), block(NW_ * 64);                                                        \
-    if (zo) qkv_mfma_kernel<DVC_, W, NW_, TM_, true><<<grid, block, 0, st>>>(q_codes, f, H, Nq, dv, BH, per_bh, tiles_per_block, FastDiv(per_bh), FastDiv(H));     \
-    else qkv_mfma_kernel<DVC_, W, NW_, TM_, false><<<grid, block, 0, st>>>(q_codes, f, H, Nq, dv, BH, per_bh, tiles_per_block, FastDiv(per_bh), FastDiv(H));
+    if (zo && f.rows_ahead) SA_QKV_KERNEL(DVC_, NW_, TM_, true, true);                                                              \
+    else if (zo) SA_QKV_KERNEL(DVC_, NW_, TM_, true, false);                                                                        \
+    else if (f.rows_ahead) SA_QKV_KERNEL(DVC_, NW_, TM_, false, true);                                                              \
+    else SA_QKV_KERNEL(DVC_, NW_, TM_, false, false);
     if (dv >= 64 && BH * (dv / 64) * (n_tiles / 32) >= 256) {
         const long base = BH * (dv / 64);
         int per_bh = (int)((256 + base - 1) / base);
@@ -715,6 +716,7 @@ void launch_qkv_w(const uint64_t *q_codes, const AddFused &f, long BH, int H, in
         SA_QKV(32, 8, 1)
     }
 #undef SA_QKV
+#undef SA_QKV_KERNEL
 }
 
 }  // namespace

@@ -52,7 +52,7 @@ def kernels():
 
 
 @pytest.mark.parametrize("pattern,instances", [
-    (r"qkv_mfma_kernel", 12),
+    (r"qkv_mfma_kernel", 24),
     (r"ktv_mfma_kernel|ktv_qkv_kernel", 28),
     (r"norm_linear_kernel", 4),
     (r"gemm_kernel.*HashStore", 8),
