@@ -397,8 +397,10 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
     // The convolution that follows {0,1} codes reads and writes them, and reads V: up to 120 MiB of either both are still in the last-level
     // cache (256 MiB) then.  More outputs leave as a stream, which ends the launch sooner than the convolution is held up (hash, attention and
     // convolution, streamed and kept, us: 16 x 4096 tokens x 256 115.6, 108.9; 2 x 16384 x 256 63.3, 61.3; 222 x 196 x 384 124.8, 117.8; 2 x 16384 x 768
-    // 215.3, 206.4; 17 x 784 x 256 37.0, 36.5; 445 x 196 x 384, 128 MiB, 236.8, 243.5; 166 x 784 x 384 337.9, 343.4).
-    f.keep = mode.zero_one && BH * Nq * dv * 4 <= 120L << 20;
+    // 215.3, 206.4; 17 x 784 x 256 37.0, 36.5; 445 x 196 x 384, 128 MiB, 236.8, 243.5; 166 x 784 x 384 337.9, 343.4).  So do those of
+    // tokens of one line, 32 columns, beyond 8 MiB (32 x 3136 x 32 32.5, 33.4; 9 x 16384 41.1, 42.0; 318 x 784 57.2, 57.5; 47 x 16384 157.1, 158.3; but 31 x
+    // 16384 112.7, 111.1).
+    f.keep = mode.zero_one && BH * Nq * dv * 4 <= (H * dv >= 64 ? 120L : 8L) << 20;
 
     if (phases & 1) {
         if (Nk == 0) {
