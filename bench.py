@@ -35,11 +35,11 @@ PEAK_TFLOPS = {                  # dense peaks of MI355X
 
 # Steps that the per-kernel pass launches alone, and how a block runs them: nothing of it is an entry point of its own there.
 IN_BLOCK = {
-    "dispatch": "rides in the launch of the hash (up to 32768 tokens)",
+    "dispatch": "rides in the launch of the hash (up to 32768 tokens; of few rows in the MLP's)",
     "shift_decode": "rides in the launch of the hash",
     "quantize": "part of the launch of Q (K^T V)",
-    "mult_fc1": "one launch with shift_fc1", "shift_fc1": "one launch with mult_fc1",
-    "mult_fc2": "one launch with shift_fc2", "shift_fc2": "one launch with mult_fc2",
+    "mult_fc1": "one launch with shift_fc1 (few rows: the whole MLP)", "shift_fc1": "one launch with mult_fc1 (few rows: the whole MLP)",
+    "mult_fc2": "one launch with shift_fc2 (few rows: the whole MLP)", "shift_fc2": "one launch with mult_fc2 (few rows: the whole MLP)",
 }
 
 
