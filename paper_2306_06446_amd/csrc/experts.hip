@@ -68,8 +68,9 @@ __global__ __launch_bounds__(256, OCC) void expert_pair_kernel(GemmArgs gs, Stor
 // The same with two heights of one expert's tiles: its last rows go to the lower ones, where that fills the last round of workgroups better.
 // 12608 tokens, 70 % of them to the Shift expert: 3072 <- 768 has 840 + 480 tiles for 512 places, and 48 CUs with a sixth tile took 18 us longer
 // than the others (73 us by the tiles' own clocks; with 80 % of the Mult rows in lower tiles 67); 768 <- 3072 has 315 + 180, and the CUs with two high
-// Shift tiles were done 8 us after the others (61 and 58).  Of that the clock takes half back, the card being at its power limit: block 203.6 ->
-// 199.7 us, layer 313.1 -> 308.0; 18912 tokens, 50 % 299.7 -> 288; where no rows are taken the same as without (4728 to 15760 tokens within 0.5 %).
+// Shift tiles were done 8 us after the others (61 and 58).  Of that the clock takes half back, the card being at its power limit: block 201.4 ->
+// 197.4 us (50 %: 224.6, 224.1), layer 315.7 -> 308.6; block of 18912 tokens, 50 %, 302.9 -> 300.6; where no rows are taken the same as without (4728
+// to 15760 tokens within 0.5 %).
 // SPLIT_SHIFT: the Shift expert's (TileL: its lower tiles), else the Mult expert's.
 template <class TileS, class StoreS, class TileM, class StoreM, class TileL, bool SPLIT_SHIFT, int OCC>
 __global__ __launch_bounds__(256, OCC) void expert_split_kernel(GemmArgs gs, StoreS ss, GemmArgs gm, StoreM sm, int most) {

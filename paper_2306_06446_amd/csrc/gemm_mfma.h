@@ -85,7 +85,8 @@ struct GemmArgs {
     int K, N;               // K: extent of the contraction, a whole number of 64-byte stages; row length of the B planes
     // How the tiles are shared out to the XCDs (see tile_of), set by the launcher with share_out.  Kernels start with this: made there
     // from col_groups, divisions one after the other came before every tile's first load (two experts in one launch: 576 instructions, now 130;
-    // 12608 x 768 <- 768 as a Mult and a Shift expert 30.35 -> 30.14 us, 12608 x 1536 <- 384 and back 50.1 -> 49.6).
+    // 12608 x 768 <- 768 as a Mult and a Shift expert 30.35 -> 30.14 us, 12608 x 1536 <- 384 and back 50.1 -> 49.6; 25000 x 768 <- 256 32.1 -> 32.7 and
+    // 12608 x 768 <- 256, 70 %, 20.8 -> 20.4, by how a round's workgroups fall in step).
     int log_groups = 0, col_tiles = 0, cols_per_group = 1;
     FastDiv by_cols{1};
     void share_out(int BN, int col_groups) {
