@@ -457,8 +457,7 @@ int run_additive(const uint64_t *q_codes, const uint64_t *k_codes, const float *
     if ((phases & 2) && Nq > 0) {
         // Made just before its stores, a row's address lets the wavefronts of a CU take turns row by row, all at the same rows of tiles that lie
         // a power of two apart.  As long as the caches take the outputs that costs nothing; beyond, memory falls behind, by how the card's
-        // pages lie (both products on three cards, us, as the compiler
-        // makes them, just before and ahead: 6 x 6482 tokens x 4 heads x 64 bits x 64 27.9; 31.7, 27.8, 25.7; 26.5, 8 x 16384 63.8; 69.6, 64.6, 61.1; 61.9;
+        // pages lie (both products on three cards, us, as the compiler makes them, just before and ahead: 6 x 6482 tokens x 4 heads x 64 bits x 64 27.9; 31.7, 27.8, 25.7; 26.5, 8 x 16384 63.8; 69.6, 64.6, 61.1; 61.9;
         // 16 MiB of outputs, 1 x 16384, 18.0; 16.6, 16.6, 16.3; 16.7, 64 x 784 x 2 heads x 32 15.4; 14.0; 14.6).
         const long row_bytes = (f.out ? 4 : 0) + (f.xq ? 1 : 0) + (f.xh ? 2 : 0);
         f.rows_ahead = BH * Nq * dv * row_bytes > 24L << 20;

@@ -399,7 +399,8 @@ __device__ __forceinline__ void load_codes(const uint64_t *__restrict__ q_codes,
 template <int TM, int W, bool ZO>
 constexpr bool kCodesAhead = ZO ? TM > 1 && W < 4 : TM > 1 || W < 4;
 
-// SUMS: K^T V may come as partials.  AHEAD: the addresses of a tile's rows are made before the first one leaves.  part and rest: of block = rest * blocks_per_bh + part, rest = bh * column groups + column group
+// SUMS: K^T V may come as partials.  AHEAD: the addresses of a tile's rows are made before the first one leaves.
+// part and rest: of block = rest * blocks_per_bh + part, rest = bh * column groups + column group
 template <int DVC, int W, int NW, int TM, bool ZO, bool SUMS, bool AHEAD>
 __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, const AddFused &f, int H, FastDiv by_h, int Nq, int DV,
                                           long BH, int tiles_per_block, int part, int rest, uint8_t *lds) {
@@ -605,7 +606,8 @@ __device__ __forceinline__ void qkv_block(const uint64_t *__restrict__ q_codes, 
             // the first time, and few have more than one tile: what its instructions take to arrive counts.  So those of the common forms
             // have no others between them, and a row's address is made from the row's before, where it is used.  All made ahead of the tiles, as
             // the compiler does with tile_at + row * row_step, they were 300 instructions and most of the registers: Q(K^T V) of 32 x 3136
-            // queries x 1 head x 64 bits 8.0 -> 6.6 us, both products of 1 x 3 x 197 x 64 bits 7.9 -> 7.4.  rows_ahead: see there.
+            // queries x 1 head x 64 bits 8.0 -> 6.6 us, both products of 1 x 3 x 197 x 64 bits 7.9 -> 7.4.  AHEAD: as AddFused::rows_ahead asks
+            // (run_additive says when).
             auto store_rows = [&](auto whole_c, auto forms_c) {
                 constexpr bool WHOLE = decltype(whole_c)::value;      // all 32 queries exist
                 constexpr int FORMS = decltype(forms_c)::value;

@@ -324,7 +324,7 @@ struct AddFused {
     int8_t *xq = nullptr;
     _Float16 *xh = nullptr;
     float act_inv_scale = 0.0f;
-    bool keep = false;       // {0,1} codes: the outputs stay in the L2s for who reads them next
+    bool keep = false;       // {0,1} codes: the outputs stay in the caches for who reads them next
     bool rows_ahead = false; // (launch_qkv_mfma) the addresses of a tile's rows are made before the first one leaves
 };
 bool additive_mfma_ktv_supported(int nbits, int dv);
